@@ -115,7 +115,8 @@ typedef struct daris_layer {
 typedef struct daris_dnn {
   int32_t n_layers;
   int32_t in_c, in_h, in_w;
-  int32_t dtype; /* DARIS_FP32: fp32 storage, fp32 MFMA.  DARIS_BF16: bf16 weights/activations, fp32 accumulate */
+  int32_t dtype; /* DARIS_FP32: fp32 storage, products of full fp32 operands (three bf16 parts each), fp32 accumulate.
+                    DARIS_BF16: bf16 weights/activations, fp32 accumulate */
   const daris_layer* layers;
 } daris_dnn;
 

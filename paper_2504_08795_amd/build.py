@@ -1,5 +1,5 @@
-"""Builds libdaris.so for gfx950 with hipcc, in-tree: the device code object (every kernel of csrc/kernels.hip), linked
-into the library as data, and the host runtime that dispatches it (HSA queues) behind the C ABI."""
+"""Builds libdaris.so for gfx950 with hipcc, in-tree: the device code objects (every kernel of csrc/*kernels.hip), linked
+into the library as data, and the host runtime that dispatches them (HSA queues) behind the C ABI."""
 import os
 import subprocess
 import sys
@@ -7,7 +7,8 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libdaris.so")
-CODE_OBJECT = os.path.join(CSRC, "daris_kernels.co")
+# device source -> symbol prefix of its code object in the library
+DEVICE_SOURCES = {"kernels.hip": "daris_kernels", "block_kernels.hip": "daris_block_kernels"}
 HOST_SOURCES = ["aql.cpp", "launch.cpp", "sched_core.cpp", "net_plan.cpp", "daris_api.cpp"]
 COMMON = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-Wall", "-Wno-unused-function"]
 # no packed fp32 arithmetic in device code (some forms have given wrong results on this hardware)
@@ -16,12 +17,12 @@ HOST_FLAGS = COMMON + ["-fPIC"]
 
 BLOB_ASM = """
     .section .rodata
-    .global daris_kernels_co
-    .global daris_kernels_co_end
+    .global {name}_co
+    .global {name}_co_end
     .balign 4096
-daris_kernels_co:
+{name}_co:
     .incbin "{path}"
-daris_kernels_co_end:
+{name}_co_end:
     .byte 0
     .section .note.GNU-stack,"",@progbits
 """
@@ -35,10 +36,14 @@ def _run(cmd, verbose):
 
 def build(verbose: bool = False) -> str:
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-    _run([hipcc] + DEVICE_FLAGS + ["-c", os.path.join(CSRC, "kernels.hip"), "-o", CODE_OBJECT], verbose)
+    asm = ""
+    for src, name in DEVICE_SOURCES.items():
+        code_object = os.path.join(CSRC, name + ".co")
+        _run([hipcc] + DEVICE_FLAGS + ["-c", os.path.join(CSRC, src), "-o", code_object], verbose)
+        asm += BLOB_ASM.format(name=name, path=code_object)
     blob_s = os.path.join(CSRC, "kernels_blob.S.tmp.s")
     with open(blob_s, "w") as f:
-        f.write(BLOB_ASM.format(path=CODE_OBJECT))
+        f.write(asm)
     objs = [os.path.join(CSRC, "kernels_blob.o")]
     _run(["gcc", "-c", blob_s, "-o", objs[0]], verbose)
     os.remove(blob_s)

@@ -102,7 +102,7 @@ hsa_status_t scan_symbols(hsa_executable_t, hsa_agent_t, hsa_executable_symbol_t
 
 }  // namespace
 
-std::string AqlRuntime::init(int hip_device, const void* image, size_t bytes) {
+std::string AqlRuntime::init(int hip_device, const std::vector<Image>& images) {
   if (ready_) return "";
   hsa_status_t st = hsa_init();  // reference counted: HIP holds its own reference
   if (st != HSA_STATUS_SUCCESS) return hsa_err("hsa_init", st);
@@ -142,14 +142,18 @@ std::string AqlRuntime::init(int hip_device, const void* image, size_t bytes) {
   uint64_t freq = 0;
   if (hsa_system_get_info(HSA_SYSTEM_INFO_TIMESTAMP_FREQUENCY, &freq) == HSA_STATUS_SUCCESS && freq > 0) ticks_per_us_ = (double)freq / 1e6;
 
-  image_.assign((const char*)image, (const char*)image + bytes);
-  if (image_.empty()) {
-    hsa_shut_down();
-    return "the library was built without its kernel code object";
+  st = hsa_executable_create_alt(HSA_PROFILE_FULL, HSA_DEFAULT_FLOAT_ROUNDING_MODE_DEFAULT, nullptr, &exec_);
+  for (const Image& im : images) {
+    if (im.bytes == 0) {
+      hsa_shut_down();
+      return "the library was built without one of its kernel code objects";
+    }
+    images_.emplace_back((const char*)im.data, (const char*)im.data + im.bytes);
+    hsa_code_object_reader_t reader{};
+    if (st == HSA_STATUS_SUCCESS) st = hsa_code_object_reader_create_from_memory(images_.back().data(), images_.back().size(), &reader);
+    if (st == HSA_STATUS_SUCCESS) readers_.push_back(reader);
+    if (st == HSA_STATUS_SUCCESS) st = hsa_executable_load_agent_code_object(exec_, gpu_, reader, nullptr, nullptr);
   }
-  st = hsa_code_object_reader_create_from_memory(image_.data(), image_.size(), &reader_);
-  if (st == HSA_STATUS_SUCCESS) st = hsa_executable_create_alt(HSA_PROFILE_FULL, HSA_DEFAULT_FLOAT_ROUNDING_MODE_DEFAULT, nullptr, &exec_);
-  if (st == HSA_STATUS_SUCCESS) st = hsa_executable_load_agent_code_object(exec_, gpu_, reader_, nullptr, nullptr);
   if (st == HSA_STATUS_SUCCESS) st = hsa_executable_freeze(exec_, nullptr);
   if (st != HSA_STATUS_SUCCESS) {
     hsa_shut_down();
@@ -160,7 +164,9 @@ std::string AqlRuntime::init(int hip_device, const void* image, size_t bytes) {
   if (!ss.error.empty() || kernels_.empty()) {
     std::string e = ss.error.empty() ? "the code object holds no kernels" : ss.error;
     hsa_executable_destroy(exec_);
-    hsa_code_object_reader_destroy(reader_);
+    for (hsa_code_object_reader_t r : readers_) hsa_code_object_reader_destroy(r);
+    readers_.clear();
+    images_.clear();
     kernels_.clear();
     hsa_shut_down();
     return e;
@@ -172,9 +178,10 @@ std::string AqlRuntime::init(int hip_device, const void* image, size_t bytes) {
 void AqlRuntime::shutdown() {
   if (!ready_) return;
   hsa_executable_destroy(exec_);
-  hsa_code_object_reader_destroy(reader_);
+  for (hsa_code_object_reader_t r : readers_) hsa_code_object_reader_destroy(r);
+  readers_.clear();
   kernels_.clear();
-  image_.clear();
+  images_.clear();
   ready_ = false;
   hsa_shut_down();
 }

@@ -31,8 +31,12 @@ struct AqlKernel {
 // Process-wide state: HSA agents and memory pools, the loaded code object and its kernels.
 class AqlRuntime {
  public:
-  // Attaches to the GPU that HIP calls `hip_device` and loads the code object image.  Returns "" or an error text.
-  std::string init(int hip_device, const void* image, size_t bytes);
+  struct Image {
+    const void* data;
+    size_t bytes;
+  };
+  // Attaches to the GPU that HIP calls `hip_device` and loads the code objects.  Returns "" or an error text.
+  std::string init(int hip_device, const std::vector<Image>& images);
   void shutdown();
   bool ready() const { return ready_; }
 
@@ -53,8 +57,8 @@ class AqlRuntime {
   hsa_agent_t gpu_{}, cpu_{};
   hsa_amd_memory_pool_t host_pool_{};
   hsa_executable_t exec_{};
-  hsa_code_object_reader_t reader_{};
-  std::vector<char> image_;
+  std::vector<hsa_code_object_reader_t> readers_;
+  std::vector<std::vector<char>> images_;
   std::unordered_map<std::string, AqlKernel> kernels_;
   double ticks_per_us_ = 100.0;
 };

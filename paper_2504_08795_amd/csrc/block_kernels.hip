@@ -1,0 +1,264 @@
+// Implicit-GEMM convolution of large fp32 layers on gfx950: 64 pixels x 64 channels per wave.
+#include <hip/hip_runtime.h>
+
+#include "device_common.h"
+#include "kernels.h"
+
+namespace daris {
+
+// A layer of many tiles is bound by what the waves load, not by its launch.  Per 16 k a 32 x 64 wave tile reads 2 KB of
+// pixels and 6 KB of weights (three bf16 parts each) for 384 cycles of matrix work; the four SIMDs of a CU together ask for
+// 32 KB in that time and the vector cache delivers 24.  A 64 x 64 tile reads 10 KB for 768 cycles, so the matrix pipe is
+// the narrower one again.  128 CUs, against the 32 x 64 tiles: 784 x 512 x 4608 59.5 -> 40 us, 3136 x 256 x 2304 62.5 -> 42,
+// 50176 x 64 x 576 57.3 -> 50 (fp32 matrix instructions: 69.7, 76.8, 76.5).  With rows and weights from fixed addresses and
+// no exchange through LDS the first takes 32 us: that much is the matrix pipe.  Rows fetched 128 bytes at a time: 42 us.
+// (bf16 layers gain nothing from it: 239.7 us for VGG-16's kernels either way.)
+//
+// The NW waves of a workgroup own the same tile and split K, as in conv_wave_body: no barrier in the K loop, the pixel
+// rows pass through a corner of LDS of the wave's own (coalesced 64-byte rows in, matrix order out), two chunks of rows and
+// weights are in flight.  The four 32 x 32 blocks of the partial tiles are then summed in wave order, NT / 256 blocks at
+// a time, which bounds the LDS at 16 KB per four waves, and finished by the same epilogue.
+template <int NW>
+__global__ __launch_bounds__(NW * 64) void conv_block_kernel(const ConvArgs p) {
+  constexpr int ES = 4;
+  constexpr int KS = 8;                      // k per step of the plan; a chunk is two steps
+  constexpr int NT = NW * 64;
+  constexpr int NP = 3;                      // parts of a weight
+  constexpr int STAGE_V = 64 * 4;            // one wave's staging buffer: 64 pixels x 4 pieces of 16 bytes
+  constexpr int BPP = NT >= 256 ? NT / 256 : 1;  // 32 x 32 blocks summed per pass: a channel quad per thread (NW = 2: two)
+  constexpr int LDS_F = NW * STAGE_V * 4 > NW * BPP * 1024 ? NW * STAGE_V * 4 : NW * BPP * 1024;
+  static_assert(NW == 2 || NW == 4 || NW == 8, "one or two blocks per pass");
+
+  __shared__ __align__(16) float red[LDS_F];
+
+  if (p.wave_prio) __builtin_amdgcn_s_setprio(3);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int li = lane & 31, lh = lane >> 5;
+  const int L = (int)blockIdx.x;
+  int mt, g;  // workgroup -> (pixel tile, weight group), tiles that read the same weights on one XCD (see conv_wave_body)
+  {
+    const int x = L & 7, q = L >> 3;
+    if (p.xmode == 1) {
+      g = (q / p.MT) * 8 + x;
+      mt = q % p.MT;
+    } else if (p.xmode == 2) {
+      const int r = 8 / p.G;
+      g = x / r;
+      mt = q * r + (x % r);
+    } else {
+      g = L / p.MT;
+      mt = L % p.MT;
+    }
+    if (g >= p.G || mt >= p.MT) return;
+  }
+  const int zi = g / p.NTn;
+  const int m0 = mt * 64, nb0 = (g - zi * p.NTn) * 2;
+  const int s_wg0 = zi * p.sz;
+  const int s_wg1 = min(s_wg0 + p.sz, p.S);
+  const int sbeg = min(s_wg0 + wave * p.sw, s_wg1);
+  const int nchunks = (min(sbeg + p.sw, s_wg1) - sbeg) >> 1;
+
+  // Walk over k = (tap, ci): a chunk never straddles a tap, so the walk is wave-uniform and lives in scalars.  A lane keeps
+  // the byte offset of its piece of each row at tap (0, 0) and one bit per tap that says whether that pixel lies inside the
+  // image; the loads go through a buffer descriptor, which returns 0 for an offset past the tensor's end, so padding and
+  // the pixels past M need no blanking and the loop body no branch.
+  const int kbeg = sbeg * KS;
+  const int tap0 = fast_div(kbeg, p.mg_cin);
+  int ci = kbeg - tap0 * p.Cin;
+  int ky = fast_div(tap0, p.mg_kw), kx = tap0 - ky * p.kw;
+  int tap = tap0;
+  const int piece = lane & 3, prow = lane >> 2;
+  int rbase[4];
+  uint32_t taps[4];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int m = m0 + 16 * r + prow;
+    const int y = fast_div(m, p.mg_wo), x = m - y * p.Wo;
+    const int iy0 = y * p.stride - p.pad, ix0 = x * p.stride - p.pad;
+    rbase[r] = (iy0 * p.W + ix0) * p.Cin * ES + piece * 16;
+    // the taps inside the image form a rectangle: rows [ya, yb), columns [xa, xb)
+    const int ya = max(0, -iy0), yb = min(p.kh, p.H - iy0), xa = max(0, -ix0), xb = min(p.kw, p.W - ix0);
+    const uint32_t cols = m < p.M && xb > xa ? ((xb - xa >= 32 ? 0u : (1u << (xb - xa))) - 1u) << xa : 0u;
+    taps[r] = 0u;
+    for (int t = ya; t < yb; ++t) taps[r] |= cols << (t * p.kw);
+  }
+  const auto xrsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p.x), 0, (int)((uint32_t)(p.H * p.W) * (uint32_t)p.Cin * ES), 0x00027000);
+  uint4 rows[2][4];
+  auto load_row = [&](int s, int r) {
+    const int off = ((ky * p.W + kx) * p.Cin + ci) * ES;
+    const uint32_t bit = tap < 32 ? 1u << tap : 0u;  // past the last tap: nothing is inside
+    const int o = (taps[r] & bit) ? rbase[r] + off : -16;
+    rows[s][r] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(xrsrc, o, 0, 0));
+  };
+  auto advance = [&]() {  // to the next chunk
+    ci += 2 * KS;
+    const bool next = ci >= p.Cin;
+    ci = next ? ci - p.Cin : ci;
+    tap += next ? 1 : 0;
+    kx += next ? 1 : 0;
+    const bool wrap = kx == p.kw;
+    kx = wrap ? 0 : kx;
+    ky += wrap ? 1 : 0;
+  };
+  const int wstride = (p.S >> 1) * NP * 1024;  // bytes of one channel block
+  const auto wrsrc = __builtin_amdgcn_make_buffer_rsrc((unsigned char*)const_cast<void*>(p.w) + (size_t)nb0 * wstride, 0, 2 * wstride + 12 * 1024, 0x00027000);
+  int woff = (sbeg >> 1) * NP * 1024;
+  uint4 bw[2][2][NP];
+  auto load_w = [&](int s) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int q = 0; q < NP; ++q)
+        bw[s][j][q] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(wrsrc, lane * 16, woff + j * wstride + q * 1024, 0));
+    woff += NP * 1024;
+  };
+
+  f32x16 acc[2][2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+
+  uint4* const st = reinterpret_cast<uint4*>(red) + wave * STAGE_V;
+  // A wave issues in order and the matrix pipe takes 32 cycles per instruction, so everything else a chunk needs is laid
+  // between the matrix instructions, and the scheduler is told to leave it there: the rows of the next chunk go to LDS
+  // and come back in matrix order, those of the chunk after the next are requested, and the operand just fetched is split.
+  Split8 cur[2], nxt[2];
+  uint4 a4[2][2];
+  // lanes exchange data through the wave's buffer: order the accesses of the whole wave, not only of each lane
+  auto wave_order = [&]() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  };
+  auto put_rows = [&](int s) {
+    wave_order();
+#pragma unroll
+    for (int r = 0; r < 4; ++r) st[(16 * r + prow) * 4 + (piece ^ ((prow >> 1) & 3))] = rows[s][r];
+    wave_order();
+  };
+  auto get_rows = [&]() {
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) a4[i][h] = st[(32 * i + li) * 4 + ((2 * lh + h) ^ ((li >> 1) & 3))];  // spread over the banks
+  };
+  float r0, r1;
+  uint32_t mid;
+  auto split_piece = [&](int u) {  // piece u of 16: half of the work on two of the lane's sixteen values (see split8)
+    const int i = u >> 3, e = (u >> 1) & 3;
+    const uint4& v = a4[i][e >> 1];
+    const uint32_t u0 = (e & 1) ? v.z : v.x, u1 = (e & 1) ? v.w : v.y;
+    uint4* to = nxt[i].p;
+    auto set = [&](uint4& d, uint32_t w) { (e == 0 ? d.x : e == 1 ? d.y : e == 2 ? d.z : d.w) = w; };
+    if ((u & 1) == 0) {
+      set(to[0], __builtin_amdgcn_perm(u1, u0, 0x07060302u));
+      r0 = __uint_as_float(u0) - __uint_as_float(u0 & 0xffff0000u);
+      r1 = __uint_as_float(u1) - __uint_as_float(u1 & 0xffff0000u);
+      mid = pack_bf16_rne(r0, r1);
+      set(to[1], mid);
+    } else {
+      set(to[2], pack_bf16_rne(r0 - __uint_as_float(mid << 16), r1 - __uint_as_float(mid & 0xffff0000u)));
+    }
+  };
+  auto take_next = [&]() {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) cur[i] = nxt[i];
+  };
+  auto chunk = [&](int s) {  // slot s of the weights holds this chunk's, slot s ^ 1 of the rows the next chunk's
+    constexpr int PA[6] = {2, 1, 0, 1, 0, 0}, PB[6] = {0, 1, 2, 0, 1, 0};  // from the smallest terms to the largest
+    put_rows(s ^ 1);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int n = 0; n < 24; ++n) {
+      const int t = n >> 2, i = (n >> 1) & 1, j = n & 1;
+      acc[i][j] = mfma_bf16(cur[i].p[PA[t]], bw[s][j][PB[t]], acc[i][j]);
+      if (n == 0) get_rows();
+      if (n < 4) load_row(s ^ 1, n);  // two chunks ahead (past the end of the slice: nothing is read, or never used)
+      if (n == 3) advance();
+      if (n >= 6 && n < 22) split_piece(n - 6);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    load_w(s);  // (spread over the chunk instead, each part as it falls free: 7 % slower)
+    take_next();
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto load_rows = [&](int s) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) load_row(s, r);
+    advance();
+  };
+  load_rows(0);
+  load_w(0);
+  load_rows(1);
+  load_w(1);
+  put_rows(0);
+  load_rows(0);
+  get_rows();
+#pragma unroll
+  for (int u = 0; u < 16; ++u) split_piece(u);
+  take_next();
+  int c = 0;
+  for (; c + 2 <= nchunks; c += 2) {
+    chunk(0);
+    chunk(1);
+  }
+  if (c < nchunks) chunk(0);
+
+  // --- sum the NW partial tiles in wave order, BPP blocks (i, j) per pass; epilogue per quad of consecutive channels:
+  // quad q of a block = elements 4q..4q+3 of [v][lane], i.e. pixel 8*(v/4) + 4*(lane/32) + v%4, channels lane%32 .. +3
+  const bool own_epilogue = p.splitk == 1;
+#pragma unroll
+  for (int pass = 0; pass < 4 / BPP; ++pass) {
+    __syncthreads();  // the partial tiles reuse the staging buffers, then the pass before
+#pragma unroll
+    for (int b = 0; b < BPP; ++b) {
+      const int blk = pass * BPP + b;
+#pragma unroll
+      for (int w = 0; w < 16; ++w) red[(wave * BPP + b) * 1024 + w * 64 + lane] = acc[blk >> 1][blk & 1][w];
+    }
+    __syncthreads();
+    const int b = BPP == 1 ? 0 : tid >> 8;
+#pragma unroll
+    for (int q = tid & 255; q < 256; q += NT) {
+      const int e = 4 * q, v = e >> 6, l = e & 63;
+      const int row = (v >> 2) * 8 + (l >> 5) * 4 + (v & 3), col = l & 31;
+      const int blk = pass * BPP + b;
+      const int mm = m0 + 32 * (blk >> 1) + row, n = (nb0 + (blk & 1)) * 32 + col;
+      if (mm < p.M && n < p.Cout) {
+        const size_t o = (size_t)mm * p.Cout + n;
+        float val[4] = {0.f, 0.f, 0.f, 0.f};
+        float4 bias = make_float4(0.f, 0.f, 0.f, 0.f), res = bias;
+        if (own_epilogue) {
+          bias = *(const float4*)(p.bias + n);
+          if (p.res) res = *(const float4*)((const float*)p.res + o);
+        }
+  #pragma unroll
+        for (int w = 0; w < NW; ++w) {
+          const float4 t = *(const float4*)&red[(w * BPP + b) * 1024 + e];
+          val[0] += t.x; val[1] += t.y; val[2] += t.z; val[3] += t.w;
+        }
+        if (!own_epilogue) {  // partial sums of this K slice; splitk_reduce_kernel finishes the layer
+          *(float4*)(p.ws + (size_t)zi * p.M * p.Cout + o) = make_float4(val[0], val[1], val[2], val[3]);
+        } else {
+          val[0] += bias.x; val[1] += bias.y; val[2] += bias.z; val[3] += bias.w;
+          if (p.res) {
+            val[0] += res.x; val[1] += res.y; val[2] += res.z; val[3] += res.w;
+          }
+  #pragma unroll
+          for (int i = 0; i < 4; ++i) val[i] = apply_act(val[i], p.act);
+          *(float4*)((float*)p.y + o) = make_float4(val[0], val[1], val[2], val[3]);
+        }
+      }
+    }
+  }
+}
+
+template __global__ void conv_block_kernel<2>(const ConvArgs);
+template __global__ void conv_block_kernel<4>(const ConvArgs);
+template __global__ void conv_block_kernel<8>(const ConvArgs);
+
+}  // namespace daris

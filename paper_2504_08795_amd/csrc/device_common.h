@@ -1,0 +1,130 @@
+// Device-side helpers that the kernels of every code object share: element conversions and vector packing, index division,
+// and the products of fp32 operands on the bf16 matrix instructions.
+#pragma once
+#include <hip/hip_runtime.h>
+
+#include <cstdint>
+
+namespace daris {
+
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+
+// ---- element helpers ------------------------------------------------------------------------------------------
+
+__device__ __forceinline__ float bf16_bits_to_f32(uint32_t b) { return __uint_as_float(b << 16); }
+
+// float -> bfloat16 bits, round to nearest, ties to even; NaN stays a quiet NaN.
+__device__ __forceinline__ uint32_t f32_to_bf16_bits(float f) {
+  uint32_t u = __float_as_uint(f);
+  if ((u & 0x7fffffffu) > 0x7f800000u) return (u >> 16) | 0x40u;
+  u += 0x7fffu + ((u >> 16) & 1u);
+  return u >> 16;
+}
+
+__device__ __forceinline__ float apply_act(float v, int act) {
+  if (act == 1) v = fmaxf(v, 0.f);
+  else if (act == 2) v = fminf(fmaxf(v, 0.f), 6.f);
+  return v;
+}
+
+template <bool BF16>
+__device__ __forceinline__ float load_elem(const void* p, size_t i) {
+  if (BF16) return bf16_bits_to_f32(((const uint16_t*)p)[i]);
+  return ((const float*)p)[i];
+}
+
+template <bool BF16>
+__device__ __forceinline__ void store_elem(void* p, size_t i, float v) {
+  if (BF16) ((uint16_t*)p)[i] = (uint16_t)f32_to_bf16_bits(v);
+  else ((float*)p)[i] = v;
+}
+
+// n / d for 0 <= n with n * d < 2^32, through the host-made multiplier magic = floor(2^32 / d) + 1 (0 stands for d = 1):
+// the quotient is the high word of n * magic, a handful of cycles instead of the ~40-instruction division sequence.
+__device__ __forceinline__ int fast_div(int n, uint32_t magic) { return magic ? (int)__umulhi((uint32_t)n, magic) : n; }
+
+// v if ok, else all zero bits; component-wise so that it stays a register select (a select between two uint4
+// objects would be done through their addresses and push the access to scratch / flat memory).
+__device__ __forceinline__ uint4 keep_if(bool ok, uint4 v) {
+  v.x = ok ? v.x : 0u;
+  v.y = ok ? v.y : 0u;
+  v.z = ok ? v.z : 0u;
+  v.w = ok ? v.w : 0u;
+  return v;
+}
+
+// Unpack one 16-byte vector into VEC floats (4 for fp32, 8 for bf16).
+template <bool BF16>
+__device__ __forceinline__ void unpack(const uint4& v, float* o) {
+  if (BF16) {
+    o[0] = __uint_as_float(v.x << 16); o[1] = __uint_as_float(v.x & 0xffff0000u);
+    o[2] = __uint_as_float(v.y << 16); o[3] = __uint_as_float(v.y & 0xffff0000u);
+    o[4] = __uint_as_float(v.z << 16); o[5] = __uint_as_float(v.z & 0xffff0000u);
+    o[6] = __uint_as_float(v.w << 16); o[7] = __uint_as_float(v.w & 0xffff0000u);
+  } else {
+    o[0] = __uint_as_float(v.x); o[1] = __uint_as_float(v.y); o[2] = __uint_as_float(v.z); o[3] = __uint_as_float(v.w);
+  }
+}
+
+template <bool BF16>
+__device__ __forceinline__ uint4 pack(const float* o) {
+  uint4 v;
+  if (BF16) {
+    v.x = f32_to_bf16_bits(o[0]) | (f32_to_bf16_bits(o[1]) << 16);
+    v.y = f32_to_bf16_bits(o[2]) | (f32_to_bf16_bits(o[3]) << 16);
+    v.z = f32_to_bf16_bits(o[4]) | (f32_to_bf16_bits(o[5]) << 16);
+    v.w = f32_to_bf16_bits(o[6]) | (f32_to_bf16_bits(o[7]) << 16);
+  } else {
+    v.x = __float_as_uint(o[0]); v.y = __float_as_uint(o[1]); v.z = __float_as_uint(o[2]); v.w = __float_as_uint(o[3]);
+  }
+  return v;
+}
+
+// ---- fp32 products on the bf16 matrix instructions ---------------------------------------------------------------------
+//
+// An fp32 number has 24 significant bits, a bf16 number 8: every finite fp32 number is the exact sum of three bf16 numbers
+// x1 + x2 + x3, each at most 2^-7 of the one before.  A product of two such sums has nine terms, each exact in fp32; the
+// six largest (x1y1, x1y2, x2y1, x1y3, x2y2, x3y1) leave out at most 2^-23 of |xy|, with no bias (measured on sums of 4608
+// terms against float64: the error of the plain fp32 instruction is the larger one).  v_mfma_f32_32x32x16_bf16 does in 32
+// cycles what v_mfma_f32_32x32x2_f32 does in 512, so the six take 3/8 of the matrix time.  Accumulation is fp32 as before.
+// The first part of an activation is cut off (a rounded one could overflow), all other parts are rounded to nearest even;
+// the weights' parts are made at registration.  (An infinite operand gives NaN.)
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+
+__device__ __forceinline__ uint32_t pack_bf16_rne(float a, float b) {  // one v_cvt_pk_bf16_f32
+  f32x2 v;
+  v.x = a;
+  v.y = b;
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
+}
+
+struct Split8 {
+  uint4 p[3];  // eight consecutive k: first, second, third parts
+};
+
+// lo = elements 0..3, hi = elements 4..7
+__device__ __forceinline__ Split8 split8(const uint4& lo, const uint4& hi) {
+  const uint32_t in[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+  uint32_t out[3][4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const uint32_t u0 = in[2 * i], u1 = in[2 * i + 1];
+    out[0][i] = __builtin_amdgcn_perm(u1, u0, 0x07060302u);  // the upper halves
+    const float r0 = __uint_as_float(u0) - __uint_as_float(u0 & 0xffff0000u), r1 = __uint_as_float(u1) - __uint_as_float(u1 & 0xffff0000u);
+    const uint32_t m = pack_bf16_rne(r0, r1);
+    out[1][i] = m;
+    out[2][i] = pack_bf16_rne(r0 - __uint_as_float(m << 16), r1 - __uint_as_float(m & 0xffff0000u));
+  }
+  Split8 s;
+#pragma unroll
+  for (int q = 0; q < 3; ++q) s.p[q] = make_uint4(out[q][0], out[q][1], out[q][2], out[q][3]);
+  return s;
+}
+
+__device__ __forceinline__ f32x16 mfma_bf16(const uint4& a, const uint4& b, f32x16 c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+
+}  // namespace daris

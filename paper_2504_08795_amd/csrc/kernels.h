@@ -79,9 +79,11 @@ struct FcArgs {
 struct ConvPlan {
   int32_t kernel;  // KernelId
   int splitk;      // K slices across workgroups (1 = none); > 1 needs the workspace and the reduction launch
+  int tm;                          // 2: a wave takes two pixel tiles of 32 (conv_block_*); MT and grid_x still count single tiles
   int rows;                        // pixels per wave tile: 32 (conv_wave_*: channel blocks of 32) or 16 (conv_wave16_*: blocks of 16)
   int tn, nw, S, sz, sw, MT, NTn, G, xmode;
-  int step_align;                  // K slices are multiples of this many steps (2: staged pixel operand possible)
+  int step_align;                  // K slices are multiples of this many steps
+  int staged;                      // the pixel operand may be fetched in whole 64-byte rows through LDS
   int tiles;                       // output tiles per grid.z slice
   size_t ws_bytes;                 // split-K workspace this launch needs
   uint32_t grid_x;                 // workgroups of the launch
@@ -94,7 +96,8 @@ inline bool conv_rows_staged(int cin_stride, int bf16) { return cin_stride > 0 &
 // (nominal_cus: how many CUs the grid is balanced for) only, so results do not depend on the partition a stage runs in.  step_align = 2 cuts K in whole chunks of two steps (for conv_rows_staged shapes), else 1.
 // cin_stride = the input tensor's channel stride: when it is a whole number of the 16-row kernel's K steps and the 32-row
 // plan would split K across workgroups, a 16-row plan that does not need to is chosen instead (cin_stride 0: never).
-ConvPlan plan_conv(int M, int N, int Kpad, int bf16, int step_align, int cin_stride = 0, int nominal_cus = 128);
+// allow_block = false: no 64-pixel tiles (a convolution that shares its launch or computes its input on the fly).
+ConvPlan plan_conv(int M, int N, int Kpad, int bf16, int step_align, int cin_stride = 0, int nominal_cus = 128, bool allow_block = true);
 // Plan for a second convolution that is to share a launch with `first`: the same wave-tile kernel variant, K not split
 // across workgroups.  Returns a plan with kernel == K_NONE when that is not possible.
 ConvPlan plan_conv_like(const ConvPlan& first, int M, int N, int Kpad, int bf16, int step_align, int nominal_cus = 128);
@@ -123,6 +126,7 @@ struct KernelTable {
   const AqlKernel* pair[2][6][3] = {};  // gather modes 0, 1, 3
   const AqlKernel* conv16[2][6] = {};   // 16-row tiles: [bf16][(tn - 1) * 3 + log2(nw) - 1]
   const AqlKernel* pair16[2][6] = {};
+  const AqlKernel* block[3] = {};       // 64-pixel tiles: [log2(nw) - 1]
   const AqlKernel* convdw[2][6] = {};   // 1x1 convolution with a fused depthwise producer (fp32: tn = 1 only)
   const AqlKernel *reduce[2] = {}, *dwconv[2] = {}, *maxpool[2] = {}, *gavgpool[2] = {}, *fc[2] = {}, *ingest[2] = {}, *egress[2] = {};
   const AqlKernel* cu_probe = nullptr;

@@ -6,83 +6,10 @@
 
 #include <type_traits>
 
+#include "device_common.h"
 #include "kernels.h"
 
 namespace daris {
-
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-
-// ---- element helpers ------------------------------------------------------------------------------------------
-
-__device__ __forceinline__ float bf16_bits_to_f32(uint32_t b) { return __uint_as_float(b << 16); }
-
-// float -> bfloat16 bits, round to nearest, ties to even; NaN stays a quiet NaN.
-__device__ __forceinline__ uint32_t f32_to_bf16_bits(float f) {
-  uint32_t u = __float_as_uint(f);
-  if ((u & 0x7fffffffu) > 0x7f800000u) return (u >> 16) | 0x40u;
-  u += 0x7fffu + ((u >> 16) & 1u);
-  return u >> 16;
-}
-
-__device__ __forceinline__ float apply_act(float v, int act) {
-  if (act == 1) v = fmaxf(v, 0.f);
-  else if (act == 2) v = fminf(fmaxf(v, 0.f), 6.f);
-  return v;
-}
-
-template <bool BF16>
-__device__ __forceinline__ float load_elem(const void* p, size_t i) {
-  if (BF16) return bf16_bits_to_f32(((const uint16_t*)p)[i]);
-  return ((const float*)p)[i];
-}
-
-template <bool BF16>
-__device__ __forceinline__ void store_elem(void* p, size_t i, float v) {
-  if (BF16) ((uint16_t*)p)[i] = (uint16_t)f32_to_bf16_bits(v);
-  else ((float*)p)[i] = v;
-}
-
-// n / d for 0 <= n with n * d < 2^32, through the host-made multiplier magic = floor(2^32 / d) + 1 (0 stands for d = 1):
-// the quotient is the high word of n * magic, a handful of cycles instead of the ~40-instruction division sequence.
-__device__ __forceinline__ int fast_div(int n, uint32_t magic) { return magic ? (int)__umulhi((uint32_t)n, magic) : n; }
-
-// v if ok, else all zero bits; component-wise so that it stays a register select (a select between two uint4
-// objects would be done through their addresses and push the access to scratch / flat memory).
-__device__ __forceinline__ uint4 keep_if(bool ok, uint4 v) {
-  v.x = ok ? v.x : 0u;
-  v.y = ok ? v.y : 0u;
-  v.z = ok ? v.z : 0u;
-  v.w = ok ? v.w : 0u;
-  return v;
-}
-
-// Unpack one 16-byte vector into VEC floats (4 for fp32, 8 for bf16).
-template <bool BF16>
-__device__ __forceinline__ void unpack(const uint4& v, float* o) {
-  if (BF16) {
-    o[0] = __uint_as_float(v.x << 16); o[1] = __uint_as_float(v.x & 0xffff0000u);
-    o[2] = __uint_as_float(v.y << 16); o[3] = __uint_as_float(v.y & 0xffff0000u);
-    o[4] = __uint_as_float(v.z << 16); o[5] = __uint_as_float(v.z & 0xffff0000u);
-    o[6] = __uint_as_float(v.w << 16); o[7] = __uint_as_float(v.w & 0xffff0000u);
-  } else {
-    o[0] = __uint_as_float(v.x); o[1] = __uint_as_float(v.y); o[2] = __uint_as_float(v.z); o[3] = __uint_as_float(v.w);
-  }
-}
-
-template <bool BF16>
-__device__ __forceinline__ uint4 pack(const float* o) {
-  uint4 v;
-  if (BF16) {
-    v.x = f32_to_bf16_bits(o[0]) | (f32_to_bf16_bits(o[1]) << 16);
-    v.y = f32_to_bf16_bits(o[2]) | (f32_to_bf16_bits(o[3]) << 16);
-    v.z = f32_to_bf16_bits(o[4]) | (f32_to_bf16_bits(o[5]) << 16);
-    v.w = f32_to_bf16_bits(o[6]) | (f32_to_bf16_bits(o[7]) << 16);
-  } else {
-    v.x = __float_as_uint(o[0]); v.y = __float_as_uint(o[1]); v.z = __float_as_uint(o[2]); v.w = __float_as_uint(o[3]);
-  }
-  return v;
-}
 
 // Sums the split-K partials in split order and applies the fused epilogue.  One thread per 4 output channels.
 template <bool BF16>
@@ -134,7 +61,9 @@ __device__ __forceinline__ void conv_wave_body(const ConvArgs& p, const int L, c
   // 64-byte rows (Cin * ES a multiple of 64): the pixel operand is fetched in coalesced rows and transposed through LDS;
   // 4: like 3 for a 1x1 convolution whose input is the output of a 3x3 depthwise convolution that is never stored: the
   // rows are computed here from the depthwise layer's input (p.x) and weights (dwf)
-  constexpr bool ALIGNED = MODE == 0;
+  // fp32: two K steps of 8 make one chunk of 16, the depth of the bf16 matrix instruction that takes the operands' three
+  // parts (split8); the plan cuts K in whole chunks, the weights are stored as [channel block][chunk][part][lane][16 B].
+  constexpr bool ALIGNED = BF16 && MODE == 0;
   constexpr bool STAGED = MODE == 3 || MODE == 4;
   constexpr bool DWF = MODE == 4;
   constexpr int ES = BF16 ? 2 : 4;
@@ -142,7 +71,8 @@ __device__ __forceinline__ void conv_wave_body(const ConvArgs& p, const int L, c
   constexpr int KS = 2 * VEC;
   constexpr int NT = NW * 64;
   constexpr int TILE = TN * 1024;
-  constexpr int D = 4;
+  constexpr int D = 4;                  // bf16: K steps in flight
+  constexpr int DC = DWF ? 1 : 2;   // fp32: chunks of weights in flight
   constexpr int STAGE_V = 32 * 5;  // 16-byte vectors of one wave's staging buffer: 32 pixels x (4 pieces + 1 pad)
   constexpr int LDS_F = (STAGED && NW * STAGE_V * 4 > NW * TILE) ? NW * STAGE_V * 4 : NW * TILE;
   static_assert(TN == 1 || TN == 2, "the epilogue selects between at most two channel blocks");
@@ -224,7 +154,8 @@ __device__ __forceinline__ void conv_wave_body(const ConvArgs& p, const int L, c
   const unsigned char* wptr[TN];
 #pragma unroll
   for (int j = 0; j < TN; ++j)
-    wptr[j] = (const unsigned char*)p.w + (((size_t)(nb0 + j) * p.S + sbeg) * 64 + lane) * 16;
+    wptr[j] = BF16 ? (const unsigned char*)p.w + (((size_t)(nb0 + j) * p.S + sbeg) * 64 + lane) * 16
+                   : (const unsigned char*)p.w + ((((size_t)(nb0 + j) * p.S + sbeg) >> 1) * 192 + lane) * 16;
 
   uint4 ar[D], br[D][TN];
   bool av[D];  // validity of slot d's A vector; the blanking is applied when the slot is consumed, so that a load's
@@ -297,21 +228,27 @@ __device__ __forceinline__ void conv_wave_body(const ConvArgs& p, const int L, c
     for (int v = 0; v < 16; ++v) acc[j][v] = 0.f;
 
   auto mma = [&](uint4 a4, const uint4* b) {
-    if (BF16) {
 #pragma unroll
-      for (int j = 0; j < TN; ++j)
-        acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a4), __builtin_bit_cast(bf16x8, b[j]), acc[j], 0, 0, 0);
-    } else {
-      // the TN accumulators alternate so that consecutive MFMAs are independent
+    for (int j = 0; j < TN; ++j) acc[j] = mfma_bf16(a4, b[j], acc[j]);
+  };
+  // fp32: one chunk of 16 k.  The terms go in from the smallest to the largest; the TN accumulators alternate so that
+  // consecutive instructions are independent.
+  uint4 bw[DC][TN][3];
+  auto load_wc = [&](int d) {
 #pragma unroll
-      for (int j = 0; j < TN; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a4.x), __uint_as_float(b[j].x), acc[j], 0, 0, 0);
+    for (int j = 0; j < TN; ++j) {
 #pragma unroll
-      for (int j = 0; j < TN; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a4.y), __uint_as_float(b[j].y), acc[j], 0, 0, 0);
-#pragma unroll
-      for (int j = 0; j < TN; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a4.z), __uint_as_float(b[j].z), acc[j], 0, 0, 0);
-#pragma unroll
-      for (int j = 0; j < TN; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a4.w), __uint_as_float(b[j].w), acc[j], 0, 0, 0);
+      for (int q = 0; q < 3; ++q) bw[d][j][q] = *(const uint4*)(wptr[j] + q * 1024);
+      wptr[j] += 3072;
     }
+  };
+  auto mma_chunk = [&](const uint4& lo, const uint4& hi, int d) {
+    const Split8 a = split8(lo, hi);
+    constexpr int PA[6] = {2, 1, 0, 1, 0, 0}, PB[6] = {0, 1, 2, 0, 1, 0};
+#pragma unroll
+    for (int t = 0; t < 6; ++t)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) acc[j] = mfma_bf16(a.p[PA[t]], bw[d][j][PB[t]], acc[j]);
   };
   auto compute = [&](int d) {
     uint4 a4 = keep_if(av[d], ar[d]);
@@ -329,7 +266,51 @@ __device__ __forceinline__ void conv_wave_body(const ConvArgs& p, const int L, c
   // wait only for the oldest slot.  Refills past the end of the wave's K slice fetch valid memory that is never used
   // (the weight buffer carries D KiB of slack; the A pointer always points into the input); only the computes of the
   // ragged tail are conditional.
-  if constexpr (!STAGED) {
+  if constexpr (!STAGED && !BF16) {
+    // register-fed fp32: a lane's eight k of a chunk are two quads, each inside one filter tap (channel strides are
+    // multiples of four), located from the chunk number in closed form
+    uint4 aq[DC][2];
+    bool aqv[DC][2];
+    kcur += lh * 8;
+    auto load_c = [&](int d) {
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        const int k = kcur + 4 * e;
+        const int t = MODE == 2 ? k / VEC : fast_div(k, p.mg_cin), c = k - t * p.Cin;
+        const int y = fast_div(t, p.mg_kw), x = t - y * p.kw;
+        const int iy = iy0 + y, ix = ix0 + x;
+        const bool v = a_ok && y < p.kh && (unsigned)iy < (unsigned)p.H && (unsigned)ix < (unsigned)p.W;
+        const size_t px = (size_t)(v ? iy * p.W + ix : 0);
+        if (MODE == 2) {
+          const float* q = (const float*)xb + px;
+          aq[d][e].x = __float_as_uint(q[0]);
+          aq[d][e].y = __float_as_uint(q[po1]);
+          aq[d][e].z = __float_as_uint(q[po2]);
+          aq[d][e].w = __float_as_uint(q[po3]);
+        } else {
+          aq[d][e] = *(const uint4*)(xb + (px * p.Cin + (v ? c : 0)) * ES);  // always a valid address
+        }
+        aqv[d][e] = v;
+      }
+      load_wc(d);
+      kcur += 16;
+    };
+    auto compute_c = [&](int d) { mma_chunk(keep_if(aqv[d][0], aq[d][0]), keep_if(aqv[d][1], aq[d][1]), d); };
+    const int nch = nsteps >> 1;
+#pragma unroll
+    for (int d = 0; d < DC; ++d) load_c(d);
+    int done = 0;
+    for (; done + DC <= nch; done += DC) {
+#pragma unroll
+      for (int d = 0; d < DC; ++d) {
+        compute_c(d);
+        load_c(d);
+      }
+    }
+#pragma unroll
+    for (int d = 0; d < DC; ++d)
+      if (done + d < nch) compute_c(d);
+  } else if constexpr (!STAGED) {
 #pragma unroll
     for (int d = 0; d < D; ++d) load(d);
     int done = 0;
@@ -361,22 +342,40 @@ __device__ __forceinline__ void conv_wave_body(const ConvArgs& p, const int L, c
         wptr[j] += 1024;
       }
     };
-    // rows in the wave's buffer -> MFMA order -> two K steps against the weights of pipeline slots d0, d0 + 1
-    auto exchange_and_mma = [&](int d0) {
+    // rows in the wave's buffer -> MFMA order -> two K steps against the weights of chunk slot cs (bf16: of the pipeline
+    // slots 2 cs, 2 cs + 1)
+    auto exchange_and_mma = [&](int cs) {
+      const int d0 = 2 * cs;
       // lanes exchange data through the wave's buffer: order the accesses of the whole wave, not only of each lane
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
       __builtin_amdgcn_wave_barrier();
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
       uint4 a4[2];
 #pragma unroll
-      for (int s2 = 0; s2 < 2; ++s2) a4[s2] = st[li * 5 + 2 * s2 + lh];
+      for (int s2 = 0; s2 < 2; ++s2) a4[s2] = st[li * 5 + (BF16 ? 2 * s2 + lh : 2 * lh + s2)];
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
       __builtin_amdgcn_wave_barrier();
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      if constexpr (BF16) {
 #pragma unroll
-      for (int s2 = 0; s2 < 2; ++s2) {
-        mma(a4[s2], br[d0 + s2]);
-        load_w(d0 + s2);
+        for (int s2 = 0; s2 < 2; ++s2) {
+          mma(a4[s2], br[d0 + s2]);
+          load_w(d0 + s2);
+        }
+      } else {
+        mma_chunk(a4[0], a4[1], cs);
+        __builtin_amdgcn_sched_barrier(0);  // the refill takes over the registers of the slot just used (64 fewer in all)
+        load_wc(cs);
+      }
+    };
+    constexpr int CS = BF16 ? 2 : DC;  // chunks of weights in flight
+    auto load_w_all = [&]() {
+      if constexpr (BF16) {
+#pragma unroll
+        for (int d = 0; d < D; ++d) load_w(d);
+      } else {
+#pragma unroll
+        for (int d = 0; d < DC; ++d) load_wc(d);
       }
     };
     const int nchunks = nsteps >> 1;
@@ -436,21 +435,22 @@ __device__ __forceinline__ void conv_wave_body(const ConvArgs& p, const int L, c
         for (int i = 0; i < VEC; ++i) acc[i] = apply_act(acc[i], dwf.act);
         return pack<BF16>(acc);
       };
-      auto chunk_dw = [&](int d0) {
+      auto chunk_dw = [&](int cs) {
 #pragma unroll
         for (int j = 0; j < 2; ++j) st[(16 * j + prow) * 5 + piece] = dw_value(j);
         dw_issue();  // the next chunk's operands travel while this one goes through the matrix pipe
-        exchange_and_mma(d0);
+        exchange_and_mma(cs);
       };
       dw_issue();
-#pragma unroll
-      for (int d = 0; d < D; ++d) load_w(d);
+      load_w_all();
       int c = 0;
-      for (; c + 2 <= nchunks; c += 2) {
-        chunk_dw(0);
-        chunk_dw(2);
+      for (; c + CS <= nchunks; c += CS) {
+#pragma unroll
+        for (int s = 0; s < CS; ++s) chunk_dw(s);
       }
-      if (c < nchunks) chunk_dw(0);
+#pragma unroll
+      for (int s = 0; s < CS - 1; ++s)
+        if (c + s < nchunks) chunk_dw(s);
     } else {
       int siy0[2], six0[2];
       bool sok[2];
@@ -473,8 +473,8 @@ __device__ __forceinline__ void conv_wave_body(const ConvArgs& p, const int L, c
         }
       };
       enter_rows();
-      uint4 gr[2][2];
-      bool gok[2][2];
+      uint4 gr[CS][2];
+      bool gok[CS][2];
       auto load_rows = [&](int slot) {  // the chunk at (tap, ci) into register slot `slot`, then on to the next chunk
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
@@ -492,22 +492,23 @@ __device__ __forceinline__ void conv_wave_body(const ConvArgs& p, const int L, c
         }
       };
       // one chunk: rows of register slot `slot` -> LDS -> MFMA order; weights of pipeline slots d0, d0 + 1
-      auto chunk = [&](int slot, int d0) {
+      auto chunk = [&](int slot) {
 #pragma unroll
         for (int j = 0; j < 2; ++j) st[(16 * j + prow) * 5 + piece] = keep_if(gok[slot][j], gr[slot][j]);
-        load_rows(slot);  // two chunks ahead (past the end of the slice: valid memory, never used)
-        exchange_and_mma(d0);
+        load_rows(slot);  // CS chunks ahead (past the end of the slice: valid memory, never used)
+        exchange_and_mma(slot);
       };
-      load_rows(0);
-      load_rows(1);
 #pragma unroll
-      for (int d = 0; d < D; ++d) load_w(d);
+      for (int s = 0; s < CS; ++s) load_rows(s);
+      load_w_all();
       int c = 0;
-      for (; c + 2 <= nchunks; c += 2) {
-        chunk(0, 0);
-        chunk(1, 2);
+      for (; c + CS <= nchunks; c += CS) {
+#pragma unroll
+        for (int s = 0; s < CS; ++s) chunk(s);
       }
-      if (c < nchunks) chunk(0, 0);
+#pragma unroll
+      for (int s = 0; s < CS - 1; ++s)
+        if (c + s < nchunks) chunk(s);
     }
     __syncthreads();  // the partial tiles below reuse the LDS of every wave's staging buffer
   }
@@ -600,7 +601,9 @@ __global__ __launch_bounds__(NW * 64) void conv_wave_pair_kernel(const ConvArgs 
 // goes through LDS as before, and the reduction launch disappears.  One K step is 64 bytes of a pixel: lane (i, q) =
 // (pixel row i = lane % 16, quarter q = lane / 16) loads the 16 bytes at k = step * KS + q * VEC, and the weights were
 // packed at registration as [channel block of 16][step][lane (j, q)][16 B] with the same k order.  Cin is a multiple of
-// KS, so a step never straddles a filter tap and the K walk is wave-uniform.
+// KS, so a step never straddles a filter tap and the K walk is wave-uniform.  fp32 takes two steps (32 k) at a time, in
+// three bf16 parts per operand (split8): lane (i, q) holds k = 8 q .. 8 q + 7 of the pair, the weights are
+// [channel block of 16][pair][part][lane][16 B], and the plan cuts K in whole pairs.
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 template <bool BF16, int TB, int NW>
@@ -609,8 +612,10 @@ __device__ __forceinline__ void conv_wave16_body(const ConvArgs& p, const int L)
   constexpr int VEC = 16 / ES;
   constexpr int KS = 4 * VEC;  // k per step: 16 (fp32) / 32 (bf16)
   constexpr int TILE = TB * 256;
-  constexpr int D = 4;
-  constexpr int STAGE_V = 16 * 5;  // 16-byte vectors of one wave's staging buffer: 16 pixels x (4 pieces + 1 pad)
+  constexpr int D = 4;                        // bf16: steps in flight
+  constexpr int DP = TB == 1 ? 3 : 2;         // fp32: pairs of steps in flight
+  constexpr int SR = 16 * 5;                  // 16-byte vectors of one step's rows: 16 pixels x (4 pieces + 1 pad)
+  constexpr int STAGE_V = BF16 ? SR : 2 * SR; // 16-byte vectors of one wave's staging buffer
   constexpr int LDS_F = NW * STAGE_V * 4 > NW * TILE ? NW * STAGE_V * 4 : NW * TILE;
   static_assert(TB == 1 || TB == 2, "the epilogue selects between at most two channel blocks");
 
@@ -669,10 +674,24 @@ __device__ __forceinline__ void conv_wave16_body(const ConvArgs& p, const int L)
   enter_tap();
   const unsigned char* wptr[TB];
 #pragma unroll
-  for (int j = 0; j < TB; ++j) wptr[j] = (const unsigned char*)p.w + (((size_t)(nb0 + j) * p.S + sbeg) * 64 + lane) * 16;
+  for (int j = 0; j < TB; ++j)
+    wptr[j] = BF16 ? (const unsigned char*)p.w + (((size_t)(nb0 + j) * p.S + sbeg) * 64 + lane) * 16
+                   : (const unsigned char*)p.w + ((((size_t)(nb0 + j) * p.S + sbeg) >> 1) * 192 + lane) * 16;
 
   uint4 ar[D], br[D][TB];
   bool av[D];
+  uint4 ar2[DP][2], bw[DP][TB][3];
+  bool av2[DP][2];
+  auto next_row = [&]() {
+    ci += KS;
+    if (ci >= p.Cin) {  // wave-uniform
+      ci -= p.Cin;
+      if (++kx == p.kw) { kx = 0; ++ky; }
+      enter_tap();
+    } else {
+      ap += KS * ES;
+    }
+  };
   auto load = [&](int d) {
     ar[d] = *(const uint4*)ap;
     av[d] = a_valid;
@@ -681,13 +700,20 @@ __device__ __forceinline__ void conv_wave16_body(const ConvArgs& p, const int L)
       br[d][j] = *(const uint4*)wptr[j];
       wptr[j] += 1024;
     }
-    ci += KS;
-    if (ci >= p.Cin) {  // wave-uniform
-      ci -= p.Cin;
-      if (++kx == p.kw) { kx = 0; ++ky; }
-      enter_tap();
-    } else {
-      ap += KS * ES;
+    next_row();
+  };
+  auto load_pair = [&](int d) {
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      ar2[d][e] = *(const uint4*)ap;
+      av2[d][e] = a_valid;
+      next_row();
+    }
+#pragma unroll
+    for (int j = 0; j < TB; ++j) {
+#pragma unroll
+      for (int q = 0; q < 3; ++q) bw[d][j][q] = *(const uint4*)(wptr[j] + q * 1024);
+      wptr[j] += 3072;
     }
   };
 
@@ -723,36 +749,60 @@ __device__ __forceinline__ void conv_wave16_body(const ConvArgs& p, const int L)
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    if (BF16) {
+#pragma unroll
+    for (int j = 0; j < TB; ++j)
+      acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a4), __builtin_bit_cast(bf16x8, br[d][j]), acc[j], 0, 0, 0);
+  };
+  auto compute_pair = [&](int d) {
+#pragma unroll
+    for (int e = 0; e < 2; ++e) st[e * SR + prow * 5 + piece] = keep_if(av2[d][e], ar2[d][e]);
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    const int at = (lq >> 1) * SR + li * 5 + 2 * (lq & 1);
+    const uint4 lo = st[at], hi = st[at + 1];
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    const Split8 a = split8(lo, hi);
+    constexpr int PA[6] = {2, 1, 0, 1, 0, 0}, PB[6] = {0, 1, 2, 0, 1, 0};  // from the smallest terms to the largest
+#pragma unroll
+    for (int t = 0; t < 6; ++t)
 #pragma unroll
       for (int j = 0; j < TB; ++j)
-        acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a4), __builtin_bit_cast(bf16x8, br[d][j]), acc[j], 0, 0, 0);
-    } else {
-#pragma unroll
-      for (int j = 0; j < TB; ++j) acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a4.x), __uint_as_float(br[d][j].x), acc[j], 0, 0, 0);
-#pragma unroll
-      for (int j = 0; j < TB; ++j) acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a4.y), __uint_as_float(br[d][j].y), acc[j], 0, 0, 0);
-#pragma unroll
-      for (int j = 0; j < TB; ++j) acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a4.z), __uint_as_float(br[d][j].z), acc[j], 0, 0, 0);
-#pragma unroll
-      for (int j = 0; j < TB; ++j) acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a4.w), __uint_as_float(br[d][j].w), acc[j], 0, 0, 0);
-    }
+        acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a.p[PA[t]]), __builtin_bit_cast(bf16x8, bw[d][j][PB[t]]), acc[j], 0, 0, 0);
   };
 
   // the same D-deep software pipeline as the 32-row kernel: unconditional loads, conditional computes only in the tail
-#pragma unroll
-  for (int d = 0; d < D; ++d) load(d);
   int done = 0;
-  for (; done + D <= nsteps; done += D) {
+  if constexpr (BF16) {
 #pragma unroll
-    for (int d = 0; d < D; ++d) {
-      compute(d);
-      load(d);
+    for (int d = 0; d < D; ++d) load(d);
+    for (; done + D <= nsteps; done += D) {
+#pragma unroll
+      for (int d = 0; d < D; ++d) {
+        compute(d);
+        load(d);
+      }
     }
-  }
 #pragma unroll
-  for (int d = 0; d < D; ++d)
-    if (done + d < nsteps) compute(d);
+    for (int d = 0; d < D; ++d)
+      if (done + d < nsteps) compute(d);
+  } else {
+    const int np = nsteps >> 1;
+#pragma unroll
+    for (int d = 0; d < DP; ++d) load_pair(d);
+    for (; done + DP <= np; done += DP) {
+#pragma unroll
+      for (int d = 0; d < DP; ++d) {
+        compute_pair(d);
+        load_pair(d);
+      }
+    }
+#pragma unroll
+    for (int d = 0; d < DP - 1; ++d)
+      if (done + d < np) compute_pair(d);
+  }
 
   // partial tiles of the NW waves summed in wave order; accumulator v of lane l is pixel 4 * (l / 16) + v, channel l % 16
   __syncthreads();  // the partial tiles reuse the LDS of every wave's staging buffer

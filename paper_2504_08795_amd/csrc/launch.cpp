@@ -26,7 +26,7 @@ static inline int cdiv(int a, int b) { return (a + b - 1) / b; }
 // round's worth of work.  1 = perfectly even; 98 workgroups on 96 CUs: 1.96.
 static double round_waste(int groups, int cus) { return (double)cdiv(groups, cus) * cus / groups; }
 
-static ConvPlan plan_conv_wave(int M, int N, int Kpad, int bf16, int step_align, int nominal_cus, int force_tn = 0, int force_nw = 0) {
+static ConvPlan plan_conv_wave(int M, int N, int Kpad, int bf16, int step_align, int nominal_cus, bool allow_block, int force_tn = 0, int force_nw = 0) {
   const int kNominalWaveSlots = 4 * nominal_cus;  // SIMDs of the partition size the plan is balanced for
   // Measured on a 128-CU partition (fp32, ResNet-18 shapes): the K loop itself runs near the MFMA rate; what a
   // launch pays for is its fixed cost and idle CUs.  Best found: 8 waves per workgroup splitting K, and enough
@@ -47,14 +47,19 @@ static ConvPlan plan_conv_wave(int M, int N, int Kpad, int bf16, int step_align,
     if (t2 > nominal_cus && t2 <= 2 * nominal_cus && round_waste(t2, nominal_cus) > 1.3 && round_waste(2 * t2, nominal_cus) < round_waste(t2, nominal_cus)) tn = 1;
   }
   if (force_tn) tn = force_tn;
-  // Fetching the pixel operand as coalesced rows through LDS pays where a launch is bound by its loads: every bf16 shape
-  // (+11 % on the saturated ResNet-50 set) and 32-channel fp32 tiles.  fp32 tiles of 64 channels are bound by the matrix
-  // pipe; there the extra LDS round trip and registers cost 10-25 % (measured on VGG-16's layers; still 10 % with the
-  // register count held at 128), so they stay register-fed.
-  if (step_align > 1 && !bf16 && tn == 2) step_align = 1;
-  const int tiles = cdiv(M, 32) * (nb / tn);
+  // Fetching the pixel operand as coalesced rows through LDS pays where a launch is bound by its loads.
+  const int staged = step_align > 1;
+  if (!bf16) step_align = 2;  // the fp32 kernels take K in chunks of two steps
+  // 64 x 64 tiles (conv_block_*) once they nearly fill the partition, if K is at least 256 (3136 x 128 x 256: 7.5 us against
+  // 8.8, 3072 x 64 x 576 on 64 CUs 9.9 against 12.7; but 784 x 512 x 128: 6.0 against 5.4)
+  const bool block = allow_block && !bf16 && staged && nb % 2 == 0 && cdiv(M, 64) * (nb / 2) >= nominal_cus * 3 / 4 && S >= 32;
+  if (block) tn = 2;
+  const int tiles = (block ? cdiv(M, 64) : cdiv(M, 32)) * (nb / tn);
   int nw = bf16 ? 4 : 8;  // bf16 steps are short: fewer waves to sum through LDS beat a finer K split (measured 0.4-0.8 us per layer)
   while (nw > 2 && (S / nw < 4 || tiles * nw > 8 * kNominalWaveSlots)) nw /= 2;  // >= 4 steps per wave, <= 8 waves per SIMD
+  // ... whose workgroups are the smaller the more of them a CU gets: 104 tiles on 128 CUs 41 us with 8 waves, 51 with 4 (784 x
+  // 512 x 4608); 196 tiles 46, 43 and, with 2 waves, 72 (3136 x 256 x 2304); 392 tiles 56, 47 and 43 (12544 x 128 x 1152)
+  if (block) nw = tiles > nominal_cus * 5 / 2 ? 2 : tiles > nominal_cus * 3 / 2 ? 4 : 8;
   int z = nominal_cus / tiles;
   if (z < 1) z = 1;
   const int max_by_k = S / (nw * 6) > 0 ? S / (nw * 6) : 1;
@@ -65,7 +70,7 @@ static ConvPlan plan_conv_wave(int M, int N, int Kpad, int bf16, int step_align,
     // (S / z) * tn * c cycles of MFMA time per SIMD, so a K split can even out the last round (200 tiles: z = 1 and 2
     // need the time of 2 whole tiles, z = 3 that of 5/3).  Model checked against measured VGG-16 layers (within 3 %):
     // loop time x 1.3 + a reduction pass of 3 us + its traffic at 1.5 TB/s.
-    const double cyc = bf16 ? tn * 8.0 : tn * 64.0;
+    const double cyc = block ? 96.0 : bf16 ? tn * 8.0 : (tn == 1 ? 40.0 : 64.0);
     double best = 1e30;
     for (int zz = 1; zz <= 6 && S / (nw * zz) >= 6; ++zz) {
       const double rounds = (double)cdiv(tiles * zz, nominal_cus);
@@ -86,12 +91,14 @@ static ConvPlan plan_conv_wave(int M, int N, int Kpad, int bf16, int step_align,
   const int sz = cdiv(cdiv(S, z), step_align) * step_align;
   z = cdiv(S, sz);
   pl.rows = 32;
+  pl.tm = block ? 2 : 1;
   pl.tn = tn;
   pl.nw = nw;
   pl.S = S;
   pl.sz = sz;
   pl.sw = cdiv(cdiv(sz, nw), step_align) * step_align;
   pl.step_align = step_align;
+  pl.staged = staged;
   pl.splitk = z;
   pl.tiles = tiles;
   pl.threads = nw * 64;
@@ -120,7 +127,7 @@ static ConvPlan plan_conv_wave(int M, int N, int Kpad, int bf16, int step_align,
 static ConvPlan plan_conv_wave16(int M, int N, int Kpad, int bf16, int nominal_cus, int force_tn = 0, int force_nw = 0) {
   ConvPlan pl = ConvPlan();
   const int ks = bf16 ? 32 : 16;
-  if (Kpad % ks) return pl;
+  if (Kpad % 32) return pl;  // whole steps (bf16), pairs of steps (fp32)
   const int S = Kpad / ks;
   const int nb = cdiv(N, 16), mt = cdiv(M, 16);
   // two channel blocks per wave halve the reads of the pixel operand: taken when that still gives nearly one workgroup per CU
@@ -142,12 +149,14 @@ static ConvPlan plan_conv_wave16(int M, int N, int Kpad, int bf16, int nominal_c
     return pl;
   }
   pl.rows = 16;
+  pl.tm = 1;
   pl.tn = tn;
   pl.nw = nw;
   pl.S = S;
   pl.sz = S;
-  pl.sw = cdiv(S, nw);
-  pl.step_align = 1;
+  pl.sw = bf16 ? cdiv(S, nw) : 2 * cdiv(S / 2, nw);
+  pl.step_align = bf16 ? 1 : 2;
+  pl.staged = 1;
   pl.splitk = 1;
   pl.tiles = tiles;
   pl.threads = nw * 64;
@@ -170,10 +179,10 @@ static ConvPlan plan_conv_wave16(int M, int N, int Kpad, int bf16, int nominal_c
   return pl;
 }
 
-ConvPlan plan_conv(int M, int N, int Kpad, int bf16, int step_align, int cin_stride, int nominal_cus) {
+ConvPlan plan_conv(int M, int N, int Kpad, int bf16, int step_align, int cin_stride, int nominal_cus, bool allow_block) {
   if (nominal_cus < 8) nominal_cus = 8;
   if (nominal_cus > 256) nominal_cus = 256;
-  const ConvPlan pl = plan_conv_wave(M, N, Kpad, bf16, step_align, nominal_cus);
+  const ConvPlan pl = plan_conv_wave(M, N, Kpad, bf16, step_align, nominal_cus, allow_block);
   if (pl.splitk > 1 && cin_stride > 0 && cin_stride % (bf16 ? 32 : 16) == 0) {
     const ConvPlan p16 = plan_conv_wave16(M, N, Kpad, bf16, nominal_cus);
     if (p16.kernel != K_NONE) return p16;
@@ -187,7 +196,7 @@ ConvPlan plan_conv_like(const ConvPlan& first, int M, int N, int Kpad, int bf16,
   if (nominal_cus > 256) nominal_cus = 256;
   if (first.rows == 16) return plan_conv_wave16(M, N, Kpad, bf16, nominal_cus, first.tn, first.nw);
   if (cdiv(N, 32) % first.tn != 0) return none;
-  return plan_conv_wave(M, N, Kpad, bf16, step_align, nominal_cus, first.tn, first.nw);
+  return plan_conv_wave(M, N, Kpad, bf16, step_align, nominal_cus, false, first.tn, first.nw);
 }
 
 
@@ -274,6 +283,7 @@ std::string KernelTable::resolve(const AqlRuntime& rt) {
     ingest[b] = get("daris::ingest_kernel<" + B + ">", kIngestBytes);
     egress[b] = get("daris::egress_kernel<" + B + ">", kIngestBytes);
   }
+  for (int v = 0; v < 3; ++v) block[v] = get("daris::conv_block_kernel<" + std::to_string(nw_[v]) + ">", sizeof(ConvArgs));
   cu_probe = get("daris::cu_probe_kernel", kProbeBytes);
   return missing;
 }
@@ -291,7 +301,7 @@ bool encode_conv(const KernelTable& kt, const ConvPlan& pl, const ConvArgs& a, i
   if (pl.rows == 16) {
     const int v16 = pl.kernel - (bf16 ? K_CONV16_BF16_T1W2 : K_CONV16_F32_T1W2);
     const int ks16 = bf16 ? 32 : 16;
-    if (v16 < 0 || v16 >= 6 || pl.threads != 64 * pl.nw || a.c_real > 0 || a.Cin % ks16 || a.Kpad % ks16 || pl.S * ks16 != a.Kpad) return false;
+    if (v16 < 0 || v16 >= 6 || pl.threads != 64 * pl.nw || a.c_real > 0 || a.Cin % ks16 || a.Kpad % 32 || pl.S * ks16 != a.Kpad || pl.sw % pl.step_align) return false;
     if (pl.splitk > 1 && !a.ws) return false;
     if (!push(out, kt.conv16[bf16][v16], pl.kernel, pl.grid_x, (uint32_t)pl.threads, &a, sizeof(a))) return false;
     return push_reduce(kt, pl, a, bf16, out);
@@ -300,16 +310,27 @@ bool encode_conv(const KernelTable& kt, const ConvPlan& pl, const ConvArgs& a, i
   if (variant < 0 || variant >= 6 || pl.threads != 64 * pl.nw) return false;
   // 0: a K step never straddles a filter tap; 1: general walk; 2: layer 0 reading the caller's fp32 [C][H][W] input;
   // 3: a pixel's channels are whole 64-byte rows and the plan cuts K in chunks of two steps: pixel operand through LDS
-  const int mode = a.c_real > 0 ? 2 : (conv_rows_staged(a.Cin, bf16) && pl.step_align == 2 ? 3 : (a.Cin % (bf16 ? 16 : 8) == 0 ? 0 : 1));
-  if (mode == 3 && (pl.S % 2 || pl.sz % 2 || pl.sw % 2)) return false;
+  const int mode = a.c_real > 0 ? 2 : (conv_rows_staged(a.Cin, bf16) && pl.staged ? 3 : (a.Cin % (bf16 ? 16 : 8) == 0 ? 0 : 1));
+  if ((mode == 3 || !bf16) && (pl.S % 2 || pl.sz % 2 || pl.sw % 2)) return false;
   if (mode == 2 && (a.Cin != (bf16 ? 8 : 4) || a.c_real > 4)) return false;
   if (pl.splitk > 1 && !a.ws) return false;
+  if (pl.tm == 2) {
+    // what conv_block_kernel assumes: whole 64-byte rows, K cut in chunks of two steps, one bit per filter tap, signed
+    // 32-bit byte offsets into the input and into the weights of two channel blocks
+    if (bf16 || mode != 3 || pl.tn != 2 || a.kh * a.kw > 31 || a.pad >= a.kh) return false;
+    if ((uint64_t)(a.H + a.pad) * a.W * a.Cin * 4 >= (1ull << 31) || (uint64_t)pl.S * 3072 + 12288 >= (1ull << 31)) return false;
+    ConvArgs b = a;
+    b.MT = cdiv(a.M, 64);
+    const uint32_t grid = (uint32_t)(b.xmode == 2 ? 8 * cdiv(b.MT, 8 / b.G) : b.G * b.MT);
+    if (!push(out, kt.block[variant % 3], pl.kernel, grid, (uint32_t)pl.threads, &b, sizeof(b))) return false;
+    return push_reduce(kt, pl, a, bf16, out);
+  }
   if (!push(out, kt.conv[bf16][variant][mode], pl.kernel, pl.grid_x, (uint32_t)pl.threads, &a, sizeof(a))) return false;
   return push_reduce(kt, pl, a, bf16, out);
 }
 
 bool conv_dw_fusable(const ConvPlan& pl, int bf16) {
-  if (pl.rows != 32 || pl.step_align != 2 || (!bf16 && pl.tn != 1) || (bf16 && pl.nw == 8)) return false;  // no such kernel variant
+  if (pl.rows != 32 || pl.tm != 1 || !pl.staged || (!bf16 && pl.tn != 1) || (bf16 && pl.nw == 8)) return false;  // no such kernel variant
   return pl.MT >= 96 && pl.NTn == 1;
 }
 
@@ -321,7 +342,7 @@ bool encode_conv_dw(const KernelTable& kt, const ConvPlan& pl, const ConvArgs& a
   // what the kernel's producer assumes: a 1x1 / stride 1 / unpadded convolution over whole 64-byte rows, K cut in chunks of two steps,
   // a depthwise input that maps onto the convolution's pixels, and offsets that fit 32 bits
   if (a.kh != 1 || a.kw != 1 || a.stride != 1 || a.pad != 0 || a.c_real > 0 || a.Kpad != a.Cin || a.H != a.Ho || a.W != a.Wo) return false;
-  if (!conv_rows_staged(a.Cin, bf16) || pl.step_align != 2 || pl.S % 2 || pl.sz % 2 || pl.sw % 2 || a.Cin < (bf16 ? 32 : 16)) return false;
+  if (!conv_rows_staged(a.Cin, bf16) || !pl.staged || pl.S % 2 || pl.sz % 2 || pl.sw % 2 || a.Cin < (bf16 ? 32 : 16)) return false;
   if (!d.w || !d.bias || (d.stride != 1 && d.stride != 2) || (d.H + 2 - 3) / d.stride + 1 != a.H || (d.W + 2 - 3) / d.stride + 1 != a.W) return false;
   if ((uint64_t)d.H * (uint64_t)d.W * (uint64_t)a.Cin >= (1ull << 31)) return false;
   if (pl.splitk > 1 && !a.ws) return false;
@@ -339,7 +360,7 @@ bool encode_conv_pair(const KernelTable& kt, const ConvPlan& pl0, const ConvArgs
     const int ks16 = bf16 ? 32 : 16;
     const int v16 = pl0.kernel - (bf16 ? K_CONV16_BF16_T1W2 : K_CONV16_F32_T1W2);
     if (pl1.rows != 16 || pl0.kernel != pl1.kernel || v16 < 0 || v16 >= 6 || pl0.splitk != 1 || pl1.splitk != 1 || a0.c_real > 0 || a1.c_real > 0 ||
-        a0.Cin % ks16 || a1.Cin % ks16 || pl0.S * ks16 != a0.Kpad || pl1.S * ks16 != a1.Kpad)
+        a0.Cin % ks16 || a1.Cin % ks16 || a0.Kpad % 32 || a1.Kpad % 32 || pl0.sw % pl0.step_align || pl1.sw % pl1.step_align || pl0.S * ks16 != a0.Kpad || pl1.S * ks16 != a1.Kpad)
       return false;
     PairArgs pa;
     std::memset(&pa, 0, sizeof(pa));
@@ -350,9 +371,9 @@ bool encode_conv_pair(const KernelTable& kt, const ConvPlan& pl0, const ConvArgs
   }
   const int ks = bf16 ? 16 : 8;
   const bool aligned = a0.Cin % ks == 0;
-  if (pl0.kernel != pl1.kernel || pl0.rows != 32 || aligned != (a1.Cin % ks == 0) || pl1.splitk != 1 || a0.c_real > 0 || a1.c_real > 0) return false;
-  const bool staged = conv_rows_staged(a0.Cin, bf16) && conv_rows_staged(a1.Cin, bf16) && pl0.step_align == 2 && pl1.step_align == 2;
-  if (staged && (pl0.S % 2 || pl0.sz % 2 || pl0.sw % 2 || pl1.S % 2 || pl1.sz % 2 || pl1.sw % 2)) return false;
+  if (pl0.kernel != pl1.kernel || pl0.rows != 32 || pl0.tm != 1 || pl1.tm != 1 || aligned != (a1.Cin % ks == 0) || pl1.splitk != 1 || a0.c_real > 0 || a1.c_real > 0) return false;
+  const bool staged = conv_rows_staged(a0.Cin, bf16) && conv_rows_staged(a1.Cin, bf16) && pl0.staged && pl1.staged;
+  if ((staged || !bf16) && (pl0.S % 2 || pl0.sz % 2 || pl0.sw % 2 || pl1.S % 2 || pl1.sz % 2 || pl1.sw % 2)) return false;
   const int variant = pl0.kernel - (bf16 ? K_CONVW_BF16_T1W2 : K_CONVW_F32_T1W2);
   if (variant < 0 || variant >= 6 || (pl0.splitk > 1 && !a0.ws)) return false;
   PairArgs pa;

@@ -1,6 +1,7 @@
 #include "net_plan.h"
 
 #include <algorithm>
+#include <cmath>
 #include <cstdlib>
 #include <cstring>
 #include <limits>
@@ -15,6 +16,19 @@ uint16_t host_f32_to_bf16(float f) {
   if ((u & 0x7fffffffu) > 0x7f800000u) return (uint16_t)((u >> 16) | 0x40u);  // NaN
   u += 0x7fffu + ((u >> 16) & 1u);                                           // nearest, ties to even
   return (uint16_t)(u >> 16);
+}
+
+// f as the sum of three bf16 numbers, exact for every finite f whose third part is no denormal.
+static void split_bf16(float f, uint16_t out[3]) {
+  for (int p = 0; p < 3; ++p) {
+    uint16_t h = host_f32_to_bf16(f);
+    if ((h & 0x7fffu) == 0x7f80u && std::isfinite(f)) h -= 1;  // rounding up would overflow: the largest finite number
+    const uint32_t u = (uint32_t)h << 16;
+    float v;
+    std::memcpy(&v, &u, 4);
+    out[p] = h;
+    f = std::isfinite(v) ? f - v : 0.f;
+  }
 }
 
 std::string build_plan(const daris_dnn& dnn, bool keep_activations, bool pair_launches, bool fuse_ingest, bool staged_rows, bool small_tiles, bool fuse_dw,
@@ -64,7 +78,7 @@ std::string build_plan(const daris_dnn& dnn, bool keep_activations, bool pair_la
         L.macs = (int64_t)o.H * o.W * d.c_out * (d.c_in / d.groups) * d.k * d.k;
         if (!L.depthwise) {
           L.K = d.k * d.k * in.Cs;
-          L.Kpad = round_up(L.K, 2 * vec);  // whole K steps of the convolution kernel (two 16-byte vectors per pixel)
+          L.Kpad = round_up(L.K, 16);  // what one matrix instruction takes: one K step (bf16), two (fp32)
           // the kernels divide pixel and k indices by Wo, Cin and kw with 32-bit multipliers: operands must stay small
           if ((uint64_t)(o.H * (uint64_t)o.W + 64) * (uint64_t)o.W >= (1ull << 32) || (uint64_t)(L.Kpad + 64) * (uint64_t)in.Cs >= (1ull << 32))
             return "layer " + std::to_string(l) + ": tensor too large for the kernels' index arithmetic";
@@ -121,9 +135,18 @@ std::string build_plan(const daris_dnn& dnn, bool keep_activations, bool pair_la
     if (A.in_t != B.in_t || B.res_t == l + 1) continue;
     LayerPlan& heavy = A.macs > B.macs ? A : B;
     LayerPlan& light = A.macs > B.macs ? B : A;
+    const ConvPlan own = heavy.cp;
+    const int sa = staged_rows && conv_rows_staged(net.tensor(heavy.in_t).Cs, net.bf16) ? 2 : 1;
+    if (heavy.cp.tm == 2)
+      heavy.cp = plan_conv(heavy.out.H * heavy.out.W, heavy.out.Cs, heavy.Kpad, net.bf16, sa, small_tiles ? net.tensor(heavy.in_t).Cs : 0, plan_cus, false);
     const ConvPlan like = plan_conv_like(heavy.cp, light.out.H * light.out.W, light.out.Cs, light.Kpad, net.bf16,
                                          staged_rows && conv_rows_staged(net.tensor(light.in_t).Cs, net.bf16) ? 2 : 1, plan_cus);
-    if (like.kernel == K_NONE) continue;
+    if (like.kernel == K_NONE) {
+      heavy.cp = own;
+      continue;
+    }
+    heavy.kernel_id = heavy.cp.kernel;
+    net.ws_bytes = std::max(net.ws_bytes, heavy.cp.ws_bytes);
     light.cp = like;
     light.kernel_id = like.kernel;
     A.pair_with = l + 1;
@@ -142,7 +165,8 @@ std::string build_plan(const daris_dnn& dnn, bool keep_activations, bool pair_la
       if (net.layers[q].in_t == l + 1 || net.layers[q].res_t == l + 1) only_reader = false;
     if (!only_reader || !conv_rows_staged(A.out.Cs, net.bf16)) continue;
     ConvPlan cp = B.cp;
-    if (cp.rows != 32) cp = plan_conv(B.out.H * B.out.W, B.out.Cs, B.Kpad, net.bf16, 2, 0, plan_cus);  // the fused producer exists for 32-pixel tiles
+    if (cp.rows != 32 || cp.tm != 1)  // the fused producer exists for 32-pixel tiles
+      cp = plan_conv(B.out.H * B.out.W, B.out.Cs, B.Kpad, net.bf16, 2, 0, plan_cus, false);
     if (!conv_dw_fusable(cp, net.bf16)) continue;  // the separate launch is faster (or no such kernel variant)
     B.cp = cp;
     B.kernel_id = cp.kernel;
@@ -272,6 +296,27 @@ void pack_conv(const NetPlan& net, const LayerPlan& L, const float* w, const flo
     wp->assign((size_t)kk * in.Cs * es, 0);
     for (int c = 0; c < d.c_out; ++c)
       for (int t = 0; t < kk; ++t) put<float>(wp, (size_t)t * in.Cs + c, w[(size_t)c * kk + t], bf);
+    return;
+  }
+  if (!bf) {
+    // fp32: three bf16 parts per weight (see split8 in kernels.hip), [channel block of R][chunk][part][lane = i + R q][8],
+    // element e of lane (i, q) in chunk s is W[n = R nb + i][k = s * CK + 8 q + e]; a chunk is what one matrix instruction
+    // takes, CK = 16 (R = 32) or 32 (R = 16)
+    const int R = L.cp.rows, ck = R == 16 ? 32 : 16, nch = L.Kpad / ck;
+    const int nblocks = (L.out.Cs + R - 1) / R;
+    const int nb_alloc = (nblocks + L.cp.tn - 1) / L.cp.tn * L.cp.tn;
+    wp->assign((size_t)nb_alloc * nch * 3 * 1024 + 12 * 1024, 0);  // + slack for the pipeline's refills past the last chunk
+    uint16_t* out = reinterpret_cast<uint16_t*>(wp->data());
+    for (int o = 0; o < d.c_out; ++o)
+      for (int ci = 0; ci < d.c_in; ++ci)
+        for (int t = 0; t < kk; ++t) {
+          const int k = t * in.Cs + ci;
+          const int s = k / ck, q = (k % ck) / 8, e = k % 8;
+          const size_t at = ((size_t)(o / R) * nch + s) * 3 * 512 + (size_t)(o % R + R * q) * 8 + e;
+          uint16_t part[3];
+          split_bf16(w[((size_t)o * d.c_in + ci) * kk + t], part);
+          for (int p = 0; p < 3; ++p) out[at + (size_t)p * 512] = part[p];
+        }
     return;
   }
   if (L.cp.rows == 16) {

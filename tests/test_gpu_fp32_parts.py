@@ -1,0 +1,56 @@
+"""fp32 convolutions whose products run on the bf16 matrix instructions in three parts per operand: as exact as fp32
+arithmetic against float64, over the whole exponent range in which the third part is representable; and the kernel that
+takes 64 x 64 tiles per wave at the edges of its tiles, taps, K slices and wave counts."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2504_08795_amd as D
+import workloads as wl
+from gpu_helpers import GpuNet
+
+pytestmark = pytest.mark.gpu
+N = wl.nets
+
+
+def _conv(cin, h, w, cout, k, s, p, scale_x=1.0, scale_w=1.0, plan_cus=0, seed=3):
+    rng = np.random.default_rng(seed)
+    L = [N.Layer(op=N.OP_CONV, c_in=cin, c_out=cout, k=k, stride=s, pad=p, act=0, in_from=-1)]
+    wt = (rng.normal(0, np.sqrt(2.0 / (cin * k * k)), (cout, cin, k, k)) * scale_w).astype(np.float32)
+    x = (rng.normal(0, 1, (cin, h, w)) * scale_x).astype(np.float32)
+    b = (rng.normal(0, 0.3, cout) * scale_x * scale_w).astype(np.float32)
+    with GpuNet(L, [(wt, b)], (cin, h, w), "fp32", plan_cus=plan_cus) as g:
+        got = g.forward(x).astype(np.float64)
+        plan = D.daris_get_launch_plan(g.task, 0)
+    want = torch.nn.functional.conv2d(torch.from_numpy(x).double()[None], torch.from_numpy(wt).double(), torch.from_numpy(b).double(),
+                                      stride=s, padding=p).numpy().ravel()
+    return float(np.linalg.norm(got - want) / np.linalg.norm(want)), plan
+
+
+@pytest.mark.parametrize("scale_x,scale_w", [(1.0, 1.0), (1e30, 1e-3), (1e-20, 1e-8), (3e4, 1e33)])
+@pytest.mark.parametrize("cin,h,w,cout,k", [(512, 7, 7, 512, 3), (128, 28, 28, 128, 3), (24, 13, 13, 40, 1), (4, 9, 9, 8, 3)])
+def test_three_part_products_are_fp32_products(cin, h, w, cout, k, scale_x, scale_w):
+    err, _ = _conv(cin, h, w, cout, k, 1, k // 2, scale_x, scale_w)
+    assert err <= 5e-7, err       # sqrt(4608) * 2^-25 = 2e-6 is what plain fp32 sums may show; the fp32 instruction: 4.3e-7
+
+
+# (cin, h, w, cout, k, stride, pad, plan_cus): what it is about
+BLOCK_CASES = [
+    (64, 56, 56, 64, 3, 1, 1, 32),     # M = 3136 = 49 tiles of 64: 49 workgroups of 4 waves
+    (32, 41, 43, 64, 3, 1, 1, 32),     # ragged last tile (1763 = 27 * 64 + 35), K = 288
+    (64, 48, 47, 128, 3, 2, 1, 8),     # stride 2, many tiles for few CUs: 2 waves
+    (256, 23, 29, 64, 1, 1, 0, 8),     # 1x1: one tap, K = 256, the smallest; last tile of 27 pixels
+    (16, 33, 33, 192, 5, 1, 2, 32),    # 5x5 with 25 taps, one chunk per tap, three channel tiles
+    (48, 21, 20, 64, 3, 1, 0, 8),      # no padding, three chunks per tap
+    (512, 28, 28, 512, 3, 1, 1, 128),  # 104 workgroups of 8 waves
+    (512, 28, 28, 512, 3, 1, 1, 48),   # K split over workgroups as well
+    (64, 3, 200, 64, 3, 1, 1, 8),      # wide and flat: every row touches the border
+]
+
+
+@pytest.mark.parametrize("case", BLOCK_CASES, ids=lambda c: "x".join(map(str, c)))
+def test_block_tiles(case):
+    cin, h, w, cout, k, s, p, cus = case
+    err, plan = _conv(cin, h, w, cout, k, s, p, plan_cus=cus)
+    assert plan["tn"] == 2 and (plan["M"] + 63) // 64 * plan["NTn"] >= cus * 3 // 4      # the case runs the kernel it names
+    assert err <= 5e-7, err
