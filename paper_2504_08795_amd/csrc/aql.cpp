@@ -306,10 +306,11 @@ void AqlQueue::write_packet(uint64_t idx, const AqlKernel& k, uint32_t groups, u
   p->kernarg_address = const_cast<void*>(kernarg);
   p->reserved2 = 0;
   p->completion_signal = completion;
-  // in order (barrier bit); acquire: what earlier packets wrote is visible to this kernel; release: what it writes is
-  // visible to the next packet of any queue of the device, or (system scope) to the host as well
+  // in order (barrier bit); acquire: what earlier packets wrote is visible to this kernel; release: only where the host, a
+  // copy engine or another queue is to see what this kernel wrote -- the kernels write their results through to where the
+  // whole device sees them and wait for it before they end, so the next packet of this queue needs no fence
   const unsigned acq = (flags & kAcquireSystem) ? HSA_FENCE_SCOPE_SYSTEM : HSA_FENCE_SCOPE_AGENT;
-  const unsigned rel = (flags & kReleaseSystem) ? HSA_FENCE_SCOPE_SYSTEM : HSA_FENCE_SCOPE_AGENT;
+  const unsigned rel = (flags & kReleaseSystem) ? HSA_FENCE_SCOPE_SYSTEM : (flags & kReleaseDevice) ? HSA_FENCE_SCOPE_AGENT : HSA_FENCE_SCOPE_NONE;
   const uint16_t header = (uint16_t)((HSA_PACKET_TYPE_KERNEL_DISPATCH << HSA_PACKET_HEADER_TYPE) | (1u << HSA_PACKET_HEADER_BARRIER) |
                                      (acq << HSA_PACKET_HEADER_SCACQUIRE_FENCE_SCOPE) | (rel << HSA_PACKET_HEADER_SCRELEASE_FENCE_SCOPE));
   __atomic_store_n((uint16_t*)p, header, __ATOMIC_RELEASE);

@@ -76,7 +76,8 @@ class AqlQueue {
   bool drain(hsa_signal_t s, int64_t limit_ns);
 
   enum : unsigned {
-    kReleaseSystem = 1,  // when the kernel completes its writes are visible to the host too (default: to this device)
+    kReleaseSystem = 1,  // when the kernel completes its writes are visible to the host too
+    kReleaseDevice = 4,  // ... to every queue of this device (default: to the next packet of this queue, see write_packet)
     kAcquireSystem = 2,  // the kernel sees what the host, copy engines and other devices wrote before (default: this device)
   };
   // Appends one kernel: `groups` workgroups of `threads` threads whose argument block already lies in device memory at

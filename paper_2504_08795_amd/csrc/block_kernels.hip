@@ -242,7 +242,7 @@ __global__ __launch_bounds__(NW * 64) void conv_block_kernel(const ConvArgs p) {
           val[0] += t.x; val[1] += t.y; val[2] += t.z; val[3] += t.w;
         }
         if (!own_epilogue) {  // partial sums of this K slice; splitk_reduce_kernel finishes the layer
-          *(float4*)(p.ws + (size_t)zi * p.M * p.Cout + o) = make_float4(val[0], val[1], val[2], val[3]);
+          put(p.ws + (size_t)zi * p.M * p.Cout + o, make_float4(val[0], val[1], val[2], val[3]));
         } else {
           val[0] += bias.x; val[1] += bias.y; val[2] += bias.z; val[3] += bias.w;
           if (p.res) {
@@ -250,11 +250,12 @@ __global__ __launch_bounds__(NW * 64) void conv_block_kernel(const ConvArgs p) {
           }
   #pragma unroll
           for (int i = 0; i < 4; ++i) val[i] = apply_act(val[i], p.act);
-          *(float4*)((float*)p.y + o) = make_float4(val[0], val[1], val[2], val[3]);
+          put((float*)p.y + o, make_float4(val[0], val[1], val[2], val[3]));
         }
       }
     }
   }
+  puts_done();
 }
 
 template __global__ void conv_block_kernel<2>(const ConvArgs);

@@ -433,7 +433,7 @@ const char* enqueue_range(TaskRt& T, int lo, int hi, const JobIo& io, StreamRt& 
     if (i == hi - 1 && o.done.handle) sig = o.done;
     else if (o.sample && i < hi - 1) sig = S.tsig[i - lo];
     else if (i == lo) sig = o.first;
-    const unsigned fl = ((i == hi - 1 && o.release_system) ? AqlQueue::kReleaseSystem : 0u) | ((i == lo && o.acquire_system) ? AqlQueue::kAcquireSystem : 0u);
+    const unsigned fl = (i < hi - 1 ? 0u : o.release_system ? AqlQueue::kReleaseSystem : AqlQueue::kReleaseDevice) | ((i == lo && o.acquire_system) ? AqlQueue::kAcquireSystem : 0u);
     const void* dev = r.dev;
     const bool is_in = i == T.in_launch, is_out = i == T.out_launch;
     if (is_in || is_out) {

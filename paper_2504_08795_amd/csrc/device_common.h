@@ -34,11 +34,24 @@ __device__ __forceinline__ float load_elem(const void* p, size_t i) {
   return ((const float*)p)[i];
 }
 
-template <bool BF16>
-__device__ __forceinline__ void store_elem(void* p, size_t i, float v) {
-  if (BF16) ((uint16_t*)p)[i] = (uint16_t)f32_to_bf16_bits(v);
-  else ((float*)p)[i] = v;
+// What a kernel leaves for the next one is written through to where all eight XCDs see it, and every wave waits for its
+// stores before it ends.  The packets of a stage therefore need no release fence (a write-back of eight L2s after every
+// kernel: 0.5 us of the 5 us that a launch of a small layer takes).
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ void put(void* p, const uint4& v) {
+  __builtin_amdgcn_global_store_b128((u32x4 __attribute__((address_space(1)))*)p, __builtin_bit_cast(u32x4, v), "agent");
 }
+__device__ __forceinline__ void put(void* p, const float4& v) { put(p, __builtin_bit_cast(uint4, v)); }
+__device__ __forceinline__ void put(void* p, const uint2& v) {
+  __hip_atomic_store((uint64_t*)p, __builtin_bit_cast(uint64_t, v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void put(float* p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+template <bool BF16>
+__device__ __forceinline__ void put_elem(void* p, size_t i, float v) {
+  if (BF16) __hip_atomic_store((uint16_t*)p + i, (uint16_t)f32_to_bf16_bits(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  else put((float*)p + i, v);
+}
+__device__ __forceinline__ void puts_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
 // n / d for 0 <= n with n * d < 2^32, through the host-made multiplier magic = floor(2^32 / d) + 1 (0 stands for d = 1):
 // the quotient is the high word of n * magic, a handful of cycles instead of the ~40-instruction division sequence.
