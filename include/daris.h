@@ -256,9 +256,8 @@ daris_status daris_forward(daris_task t, const void* d_input, void* d_logits, da
  * captures a HIP graph, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, same kernels in the same
  * order, hence bit-identical logits; but the task's activation tensors and split-K partial sums live in a static device
  * array of 16 MiB that the library's device image brings along (every GPU the library was initialised on holds its own
- * copy until the process ends) instead of the buffers allocated at registration, and every launch's argument block goes
- * through the queue's ring of host-visible memory.  The call allocates nothing: no hipMalloc / hipFree, no pinned memory,
- * no queue or signal; the first call for a task encodes that task's launches against the array in ordinary host memory.
+ * copy until the process ends) instead of the buffers allocated at registration.  The call allocates nothing: no hipMalloc /
+ * hipFree, no pinned memory, no queue or signal (the launches are encoded against the array at registration).
  *   - The streams must exist already (daris_commit, or any execution, came first: creating them allocates);
  *     DARIS_ESTATE otherwise.
  *   - The task's activation slots plus workspace must fit the array (every configured network but VGG-16 does);

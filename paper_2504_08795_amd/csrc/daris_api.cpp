@@ -74,6 +74,15 @@ struct LaunchRt {
   double flops = 0;           // arithmetic of the layer(s) a dense-convolution launch computes, else 0
 };
 
+// A whole network as launches in execution order, encoded at registration; layer l issues launches [layer_lo[l],
+// layer_lo[l + 1]) (none for the earlier member of a launch pair).
+struct LaunchSeq {
+  std::vector<LaunchRt> launches;
+  std::vector<int> layer_lo;
+  int in_launch = -1, out_launch = -1;  // the launches that read the job's input / write its logits
+  uint32_t in_off = 0, out_off = 0;     // byte offset of that pointer inside the argument block
+};
+
 // Argument blocks of the input-reading and the logits-writing launch, one per buffer of a set of I/O buffers.
 struct IoVariants {
   char* dev = nullptr;
@@ -91,18 +100,9 @@ struct TaskRt {
   void* pool_out = nullptr;
   int32_t n_inputs = 0, n_slots = 0;
   std::unordered_map<uint32_t, JobIo> io;  // per released job
-  // the whole network as launches in execution order, encoded at registration; layer l issues launches
-  // [layer_lo[l], layer_lo[l + 1]) (none for the earlier member of a launch pair)
-  std::vector<LaunchRt> launches;
-  std::vector<int> layer_lo;
-  int in_launch = -1, out_launch = -1;  // the launches that read the job's input / write its logits
-  uint32_t in_off = 0, out_off = 0;     // byte offset of that pointer inside the argument block
+  LaunchSeq seq;                        // the network on the task's own buffers
+  LaunchSeq static_seq;                 // ... on the static device scratch (daris_forward_static); empty where it does not fit
   IoVariants pool;                      // argument blocks for the buffers of daris_task_set_io
-  // the same network encoded on the static device scratch (daris_forward_static), built at its first call; host memory only
-  std::vector<LaunchRt> static_launches;
-  std::vector<int> static_layer_lo;
-  int static_in = -1, static_out = -1;
-  uint32_t static_in_off = 0, static_out_off = 0;
   // virtual execution times: (stage, partition) -> (job_lo, values)
   std::map<std::pair<int, int>, std::pair<int64_t, std::vector<int64_t>>> vt;
   // library-driven runs
@@ -219,43 +219,35 @@ ConvArgs conv_args(TaskRt& T, int l, void* y, const std::vector<void*>& slots, f
   return a;
 }
 
-// Where the launch sequence of a network reads a job's input and writes its logits.
-struct IoLaunches {
-  int in_launch = -1, out_launch = -1;  // indices into the launch sequence
-  uint32_t in_off = 0, out_off = 0;     // byte offset of that pointer inside the argument block
-};
-
 // Encodes the whole network of T as launches in execution order, with its activation tensors in `slots` (one device
 // buffer per slot of the plan) and its split-K partial sums in `ws`; the weights must be on the device.  The two pointers
 // that change from job to job (the input of the first launch, the logits of the last) stay null in the argument blocks.
 // Returns "" or an error text.
-std::string encode_network(TaskRt& T, const std::vector<void*>& slots, float* ws, std::vector<LaunchRt>* launches, std::vector<int>* layer_lo,
-                           IoLaunches* iol) {
+std::string encode_network(TaskRt& T, const std::vector<void*>& slots, float* ws, LaunchSeq* seq) {
   NetPlan& net = T.net;
   const int n = (int)net.layers.size();
   const int bf16 = net.bf16;
   std::vector<KernelLaunch> ks;
-  launches->clear();
-  layer_lo->assign(n + 1, 0);
-  *iol = IoLaunches();
+  *seq = LaunchSeq();
+  seq->layer_lo.assign(n + 1, 0);
   auto take = [&](double flops) {
     for (size_t i = 0; i < ks.size(); ++i) {
       LaunchRt r;
       r.kl = ks[i];
       r.flops = i == 0 ? flops : 0;
-      launches->push_back(r);
+      seq->launches.push_back(r);
     }
     ks.clear();
   };
   if (!net.fuse_ingest) {
     if (!encode_ingest(g_kt, nullptr, slots[net.ingest.slot], net.ingest.C, net.ingest.Cs, net.ingest.H, net.ingest.W, bf16, &ks))
       return "input conversion launch";
-    iol->in_launch = 0;
-    iol->in_off = kIngestInputOffset;
+    seq->in_launch = 0;
+    seq->in_off = kIngestInputOffset;
     take(0);
   }
   for (int l = 0; l < n; ++l) {
-    (*layer_lo)[l] = (int)launches->size();
+    seq->layer_lo[l] = (int)seq->launches.size();
     LayerPlan& L = net.layers[l];
     const TensorInfo& in = net.tensor(L.in_t);
     const void* x = slots[in.slot];
@@ -295,8 +287,8 @@ std::string encode_network(TaskRt& T, const std::vector<void*>& slots, float* ws
             ok = L.macs >= O.macs ? encode_conv_pair(g_kt, L.cp, a, O.cp, b, bf16, &ks) : encode_conv_pair(g_kt, O.cp, b, L.cp, a, bf16, &ks);
           } else {
             if (l == 0 && net.fuse_ingest) {
-              iol->in_launch = (int)launches->size();
-              iol->in_off = kConvInputOffset;
+              seq->in_launch = (int)seq->launches.size();
+              seq->in_off = kConvInputOffset;
             }
             ok = encode_conv(g_kt, L.cp, a, bf16, &ks);
           }
@@ -316,8 +308,8 @@ std::string encode_network(TaskRt& T, const std::vector<void*>& slots, float* ws
         a.K = L.K; a.N = L.d.c_out; a.Ns = direct ? L.d.c_out : L.out.Cs;
         a.act = L.d.act; a.out_f32 = direct ? 1 : 0;
         if (direct) {
-          iol->out_launch = (int)launches->size();
-          iol->out_off = kFcOutputOffset;
+          seq->out_launch = (int)seq->launches.size();
+          seq->out_off = kFcOutputOffset;
         }
         ok = encode_fc(g_kt, a, bf16, &ks);
         break;
@@ -326,42 +318,62 @@ std::string encode_network(TaskRt& T, const std::vector<void*>& slots, float* ws
     if (!ok) return "launch of layer " + std::to_string(l) + " (" + kernel_name(L.kernel_id) + ")";
     take(flops);
   }
-  (*layer_lo)[n] = (int)launches->size();
+  seq->layer_lo[n] = (int)seq->launches.size();
   if (!net.final_direct) {
     const TensorInfo& o = net.layers[n - 1].out;
     if (!encode_egress(g_kt, slots[o.slot], nullptr, o.C, o.Cs, o.H, o.W, bf16, &ks)) return "output conversion launch";
-    iol->out_launch = (int)launches->size();
-    iol->out_off = kEgressOutputOffset;
+    seq->out_launch = (int)seq->launches.size();
+    seq->out_off = kEgressOutputOffset;
     take(0);
   }
   return "";
 }
 
-// Encodes T's network on its own buffers and uploads the argument blocks into one device buffer; a job brings its own
-// copies of the two job-dependent blocks (JobIo).  Returns "" or an error text.
+// Layout of T's network on the static device scratch: the plan's activation slots one after the other, 256 bytes apart at
+// least, then the split-K workspace.  Returns the bytes it takes; slots may be null.
+size_t static_layout(const NetPlan& net, unsigned char* base, std::vector<void*>* slots, float** ws) {
+  auto up = [](size_t v) { return (v + 255) / 256 * 256; };
+  size_t off = 0;
+  for (size_t b : net.slot_bytes) {
+    if (slots) slots->push_back(base + off);
+    off += up(b);
+  }
+  if (ws) *ws = reinterpret_cast<float*>(base + off);
+  return off + up(net.ws_bytes);
+}
+
+// Encodes T's network on its own buffers and, where it fits, on the static scratch, and uploads the argument blocks into
+// one device buffer; a job brings its own copies of the two job-dependent blocks (JobIo).  Returns "" or an error text.
 std::string build_launches(TaskRt& T) {
-  IoLaunches iol;
-  std::string err = encode_network(T, T.slots, T.ws, &T.launches, &T.layer_lo, &iol);
+  std::string err = encode_network(T, T.slots, T.ws, &T.seq);
   if (!err.empty()) return err;
-  T.in_launch = iol.in_launch;
-  T.out_launch = iol.out_launch;
-  T.in_off = iol.in_off;
-  T.out_off = iol.out_off;
+  T.static_seq = LaunchSeq();
+  unsigned char* base = static_cast<unsigned char*>(static_scratch_ptr(G->device));
+  if (base && static_layout(T.net, nullptr, nullptr, nullptr) <= (size_t)DARIS_STATIC_SCRATCH_BYTES) {
+    std::vector<void*> slots;
+    float* ws = nullptr;
+    static_layout(T.net, base, &slots, &ws);
+    err = encode_network(T, slots, ws, &T.static_seq);
+    if (!err.empty()) return err;
+  }
   // one device buffer for all argument blocks, 64 bytes apart at least
   std::vector<unsigned char> img;
   std::vector<size_t> off;
-  for (LaunchRt& r : T.launches) {
-    off.push_back(img.size());
-    img.insert(img.end(), r.kl.args, r.kl.args + r.kl.nbytes);
-    img.resize((img.size() + 63) / 64 * 64, 0);
-  }
+  for (LaunchSeq* q : {&T.seq, &T.static_seq})
+    for (LaunchRt& r : q->launches) {
+      off.push_back(img.size());
+      img.insert(img.end(), r.kl.args, r.kl.args + r.kl.nbytes);
+      img.resize((img.size() + 63) / 64 * 64, 0);
+    }
   void* dev = nullptr;
   hipError_t e = hipMalloc(&dev, img.size());
   if (e != hipSuccess) return std::string("argument buffer: ") + hipGetErrorString(e);
   T.owned.push_back(dev);
   e = hipMemcpy(dev, img.data(), img.size(), hipMemcpyHostToDevice);
   if (e != hipSuccess) return std::string("argument upload: ") + hipGetErrorString(e);
-  for (size_t i = 0; i < T.launches.size(); ++i) T.launches[i].dev = (const char*)dev + off[i];
+  size_t at = 0;
+  for (LaunchSeq* q : {&T.seq, &T.static_seq})
+    for (LaunchRt& r : q->launches) r.dev = (const char*)dev + off[at++];
   return "";
 }
 
@@ -377,22 +389,22 @@ void free_variants(IoVariants* v) {
 hipError_t build_variants(TaskRt& T, const void* in_base, int n_in, size_t in_stride, void* out_base, int n_out, size_t out_stride,
                           IoVariants* v) {
   free_variants(v);
-  if (T.in_launch < 0 || T.out_launch < 0 || T.in_launch == T.out_launch) return hipSuccess;
-  const KernelLaunch& ki = T.launches[T.in_launch].kl;
-  const KernelLaunch& ko = T.launches[T.out_launch].kl;
+  if (T.seq.in_launch < 0 || T.seq.out_launch < 0 || T.seq.in_launch == T.seq.out_launch) return hipSuccess;
+  const KernelLaunch& ki = T.seq.launches[T.seq.in_launch].kl;
+  const KernelLaunch& ko = T.seq.launches[T.seq.out_launch].kl;
   const size_t bi = (ki.nbytes + 63) / 64 * 64, bo = (ko.nbytes + 63) / 64 * 64;
   std::vector<unsigned char> img((size_t)n_in * bi + (size_t)n_out * bo, 0);
   for (int i = 0; i < n_in; ++i) {
     unsigned char* blk = img.data() + (size_t)i * bi;
     std::memcpy(blk, ki.args, ki.nbytes);
     const void* ptr = (const char*)in_base + (size_t)i * in_stride;
-    std::memcpy(blk + T.in_off, &ptr, sizeof(ptr));
+    std::memcpy(blk + T.seq.in_off, &ptr, sizeof(ptr));
   }
   for (int i = 0; i < n_out; ++i) {
     unsigned char* blk = img.data() + (size_t)n_in * bi + (size_t)i * bo;
     std::memcpy(blk, ko.args, ko.nbytes);
     void* ptr = (char*)out_base + (size_t)i * out_stride;
-    std::memcpy(blk + T.out_off, &ptr, sizeof(ptr));
+    std::memcpy(blk + T.seq.out_off, &ptr, sizeof(ptr));
   }
   hipError_t e = hipMalloc((void**)&v->dev, img.size());
   if (e != hipSuccess) {
@@ -417,9 +429,9 @@ struct EnqueueOpts {
   bool sample = false;          // every launch completes a signal of S.tsig, so that its time stamps can be read
 };
 
-// Appends launches [lo, hi) of T to S's queue (S.hw->mu held).  Returns nullptr or an error text.
-const char* enqueue_range(TaskRt& T, int lo, int hi, const JobIo& io, StreamRt& S, const EnqueueOpts& o) {
-  if (lo < 0 || hi > (int)T.launches.size() || lo >= hi) return "empty launch range";
+// Appends launches [lo, hi) of a network to S's queue (S.hw->mu held).  Returns nullptr or an error text.
+const char* enqueue_range(const LaunchSeq& q, int lo, int hi, const JobIo& io, StreamRt& S, const EnqueueOpts& o) {
+  if (lo < 0 || hi > (int)q.launches.size() || lo >= hi) return "empty launch range";
   if (o.sample) {
     while ((int)S.tsig.size() < hi - lo - 1) {
       hsa_signal_t sg = g_rt.new_signal(1);
@@ -428,14 +440,14 @@ const char* enqueue_range(TaskRt& T, int lo, int hi, const JobIo& io, StreamRt& 
     }
   }
   for (int i = lo; i < hi; ++i) {
-    const LaunchRt& r = T.launches[i];
+    const LaunchRt& r = q.launches[i];
     hsa_signal_t sig{0};
     if (i == hi - 1 && o.done.handle) sig = o.done;
     else if (o.sample && i < hi - 1) sig = S.tsig[i - lo];
     else if (i == lo) sig = o.first;
     const unsigned fl = (i < hi - 1 ? 0u : o.release_system ? AqlQueue::kReleaseSystem : AqlQueue::kReleaseDevice) | ((i == lo && o.acquire_system) ? AqlQueue::kAcquireSystem : 0u);
     const void* dev = r.dev;
-    const bool is_in = i == T.in_launch, is_out = i == T.out_launch;
+    const bool is_in = i == q.in_launch, is_out = i == q.out_launch;
     if (is_in || is_out) {
       if (is_in && !is_out && io.in_args) dev = io.in_args;
       else if (is_out && !is_in && io.out_args) dev = io.out_args;
@@ -443,8 +455,8 @@ const char* enqueue_range(TaskRt& T, int lo, int hi, const JobIo& io, StreamRt& 
         if ((is_in && !io.in) || (is_out && !io.out)) return "job without I/O buffers";
         alignas(8) unsigned char blk[sizeof(KernelLaunch::args)];
         std::memcpy(blk, r.kl.args, r.kl.nbytes);
-        if (is_in) std::memcpy(blk + T.in_off, &io.in, sizeof(void*));
-        if (is_out) std::memcpy(blk + T.out_off, &io.out, sizeof(void*));
+        if (is_in) std::memcpy(blk + q.in_off, &io.in, sizeof(void*));
+        if (is_out) std::memcpy(blk + q.out_off, &io.out, sizeof(void*));
         if (!S.hw->q.dispatch_copy(*r.kl.k, r.kl.groups, r.kl.threads, blk, r.kl.nbytes, sig, fl)) return "packet rejected";
         continue;
       }
@@ -459,8 +471,8 @@ void stage_range(const TaskRt& T, int stage, int* lo, int* hi) {
   const int n = (int)net.layers.size();
   const int first = net.stage_first[stage];
   const int end = stage + 1 < (int)net.stage_first.size() ? net.stage_first[stage + 1] : n;
-  *lo = stage == 0 ? 0 : T.layer_lo[first];
-  *hi = end == n ? (int)T.launches.size() : T.layer_lo[end];
+  *lo = stage == 0 ? 0 : T.seq.layer_lo[first];
+  *hi = end == n ? (int)T.seq.launches.size() : T.seq.layer_lo[end];
 }
 
 // Enqueues one stage of a job on S (S.hw->mu held); S.done completes with it.  Inside a job the next stage runs on this
@@ -479,7 +491,7 @@ const char* enqueue_stage(TaskRt& T, int stage, const JobIo& io, StreamRt& S, bo
   S.pend_hi = hi;
   S.pend_sample = sample;
   S.pend_prof = prof;
-  return enqueue_range(T, lo, hi, io, S, o);
+  return enqueue_range(T.seq, lo, hi, io, S, o);
 }
 
 // After S.done was seen complete: reads the time stamps the stage asked for (kernel timing into the global sums; the
@@ -493,7 +505,7 @@ int64_t finish_stage(TaskRt& T, StreamRt& S) {
     for (int i = lo; i < hi; ++i) {
       const hsa_signal_t sg = i == hi - 1 ? S.done : S.tsig[i - lo];
       if (!g_rt.dispatch_time_us(sg, &a, &b)) continue;
-      const LaunchRt& r = T.launches[i];
+      const LaunchRt& r = T.seq.launches[i];
       const int k = r.kl.kernel_id;
       if (k > K_NONE && k < K_COUNT) {
         G->tm_launches[k]++;
@@ -531,17 +543,20 @@ daris_status gpu_wait_failed(const StreamRt& S, const char* what) {
   return fail(DARIS_EHIP, "%s", buf);
 }
 
-// API thread, G->mu held: runs launches [lo, hi) of T on S and waits for them.
-daris_status run_direct(TaskRt& T, int lo, int hi, const JobIo& io, StreamRt& S) {
+// API thread, G->mu held: runs launches [lo, hi) of a network on S and waits for them.
+daris_status run_direct(const LaunchSeq& q, int lo, int hi, const JobIo& io, StreamRt& S) {
   EnqueueOpts o;
   o.done = G->util_sig;
   o.release_system = o.acquire_system = true;
   const char* err;
   {
     std::lock_guard<std::mutex> ql(S.hw->mu);
-    err = enqueue_range(T, lo, hi, io, S, o);
+    err = enqueue_range(q, lo, hi, io, S, o);
   }
-  if (err) return fail(DARIS_EHIP, "%s", err);
+  if (err) {
+    // launches that are queued already keep running on the network's buffers: the next call would race with them
+    return gpu_wait_failed(S, err);
+  }
   if (!aql_wait(G->util_sig, &S.hw->q)) return gpu_wait_failed(S, "direct execution");
   return DARIS_OK;
 }
@@ -1030,7 +1045,6 @@ daris_status daris_split_stages(daris_task t, int k) {
   }
   if (refused && !G->nodev) {
     TaskRt& T = *G->tasks[t];
-    T.static_launches.clear();
     const std::string err = build_launches(T);
     if (!err.empty()) return fail(DARIS_EHIP, "%s", err.c_str());
   }
@@ -1386,12 +1400,14 @@ daris_status daris_forward(daris_task t, const void* d_input, void* d_logits, da
   JobIo io;
   io.in = d_input;
   io.out = d_logits;
-  return run_direct(T, 0, (int)T.launches.size(), io, *G->parts[p].streams[0]);
+  return run_direct(T.seq, 0, (int)T.seq.launches.size(), io, *G->parts[p].streams[0]);
 }
 
 // For callers that cannot allocate device memory.  Nothing below calls hipMalloc, hipFree or any routine that allocates
 // device or pinned memory: the queues, signals and argument rings exist already, the network's tensors go into the static
-// device array, and each launch's argument block travels through its queue's ring of host-coherent memory.
+// device array, and the launches' argument blocks were uploaded when the task was registered (through the queue's ring of
+// host-coherent memory, as each launch once did, every kernel waits for its arguments over the bus: 317 us instead of 135
+// for ResNet-18 in bf16); only the two that name the caller's buffers travel with the call.
 daris_status daris_forward_static(daris_task t, const void* d_input, void* d_logits, daris_part p) {
   daris_status st = check_task(t);
   if (st != DARIS_OK) return st;
@@ -1403,54 +1419,16 @@ daris_status daris_forward_static(daris_task t, const void* d_input, void* d_log
   std::lock_guard<std::mutex> lk(G->mu);
   if (G->core.has_active(t)) return fail(DARIS_ESTATE, "task %d has an active job", t);
   TaskRt& T = *G->tasks[t];
-  unsigned char* base = static_cast<unsigned char*>(static_scratch_ptr(G->device));
-  if (!base) return fail(DARIS_EHIP, "the static scratch of device %d was not set up", G->device);
-  // layout: the plan's activation slots one after the other, 256 bytes apart at least, then the split-K workspace
-  const NetPlan& net = T.net;
-  auto up = [](size_t v) { return (v + 255) / 256 * 256; };
-  size_t need = up(net.ws_bytes);
-  for (size_t b : net.slot_bytes) need += up(b);
-  if (need > (size_t)DARIS_STATIC_SCRATCH_BYTES)
-    return fail(DARIS_ERANGE, "task %d needs %zu bytes of activation buffers and split-K workspace; the static scratch holds %u", t, need,
-                (unsigned)DARIS_STATIC_SCRATCH_BYTES);
-  if (T.static_launches.empty()) {
-    std::vector<void*> slots(net.slot_bytes.size());
-    size_t off = 0;
-    for (size_t i = 0; i < slots.size(); ++i) {
-      slots[i] = base + off;
-      off += up(net.slot_bytes[i]);
-    }
-    IoLaunches iol;
-    const std::string err = encode_network(T, slots, reinterpret_cast<float*>(base + off), &T.static_launches, &T.static_layer_lo, &iol);
-    if (!err.empty()) {
-      T.static_launches.clear();
-      return fail(DARIS_EHIP, "%s", err.c_str());
-    }
-    T.static_in = iol.in_launch;
-    T.static_out = iol.out_launch;
-    T.static_in_off = iol.in_off;
-    T.static_out_off = iol.out_off;
-  }
+  if (!static_scratch_ptr(G->device)) return fail(DARIS_EHIP, "the static scratch of device %d was not set up", G->device);
+  if (T.static_seq.launches.empty())
+    return fail(DARIS_ERANGE, "task %d needs %zu bytes of activation buffers and split-K workspace; the static scratch holds %u", t,
+                static_layout(T.net, nullptr, nullptr, nullptr), (unsigned)DARIS_STATIC_SCRATCH_BYTES);
   HIP_TRY(hipDeviceSynchronize());  // the caller's streams may still be writing the two buffers (see daris_task_set_io)
-  StreamRt& S = *G->parts[p].streams[0];
-  const int n = (int)T.static_launches.size();
-  {
-    std::lock_guard<std::mutex> ql(S.hw->mu);
-    for (int i = 0; i < n; ++i) {
-      const KernelLaunch& kl = T.static_launches[i].kl;
-      alignas(8) unsigned char blk[sizeof(KernelLaunch::args)];
-      std::memcpy(blk, kl.args, kl.nbytes);
-      if (i == T.static_in) std::memcpy(blk + T.static_in_off, &d_input, sizeof(void*));
-      if (i == T.static_out) std::memcpy(blk + T.static_out_off, &d_logits, sizeof(void*));
-      const unsigned fl = (i == 0 ? AqlQueue::kAcquireSystem : 0u) | (i == n - 1 ? AqlQueue::kReleaseSystem : 0u);
-      if (!S.hw->q.dispatch_copy(*kl.k, kl.groups, kl.threads, blk, kl.nbytes, i == n - 1 ? G->util_sig : hsa_signal_t{0}, fl)) {
-        // Launches already queued keep running on the static array; the next call would race with them.
-        return gpu_wait_failed(S, "daris_forward_static: packet rejected");
-      }
-    }
-  }
-  if (!aql_wait(G->util_sig, &S.hw->q)) return gpu_wait_failed(S, "daris_forward_static");
-  return DARIS_OK;
+  JobIo io;
+  io.in = d_input;
+  io.out = d_logits;
+  // (a packet that is refused leaves launches queued on the static array: run_direct fails for good then)
+  return run_direct(T.static_seq, 0, (int)T.static_seq.launches.size(), io, *G->parts[p].streams[0]);
 }
 
 daris_status daris_read_layer(daris_task t, int layer, float* host_out, int64_t cap_elems) {
@@ -1510,7 +1488,7 @@ daris_status daris_profile_layers(daris_task t, daris_part p, int reps, float* m
   daris_status result = DARIS_OK;
   std::lock_guard<std::mutex> ql(S.hw->mu);
   for (int l = 0; l < n && result == DARIS_OK; ++l) {
-    const int lo = T.layer_lo[l], hi = T.layer_lo[l + 1];
+    const int lo = T.seq.layer_lo[l], hi = T.seq.layer_lo[l + 1];
     ms_per_layer[l] = 0.f;
     if (kernel_id) kernel_id[l] = T.net.layers[l].kernel_id;
     if (flops) flops[l] = 2.0 * (double)T.net.layers[l].macs;
@@ -1524,7 +1502,7 @@ daris_status daris_profile_layers(daris_task t, daris_part p, int reps, float* m
       if (r == reps - 1) o.done = G->util_sig;
       o.acquire_system = r == -1;
       o.release_system = r == reps - 1;
-      err = enqueue_range(T, lo, hi, io, S, o);
+      err = enqueue_range(T.seq, lo, hi, io, S, o);
     }
     if (err) {
       result = fail(DARIS_EHIP, "profiling layer %d: %s", l, err);
@@ -1658,7 +1636,7 @@ daris_status daris_calibrate_afet(daris_task t, daris_part p, int reps) {
       int lo, hi;
       stage_range(T, j, &lo, &hi);
       auto t0 = std::chrono::steady_clock::now();
-      result = run_direct(T, lo, hi, io, S);
+      result = run_direct(T.seq, lo, hi, io, S);
       auto t1 = std::chrono::steady_clock::now();
       if (result != DARIS_OK) break;
       const int64_t ns = std::chrono::duration_cast<std::chrono::nanoseconds>(t1 - t0).count();
@@ -1738,7 +1716,7 @@ daris_status daris_calibrate_afet_loaded(daris_task t, daris_part p, int reps) {
         eo.done = Q.done;  // no job is active, so the stream's worker is not using its signal
         eo.acquire_system = eo.release_system = true;
         std::lock_guard<std::mutex> ql(Q.hw->mu);
-        const char* err = enqueue_range(O, 0, (int)O.launches.size(), io, Q, eo);
+        const char* err = enqueue_range(O.seq, 0, (int)O.seq.launches.size(), io, Q, eo);
         if (err) result = fail(DARIS_EHIP, "calibration load: %s", err);
         else loaded.push_back(&Q);
       }
@@ -1751,7 +1729,7 @@ daris_status daris_calibrate_afet_loaded(daris_task t, daris_part p, int reps) {
       int lo, hi;
       stage_range(T, j, &lo, &hi);
       auto t0 = std::chrono::steady_clock::now();
-      result = run_direct(T, lo, hi, io, S);
+      result = run_direct(T.seq, lo, hi, io, S);
       auto t1 = std::chrono::steady_clock::now();
       if (r > 0) sum[j] += std::chrono::duration_cast<std::chrono::nanoseconds>(t1 - t0).count();
     }
