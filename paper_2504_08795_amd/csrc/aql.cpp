@@ -57,6 +57,22 @@ hsa_status_t scan_host_pools(hsa_amd_memory_pool_t p, void* data) {
   return HSA_STATUS_SUCCESS;
 }
 
+hsa_status_t scan_device_pools(hsa_amd_memory_pool_t p, void* data) {
+  PoolScan* s = (PoolScan*)data;
+  hsa_amd_segment_t seg;
+  uint32_t flags = 0;
+  bool alloc_ok = false;
+  if (hsa_amd_memory_pool_get_info(p, HSA_AMD_MEMORY_POOL_INFO_SEGMENT, &seg) != HSA_STATUS_SUCCESS || seg != HSA_AMD_SEGMENT_GLOBAL)
+    return HSA_STATUS_SUCCESS;
+  hsa_amd_memory_pool_get_info(p, HSA_AMD_MEMORY_POOL_INFO_GLOBAL_FLAGS, &flags);
+  hsa_amd_memory_pool_get_info(p, HSA_AMD_MEMORY_POOL_INFO_RUNTIME_ALLOC_ALLOWED, &alloc_ok);
+  if ((flags & HSA_AMD_MEMORY_POOL_GLOBAL_FLAG_COARSE_GRAINED) && alloc_ok && !s->found) {
+    s->pool = p;
+    s->found = true;
+  }
+  return HSA_STATUS_SUCCESS;
+}
+
 struct SymbolScan {
   std::unordered_map<std::string, AqlKernel>* out;
   std::string error;
@@ -139,6 +155,13 @@ std::string AqlRuntime::init(int hip_device, const std::vector<Image>& images) {
     return "no host memory pool for kernel arguments";
   }
   host_pool_ = ps.pool;
+  PoolScan ds;
+  hsa_amd_agent_iterate_memory_pools(gpu_, scan_device_pools, &ds);
+  hsa_amd_hdp_flush_t hdp{};
+  if (ds.found && hsa_agent_get_info(gpu_, (hsa_agent_info_t)HSA_AMD_AGENT_INFO_HDP_FLUSH, &hdp) == HSA_STATUS_SUCCESS && hdp.HDP_MEM_FLUSH_CNTL) {
+    device_pool_ = ds.pool;
+    hdp_flush_ = hdp.HDP_MEM_FLUSH_CNTL;
+  }
   uint64_t freq = 0;
   if (hsa_system_get_info(HSA_SYSTEM_INFO_TIMESTAMP_FREQUENCY, &freq) == HSA_STATUS_SUCCESS && freq > 0) ticks_per_us_ = (double)freq / 1e6;
 
@@ -199,6 +222,29 @@ void* AqlRuntime::alloc_host_coherent(size_t bytes) {
     return nullptr;
   }
   return p;
+}
+
+void* AqlRuntime::alloc_device_for_host(size_t bytes) {
+  if (!hdp_flush_) return nullptr;
+  void* p = nullptr;
+  if (hsa_amd_memory_pool_allocate(device_pool_, bytes, 0, &p) != HSA_STATUS_SUCCESS) return nullptr;
+  hsa_amd_memory_pool_access_t access = HSA_AMD_MEMORY_POOL_ACCESS_NEVER_ALLOWED;
+  hsa_agent_t both[2] = {gpu_, cpu_};
+  if (hsa_amd_agent_memory_pool_get_info(cpu_, device_pool_, HSA_AMD_AGENT_MEMORY_POOL_INFO_ACCESS, &access) != HSA_STATUS_SUCCESS ||
+      access == HSA_AMD_MEMORY_POOL_ACCESS_NEVER_ALLOWED || hsa_amd_agents_allow_access(2, both, nullptr, p) != HSA_STATUS_SUCCESS) {
+    hsa_amd_memory_pool_free(p);
+    return nullptr;
+  }
+  return p;
+}
+
+void AqlRuntime::flush_host_writes(const void* last) const {
+  // The writes leave the write-combining buffers, then the device's host data path; a read over the link cannot overtake
+  // them, so once it has returned they are where the device reads.  (About 1 us, half of what the kernel would wait for
+  // arguments in host memory; without the read the order of writes and doorbell inside the device would be an assumption.)
+  __builtin_ia32_sfence();
+  __atomic_store_n(hdp_flush_, 1u, __ATOMIC_RELEASE);
+  (void)*(const volatile uint32_t*)last;
 }
 
 void AqlRuntime::free_mem(void* p) {
@@ -270,7 +316,9 @@ std::string AqlQueue::create(AqlRuntime* rt, const uint32_t mask[8]) {
     destroy();
     return hsa_err("hsa_amd_queue_cu_set_mask", st);
   }
-  ring_ = (char*)rt->alloc_host_coherent((size_t)kSlots * kSlotBytes);
+  ring_ = (char*)rt->alloc_device_for_host((size_t)kSlots * kSlotBytes);
+  ring_on_device_ = ring_ != nullptr;
+  if (!ring_) ring_ = (char*)rt->alloc_host_coherent((size_t)kSlots * kSlotBytes);
   if (!ring_) {
     destroy();
     return "argument ring allocation failed";
@@ -354,6 +402,10 @@ bool AqlQueue::dispatch_copy(const AqlKernel& k, uint32_t groups, uint32_t threa
   if (idx == kNoSlot) return false;
   char* slot = ring_ + (size_t)(idx & (kSlots - 1)) * kSlotBytes;
   std::memcpy(slot, args, bytes);
+  if (ring_on_device_) {
+    rt_->flush_host_writes(slot + (bytes - 1) / 4 * 4);
+    flags |= kAcquireSystem;  // the device's caches may hold the slot's last contents
+  }
   write_packet(idx, k, groups, threads, slot, completion, flags);
   return true;
 }

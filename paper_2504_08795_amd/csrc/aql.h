@@ -46,6 +46,10 @@ class AqlRuntime {
   hsa_agent_t gpu() const { return gpu_; }
   // Host memory the GPU reads coherently (argument rings of dispatch_copy).
   void* alloc_host_coherent(size_t bytes);
+  // Device memory that the host writes through the PCIe aperture, or nullptr where it cannot; flush_host_writes() with the
+  // address of the last word written, before the doorbell.
+  void* alloc_device_for_host(size_t bytes);
+  void flush_host_writes(const void* last) const;
   void free_mem(void* p);
   hsa_signal_t new_signal(int64_t initial);
   void free_signal(hsa_signal_t s);
@@ -55,7 +59,8 @@ class AqlRuntime {
  private:
   bool ready_ = false;
   hsa_agent_t gpu_{}, cpu_{};
-  hsa_amd_memory_pool_t host_pool_{};
+  hsa_amd_memory_pool_t host_pool_{}, device_pool_{};
+  uint32_t* hdp_flush_ = nullptr;  // null: no device memory for the host
   hsa_executable_t exec_{};
   std::vector<hsa_code_object_reader_t> readers_;
   std::vector<std::vector<char>> images_;
@@ -86,9 +91,9 @@ class AqlQueue {
   // not 0) is decremented.  One producer at a time.
   bool dispatch(const AqlKernel& k, uint32_t groups, uint32_t threads, const void* kernarg, hsa_signal_t completion = hsa_signal_t{0},
                 unsigned flags = 0);
-  // The same for arguments that exist only now (a caller's buffer address): they are copied into a ring of
-  // host-coherent memory, which the kernel reads over the bus (slower for the kernel than device memory).  Returns
-  // false if `bytes` is not what the kernel expects.
+  // The same for arguments that exist only now (a caller's buffer address): they are copied into a ring of device memory
+  // that the host writes through the PCIe aperture, or, where the host has no access to device memory, of host-coherent
+  // memory (the kernel then waits for its arguments over the bus).  Returns false if `bytes` is not what the kernel expects.
   bool dispatch_copy(const AqlKernel& k, uint32_t groups, uint32_t threads, const void* args, uint32_t bytes,
                      hsa_signal_t completion = hsa_signal_t{0}, unsigned flags = 0);
   // Time stamps for dispatches that carry a completion signal.
@@ -105,7 +110,8 @@ class AqlQueue {
                     unsigned flags);
   AqlRuntime* rt_ = nullptr;
   hsa_queue_t* q_ = nullptr;
-  char* ring_ = nullptr;  // host-coherent argument slots
+  char* ring_ = nullptr;  // argument slots of dispatch_copy
+  bool ring_on_device_ = false;
   std::atomic<bool> dead_{false};
 };
 
