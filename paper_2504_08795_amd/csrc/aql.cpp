@@ -354,7 +354,9 @@ void AqlQueue::write_packet(uint64_t idx, const AqlKernel& k, uint32_t groups, u
   p->kernarg_address = const_cast<void*>(kernarg);
   p->reserved2 = 0;
   p->completion_signal = completion;
-  // in order (barrier bit); acquire: what earlier packets wrote is visible to this kernel; release: only where the host, a
+  // in order (barrier bit); acquire: at device scope every cache above the memory drops what it holds, so the kernel sees
+  // what earlier packets, other XCDs, copy engines and the host (through the PCIe aperture) have written into this
+  // device's memory -- system scope, for memory elsewhere, takes 2 us longer; release: only where the host, a
   // copy engine or another queue is to see what this kernel wrote -- the kernels write their results through to where the
   // whole device sees them and wait for it before they end, so the next packet of this queue needs no fence
   const unsigned acq = (flags & kAcquireSystem) ? HSA_FENCE_SCOPE_SYSTEM : HSA_FENCE_SCOPE_AGENT;
@@ -404,7 +406,6 @@ bool AqlQueue::dispatch_copy(const AqlKernel& k, uint32_t groups, uint32_t threa
   std::memcpy(slot, args, bytes);
   if (ring_on_device_) {
     rt_->flush_host_writes(slot + (bytes - 1) / 4 * 4);
-    flags |= kAcquireSystem;  // the device's caches may hold the slot's last contents
   }
   write_packet(idx, k, groups, threads, slot, completion, flags);
   return true;

@@ -424,8 +424,9 @@ hipError_t build_variants(TaskRt& T, const void* in_base, int n_in, size_t in_st
 struct EnqueueOpts {
   hsa_signal_t done{0};   // completes with the last launch
   hsa_signal_t first{0};  // completes with the first launch (ignored when that launch carries `done`, or when sampling)
-  bool release_system = false;  // the last launch makes its writes visible to the host and to other processes' copies
-  bool acquire_system = false;  // the first launch sees what copies and other queues of the system wrote before
+  // to whom the last launch makes everything written so far visible: the host and copy engines (kReleaseSystem), every
+  // queue of the device (kReleaseDevice), or only this queue (0)
+  unsigned release = AqlQueue::kReleaseDevice;
   bool sample = false;          // every launch completes a signal of S.tsig, so that its time stamps can be read
 };
 
@@ -445,7 +446,7 @@ const char* enqueue_range(const LaunchSeq& q, int lo, int hi, const JobIo& io, S
     if (i == hi - 1 && o.done.handle) sig = o.done;
     else if (o.sample && i < hi - 1) sig = S.tsig[i - lo];
     else if (i == lo) sig = o.first;
-    const unsigned fl = (i < hi - 1 ? 0u : o.release_system ? AqlQueue::kReleaseSystem : AqlQueue::kReleaseDevice) | ((i == lo && o.acquire_system) ? AqlQueue::kAcquireSystem : 0u);
+    const unsigned fl = i < hi - 1 ? 0u : o.release;
     const void* dev = r.dev;
     const bool is_in = i == q.in_launch, is_out = i == q.out_launch;
     if (is_in || is_out) {
@@ -484,8 +485,7 @@ const char* enqueue_stage(TaskRt& T, int stage, const JobIo& io, StreamRt& S, bo
   EnqueueOpts o;
   o.done = S.done;
   o.first = prof ? S.begin : hsa_signal_t{0};
-  o.release_system = stage + 1 == (int)T.net.stage_first.size();
-  o.acquire_system = stage == 0;
+  if (stage + 1 == (int)T.net.stage_first.size()) o.release = AqlQueue::kReleaseSystem;
   o.sample = sample;
   S.pend_lo = lo;
   S.pend_hi = hi;
@@ -547,7 +547,7 @@ daris_status gpu_wait_failed(const StreamRt& S, const char* what) {
 daris_status run_direct(const LaunchSeq& q, int lo, int hi, const JobIo& io, StreamRt& S) {
   EnqueueOpts o;
   o.done = G->util_sig;
-  o.release_system = o.acquire_system = true;
+  o.release = AqlQueue::kReleaseSystem;
   const char* err;
   {
     std::lock_guard<std::mutex> ql(S.hw->mu);
@@ -1500,8 +1500,7 @@ daris_status daris_profile_layers(daris_task t, daris_part p, int reps, float* m
       EnqueueOpts o;
       if (r == 0 && !one) o.first = first;
       if (r == reps - 1) o.done = G->util_sig;
-      o.acquire_system = r == -1;
-      o.release_system = r == reps - 1;
+      o.release = r == reps - 1 ? AqlQueue::kReleaseSystem : 0u;
       err = enqueue_range(T.seq, lo, hi, io, S, o);
     }
     if (err) {
@@ -1714,7 +1713,7 @@ daris_status daris_calibrate_afet_loaded(daris_task t, daris_part p, int reps) {
         io.out = out[o];
         EnqueueOpts eo;
         eo.done = Q.done;  // no job is active, so the stream's worker is not using its signal
-        eo.acquire_system = eo.release_system = true;
+        eo.release = AqlQueue::kReleaseSystem;
         std::lock_guard<std::mutex> ql(Q.hw->mu);
         const char* err = enqueue_range(O.seq, 0, (int)O.seq.launches.size(), io, Q, eo);
         if (err) result = fail(DARIS_EHIP, "calibration load: %s", err);
