@@ -1,6 +1,7 @@
 // Implicit-GEMM convolution of large fp32 layers on gfx950: 64 pixels x 64 channels per wave.
 #include <hip/hip_runtime.h>
 
+#include "layer_bodies.h"
 #include "device_common.h"
 #include "kernels.h"
 
@@ -19,7 +20,8 @@ namespace daris {
 // weights are in flight.  The four 32 x 32 blocks of the partial tiles are then summed in wave order, NT / 256 blocks at
 // a time, which bounds the LDS at 16 KB per four waves, and finished by the same epilogue.
 template <int NW>
-__global__ __launch_bounds__(NW * 64) void conv_block_kernel(const ConvArgs p) {
+__global__ __launch_bounds__(NW * 64) void conv_block_kernel(const ConvArgs) {
+  const ConvArgs p = conv_args_at((ConstPtr)__builtin_amdgcn_kernarg_segment_ptr());
   constexpr int ES = 4;
   constexpr int KS = 8;                      // k per step of the plan; a chunk is two steps
   constexpr int NT = NW * 64;
@@ -35,24 +37,9 @@ __global__ __launch_bounds__(NW * 64) void conv_block_kernel(const ConvArgs p) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int li = lane & 31, lh = lane >> 5;
-  const int L = (int)blockIdx.x;
-  int mt, g;  // workgroup -> (pixel tile, weight group), tiles that read the same weights on one XCD (see conv_wave_body)
-  {
-    const int x = L & 7, q = L >> 3;
-    if (p.xmode == 1) {
-      g = (q / p.MT) * 8 + x;
-      mt = q % p.MT;
-    } else if (p.xmode == 2) {
-      const int r = 8 / p.G;
-      g = x / r;
-      mt = q * r + (x % r);
-    } else {
-      g = L / p.MT;
-      mt = L % p.MT;
-    }
-    if (g >= p.G || mt >= p.MT) return;
-  }
-  const int zi = g / p.NTn;
+  int mt, g;
+  if (!conv_tile_of(p, (int)blockIdx.x, &mt, &g)) return;
+  const int zi = p.splitk == 1 ? 0 : g / p.NTn;
   const int m0 = mt * 64, nb0 = (g - zi * p.NTn) * 2;
   const int s_wg0 = zi * p.sz;
   const int s_wg1 = min(s_wg0 + p.sz, p.S);

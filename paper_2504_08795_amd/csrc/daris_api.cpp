@@ -207,10 +207,10 @@ ConvArgs conv_args(TaskRt& T, int l, void* y, const std::vector<void*>& slots, f
   a.res = L.res_t >= 0 ? slots[net.tensor(L.res_t).slot] : nullptr;
   a.H = in.H; a.W = in.W; a.Cin = in.Cs; a.Ho = L.out.H; a.Wo = L.out.W; a.Cout = L.out.Cs;
   a.kh = a.kw = L.d.k; a.stride = L.d.stride; a.pad = L.d.pad;
-  a.K = L.K; a.Kpad = L.Kpad; a.M = L.out.H * L.out.W; a.act = L.d.act;
+  a.Kpad = L.Kpad; a.M = L.out.H * L.out.W; a.act = L.d.act;
   a.splitk = L.cp.splitk; a.S = L.cp.S; a.sz = L.cp.sz; a.sw = L.cp.sw;
   a.MT = L.cp.MT; a.NTn = L.cp.NTn; a.G = L.cp.G; a.xmode = L.cp.xmode;
-  a.mg_wo = div_magic((uint32_t)a.Wo); a.mg_cin = div_magic((uint32_t)a.Cin); a.mg_kw = div_magic((uint32_t)a.kw);
+  a.mg_wo = div_magic((uint32_t)a.Wo); a.mg_cin = div_magic((uint32_t)a.Cin); a.mg_kw = div_magic((uint32_t)a.kw); a.mg_mt = tile_magic(L.cp.grid_x, a.MT);
   a.c_real = 0;
   if (l == 0 && net.fuse_ingest) {  // layer 0 gathers from the job's fp32 [C][H][W] input: the pointer is filled in per job
     a.x = nullptr;

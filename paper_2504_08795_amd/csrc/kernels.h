@@ -24,6 +24,8 @@ enum KernelId : int32_t {
 };
 const char* kernel_name(int32_t id);
 
+constexpr uint32_t kNoMagic = 0xffffffffu;
+
 struct ConvArgs {
   const void* x;      // [H][W][Cin]; with c_real > 0: the network input as the caller gives it, float [c_real][H][W]
   const void* w;      // packed weights in MFMA fragment order (see pack_conv)
@@ -33,7 +35,8 @@ struct ConvArgs {
   float* ws;          // split-K partial sums (splitk > 1)
   int H, W, Cin, Ho, Wo, Cout;
   int kh, kw, stride, pad;
-  int K, Kpad, M;
+  uint32_t mg_mt;  // multiplier for division by MT, or kNoMagic
+  int Kpad, M;
   int act;
   int splitk;  // grid.z
   int S, sz, sw;  // K steps in total, per K slice of a workgroup, per wave
@@ -103,6 +106,8 @@ ConvPlan plan_conv(int M, int N, int Kpad, int bf16, int step_align, int cin_str
 ConvPlan plan_conv_like(const ConvPlan& first, int M, int N, int Kpad, int bf16, int step_align, int nominal_cus = 128);
 // Multiplier for fast_div: floor(2^32 / d) + 1, or 0 for d == 1.  Exact for every n >= 0 with n * d < 2^32.
 inline uint32_t div_magic(uint32_t d) { return d <= 1 ? 0u : (uint32_t)((1ull << 32) / d) + 1u; }
+// ... for the tile order of a convolution: the multiplier for division of a workgroup number by MT.
+inline uint32_t tile_magic(uint64_t groups, int MT) { return groups * (uint64_t)MT < (1ull << 32) ? div_magic((uint32_t)MT) : kNoMagic; }
 
 // ---- launches ------------------------------------------------------------------------------------------------------------
 //

@@ -321,6 +321,7 @@ bool encode_conv(const KernelTable& kt, const ConvPlan& pl, const ConvArgs& a, i
     if ((uint64_t)(a.H + a.pad) * a.W * a.Cin * 4 >= (1ull << 31) || (uint64_t)pl.S * 3072 + 12288 >= (1ull << 31)) return false;
     ConvArgs b = a;
     b.MT = cdiv(a.M, 64);
+    b.mg_mt = tile_magic((uint64_t)b.MT * b.G, b.MT);
     const uint32_t grid = (uint32_t)(b.xmode == 2 ? 8 * cdiv(b.MT, 8 / b.G) : b.G * b.MT);
     if (!push(out, kt.block[variant % 3], pl.kernel, grid, (uint32_t)pl.threads, &b, sizeof(b))) return false;
     return push_reduce(kt, pl, a, bf16, out);
