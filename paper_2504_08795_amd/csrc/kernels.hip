@@ -52,7 +52,7 @@ __global__ __launch_bounds__(NW * 64) void conv_wave_kernel(const ConvArgs) {
   __shared__ __align__(16) float red[conv_wave_lds<BF16, TN, NW, MODE>()];
   int mt, g;
   if (!conv_tile_of(p, (int)blockIdx.x, &mt, &g)) return;
-  conv_wave_body<BF16, TN, NW, MODE, 2, false>(p, mt, g, red, DwFusedArgs(), [] {});
+  conv_wave_body<BF16, TN, NW, MODE, 2>(p, mt, g, red, DwFusedArgs());
   puts_done();
 }
 
@@ -64,7 +64,7 @@ __global__ __launch_bounds__(NW * 64) void conv_wave_dw_kernel(const ConvArgs, c
   __shared__ __align__(16) float red[conv_wave_lds<BF16, TN, NW, 4>()];
   int mt, g;
   if (!conv_tile_of(p, (int)blockIdx.x, &mt, &g)) return;
-  conv_wave_body<BF16, TN, NW, 4, 1, false>(p, mt, g, red, d, [] {});
+  conv_wave_body<BF16, TN, NW, 4, 1>(p, mt, g, red, d);
   puts_done();
 }
 // Two independent convolutions of the same kernel variant in one launch (a residual block's first convolution and
@@ -77,7 +77,7 @@ __global__ __launch_bounds__(NW * 64) void conv_wave_pair_kernel(const ConvArgs,
   const ConvArgs p = conv_args_at((ConstPtr)__builtin_amdgcn_kernarg_segment_ptr() + (second ? sizeof(ConvArgs) : 0));
   int mt, g;
   if (!conv_tile_of(p, (int)blockIdx.x - (second ? n0 : 0), &mt, &g)) return;
-  conv_wave_body<BF16, TN, NW, MODE, 2, false>(p, mt, g, red, DwFusedArgs(), [] {});
+  conv_wave_body<BF16, TN, NW, MODE, 2>(p, mt, g, red, DwFusedArgs());
   puts_done();
 }
 
@@ -87,7 +87,7 @@ __global__ __launch_bounds__(NW * 64) void conv_wave16_kernel(const ConvArgs) {
   __shared__ __align__(16) float red[conv_wave16_lds<BF16, TB, NW>()];
   int mt, g;
   if (!conv_tile_of(p, (int)blockIdx.x, &mt, &g)) return;
-  conv_wave16_body<BF16, TB, NW, false>(p, mt, g, red, [] {});
+  conv_wave16_body<BF16, TB, NW>(p, mt, g, red);
   puts_done();
 }
 
@@ -99,7 +99,7 @@ __global__ __launch_bounds__(NW * 64) void conv_wave16_pair_kernel(const ConvArg
   const ConvArgs p = conv_args_at((ConstPtr)__builtin_amdgcn_kernarg_segment_ptr() + (second ? sizeof(ConvArgs) : 0));
   int mt, g;
   if (!conv_tile_of(p, (int)blockIdx.x - (second ? n0 : 0), &mt, &g)) return;
-  conv_wave16_body<BF16, TB, NW, false>(p, mt, g, red, [] {});
+  conv_wave16_body<BF16, TB, NW>(p, mt, g, red);
   puts_done();
 }
 

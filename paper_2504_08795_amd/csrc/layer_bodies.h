@@ -54,15 +54,14 @@ __device__ __forceinline__ ConvArgs conv_args_at(ConstPtr src) {
 // which splitk_reduce_kernel adds in z order (a device-wide fence per workgroup for an in-kernel reduction was
 // measured to cost several times the extra launch).
 //
-// FLOW: ready() is called once by every thread, after what does not depend on earlier layers has been requested (weights,
-// bias) and before anything that does (pixels, residual operand).  Otherwise the pixels are requested first: loads return
-// in order, and what they pass through on their way to the matrix pipe takes longer (0.25 us per launch the other way round).
+// The pixels are requested before the weights: loads return in order, and what the pixels pass through on their way to the
+// matrix pipe takes longer (0.25 us per launch the other way round).
 template <bool BF16, int TN, int NW, int MODE>
 constexpr int conv_wave_lds() {  // floats of LDS
   return (MODE == 3 || MODE == 4) && NW * 32 * 5 * 4 > NW * TN * 1024 ? NW * 32 * 5 * 4 : NW * TN * 1024;
 }
-template <bool BF16, int TN, int NW, int MODE, int DC, bool FLOW, typename Ready>
-__device__ __forceinline__ void conv_wave_body(const ConvArgs& p, const int mt, const int g, float* const red, const DwFusedArgs& dwf, Ready&& ready) {
+template <bool BF16, int TN, int NW, int MODE, int DC>
+__device__ __forceinline__ void conv_wave_body(const ConvArgs& p, const int mt, const int g, float* const red, const DwFusedArgs& dwf) {
   // MODE 0: Cin a multiple of KS; 1: any Cin; 2: the network input itself, fp32 [C][H][W]; 3: a pixel's channels are whole
   // 64-byte rows (Cin * ES a multiple of 64): the pixel operand is fetched in coalesced rows and transposed through LDS;
   // 4: like 3 for a 1x1 convolution whose input is the output of a 3x3 depthwise convolution that is never stored: the
@@ -205,7 +204,7 @@ __device__ __forceinline__ void conv_wave_body(const ConvArgs& p, const int mt, 
     }
   };
 
-  if constexpr (!FLOW) fetch_res();
+  fetch_res();
 
   f32x16 acc[TN];
 #pragma unroll
@@ -283,10 +282,6 @@ __device__ __forceinline__ void conv_wave_body(const ConvArgs& p, const int mt, 
     };
     auto compute_c = [&](int d) { mma_chunk(keep_if(aqv[d][0], aq[d][0]), keep_if(aqv[d][1], aq[d][1]), d); };
     const int nch = nsteps >> 1;
-    if constexpr (FLOW) {
-      ready();
-      fetch_res();
-    }
 #pragma unroll
     for (int d = 0; d < DC; ++d) load_c(d);
     int done = 0;
@@ -301,10 +296,6 @@ __device__ __forceinline__ void conv_wave_body(const ConvArgs& p, const int mt, 
     for (int d = 0; d < DC; ++d)
       if (done + d < nch) compute_c(d);
   } else if constexpr (!STAGED) {
-    if constexpr (FLOW) {
-      ready();
-      fetch_res();
-    }
 #pragma unroll
     for (int d = 0; d < D; ++d) load(d);
     int done = 0;
@@ -435,7 +426,6 @@ __device__ __forceinline__ void conv_wave_body(const ConvArgs& p, const int mt, 
         dw_issue();  // the next chunk's operands travel while this one goes through the matrix pipe
         exchange_and_mma(cs);
       };
-      static_assert(!FLOW, "not a tile of a run of layers");
       dw_issue();
       load_w_all();
       int c = 0;
@@ -491,14 +481,9 @@ __device__ __forceinline__ void conv_wave_body(const ConvArgs& p, const int mt, 
         load_rows(slot);  // CS chunks ahead (past the end of the slice: valid memory, never used)
         exchange_and_mma(slot);
       };
-      if constexpr (FLOW) {
-        load_w_all();
-        ready();
-        fetch_res();
-      }
 #pragma unroll
       for (int s = 0; s < CS; ++s) load_rows(s);
-      if constexpr (!FLOW) load_w_all();
+      load_w_all();
       int c = 0;
       for (; c + CS <= nchunks; c += CS) {
         chunk(0);
@@ -585,8 +570,8 @@ template <bool BF16, int TB, int NW>
 constexpr int conv_wave16_lds() {  // floats of LDS
   return NW * (BF16 ? 1 : 2) * 16 * 5 * 4 > NW * TB * 256 ? NW * (BF16 ? 1 : 2) * 16 * 5 * 4 : NW * TB * 256;
 }
-template <bool BF16, int TB, int NW, bool FLOW, typename Ready>
-__device__ __forceinline__ void conv_wave16_body(const ConvArgs& p, const int mt, const int g, float* const red, Ready&& ready) {
+template <bool BF16, int TB, int NW>
+__device__ __forceinline__ void conv_wave16_body(const ConvArgs& p, const int mt, const int g, float* const red) {
   constexpr int ES = BF16 ? 2 : 4;
   constexpr int VEC = 16 / ES;
   constexpr int KS = 4 * VEC;  // k per step: 16 (fp32) / 32 (bf16)
@@ -678,13 +663,6 @@ __device__ __forceinline__ void conv_wave16_body(const ConvArgs& p, const int mt
       wptr[j] += 3072;
     }
   };
-  if constexpr (FLOW) {
-#pragma unroll
-    for (int d = 0; d < (BF16 ? D : DP); ++d) {
-      if constexpr (BF16) load_b(d);
-      else load_b_pair(d);
-    }
-  }
 
   // epilogue operands fetched ahead of the K loop: this thread's quad of consecutive channels (see below)
   constexpr int QUADS = TILE / 4;
@@ -700,7 +678,6 @@ __device__ __forceinline__ void conv_wave16_body(const ConvArgs& p, const int mt
   using ResVec = typename std::conditional<BF16, uint2, uint4>::type;
   ResVec res_pre = ResVec();
   const bool use_res = own_epilogue && p.res != nullptr;
-  if constexpr (FLOW) ready();
   if (use_res && q_ok) res_pre = *(const ResVec*)((const unsigned char*)p.res + ((size_t)qm * p.Cout + qn) * ES);
 
   f32x4 acc[TB];
@@ -749,7 +726,7 @@ __device__ __forceinline__ void conv_wave16_body(const ConvArgs& p, const int mt
 #pragma unroll
     for (int d = 0; d < D; ++d) {
       load_a(d);
-      if constexpr (!FLOW) load_b(d);
+      load_b(d);
     }
     for (; done + D <= nsteps; done += D) {
 #pragma unroll
@@ -767,7 +744,7 @@ __device__ __forceinline__ void conv_wave16_body(const ConvArgs& p, const int mt
 #pragma unroll
     for (int d = 0; d < DP; ++d) {
       load_a_pair(d);
-      if constexpr (!FLOW) load_b_pair(d);
+      load_b_pair(d);
     }
     for (; done + DP <= np; done += DP) {
 #pragma unroll
