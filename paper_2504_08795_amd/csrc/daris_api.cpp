@@ -260,7 +260,7 @@ std::string encode_network(TaskRt& T, const std::vector<void*>& slots, float* ws
         if (L.depthwise && L.fused_dw) {
           ok = true;  // computed inside the next layer's launch
         } else if (L.depthwise) {
-          DwArgs a;
+          DwArgs a = DwArgs();
           a.x = x; a.w = L.w_dev; a.bias = L.b_dev; a.y = y;
           a.H = in.H; a.W = in.W; a.C = in.Cs; a.Ho = L.out.H; a.Wo = L.out.W;
           a.k = L.d.k; a.stride = L.d.stride; a.pad = L.d.pad; a.act = L.d.act;
@@ -296,14 +296,14 @@ std::string encode_network(TaskRt& T, const std::vector<void*>& slots, float* ws
         break;
       case DARIS_OP_MAXPOOL:
       case DARIS_OP_GAVGPOOL: {
-        PoolArgs a;
+        PoolArgs a = PoolArgs();
         a.x = x; a.y = y; a.H = in.H; a.W = in.W; a.C = in.Cs; a.Ho = L.out.H; a.Wo = L.out.W;
         a.k = L.d.k; a.stride = L.d.stride; a.pad = L.d.pad;
         ok = L.d.op == DARIS_OP_MAXPOOL ? encode_maxpool(g_kt, a, bf16, &ks) : encode_gavgpool(g_kt, a, bf16, &ks);
         break;
       }
       case DARIS_OP_FC: {
-        FcArgs a;
+        FcArgs a = FcArgs();
         a.x = x; a.w = L.w_dev; a.bias = L.b_dev; a.y = y;
         a.K = L.K; a.N = L.d.c_out; a.Ns = direct ? L.d.c_out : L.out.Cs;
         a.act = L.d.act; a.out_f32 = direct ? 1 : 0;

@@ -60,18 +60,35 @@ __device__ __forceinline__ int fast_div(int n, uint32_t magic) { return magic ? 
 // A kernel's arguments (or any constant block) in one batch of scalar loads.  Left to itself the compiler fetches the
 // fields it needs first, branches, and fetches the rest: one more trip to memory, 0.25 us per launch.
 typedef int i32x8 __attribute__((ext_vector_type(8)));
+typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef i32x8 i32x8_a4 __attribute__((aligned(4)));
+typedef i32x4 i32x4_a4 __attribute__((aligned(4)));
 typedef const unsigned char __attribute__((address_space(4))) * ConstPtr;
 
 template <typename T>
 __device__ __forceinline__ T grab(ConstPtr src) {
-  static_assert(sizeof(T) == 160, "five vectors of eight words");
-  i32x8 v[5];
-#pragma unroll
-  for (int i = 0; i < 5; ++i) v[i] = *(const i32x8_a4 __attribute__((address_space(4)))*)(src + 32 * i);
-  asm volatile("" : "+s"(v[0]), "+s"(v[1]), "+s"(v[2]), "+s"(v[3]), "+s"(v[4]));
+  static_assert(sizeof(T) == 160 || sizeof(T) == 80 || sizeof(T) == 64, "vectors of eight or four words");
   T t;
-  __builtin_memcpy(&t, v, sizeof(T));
+  if constexpr (sizeof(T) == 160) {
+    i32x8 v[5];
+#pragma unroll
+    for (int i = 0; i < 5; ++i) v[i] = *(const i32x8_a4 __attribute__((address_space(4)))*)(src + 32 * i);
+    asm volatile("" : "+s"(v[0]), "+s"(v[1]), "+s"(v[2]), "+s"(v[3]), "+s"(v[4]));
+    __builtin_memcpy(&t, v, sizeof(T));
+  } else if constexpr (sizeof(T) == 80) {
+    struct { i32x8 a[2]; i32x4 b; } v;
+    v.a[0] = *(const i32x8_a4 __attribute__((address_space(4)))*)src;
+    v.a[1] = *(const i32x8_a4 __attribute__((address_space(4)))*)(src + 32);
+    v.b = *(const i32x4_a4 __attribute__((address_space(4)))*)(src + 64);
+    asm volatile("" : "+s"(v.a[0]), "+s"(v.a[1]), "+s"(v.b));
+    __builtin_memcpy(&t, &v, sizeof(T));
+  } else {
+    i32x8 v[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) v[i] = *(const i32x8_a4 __attribute__((address_space(4)))*)(src + 32 * i);
+    asm volatile("" : "+s"(v[0]), "+s"(v[1]));
+    __builtin_memcpy(&t, v, sizeof(T));
+  }
   return t;
 }
 

@@ -62,12 +62,15 @@ struct DwArgs {
   const float* bias;  // [C]
   void* y;            // [Ho][Wo][C]
   int H, W, C, Ho, Wo, k, stride, pad, act;
+  uint32_t mg_cv, mg_wo;  // multipliers for division by the channel vectors of a pixel and by Wo, or kNoMagic (set by encode_dwconv)
+  uint32_t per_xcd;       // workgroups of one XCD (set by encode_dwconv)
 };
 
 struct PoolArgs {
   const void* x;
   void* y;
   int H, W, C, Ho, Wo, k, stride, pad;
+  uint32_t mg_cv, mg_wo, per_xcd;  // as in DwArgs (set by encode_maxpool; gavgpool has no use for them)
 };
 
 struct FcArgs {
@@ -76,6 +79,7 @@ struct FcArgs {
   const float* bias;  // [N]
   void* y;            // [Ns], element type of the task, or float when out_f32; outputs N..Ns-1 are written as 0
   int K, N, Ns, act, out_f32;
+  int spare[3];  // the block is fetched in two vectors of eight words
 };
 
 // Kernel and tile configuration chosen on the host for one dense convolution.
@@ -133,7 +137,7 @@ struct KernelTable {
   const AqlKernel* pair16[2][6] = {};
   const AqlKernel* block[3] = {};       // 64-pixel tiles: [log2(nw) - 1]
   const AqlKernel* convdw[2][6] = {};   // 1x1 convolution with a fused depthwise producer (fp32: tn = 1 only)
-  const AqlKernel *reduce[2] = {}, *dwconv[2] = {}, *maxpool[2] = {}, *gavgpool[2] = {}, *fc[2] = {}, *ingest[2] = {}, *egress[2] = {};
+  const AqlKernel *reduce[2] = {}, *dwconv[2][2] = {} /* [bf16][3x3] */, *maxpool[2][3] = {} /* [bf16][any, 2x2, 3x3] */, *gavgpool[2] = {}, *fc[2] = {}, *ingest[2] = {}, *egress[2] = {};
   const AqlKernel* cu_probe = nullptr;
   // "" or the name of the first kernel that is missing or whose argument size is not what this header declares
   std::string resolve(const AqlRuntime& rt);

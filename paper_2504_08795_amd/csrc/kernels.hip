@@ -13,20 +13,30 @@
 namespace daris {
 
 // Sums the split-K partials in split order and applies the fused epilogue.  One thread per 4 output channels.
+// N / 4 = n4; mg_n4: the multiplier for division by it.  Partials travel four at a time, one trip to memory per four slices.
 template <bool BF16>
 __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restrict__ ws, const float* __restrict__ bias,
-                                                            const void* res, void* y, int M, int N, int splitk, int act) {
-  const size_t idx = (size_t)blockIdx.x * 256 + threadIdx.x;
-  const size_t total4 = (size_t)M * N / 4;
-  if (idx >= total4) return;
-  const size_t o = idx * 4;
-  const int n = (int)(o % N);
-  float4 s = *(const float4*)(ws + o);
-  for (int z = 1; z < splitk; ++z) {
-    const float4 t = *(const float4*)(ws + (size_t)z * M * N + o);
-    s.x += t.x; s.y += t.y; s.z += t.z; s.w += t.w;
-  }
+                                                            const void* res, void* y, int M, int N, int splitk, int act, uint32_t mg_n4) {
+  const uint32_t idx = blockIdx.x * 256u + threadIdx.x, n4 = (uint32_t)N >> 2;
+  const size_t o = (size_t)idx * 4;
+  const uint32_t row = mg_n4 == kNoMagic ? idx / n4 : (uint32_t)fast_div((int)idx, mg_n4);
+  if (row >= (uint32_t)M) return;
+  const int n = (int)(idx - row * n4) * 4;
   const float4 b = *(const float4*)(bias + n);
+  const size_t slice = (size_t)M * N;
+  float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+  for (int z = 0; z < splitk; z += 4) {
+    float4 t[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) t[u] = *(const float4*)(ws + (size_t)min(z + u, splitk - 1) * slice + o);
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (z + u < splitk) {  // (slice 0 as it is: 0 + -0 would lose the sign)
+        const bool first = z + u == 0;
+        s.x = first ? t[u].x : s.x + t[u].x; s.y = first ? t[u].y : s.y + t[u].y;
+        s.z = first ? t[u].z : s.z + t[u].z; s.w = first ? t[u].w : s.w + t[u].w;
+      }
+  }
   float v[4] = {s.x + b.x, s.y + b.y, s.z + b.z, s.w + b.w};
   if (res) {
 #pragma unroll
@@ -104,27 +114,31 @@ __global__ __launch_bounds__(NW * 64) void conv_wave16_pair_kernel(const ConvArg
 }
 
 // ---- the memory-bound layers (layer_bodies.h) -----------------------------------------------------------------------------
-template <bool BF16>
-__global__ __launch_bounds__(256) void dwconv_kernel(const DwArgs a) {
-  dwconv_point<BF16>(a, (size_t)blockIdx.x * 256 + threadIdx.x);
+template <bool BF16, int K>
+__global__ __launch_bounds__(256) void dwconv_kernel(const DwArgs) {
+  const DwArgs a = args_at<DwArgs>((ConstPtr)__builtin_amdgcn_kernarg_segment_ptr());
+  dwconv_point<BF16, K>(a, point_of<BF16>(a, (int)blockIdx.x, (int)threadIdx.x));
+  puts_done();
+}
+
+template <bool BF16, int K>
+__global__ __launch_bounds__(256) void maxpool_kernel(const PoolArgs) {
+  const PoolArgs a = args_at<PoolArgs>((ConstPtr)__builtin_amdgcn_kernarg_segment_ptr());
+  maxpool_point<BF16, K>(a, point_of<BF16>(a, (int)blockIdx.x, (int)threadIdx.x));
   puts_done();
 }
 
 template <bool BF16>
-__global__ __launch_bounds__(256) void maxpool_kernel(const PoolArgs a) {
-  maxpool_point<BF16>(a, (size_t)blockIdx.x * 256 + threadIdx.x);
-  puts_done();
-}
-
-template <bool BF16>
-__global__ __launch_bounds__(256) void gavgpool_kernel(const PoolArgs a) {
+__global__ __launch_bounds__(256) void gavgpool_kernel(const PoolArgs) {
+  const PoolArgs a = args_at<PoolArgs>((ConstPtr)__builtin_amdgcn_kernarg_segment_ptr());
   __shared__ float part[4][64];
   gavgpool_group<BF16>(a, (int)blockIdx.x, (int)threadIdx.x, part);
   puts_done();
 }
 
 template <bool BF16>
-__global__ __launch_bounds__(256) void fc_kernel(const FcArgs a) {
+__global__ __launch_bounds__(256) void fc_kernel(const FcArgs) {
+  const FcArgs a = args_at<FcArgs>((ConstPtr)__builtin_amdgcn_kernarg_segment_ptr());
   fc_row<BF16>(a, (int)(blockIdx.x * 4 + (threadIdx.x >> 6)), (int)(threadIdx.x & 63));
   puts_done();
 }
@@ -185,9 +199,12 @@ __global__ __launch_bounds__(64) void cu_probe_kernel(uint32_t* out, int spin) {
   DARIS_INST_CONV(B, 1, 2) DARIS_INST_CONV(B, 1, 4) DARIS_INST_CONV(B, 1, 8)                        \
   DARIS_INST_CONV(B, 2, 2) DARIS_INST_CONV(B, 2, 4) DARIS_INST_CONV(B, 2, 8)                        \
   DARIS_INST_CONV16(B, 1) DARIS_INST_CONV16(B, 2)                                                   \
-  template __global__ void splitk_reduce_kernel<B>(const float*, const float*, const void*, void*, int, int, int, int); \
-  template __global__ void dwconv_kernel<B>(const DwArgs);                                         \
-  template __global__ void maxpool_kernel<B>(const PoolArgs);                                      \
+  template __global__ void splitk_reduce_kernel<B>(const float*, const float*, const void*, void*, int, int, int, int, uint32_t); \
+  template __global__ void dwconv_kernel<B, 0>(const DwArgs);                                      \
+  template __global__ void dwconv_kernel<B, 3>(const DwArgs);                                      \
+  template __global__ void maxpool_kernel<B, 0>(const PoolArgs);                                   \
+  template __global__ void maxpool_kernel<B, 2>(const PoolArgs);                                   \
+  template __global__ void maxpool_kernel<B, 3>(const PoolArgs);                                   \
   template __global__ void gavgpool_kernel<B>(const PoolArgs);                                     \
   template __global__ void fc_kernel<B>(const FcArgs);                                             \
   template __global__ void ingest_kernel<B>(const float*, void*, int, int, int);                   \

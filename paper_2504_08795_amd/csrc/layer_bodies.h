@@ -29,7 +29,7 @@ __device__ __forceinline__ bool conv_tile_of(const ConvArgs& p, const int L, int
   return *g < p.G && *mt < p.MT;
 }
 
-// The arguments of a convolution at `src`.
+// The arguments of a layer at `src`.
 __device__ __forceinline__ ConvArgs conv_args_at(ConstPtr src) {
   ConvArgs p = grab<ConvArgs>(src);
   p.x = in_memory(p.x);
@@ -39,6 +39,17 @@ __device__ __forceinline__ ConvArgs conv_args_at(ConstPtr src) {
   p.y = in_memory(p.y);
   p.ws = in_memory(p.ws);
   return p;
+}
+template <typename Args>
+__device__ __forceinline__ Args args_at(ConstPtr src) {
+  Args a = grab<Args>(src);
+  a.x = in_memory(a.x);
+  a.y = in_memory(a.y);
+  if constexpr (!std::is_same<Args, PoolArgs>::value) {
+    a.w = in_memory(a.w);
+    a.bias = in_memory(a.bias);
+  }
+  return a;
 }
 
 // ---- wave-tile implicit GEMM ---------------------------------------------------------------------------------------
@@ -800,68 +811,134 @@ __device__ __forceinline__ void conv_wave16_body(const ConvArgs& p, const int mt
   }
 }
 
-// ---- depthwise convolution: memory bound, one thread per (output pixel, 16-byte channel vector) -----------------------
-template <bool BF16>
-__device__ __forceinline__ void dwconv_point(const DwArgs& a, const size_t idx) {
+// ---- pointwise layers: one thread per (output pixel, 16-byte channel vector) ----------------------------------------------
+//
+// Bound by the trip to memory, not by bytes: a layer of MobileNetV2 has one to two waves per SIMD and nothing to hide a load
+// behind.  With the filter size known at compile time every load of a window is in flight at once (one trip instead of one per
+// tap), and the thread's place comes from multiplications.  fp32 on 128 CUs: depthwise 14x14x384 3.29 -> 2.16 us, 28x28x192
+// 3.48 -> 2.88, 7x7x960 3.33 -> 2.16; 3x3 pooling of 112x112x64 3.55 -> 2.34, 2x2 pooling of 224x224x64 3.80 -> 2.77
+// (an empty launch: 1.5).  K = 0: any other filter size, and tensors whose byte
+// offsets do not fit 31 bits, tap by tap.
+// Workgroups L, L + 8, L + 16, ... run on one XCD: it gets a band of consecutive rows, so that the rows a band's windows
+// share come from memory into its L2 once.
+struct Point {
+  int c0, m, oy, ox;  // first channel, output pixel
+  bool ok;
+};
+template <bool BF16, typename Args>
+__device__ __forceinline__ Point point_of(const Args& a, const int L, const int tid) {
+  constexpr int VEC = BF16 ? 8 : 4;
+  const uint32_t idx = ((uint32_t)(L & 7) * a.per_xcd + (uint32_t)(L >> 3)) * 256u + (uint32_t)tid;
+  const uint32_t cvn = (uint32_t)a.C / VEC;
+  Point t;
+  const uint32_t m = a.mg_cv == kNoMagic ? idx / cvn : (uint32_t)fast_div((int)idx, a.mg_cv);
+  t.m = (int)m;
+  t.c0 = (int)(idx - m * cvn) * VEC;
+  t.ok = m < (uint32_t)a.Ho * (uint32_t)a.Wo;
+  t.oy = a.mg_wo == kNoMagic ? (int)(m / (uint32_t)a.Wo) : fast_div((int)m, a.mg_wo);
+  t.ox = t.m - t.oy * a.Wo;
+  return t;
+}
+
+// depthwise convolution
+template <bool BF16, int K>
+__device__ __forceinline__ void dwconv_point(const DwArgs& a, const Point& t) {
   constexpr int VEC = BF16 ? 8 : 4;
   constexpr int ES = BF16 ? 2 : 4;
-  const int cvn = a.C / VEC;
-  if (idx >= (size_t)a.Ho * a.Wo * cvn) return;
-  const int cv = (int)(idx % cvn);
-  const int m = (int)(idx / cvn);
-  const int oy = m / a.Wo, ox = m - oy * a.Wo;
-  const int c0 = cv * VEC;
+  if (!t.ok) return;
   float acc[VEC];
-#pragma unroll
-  for (int i = 0; i < VEC; ++i) acc[i] = a.bias[c0 + i];
   const unsigned char* xb = (const unsigned char*)a.x;
   const unsigned char* wb = (const unsigned char*)a.w;
-  for (int ky = 0; ky < a.k; ++ky) {
-    const int iy = oy * a.stride + ky - a.pad;
-    if ((unsigned)iy >= (unsigned)a.H) continue;
-    for (int kx = 0; kx < a.k; ++kx) {
-      const int ix = ox * a.stride + kx - a.pad;
-      if ((unsigned)ix >= (unsigned)a.W) continue;
-      float xv[VEC], wv[VEC];
-      unpack<BF16>(*(const uint4*)(xb + ((size_t)(iy * a.W + ix) * a.C + c0) * ES), xv);
-      unpack<BF16>(*(const uint4*)(wb + ((size_t)(ky * a.k + kx) * a.C + c0) * ES), wv);
+  const int iy0 = t.oy * a.stride - a.pad, ix0 = t.ox * a.stride - a.pad;
+  if constexpr (K > 0) {
+    const int step = a.C * ES, first = (iy0 * a.W + ix0) * step + t.c0 * ES;  // byte offsets (may start outside the image)
+    uint4 xv[K * K], wv[K * K];
+    bool in[K * K];
 #pragma unroll
-      for (int i = 0; i < VEC; ++i) acc[i] = fmaf(xv[i], wv[i], acc[i]);
+    for (int i = 0; i < K * K; ++i) {
+      const int iy = iy0 + i / K, ix = ix0 + i % K;
+      in[i] = (unsigned)iy < (unsigned)a.H && (unsigned)ix < (unsigned)a.W;
+      xv[i] = *(const uint4*)(xb + (uint32_t)(in[i] ? first + (i / K * a.W + i % K) * step : 0));  // always a valid address
+      wv[i] = *(const uint4*)(wb + (uint32_t)(t.c0 * ES + i * step));
+    }
+#pragma unroll
+    for (int q = 0; q < VEC / 4; ++q) {
+      const float4 b = *(const float4*)(a.bias + t.c0 + 4 * q);
+      acc[4 * q] = b.x; acc[4 * q + 1] = b.y; acc[4 * q + 2] = b.z; acc[4 * q + 3] = b.w;
+    }
+#pragma unroll
+    for (int j = 0; j < K * K; ++j) {
+      float xf[VEC], wf[VEC];
+      unpack<BF16>(xv[j], xf);
+      unpack<BF16>(wv[j], wf);
+#pragma unroll
+      for (int i = 0; i < VEC; ++i) acc[i] = in[j] ? fmaf(xf[i], wf[i], acc[i]) : acc[i];
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < VEC; ++i) acc[i] = a.bias[t.c0 + i];
+    for (int ky = 0; ky < a.k; ++ky) {
+      const int iy = iy0 + ky;
+      if ((unsigned)iy >= (unsigned)a.H) continue;
+      for (int kx = 0; kx < a.k; ++kx) {
+        const int ix = ix0 + kx;
+        if ((unsigned)ix >= (unsigned)a.W) continue;
+        float xf[VEC], wf[VEC];
+        unpack<BF16>(*(const uint4*)(xb + ((size_t)(iy * a.W + ix) * a.C + t.c0) * ES), xf);
+        unpack<BF16>(*(const uint4*)(wb + ((size_t)(ky * a.k + kx) * a.C + t.c0) * ES), wf);
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) acc[i] = fmaf(xf[i], wf[i], acc[i]);
+      }
     }
   }
 #pragma unroll
   for (int i = 0; i < VEC; ++i) acc[i] = apply_act(acc[i], a.act);
-  put((unsigned char*)a.y + ((size_t)m * a.C + c0) * ES, pack<BF16>(acc));
+  put((unsigned char*)a.y + ((size_t)t.m * a.C + t.c0) * ES, pack<BF16>(acc));
 }
 
-// ---- max pooling: padding acts as -inf --------------------------------------------------------------------------------
-template <bool BF16>
-__device__ __forceinline__ void maxpool_point(const PoolArgs& a, const size_t idx) {
+// max pooling: padding acts as -inf
+template <bool BF16, int K>
+__device__ __forceinline__ void maxpool_point(const PoolArgs& a, const Point& t) {
   constexpr int VEC = BF16 ? 8 : 4;
   constexpr int ES = BF16 ? 2 : 4;
-  const int cvn = a.C / VEC;
-  if (idx >= (size_t)a.Ho * a.Wo * cvn) return;
-  const int cv = (int)(idx % cvn);
-  const int m = (int)(idx / cvn);
-  const int oy = m / a.Wo, ox = m - oy * a.Wo;
-  const int c0 = cv * VEC;
+  if (!t.ok) return;
   float best[VEC];
 #pragma unroll
   for (int i = 0; i < VEC; ++i) best[i] = -INFINITY;
   const unsigned char* xb = (const unsigned char*)a.x;
-  for (int ky = 0; ky < a.k; ++ky) {
-    const int iy = oy * a.stride + ky - a.pad;
-    if ((unsigned)iy >= (unsigned)a.H) continue;
-    for (int kx = 0; kx < a.k; ++kx) {
-      const int ix = ox * a.stride + kx - a.pad;
-      if ((unsigned)ix >= (unsigned)a.W) continue;
-      float xv[VEC];
-      unpack<BF16>(*(const uint4*)(xb + ((size_t)(iy * a.W + ix) * a.C + c0) * ES), xv);
+  const int iy0 = t.oy * a.stride - a.pad, ix0 = t.ox * a.stride - a.pad;
+  if constexpr (K > 0) {
+    const int step = a.C * ES, first = (iy0 * a.W + ix0) * step + t.c0 * ES;  // byte offsets (may start outside the image)
+    uint4 xv[K * K];
+    bool in[K * K];
 #pragma unroll
-      for (int i = 0; i < VEC; ++i) best[i] = fmaxf(best[i], xv[i]);
+    for (int i = 0; i < K * K; ++i) {
+      const int iy = iy0 + i / K, ix = ix0 + i % K;
+      in[i] = (unsigned)iy < (unsigned)a.H && (unsigned)ix < (unsigned)a.W;
+      xv[i] = *(const uint4*)(xb + (uint32_t)(in[i] ? first + (i / K * a.W + i % K) * step : 0));  // always a valid address
+    }
+#pragma unroll
+    for (int j = 0; j < K * K; ++j) {
+      float xf[VEC];
+      unpack<BF16>(xv[j], xf);
+#pragma unroll
+      for (int i = 0; i < VEC; ++i) best[i] = in[j] ? fmaxf(best[i], xf[i]) : best[i];
+    }
+  } else {
+    for (int ky = 0; ky < a.k; ++ky) {
+      const int iy = iy0 + ky;
+      if ((unsigned)iy >= (unsigned)a.H) continue;
+      for (int kx = 0; kx < a.k; ++kx) {
+        const int ix = ix0 + kx;
+        if ((unsigned)ix >= (unsigned)a.W) continue;
+        float xf[VEC];
+        unpack<BF16>(*(const uint4*)(xb + ((size_t)(iy * a.W + ix) * a.C + t.c0) * ES), xf);
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) best[i] = fmaxf(best[i], xf[i]);
+      }
     }
   }
-  put((unsigned char*)a.y + ((size_t)m * a.C + c0) * ES, pack<BF16>(best));
+  put((unsigned char*)a.y + ((size_t)t.m * a.C + t.c0) * ES, pack<BF16>(best));
 }
 
 // ---- global average pooling: 64 channels per 256 threads, 4 threads per channel over the pixels, LDS sum ------------
@@ -872,8 +949,21 @@ __device__ __forceinline__ void gavgpool_group(const PoolArgs& a, const int grou
   const int c = group * 64 + cl;
   const int hw = a.H * a.W;
   float s = 0.f;
-  if (c < a.C)
-    for (int i = q; i < hw; i += 4) s += load_elem<BF16>(a.x, (size_t)i * a.C + c);
+  if (c < a.C) {
+    int i = q;
+    for (; i + 24 < hw; i += 28) {  // seven loads in flight (a 7 x 7 map: two trips to memory)
+      float v[7];
+#pragma unroll
+      for (int u = 0; u < 7; ++u) v[u] = load_elem<BF16>(a.x, (size_t)(i + 4 * u) * a.C + c);
+#pragma unroll
+      for (int u = 0; u < 7; ++u) s += v[u];
+    }
+    float v[6];
+#pragma unroll
+    for (int u = 0; u < 6; ++u) v[u] = load_elem<BF16>(a.x, (size_t)min(i + 4 * u, hw - 1) * a.C + c);
+#pragma unroll
+    for (int u = 0; u < 6; ++u) s += i + 4 * u < hw ? v[u] : 0.f;
+  }
   part[q][cl] = s;
   __syncthreads();
   if (q == 0 && c < a.C) put_elem<BF16>(a.y, c, (part[0][cl] + part[1][cl] + part[2][cl] + part[3][cl]) / (float)hw);
@@ -892,6 +982,7 @@ __device__ __forceinline__ void fc_row(const FcArgs& a, const int n, const int l
   const unsigned char* wrow = (const unsigned char*)a.w + (size_t)n * a.K * ES;
   const unsigned char* xb = (const unsigned char*)a.x;
   const int nvec = a.K / VEC;
+  float bias = a.bias[n];  // (behind the sums it would be one more trip to memory)
   // Short rows are latency-bound: four independent 16-byte weight loads in flight per lane, each with its own partial sum.
   // Long rows (VGG-16's first FC: 100 KB per wave, 411 MB in all) are pure streaming and run at the memory system's
   // rate with one load per lane; more loads in flight slowed them down (measured: 84 -> 110 us), so they keep the plain loop.
@@ -922,10 +1013,11 @@ __device__ __forceinline__ void fc_row(const FcArgs& a, const int n, const int l
     for (int i = 0; i < VEC; ++i) acc4[0] = fmaf(wv[i], xv[i], acc4[0]);
   }
   float acc = (acc4[0] + acc4[1]) + (acc4[2] + acc4[3]);
+  asm volatile("" : "+v"(bias));
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
   if (lane == 0) {
-    const float v = apply_act(acc + a.bias[n], a.act);
+    const float v = apply_act(acc + bias, a.act);
     if (a.out_f32) put((float*)a.y + n, v);
     else put_elem<BF16>(a.y, n, v);
   }
