@@ -228,6 +228,10 @@ __global__ __launch_bounds__(NW * 64) void conv_block_kernel(const ConvArgs) {
           const float4 t = *(const float4*)&red[(w * BPP + b) * 1024 + e];
           val[0] += t.x; val[1] += t.y; val[2] += t.z; val[3] += t.w;
         }
+        if (__builtin_expect(any_nan(make_float4(val[0], val[1], val[2], val[3])), 0)) {
+          const float4 s = plain_sums<3, 32>(p, DwFusedArgs(), mm, n, s_wg0 * KS, s_wg1 * KS);
+          val[0] = s.x; val[1] = s.y; val[2] = s.z; val[3] = s.w;
+        }
         if (!own_epilogue) {  // partial sums of this K slice; splitk_reduce_kernel finishes the layer
           put(p.ws + (size_t)zi * p.M * p.Cout + o, make_float4(val[0], val[1], val[2], val[3]));
         } else {

@@ -144,7 +144,8 @@ __device__ __forceinline__ uint4 pack(const float* o) {
 // terms against float64: the error of the plain fp32 instruction is the larger one).  v_mfma_f32_32x32x16_bf16 does in 32
 // cycles what v_mfma_f32_32x32x2_f32 does in 512, so the six take 3/8 of the matrix time.  Accumulation is fp32 as before.
 // The first part of an activation is cut off (a rounded one could overflow), all other parts are rounded to nearest even;
-// the weights' parts are made at registration.  (An infinite operand gives NaN.)
+// the weights' parts are made at registration.  (An infinite operand gives
+// NaN; plain_sums in layer_bodies.h puts that right.)
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 

@@ -52,6 +52,52 @@ __device__ __forceinline__ Args args_at(ConstPtr src) {
   return a;
 }
 
+// Sums over k in [k0, k1) for pixel m, channels n..n+3 in plain fp32 arithmetic, for the sums that the products in three
+// parts leave as NaN: an infinite operand, or parts that overflow, where the fp32 product does not.  (Rare, so it is slow: one
+// thread walks k; the weights are put together from their parts, which is exact.)  MODE as in conv_wave_body, R = channels
+// of a weight block.
+__device__ __forceinline__ bool any_nan(const float4& v) { return __builtin_isunordered(v.x, v.y) | __builtin_isunordered(v.z, v.w); }
+template <int MODE, int R>
+__device__ __forceinline__ float4 plain_sums(const ConvArgs& p, const DwFusedArgs& dwf, const int m, const int n, const int k0, const int k1) {
+  constexpr int CK = R == 16 ? 32 : 16;  // k of a chunk of weights
+  const int y = fast_div(m, p.mg_wo), x = m - y * p.Wo;
+  const unsigned char* const wn = (const unsigned char*)p.w + (size_t)(n / R) * (p.Kpad / CK) * 3072 + (n % R) * 16;
+  float s[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+  for (int k = k0; k < k1; ++k) {
+    const int tap = MODE == 2 ? k >> 2 : fast_div(k, p.mg_cin), c = MODE == 2 ? k & 3 : k - tap * p.Cin;
+    const int ky = fast_div(tap, p.mg_kw), kx = tap - ky * p.kw;
+    if (ky >= p.kh || (MODE == 2 && c >= p.c_real)) continue;  // padding of K
+    const int iy = y * p.stride - p.pad + ky, ix = x * p.stride - p.pad + kx;
+    float v = 0.f;
+    if ((unsigned)iy < (unsigned)p.H && (unsigned)ix < (unsigned)p.W) {
+      if constexpr (MODE == 4) {
+        v = dwf.bias[c];
+#pragma unroll 1
+        for (int t = 0; t < 9; ++t) {
+          const int jy = iy * dwf.stride - 1 + t / 3, jx = ix * dwf.stride - 1 + t % 3;
+          if ((unsigned)jy < (unsigned)dwf.H && (unsigned)jx < (unsigned)dwf.W)
+            v = fmaf(((const float*)p.x)[(size_t)(jy * dwf.W + jx) * p.Cin + c], ((const float*)dwf.w)[(size_t)t * p.Cin + c], v);
+        }
+        v = apply_act(v, dwf.act);
+      } else if constexpr (MODE == 2) {
+        v = ((const float*)p.x)[(size_t)c * p.H * p.W + iy * p.W + ix];
+      } else {
+        v = ((const float*)p.x)[(size_t)(iy * p.W + ix) * p.Cin + c];
+      }
+    }
+    const unsigned char* const wk = wn + (size_t)(k / CK) * 3072 + (k % CK / 8) * R * 16 + (k % 8) * 2;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      float w[3];
+#pragma unroll
+      for (int q = 0; q < 3; ++q) w[q] = bf16_bits_to_f32(*(const uint16_t*)(wk + q * 1024 + i * 16));
+      s[i] = fmaf(v, (w[2] + w[1]) + w[0], s[i]);
+    }
+  }
+  return make_float4(s[0], s[1], s[2], s[3]);
+}
+
 // ---- wave-tile implicit GEMM ---------------------------------------------------------------------------------------
 //
 // For the small-M, deep-K convolutions of batch-1 inference an output tile shared through LDS buys nothing: there
@@ -512,17 +558,40 @@ __device__ __forceinline__ void conv_wave_body(const ConvArgs& p, const int mt, 
     for (int v = 0; v < 16; ++v) red[wave * TILE + (j * 16 + v) * 64 + lane] = acc[j][v];
   __syncthreads();
   // --- epilogue per channel quad: pixel m0 + 8*(v/4) + 4*(lane/32) + v%4, channels 32*(nb0+j) + lane%32 .. +3 ---------
+  float4 sums[RQ];
+#pragma unroll
+  for (int r = 0; r < RQ; ++r) {
+    const int e = 4 * (tid + r * NT);
+    if (QUADS % NT != 0 && e >= TILE) {  // (the threads past the tile: 32-channel tiles of 8 waves)
+      sums[r] = make_float4(0.f, 0.f, 0.f, 0.f);
+      continue;
+    }
+    sums[r] = *(const float4*)&red[e];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) {
+      const float4 t = *(const float4*)&red[w * TILE + e];
+      sums[r].x += t.x; sums[r].y += t.y; sums[r].z += t.z; sums[r].w += t.w;
+    }
+  }
+  if constexpr (!BF16) {
+    bool nan = false;
+#pragma unroll
+    for (int r = 0; r < RQ; ++r) nan |= any_nan(sums[r]);
+    if (__builtin_expect(nan, 0)) {  // (out of the way: a launch fetches its code anew, and a longer path costs 0.2 us)
+#pragma unroll
+      for (int r = 0; r < RQ; ++r) {
+        const int e = 4 * (tid + r * NT), j = e >> 10, v = (e >> 6) & 15, l = e & 63;
+        const int mm = m0 + (v >> 2) * 8 + (l >> 5) * 4 + (v & 3), n = (nb0 + j) * 32 + (l & 31);
+        if (any_nan(sums[r]) && mm < p.M && n < p.Cout) sums[r] = plain_sums<MODE, 32>(p, dwf, mm, n, s_wg0 * KS, s_wg1 * KS);
+      }
+    }
+  }
 #pragma unroll
   for (int r = 0; r < RQ; ++r) {
     const int q = tid + r * NT;
     if (QUADS % NT != 0 && q >= QUADS) break;
     const int e = 4 * q;
-    float4 sum = *(const float4*)&red[e];
-#pragma unroll
-    for (int w = 1; w < NW; ++w) {
-      const float4 t = *(const float4*)&red[w * TILE + e];
-      sum.x += t.x; sum.y += t.y; sum.z += t.z; sum.w += t.w;
-    }
+    const float4 sum = sums[r];
     const int j = e >> 10, v = (e >> 6) & 15, l = e & 63;
     const int mm = m0 + (v >> 2) * 8 + (l >> 5) * 4 + (v & 3);
     const int n = (nb0 + j) * 32 + (l & 31);
@@ -784,6 +853,8 @@ __device__ __forceinline__ void conv_wave16_body(const ConvArgs& p, const int mt
     const float4 t = *(const float4*)&red[w * TILE + qe];
     sum.x += t.x; sum.y += t.y; sum.z += t.z; sum.w += t.w;
   }
+  if constexpr (!BF16)
+    if (__builtin_expect(any_nan(sum), 0)) sum = plain_sums<3, 16>(p, DwFusedArgs(), qm, qn, s_wg0 * KS, s_wg1 * KS);
   const size_t o = (size_t)qm * p.Cout + qn;
   if (!own_epilogue) {
     put(p.ws + (size_t)zi * p.M * p.Cout + o, sum);

@@ -54,3 +54,37 @@ def test_block_tiles(case):
     err, plan = _conv(cin, h, w, cout, k, s, p, plan_cus=cus)
     assert plan["tn"] == 2 and (plan["M"] + 63) // 64 * plan["NTn"] >= cus * 3 // 4      # the case runs the kernel it names
     assert err <= 5e-7, err
+
+
+# (cin, h, w, cout, k, stride, pad, plan_cus): the kernel that it runs
+NONFINITE_CASES = [
+    (3, 31, 29, 40, 3, 2, 1, 128),     # the network input as the caller gives it
+    (20, 13, 13, 40, 1, 1, 0, 128),    # pixels straight into registers, 32 x 32 tiles
+    (128, 14, 14, 128, 3, 1, 1, 16),   # staged rows
+    (128, 9, 7, 32, 3, 1, 1, 256),     # K split over workgroups, or 16-pixel tiles
+    (512, 7, 7, 512, 3, 1, 1, 128),    # 16-pixel tiles
+    (64, 41, 43, 64, 3, 1, 1, 32),     # 64 x 64 tiles
+]
+
+
+@pytest.mark.parametrize("case", NONFINITE_CASES, ids=lambda c: "x".join(map(str, c)))
+def test_infinities_and_nan_pass_as_in_fp32_arithmetic(case):
+    cin, h, w, cout, k, s, p, cus = case
+    rng = np.random.default_rng(11)
+    x = rng.normal(0, 1, (cin, h, w)).astype(np.float32)
+    wt = rng.normal(0, np.sqrt(2.0 / (cin * k * k)), (cout, cin, k, k)).astype(np.float32)
+    wt[0, 0, 0, 0] = np.inf
+    b = rng.normal(0, 0.3, cout).astype(np.float32)
+    x[0, 0, 0], x[1, h - 1, w - 1], x[cin - 1, h // 2, w // 2] = np.inf, -np.inf, np.nan
+    x[0, h // 2, 0] = 3.4e38       # its upper half alone is finite, rounded to bf16 it would not be
+    wt[1:, 0] *= 0.1               # ... and the products stay finite
+    L = [N.Layer(op=N.OP_CONV, c_in=cin, c_out=cout, k=k, stride=s, pad=p, act=0, in_from=-1)]
+    with GpuNet(L, [(wt, b)], (cin, h, w), "fp32", plan_cus=cus) as g:
+        got = g.forward(x).astype(np.float64).reshape(cout, -1)[1:]
+    want = torch.nn.functional.conv2d(torch.from_numpy(x).double()[None], torch.from_numpy(wt).double(), torch.from_numpy(b).double(),
+                                      stride=s, padding=p).numpy().reshape(cout, -1)[1:]      # (channel 0: 0 * inf at the border)
+    big = np.abs(want) > 1e30
+    assert np.array_equal(np.isnan(got), np.isnan(want)) and np.isinf(want).any() and np.isnan(want).any()
+    assert np.array_equal(got[np.isinf(want)], want[np.isinf(want)])
+    for part in (np.isfinite(want) & ~big, np.isfinite(want) & big):
+        assert np.linalg.norm(got[part] - want[part]) <= 5e-7 * max(np.linalg.norm(want[part]), 1e-30)
