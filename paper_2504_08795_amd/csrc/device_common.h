@@ -61,34 +61,33 @@ __device__ __forceinline__ int fast_div(int n, uint32_t magic) { return magic ? 
 // fields it needs first, branches, and fetches the rest: one more trip to memory, 0.25 us per launch.
 typedef int i32x8 __attribute__((ext_vector_type(8)));
 typedef int i32x4 __attribute__((ext_vector_type(4)));
+typedef int i32x2 __attribute__((ext_vector_type(2)));
 typedef i32x8 i32x8_a4 __attribute__((aligned(4)));
 typedef i32x4 i32x4_a4 __attribute__((aligned(4)));
+typedef i32x2 i32x2_a4 __attribute__((aligned(4)));
 typedef const unsigned char __attribute__((address_space(4))) * ConstPtr;
 
 template <typename T>
 __device__ __forceinline__ T grab(ConstPtr src) {
-  static_assert(sizeof(T) == 160 || sizeof(T) == 80 || sizeof(T) == 64, "vectors of eight or four words");
+  constexpr int N = sizeof(T), W = N / 32, R = N % 32;  // vectors of eight words, then one of four, then one of two
+  static_assert(N % 8 == 0 && W >= 1 && W <= 5 && R % 8 == 0 && R != 8, "no such argument block");
+  struct {
+    i32x8 w[W];
+    i32x4 q;
+    i32x2 d;
+  } v;
+#pragma unroll
+  for (int i = 0; i < W; ++i) v.w[i] = *(const i32x8_a4 __attribute__((address_space(4)))*)(src + 32 * i);
+  if constexpr (R >= 16) v.q = *(const i32x4_a4 __attribute__((address_space(4)))*)(src + 32 * W);
+  if constexpr (R == 24) v.d = *(const i32x2_a4 __attribute__((address_space(4)))*)(src + 32 * W + 16);
+  if constexpr (W == 5) asm volatile("" : "+s"(v.w[0]), "+s"(v.w[1]), "+s"(v.w[2]), "+s"(v.w[3]), "+s"(v.w[4]));
+  else if constexpr (W == 2 && R == 24) asm volatile("" : "+s"(v.w[0]), "+s"(v.w[1]), "+s"(v.q), "+s"(v.d));
+  else if constexpr (W == 2 && R == 0) asm volatile("" : "+s"(v.w[0]), "+s"(v.w[1]));
+  else if constexpr (W == 1 && R == 24) asm volatile("" : "+s"(v.w[0]), "+s"(v.q), "+s"(v.d));
+  else if constexpr (W == 1 && R == 16) asm volatile("" : "+s"(v.w[0]), "+s"(v.q));
+  else static_assert(N == 0, "no such argument block");
   T t;
-  if constexpr (sizeof(T) == 160) {
-    i32x8 v[5];
-#pragma unroll
-    for (int i = 0; i < 5; ++i) v[i] = *(const i32x8_a4 __attribute__((address_space(4)))*)(src + 32 * i);
-    asm volatile("" : "+s"(v[0]), "+s"(v[1]), "+s"(v[2]), "+s"(v[3]), "+s"(v[4]));
-    __builtin_memcpy(&t, v, sizeof(T));
-  } else if constexpr (sizeof(T) == 80) {
-    struct { i32x8 a[2]; i32x4 b; } v;
-    v.a[0] = *(const i32x8_a4 __attribute__((address_space(4)))*)src;
-    v.a[1] = *(const i32x8_a4 __attribute__((address_space(4)))*)(src + 32);
-    v.b = *(const i32x4_a4 __attribute__((address_space(4)))*)(src + 64);
-    asm volatile("" : "+s"(v.a[0]), "+s"(v.a[1]), "+s"(v.b));
-    __builtin_memcpy(&t, &v, sizeof(T));
-  } else {
-    i32x8 v[2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i) v[i] = *(const i32x8_a4 __attribute__((address_space(4)))*)(src + 32 * i);
-    asm volatile("" : "+s"(v[0]), "+s"(v[1]));
-    __builtin_memcpy(&t, v, sizeof(T));
-  }
+  __builtin_memcpy(&t, &v, N);
   return t;
 }
 

@@ -62,15 +62,27 @@ struct DwArgs {
   const float* bias;  // [C]
   void* y;            // [Ho][Wo][C]
   int H, W, C, Ho, Wo, k, stride, pad, act;
-  uint32_t mg_cv, mg_wo;  // multipliers for division by the channel vectors of a pixel and by Wo, or kNoMagic (set by encode_dwconv)
-  uint32_t per_xcd;       // workgroups of one XCD (set by encode_dwconv)
 };
 
 struct PoolArgs {
   const void* x;
   void* y;
   int H, W, C, Ho, Wo, k, stride, pad;
-  uint32_t mg_cv, mg_wo, per_xcd;  // as in DwArgs (set by encode_maxpool; gavgpool has no use for them)
+};
+
+// The kernels for windows of a size known at compile time (dwconv_window_kernel, maxpool_window_kernel) find a thread's place
+// by multiplications.
+struct PointPlace {
+  uint32_t mg_cv, mg_wo;  // multipliers for division by the channel vectors of a pixel and by Wo, or kNoMagic
+  uint32_t per_xcd;       // workgroups of one XCD
+};
+struct DwWindowArgs {
+  DwArgs a;
+  PointPlace at;
+};
+struct PoolWindowArgs {
+  PoolArgs a;
+  PointPlace at;
 };
 
 struct FcArgs {
@@ -79,7 +91,7 @@ struct FcArgs {
   const float* bias;  // [N]
   void* y;            // [Ns], element type of the task, or float when out_f32; outputs N..Ns-1 are written as 0
   int K, N, Ns, act, out_f32;
-  int spare[3];  // the block is fetched in two vectors of eight words
+  int stream;    // 1: the matrix is read past the last cache (set by encode_fc)  // the block is fetched in two vectors of eight words
 };
 
 // Kernel and tile configuration chosen on the host for one dense convolution.
@@ -137,7 +149,8 @@ struct KernelTable {
   const AqlKernel* pair16[2][6] = {};
   const AqlKernel* block[3] = {};       // 64-pixel tiles: [log2(nw) - 1]
   const AqlKernel* convdw[2][6] = {};   // 1x1 convolution with a fused depthwise producer (fp32: tn = 1 only)
-  const AqlKernel *reduce[2] = {}, *dwconv[2][2] = {} /* [bf16][3x3] */, *maxpool[2][3] = {} /* [bf16][any, 2x2, 3x3] */, *gavgpool[2] = {}, *fc[2] = {}, *ingest[2] = {}, *egress[2] = {};
+  const AqlKernel *reduce[2] = {}, *dwconv[2] = {}, *maxpool[2] = {}, *gavgpool[2] = {}, *fc[2] = {}, *ingest[2] = {}, *egress[2] = {};
+  const AqlKernel *dwconv3[2] = {}, *maxpool_k[2][2] = {};  // 3x3 windows; 2x2 and 3x3 windows
   const AqlKernel* cu_probe = nullptr;
   // "" or the name of the first kernel that is missing or whose argument size is not what this header declares
   std::string resolve(const AqlRuntime& rt);

@@ -13,13 +13,13 @@
 namespace daris {
 
 // Sums the split-K partials in split order and applies the fused epilogue.  One thread per 4 output channels.
-// N / 4 = n4; mg_n4: the multiplier for division by it.  Partials travel four at a time, one trip to memory per four slices.
+// Partials travel four at a time, one trip to memory per four slices.
 template <bool BF16>
 __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restrict__ ws, const float* __restrict__ bias,
-                                                            const void* res, void* y, int M, int N, int splitk, int act, uint32_t mg_n4) {
+                                                            const void* res, void* y, int M, int N, int splitk, int act) {
   const uint32_t idx = blockIdx.x * 256u + threadIdx.x, n4 = (uint32_t)N >> 2;
   const size_t o = (size_t)idx * 4;
-  const uint32_t row = mg_n4 == kNoMagic ? idx / n4 : (uint32_t)fast_div((int)idx, mg_n4);
+  const uint32_t row = idx / n4;
   if (row >= (uint32_t)M) return;
   const int n = (int)(idx - row * n4) * 4;
   const float4 b = *(const float4*)(bias + n);
@@ -114,17 +114,16 @@ __global__ __launch_bounds__(NW * 64) void conv_wave16_pair_kernel(const ConvArg
 }
 
 // ---- the memory-bound layers (layer_bodies.h) -----------------------------------------------------------------------------
-template <bool BF16, int K>
-__global__ __launch_bounds__(256) void dwconv_kernel(const DwArgs) {
-  const DwArgs a = args_at<DwArgs>((ConstPtr)__builtin_amdgcn_kernarg_segment_ptr());
-  dwconv_point<BF16, K>(a, point_of<BF16>(a, (int)blockIdx.x, (int)threadIdx.x));
+template <bool BF16>
+__global__ __launch_bounds__(256) void dwconv_kernel(const DwArgs a) {
+  dwconv_point<BF16, 0>(a, point_of<BF16>(a, blockIdx.x * 256u + threadIdx.x));
   puts_done();
 }
 
-template <bool BF16, int K>
+template <bool BF16>
 __global__ __launch_bounds__(256) void maxpool_kernel(const PoolArgs) {
   const PoolArgs a = args_at<PoolArgs>((ConstPtr)__builtin_amdgcn_kernarg_segment_ptr());
-  maxpool_point<BF16, K>(a, point_of<BF16>(a, (int)blockIdx.x, (int)threadIdx.x));
+  maxpool_point<BF16, 0>(a, point_of<BF16>(a, blockIdx.x * 256u + threadIdx.x));
   puts_done();
 }
 
@@ -199,12 +198,9 @@ __global__ __launch_bounds__(64) void cu_probe_kernel(uint32_t* out, int spin) {
   DARIS_INST_CONV(B, 1, 2) DARIS_INST_CONV(B, 1, 4) DARIS_INST_CONV(B, 1, 8)                        \
   DARIS_INST_CONV(B, 2, 2) DARIS_INST_CONV(B, 2, 4) DARIS_INST_CONV(B, 2, 8)                        \
   DARIS_INST_CONV16(B, 1) DARIS_INST_CONV16(B, 2)                                                   \
-  template __global__ void splitk_reduce_kernel<B>(const float*, const float*, const void*, void*, int, int, int, int, uint32_t); \
-  template __global__ void dwconv_kernel<B, 0>(const DwArgs);                                      \
-  template __global__ void dwconv_kernel<B, 3>(const DwArgs);                                      \
-  template __global__ void maxpool_kernel<B, 0>(const PoolArgs);                                   \
-  template __global__ void maxpool_kernel<B, 2>(const PoolArgs);                                   \
-  template __global__ void maxpool_kernel<B, 3>(const PoolArgs);                                   \
+  template __global__ void splitk_reduce_kernel<B>(const float*, const float*, const void*, void*, int, int, int, int); \
+  template __global__ void dwconv_kernel<B>(const DwArgs);                                         \
+  template __global__ void maxpool_kernel<B>(const PoolArgs);                                      \
   template __global__ void gavgpool_kernel<B>(const PoolArgs);                                     \
   template __global__ void fc_kernel<B>(const FcArgs);                                             \
   template __global__ void ingest_kernel<B>(const float*, void*, int, int, int);                   \

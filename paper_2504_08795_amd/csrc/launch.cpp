@@ -204,13 +204,12 @@ ConvPlan plan_conv_like(const ConvPlan& first, int M, int N, int Kpad, int bf16,
 
 namespace {
 
-struct ReduceArgs {  // splitk_reduce_kernel(ws, bias, res, y, M, N, splitk, act, mg_n4)
+struct ReduceArgs {  // splitk_reduce_kernel(ws, bias, res, y, M, N, splitk, act)
   const float* ws;
   const float* bias;
   const void* res;
   void* y;
   int M, N, splitk, act;
-  uint32_t mg_n4;
 };
 struct IngestArgs {  // ingest_kernel / egress_kernel (x, y, C, Cs, HW)
   const void* x;
@@ -229,9 +228,9 @@ struct ConvDwArgs {  // conv_wave_dw_kernel(p, d)
   ConvArgs p;
   DwFusedArgs d;
 };
-constexpr uint32_t kIngestBytes = 28, kProbeBytes = 12, kPairBytes = 2 * sizeof(ConvArgs) + 4, kReduceBytes = 52;
+constexpr uint32_t kIngestBytes = 28, kProbeBytes = 12, kPairBytes = 2 * sizeof(ConvArgs) + 4;
 static_assert(sizeof(DwFusedArgs) == 32 && sizeof(ConvDwArgs) == 192 && offsetof(ConvDwArgs, d) == sizeof(ConvArgs), "fused depthwise arguments");
-static_assert(sizeof(ConvArgs) == 160 && sizeof(DwArgs) == 80 && sizeof(PoolArgs) == 64 && sizeof(FcArgs) == 64 && offsetof(ReduceArgs, mg_n4) + 4 == kReduceBytes,
+static_assert(sizeof(ConvArgs) == 160 && sizeof(DwArgs) == 72 && sizeof(PoolArgs) == 48 && sizeof(FcArgs) == 56 && sizeof(ReduceArgs) == 48 && sizeof(DwWindowArgs) == 88 && sizeof(PoolWindowArgs) == 64,
               "argument structures must match what the kernels were compiled for");
 static_assert(offsetof(ConvArgs, x) == kConvInputOffset && offsetof(FcArgs, y) == kFcOutputOffset && offsetof(IngestArgs, x) == kIngestInputOffset &&
                   offsetof(IngestArgs, y) == kEgressOutputOffset && offsetof(PairArgs, p1) == sizeof(ConvArgs) &&
@@ -276,10 +275,11 @@ std::string KernelTable::resolve(const AqlRuntime& rt) {
       if (b ? nw_[v] != 8 : tn_[v] == 1)
         convdw[b][v] = get("daris::conv_wave_dw_kernel<" + B + ", " + std::to_string(tn_[v]) + ", " + std::to_string(nw_[v]) + ">", sizeof(ConvDwArgs));
     }
-    reduce[b] = get("daris::splitk_reduce_kernel<" + B + ">", kReduceBytes);
-    for (int v = 0; v < 2; ++v) dwconv[b][v] = get("daris::dwconv_kernel<" + B + (v ? ", 3>" : ", 0>"), sizeof(DwArgs));
-    static const char* const pool_k[3] = {", 0>", ", 2>", ", 3>"};
-    for (int v = 0; v < 3; ++v) maxpool[b][v] = get("daris::maxpool_kernel<" + B + pool_k[v], sizeof(PoolArgs));
+    reduce[b] = get("daris::splitk_reduce_kernel<" + B + ">", sizeof(ReduceArgs));
+    dwconv[b] = get("daris::dwconv_kernel<" + B + ">", sizeof(DwArgs));
+    maxpool[b] = get("daris::maxpool_kernel<" + B + ">", sizeof(PoolArgs));
+    dwconv3[b] = get("daris::dwconv_window_kernel<" + B + ", 3>", sizeof(DwWindowArgs));
+    for (int v = 0; v < 2; ++v) maxpool_k[b][v] = get("daris::maxpool_window_kernel<" + B + (v ? ", 3>" : ", 2>"), sizeof(PoolWindowArgs));
     gavgpool[b] = get("daris::gavgpool_kernel<" + B + ">", sizeof(PoolArgs));
     fc[b] = get("daris::fc_kernel<" + B + ">", sizeof(FcArgs));
     ingest[b] = get("daris::ingest_kernel<" + B + ">", kIngestBytes);
@@ -295,8 +295,8 @@ std::string KernelTable::resolve(const AqlRuntime& rt) {
 static bool push_reduce(const KernelTable& kt, const ConvPlan& pl, const ConvArgs& a, int bf16, std::vector<KernelLaunch>* out) {
   if (pl.splitk <= 1) return true;
   const size_t total4 = (size_t)a.M * a.Cout / 4;
-  ReduceArgs r{a.ws, a.bias, a.res, a.y, a.M, a.Cout, pl.splitk, a.act, tile_magic((total4 + 255) / 256 * 256, a.Cout / 4)};
-  return push(out, kt.reduce[bf16], K_SPLITK_REDUCE, (uint32_t)((total4 + 255) / 256), 256, &r, kReduceBytes);
+  ReduceArgs r{a.ws, a.bias, a.res, a.y, a.M, a.Cout, pl.splitk, a.act};
+  return push(out, kt.reduce[bf16], K_SPLITK_REDUCE, (uint32_t)((total4 + 255) / 256), 256, &r, sizeof(ReduceArgs));
 }
 
 bool encode_conv(const KernelTable& kt, const ConvPlan& pl, const ConvArgs& a, int bf16, std::vector<KernelLaunch>* out) {
@@ -388,31 +388,39 @@ bool encode_conv_pair(const KernelTable& kt, const ConvPlan& pl0, const ConvArgs
   return push_reduce(kt, pl0, a0, bf16, out);
 }
 
-// Grid and place finding of a pointwise layer (point_of): workgroups in multiples of 8, one band of them per XCD.
+// Grid and place finding of a window kernel (point_of): workgroups in multiples of 8, one band of them per XCD.
 template <typename Args>
-static uint32_t point_grid(Args* a, int bf16) {
-  const uint32_t cvn = (uint32_t)(a->C / (bf16 ? 8 : 4));
-  const uint64_t total = (uint64_t)a->Ho * a->Wo * cvn;
-  a->per_xcd = (uint32_t)((total + 2047) / 2048);
-  const uint64_t threads = (uint64_t)a->per_xcd * 2048;
-  a->mg_cv = tile_magic(threads, (int)cvn);
-  a->mg_wo = tile_magic((threads + cvn - 1) / cvn, a->Wo);
-  return threads < (1ull << 32) ? 8 * a->per_xcd : 0;
+static uint32_t point_grid(const Args& a, int bf16, PointPlace* at) {
+  const uint32_t cvn = (uint32_t)(a.C / (bf16 ? 8 : 4));
+  const uint64_t total = (uint64_t)a.Ho * a.Wo * cvn;
+  at->per_xcd = (uint32_t)((total + 2047) / 2048);
+  const uint64_t threads = (uint64_t)at->per_xcd * 2048;
+  at->mg_cv = tile_magic(threads, (int)cvn);
+  at->mg_wo = tile_magic((threads + cvn - 1) / cvn, a.Wo);
+  return threads < (1ull << 32) ? 8 * at->per_xcd : 0;
 }
 // Byte offsets into the input, padding included, fit a signed 32-bit number.
 template <typename Args>
 static bool offsets_fit(const Args& a, int bf16) {
   return (uint64_t)(a.H + 2 * a.pad + a.k) * (uint64_t)(a.W + 2 * a.pad + a.k) * a.C * (bf16 ? 2 : 4) < (1ull << 31);
 }
-bool encode_dwconv(const KernelTable& kt, const DwArgs& layer, int bf16, std::vector<KernelLaunch>* out) {
-  DwArgs a = layer;
-  const uint32_t groups = point_grid(&a, bf16);
-  return push(out, kt.dwconv[bf16][a.k == 3 && offsets_fit(a, bf16)], K_DWCONV, groups, 256, &a, sizeof(a));
+bool encode_dwconv(const KernelTable& kt, const DwArgs& a, int bf16, std::vector<KernelLaunch>* out) {
+  if (a.k == 3 && offsets_fit(a, bf16)) {
+    DwWindowArgs w{a, PointPlace()};
+    const uint32_t groups = point_grid(a, bf16, &w.at);
+    return push(out, kt.dwconv3[bf16], K_DWCONV, groups, 256, &w, sizeof(w));
+  }
+  const size_t total = (size_t)a.Ho * a.Wo * (a.C / (bf16 ? 8 : 4));
+  return push(out, kt.dwconv[bf16], K_DWCONV, (uint32_t)((total + 255) / 256), 256, &a, sizeof(a));
 }
-bool encode_maxpool(const KernelTable& kt, const PoolArgs& layer, int bf16, std::vector<KernelLaunch>* out) {
-  PoolArgs a = layer;
-  const uint32_t groups = point_grid(&a, bf16);
-  return push(out, kt.maxpool[bf16][!offsets_fit(a, bf16) ? 0 : a.k == 2 ? 1 : a.k == 3 ? 2 : 0], K_MAXPOOL, groups, 256, &a, sizeof(a));
+bool encode_maxpool(const KernelTable& kt, const PoolArgs& a, int bf16, std::vector<KernelLaunch>* out) {
+  if ((a.k == 2 || a.k == 3) && offsets_fit(a, bf16)) {
+    PoolWindowArgs w{a, PointPlace()};
+    const uint32_t groups = point_grid(a, bf16, &w.at);
+    return push(out, kt.maxpool_k[bf16][a.k - 2], K_MAXPOOL, groups, 256, &w, sizeof(w));
+  }
+  const size_t total = (size_t)a.Ho * a.Wo * (a.C / (bf16 ? 8 : 4));
+  return push(out, kt.maxpool[bf16], K_MAXPOOL, (uint32_t)((total + 255) / 256), 256, &a, sizeof(a));
 }
 bool encode_gavgpool(const KernelTable& kt, const PoolArgs& a, int bf16, std::vector<KernelLaunch>* out) {
   return push(out, kt.gavgpool[bf16], K_GAVGPOOL, (uint32_t)cdiv(a.C, 64), 256, &a, sizeof(a));

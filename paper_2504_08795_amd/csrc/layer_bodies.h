@@ -41,14 +41,19 @@ __device__ __forceinline__ ConvArgs conv_args_at(ConstPtr src) {
   return p;
 }
 template <typename Args>
-__device__ __forceinline__ Args args_at(ConstPtr src) {
-  Args a = grab<Args>(src);
+__device__ __forceinline__ void args_in_memory(Args& a) {
   a.x = in_memory(a.x);
   a.y = in_memory(a.y);
   if constexpr (!std::is_same<Args, PoolArgs>::value) {
     a.w = in_memory(a.w);
     a.bias = in_memory(a.bias);
   }
+}
+template <typename Args>
+__device__ __forceinline__ Args args_at(ConstPtr src) {
+  Args a = grab<Args>(src);
+  if constexpr (std::is_same<Args, DwWindowArgs>::value || std::is_same<Args, PoolWindowArgs>::value) args_in_memory(a.a);
+  else args_in_memory(a);
   return a;
 }
 
@@ -897,16 +902,26 @@ struct Point {
   bool ok;
 };
 template <bool BF16, typename Args>
-__device__ __forceinline__ Point point_of(const Args& a, const int L, const int tid) {
-  constexpr int VEC = BF16 ? 8 : 4;
-  const uint32_t idx = ((uint32_t)(L & 7) * a.per_xcd + (uint32_t)(L >> 3)) * 256u + (uint32_t)tid;
-  const uint32_t cvn = (uint32_t)a.C / VEC;
+__device__ __forceinline__ Point point_of(const Args& a, const PointPlace& at, const int L, const int tid) {
+  const uint32_t idx = ((uint32_t)(L & 7) * at.per_xcd + (uint32_t)(L >> 3)) * 256u + (uint32_t)tid;
+  const uint32_t cvn = (uint32_t)a.C / (BF16 ? 8 : 4);
+  const uint32_t m = at.mg_cv == kNoMagic ? idx / cvn : (uint32_t)fast_div((int)idx, at.mg_cv);
   Point t;
-  const uint32_t m = a.mg_cv == kNoMagic ? idx / cvn : (uint32_t)fast_div((int)idx, a.mg_cv);
   t.m = (int)m;
-  t.c0 = (int)(idx - m * cvn) * VEC;
+  t.c0 = (int)(idx - m * cvn) * (BF16 ? 8 : 4);
   t.ok = m < (uint32_t)a.Ho * (uint32_t)a.Wo;
-  t.oy = a.mg_wo == kNoMagic ? (int)(m / (uint32_t)a.Wo) : fast_div((int)m, a.mg_wo);
+  t.oy = at.mg_wo == kNoMagic ? (int)(m / (uint32_t)a.Wo) : fast_div((int)m, at.mg_wo);
+  t.ox = t.m - t.oy * a.Wo;
+  return t;
+}
+template <bool BF16, typename Args>
+__device__ __forceinline__ Point point_of(const Args& a, const uint32_t idx) {  // any filter size: threads in order
+  const uint32_t cvn = (uint32_t)a.C / (BF16 ? 8 : 4), m = idx / cvn;
+  Point t;
+  t.m = (int)m;
+  t.c0 = (int)(idx - m * cvn) * (BF16 ? 8 : 4);
+  t.ok = m < (uint32_t)a.Ho * (uint32_t)a.Wo;
+  t.oy = (int)(m / (uint32_t)a.Wo);
   t.ox = t.m - t.oy * a.Wo;
   return t;
 }
