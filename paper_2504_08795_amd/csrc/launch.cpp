@@ -425,7 +425,10 @@ bool encode_maxpool(const KernelTable& kt, const PoolArgs& a, int bf16, std::vec
 bool encode_gavgpool(const KernelTable& kt, const PoolArgs& a, int bf16, std::vector<KernelLaunch>* out) {
   return push(out, kt.gavgpool[bf16], K_GAVGPOOL, (uint32_t)cdiv(a.C, 64), 256, &a, sizeof(a));
 }
-bool encode_fc(const KernelTable& kt, const FcArgs& a, int bf16, std::vector<KernelLaunch>* out) {
+bool encode_fc(const KernelTable& kt, const FcArgs& layer, int bf16, std::vector<KernelLaunch>* out) {
+  FcArgs a = layer;
+  // Half of the 256 MB last cache or more: what is left of it at the next frame is little (fc_row has the measurements).
+  a.stream = (uint64_t)a.N * a.K * (bf16 ? 2 : 4) >= (128ull << 20) && a.K / (bf16 ? 8 : 4) > 2048;
   return push(out, kt.fc[bf16], K_FC, (uint32_t)cdiv(a.Ns, 4), 256, &a, sizeof(a));
 }
 bool encode_ingest(const KernelTable& kt, const float* x, void* y, int C, int Cs, int H, int W, int bf16, std::vector<KernelLaunch>* out) {

@@ -1071,7 +1071,10 @@ __device__ __forceinline__ void fc_row(const FcArgs& a, const int n, const int l
   float bias = a.bias[n];  // (behind the sums it would be one more trip to memory)
   // Short rows are latency-bound: four independent 16-byte weight loads in flight per lane, each with its own partial sum.
   // Long rows (VGG-16's first FC: 100 KB per wave, 411 MB in all) are pure streaming and run at the memory system's
-  // rate with one load per lane; more loads in flight slowed them down (measured: 84 -> 110 us), so they keep the plain loop.
+  // rate with one load per lane (bf16, rows half as long: two); more loads in flight slowed them down (measured: 84 -> 110 us).
+  // A matrix that the last cache cannot hold from one frame to the next is read past it (stream), so that it does not drive
+  // out the other layers' weights and tensors: VGG-16 on 128 CUs, fp32 570 -> 531 us a frame, bf16 316 -> 292 with one load
+  // per lane, 286 with two (fp32 with two: 552; a row per workgroup instead of per wave: 557 and 284).
   float acc4[4] = {0.f, 0.f, 0.f, 0.f};
   int v = lane;
   if (nvec <= 2048) {
@@ -1083,6 +1086,25 @@ __device__ __forceinline__ void fc_row(const FcArgs& a, const int n, const int l
       for (int u = 0; u < 4; ++u) xq[u] = *(const uint4*)(xb + (size_t)(v + 64 * u) * 16);
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
+        float wv[VEC], xv[VEC];
+        unpack<BF16>(wq[u], wv);
+        unpack<BF16>(xq[u], xv);
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) acc4[u] = fmaf(wv[i], xv[i], acc4[u]);
+      }
+    }
+  }
+  if (a.stream) {
+    constexpr int U = BF16 ? 2 : 1;
+    for (; v + 64 * (U - 1) < nvec; v += 64 * U) {
+      uint4 wq[U], xq[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        wq[u] = __builtin_bit_cast(uint4, __builtin_nontemporal_load((const u32x4 __attribute__((address_space(1)))*)(uintptr_t)(wrow + (size_t)(v + 64 * u) * 16)));
+#pragma unroll
+      for (int u = 0; u < U; ++u) xq[u] = *(const uint4*)(xb + (size_t)(v + 64 * u) * 16);
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
         float wv[VEC], xv[VEC];
         unpack<BF16>(wq[u], wv);
         unpack<BF16>(xq[u], xv);
