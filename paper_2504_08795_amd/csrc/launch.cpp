@@ -142,8 +142,9 @@ static ConvPlan plan_conv_wave16(int M, int N, int Kpad, int bf16, int nominal_c
   if (nb % tn) return pl;
   const int tiles = mt * (nb / tn);
   // bf16: 8 waves once K is 2048 or more (128 CUs, 4 -> 8 waves: 49 x 512 x 4608 6.4 -> 5.0 us, 49 x 512 x 2048 4.3 -> 3.9, 196 x
-  // 256 x 2304 4.68 -> 4.53; but 196 x 256 x 1024 3.64 -> 3.72).  The 32-pixel tiles gain nothing from it.
-  int nw = bf16 && S < 64 ? 4 : 8;
+  // 256 x 2304 4.68 -> 4.53; but 196 x 256 x 1024 3.64 -> 3.72), unless CUs get two workgroups anyway (208 tiles planned for 192
+  // CUs: ResNet-18 105.4 us with 4 waves, 107.1 with 8).  The 32-pixel tiles gain nothing from it.
+  int nw = bf16 && (S < 64 || tiles > nominal_cus) ? 4 : 8;
   while (nw > 2 && S / nw < 4) nw /= 2;
   if (force_nw) {  // second problem of a two-problem launch: the first one's kernel variant, whatever its own shape
     nw = force_nw;
