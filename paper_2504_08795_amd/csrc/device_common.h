@@ -9,18 +9,21 @@ namespace daris {
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
 // ---- element helpers ------------------------------------------------------------------------------------------
 
 __device__ __forceinline__ float bf16_bits_to_f32(uint32_t b) { return __uint_as_float(b << 16); }
 
-// float -> bfloat16 bits, round to nearest, ties to even; NaN stays a quiet NaN.
-__device__ __forceinline__ uint32_t f32_to_bf16_bits(float f) {
-  uint32_t u = __float_as_uint(f);
-  if ((u & 0x7fffffffu) > 0x7f800000u) return (u >> 16) | 0x40u;
-  u += 0x7fffu + ((u >> 16) & 1u);
-  return u >> 16;
+// float -> bfloat16 bits, round to nearest, ties to even; NaN stays a quiet NaN.  One v_cvt_pk_bf16_f32.
+__device__ __forceinline__ uint32_t pack_bf16_rne(float a, float b) {
+  f32x2 v;
+  v.x = a;
+  v.y = b;
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
 }
+__device__ __forceinline__ uint32_t f32_to_bf16_bits(float f) { return pack_bf16_rne(f, 0.f) & 0xffffu; }
 
 __device__ __forceinline__ float apply_act(float v, int act) {
   if (act == 1) v = fmaxf(v, 0.f);
@@ -125,10 +128,10 @@ template <bool BF16>
 __device__ __forceinline__ uint4 pack(const float* o) {
   uint4 v;
   if (BF16) {
-    v.x = f32_to_bf16_bits(o[0]) | (f32_to_bf16_bits(o[1]) << 16);
-    v.y = f32_to_bf16_bits(o[2]) | (f32_to_bf16_bits(o[3]) << 16);
-    v.z = f32_to_bf16_bits(o[4]) | (f32_to_bf16_bits(o[5]) << 16);
-    v.w = f32_to_bf16_bits(o[6]) | (f32_to_bf16_bits(o[7]) << 16);
+    v.x = pack_bf16_rne(o[0], o[1]);
+    v.y = pack_bf16_rne(o[2], o[3]);
+    v.z = pack_bf16_rne(o[4], o[5]);
+    v.w = pack_bf16_rne(o[6], o[7]);
   } else {
     v.x = __float_as_uint(o[0]); v.y = __float_as_uint(o[1]); v.z = __float_as_uint(o[2]); v.w = __float_as_uint(o[3]);
   }
@@ -145,16 +148,6 @@ __device__ __forceinline__ uint4 pack(const float* o) {
 // The first part of an activation is cut off (a rounded one could overflow), all other parts are rounded to nearest even;
 // the weights' parts are made at registration.  (An infinite operand gives
 // NaN; plain_sums in layer_bodies.h puts that right.)
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-
-__device__ __forceinline__ uint32_t pack_bf16_rne(float a, float b) {  // one v_cvt_pk_bf16_f32
-  f32x2 v;
-  v.x = a;
-  v.y = b;
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
-}
-
 struct Split8 {
   uint4 p[3];  // eight consecutive k: first, second, third parts
 };

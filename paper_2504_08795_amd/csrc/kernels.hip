@@ -46,8 +46,8 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restr
   for (int i = 0; i < 4; ++i) v[i] = apply_act(v[i], act);
   if (BF16) {
     uint2 out;
-    out.x = f32_to_bf16_bits(v[0]) | (f32_to_bf16_bits(v[1]) << 16);
-    out.y = f32_to_bf16_bits(v[2]) | (f32_to_bf16_bits(v[3]) << 16);
+    out.x = pack_bf16_rne(v[0], v[1]);
+    out.y = pack_bf16_rne(v[2], v[3]);
     put((uint16_t*)y + o, out);
   } else {
     put((float*)y + o, make_float4(v[0], v[1], v[2], v[3]));

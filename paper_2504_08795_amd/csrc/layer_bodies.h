@@ -300,8 +300,8 @@ __device__ __forceinline__ void conv_wave_body(const ConvArgs& p, const int mt, 
   auto compute = [&](int d) {
     uint4 a4 = keep_if(av[d], ar[d]);
     if (MODE == 2 && BF16) {  // four fp32 channels -> the 8-channel bf16 vector of the tap (same rounding as the conversion kernel)
-      a4.x = f32_to_bf16_bits(__uint_as_float(a4.x)) | (f32_to_bf16_bits(__uint_as_float(a4.y)) << 16);
-      a4.y = f32_to_bf16_bits(__uint_as_float(a4.z)) | (f32_to_bf16_bits(__uint_as_float(a4.w)) << 16);
+      a4.x = pack_bf16_rne(__uint_as_float(a4.x), __uint_as_float(a4.y));
+      a4.y = pack_bf16_rne(__uint_as_float(a4.z), __uint_as_float(a4.w));
       a4.z = 0u;
       a4.w = 0u;
     }
@@ -626,8 +626,8 @@ __device__ __forceinline__ void conv_wave_body(const ConvArgs& p, const int mt, 
         for (int i = 0; i < 4; ++i) val[i] = apply_act(val[i], p.act);
         if (BF16) {
           uint2 out;
-          out.x = f32_to_bf16_bits(val[0]) | (f32_to_bf16_bits(val[1]) << 16);
-          out.y = f32_to_bf16_bits(val[2]) | (f32_to_bf16_bits(val[3]) << 16);
+          out.x = pack_bf16_rne(val[0], val[1]);
+          out.y = pack_bf16_rne(val[2], val[3]);
           put((uint16_t*)p.y + o, out);
         } else {
           put((float*)p.y + o, make_float4(val[0], val[1], val[2], val[3]));
@@ -879,8 +879,8 @@ __device__ __forceinline__ void conv_wave16_body(const ConvArgs& p, const int mt
   for (int i = 0; i < 4; ++i) val[i] = apply_act(val[i], p.act);
   if (BF16) {
     uint2 out;
-    out.x = f32_to_bf16_bits(val[0]) | (f32_to_bf16_bits(val[1]) << 16);
-    out.y = f32_to_bf16_bits(val[2]) | (f32_to_bf16_bits(val[3]) << 16);
+    out.x = pack_bf16_rne(val[0], val[1]);
+    out.y = pack_bf16_rne(val[2], val[3]);
     put((uint16_t*)p.y + o, out);
   } else {
     put((float*)p.y + o, make_float4(val[0], val[1], val[2], val[3]));
