@@ -317,7 +317,7 @@ bool encode_conv(const KernelTable& kt, const ConvPlan& pl, const ConvArgs& a, i
   // 3: a pixel's channels are whole 64-byte rows and the plan cuts K in chunks of two steps: pixel operand through LDS
   const int mode = a.c_real > 0 ? 2 : (conv_rows_staged(a.Cin, bf16) && pl.staged ? 3 : (a.Cin % (bf16 ? 16 : 8) == 0 ? 0 : 1));
   if ((mode == 3 || !bf16) && (pl.S % 2 || pl.sz % 2 || pl.sw % 2)) return false;
-  if (mode == 2 && (a.Cin != (bf16 ? 8 : 4) || a.c_real > 4)) return false;
+  if (mode == 2 && (a.Cin != (bf16 ? 8 : 4) || a.c_real > 4 || (uint64_t)a.c_real * a.H * a.W * 4 >= (1ull << 31))) return false;
   if (pl.splitk > 1 && !a.ws) return false;
   if (pl.tm == 2) {
     // what conv_block_kernel assumes: whole 64-byte rows, K cut in chunks of two steps, one bit per filter tap, signed

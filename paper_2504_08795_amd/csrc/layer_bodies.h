@@ -180,17 +180,28 @@ __device__ __forceinline__ void conv_wave_body(const ConvArgs& p, const int mt, 
   // MODE 2 reads the caller's fp32 [C][H][W] input directly (no separate layout conversion launch): the padded channel
   // count equals VEC, so a lane's vector is one filter tap, gathered as four scalar loads from the channel planes.
   // Planes beyond the real channel count repeat the last real one; their weights are zero.
-  const size_t plane = (size_t)p.H * p.W;
-  const size_t po1 = (size_t)min(1, p.c_real - 1) * plane, po2 = (size_t)min(2, p.c_real - 1) * plane,
-               po3 = (size_t)min(3, p.c_real - 1) * plane;
+  // The loads go through a buffer descriptor: one 32-bit offset per tap for all planes, and 0 comes back where the tap lies
+  // outside the image, which takes half of the vector instructions out of the gather (12544 x 64 x 196
+  // on 128 CUs: fp32 11.2 -> 10.6 us, bf16 8.3 -> 7.5; 50176 x 64 x 27: 12.6 -> 12.1).
+  const int plane = p.H * p.W * 4;
+  const auto irsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p.x), 0, MODE == 2 ? p.c_real * plane : 0, 0x00027000);
+  const int po1 = min(1, p.c_real - 1) * plane, po2 = min(2, p.c_real - 1) * plane, po3 = min(3, p.c_real - 1) * plane;
+  auto tap_pixels = [&](bool ok, int iy, int ix) {  // MODE 2
+    const int o = ok ? (iy * p.W + ix) * 4 : -4;
+    return make_uint4(__builtin_amdgcn_raw_buffer_load_b32(irsrc, o, 0, 0), __builtin_amdgcn_raw_buffer_load_b32(irsrc, o, po1, 0),
+                      __builtin_amdgcn_raw_buffer_load_b32(irsrc, o, po2, 0), __builtin_amdgcn_raw_buffer_load_b32(irsrc, o, po3, 0));
+  };
+  int tap_y = 0, tap_x = 0;
   auto locate = [&]() {  // !ALIGNED: this lane's vector of step kcur
     const int k = kcur + lh * VEC;
     const int t = MODE == 2 ? k / VEC : fast_div(k, p.mg_cin), c = k - t * p.Cin;
     const int y = fast_div(t, p.mg_kw), x = t - y * p.kw;
     const int iy = iy0 + y, ix = ix0 + x;
     a_valid = a_ok && y < p.kh && (unsigned)iy < (unsigned)p.H && (unsigned)ix < (unsigned)p.W;
-    if (MODE == 2) ap = xb + (size_t)(a_valid ? iy * p.W + ix : 0) * 4;
-    else ap = xb + ((size_t)(a_valid ? iy * p.W + ix : 0) * p.Cin + c) * ES;
+    if (MODE == 2) {
+      tap_y = iy;
+      tap_x = ix;
+    } else ap = xb + ((size_t)(a_valid ? iy * p.W + ix : 0) * p.Cin + c) * ES;
   };
   if (ALIGNED) enter_tap();
   const unsigned char* wptr[TN];
@@ -204,16 +215,9 @@ __device__ __forceinline__ void conv_wave_body(const ConvArgs& p, const int mt, 
                // result is not touched (and not waited for) until D-1 later steps have been issued
   auto load = [&](int d) {
     if (!ALIGNED) locate();
-    if (MODE == 2) {
-      const float* q = (const float*)ap;
-      ar[d].x = __float_as_uint(q[0]);
-      ar[d].y = __float_as_uint(q[po1]);
-      ar[d].z = __float_as_uint(q[po2]);
-      ar[d].w = __float_as_uint(q[po3]);
-    } else {
-      ar[d] = *(const uint4*)ap;
-    }
-    av[d] = a_valid;
+    if (MODE == 2) ar[d] = tap_pixels(a_valid, tap_y, tap_x);
+    else ar[d] = *(const uint4*)ap;
+    av[d] = MODE == 2 || a_valid;
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
       br[d][j] = *(const uint4*)wptr[j];
@@ -327,17 +331,9 @@ __device__ __forceinline__ void conv_wave_body(const ConvArgs& p, const int mt, 
         const int y = fast_div(t, p.mg_kw), x = t - y * p.kw;
         const int iy = iy0 + y, ix = ix0 + x;
         const bool v = a_ok && y < p.kh && (unsigned)iy < (unsigned)p.H && (unsigned)ix < (unsigned)p.W;
-        const size_t px = (size_t)(v ? iy * p.W + ix : 0);
-        if (MODE == 2) {
-          const float* q = (const float*)xb + px;
-          aq[d][e].x = __float_as_uint(q[0]);
-          aq[d][e].y = __float_as_uint(q[po1]);
-          aq[d][e].z = __float_as_uint(q[po2]);
-          aq[d][e].w = __float_as_uint(q[po3]);
-        } else {
-          aq[d][e] = *(const uint4*)(xb + (px * p.Cin + (v ? c : 0)) * ES);  // always a valid address
-        }
-        aqv[d][e] = v;
+        if (MODE == 2) aq[d][e] = tap_pixels(v, iy, ix);
+        else aq[d][e] = *(const uint4*)(xb + ((size_t)(v ? iy * p.W + ix : 0) * p.Cin + (v ? c : 0)) * ES);  // always a valid address
+        aqv[d][e] = MODE == 2 || v;
       }
       load_wc(d);
       kcur += 16;

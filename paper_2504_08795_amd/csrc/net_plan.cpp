@@ -185,7 +185,7 @@ std::string build_plan(const daris_dnn& dnn, bool keep_activations, bool pair_la
     bool only_reader = true;
     for (int l = 1; l < n; ++l)
       if (net.layers[l].in_t == 0 || net.layers[l].res_t == 0) only_reader = false;
-    net.fuse_ingest = !keep_activations && fuse_ingest && L0.d.op == DARIS_OP_CONV && !L0.depthwise &&
+    net.fuse_ingest = !keep_activations && fuse_ingest && (uint64_t)dnn.in_c * dnn.in_h * dnn.in_w * 4 < (1ull << 31) && L0.d.op == DARIS_OP_CONV && !L0.depthwise &&
                       L0.in_t == 0 && L0.res_t < 0 && L0.pair_with < 0 && only_reader && net.ingest.Cs == vec && dnn.in_c <= 4;
   }
   const TensorInfo& fin = net.layers[n - 1].out;

@@ -61,3 +61,24 @@ def test_split_k_reduction(cin, h, w, cout, res, dtype):
     e_max, e_l2 = rel_err(got, oracle_logits(layers, wts, x, dtype))
     tol = {"fp32": 2e-5, "bf16": 1.5e-2}[dtype]
     assert e_max <= tol and e_l2 <= tol, (e_max, e_l2)
+
+
+@pytest.mark.parametrize("c", [1, 3])
+def test_bf16_rounding(c):
+    """fp32 inputs rounded to bf16 on their way in: ties both ways, the carry into the exponent, overflow, denormals, infinities."""
+    bits = np.array([0x3f808000, 0x3f818000, 0x3f807fff, 0x3f808001, 0x3fffffff, 0x7f7fffff, 0xff7fffff, 0x7f7f7fff, 0x7f800000, 0xff800000, 0x80000000,
+                     0x00018000, 0x00008000, 0x00008001, 0x807fffff, 0x00800000, 0xbf808000, 0xbf818000], np.uint32)
+    x = np.resize(bits, (c, 3, 6)).view(np.float32)
+    got, want = _run(N.Layer(op=N.OP_MAXPOOL, c_in=c, c_out=c, k=1, stride=1, pad=0, in_from=-1), (None, None), x, "bf16")
+    np.testing.assert_array_equal(got, want)
+
+
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("c,h,w,cout,k,s,p", [(1, 5, 4, 8, 3, 1, 1), (2, 9, 11, 40, 5, 2, 4), (4, 13, 7, 64, 7, 2, 3), (3, 40, 33, 96, 3, 2, 0), (3, 1, 1, 16, 1, 1, 0)])
+def test_first_convolution_reads_the_image(c, h, w, cout, k, s, p, dtype):
+    """One to four planes, padding wider than the window's centre, windows with most taps outside the image."""
+    rng = np.random.default_rng(9)
+    L = N.Layer(op=N.OP_CONV, c_in=c, c_out=cout, k=k, stride=s, pad=p, act=0, in_from=-1)
+    wt = rng.normal(0, (2.0 / (c * k * k)) ** 0.5, (cout, c, k, k)).astype(np.float32), rng.normal(0, 0.3, cout).astype(np.float32)
+    e_max, e_l2 = rel_err(*_run(L, wt, rng.normal(0, 1, (c, h, w)).astype(np.float32), dtype))
+    assert e_max <= TOL[dtype] and e_l2 <= TOL[dtype], (e_max, e_l2)
