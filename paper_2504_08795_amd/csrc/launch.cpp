@@ -122,8 +122,11 @@ static ConvPlan plan_conv_wave(int M, int N, int Kpad, int bf16, int step_align,
 }
 
 // 16-pixel tiles of tn 16-channel blocks, K split among the waves of a workgroup only.  Chosen for layers whose 32-row
-// plan needs a reduction launch; returns kernel == K_NONE when the shape does not fill three quarters of the nominal
-// partition either, or is too shallow to split eight (four) ways.
+// plan needs a reduction launch; returns kernel == K_NONE when a wave would walk more than 18 steps while the shape does not fill
+// three quarters of the nominal partition either, or when it is too shallow to split eight (four) ways.  Up to 18 steps the walk is
+// shorter than the reduction launch, however few the tiles (us with 32-pixel tiles and a reduction -> with 16-pixel tiles:
+// fp32 40 tiles of 7.5 steps 6.4 -> 3.9, 128 tiles of 16 steps planned for 192 CUs 6.7 -> 5.2, but of 36 steps 7.9 -> 8.5; bf16 of 8
+// steps 5.3 -> 3.8, of 18 steps 5.8 -> 4.9).
 static ConvPlan plan_conv_wave16(int M, int N, int Kpad, int bf16, int nominal_cus, int force_tn = 0, int force_nw = 0) {
   ConvPlan pl = ConvPlan();
   const int ks = bf16 ? 32 : 16;
@@ -148,7 +151,7 @@ static ConvPlan plan_conv_wave16(int M, int N, int Kpad, int bf16, int nominal_c
   while (nw > 2 && S / nw < 4) nw /= 2;
   if (force_nw) {  // second problem of a two-problem launch: the first one's kernel variant, whatever its own shape
     nw = force_nw;
-  } else if (tiles < nominal_cus * 3 / 4 || tiles > 4 * nominal_cus || S / nw < 2) {
+  } else if ((tiles < nominal_cus * 3 / 4 && S / nw > 18) || tiles > 4 * nominal_cus || S / nw < 2) {
     return pl;
   }
   pl.rows = 16;

@@ -4,6 +4,7 @@ average pooling around its batch of seven loads."""
 import numpy as np
 import pytest
 
+import paper_2504_08795_amd as D
 import workloads as wl
 from gpu_helpers import GpuNet, oracle_logits, rel_err
 
@@ -82,3 +83,21 @@ def test_first_convolution_reads_the_image(c, h, w, cout, k, s, p, dtype):
     wt = rng.normal(0, (2.0 / (c * k * k)) ** 0.5, (cout, c, k, k)).astype(np.float32), rng.normal(0, 0.3, cout).astype(np.float32)
     e_max, e_l2 = rel_err(*_run(L, wt, rng.normal(0, 1, (c, h, w)).astype(np.float32), dtype))
     assert e_max <= TOL[dtype] and e_l2 <= TOL[dtype], (e_max, e_l2)
+
+
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("cin,h,w,cout,k,cus", [(960, 7, 7, 160, 1, 128), (256, 3, 5, 24, 3, 128), (512, 7, 7, 512, 3, 192), (2048, 7, 7, 512, 1, 256), (128, 1, 1, 20, 1, 128)])
+def test_few_small_tiles(cin, h, w, cout, k, cus, dtype):
+    """16-pixel tiles that do not fill the partition: up to 18 steps a wave, and just past it (512 channels, 3x3, fp32)."""
+    rng = np.random.default_rng(10)
+    L = N.Layer(op=N.OP_CONV, c_in=cin, c_out=cout, k=k, stride=1, pad=k // 2, act=0, in_from=-1)
+    wt = rng.normal(0, (2.0 / (cin * k * k)) ** 0.5, (cout, cin, k, k)).astype(np.float32), rng.normal(0, 0.3, cout).astype(np.float32)
+    x = rng.normal(0, 1, (cin, h, w)).astype(np.float32)
+    with GpuNet([L], [wt], x.shape, dtype, plan_cus=cus) as g:
+        got = g.forward(x)
+        plan = D.daris_get_launch_plan(g.task, 0)
+    steps = cin * k * k // (16 if dtype == "fp32" else 32) // plan["nw"]
+    assert (plan["rows"] == 16) == (cin > 128 and steps <= 18), plan      # (the smallest one splits K in neither kernel)
+    e_max, e_l2 = rel_err(got, oracle_logits([L], [wt], x, dtype))
+    tol = {"fp32": 2e-5, "bf16": 6e-3}[dtype]  # sqrt(4608) * 2^-24 of the row norm and a margin; one bf16 rounding and a margin
+    assert e_max <= tol and e_l2 <= tol, (e_max, e_l2)
