@@ -637,7 +637,7 @@ __device__ __forceinline__ void conv_wave_body(const ConvArgs& p, const int mt, 
 //
 // A layer with few output pixels and many channels (the 14x14 and 7x7 stages of a ResNet) has too few 32 x 32 tiles to
 // fill a partition; the kernel above then splits K across workgroups and a second launch sums the partial tiles.  Here a
-// wave owns 16 pixels x (16 * TB) channels (v_mfma_f32_16x16x4_f32 / 16x16x32_bf16): at the same matrix rate there are
+// wave owns 16 pixels x (16 * TB) channels (v_mfma_f32_16x16x32_bf16): at the same matrix rate there are
 // two to four times as many tiles, so the partition fills with K split only among the NW waves of a workgroup, the sum
 // goes through LDS as before, and the reduction launch disappears.  One K step is 64 bytes of a pixel: lane (i, q) =
 // (pixel row i = lane % 16, quarter q = lane / 16) loads the 16 bytes at k = step * KS + q * VEC, and the weights were
