@@ -111,12 +111,19 @@ struct ConvPlan {
 // True when every pixel's channel vector is a whole number of 64-byte rows, the shape for which the convolution kernel
 // fetches the pixel operand in coalesced rows through LDS (chunks of two K steps).
 inline bool conv_rows_staged(int cin_stride, int bf16) { return cin_stride > 0 && (cin_stride * (bf16 ? 2 : 4)) % 64 == 0; }
+// Whether the kernel of 64 x 64 tiles can run an fp32 convolution of this geometry: it keeps one bit per filter tap in a word
+// and walks the rows of taps inside the image as a rectangle of them, and its byte offsets into the input and into the weights
+// of two channel blocks are signed 32-bit numbers.
+inline bool conv_block_takes(int H, int W, int cin_stride, int k, int pad, int Kpad) {
+  return k * k <= 31 && pad < k && conv_rows_staged(cin_stride, 0) && (uint64_t)(H + pad) * (uint64_t)W * (uint64_t)cin_stride * 4 < (1ull << 31) &&
+         (uint64_t)(Kpad / 8) * 3072 + 12288 < (1ull << 31);
+}
 // bf16 = 0/1.  Chooses tile shape, waves per workgroup and split-K from (M, N, Kpad) and the nominal partition size
 // (nominal_cus: how many CUs the grid is balanced for) only, so results do not depend on the partition a stage runs in.  step_align = 2 cuts K in whole chunks of two steps (for conv_rows_staged shapes), else 1.
 // cin_stride = the input tensor's channel stride: when it is a whole number of the 16-row kernel's K steps and the 32-row
 // plan would split K across workgroups, a 16-row plan that does not need to is chosen instead (cin_stride 0: never).
-// allow_block = false: no 64-pixel tiles (a convolution that shares its launch or computes its input on the fly).
-ConvPlan plan_conv(int M, int N, int Kpad, int bf16, int step_align, int cin_stride = 0, int nominal_cus = 128, bool allow_block = true);
+// allow_block = false: no 64-pixel tiles (a convolution that conv_block_takes refuses, shares its launch or computes its input on the fly).
+ConvPlan plan_conv(int M, int N, int Kpad, int bf16, int step_align, int cin_stride, int nominal_cus, bool allow_block);
 // Plan for a second convolution that is to share a launch with `first`: the same wave-tile kernel variant, K not split
 // across workgroups.  Returns a plan with kernel == K_NONE when that is not possible.
 ConvPlan plan_conv_like(const ConvPlan& first, int M, int N, int Kpad, int bf16, int step_align, int nominal_cus = 128);

@@ -323,10 +323,8 @@ bool encode_conv(const KernelTable& kt, const ConvPlan& pl, const ConvArgs& a, i
   if (mode == 2 && (a.Cin != (bf16 ? 8 : 4) || a.c_real > 4 || (uint64_t)a.c_real * a.H * a.W * 4 >= (1ull << 31))) return false;
   if (pl.splitk > 1 && !a.ws) return false;
   if (pl.tm == 2) {
-    // what conv_block_kernel assumes: whole 64-byte rows, K cut in chunks of two steps, one bit per filter tap, signed
-    // 32-bit byte offsets into the input and into the weights of two channel blocks
-    if (bf16 || mode != 3 || pl.tn != 2 || a.kh * a.kw > 31 || a.pad >= a.kh) return false;
-    if ((uint64_t)(a.H + a.pad) * a.W * a.Cin * 4 >= (1ull << 31) || (uint64_t)pl.S * 3072 + 12288 >= (1ull << 31)) return false;
+    // what conv_block_kernel assumes: whole 64-byte rows, K cut in chunks of two steps, and the limits of conv_block_takes
+    if (bf16 || mode != 3 || pl.tn != 2 || a.kh != a.kw || !conv_block_takes(a.H, a.W, a.Cin, a.kh, a.pad, a.Kpad)) return false;
     ConvArgs b = a;
     b.MT = cdiv(a.M, 64);
     b.mg_mt = tile_magic((uint64_t)b.MT * b.G, b.MT);

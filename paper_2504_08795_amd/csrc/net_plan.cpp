@@ -82,7 +82,8 @@ std::string build_plan(const daris_dnn& dnn, bool keep_activations, bool pair_la
           // the kernels divide pixel and k indices by Wo, Cin and kw with 32-bit multipliers: operands must stay small
           if ((uint64_t)(o.H * (uint64_t)o.W + 64) * (uint64_t)o.W >= (1ull << 32) || (uint64_t)(L.Kpad + 64) * (uint64_t)in.Cs >= (1ull << 32))
             return "layer " + std::to_string(l) + ": tensor too large for the kernels' index arithmetic";
-          L.cp = plan_conv(o.H * o.W, o.Cs, L.Kpad, net.bf16, staged_rows && conv_rows_staged(in.Cs, net.bf16) ? 2 : 1, small_tiles ? in.Cs : 0, plan_cus);
+          L.cp = plan_conv(o.H * o.W, o.Cs, L.Kpad, net.bf16, staged_rows && conv_rows_staged(in.Cs, net.bf16) ? 2 : 1, small_tiles ? in.Cs : 0, plan_cus,
+                           conv_block_takes(in.H, in.W, in.Cs, d.k, d.pad, L.Kpad));
           L.kernel_id = L.cp.kernel;
           net.ws_bytes = std::max(net.ws_bytes, L.cp.ws_bytes);
         } else {

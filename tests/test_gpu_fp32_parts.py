@@ -56,6 +56,16 @@ def test_block_tiles(case):
     assert err <= 5e-7, err
 
 
+@pytest.mark.parametrize("case", [(64, 112, 112, 64, 7, 1, 3, 128), (64, 56, 56, 64, 6, 1, 3, 32), (16, 64, 64, 64, 9, 1, 4, 32), (256, 56, 56, 256, 1, 1, 1, 128)],
+                         ids=lambda c: "x".join(map(str, c)))
+def test_large_layers_that_block_tiles_cannot_take(case):
+    """More filter taps than a word has bits, padding as wide as the window: enough tiles of 64 pixels, but another kernel."""
+    cin, h, w, cout, k, s, p, cus = case
+    err, plan = _conv(cin, h, w, cout, k, s, p, plan_cus=cus)
+    assert (plan["M"] + 63) // 64 * plan["NTn"] >= cus * 3 // 4
+    assert err <= 5e-7, err
+
+
 # (cin, h, w, cout, k, stride, pad, plan_cus): the kernel that it runs
 NONFINITE_CASES = [
     (3, 31, 29, 40, 3, 2, 1, 128),     # the network input as the caller gives it

@@ -1,0 +1,64 @@
+"""Every launch plan that the planner makes for a dense convolution is one that the encoder accepts: what the planner and the
+encoder each assume about a kernel must not differ, or a layer that some kernel could run is refused at registration.  The
+planner and the encoders are compiled into a small executable (`tests/host_plans/driver.cpp`), no GPU needed."""
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+CSRC = os.path.join(os.path.dirname(HERE), "paper_2504_08795_amd", "csrc")
+
+
+@pytest.fixture(scope="module")
+def plans(tmp_path_factory):
+    exe = str(tmp_path_factory.mktemp("plans") / "driver")
+    subprocess.check_call([os.environ.get("CXX", "g++"), "-O1", "-std=c++17", "-I/opt/rocm/include", "-o", exe, os.path.join(HERE, "host_plans", "driver.cpp"),
+                           os.path.join(CSRC, "net_plan.cpp"), os.path.join(CSRC, "launch.cpp")])
+
+    def run(shapes):
+        r = subprocess.run([exe], input="\n".join(" ".join(map(str, s)) for s in shapes) + "\n", capture_output=True, text=True, check=True)
+        return [ln.split(maxsplit=1) if ln.startswith("-1") else [int(v) for v in ln.split()] for ln in r.stdout.splitlines()]
+    return run
+
+
+# fp32: (c_in, h, w, c_out, k, stride, pad, plan CUs) -- enough tiles for the 64 x 64 kernel, which cannot take them
+NOT_FOR_BLOCKS = [
+    (64, 112, 112, 64, 7, 1, 3, 128),     # 49 taps
+    (512, 28, 28, 512, 7, 1, 3, 128),
+    (64, 56, 56, 64, 6, 1, 3, 32),        # 36 taps
+    (16, 64, 64, 64, 9, 1, 4, 32),        # 81 taps
+    (256, 56, 56, 256, 1, 1, 1, 128),     # padding as wide as the window
+    (256, 1500, 1500, 64, 3, 1, 1, 128),  # 2.3 GB of input
+]
+
+
+def test_layers_that_the_64_pixel_tiles_cannot_take_keep_a_kernel(plans):
+    for s, p in zip(NOT_FOR_BLOCKS, plans([(0,) + s for s in NOT_FOR_BLOCKS])):
+        assert p[0] == 1 and p[2] != 64, (s, p)
+    for s, p in zip([(64, 112, 112, 64, 5, 1, 2, 128)], plans([(0, 64, 112, 112, 64, 5, 1, 2, 128)])):
+        assert p[0] == 1 and p[2] == 64, (s, p)            # 25 taps: one that it takes
+
+
+def test_every_plan_can_be_encoded(plans):
+    rng = np.random.default_rng(17)
+    shapes = []
+    for i in range(4000):
+        k = int(rng.choice([1, 1, 2, 3, 3, 4, 5, 6, 7, 9, 11]))
+        big = i % 50 == 0                                   # inputs around 2 GiB
+        h, w = (int(v) for v in (rng.integers(900, 1700, 2) if big else 2 ** rng.uniform(0, 8, 2)))
+        cin = int(rng.choice([1, 3, 4, 16, 24, 32, 48, 64, 128, 256, 512, 960, 2048])) if not big else 256
+        cout = int(rng.choice([4, 8, 24, 64, 128, 192, 256, 512, 1000]))
+        p = int(rng.integers(0, k + 2))
+        if min(h, w) + 2 * p < k:
+            continue
+        shapes.append((i & 1, cin, h, w, cout, k, int(rng.integers(1, 4)), p, int(rng.choice([8, 32, 64, 96, 128, 192, 256]))))
+    got = plans(shapes)
+    assert len(got) == len(shapes) > 3000
+    refused = [s for s, p in zip(shapes, got) if p[0] == 0]
+    assert not refused, refused[:5]
+    for s, p in zip(shapes, got):
+        if p[0] == "-1":                                    # refused in words: only where the index arithmetic says so
+            assert "index arithmetic" in p[1], (s, p)
+    assert {p[2] for p in got if p[0] == 1} == {16, 32, 64} and sum(p[2] == 64 for p in got if p[0] == 1) > 50
