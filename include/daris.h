@@ -20,6 +20,8 @@
  *     themselves; daris_release_job, the hot path, does not.
  *   - Times are int64 nanoseconds.  In virtual-time mode they are positions on the library's virtual clock;
  *     in real-time mode they count from the library's epoch (set by daris_commit()).
+ *   - The time of a stage does not depend on its data but for one case: an fp32 convolution tile that meets an infinity, a NaN
+ *     or an overflow is computed twice, at most 2.5 times the layer's ordinary time.
  *   - Utilisations (eq. 3-7) are evaluated in Q32 fixed point: u = floor(mret * 2^32 / T).
  */
 #ifndef DARIS_H

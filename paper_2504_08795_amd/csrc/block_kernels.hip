@@ -101,13 +101,11 @@ __global__ __launch_bounds__(NW * 64) void conv_block_kernel(const ConvArgs) {
     woff += NP * 1024;
   };
 
-  f32x16 acc[2][2];
+  f32x16 acc[4];  // block (i, j) of 32 pixels x 32 channels at 2 i + j
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < 4; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+    for (int v = 0; v < 16; ++v) acc[i][v] = 0.f;
 
   uint4* const st = reinterpret_cast<uint4*>(red) + wave * STAGE_V;
   // A wave issues in order and the matrix pipe takes 32 cycles per instruction, so everything else a chunk needs is laid
@@ -162,7 +160,7 @@ __global__ __launch_bounds__(NW * 64) void conv_block_kernel(const ConvArgs) {
 #pragma unroll
     for (int n = 0; n < 24; ++n) {
       const int t = n >> 2, i = (n >> 1) & 1, j = n & 1;
-      acc[i][j] = mfma_bf16(cur[i].p[PA[t]], bw[s][j][PB[t]], acc[i][j]);
+      acc[2 * i + j] = mfma_bf16(cur[i].p[PA[t]], bw[s][j][PB[t]], acc[2 * i + j]);
       if (n == 0) get_rows();
       if (n < 4) load_row(s ^ 1, n);  // two chunks ahead (past the end of the slice: nothing is read, or never used)
       if (n == 3) advance();
@@ -198,16 +196,28 @@ __global__ __launch_bounds__(NW * 64) void conv_block_kernel(const ConvArgs) {
   // --- sum the NW partial tiles in wave order, BPP blocks (i, j) per pass; epilogue per quad of consecutive channels:
   // quad q of a block = elements 4q..4q+3 of [v][lane], i.e. pixel 8*(v/4) + 4*(lane/32) + v%4, channels lane%32 .. +3
   const bool own_epilogue = p.splitk == 1;
-#pragma unroll
-  for (int pass = 0; pass < 4 / BPP; ++pass) {
+  auto park = [&](int pass) {
     __syncthreads();  // the partial tiles reuse the staging buffers, then the pass before
 #pragma unroll
-    for (int b = 0; b < BPP; ++b) {
-      const int blk = pass * BPP + b;
+    for (int k = 0; k < BPP; ++k) {
 #pragma unroll
-      for (int w = 0; w < 16; ++w) red[(wave * BPP + b) * 1024 + w * 64 + lane] = acc[blk >> 1][blk & 1][w];
+      for (int w = 0; w < 16; ++w) red[(wave * BPP + k) * 1024 + w * 64 + lane] = acc[pass * BPP + k][w];
     }
+  };
+  park(0);
+  if (__builtin_expect(!all_finite(acc), 0)) spoil(red + wave * BPP * 1024, BPP * 16);
+  __syncthreads();
+  if (__builtin_expect(spoiled(red[lane % NW * BPP * 1024 + lane]), 0)) {  // every thread of the workgroup or none
+    plain_products<3, 32, 2, 2>(p, DwFusedArgs(), m0, nb0, sbeg, 2 * nchunks, acc);
+    park(0);
     __syncthreads();
+  }
+#pragma unroll
+  for (int pass = 0; pass < 4 / BPP; ++pass) {
+    if (pass > 0) {
+      park(pass);
+      __syncthreads();
+    }
     const int b = BPP == 1 ? 0 : tid >> 8;
 #pragma unroll
     for (int q = tid & 255; q < 256; q += NT) {
@@ -227,10 +237,6 @@ __global__ __launch_bounds__(NW * 64) void conv_block_kernel(const ConvArgs) {
         for (int w = 0; w < NW; ++w) {
           const float4 t = *(const float4*)&red[(w * BPP + b) * 1024 + e];
           val[0] += t.x; val[1] += t.y; val[2] += t.z; val[3] += t.w;
-        }
-        if (__builtin_expect(any_nan(make_float4(val[0], val[1], val[2], val[3])), 0)) {
-          const float4 s = plain_sums<3, 32>(p, DwFusedArgs(), mm, n, s_wg0 * KS, s_wg1 * KS);
-          val[0] = s.x; val[1] = s.y; val[2] = s.z; val[3] = s.w;
         }
         if (!own_epilogue) {  // partial sums of this K slice; splitk_reduce_kernel finishes the layer
           put(p.ws + (size_t)zi * p.M * p.Cout + o, make_float4(val[0], val[1], val[2], val[3]));

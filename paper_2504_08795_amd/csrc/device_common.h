@@ -147,7 +147,7 @@ __device__ __forceinline__ uint4 pack(const float* o) {
 // cycles what v_mfma_f32_32x32x2_f32 does in 512, so the six take 3/8 of the matrix time.  Accumulation is fp32 as before.
 // The first part of an activation is cut off (a rounded one could overflow), all other parts are rounded to nearest even;
 // the weights' parts are made at registration.  (An infinite operand gives
-// NaN; plain_sums in layer_bodies.h puts that right.)
+// NaN; plain_products in layer_bodies.h puts that right.)
 struct Split8 {
   uint4 p[3];  // eight consecutive k: first, second, third parts
 };

@@ -57,50 +57,109 @@ __device__ __forceinline__ Args args_at(ConstPtr src) {
   return a;
 }
 
-// Sums over k in [k0, k1) for pixel m, channels n..n+3 in plain fp32 arithmetic, for the sums that the products in three
-// parts leave as NaN: an infinite operand, or parts that overflow, where the fp32 product does not.  (Rare, so it is slow: one
-// thread walks k; the weights are put together from their parts, which is exact.)  MODE as in conv_wave_body, R = channels
-// of a weight block.
-__device__ __forceinline__ bool any_nan(const float4& v) { return __builtin_isunordered(v.x, v.y) | __builtin_isunordered(v.z, v.w); }
-template <int MODE, int R>
-__device__ __forceinline__ float4 plain_sums(const ConvArgs& p, const DwFusedArgs& dwf, const int m, const int n, const int k0, const int k1) {
-  constexpr int CK = R == 16 ? 32 : 16;  // k of a chunk of weights
+// ---- tiles in plain fp32 arithmetic ---------------------------------------------------------------------------------
+//
+// An infinite operand, or parts that overflow where the fp32 product does not, leave the products in three parts as NaN or
+// infinite.  A wave that finds such a value in its partial tile (all_finite) spoils the whole tile, so every thread
+// of the workgroup meets a NaN in the sums that it reads anyway, and the workgroup walks its K slice a second time on the fp32
+// matrix instructions (plain_products).  Nothing else in the launch depends on the data, so a launch in which every tile is
+// taken twice is the longest there can be: the second walk, 8/3 of the first one's matrix time and with one chunk in flight,
+// is bounded by the same K.
+// The look at the partial tile is one instruction for two values (|a| |b| summed up: infinite or NaN as soon as one of them
+// is, or both are past 2^63), and only then one for each; it follows the stores of the tile to LDS, in whose shadow it runs.
+template <int N, typename Acc>
+__device__ __forceinline__ bool all_finite(const Acc (&acc)[N]) {  // over the whole wave
+  constexpr int V = sizeof(Acc) / sizeof(float);
+  float t[2] = {0.f, 0.f};
+#pragma unroll
+  for (int j = 0; j < N; ++j)
+#pragma unroll
+    for (int v = 0; v < V; v += 2) t[(v >> 1) & 1] = fmaf(__builtin_fabsf(acc[j][v]), __builtin_fabsf(acc[j][v + 1]), t[(v >> 1) & 1]);
+  if (__builtin_expect(__ballot(!(t[0] + t[1] < INFINITY)) == 0, 1)) return true;
+  float s = 0.f;
+#pragma unroll
+  for (int j = 0; j < N; ++j)
+#pragma unroll
+    for (int v = 0; v < V; ++v) s += __builtin_fabsf(acc[j][v]);
+  return __ballot(!(s < INFINITY)) == 0;
+}
+// The wave's partial tile, `words` floats a lane from `tile` on, becomes NaN.
+__device__ __forceinline__ void spoil(float* const tile, const int words) {
+#pragma unroll 1
+  for (int i = 0; i < words; ++i) tile[64 * i + (threadIdx.x & 63)] = __builtin_nanf("");
+}
+__device__ __forceinline__ bool spoiled(const float v) { return __ballot(__builtin_isnan(v)) != 0; }
+
+// Pixel operand at k .. k + 3 (one filter tap, channel strides being multiples of four) of pixel m; MODE as in conv_wave_body.
+template <int MODE>
+__device__ __forceinline__ float4 pixel_quad(const ConvArgs& p, const DwFusedArgs& dwf, const int m, const int k) {
   const int y = fast_div(m, p.mg_wo), x = m - y * p.Wo;
-  const unsigned char* const wn = (const unsigned char*)p.w + (size_t)(n / R) * (p.Kpad / CK) * 3072 + (n % R) * 16;
-  float s[4] = {0.f, 0.f, 0.f, 0.f};
+  const int tap = MODE == 2 ? k >> 2 : fast_div(k, p.mg_cin), c = MODE == 2 ? 0 : k - tap * p.Cin;
+  const int ky = fast_div(tap, p.mg_kw), kx = tap - ky * p.kw;
+  const int iy = y * p.stride - p.pad + ky, ix = x * p.stride - p.pad + kx;
+  float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (m >= p.M || ky >= p.kh || (unsigned)iy >= (unsigned)p.H || (unsigned)ix >= (unsigned)p.W) return v;
+  if constexpr (MODE == 4) {
+    v = *(const float4*)(dwf.bias + c);
 #pragma unroll 1
-  for (int k = k0; k < k1; ++k) {
-    const int tap = MODE == 2 ? k >> 2 : fast_div(k, p.mg_cin), c = MODE == 2 ? k & 3 : k - tap * p.Cin;
-    const int ky = fast_div(tap, p.mg_kw), kx = tap - ky * p.kw;
-    if (ky >= p.kh || (MODE == 2 && c >= p.c_real)) continue;  // padding of K
-    const int iy = y * p.stride - p.pad + ky, ix = x * p.stride - p.pad + kx;
-    float v = 0.f;
-    if ((unsigned)iy < (unsigned)p.H && (unsigned)ix < (unsigned)p.W) {
-      if constexpr (MODE == 4) {
-        v = dwf.bias[c];
-#pragma unroll 1
-        for (int t = 0; t < 9; ++t) {
-          const int jy = iy * dwf.stride - 1 + t / 3, jx = ix * dwf.stride - 1 + t % 3;
-          if ((unsigned)jy < (unsigned)dwf.H && (unsigned)jx < (unsigned)dwf.W)
-            v = fmaf(((const float*)p.x)[(size_t)(jy * dwf.W + jx) * p.Cin + c], ((const float*)dwf.w)[(size_t)t * p.Cin + c], v);
-        }
-        v = apply_act(v, dwf.act);
-      } else if constexpr (MODE == 2) {
-        v = ((const float*)p.x)[(size_t)c * p.H * p.W + iy * p.W + ix];
-      } else {
-        v = ((const float*)p.x)[(size_t)(iy * p.W + ix) * p.Cin + c];
-      }
+    for (int t = 0; t < 9; ++t) {
+      const int jy = iy * dwf.stride - 1 + t / 3, jx = ix * dwf.stride - 1 + t % 3;
+      if ((unsigned)jy >= (unsigned)dwf.H || (unsigned)jx >= (unsigned)dwf.W) continue;
+      const float4 in = *(const float4*)((const float*)p.x + (size_t)(jy * dwf.W + jx) * p.Cin + c), w = *(const float4*)((const float*)dwf.w + (size_t)t * p.Cin + c);
+      v.x = fmaf(in.x, w.x, v.x); v.y = fmaf(in.y, w.y, v.y); v.z = fmaf(in.z, w.z, v.z); v.w = fmaf(in.w, w.w, v.w);
     }
-    const unsigned char* const wk = wn + (size_t)(k / CK) * 3072 + (k % CK / 8) * R * 16 + (k % 8) * 2;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      float w[3];
-#pragma unroll
-      for (int q = 0; q < 3; ++q) w[q] = bf16_bits_to_f32(*(const uint16_t*)(wk + q * 1024 + i * 16));
-      s[i] = fmaf(v, (w[2] + w[1]) + w[0], s[i]);
-    }
+    v.x = apply_act(v.x, dwf.act); v.y = apply_act(v.y, dwf.act); v.z = apply_act(v.z, dwf.act); v.w = apply_act(v.w, dwf.act);
+  } else if constexpr (MODE == 2) {
+    const float* const at = (const float*)p.x + (size_t)iy * p.W + ix;
+    const size_t plane = (size_t)p.H * p.W;
+    v.x = at[0];
+    if (p.c_real > 1) v.y = at[plane];
+    if (p.c_real > 2) v.z = at[2 * plane];
+    if (p.c_real > 3) v.w = at[3 * plane];
+  } else {
+    v = *(const float4*)((const float*)p.x + (size_t)(iy * p.W + ix) * p.Cin + c);
   }
-  return make_float4(s[0], s[1], s[2], s[3]);
+  return v;
+}
+
+// acc[i * TN + j] = the wave's partial tile of pixels m0 + R i .. and channel blocks nb0 + j over K steps [s0, s0 + nsteps), R = 32
+// or 16.  The weights are put together from their parts, which is exact; a lane's eight k of a chunk go through the matrix
+// pipe one at a time.
+template <int MODE, int R, int TM, int TN, typename Acc>
+__device__ __forceinline__ void plain_products(const ConvArgs& p, const DwFusedArgs& dwf, const int m0, const int nb0, const int s0, const int nsteps, Acc (&acc)[TM * TN]) {
+  constexpr int CK = R == 16 ? 32 : 16;  // k of a chunk = two steps of the plan
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int i = 0; i < TM * TN; ++i) acc[i] = Acc(0.f);
+  const unsigned char* const wb = (const unsigned char*)p.w + (size_t)nb0 * (p.S >> 1) * 3072 + lane * 16;
+#pragma unroll 1
+  for (int c = s0 >> 1; c < (s0 + nsteps) >> 1; ++c) {
+    float a[TM][8], b[TN][8];
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+      float w[3][8];
+#pragma unroll
+      for (int q = 0; q < 3; ++q) unpack<true>(*(const uint4*)(wb + ((size_t)j * (p.S >> 1) + c) * 3072 + q * 1024), w[q]);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) b[j][e] = (w[2][e] + w[1][e]) + w[0][e];
+    }
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const float4 v = pixel_quad<MODE>(p, dwf, m0 + R * i + lane % R, c * CK + 8 * (lane / R) + 4 * h);
+        a[i][4 * h] = v.x; a[i][4 * h + 1] = v.y; a[i][4 * h + 2] = v.z; a[i][4 * h + 3] = v.w;
+      }
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+          if constexpr (R == 16) acc[i * TN + j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][e], b[j][e], acc[i * TN + j], 0, 0, 0);
+          else acc[i * TN + j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i][e], b[j][e], acc[i * TN + j], 0, 0, 0);
+        }
+  }
 }
 
 // ---- wave-tile implicit GEMM ---------------------------------------------------------------------------------------
@@ -553,38 +612,43 @@ __device__ __forceinline__ void conv_wave_body(const ConvArgs& p, const int mt, 
   }
 
   // --- sum the NW partial tiles in wave order; tile element e = (j*16 + v)*64 + lane --------------------------------
+  auto park = [&]() {
 #pragma unroll
-  for (int j = 0; j < TN; ++j)
+    for (int j = 0; j < TN; ++j)
 #pragma unroll
-    for (int v = 0; v < 16; ++v) red[wave * TILE + (j * 16 + v) * 64 + lane] = acc[j][v];
-  __syncthreads();
+      for (int v = 0; v < 16; ++v) red[wave * TILE + (j * 16 + v) * 64 + lane] = acc[j][v];
+  };
   // --- epilogue per channel quad: pixel m0 + 8*(v/4) + 4*(lane/32) + v%4, channels 32*(nb0+j) + lane%32 .. +3 ---------
   float4 sums[RQ];
+  auto add_up = [&]() {
 #pragma unroll
-  for (int r = 0; r < RQ; ++r) {
-    const int e = 4 * (tid + r * NT);
-    if (QUADS % NT != 0 && e >= TILE) {  // (the threads past the tile: 32-channel tiles of 8 waves)
-      sums[r] = make_float4(0.f, 0.f, 0.f, 0.f);
-      continue;
-    }
-    sums[r] = *(const float4*)&red[e];
-#pragma unroll
-    for (int w = 1; w < NW; ++w) {
-      const float4 t = *(const float4*)&red[w * TILE + e];
-      sums[r].x += t.x; sums[r].y += t.y; sums[r].z += t.z; sums[r].w += t.w;
-    }
-  }
-  if constexpr (!BF16) {
-    bool nan = false;
-#pragma unroll
-    for (int r = 0; r < RQ; ++r) nan |= any_nan(sums[r]);
-    if (__builtin_expect(nan, 0)) {  // (out of the way: a launch fetches its code anew, and a longer path costs 0.2 us)
-#pragma unroll
-      for (int r = 0; r < RQ; ++r) {
-        const int e = 4 * (tid + r * NT), j = e >> 10, v = (e >> 6) & 15, l = e & 63;
-        const int mm = m0 + (v >> 2) * 8 + (l >> 5) * 4 + (v & 3), n = (nb0 + j) * 32 + (l & 31);
-        if (any_nan(sums[r]) && mm < p.M && n < p.Cout) sums[r] = plain_sums<MODE, 32>(p, dwf, mm, n, s_wg0 * KS, s_wg1 * KS);
+    for (int r = 0; r < RQ; ++r) {
+      const int e = 4 * (tid + r * NT);
+      if (QUADS % NT != 0 && wave >= QUADS / 64) {  // (the waves past the tile: 32-channel tiles of 8 waves)
+        sums[r] = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (!BF16) sums[r].x = red[lane % NW * TILE + lane];  // ... look whether one of the partial tiles is spoiled
+        continue;
       }
+      sums[r] = *(const float4*)&red[e];
+#pragma unroll
+      for (int w = 1; w < NW; ++w) {
+        const float4 t = *(const float4*)&red[w * TILE + e];
+        sums[r].x += t.x; sums[r].y += t.y; sums[r].z += t.z; sums[r].w += t.w;
+      }
+    }
+  };
+  park();
+  if constexpr (!BF16)
+    if (__builtin_expect(!all_finite(acc), 0)) spoil(red + wave * TILE, 16 * TN);
+  __syncthreads();
+  add_up();
+  if constexpr (!BF16) {
+    if (__builtin_expect(spoiled(sums[0].x), 0)) {  // every thread of the workgroup or none (out of the way: a launch fetches its code anew, and a longer path costs 0.2 us)
+      __syncthreads();
+      plain_products<MODE, 32, 1, TN>(p, dwf, m0, nb0, sbeg, nsteps, acc);
+      park();
+      __syncthreads();
+      add_up();
     }
   }
 #pragma unroll
@@ -841,21 +905,41 @@ __device__ __forceinline__ void conv_wave16_body(const ConvArgs& p, const int mt
   }
 
   // partial tiles of the NW waves summed in wave order; accumulator v of lane l is pixel 4 * (l / 16) + v, channel l % 16
+  auto park = [&]() {
+#pragma unroll
+    for (int j = 0; j < TB; ++j)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) red[wave * TILE + (j * 4 + v) * 64 + lane] = acc[j][v];
+  };
+  float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
+  auto add_up = [&]() {
+    if (wave >= QUADS / 64) {
+      if (!BF16) sum.x = red[lane % NW * TILE + lane];  // no part in the epilogue, but in the second walk where a tile is spoiled
+      return;
+    }
+    sum = *(const float4*)&red[qe];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) {
+      const float4 t = *(const float4*)&red[w * TILE + qe];
+      sum.x += t.x; sum.y += t.y; sum.z += t.z; sum.w += t.w;
+    }
+  };
   __syncthreads();  // the partial tiles reuse the LDS of every wave's staging buffer
-#pragma unroll
-  for (int j = 0; j < TB; ++j)
-#pragma unroll
-    for (int v = 0; v < 4; ++v) red[wave * TILE + (j * 4 + v) * 64 + lane] = acc[j][v];
-  __syncthreads();
-  if (!q_ok) return;
-  float4 sum = *(const float4*)&red[qe];
-#pragma unroll
-  for (int w = 1; w < NW; ++w) {
-    const float4 t = *(const float4*)&red[w * TILE + qe];
-    sum.x += t.x; sum.y += t.y; sum.z += t.z; sum.w += t.w;
-  }
+  park();
   if constexpr (!BF16)
-    if (__builtin_expect(any_nan(sum), 0)) sum = plain_sums<3, 16>(p, DwFusedArgs(), qm, qn, s_wg0 * KS, s_wg1 * KS);
+    if (__builtin_expect(!all_finite(acc), 0)) spoil(red + wave * TILE, 4 * TB);
+  __syncthreads();
+  add_up();
+  if constexpr (!BF16) {
+    if (__builtin_expect(spoiled(sum.x), 0)) {
+      __syncthreads();
+      plain_products<3, 16, 1, TB>(p, DwFusedArgs(), m0, nb0, sbeg, nsteps, acc);
+      park();
+      __syncthreads();
+      add_up();
+    }
+  }
+  if (!q_ok) return;
   const size_t o = (size_t)qm * p.Cout + qn;
   if (!own_epilogue) {
     put(p.ws + (size_t)zi * p.M * p.Cout + o, sum);

@@ -1,6 +1,8 @@
 """fp32 convolutions whose products run on the bf16 matrix instructions in three parts per operand: as exact as fp32
 arithmetic against float64, over the whole exponent range in which the third part is representable; and the kernel that
 takes 64 x 64 tiles per wave at the edges of its tiles, taps, K slices and wave counts."""
+import time
+
 import numpy as np
 import pytest
 import torch
@@ -98,3 +100,46 @@ def test_infinities_and_nan_pass_as_in_fp32_arithmetic(case):
     assert np.array_equal(got[np.isinf(want)], want[np.isinf(want)])
     for part in (np.isfinite(want) & ~big, np.isfinite(want) & big):
         assert np.linalg.norm(got[part] - want[part]) <= 5e-7 * max(np.linalg.norm(want[part]), 1e-30)
+
+
+def test_infinities_and_nan_through_a_fused_depthwise_layer():
+    """Expansion, depthwise and projection with the depthwise layer inside the projection's launch; all weights positive, so
+    that an infinite pixel stays one."""
+    rng = np.random.default_rng(12)
+    layers = [N.Layer(op=N.OP_CONV, c_in=3, c_out=32, k=1, stride=1, pad=0, act=0, in_from=-1),
+              N.Layer(op=N.OP_CONV, c_in=32, c_out=32, k=3, stride=1, pad=1, groups=32, act=0, in_from=0),
+              N.Layer(op=N.OP_CONV, c_in=32, c_out=16, k=1, stride=1, pad=0, act=0, in_from=1)]
+    wts = [((rng.random((L.c_out, L.c_in // L.groups, L.k, L.k)) * 0.1 + 0.01).astype(np.float32), rng.normal(0, 0.3, L.c_out).astype(np.float32)) for L in layers]
+    x = rng.normal(0, 1, (3, 56, 57)).astype(np.float32)
+    x[0, 5, 6], x[1, 30, 56], x[2, 55, 20] = np.inf, -np.inf, np.nan
+    with GpuNet(layers, wts, x.shape, "fp32") as g:
+        assert D.daris_get_launch_plan(g.task, 1)["pair_with"] == 2      # the case runs the kernel it names
+        got = g.forward(x).astype(np.float64).reshape(16, -1)
+    want = torch.from_numpy(x).double()[None]
+    for L, (w, b) in zip(layers, wts):
+        want = torch.nn.functional.conv2d(want, torch.from_numpy(w).double(), torch.from_numpy(b).double(), stride=L.stride, padding=L.pad, groups=L.groups)
+    want = want.numpy().reshape(16, -1)
+    fin = np.isfinite(want)
+    assert np.array_equal(np.isnan(got), np.isnan(want)) and np.isinf(want).any() and np.isnan(want).any()
+    assert np.array_equal(got[np.isinf(want)], want[np.isinf(want)])
+    assert np.linalg.norm(got[fin] - want[fin]) <= 2e-6 * np.linalg.norm(want[fin])      # three layers of at most 32 terms in fp32
+
+
+def test_the_time_of_a_layer_is_bounded_whatever_its_input():
+    """Stages are not preempted, so no frame may take a layer far longer than others do.  A layer whose sums all have to be
+    taken again in fp32 arithmetic takes 2.4 times as long (the matrix instructions: 8/3); the bound leaves room for noise."""
+    cin = cout = 512
+    rng = np.random.default_rng(13)
+    L = [N.Layer(op=N.OP_CONV, c_in=cin, c_out=cout, k=3, stride=1, pad=1, act=0, in_from=-1)]
+    wt = rng.normal(0, 0.02, (cout, cin, 3, 3)).astype(np.float32), np.zeros(cout, np.float32)
+    best = {}
+    with GpuNet(L, [wt], (cin, 28, 28), "fp32") as g:
+        y = torch.zeros(g.n_out, device="cuda")
+        for what, v in (("ordinary", 1.0), ("infinite", float("inf")), ("nan", float("nan"))):
+            x = torch.randn((cin, 28, 28), device="cuda") * v
+            torch.cuda.synchronize()
+            for _ in range(10):
+                t0 = time.perf_counter()
+                D.daris_forward(g.task, x, y, g.parts[0])
+                best[what] = min(best.get(what, 1.0), time.perf_counter() - t0)
+    assert best["infinite"] < 4 * best["ordinary"] and best["nan"] < 4 * best["ordinary"], best
