@@ -21,7 +21,7 @@
  *   - Times are int64 nanoseconds.  In virtual-time mode they are positions on the library's virtual clock;
  *     in real-time mode they count from the library's epoch (set by daris_commit()).
  *   - The time of a stage does not depend on its data but for one case: an fp32 convolution tile that meets an infinity, a NaN
- *     or an overflow is computed twice, at most 2.5 times the layer's ordinary time.
+ *     or an overflow, or nothing but sums below 2^-103, is computed twice: less than four times the layer's ordinary time.
  *   - Utilisations (eq. 3-7) are evaluated in Q32 fixed point: u = floor(mret * 2^32 / T).
  */
 #ifndef DARIS_H
@@ -117,7 +117,10 @@ typedef struct daris_layer {
 typedef struct daris_dnn {
   int32_t n_layers;
   int32_t in_c, in_h, in_w;
-  int32_t dtype; /* DARIS_FP32: fp32 storage, products of full fp32 operands (three bf16 parts each), fp32 accumulate.
+  int32_t dtype; /* DARIS_FP32: fp32 activations, fp32 accumulate.  A dense convolution forms its products from three bf16
+                    parts per operand, which hold a number of 2^-110 and more in full (a smaller one to 2^-134): each product
+                    within 2^-23 of the exact one.  Sums that are not finite, and tiles whose sums are all below 2^-103, are
+                    taken again with fp32 products.  All other layers: fp32 arithmetic.
                     DARIS_BF16: bf16 weights/activations, fp32 accumulate */
   const daris_layer* layers;
 } daris_dnn;

@@ -205,7 +205,7 @@ __global__ __launch_bounds__(NW * 64) void conv_block_kernel(const ConvArgs) {
     }
   };
   park(0);
-  if (__builtin_expect(!all_finite(acc), 0)) spoil(red + wave * BPP * 1024, BPP * 16);
+  spoil_unless_in_range(acc, red + wave * BPP * 1024, BPP * 16);
   __syncthreads();
   if (__builtin_expect(spoiled(red[lane % NW * BPP * 1024 + lane]), 0)) {  // every thread of the workgroup or none
     plain_products<3, 32, 2, 2>(p, DwFusedArgs(), m0, nb0, sbeg, 2 * nchunks, acc);

@@ -140,14 +140,16 @@ __device__ __forceinline__ uint4 pack(const float* o) {
 
 // ---- fp32 products on the bf16 matrix instructions ---------------------------------------------------------------------
 //
-// An fp32 number has 24 significant bits, a bf16 number 8: every finite fp32 number is the exact sum of three bf16 numbers
-// x1 + x2 + x3, each at most 2^-7 of the one before.  A product of two such sums has nine terms, each exact in fp32; the
-// six largest (x1y1, x1y2, x2y1, x1y3, x2y2, x3y1) leave out at most 2^-23 of |xy|, with no bias (measured on sums of 4608
-// terms against float64: the error of the plain fp32 instruction is the larger one).  v_mfma_f32_32x32x16_bf16 does in 32
+// An fp32 number has 24 significant bits, a bf16 number 8 and the same exponents: a finite fp32 number of 2^-110 and more is the
+// exact sum of three bf16 numbers x1 + x2 + x3, each at most 2^-7 of the one before; below that the third part, and from 2^-118
+// on the second, is rounded to the smallest bf16 number (2^-133), so that up to 2^-134 is lost.  A product of two such sums has
+// nine terms, each exact in fp32; the six largest (x1y1, x1y2, x2y1, x1y3, x2y2, x3y1) leave out at most 2^-23 of |xy|, with no
+// bias, where the fp32 instruction loses nothing before it adds (but measured on sums of 4608 terms against float64 its error is
+// the larger one: 4.2e-7 against 3.6e-7).  v_mfma_f32_32x32x16_bf16 does in 32
 // cycles what v_mfma_f32_32x32x2_f32 does in 512, so the six take 3/8 of the matrix time.  Accumulation is fp32 as before.
 // The first part of an activation is cut off (a rounded one could overflow), all other parts are rounded to nearest even;
 // the weights' parts are made at registration.  (An infinite operand gives
-// NaN; plain_products in layer_bodies.h puts that right.)
+// NaN; plain_products in layer_bodies.h puts that right, and a tile of pixels so small that they lose bits.)
 struct Split8 {
   uint4 p[3];  // eight consecutive k: first, second, third parts
 };

@@ -60,33 +60,33 @@ __device__ __forceinline__ Args args_at(ConstPtr src) {
 // ---- tiles in plain fp32 arithmetic ---------------------------------------------------------------------------------
 //
 // An infinite operand, or parts that overflow where the fp32 product does not, leave the products in three parts as NaN or
-// infinite.  A wave that finds such a value in its partial tile (all_finite) spoils the whole tile, so every thread
-// of the workgroup meets a NaN in the sums that it reads anyway, and the workgroup walks its K slice a second time on the fp32
-// matrix instructions (plain_products).  Nothing else in the launch depends on the data, so a launch in which every tile is
-// taken twice is the longest there can be: the second walk, 8/3 of the first one's matrix time and with one chunk in flight,
-// is bounded by the same K.
-// The look at the partial tile is one instruction for two values (|a| |b| summed up: infinite or NaN as soon as one of them
-// is, or both are past 2^63), and only then one for each; it follows the stores of the tile to LDS, in whose shadow it runs.
+// infinite, and pixels so small that their third part falls below the smallest bf16 number leave sums below 2^-103 short of
+// bits.  A wave that finds its partial tile not finite, or all of it below 2^-103 (and not all of it 0), spoils the whole tile, so
+// every thread of the workgroup meets a NaN in the sums that it reads anyway, and the workgroup walks its K slice a second time
+// on the fp32 matrix instructions (plain_products).  Nothing else in the launch depends on the data, so a launch in which every
+// tile is taken twice is the longest there can be: the second walk, 8/3 of the first one's matrix time and with one chunk in
+// flight, is bounded by the same K.
+// The look at the partial tile is one instruction for two values, v_maximum3_f32 of their magnitudes, which keeps NaN.  A lane's
+// largest magnitude times 2^-23 is denormal if it is below 2^-103 and not 0, so one test of its class finds all that is to be
+// looked at closely: nothing that can be measured, where a second comparison costs 0.05 us a launch.  `tile` = the wave's
+// partial tile in LDS, `words` floats a lane.
 template <int N, typename Acc>
-__device__ __forceinline__ bool all_finite(const Acc (&acc)[N]) {  // over the whole wave
+__device__ __forceinline__ void spoil_unless_in_range(const Acc (&acc)[N], float* const tile, const int words) {
   constexpr int V = sizeof(Acc) / sizeof(float);
   float t[2] = {0.f, 0.f};
 #pragma unroll
   for (int j = 0; j < N; ++j)
 #pragma unroll
-    for (int v = 0; v < V; v += 2) t[(v >> 1) & 1] = fmaf(__builtin_fabsf(acc[j][v]), __builtin_fabsf(acc[j][v + 1]), t[(v >> 1) & 1]);
-  if (__builtin_expect(__ballot(!(t[0] + t[1] < INFINITY)) == 0, 1)) return true;
-  float s = 0.f;
-#pragma unroll
-  for (int j = 0; j < N; ++j)
-#pragma unroll
-    for (int v = 0; v < V; ++v) s += __builtin_fabsf(acc[j][v]);
-  return __ballot(!(s < INFINITY)) == 0;
-}
-// The wave's partial tile, `words` floats a lane from `tile` on, becomes NaN.
-__device__ __forceinline__ void spoil(float* const tile, const int words) {
+    for (int v = 0; v < V; v += 2)
+      t[(v >> 1) & 1] = __builtin_elementwise_maximum(__builtin_elementwise_maximum(__builtin_fabsf(acc[j][v]), __builtin_fabsf(acc[j][v + 1])), t[(v >> 1) & 1]);
+  const float largest = __builtin_elementwise_maximum(t[0], t[1]);
+  constexpr int kNanInfDenormal = 0x283;  // signalling and quiet NaN, positive denormal, +infinity
+  if (__builtin_expect(__ballot(__builtin_amdgcn_classf(largest * 0x1p-23f, kNanInfDenormal)) != 0, 0)) {
+    if (__ballot(!(largest < INFINITY)) != 0 || __ballot(largest >= 0x1p-103f) == 0) {
 #pragma unroll 1
-  for (int i = 0; i < words; ++i) tile[64 * i + (threadIdx.x & 63)] = __builtin_nanf("");
+      for (int i = 0; i < words; ++i) tile[64 * i + (threadIdx.x & 63)] = __builtin_nanf("");
+    }
+  }
 }
 __device__ __forceinline__ bool spoiled(const float v) { return __ballot(__builtin_isnan(v)) != 0; }
 
@@ -123,7 +123,7 @@ __device__ __forceinline__ float4 pixel_quad(const ConvArgs& p, const DwFusedArg
 }
 
 // acc[i * TN + j] = the wave's partial tile of pixels m0 + R i .. and channel blocks nb0 + j over K steps [s0, s0 + nsteps), R = 32
-// or 16.  The weights are put together from their parts, which is exact; a lane's eight k of a chunk go through the matrix
+// or 16.  The weights are put together from their parts (exact but for weights below 2^-110, see split8); a lane's eight k of a chunk go through the matrix
 // pipe one at a time.
 template <int MODE, int R, int TM, int TN, typename Acc>
 __device__ __forceinline__ void plain_products(const ConvArgs& p, const DwFusedArgs& dwf, const int m0, const int nb0, const int s0, const int nsteps, Acc (&acc)[TM * TN]) {
@@ -638,8 +638,7 @@ __device__ __forceinline__ void conv_wave_body(const ConvArgs& p, const int mt, 
     }
   };
   park();
-  if constexpr (!BF16)
-    if (__builtin_expect(!all_finite(acc), 0)) spoil(red + wave * TILE, 16 * TN);
+  if constexpr (!BF16) spoil_unless_in_range(acc, red + wave * TILE, 16 * TN);
   __syncthreads();
   add_up();
   if constexpr (!BF16) {
@@ -926,8 +925,7 @@ __device__ __forceinline__ void conv_wave16_body(const ConvArgs& p, const int mt
   };
   __syncthreads();  // the partial tiles reuse the LDS of every wave's staging buffer
   park();
-  if constexpr (!BF16)
-    if (__builtin_expect(!all_finite(acc), 0)) spoil(red + wave * TILE, 4 * TB);
+  if constexpr (!BF16) spoil_unless_in_range(acc, red + wave * TILE, 4 * TB);
   __syncthreads();
   add_up();
   if constexpr (!BF16) {

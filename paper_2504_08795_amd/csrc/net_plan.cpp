@@ -18,7 +18,7 @@ uint16_t host_f32_to_bf16(float f) {
   return (uint16_t)(u >> 16);
 }
 
-// f as the sum of three bf16 numbers, exact for every finite f whose third part is no denormal.
+// f as the sum of three bf16 numbers, exact for every finite f of 2^-110 and more (and 0); below that up to 2^-134 is lost.
 static void split_bf16(float f, uint16_t out[3]) {
   for (int p = 0; p < 3; ++p) {
     uint16_t h = host_f32_to_bf16(f);

@@ -36,6 +36,23 @@ def test_three_part_products_are_fp32_products(cin, h, w, cout, k, scale_x, scal
     assert err <= 5e-7, err       # sqrt(4608) * 2^-25 = 2e-6 is what plain fp32 sums may show; the fp32 instruction: 4.3e-7
 
 
+@pytest.mark.parametrize("scale_x,scale_w", [(1e-33, 1.0), (1e-35, 1.0), (1e-37, 1.0), (1e-36, 1e3)])
+@pytest.mark.parametrize("cin,h,w,cout,k", [(512, 7, 7, 512, 3), (128, 28, 28, 128, 3), (24, 13, 13, 40, 1), (4, 9, 9, 8, 3), (256, 56, 56, 256, 3), (3, 31, 29, 40, 3)])
+def test_small_pixels_keep_their_bits(cin, h, w, cout, k, scale_x, scale_w):
+    """Pixels whose third part is below the smallest bf16 number: their sums are taken with fp32 products."""
+    err, _ = _conv(cin, h, w, cout, k, 1, k // 2, scale_x, scale_w)
+    assert err <= 5e-7, err
+
+
+@pytest.mark.parametrize("scale_w", [1e-33, 1e-36])
+def test_small_weights_keep_what_bf16_resolves(scale_w):
+    """A weight is kept in its three parts: off by at most 2^-134, hence a sum by 2^-134 / (weights' standard deviation) of itself
+    (K terms of either kind add up alike)."""
+    cin, k = 128, 3
+    err, _ = _conv(cin, 28, 28, 128, k, 1, 1, 1.0, scale_w)
+    assert err <= 5e-7 + 2.0 ** -134 / (scale_w * np.sqrt(2.0 / (cin * k * k))), err
+
+
 # (cin, h, w, cout, k, stride, pad, plan_cus): what it is about
 BLOCK_CASES = [
     (64, 56, 56, 64, 3, 1, 1, 32),     # M = 3136 = 49 tiles of 64: 49 workgroups of 4 waves
@@ -126,8 +143,9 @@ def test_infinities_and_nan_through_a_fused_depthwise_layer():
 
 
 def test_the_time_of_a_layer_is_bounded_whatever_its_input():
-    """Stages are not preempted, so no frame may take a layer far longer than others do.  A layer whose sums all have to be
-    taken again in fp32 arithmetic takes 2.4 times as long (the matrix instructions: 8/3); the bound leaves room for noise."""
+    """Stages are not preempted, so no frame may take a layer far longer than others do.  A frame through one layer whose
+    sums all have to be taken again with fp32 products takes 2.4 times as long (the layer's matrix instructions: 1 + 8/3 times as
+    long, plus what a frame costs besides); the bound leaves room for noise."""
     cin = cout = 512
     rng = np.random.default_rng(13)
     L = [N.Layer(op=N.OP_CONV, c_in=cin, c_out=cout, k=3, stride=1, pad=1, act=0, in_from=-1)]
