@@ -12,7 +12,9 @@
  *     throws or aborts.  daris_last_error() gives the text of the calling thread's last failure.
  *   - All calls come from one API thread.  The library runs one internal scheduler thread in real-time mode.
  *   - "host" pointers are ordinary CPU memory, read during the call only (the library copies what it keeps).
- *     "device" pointers are HIP device memory owned by the caller, which must stay valid until the job that
+ *     "device" pointers are HIP device memory owned by the caller -- of the library's GPU, or other memory that this GPU
+ *     can access (a peer's, pinned host memory), whose inputs the library acquires at system scope, for 2 us a job --
+ *     which must stay valid until the job that
  *     uses them has completed (daris_run_until_idle() or the blocking run calls return).  The library's kernels run
  *     on queues of its own, not on a HIP stream: what the caller's streams wrote into an input buffer must be
  *     complete (stream or device synchronised) before the job is released, and logits are complete and visible

@@ -64,8 +64,9 @@ daris_status fail(daris_status code, const char* fmt, ...) {
 struct JobIo {
   const void* in = nullptr;
   void* out = nullptr;
+  bool in_elsewhere = false;  // the input does not lie in this GPU's memory (see on_own_device)
   // device-resident argument blocks of the two launches that touch these buffers, prepared ahead (I/O pools); nullptr:
-  // the block is patched at launch time and travels through the queue's host-coherent ring
+  // the block is patched at launch time and travels through the queue's argument ring
   const void* in_args = nullptr;
   const void* out_args = nullptr;
 };
@@ -100,6 +101,7 @@ struct TaskRt {
   // I/O
   const void* pool_in = nullptr;
   void* pool_out = nullptr;
+  bool pool_in_elsewhere = false;
   int32_t n_inputs = 0, n_slots = 0;
   std::unordered_map<uint32_t, JobIo> io;  // per released job
   LaunchSeq seq;                        // the network on the task's own buffers
@@ -191,6 +193,18 @@ Global* G = nullptr;
 
 int64_t now_ns() {
   return std::chrono::duration_cast<std::chrono::nanoseconds>(std::chrono::steady_clock::now() - G->epoch).count();
+}
+
+// Whether p is memory of the library's own GPU.  Packets acquire at device scope, which makes the kernel see whatever was written
+// into this GPU's memory; an input in another GPU's memory or in the host's may be held by caches that only a system-scope
+// acquire drops, so the launch that reads it asks for one (2 us).
+bool on_own_device(const void* p) {
+  hipPointerAttribute_t a;
+  if (hipPointerGetAttributes(&a, p) != hipSuccess) {
+    (void)hipGetLastError();  // (an address HIP does not know: leave no error behind for the caller's next call)
+    return false;
+  }
+  return a.type == hipMemoryTypeDevice && a.device == G->device;
 }
 
 // ---- stage execution ----------------------------------------------------------------------------------------------
@@ -448,9 +462,9 @@ const char* enqueue_range(const LaunchSeq& q, int lo, int hi, const JobIo& io, S
     if (i == hi - 1 && o.done.handle) sig = o.done;
     else if (o.sample && i < hi - 1) sig = S.tsig[i - lo];
     else if (i == lo) sig = o.first;
-    const unsigned fl = i < hi - 1 ? 0u : o.release;
-    const void* dev = r.dev;
     const bool is_in = i == q.in_launch, is_out = i == q.out_launch;
+    const unsigned fl = (i < hi - 1 ? 0u : o.release) | (is_in && io.in_elsewhere ? (unsigned)AqlQueue::kAcquireSystem : 0u);
+    const void* dev = r.dev;
     if (is_in || is_out) {
       if (is_in && !is_out && io.in_args) dev = io.in_args;
       else if (is_out && !is_in && io.out_args) dev = io.out_args;
@@ -675,6 +689,7 @@ JobIo pool_io(TaskRt& T, uint32_t job) {
   const uint32_t i = job % (uint32_t)T.n_inputs, j = job % (uint32_t)T.n_slots;
   io.in = (const float*)T.pool_in + (size_t)i * in_elems;
   io.out = (float*)T.pool_out + (size_t)j * n.n_out;
+  io.in_elsewhere = T.pool_in_elsewhere;
   if (i < T.pool.in.size()) io.in_args = T.pool.in[i];
   if (j < T.pool.out.size()) io.out_args = T.pool.out[j];
   return io;
@@ -1174,6 +1189,7 @@ daris_status daris_release_job(daris_task t, const void* d_input, void* d_logits
   JobIo io;
   io.in = d_input;
   io.out = d_logits;
+  io.in_elsewhere = !G->nodev && !on_own_device(d_input);
   if (G->vt) {
     if (release_ns < 0 || release_ns < G->vt_now) return fail(DARIS_ESTATE, "virtual release times must not decrease");
     if (release_ns > G->vt_now) {
@@ -1243,6 +1259,7 @@ daris_status daris_task_set_io(daris_task t, const void* d_inputs, int32_t n_inp
     // The jobs run on queues of the library's own, unordered with the caller's HIP streams: wait here, once, for whatever
     // those streams are still writing into the pools (inputs being uploaded, logits being pre-filled).
     HIP_TRY(hipDeviceSynchronize());
+    T.pool_in_elsewhere = !on_own_device(d_inputs);
     // argument blocks for every buffer of the two pools, so that a release writes nothing but packets
     free_variants(&T.pool);
     if ((int64_t)n_inputs + n_slots <= (1 << 20)) {
@@ -1403,6 +1420,7 @@ daris_status daris_forward(daris_task t, const void* d_input, void* d_logits, da
   JobIo io;
   io.in = d_input;
   io.out = d_logits;
+  io.in_elsewhere = !on_own_device(d_input);
   return run_direct(T.seq, 0, (int)T.seq.launches.size(), io, *G->parts[p].streams[0]);
 }
 
@@ -1430,6 +1448,7 @@ daris_status daris_forward_static(daris_task t, const void* d_input, void* d_log
   JobIo io;
   io.in = d_input;
   io.out = d_logits;
+  io.in_elsewhere = !on_own_device(d_input);
   // (a packet that is refused leaves launches queued on the static array: run_direct fails for good then)
   return run_direct(T.static_seq, 0, (int)T.static_seq.launches.size(), io, *G->parts[p].streams[0]);
 }

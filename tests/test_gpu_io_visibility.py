@@ -49,3 +49,44 @@ def test_rewritten_inputs_and_changing_buffers(net, dtype, hw):
             assert torch.equal(y, want[k]), (r, k, how)
     finally:
         D.daris_shutdown()
+
+
+def test_inputs_in_host_memory():
+    """An input that does not lie in the GPU's own memory (pinned host memory here; a peer's is alike) is acquired at system
+    scope: what the host wrote last is what the next job reads, through every entry point, in one buffer again and again."""
+    layers, shp = wl.build_net("tiny")
+    weights = wl.make_weights(layers, 3)
+    n_out, kinds = layers[-1].c_out, 5
+    frames = np.random.default_rng(9).normal(0, 1, (kinds,) + shp).astype(np.float32)
+    on_device = torch.from_numpy(frames).cuda()
+    D.daris_init(0, 0, 0)
+    try:
+        part = D.daris_create_partition(128)
+        dnn, keep = D.make_dnn(layers, weights, shp, "fp32")
+        t = D.daris_register_task(dnn, 10**8, 10**8, D.HP)
+        D.daris_commit()
+        want = torch.empty((kinds, n_out), device="cuda")
+        for i in range(kinds):
+            D.daris_forward(t, on_device[i], want[i], part)
+        x = torch.zeros((2,) + shp, pin_memory=True)
+        y = torch.zeros((2, n_out), device="cuda")
+        for r in range(60):
+            a, b = r % kinds, (3 * r + 1) % kinds
+            x[0], x[1] = torch.from_numpy(frames[a]), torch.from_numpy(frames[b])
+            y.zero_()
+            torch.cuda.synchronize()
+            if r % 4 == 3:
+                D.daris_task_set_io(t, x, 2, y, 2)
+                first = D.daris_get_stats(t)["released"] % 2
+                D.daris_run_closed_loop([2])
+                assert torch.equal(y[first], want[(a, b)[first]])
+            else:
+                for i in range(2):
+                    if r % 4 == 2:
+                        D.daris_release_job(t, x[i], y[i])
+                        D.daris_run_until_idle()
+                    else:
+                        (D.daris_forward, D.daris_forward_static)[r % 4](t, x[i], y[i], part)
+            assert torch.equal(y[0], want[a]) and torch.equal(y[1], want[b]), r
+    finally:
+        D.daris_shutdown()
