@@ -14,11 +14,10 @@ extern "C" {
 
 /* Launch plan of one layer, for inspection and for host-side checks of what the kernels assume (no device needed).
  * Writes 27 values into out (host int64[cap >= 27]) and returns 27: [0] kernel id (daris_kernel_name), [1] 1 = dense
- * convolution (the rest is meaningful only then), [2] pixels per wave tile (32, or 16: then channel blocks are 16 wide too), [3] M = output
+ * convolution (the rest is meaningful only then), [2] pixels per wave tile (32, 64, or 16: then channel blocks are 16 wide too), [3] M = output
  * pixels, [4] N = output channels incl. padding, [5] K, [6] K padded, [7] channel blocks per wave tile, [8] waves
  * per workgroup, [9] K steps in total, [10] per workgroup slice, [11] per wave, [12] split-K factor, [13] pixel tiles,
- * [14] channel tiles, [15] weight groups, [16] workgroup order mode, [17..19] grid x y z (counted in single tiles: large
- * fp32 layers are launched with two pixel tiles per workgroup, half as many), [20] threads per workgroup,
+ * [14] channel tiles, [15] weight groups, [16] workgroup order mode, [17..19] grid x y z, [20] threads per workgroup,
  * [21] split-K workspace bytes, [22] layer it shares a launch with or -1, [23] 1 = the joint launch is issued at this
  * layer, [24] activation slot of the layer's output (-1: the caller's logits), [25] slot of its input, [26] slot of its
  * residual operand or -1.  A slot is a device buffer shared by tensors whose lifetimes do not overlap. */

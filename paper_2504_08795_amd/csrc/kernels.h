@@ -19,6 +19,8 @@ enum KernelId : int32_t {
   // the same with 16-pixel tiles of TN 16-channel blocks (deep, skinny layers)
   K_CONV16_F32_T1W2, K_CONV16_F32_T1W4, K_CONV16_F32_T1W8, K_CONV16_F32_T2W2, K_CONV16_F32_T2W4, K_CONV16_F32_T2W8,
   K_CONV16_BF16_T1W2, K_CONV16_BF16_T1W4, K_CONV16_BF16_T1W8, K_CONV16_BF16_T2W2, K_CONV16_BF16_T2W4, K_CONV16_BF16_T2W8,
+  // the same with 64 pixels x 64 channels per wave (fp32 layers of many tiles)
+  K_CONV64_F32_T2W2, K_CONV64_F32_T2W4, K_CONV64_F32_T2W8,
   K_SPLITK_REDUCE, K_DWCONV, K_MAXPOOL, K_GAVGPOOL, K_FC, K_INGEST, K_EGRESS,
   K_COUNT
 };
@@ -98,8 +100,7 @@ struct FcArgs {
 struct ConvPlan {
   int32_t kernel;  // KernelId
   int splitk;      // K slices across workgroups (1 = none); > 1 needs the workspace and the reduction launch
-  int tm;                          // 2: a wave takes two pixel tiles of 32 (conv_block_*); MT and grid_x still count single tiles
-  int rows;                        // pixels per wave tile: 32 (conv_wave_*: channel blocks of 32) or 16 (conv_wave16_*: blocks of 16)
+  int rows;                        // pixels per wave tile: 32 (conv_wave_*), 64 (conv_block_*), both with channel blocks of 32, or 16 (conv_wave16_*: blocks of 16)
   int tn, nw, S, sz, sw, MT, NTn, G, xmode;
   int step_align;                  // K slices are multiples of this many steps
   int staged;                      // the pixel operand may be fetched in whole 64-byte rows through LDS

@@ -16,6 +16,7 @@ static const char* const kNames[K_COUNT] = {
     "conv_wave_bf16_t1w2", "conv_wave_bf16_t1w4", "conv_wave_bf16_t1w8", "conv_wave_bf16_t2w2", "conv_wave_bf16_t2w4", "conv_wave_bf16_t2w8",
     "conv_wave16_f32_t1w2", "conv_wave16_f32_t1w4", "conv_wave16_f32_t1w8", "conv_wave16_f32_t2w2", "conv_wave16_f32_t2w4", "conv_wave16_f32_t2w8",
     "conv_wave16_bf16_t1w2", "conv_wave16_bf16_t1w4", "conv_wave16_bf16_t1w8", "conv_wave16_bf16_t2w2", "conv_wave16_bf16_t2w4", "conv_wave16_bf16_t2w8",
+    "conv_wave64_f32_t2w2", "conv_wave64_f32_t2w4", "conv_wave64_f32_t2w8",
     "splitk_reduce", "dwconv", "maxpool", "gavgpool", "fc", "ingest", "egress"};
 
 const char* kernel_name(int32_t id) { return (id >= 0 && id < K_COUNT) ? kNames[id] : "?"; }
@@ -90,8 +91,7 @@ static ConvPlan plan_conv_wave(int M, int N, int Kpad, int bf16, int step_align,
   // operand in chunks of two steps; S is then even as well)
   const int sz = cdiv(cdiv(S, z), step_align) * step_align;
   z = cdiv(S, sz);
-  pl.rows = 32;
-  pl.tm = block ? 2 : 1;
+  pl.rows = block ? 64 : 32;
   pl.tn = tn;
   pl.nw = nw;
   pl.S = S;
@@ -102,7 +102,7 @@ static ConvPlan plan_conv_wave(int M, int N, int Kpad, int bf16, int step_align,
   pl.splitk = z;
   pl.tiles = tiles;
   pl.threads = nw * 64;
-  pl.MT = cdiv(M, 32);  // (the division multipliers are filled in by the caller, which knows Wo, Cin and kw)
+  pl.MT = cdiv(M, pl.rows);  // (the division multipliers are filled in by the caller, which knows Wo, Cin and kw)
   pl.NTn = nb / tn;
   pl.G = pl.NTn * z;
   if (pl.G % 8 == 0) {
@@ -117,7 +117,7 @@ static ConvPlan plan_conv_wave(int M, int N, int Kpad, int bf16, int step_align,
   }
   pl.ws_bytes = z > 1 ? (size_t)z * M * N * sizeof(float) : 0;
   const int wi = nw == 2 ? 0 : (nw == 4 ? 1 : 2);
-  pl.kernel = (bf16 ? K_CONVW_BF16_T1W2 : K_CONVW_F32_T1W2) + (tn - 1) * 3 + wi;
+  pl.kernel = block ? K_CONV64_F32_T2W2 + wi : (bf16 ? K_CONVW_BF16_T1W2 : K_CONVW_F32_T1W2) + (tn - 1) * 3 + wi;
   return pl;
 }
 
@@ -155,7 +155,6 @@ static ConvPlan plan_conv_wave16(int M, int N, int Kpad, int bf16, int nominal_c
     return pl;
   }
   pl.rows = 16;
-  pl.tm = 1;
   pl.tn = tn;
   pl.nw = nw;
   pl.S = S;
@@ -314,30 +313,28 @@ bool encode_conv(const KernelTable& kt, const ConvPlan& pl, const ConvArgs& a, i
     if (!push(out, kt.conv16[bf16][v16], pl.kernel, pl.grid_x, (uint32_t)pl.threads, &a, sizeof(a))) return false;
     return push_reduce(kt, pl, a, bf16, out);
   }
+  if (pl.rows == 64) {
+    // what conv_block_kernel assumes: whole 64-byte rows, K cut in chunks of two steps, and the limits of conv_block_takes
+    const int v64 = pl.kernel - K_CONV64_F32_T2W2;
+    if (v64 < 0 || v64 >= 3 || pl.threads != 64 * pl.nw || bf16 || a.c_real > 0 || !pl.staged || pl.tn != 2 || pl.S % 2 || pl.sz % 2 || pl.sw % 2) return false;
+    if (a.kh != a.kw || !conv_block_takes(a.H, a.W, a.Cin, a.kh, a.pad, a.Kpad) || (pl.splitk > 1 && !a.ws)) return false;
+    if (!push(out, kt.block[v64], pl.kernel, pl.grid_x, (uint32_t)pl.threads, &a, sizeof(a))) return false;
+    return push_reduce(kt, pl, a, bf16, out);
+  }
   const int variant = pl.kernel - (bf16 ? K_CONVW_BF16_T1W2 : K_CONVW_F32_T1W2);
-  if (variant < 0 || variant >= 6 || pl.threads != 64 * pl.nw) return false;
+  if (variant < 0 || variant >= 6 || pl.rows != 32 || pl.threads != 64 * pl.nw) return false;
   // 0: a K step never straddles a filter tap; 1: general walk; 2: layer 0 reading the caller's fp32 [C][H][W] input;
   // 3: a pixel's channels are whole 64-byte rows and the plan cuts K in chunks of two steps: pixel operand through LDS
   const int mode = a.c_real > 0 ? 2 : (conv_rows_staged(a.Cin, bf16) && pl.staged ? 3 : (a.Cin % (bf16 ? 16 : 8) == 0 ? 0 : 1));
   if ((mode == 3 || !bf16) && (pl.S % 2 || pl.sz % 2 || pl.sw % 2)) return false;
   if (mode == 2 && (a.Cin != (bf16 ? 8 : 4) || a.c_real > 4 || (uint64_t)a.c_real * a.H * a.W * 4 >= (1ull << 31))) return false;
   if (pl.splitk > 1 && !a.ws) return false;
-  if (pl.tm == 2) {
-    // what conv_block_kernel assumes: whole 64-byte rows, K cut in chunks of two steps, and the limits of conv_block_takes
-    if (bf16 || mode != 3 || pl.tn != 2 || a.kh != a.kw || !conv_block_takes(a.H, a.W, a.Cin, a.kh, a.pad, a.Kpad)) return false;
-    ConvArgs b = a;
-    b.MT = cdiv(a.M, 64);
-    b.mg_mt = tile_magic((uint64_t)b.MT * b.G, b.MT);
-    const uint32_t grid = (uint32_t)(b.xmode == 2 ? 8 * cdiv(b.MT, 8 / b.G) : b.G * b.MT);
-    if (!push(out, kt.block[variant % 3], pl.kernel, grid, (uint32_t)pl.threads, &b, sizeof(b))) return false;
-    return push_reduce(kt, pl, a, bf16, out);
-  }
   if (!push(out, kt.conv[bf16][variant][mode], pl.kernel, pl.grid_x, (uint32_t)pl.threads, &a, sizeof(a))) return false;
   return push_reduce(kt, pl, a, bf16, out);
 }
 
 bool conv_dw_fusable(const ConvPlan& pl, int bf16) {
-  if (pl.rows != 32 || pl.tm != 1 || !pl.staged || (!bf16 && pl.tn != 1) || (bf16 && pl.nw == 8)) return false;  // no such kernel variant
+  if (pl.rows != 32 || !pl.staged || (!bf16 && pl.tn != 1) || (bf16 && pl.nw == 8)) return false;  // no such kernel variant
   return pl.MT >= 96 && pl.NTn == 1;
 }
 
@@ -378,7 +375,7 @@ bool encode_conv_pair(const KernelTable& kt, const ConvPlan& pl0, const ConvArgs
   }
   const int ks = bf16 ? 16 : 8;
   const bool aligned = a0.Cin % ks == 0;
-  if (pl0.kernel != pl1.kernel || pl0.rows != 32 || pl0.tm != 1 || pl1.tm != 1 || aligned != (a1.Cin % ks == 0) || pl1.splitk != 1 || a0.c_real > 0 || a1.c_real > 0) return false;
+  if (pl0.kernel != pl1.kernel || pl0.rows != 32 || pl1.rows != 32 || aligned != (a1.Cin % ks == 0) || pl1.splitk != 1 || a0.c_real > 0 || a1.c_real > 0) return false;
   const bool staged = conv_rows_staged(a0.Cin, bf16) && conv_rows_staged(a1.Cin, bf16) && pl0.staged && pl1.staged;
   if ((staged || !bf16) && (pl0.S % 2 || pl0.sz % 2 || pl0.sw % 2 || pl1.S % 2 || pl1.sz % 2 || pl1.sw % 2)) return false;
   const int variant = pl0.kernel - (bf16 ? K_CONVW_BF16_T1W2 : K_CONVW_F32_T1W2);

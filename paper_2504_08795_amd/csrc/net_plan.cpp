@@ -138,7 +138,7 @@ std::string build_plan(const daris_dnn& dnn, bool keep_activations, bool pair_la
     LayerPlan& light = A.macs > B.macs ? B : A;
     const ConvPlan own = heavy.cp;
     const int sa = staged_rows && conv_rows_staged(net.tensor(heavy.in_t).Cs, net.bf16) ? 2 : 1;
-    if (heavy.cp.tm == 2)
+    if (heavy.cp.rows == 64)
       heavy.cp = plan_conv(heavy.out.H * heavy.out.W, heavy.out.Cs, heavy.Kpad, net.bf16, sa, small_tiles ? net.tensor(heavy.in_t).Cs : 0, plan_cus, false);
     const ConvPlan like = plan_conv_like(heavy.cp, light.out.H * light.out.W, light.out.Cs, light.Kpad, net.bf16,
                                          staged_rows && conv_rows_staged(net.tensor(light.in_t).Cs, net.bf16) ? 2 : 1, plan_cus);
@@ -166,7 +166,7 @@ std::string build_plan(const daris_dnn& dnn, bool keep_activations, bool pair_la
       if (net.layers[q].in_t == l + 1 || net.layers[q].res_t == l + 1) only_reader = false;
     if (!only_reader || !conv_rows_staged(A.out.Cs, net.bf16)) continue;
     ConvPlan cp = B.cp;
-    if (cp.rows != 32 || cp.tm != 1)  // the fused producer exists for 32-pixel tiles
+    if (cp.rows != 32)  // the fused producer exists for 32-pixel tiles
       cp = plan_conv(B.out.H * B.out.W, B.out.Cs, B.Kpad, net.bf16, 2, 0, plan_cus, false);
     if (!conv_dw_fusable(cp, net.bf16)) continue;  // the separate launch is faster (or no such kernel variant)
     B.cp = cp;
@@ -300,10 +300,10 @@ void pack_conv(const NetPlan& net, const LayerPlan& L, const float* w, const flo
     return;
   }
   if (!bf) {
-    // fp32: three bf16 parts per weight (see split8 in kernels.hip), [channel block of R][chunk][part][lane = i + R q][8],
+    // fp32: three bf16 parts per weight (see split8 in device_common.h), [channel block of R][chunk][part][lane = i + R q][8],
     // element e of lane (i, q) in chunk s is W[n = R nb + i][k = s * CK + 8 q + e]; a chunk is what one matrix instruction
     // takes, CK = 16 (R = 32) or 32 (R = 16)
-    const int R = L.cp.rows, ck = R == 16 ? 32 : 16, nch = L.Kpad / ck;
+    const int R = L.cp.rows == 16 ? 16 : 32, ck = R == 16 ? 32 : 16, nch = L.Kpad / ck;
     const int nblocks = (L.out.Cs + R - 1) / R;
     const int nb_alloc = (nblocks + L.cp.tn - 1) / L.cp.tn * L.cp.tn;
     wp->assign((size_t)nb_alloc * nch * 3 * 1024 + 12 * 1024, 0);  // + slack for the pipeline's refills past the last chunk

@@ -155,15 +155,17 @@ def run_saturated(g: GpuTaskSet, total_jobs, driver_profile=False):
     return res
 
 
-PEAK_TFLOPS = {"fp32": 157.3, "bf16": 2500.0}   # MI355X dense MFMA peaks
+# MI355X dense MFMA peaks; the fp32 convolutions form each product from six bf16 ones
+PEAK_TFLOPS = {"fp32": 416.7, "bf16": 2500.0}
 PEAK_HBM_GBS = 8000.0
 
 
 def layer_rooflines(layers, shp, dtype):
     """Per layer: (algorithmic FLOPs, algorithmic bytes, t_roof in us on the whole chip).  Bytes = weights once + one fp32
     bias per output channel + the input tensor(s) read once + the output written once, at the element size of the task;
-    FLOPs = 2 x MACs; t_roof = max(FLOPs / dense MFMA peak of the dtype, bytes / HBM peak).  Host arithmetic on the layer
-    table only."""
+    FLOPs = 2 x MACs; t_roof = max(FLOPs / dense MFMA peak of the dtype, bytes / HBM peak).  (In device memory a weight of an
+    fp32 dense convolution takes 6 bytes, its three bf16 parts; what the layer cannot do without is 4.)  Host arithmetic on
+    the layer table only."""
     import workloads as wl
     es = 4 if dtype == "fp32" else 2
     shapes = wl.layer_shapes(layers, shp)

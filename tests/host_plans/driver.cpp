@@ -66,7 +66,7 @@ int main() {
     a.c_real = net.fuse_ingest ? net.in_c : 0;
     std::vector<KernelLaunch> out;
     const bool ok = encode_conv(kt, P.cp, a, net.bf16, &out);
-    std::printf("%d %d %d %d %d\n", ok ? 1 : 0, P.cp.kernel, P.cp.tm == 2 ? 64 : P.cp.rows, P.cp.threads, P.cp.splitk);
+    std::printf("%d %d %d %d %d\n", ok ? 1 : 0, P.cp.kernel, P.cp.rows, P.cp.threads, P.cp.splitk);
   }
   return 0;
 }
