@@ -151,7 +151,7 @@ struct KernelLaunch {
 
 // Every kernel of the code object, looked up once.
 struct KernelTable {
-  const AqlKernel* conv[2][6][4] = {};  // [bf16][(tn - 1) * 3 + log2(nw) - 1][gather mode 0..3]
+  const AqlKernel* conv[2][6][4] = {};  // [bf16][(tn - 1) * 3 + log2(nw) - 1][gather mode 0..3] (fp32: no mode 0)
   const AqlKernel* pair[2][6][3] = {};  // gather modes 0, 1, 3
   const AqlKernel* conv16[2][6] = {};   // 16-row tiles: [bf16][(tn - 1) * 3 + log2(nw) - 1]
   const AqlKernel* pair16[2][6] = {};

@@ -178,13 +178,14 @@ __global__ __launch_bounds__(64) void cu_probe_kernel(uint32_t* out, int spin) {
 
 // ---- explicit instantiations: the host never references the kernels (they are dispatched by name from the code object) --------
 #define DARIS_INST_CONV(B, TN_, NW_)                                                              \
-  template __global__ void conv_wave_kernel<B, TN_, NW_, 0>(const ConvArgs);                      \
   template __global__ void conv_wave_kernel<B, TN_, NW_, 1>(const ConvArgs);                      \
   template __global__ void conv_wave_kernel<B, TN_, NW_, 2>(const ConvArgs);                      \
   template __global__ void conv_wave_kernel<B, TN_, NW_, 3>(const ConvArgs);                      \
-  template __global__ void conv_wave_pair_kernel<B, TN_, NW_, 0>(const ConvArgs, const ConvArgs, const int); \
   template __global__ void conv_wave_pair_kernel<B, TN_, NW_, 1>(const ConvArgs, const ConvArgs, const int); \
   template __global__ void conv_wave_pair_kernel<B, TN_, NW_, 3>(const ConvArgs, const ConvArgs, const int);
+#define DARIS_INST_CONV_ALIGNED(TN_, NW_) /* gather mode 0: bf16 only */                          \
+  template __global__ void conv_wave_kernel<true, TN_, NW_, 0>(const ConvArgs);                   \
+  template __global__ void conv_wave_pair_kernel<true, TN_, NW_, 0>(const ConvArgs, const ConvArgs, const int);
 #define DARIS_INST_CONV16(B, TB_)                                                                  \
   template __global__ void conv_wave16_kernel<B, TB_, 2>(const ConvArgs);                          \
   template __global__ void conv_wave16_kernel<B, TB_, 4>(const ConvArgs);                          \
@@ -207,6 +208,8 @@ __global__ __launch_bounds__(64) void cu_probe_kernel(uint32_t* out, int spin) {
   template __global__ void egress_kernel<B>(const void*, float*, int, int, int);
 DARIS_INST_ALL(false)
 DARIS_INST_ALL(true)
+DARIS_INST_CONV_ALIGNED(1, 2) DARIS_INST_CONV_ALIGNED(1, 4) DARIS_INST_CONV_ALIGNED(1, 8)
+DARIS_INST_CONV_ALIGNED(2, 2) DARIS_INST_CONV_ALIGNED(2, 4) DARIS_INST_CONV_ALIGNED(2, 8)
 // Fused depthwise variants.  fp32 tiles of 64 channels are never staged, so they have none; bf16 plans never use 8 waves per
 // workgroup, and those variants would need scratch memory, which the dispatch path does not provide.
 DARIS_INST_CONVDW(false, 1, 2) DARIS_INST_CONVDW(false, 1, 4) DARIS_INST_CONVDW(false, 1, 8)
@@ -214,6 +217,7 @@ DARIS_INST_CONVDW(true, 1, 2) DARIS_INST_CONVDW(true, 1, 4) DARIS_INST_CONVDW(tr
 #undef DARIS_INST_CONVDW
 #undef DARIS_INST_ALL
 #undef DARIS_INST_CONV
+#undef DARIS_INST_CONV_ALIGNED
 #undef DARIS_INST_CONV16
 
 }  // namespace daris

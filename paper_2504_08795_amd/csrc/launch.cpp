@@ -270,9 +270,10 @@ std::string KernelTable::resolve(const AqlRuntime& rt) {
     const std::string B = b ? "true" : "false";
     for (int v = 0; v < 6; ++v) {
       const std::string tp = B + ", " + std::to_string(tn_[v]) + ", " + std::to_string(nw_[v]) + ", ";
-      for (int m = 0; m < 4; ++m) conv[b][v][m] = get("daris::conv_wave_kernel<" + tp + std::to_string(m) + ">", sizeof(ConvArgs));
+      // (fp32 has no gather mode 0: what it would gain, a walk in scalars, mode 1 does in closed form for quads of channels)
+      for (int m = b ? 0 : 1; m < 4; ++m) conv[b][v][m] = get("daris::conv_wave_kernel<" + tp + std::to_string(m) + ">", sizeof(ConvArgs));
       static const int pair_modes[3] = {0, 1, 3};
-      for (int m = 0; m < 3; ++m) pair[b][v][m] = get("daris::conv_wave_pair_kernel<" + tp + std::to_string(pair_modes[m]) + ">", kPairBytes);
+      for (int m = b ? 0 : 1; m < 3; ++m) pair[b][v][m] = get("daris::conv_wave_pair_kernel<" + tp + std::to_string(pair_modes[m]) + ">", kPairBytes);
     }
     for (int v = 0; v < 6; ++v) {
       conv16[b][v] = get("daris::conv_wave16_kernel<" + B + ", " + std::to_string(tn_[v]) + ", " + std::to_string(nw_[v]) + ">", sizeof(ConvArgs));
@@ -323,9 +324,9 @@ bool encode_conv(const KernelTable& kt, const ConvPlan& pl, const ConvArgs& a, i
   }
   const int variant = pl.kernel - (bf16 ? K_CONVW_BF16_T1W2 : K_CONVW_F32_T1W2);
   if (variant < 0 || variant >= 6 || pl.rows != 32 || pl.threads != 64 * pl.nw) return false;
-  // 0: a K step never straddles a filter tap; 1: general walk; 2: layer 0 reading the caller's fp32 [C][H][W] input;
+  // 0: a K step never straddles a filter tap (bf16); 1: general walk; 2: layer 0 reading the caller's fp32 [C][H][W] input;
   // 3: a pixel's channels are whole 64-byte rows and the plan cuts K in chunks of two steps: pixel operand through LDS
-  const int mode = a.c_real > 0 ? 2 : (conv_rows_staged(a.Cin, bf16) && pl.staged ? 3 : (a.Cin % (bf16 ? 16 : 8) == 0 ? 0 : 1));
+  const int mode = a.c_real > 0 ? 2 : (conv_rows_staged(a.Cin, bf16) && pl.staged ? 3 : (bf16 && a.Cin % 16 == 0 ? 0 : 1));
   if ((mode == 3 || !bf16) && (pl.S % 2 || pl.sz % 2 || pl.sw % 2)) return false;
   if (mode == 2 && (a.Cin != (bf16 ? 8 : 4) || a.c_real > 4 || (uint64_t)a.c_real * a.H * a.W * 4 >= (1ull << 31))) return false;
   if (pl.splitk > 1 && !a.ws) return false;
@@ -373,9 +374,8 @@ bool encode_conv_pair(const KernelTable& kt, const ConvPlan& pl0, const ConvArgs
     pa.n0 = (int)((pl0.grid_x + 7) / 8 * 8);
     return push(out, kt.pair16[bf16][v16], pl0.kernel, (uint32_t)pa.n0 + pl1.grid_x, (uint32_t)pl0.threads, &pa, kPairBytes);
   }
-  const int ks = bf16 ? 16 : 8;
-  const bool aligned = a0.Cin % ks == 0;
-  if (pl0.kernel != pl1.kernel || pl0.rows != 32 || pl1.rows != 32 || aligned != (a1.Cin % ks == 0) || pl1.splitk != 1 || a0.c_real > 0 || a1.c_real > 0) return false;
+  const bool aligned = bf16 && a0.Cin % 16 == 0;
+  if (pl0.kernel != pl1.kernel || pl0.rows != 32 || pl1.rows != 32 || aligned != (bf16 && a1.Cin % 16 == 0) || pl1.splitk != 1 || a0.c_real > 0 || a1.c_real > 0) return false;
   const bool staged = conv_rows_staged(a0.Cin, bf16) && conv_rows_staged(a1.Cin, bf16) && pl0.staged && pl1.staged;
   if ((staged || !bf16) && (pl0.S % 2 || pl0.sz % 2 || pl0.sw % 2 || pl1.S % 2 || pl1.sz % 2 || pl1.sw % 2)) return false;
   const int variant = pl0.kernel - (bf16 ? K_CONVW_BF16_T1W2 : K_CONVW_F32_T1W2);

@@ -183,13 +183,14 @@ constexpr int conv_wave_lds() {  // floats of LDS
 }
 template <bool BF16, int TN, int NW, int MODE, int DC>
 __device__ __forceinline__ void conv_wave_body(const ConvArgs& p, const int mt, const int g, float* const red, const DwFusedArgs& dwf) {
-  // MODE 0: Cin a multiple of KS; 1: any Cin; 2: the network input itself, fp32 [C][H][W]; 3: a pixel's channels are whole
+  // MODE 0 (bf16): Cin a multiple of KS; 1: any Cin; 2: the network input itself, fp32 [C][H][W]; 3: a pixel's channels are whole
   // 64-byte rows (Cin * ES a multiple of 64): the pixel operand is fetched in coalesced rows and transposed through LDS;
   // 4: like 3 for a 1x1 convolution whose input is the output of a 3x3 depthwise convolution that is never stored: the
   // rows are computed here from the depthwise layer's input (p.x) and weights (dwf)
   // fp32: two K steps of 8 make one chunk of 16, the depth of the bf16 matrix instruction that takes the operands' three
   // parts (split8); the plan cuts K in whole chunks, the weights are stored as [channel block][chunk][part][lane][16 B].
-  constexpr bool ALIGNED = BF16 && MODE == 0;
+  constexpr bool ALIGNED = MODE == 0;
+  static_assert(BF16 || MODE != 0, "fp32 locates its quads of channels in closed form whatever Cin is");
   constexpr bool STAGED = MODE == 3 || MODE == 4;
   constexpr bool DWF = MODE == 4;
   constexpr int ES = BF16 ? 2 : 4;

@@ -1,7 +1,8 @@
-// Plans and encodes one dense convolution per input line and says what would be launched.  Links the library's planner and
+// Plans and encodes one dense convolution per input line, or two that read the same tensor, and says what would be launched.  Links the library's planner and
 // encoders (net_plan.cpp, launch.cpp) against a kernel table without a device, so that a plan which its own encoder refuses is
 // found on the CPU.
-// Line: DTYPE(0 fp32, 1 bf16) C_IN H W C_OUT K STRIDE PAD PLAN_CUS.  Answer: ENCODED KERNEL_ID PIXELS_PER_WAVE THREADS SPLIT_K.
+// Line: DTYPE(0 fp32, 1 bf16) C_IN H W C_OUT K STRIDE PAD PLAN_CUS, and of the second convolution C_OUT (0: none) K STRIDE PAD.
+// Answer, of the first convolution: ENCODED KERNEL_ID PIXELS_PER_WAVE THREADS SPLIT_K SHARES_A_LAUNCH; or -1 and why not.
 #include <cstdio>
 #include <cstring>
 #include <string>
@@ -41,32 +42,42 @@ int main() {
     std::fprintf(stderr, "kernel %s\n", missing.c_str());
     return 2;
   }
-  int dtype, cin, h, w, cout, k, s, p, cus;
-  while (std::scanf("%d %d %d %d %d %d %d %d %d", &dtype, &cin, &h, &w, &cout, &k, &s, &p, &cus) == 9) {
-    daris_layer L;
-    std::memset(&L, 0, sizeof L);
-    L.op = DARIS_OP_CONV; L.c_in = cin; L.c_out = cout; L.k = k; L.stride = s; L.pad = p; L.groups = 1; L.in_from = -1; L.res_from = -1;
+  int dtype, cin, h, w, cus, cout[2], k[2], s[2], p[2];
+  while (std::scanf("%d %d %d %d %d %d %d %d %d %d %d %d %d", &dtype, &cin, &h, &w, &cout[0], &k[0], &s[0], &p[0], &cus, &cout[1], &k[1], &s[1], &p[1]) == 13) {
+    daris_layer L[2];
+    std::memset(L, 0, sizeof L);
+    for (int i = 0; i < 2; ++i) {
+      L[i].op = DARIS_OP_CONV; L[i].c_in = cin; L[i].c_out = cout[i]; L[i].k = k[i]; L[i].stride = s[i]; L[i].pad = p[i]; L[i].groups = 1;
+      L[i].in_from = -1; L[i].res_from = -1;
+    }
     daris_dnn d;
-    d.n_layers = 1; d.in_c = cin; d.in_h = h; d.in_w = w; d.dtype = dtype; d.layers = &L;
+    d.n_layers = cout[1] ? 2 : 1; d.in_c = cin; d.in_h = h; d.in_w = w; d.dtype = dtype; d.layers = L;
     NetPlan net;
     const std::string err = build_plan(d, false, true, true, true, true, true, cus, &net);
     if (!err.empty()) {
       std::printf("-1 %s\n", err.c_str());
       continue;
     }
-    const LayerPlan& P = net.layers[0];
     const TensorInfo& in = net.tensor(0);
     static float ws;
-    ConvArgs a;
-    std::memset(&a, 0, sizeof a);
-    a.ws = &ws;
-    a.H = in.H; a.W = in.W; a.Cin = in.Cs; a.Ho = P.out.H; a.Wo = P.out.W; a.Cout = P.out.Cs;
-    a.kh = a.kw = k; a.stride = s; a.pad = p; a.Kpad = P.Kpad; a.M = P.out.H * P.out.W;
-    a.splitk = P.cp.splitk; a.S = P.cp.S; a.sz = P.cp.sz; a.sw = P.cp.sw; a.MT = P.cp.MT; a.NTn = P.cp.NTn; a.G = P.cp.G; a.xmode = P.cp.xmode;
-    a.c_real = net.fuse_ingest ? net.in_c : 0;
+    ConvArgs a[2];
+    std::memset(a, 0, sizeof a);
+    for (int i = 0; i < d.n_layers; ++i) {
+      const LayerPlan& P = net.layers[i];
+      ConvArgs& c = a[i];
+      c.ws = &ws;
+      c.H = in.H; c.W = in.W; c.Cin = in.Cs; c.Ho = P.out.H; c.Wo = P.out.W; c.Cout = P.out.Cs;
+      c.kh = c.kw = k[i]; c.stride = s[i]; c.pad = p[i]; c.Kpad = P.Kpad; c.M = P.out.H * P.out.W;
+      c.splitk = P.cp.splitk; c.S = P.cp.S; c.sz = P.cp.sz; c.sw = P.cp.sw; c.MT = P.cp.MT; c.NTn = P.cp.NTn; c.G = P.cp.G; c.xmode = P.cp.xmode;
+      c.c_real = i == 0 && net.fuse_ingest ? net.in_c : 0;
+    }
     std::vector<KernelLaunch> out;
-    const bool ok = encode_conv(kt, P.cp, a, net.bf16, &out);
-    std::printf("%d %d %d %d %d\n", ok ? 1 : 0, P.cp.kernel, P.cp.rows, P.cp.threads, P.cp.splitk);
+    const LayerPlan &A = net.layers[0], &B = net.layers[d.n_layers - 1];
+    const bool pair = A.pair_with >= 0;
+    bool ok;
+    if (pair) ok = B.macs >= A.macs ? encode_conv_pair(kt, B.cp, a[1], A.cp, a[0], net.bf16, &out) : encode_conv_pair(kt, A.cp, a[0], B.cp, a[1], net.bf16, &out);
+    else ok = encode_conv(kt, A.cp, a[0], net.bf16, &out) && (d.n_layers == 1 || encode_conv(kt, B.cp, a[1], net.bf16, &out));
+    std::printf("%d %d %d %d %d %d\n", ok ? 1 : 0, A.cp.kernel, A.cp.rows, A.cp.threads, A.cp.splitk, pair ? 1 : 0);
   }
   return 0;
 }

@@ -18,7 +18,7 @@ def plans(tmp_path_factory):
                            os.path.join(CSRC, "net_plan.cpp"), os.path.join(CSRC, "launch.cpp")])
 
     def run(shapes):
-        r = subprocess.run([exe], input="\n".join(" ".join(map(str, s)) for s in shapes) + "\n", capture_output=True, text=True, check=True)
+        r = subprocess.run([exe], input="\n".join(" ".join(map(str, s if len(s) == 13 else s + (0, 1, 1, 0))) for s in shapes) + "\n", capture_output=True, text=True, check=True)
         return [ln.split(maxsplit=1) if ln.startswith("-1") else [int(v) for v in ln.split()] for ln in r.stdout.splitlines()]
     return run
 
@@ -62,3 +62,21 @@ def test_every_plan_can_be_encoded(plans):
         if p[0] == "-1":                                    # refused in words: only where the index arithmetic says so
             assert "index arithmetic" in p[1], (s, p)
     assert {p[2] for p in got if p[0] == 1} == {16, 32, 64} and sum(p[2] == 64 for p in got if p[0] == 1) > 50
+
+
+def test_every_joint_launch_can_be_encoded(plans):
+    """Two convolutions that read the same tensor: whatever the planner joins, the encoder takes."""
+    rng = np.random.default_rng(18)
+    shapes = []
+    for _ in range(3000):
+        h, w = (int(v) for v in 2 ** rng.uniform(2, 7.5, 2))
+        ks = [int(rng.choice([1, 1, 3, 5, 7])) for _ in range(2)]
+        cin = int(rng.choice([4, 8, 20, 24, 32, 64, 128, 256, 512, 1024]))
+        one = [(int(rng.choice([8, 24, 64, 96, 128, 256, 512, 2048])), k, int(rng.integers(1, 3)), int(rng.integers(0, k + 1))) for k in ks]
+        if min(h, w) < max(ks):
+            continue
+        shapes.append((int(rng.integers(0, 2)), cin, h, w) + one[0] + (int(rng.choice([8, 32, 64, 96, 128, 192, 256])),) + one[1])
+    got = plans(shapes)
+    refused = [s for s, p in zip(shapes, got) if p[0] == 0]
+    assert len(got) == len(shapes) > 2000 and not refused, refused[:5]
+    assert sum(p[0] == 1 and p[5] for p in got) > 500
