@@ -190,6 +190,24 @@ def test_fc(c, h, w, n, act, dtype):
     run_case(layers, (c, h, w), dtype)
 
 
+# (dtype, c, h, w, n): vectors of 16 bytes a row, and what is left after the loop of one (fp32) or two (bf16) loads per lane
+FC_STREAM_CASES = [("bf16", 40, 23, 29, 2521),   # 3335 = 26 * 128 + 7, 134.5 MB
+                   ("bf16", 8, 2137, 1, 3930),   # 2137 = 16 * 128 + 89: the rest takes two passes
+                   ("bf16", 16, 32, 36, 7300),   # 2304 = 18 * 128: nothing is left
+                   ("fp32", 8, 2051, 1, 2050),   # 4102 = 64 * 64 + 6
+                   ("fp32", 64, 16, 12, 2733)]   # 3072 = 48 * 64
+
+
+@pytest.mark.parametrize("case", FC_STREAM_CASES, ids=lambda c: "x".join(map(str, c)))
+def test_fc_matrices_read_past_the_last_cache(case):
+    """Matrices of 128 MiB and more with rows of more than 2048 vectors: the streaming loop and its remainder."""
+    dtype, c, h, w, n = case
+    es = 2 if dtype == "bf16" else 4
+    assert n * c * h * w * es >= 128 << 20 and c * h * w * es // 16 > 2048      # the case runs the loop it names
+    layers = [N.Layer(op=N.OP_FC, c_in=c * h * w, c_out=n, act=0, in_from=-1)]
+    run_case(layers, (c, h, w), dtype, tol=2e-5)      # the logits stay in fp32: sqrt(K) * 2^-24 = 1e-5 in either type
+
+
 @pytest.mark.parametrize("dtype", ["fp32", "bf16"])
 def test_fc_chain_with_padded_vector(dtype):
     """FC -> FC where the intermediate vector length (10) is not a multiple of the 16-byte vector."""
