@@ -18,7 +18,7 @@ namespace daris {
 // The NW waves of a workgroup own the same tile and split K, as in conv_wave_body: no barrier in the K loop, the pixel
 // rows pass through a corner of LDS of the wave's own (coalesced 64-byte rows in, matrix order out), two chunks of rows and
 // weights are in flight.  The four 32 x 32 blocks of the partial tiles are then summed in wave order, NT / 256 blocks at
-// a time, which bounds the LDS at 16 KB per four waves, and finished by the same epilogue.
+// a time, which bounds the LDS at 8, 16 and 64 KB for 2, 4 and 8 waves, and finished by the same epilogue.
 template <int NW>
 __global__ __launch_bounds__(NW * 64) void conv_block_kernel(const ConvArgs) {
   const ConvArgs p = conv_args_at((ConstPtr)__builtin_amdgcn_kernarg_segment_ptr());

@@ -93,7 +93,7 @@ struct FcArgs {
   const float* bias;  // [N]
   void* y;            // [Ns], element type of the task, or float when out_f32; outputs N..Ns-1 are written as 0
   int K, N, Ns, act, out_f32;
-  int stream;    // 1: the matrix is read past the last cache (set by encode_fc)  // the block is fetched in two vectors of eight words
+  int stream;    // 1: the matrix is read past the last cache (set by encode_fc)
 };
 
 // Kernel and tile configuration chosen on the host for one dense convolution.
@@ -174,9 +174,12 @@ bool encode_conv_pair(const KernelTable& kt, const ConvPlan& pl0, const ConvArgs
 bool encode_conv_dw(const KernelTable& kt, const ConvPlan& pl, const ConvArgs& a, const DwFusedArgs& d, int bf16, std::vector<KernelLaunch>* out);
 // Whether a depthwise 3x3 layer in front of the 1x1 convolution planned as pl should be computed inside that convolution's
 // launch.  Measured on MobileNetV2's blocks: the producer re-reads the depthwise input up to nine times through one CU's
-// vector cache and pays a memory latency per chunk of 64 bytes of channels, so it wins only where the convolution has enough
+// vector cache and pays a memory latency per chunk of 64 bytes of channels, so it can only win where the convolution has enough
 // workgroups to fill a partition and a single channel block (no repetition per block, few chunks per wave); elsewhere the
-// separate, fully parallel depthwise launch is faster (by 1.3 to 5 us per block).
+// separate, fully parallel depthwise launch is faster (by 1.3 to 5 us per block).  There it saves a launch, and since both separate
+// launches have become faster it is about even.  us fused / both separate, fp32, the three blocks: 128 CUs 6.7 / 6.9, 6.7 / 6.7, 6.9 / 7.1
+// (frame 211.1 / 211.6); 192 CUs 5.6 / 6.4, 6.8 / 6.2, 6.9 / 6.6 (207.7 / 206.8); 96 CUs 8.9 / 7.7, 7.7 / 7.2, 7.7 / 7.9 (223.5 / 219.9); 64 CUs 11.4 / 9.2,
+// 7.7 / 8.1, 8.1 / 9.1 (237.3 / 236.1); bf16 on 128 CUs 5.8 / 6.2, 6.6 / 5.9 (181.7 / 180.9).
 bool conv_dw_fusable(const ConvPlan& pl, int bf16);
 bool encode_dwconv(const KernelTable& kt, const DwArgs& a, int bf16, std::vector<KernelLaunch>* out);
 bool encode_maxpool(const KernelTable& kt, const PoolArgs& a, int bf16, std::vector<KernelLaunch>* out);

@@ -210,8 +210,9 @@ DARIS_INST_ALL(false)
 DARIS_INST_ALL(true)
 DARIS_INST_CONV_ALIGNED(1, 2) DARIS_INST_CONV_ALIGNED(1, 4) DARIS_INST_CONV_ALIGNED(1, 8)
 DARIS_INST_CONV_ALIGNED(2, 2) DARIS_INST_CONV_ALIGNED(2, 4) DARIS_INST_CONV_ALIGNED(2, 8)
-// Fused depthwise variants.  fp32 tiles of 64 channels are never staged, so they have none; bf16 plans never use 8 waves per
-// workgroup, and those variants would need scratch memory, which the dispatch path does not provide.
+// Fused depthwise variants.  In fp32 for 32-channel tiles only: with 64 channels they take 249 to 300 registers, and no projection of
+// MobileNetV2 with enough pixels has more than 24; bf16 plans never use 8 waves per workgroup, and those variants would need scratch memory, which the dispatch path
+// does not provide.
 DARIS_INST_CONVDW(false, 1, 2) DARIS_INST_CONVDW(false, 1, 4) DARIS_INST_CONVDW(false, 1, 8)
 DARIS_INST_CONVDW(true, 1, 2) DARIS_INST_CONVDW(true, 1, 4) DARIS_INST_CONVDW(true, 2, 2) DARIS_INST_CONVDW(true, 2, 4)
 #undef DARIS_INST_CONVDW

@@ -29,9 +29,9 @@ static double round_waste(int groups, int cus) { return (double)cdiv(groups, cus
 
 static ConvPlan plan_conv_wave(int M, int N, int Kpad, int bf16, int step_align, int nominal_cus, bool allow_block, int force_tn = 0, int force_nw = 0) {
   const int kNominalWaveSlots = 4 * nominal_cus;  // SIMDs of the partition size the plan is balanced for
-  // Measured on a 128-CU partition (fp32, ResNet-18 shapes): the K loop itself runs near the MFMA rate; what a
-  // launch pays for is its fixed cost and idle CUs.  Best found: 8 waves per workgroup splitting K, and enough
-  // grid.z slices that tiles * z is about the number of CUs, while a wave keeps at least ~6 steps.
+  // What a launch of few tiles pays for is its fixed cost and idle CUs.  Best found on a 128-CU partition (ResNet-18 shapes): 8
+  // waves per workgroup splitting K, and enough grid.z slices that tiles * z is about the number of CUs, while a wave keeps
+  // at least ~6 steps.
   ConvPlan pl = ConvPlan();
   const int ks = bf16 ? 16 : 8;  // k per step: two 16-byte vectors
   const int S = Kpad / ks;
@@ -69,8 +69,12 @@ static ConvPlan plan_conv_wave(int M, int N, int Kpad, int bf16, int step_align,
   if (tiles > nominal_cus) {
     // More tiles than CUs: the launch runs in ceil(tiles * z / CUs) rounds of workgroups whose K loops take
     // (S / z) * tn * c cycles of MFMA time per SIMD, so a K split can even out the last round (200 tiles: z = 1 and 2
-    // need the time of 2 whole tiles, z = 3 that of 5/3).  Model checked against measured VGG-16 layers (within 3 %):
-    // loop time x 1.3 + a reduction pass of 3 us + its traffic at 1.5 TB/s.
+    // need the time of 2 whole tiles, z = 3 that of 5/3).  Estimate: loop time x 1.3 + a reduction pass of 3 us + its traffic at
+    // 1.5 TB/s.  It was fitted to the fp32 matrix instruction; with the three-part products, which are not bound by the matrix pipe
+    // alone, layers take 1.2 to 2.1 times as long, and for the 64 x 64 tiles it overrates the split.  us with the split that it takes
+    // and without one: 784 x 512 x 4608 on 64 CUs 70.5, 73.9, on 96 77.2, 75.2, on 192 (32-pixel tiles) 47.1, 50.4; 784 x 512 x 2304 on
+    // 96 47.2, 42.5; 3136 x 256 x 2304 on 64 82.9, 74.0, on 96 60.9, 59.7, on 192 51.2, 46.5.  On 128 CUs and in bf16 it splits none of
+    // VGG-16's layers.
     const double cyc = block ? 96.0 : bf16 ? tn * 8.0 : (tn == 1 ? 40.0 : 64.0);
     double best = 1e30;
     for (int zz = 1; zz <= 6 && S / (nw * zz) >= 6; ++zz) {
@@ -124,9 +128,12 @@ static ConvPlan plan_conv_wave(int M, int N, int Kpad, int bf16, int step_align,
 // 16-pixel tiles of tn 16-channel blocks, K split among the waves of a workgroup only.  Chosen for layers whose 32-row
 // plan needs a reduction launch; returns kernel == K_NONE when a wave would walk more than 18 steps while the shape does not fill
 // three quarters of the nominal partition either, or when it is too shallow to split eight (four) ways.  Up to 18 steps the walk is
-// shorter than the reduction launch, however few the tiles (us with 32-pixel tiles and a reduction -> with 16-pixel tiles:
-// fp32 40 tiles of 7.5 steps 6.4 -> 3.9, 128 tiles of 16 steps planned for 192 CUs 6.7 -> 5.2, but of 36 steps 7.9 -> 8.5; bf16 of 8
-// steps 5.3 -> 3.8, of 18 steps 5.8 -> 4.9).
+// shorter than the reduction launch, however few the tiles.  us with 32-pixel tiles and a reduction -> with 16-pixel tiles, 64 tiles
+// (49 x 256) on 128 CUs and 128 tiles (49 x 512) on 192: fp32 of 8 steps 6.3 -> 4.0 and 6.5 -> 4.1, 16: 6.7 -> 5.3 and 7.0 -> 5.5, 18: 6.4 ->
+// 5.6 and 6.7 -> 5.8, 24: 6.8 -> 6.6 and 7.4 -> 6.8, 28: 7.2 -> 7.3 and 7.7 -> 7.5, 32: 7.3 -> 7.9 and 8.2 -> 8.3, 36: 7.7 -> 8.5 and 8.3 -> 8.9;
+// bf16 of 8 steps 5.3 -> 3.8 and 5.4 -> 3.8, 18: 5.7 -> 4.8 and 5.9 -> 5.0.  The two meet at 24 to 32 steps: 18 leaves room.  Tiles that
+// fill three quarters are taken at any length, up to 32 steps with a gain (128 tiles on 128 CUs: 24 steps 7.5 -> 6.8, 32: 8.4 -> 8.2), at
+// 36 without one (8.8 -> 8.8; 104 tiles 8.7 -> 9.6).
 static ConvPlan plan_conv_wave16(int M, int N, int Kpad, int bf16, int nominal_cus, int force_tn = 0, int force_nw = 0) {
   ConvPlan pl = ConvPlan();
   const int ks = bf16 ? 32 : 16;
