@@ -119,8 +119,8 @@ inline bool conv_block_takes(int H, int W, int cin_stride, int k, int pad, int K
   return k * k <= 31 && pad < k && conv_rows_staged(cin_stride, 0) && (uint64_t)(H + pad) * (uint64_t)W * (uint64_t)cin_stride * 4 < (1ull << 31) &&
          (uint64_t)(Kpad / 8) * 3072 + 12288 < (1ull << 31);
 }
-// bf16 = 0/1.  Chooses tile shape, waves per workgroup and split-K from (M, N, Kpad) and the nominal partition size
-// (nominal_cus: how many CUs the grid is balanced for) only, so results do not depend on the partition a stage runs in.  step_align = 2 cuts K in whole chunks of two steps (for conv_rows_staged shapes), else 1.
+// bf16 = 0/1.  Chooses tile shape, waves per workgroup and split-K from (M, N, Kpad), allow_block and the nominal partition
+// size (nominal_cus: how many CUs the grid is balanced for) only, so results do not depend on the partition a stage runs in.  step_align = 2 cuts K in whole chunks of two steps (for conv_rows_staged shapes), else 1.
 // cin_stride = the input tensor's channel stride: when it is a whole number of the 16-row kernel's K steps and the 32-row
 // plan would split K across workgroups, a 16-row plan that does not need to is chosen instead (cin_stride 0: never).
 // allow_block = false: no 64-pixel tiles (a convolution that conv_block_takes refuses, shares its launch or computes its input on the fly).
