@@ -112,6 +112,12 @@ struct ConvPlan {
 // True when every pixel's channel vector is a whole number of 64-byte rows, the shape for which the convolution kernel
 // fetches the pixel operand in coalesced rows through LDS (chunks of two K steps).
 inline bool conv_rows_staged(int cin_stride, int bf16) { return cin_stride > 0 && (cin_stride * (bf16 ? 2 : 4)) % 64 == 0; }
+// Whether the kernels that fetch such rows (conv_rows_body) can run a convolution: their byte offsets into the input, the output
+// (for the residual operand) and a wave's slice of the weights are 31-bit numbers.
+inline bool conv_rows_take(int H, int W, int cin_stride, uint64_t M, int cout_stride, int Kpad, int bf16) {
+  const uint64_t es = bf16 ? 2 : 4, limit = 1ull << 31;
+  return conv_rows_staged(cin_stride, bf16) && (uint64_t)H * (uint64_t)W * (uint64_t)cin_stride * es < limit && M * (uint64_t)cout_stride * es < limit && (uint64_t)Kpad * 192 < limit;
+}
 // Whether the kernel of 64 x 64 tiles can run an fp32 convolution of this geometry: it keeps one bit per filter tap in a word
 // and walks the rows of taps inside the image as a rectangle of them, and its byte offsets into the input and into the weights
 // of two channel blocks are signed 32-bit numbers.

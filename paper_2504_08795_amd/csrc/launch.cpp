@@ -305,6 +305,8 @@ std::string KernelTable::resolve(const AqlRuntime& rt) {
 
 // ---- encoders ----------------------------------------------------------------------------------------------------------------
 
+static bool rows_take(const ConvArgs& a, int bf16) { return a.c_real == 0 && conv_rows_take(a.H, a.W, a.Cin, (uint64_t)a.M, a.Cout, a.Kpad, bf16); }
+
 static bool push_reduce(const KernelTable& kt, const ConvPlan& pl, const ConvArgs& a, int bf16, std::vector<KernelLaunch>* out) {
   if (pl.splitk <= 1) return true;
   const size_t total4 = (size_t)a.M * a.Cout / 4;
@@ -316,7 +318,7 @@ bool encode_conv(const KernelTable& kt, const ConvPlan& pl, const ConvArgs& a, i
   if (pl.rows == 16) {
     const int v16 = pl.kernel - (bf16 ? K_CONV16_BF16_T1W2 : K_CONV16_F32_T1W2);
     const int ks16 = bf16 ? 32 : 16;
-    if (v16 < 0 || v16 >= 6 || pl.threads != 64 * pl.nw || a.c_real > 0 || a.Cin % ks16 || a.Kpad % 32 || pl.S * ks16 != a.Kpad || pl.sw % pl.step_align) return false;
+    if (v16 < 0 || v16 >= 6 || pl.threads != 64 * pl.nw || !rows_take(a, bf16) || a.Kpad % 32 || pl.S * ks16 != a.Kpad || pl.sw % pl.step_align) return false;
     if (pl.splitk > 1 && !a.ws) return false;
     if (!push(out, kt.conv16[bf16][v16], pl.kernel, pl.grid_x, (uint32_t)pl.threads, &a, sizeof(a))) return false;
     return push_reduce(kt, pl, a, bf16, out);
@@ -333,7 +335,7 @@ bool encode_conv(const KernelTable& kt, const ConvPlan& pl, const ConvArgs& a, i
   if (variant < 0 || variant >= 6 || pl.rows != 32 || pl.threads != 64 * pl.nw) return false;
   // 0: a K step never straddles a filter tap (bf16); 1: general walk; 2: layer 0 reading the caller's fp32 [C][H][W] input;
   // 3: a pixel's channels are whole 64-byte rows and the plan cuts K in chunks of two steps: pixel operand through LDS
-  const int mode = a.c_real > 0 ? 2 : (conv_rows_staged(a.Cin, bf16) && pl.staged ? 3 : (bf16 && a.Cin % 16 == 0 ? 0 : 1));
+  const int mode = a.c_real > 0 ? 2 : (rows_take(a, bf16) && pl.staged ? 3 : (bf16 && a.Cin % 16 == 0 ? 0 : 1));
   if ((mode == 3 || !bf16) && (pl.S % 2 || pl.sz % 2 || pl.sw % 2)) return false;
   if (mode == 2 && (a.Cin != (bf16 ? 8 : 4) || a.c_real > 4 || (uint64_t)a.c_real * a.H * a.W * 4 >= (1ull << 31))) return false;
   if (pl.splitk > 1 && !a.ws) return false;
@@ -371,8 +373,8 @@ bool encode_conv_pair(const KernelTable& kt, const ConvPlan& pl0, const ConvArgs
   if (pl0.rows == 16) {
     const int ks16 = bf16 ? 32 : 16;
     const int v16 = pl0.kernel - (bf16 ? K_CONV16_BF16_T1W2 : K_CONV16_F32_T1W2);
-    if (pl1.rows != 16 || pl0.kernel != pl1.kernel || v16 < 0 || v16 >= 6 || pl0.splitk != 1 || pl1.splitk != 1 || a0.c_real > 0 || a1.c_real > 0 ||
-        a0.Cin % ks16 || a1.Cin % ks16 || a0.Kpad % 32 || a1.Kpad % 32 || pl0.sw % pl0.step_align || pl1.sw % pl1.step_align || pl0.S * ks16 != a0.Kpad || pl1.S * ks16 != a1.Kpad)
+    if (pl1.rows != 16 || pl0.kernel != pl1.kernel || v16 < 0 || v16 >= 6 || pl0.splitk != 1 || pl1.splitk != 1 || !rows_take(a0, bf16) || !rows_take(a1, bf16) ||
+        a0.Kpad % 32 || a1.Kpad % 32 || pl0.sw % pl0.step_align || pl1.sw % pl1.step_align || pl0.S * ks16 != a0.Kpad || pl1.S * ks16 != a1.Kpad)
       return false;
     PairArgs pa;
     std::memset(&pa, 0, sizeof(pa));
@@ -383,7 +385,7 @@ bool encode_conv_pair(const KernelTable& kt, const ConvPlan& pl0, const ConvArgs
   }
   const bool aligned = bf16 && a0.Cin % 16 == 0;
   if (pl0.kernel != pl1.kernel || pl0.rows != 32 || pl1.rows != 32 || aligned != (bf16 && a1.Cin % 16 == 0) || pl1.splitk != 1 || a0.c_real > 0 || a1.c_real > 0) return false;
-  const bool staged = conv_rows_staged(a0.Cin, bf16) && conv_rows_staged(a1.Cin, bf16) && pl0.staged && pl1.staged;
+  const bool staged = rows_take(a0, bf16) && rows_take(a1, bf16) && pl0.staged && pl1.staged;
   if ((staged || !bf16) && (pl0.S % 2 || pl0.sz % 2 || pl0.sw % 2 || pl1.S % 2 || pl1.sz % 2 || pl1.sw % 2)) return false;
   const int variant = pl0.kernel - (bf16 ? K_CONVW_BF16_T1W2 : K_CONVW_F32_T1W2);
   if (variant < 0 || variant >= 6 || (pl0.splitk > 1 && !a0.ws)) return false;

@@ -177,22 +177,185 @@ __device__ __forceinline__ void plain_products(const ConvArgs& p, const DwFusedA
 //
 // The pixels are requested before the weights: loads return in order, and what the pixels pass through on their way to the
 // matrix pipe takes longer (0.25 us per launch the other way round).
+// What a wave tile's launch does once the K loop is over: the partial tiles of the NW waves are summed through LDS in wave
+// order and each sum gets bias, residual and activation.  R = 32 or 16 pixels, channel blocks of the same size.  Works on quads of
+// consecutive channels: quad q of the tile = elements 4q..4q+3 = lanes l..l+3 of one accumulator row (j, v), i.e. one pixel
+// (place()) and channels R*(nb0+j) + l%R .. +3.  A thread's quads q = tid + r*NT all have the same l, so it needs the bias of
+// one channel quad per channel block; that and the residual are fetched ahead of the sums (when this launch applies them itself).
+template <int R>
+using WaveAcc = typename std::conditional<R == 32, f32x16, f32x4>::type;
+// BUFFER: everything goes through buffer descriptors, which give 0 past the end and drop what is stored there, so that nothing is
+// conditional and the compiler can count the loads (tensors below 2 GiB).
+template <bool BF16, int R, int TN, int NW, bool BUFFER>
+struct WaveEpilogue {
+  static constexpr int ES = BF16 ? 2 : 4, NT = NW * 64, V = R * R / 64, TILE = TN * R * R;  // V: accumulator rows of a block
+  static constexpr int QUADS = TILE / 4, RQ = (QUADS + NT - 1) / NT;  // quads of the tile, of a thread
+  static constexpr int NB = RQ == 1 ? 1 : TN;
+  using ResVec = typename std::conditional<BF16, uint2, uint4>::type;
+  static constexpr int kOutside = (int)0x80000000;  // an offset past the end of any tensor
+  float4 bias_j[NB];
+  ResVec res_pre[RQ];
+  int at[RQ];  // BUFFER: byte offset of the quad in the output and in the residual operand
+  bool own_epilogue, use_res;
+
+  // channel block, pixel and first channel of the quad that starts at tile element e = (j*V + v)*64 + lane
+  __device__ __forceinline__ void place(const int e, const int m0, const int nb0, int* j, int* mm, int* n) const {
+    const int v = (e >> 6) % V, l = e & 63;
+    *j = (e >> 6) / V;
+    *mm = m0 + (R == 32 ? (v >> 2) * 8 + (l >> 5) * 4 + (v & 3) : (l >> 4) * 4 + v);
+    *n = (nb0 + *j) * R + l % R;
+  }
+  __device__ __forceinline__ void fetch(const ConvArgs& p, const int m0, const int nb0, const int tid) {
+    own_epilogue = p.splitk == 1;
+    use_res = own_epilogue && p.res != nullptr;
+    const auto brsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p.bias), 0, BUFFER ? p.Cout * 4 : 0, 0x00027000);
+    const auto rrsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p.res), 0, BUFFER && use_res ? p.M * p.Cout * ES : 0, 0x00027000);
+#pragma unroll
+    for (int k = 0; k < NB; ++k) {
+      int j, mm, n;
+      place(4 * tid, m0, nb0, &j, &mm, &n);
+      if (NB > 1) n += (k - j) * R;
+      if constexpr (BUFFER) bias_j[k] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(brsrc, n * 4, 0, 0));
+      else bias_j[k] = (n < p.Cout) ? *(const float4*)(p.bias + n) : make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+#pragma unroll
+    for (int r = 0; r < RQ; ++r) {
+      res_pre[r] = ResVec();
+      const int e = 4 * (tid + r * NT);
+      int j, mm, n;
+      place(e, m0, nb0, &j, &mm, &n);
+      const bool ok = (QUADS % NT == 0 || e < TILE) && mm < p.M && n < p.Cout;
+      if constexpr (BUFFER) {
+        at[r] = ok ? (mm * p.Cout + n) * ES : kOutside;
+        if constexpr (BF16) res_pre[r] = __builtin_bit_cast(ResVec, __builtin_amdgcn_raw_buffer_load_b64(rrsrc, at[r], 0, 0));
+        else res_pre[r] = __builtin_bit_cast(ResVec, __builtin_amdgcn_raw_buffer_load_b128(rrsrc, at[r], 0, 0));
+      } else if (use_res && ok) {
+        res_pre[r] = *(const ResVec*)((const unsigned char*)p.res + ((size_t)mm * p.Cout + n) * ES);
+      }
+    }
+  }
+
+  // MODE as in conv_wave_body; acc = the wave's partial tile over K steps [sbeg, sbeg + nsteps)
+  template <int MODE>
+  __device__ __forceinline__ void finish(const ConvArgs& p, const DwFusedArgs& dwf, WaveAcc<R> (&acc)[TN], float* const red, const int m0, const int nb0, const int zi,
+                                         const int sbeg, const int nsteps) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    auto park = [&]() {
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int v = 0; v < V; ++v) red[wave * TILE + (j * V + v) * 64 + lane] = acc[j][v];
+    };
+    float4 sums[RQ];
+    auto add_up = [&]() {
+#pragma unroll
+      for (int r = 0; r < RQ; ++r) {
+        const int e = 4 * (tid + r * NT);
+        if (QUADS % NT != 0 && wave >= QUADS / 64) {  // (the waves past the tile)
+          sums[r] = make_float4(0.f, 0.f, 0.f, 0.f);
+          if (!BF16) sums[r].x = red[lane % NW * TILE + lane];  // ... look whether one of the partial tiles is spoiled
+          continue;
+        }
+        sums[r] = *(const float4*)&red[e];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) {
+          const float4 t = *(const float4*)&red[w * TILE + e];
+          sums[r].x += t.x; sums[r].y += t.y; sums[r].z += t.z; sums[r].w += t.w;
+        }
+      }
+    };
+    park();
+    if constexpr (!BF16) spoil_unless_in_range(acc, red + wave * TILE, V * TN);
+    __syncthreads();
+    add_up();
+    if constexpr (!BF16) {
+      if (__builtin_expect(spoiled(sums[0].x), 0)) {  // every thread of the workgroup or none (out of the way: a launch fetches its code anew, and a longer path costs 0.2 us)
+        __syncthreads();
+        plain_products<MODE, R, 1, TN>(p, dwf, m0, nb0, sbeg, nsteps, acc);
+        park();
+        __syncthreads();
+        add_up();
+      }
+    }
+    if (!own_epilogue) {  // partial sums of this K slice; splitk_reduce_kernel finishes the layer
+#pragma unroll
+      for (int r = 0; r < RQ; ++r) {
+        const int e = 4 * (tid + r * NT);
+        int j, mm, n;
+        place(e, m0, nb0, &j, &mm, &n);
+        if ((QUADS % NT == 0 || e < TILE) && mm < p.M && n < p.Cout) put(p.ws + (size_t)zi * p.M * p.Cout + (size_t)mm * p.Cout + n, sums[r]);
+      }
+      return;
+    }
+    // All quads are finished before the first is stored: loads and stores are counted together, so a quad that waited for its
+    // residual behind a store would wait for the store's way to memory as well, 0.5 us each (3136 x 256 x 64 in bf16, four
+    // quads a thread: 1.3 us of a launch of 4.5).
+    float val[4 * RQ];
+#pragma unroll
+    for (int r = 0; r < RQ; ++r) {
+      const int j = ((4 * (tid + r * NT)) >> 6) / V;
+      float4 b = bias_j[0];  // component-wise select: indexing the array with a run-time j would move it out of registers
+      if (NB == 2) {
+        const bool hi = j != 0;
+        b.x = hi ? bias_j[NB - 1].x : b.x; b.y = hi ? bias_j[NB - 1].y : b.y;
+        b.z = hi ? bias_j[NB - 1].z : b.z; b.w = hi ? bias_j[NB - 1].w : b.w;
+      }
+      val[4 * r] = sums[r].x + b.x; val[4 * r + 1] = sums[r].y + b.y; val[4 * r + 2] = sums[r].z + b.z; val[4 * r + 3] = sums[r].w + b.w;
+    }
+    if (use_res) {
+#pragma unroll
+      for (int r = 0; r < RQ; ++r) {
+        const ResVec rv = res_pre[r];
+        if constexpr (BF16) {
+          val[4 * r] += __uint_as_float(rv.x << 16); val[4 * r + 1] += __uint_as_float(rv.x & 0xffff0000u);
+          val[4 * r + 2] += __uint_as_float(rv.y << 16); val[4 * r + 3] += __uint_as_float(rv.y & 0xffff0000u);
+        } else {
+          val[4 * r] += __uint_as_float(rv.x); val[4 * r + 1] += __uint_as_float(rv.y);
+          val[4 * r + 2] += __uint_as_float(rv.z); val[4 * r + 3] += __uint_as_float(rv.w);
+        }
+      }
+    }
+    apply_act(val, p.act);
+    ResVec out[RQ];
+#pragma unroll
+    for (int r = 0; r < RQ; ++r) {
+      const float* const v = val + 4 * r;
+      if constexpr (BF16) {
+        out[r].x = pack_bf16_rne(v[0], v[1]);
+        out[r].y = pack_bf16_rne(v[2], v[3]);
+      } else {
+        out[r] = make_uint4(__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3]));
+      }
+    }
+    const auto yrsrc = __builtin_amdgcn_make_buffer_rsrc(p.y, 0, BUFFER ? p.M * p.Cout * ES : 0, 0x00027000);
+#pragma unroll
+    for (int r = 0; r < RQ; ++r) {
+      if constexpr (BUFFER) {
+        put_at(yrsrc, at[r], out[r]);
+      } else {
+        const int e = 4 * (tid + r * NT);
+        int j, mm, n;
+        place(e, m0, nb0, &j, &mm, &n);
+        if ((QUADS % NT == 0 || e < TILE) && mm < p.M && n < p.Cout) put((unsigned char*)p.y + ((size_t)mm * p.Cout + n) * ES, out[r]);
+      }
+    }
+  }
+};
+
 template <bool BF16, int TN, int NW, int MODE>
 constexpr int conv_wave_lds() {  // floats of LDS
-  return (MODE == 3 || MODE == 4) && NW * 32 * 5 * 4 > NW * TN * 1024 ? NW * 32 * 5 * 4 : NW * TN * 1024;
+  return MODE == 4 && NW * 32 * 5 * 4 > NW * TN * 1024 ? NW * 32 * 5 * 4 : NW * TN * 1024;
 }
 template <bool BF16, int TN, int NW, int MODE, int DC>
 __device__ __forceinline__ void conv_wave_body(const ConvArgs& p, const int mt, const int g, float* const red, const DwFusedArgs& dwf) {
-  // MODE 0 (bf16): Cin a multiple of KS; 1: any Cin; 2: the network input itself, fp32 [C][H][W]; 3: a pixel's channels are whole
-  // 64-byte rows (Cin * ES a multiple of 64): the pixel operand is fetched in coalesced rows and transposed through LDS;
-  // 4: like 3 for a 1x1 convolution whose input is the output of a 3x3 depthwise convolution that is never stored: the
-  // rows are computed here from the depthwise layer's input (p.x) and weights (dwf)
+  // MODE 0 (bf16): Cin a multiple of KS; 1: any Cin; 2: the network input itself, fp32 [C][H][W]; 4: a 1x1 convolution whose
+  // input is the output of a 3x3 depthwise convolution that is never stored: the rows are computed here from the depthwise
+  // layer's input (p.x) and weights (dwf).  (3: conv_rows_body)
   // fp32: two K steps of 8 make one chunk of 16, the depth of the bf16 matrix instruction that takes the operands' three
   // parts (split8); the plan cuts K in whole chunks, the weights are stored as [channel block][chunk][part][lane][16 B].
   constexpr bool ALIGNED = MODE == 0;
   static_assert(BF16 || MODE != 0, "fp32 locates its quads of channels in closed form whatever Cin is");
-  constexpr bool STAGED = MODE == 3 || MODE == 4;
-  constexpr bool DWF = MODE == 4;
+  constexpr bool STAGED = MODE == 4;
   constexpr int ES = BF16 ? 2 : 4;
   constexpr int VEC = 16 / ES;
   constexpr int KS = 2 * VEC;
@@ -297,40 +460,8 @@ __device__ __forceinline__ void conv_wave_body(const ConvArgs& p, const int mt, 
     }
   };
 
-  // The epilogue works on quads of consecutive channels: quad q of the tile = elements 4q..4q+3 = lanes l..l+3 of one
-  // accumulator row (j, v), i.e. one pixel and channels 32*(nb0+j) + l%32 .. +3.  A thread's quads q = tid + r*NT all
-  // have the same l, so it needs the bias of one channel quad per channel block; fetched here, before the K loop,
-  // so that the latency is hidden.
-  const int ql = (4 * tid) & 63;  // first lane of this thread's quads
-  float4 bias_j[TN];
-#pragma unroll
-  for (int j = 0; j < TN; ++j) {
-    const int n = (nb0 + j) * 32 + (ql & 31);
-    bias_j[j] = (n < p.Cout) ? *(const float4*)(p.bias + n) : make_float4(0.f, 0.f, 0.f, 0.f);
-  }
-
-  // The residual operand of this thread's quads is fetched ahead of the K loop as well (when this launch applies the epilogue
-  // itself).
-  constexpr int QUADS = TILE / 4;
-  constexpr int RQ = (QUADS + NT - 1) / NT;  // quads per thread
-  using ResVec = typename std::conditional<BF16, uint2, uint4>::type;
-  ResVec res_pre[RQ];
-  const bool own_epilogue = p.splitk == 1;
-  const bool use_res = own_epilogue && p.res != nullptr;
-  auto fetch_res = [&]() {
-#pragma unroll
-    for (int r = 0; r < RQ; ++r) {
-      res_pre[r] = ResVec();
-      const int e = 4 * (tid + r * NT);
-      const int j = e >> 10, v = (e >> 6) & 15, l = e & 63;
-      const int mm = m0 + (v >> 2) * 8 + (l >> 5) * 4 + (v & 3);
-      const int n = (nb0 + j) * 32 + (l & 31);
-      if (use_res && (QUADS % NT == 0 || e < TILE) && mm < p.M && n < p.Cout)
-        res_pre[r] = *(const ResVec*)((const unsigned char*)p.res + ((size_t)mm * p.Cout + n) * ES);
-    }
-  };
-
-  fetch_res();
+  WaveEpilogue<BF16, 32, TN, NW, false> fin;
+  fin.fetch(p, m0, nb0, tid);
 
   f32x16 acc[TN];
 #pragma unroll
@@ -428,14 +559,8 @@ __device__ __forceinline__ void conv_wave_body(const ConvArgs& p, const int mt, 
     for (int d = 0; d < D; ++d)
       if (done + d < nsteps) compute(d);
   } else {
-    // Staged pixel operand.  A load instruction is served 64 bytes per cycle only when four neighbouring lanes read one
-    // 64-byte segment; the register-fed path above has every lane in a different pixel (a different cache line), which
-    // makes the pixel operand cost four times the cycles of the same bytes of weights and binds the small layers to
-    // the load unit instead of the matrix pipe.  Here a wave fetches, per chunk of two K steps, 64 contiguous bytes
-    // of each of its 32 pixels as whole rows (lane = (pixel, 16-byte piece): 4 lanes per row, 16 rows per
-    // instruction), parks them in its own corner of LDS, and reads them back in MFMA order (lane = pixel row, half =
-    // K half).  No workgroup barrier is involved: the buffer is private to the wave.  Two chunks of rows and four steps
-    // of weights are in flight.  The plan makes every wave's K slice a whole number of chunks.
+    // The rows of a chunk of two K steps are computed where conv_rows_body would have loaded them, and pass through the wave's own
+    // corner of LDS in the same way.
     uint4* const st = reinterpret_cast<uint4*>(red) + wave * STAGE_V;
     const int piece = lane & 3, prow = lane >> 2;
     auto load_w = [&](int d) {
@@ -482,488 +607,277 @@ __device__ __forceinline__ void conv_wave_body(const ConvArgs& p, const int mt, 
       }
     };
     const int nchunks = nsteps >> 1;
-    if constexpr (DWF) {
-      // The 1x1 convolution's input row of pixel (y, x), channels c..c+VEC-1, is the depthwise layer's output there:
-      // act(bias[c] + sum over the 3x3 taps inside the image, in (ky, kx) order, of in[y*stride-1+ky][x*stride-1+kx][c] * w[tap][c]),
-      // accumulated with fused multiply-adds in exactly the order of dwconv_kernel, then rounded to the element type as a
-      // stored tensor would be.  A lane computes the 16-byte piece it would otherwise have loaded.
-      const unsigned char* dww = (const unsigned char*)dwf.w;
-      int poff[2][9];     // element offset of each tap's input pixel (0 where the tap is outside: the value is not used)
-      unsigned vmask[2];  // bit t: tap t of this lane's pixel lies inside the image
+    // The 1x1 convolution's input row of pixel (y, x), channels c..c+VEC-1, is the depthwise layer's output there:
+    // act(bias[c] + sum over the 3x3 taps inside the image, in (ky, kx) order, of in[y*stride-1+ky][x*stride-1+kx][c] * w[tap][c]),
+    // accumulated with fused multiply-adds in exactly the order of dwconv_kernel, then rounded to the element type as a
+    // stored tensor would be.  A lane computes the 16-byte piece it would otherwise have loaded.
+    const unsigned char* dww = (const unsigned char*)dwf.w;
+    int poff[2][9];     // element offset of each tap's input pixel (0 where the tap is outside: the value is not used)
+    unsigned vmask[2];  // bit t: tap t of this lane's pixel lies inside the image
 #pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const int mj = m0 + 16 * j + prow;
-        const bool okj = mj < p.M;
-        const int y = fast_div(mj, p.mg_wo), x = mj - y * p.Wo;
-        vmask[j] = 0u;
+    for (int j = 0; j < 2; ++j) {
+      const int mj = m0 + 16 * j + prow;
+      const bool okj = mj < p.M;
+      const int y = fast_div(mj, p.mg_wo), x = mj - y * p.Wo;
+      vmask[j] = 0u;
 #pragma unroll
-        for (int t = 0; t < 9; ++t) {
-          const int iy = y * dwf.stride - 1 + t / 3, ix = x * dwf.stride - 1 + t % 3;
-          const bool v = okj && (unsigned)iy < (unsigned)dwf.H && (unsigned)ix < (unsigned)dwf.W;
-          poff[j][t] = v ? (iy * dwf.W + ix) * p.Cin : 0;
-          vmask[j] |= v ? (1u << t) : 0u;
-        }
+      for (int t = 0; t < 9; ++t) {
+        const int iy = y * dwf.stride - 1 + t / 3, ix = x * dwf.stride - 1 + t % 3;
+        const bool v = okj && (unsigned)iy < (unsigned)dwf.H && (unsigned)ix < (unsigned)dwf.W;
+        poff[j][t] = v ? (iy * dwf.W + ix) * p.Cin : 0;
+        vmask[j] |= v ? (1u << t) : 0u;
       }
-      int cch = sbeg * KS;  // first channel of the wave's next chunk (wave-uniform)
-      uint4 xv[2][9], wv[9];
-      float4 bv[VEC / 4];
-      auto dw_issue = [&]() {  // loads of the chunk at cch; past the end of the slice the last chunk of the tensor is read again (never used)
-        const int c = min(cch, p.Cin - 2 * KS) + piece * VEC;
-#pragma unroll
-        for (int t = 0; t < 9; ++t) wv[t] = *(const uint4*)(dww + ((size_t)t * p.Cin + c) * ES);
-#pragma unroll
-        for (int q = 0; q < VEC / 4; ++q) bv[q] = *(const float4*)(dwf.bias + c + 4 * q);
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-          for (int t = 0; t < 9; ++t) xv[j][t] = *(const uint4*)(xb + ((size_t)poff[j][t] + c) * ES);
-        cch += 2 * KS;
-      };
-      auto dw_value = [&](int j) -> uint4 {
-        float acc[VEC];
-#pragma unroll
-        for (int q = 0; q < VEC / 4; ++q) {
-          acc[4 * q] = bv[q].x; acc[4 * q + 1] = bv[q].y; acc[4 * q + 2] = bv[q].z; acc[4 * q + 3] = bv[q].w;
-        }
-#pragma unroll
-        for (int t = 0; t < 9; ++t) {
-          float xf[VEC], wf[VEC];
-          unpack<BF16>(xv[j][t], xf);
-          unpack<BF16>(wv[t], wf);
-          const bool v = (vmask[j] >> t) & 1u;
-#pragma unroll
-          for (int i = 0; i < VEC; ++i) acc[i] = v ? fmaf(xf[i], wf[i], acc[i]) : acc[i];
-        }
-#pragma unroll
-        for (int i = 0; i < VEC; ++i) acc[i] = apply_act(acc[i], dwf.act);
-        return pack<BF16>(acc);
-      };
-      auto chunk_dw = [&](int cs) {
-#pragma unroll
-        for (int j = 0; j < 2; ++j) st[(16 * j + prow) * 5 + piece] = dw_value(j);
-        dw_issue();  // the next chunk's operands travel while this one goes through the matrix pipe
-        exchange_and_mma(cs);
-      };
-      dw_issue();
-      load_w_all();
-      int c = 0;
-      for (; c + CS <= nchunks; c += CS) {
-        chunk_dw(0);
-        if constexpr (CS == 2) chunk_dw(1);
-      }
-      if (CS == 2 && c < nchunks) chunk_dw(0);
-    } else {
-      int siy0[2], six0[2];
-      bool sok[2];
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const int mj = m0 + 16 * j + prow;
-        sok[j] = mj < p.M;
-        const int y = fast_div(mj, p.mg_wo), x = mj - y * p.Wo;
-        siy0[j] = y * p.stride - p.pad;
-        six0[j] = x * p.stride - p.pad;
-      }
-      const unsigned char* gp[2];
-      bool gv[2];
-      auto enter_rows = [&]() {  // (ky, kx, ci) are wave-uniform
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-          const int iy = siy0[j] + ky, ix = six0[j] + kx;
-          gv[j] = sok[j] && ky < p.kh && (unsigned)iy < (unsigned)p.H && (unsigned)ix < (unsigned)p.W;
-          gp[j] = xb + ((size_t)(gv[j] ? iy * p.W + ix : 0) * p.Cin + ci) * ES + piece * 16;  // always a valid address
-        }
-      };
-      enter_rows();
-      uint4 gr[CS][2];
-      bool gok[CS][2];
-      auto load_rows = [&](int slot) {  // the chunk at (tap, ci) into register slot `slot`, then on to the next chunk
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-          gr[slot][j] = *(const uint4*)gp[j];
-          gok[slot][j] = gv[j];
-        }
-        ci += 2 * KS;
-        if (ci >= p.Cin) {  // wave-uniform
-          ci -= p.Cin;
-          if (++kx == p.kw) { kx = 0; ++ky; }
-          enter_rows();
-        } else {
-#pragma unroll
-          for (int j = 0; j < 2; ++j) gp[j] += 64;
-        }
-      };
-      // one chunk: rows of register slot `slot` -> LDS -> MFMA order; weights of pipeline slots d0, d0 + 1
-      auto chunk = [&](int slot) {
-#pragma unroll
-        for (int j = 0; j < 2; ++j) st[(16 * j + prow) * 5 + piece] = keep_if(gok[slot][j], gr[slot][j]);
-        load_rows(slot);  // CS chunks ahead (past the end of the slice: valid memory, never used)
-        exchange_and_mma(slot);
-      };
-#pragma unroll
-      for (int s = 0; s < CS; ++s) load_rows(s);
-      load_w_all();
-      int c = 0;
-      for (; c + CS <= nchunks; c += CS) {
-        chunk(0);
-        if constexpr (CS == 2) chunk(1);
-      }
-      if (CS == 2 && c < nchunks) chunk(0);
     }
+    int cch = sbeg * KS;  // first channel of the wave's next chunk (wave-uniform)
+    uint4 xv[2][9], wv[9];
+    float4 bv[VEC / 4];
+    auto dw_issue = [&]() {  // loads of the chunk at cch; past the end of the slice the last chunk of the tensor is read again (never used)
+      const int c = min(cch, p.Cin - 2 * KS) + piece * VEC;
+#pragma unroll
+      for (int t = 0; t < 9; ++t) wv[t] = *(const uint4*)(dww + ((size_t)t * p.Cin + c) * ES);
+#pragma unroll
+      for (int q = 0; q < VEC / 4; ++q) bv[q] = *(const float4*)(dwf.bias + c + 4 * q);
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int t = 0; t < 9; ++t) xv[j][t] = *(const uint4*)(xb + ((size_t)poff[j][t] + c) * ES);
+      cch += 2 * KS;
+    };
+    auto dw_value = [&](int j) -> uint4 {
+      float acc[VEC];
+#pragma unroll
+      for (int q = 0; q < VEC / 4; ++q) {
+        acc[4 * q] = bv[q].x; acc[4 * q + 1] = bv[q].y; acc[4 * q + 2] = bv[q].z; acc[4 * q + 3] = bv[q].w;
+      }
+#pragma unroll
+      for (int t = 0; t < 9; ++t) {
+        float xf[VEC], wf[VEC];
+        unpack<BF16>(xv[j][t], xf);
+        unpack<BF16>(wv[t], wf);
+        const bool v = (vmask[j] >> t) & 1u;
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) acc[i] = v ? fmaf(xf[i], wf[i], acc[i]) : acc[i];
+      }
+#pragma unroll
+      for (int i = 0; i < VEC; ++i) acc[i] = apply_act(acc[i], dwf.act);
+      return pack<BF16>(acc);
+    };
+    auto chunk_dw = [&](int cs) {
+#pragma unroll
+      for (int j = 0; j < 2; ++j) st[(16 * j + prow) * 5 + piece] = dw_value(j);
+      dw_issue();  // the next chunk's operands travel while this one goes through the matrix pipe
+      exchange_and_mma(cs);
+    };
+    dw_issue();
+    load_w_all();
+    int c = 0;
+    for (; c + CS <= nchunks; c += CS) {
+      chunk_dw(0);
+      if constexpr (CS == 2) chunk_dw(1);
+    }
+    if (CS == 2 && c < nchunks) chunk_dw(0);
     __syncthreads();  // the partial tiles below reuse the LDS of every wave's staging buffer
   }
 
-  // --- sum the NW partial tiles in wave order; tile element e = (j*16 + v)*64 + lane --------------------------------
-  auto park = [&]() {
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) red[wave * TILE + (j * 16 + v) * 64 + lane] = acc[j][v];
-  };
-  // --- epilogue per channel quad: pixel m0 + 8*(v/4) + 4*(lane/32) + v%4, channels 32*(nb0+j) + lane%32 .. +3 ---------
-  float4 sums[RQ];
-  auto add_up = [&]() {
-#pragma unroll
-    for (int r = 0; r < RQ; ++r) {
-      const int e = 4 * (tid + r * NT);
-      if (QUADS % NT != 0 && wave >= QUADS / 64) {  // (the waves past the tile: 32-channel tiles of 8 waves)
-        sums[r] = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (!BF16) sums[r].x = red[lane % NW * TILE + lane];  // ... look whether one of the partial tiles is spoiled
-        continue;
-      }
-      sums[r] = *(const float4*)&red[e];
-#pragma unroll
-      for (int w = 1; w < NW; ++w) {
-        const float4 t = *(const float4*)&red[w * TILE + e];
-        sums[r].x += t.x; sums[r].y += t.y; sums[r].z += t.z; sums[r].w += t.w;
-      }
-    }
-  };
-  park();
-  if constexpr (!BF16) spoil_unless_in_range(acc, red + wave * TILE, 16 * TN);
-  __syncthreads();
-  add_up();
-  if constexpr (!BF16) {
-    if (__builtin_expect(spoiled(sums[0].x), 0)) {  // every thread of the workgroup or none (out of the way: a launch fetches its code anew, and a longer path costs 0.2 us)
-      __syncthreads();
-      plain_products<MODE, 32, 1, TN>(p, dwf, m0, nb0, sbeg, nsteps, acc);
-      park();
-      __syncthreads();
-      add_up();
-    }
-  }
-#pragma unroll
-  for (int r = 0; r < RQ; ++r) {
-    const int q = tid + r * NT;
-    if (QUADS % NT != 0 && q >= QUADS) break;
-    const int e = 4 * q;
-    const float4 sum = sums[r];
-    const int j = e >> 10, v = (e >> 6) & 15, l = e & 63;
-    const int mm = m0 + (v >> 2) * 8 + (l >> 5) * 4 + (v & 3);
-    const int n = (nb0 + j) * 32 + (l & 31);
-    if (mm < p.M && n < p.Cout) {
-      const size_t o = (size_t)mm * p.Cout + n;
-      if (!own_epilogue) {  // partial sums of this K slice; splitk_reduce_kernel finishes the layer
-        put(p.ws + (size_t)zi * p.M * p.Cout + o, sum);
-      } else {
-        float4 b = bias_j[0];  // component-wise select: indexing the array with a run-time j would move it out of registers
-        if (TN == 2) {
-          const bool hi = j != 0;
-          b.x = hi ? bias_j[TN - 1].x : b.x; b.y = hi ? bias_j[TN - 1].y : b.y;
-          b.z = hi ? bias_j[TN - 1].z : b.z; b.w = hi ? bias_j[TN - 1].w : b.w;
-        }
-        float val[4] = {sum.x + b.x, sum.y + b.y, sum.z + b.z, sum.w + b.w};
-        if (use_res) {
-          const ResVec rv = res_pre[r];
-          if constexpr (BF16) {
-            val[0] += __uint_as_float(rv.x << 16); val[1] += __uint_as_float(rv.x & 0xffff0000u);
-            val[2] += __uint_as_float(rv.y << 16); val[3] += __uint_as_float(rv.y & 0xffff0000u);
-          } else {
-            val[0] += __uint_as_float(rv.x); val[1] += __uint_as_float(rv.y);
-            val[2] += __uint_as_float(rv.z); val[3] += __uint_as_float(rv.w);
-          }
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) val[i] = apply_act(val[i], p.act);
-        if (BF16) {
-          uint2 out;
-          out.x = pack_bf16_rne(val[0], val[1]);
-          out.y = pack_bf16_rne(val[2], val[3]);
-          put((uint16_t*)p.y + o, out);
-        } else {
-          put((float*)p.y + o, make_float4(val[0], val[1], val[2], val[3]));
-        }
-      }
-    }
-  }
+  fin.template finish<MODE>(p, dwf, acc, red, m0, nb0, zi, sbeg, nsteps);
 }
 
-// ---- 16-row wave tiles for deep, skinny layers -----------------------------------------------------------------------
+// ---- wave tiles whose pixels are whole 64-byte rows (gather mode 3) ---------------------------------------------------------
 //
-// A layer with few output pixels and many channels (the 14x14 and 7x7 stages of a ResNet) has too few 32 x 32 tiles to
-// fill a partition; the kernel above then splits K across workgroups and a second launch sums the partial tiles.  Here a
-// wave owns 16 pixels x (16 * TB) channels (v_mfma_f32_16x16x32_bf16): at the same matrix rate there are
-// two to four times as many tiles, so the partition fills with K split only among the NW waves of a workgroup, the sum
-// goes through LDS as before, and the reduction launch disappears.  One K step is 64 bytes of a pixel: lane (i, q) =
-// (pixel row i = lane % 16, quarter q = lane / 16) loads the 16 bytes at k = step * KS + q * VEC, and the weights were
-// packed at registration as [channel block of 16][step][lane (j, q)][16 B] with the same k order.  Cin is a multiple of
-// KS, so a step never straddles a filter tap and the K walk is wave-uniform.  fp32 takes two steps (32 k) at a time, in
-// three bf16 parts per operand (split8): lane (i, q) holds k = 8 q .. 8 q + 7 of the pair, the weights are
-// [channel block of 16][pair][part][lane][16 B], and the plan cuts K in whole pairs.
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-
-template <bool BF16, int TB, int NW>
-constexpr int conv_wave16_lds() {  // floats of LDS
-  return NW * (BF16 ? 1 : 2) * 16 * 5 * 4 > NW * TB * 256 ? NW * (BF16 ? 1 : 2) * 16 * 5 * 4 : NW * TB * 256;
+// R = 32: 32 pixels x (32 * TN) channels per wave on v_mfma_f32_32x32x16_bf16.  R = 16: 16 pixels x (16 * TN) channels on
+// v_mfma_f32_16x16x32_bf16, for layers with few output pixels and many channels (the 14x14 and 7x7 stages of a ResNet): these
+// have too few 32 x 32 tiles to fill a partition, and would have to split K across workgroups and sum the partial tiles in
+// a second launch; at the same matrix rate there are two to four times as many 16 x 16 tiles, K is split only among the
+// NW waves of a workgroup, and the reduction launch disappears.
+//
+// A load instruction is served 64 bytes per cycle only when four neighbouring lanes read one 64-byte segment; with every lane in
+// a different pixel (a different cache line) the pixel operand costs four times the cycles of the same bytes of weights.  So a
+// wave fetches whole rows of 64 bytes (lane = (pixel, 16-byte piece)), parks them in its own corner of LDS, and reads them back
+// in MFMA order.  No workgroup barrier is involved: the buffer is private to the wave.  A chunk, what goes through together, is
+// two K steps: one row of each of 32 pixels, or two consecutive ones of each of 16.
+// R = 32: lane (i, h) of a fragment holds pixel i and k = 8 h .. 8 h + 7 of a step (bf16) or of the chunk (fp32).
+// R = 16: lane (i, q) holds pixel i and k = 8 q .. 8 q + 7 of a step (bf16) or of the chunk (fp32).
+// Weights come in the same order: [channel block of R][step][lane][16 B] in bf16, [channel block of R][chunk][part][lane][16 B] in
+// fp32, whose plan cuts K in whole chunks.
+//
+// A wave has one or two others on its SIMD and one to twenty chunks to walk, and what bounds the walk is the vector memory unit, which
+// takes about twenty cycles for every load instruction of the CU, whether its data are used or not.  So nothing is loaded that is not
+// used: DC chunks of rows and weights are in flight, and refills stop with the last chunk of the slice.  Which slot is refilled and
+// which is the last one is known at compile time on every path (rows_pipeline), so that the compiler waits for one chunk and not for
+// those behind it.  Rows outside the image are offsets past the end of a buffer descriptor, which returns 0 (an instruction whose
+// lanes are all outside takes its twenty cycles too, so refills past the end cannot be left to it).  Against unconditional
+// refills, on 128 CUs: fp32 3136 x 64 x 576 7.0 -> 5.8 us, 784 x 128 x 1152 6.8 -> 5.7, 49 x 512 x 4608 8.8 -> 8.0; bf16 784 x 512 x
+// 128 4.1 -> 2.9, 3136 x 256 x 64 3.8 -> 3.0, 196 x 256 x 1024 3.6 -> 2.8 (with WaveEpilogue's order of loads and stores).
+template <int I, int N, typename F>
+__device__ __forceinline__ void static_for(F&& f) {  // f(I), ..., f(N - 1), as compile-time constants
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>());
+    static_for<I + 1, N>(f);
+  }
 }
-template <bool BF16, int TB, int NW>
-__device__ __forceinline__ void conv_wave16_body(const ConvArgs& p, const int mt, const int g, float* const red) {
+// n chunks through DC slots: load(slot) requests the next chunk into a slot, begun() is called once when the first are on their
+// way, step(slot, refill) computes the next chunk and, if refill, requests the one DC chunks further on into the same slot.
+template <int DC, typename Load, typename Begun, typename Step>
+__device__ __forceinline__ void rows_pipeline(const int n, Load&& load, Begun&& begun, Step&& step) {
+  if (n >= DC) {
+    static_for<0, DC>(load);
+    begun();
+    int left = n - DC;  // chunks still to be requested
+    for (; left >= DC; left -= DC) static_for<0, DC>([&](auto s) { step(s, std::true_type()); });
+    static_for<0, DC>([&](auto r) {
+      if (left == r) {
+        static_for<0, r>([&](auto s) { step(s, std::true_type()); });
+        static_for<0, DC>([&](auto s) { step(std::integral_constant<int, (r + s) % DC>(), std::false_type()); });
+      }
+    });
+  } else {
+    static_for<0, DC>([&](auto k) {
+      if (n == k) {
+        static_for<0, k>(load);
+        begun();
+        static_for<0, k>([&](auto s) { step(s, std::false_type()); });
+      }
+    });
+  }
+}
+template <bool BF16, int R, int TN, int NW>
+__device__ __forceinline__ void conv_rows_body(const ConvArgs& p, const int mt, const int g, float* const red) {
   constexpr int ES = BF16 ? 2 : 4;
-  constexpr int VEC = 16 / ES;
-  constexpr int KS = 4 * VEC;  // k per step: 16 (fp32) / 32 (bf16)
-  constexpr int TILE = TB * 256;
-  constexpr int D = 4;                        // bf16: steps in flight
-  constexpr int DP = 2;                       // fp32: pairs of steps in flight (3: 9.4 us instead of 8.8 for 49 x 512 x 4608)
-  constexpr int SR = 16 * 5;                  // 16-byte vectors of one step's rows: 16 pixels x (4 pieces + 1 pad)
-  constexpr int STAGE_V = BF16 ? SR : 2 * SR; // 16-byte vectors of one wave's staging buffer
-  static_assert(TB == 1 || TB == 2, "the epilogue selects between at most two channel blocks");
+  constexpr int RK = 64 / ES;                     // k of a row
+  constexpr int KS = R == 32 ? RK / 2 : RK;       // k of a step
+  constexpr int NP = BF16 ? 2 : 3;                // 16-byte pieces of a chunk's weights per lane and channel block: steps, or parts
+  // chunks of rows and of weights in flight (bf16 tiles of 32 x 64, 784 x 512 x 128: three 2.9 us, two 3.1; 49 x 512 x 4608 in fp32:
+  // 8.3, 8.0; four, in bf16, take so many registers that 3136 x 256 x 64 goes from 3.0 to 4.2)
+  constexpr int DC = BF16 && R == 32 && TN == 2 ? 3 : 2;
+  constexpr int kOutside = (int)0x80000000;       // an offset past the end of any tensor
 
   if (p.wave_prio) __builtin_amdgcn_s_setprio(3);
   const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int li = lane & 15, lq = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform: keeps the K loop's control flow scalar
   const int zi = p.splitk == 1 ? 0 : g / p.NTn;
-  const int m0 = mt * 16, nb0 = (g - zi * p.NTn) * TB;
+  const int m0 = mt * R, nb0 = (g - zi * p.NTn) * TN;
   const int s_wg0 = zi * p.sz;
   const int s_wg1 = min(s_wg0 + p.sz, p.S);
   const int sbeg = min(s_wg0 + wave * p.sw, s_wg1);
-  const int nsteps = min(sbeg + p.sw, s_wg1) - sbeg;
+  const int nsteps = min(sbeg + p.sw, s_wg1) - sbeg, nchunks = (nsteps + 1) >> 1;
 
-  // The pixel operand is fetched as whole 64-byte rows (lane = (pixel lane / 4, 16-byte piece lane % 4): four
-  // neighbouring lanes read one contiguous row, the access shape the load unit serves at full rate) and turned into MFMA
-  // order (lane = (pixel row, quarter)) through the wave's own corner of LDS, as in the staged mode of the 32-row kernel.
-  const unsigned char* xb = (const unsigned char*)p.x;
-  const int prow = lane >> 2, piece = lane & 3;
-  const int m = m0 + prow;
-  const bool a_ok = m < p.M;
-  const int oy = fast_div(m, p.mg_wo), ox = m - oy * p.Wo;
-  const int iy0 = oy * p.stride - p.pad, ix0 = ox * p.stride - p.pad;
-  const int kcur = sbeg * KS;
-  const int tap = fast_div(kcur, p.mg_cin);
-  int ci = kcur - tap * p.Cin;
+  // Walk over k = (tap, ci): a row never straddles a tap, so the walk is wave-uniform and lives in scalars.  A lane's row offsets
+  // change only from tap to tap; inside one, a scalar offset advances.
+  constexpr int NX = R / 16;  // pixels of a lane
+  const int kbeg = sbeg * KS;
+  const int tap = fast_div(kbeg, p.mg_cin);
+  int ci = kbeg - tap * p.Cin;
   int ky = fast_div(tap, p.mg_kw), kx = tap - ky * p.kw;
-  bool a_valid;
-  const unsigned char* ap;
-  auto enter_tap = [&]() {
-    const int iy = iy0 + ky, ix = ix0 + kx;
-    a_valid = a_ok && ky < p.kh && (unsigned)iy < (unsigned)p.H && (unsigned)ix < (unsigned)p.W;
-    ap = xb + ((size_t)(a_valid ? iy * p.W + ix : 0) * p.Cin + ci) * ES + piece * 16;  // always a valid address
-  };
-  uint4* const st = reinterpret_cast<uint4*>(red) + wave * STAGE_V;
-  enter_tap();
-  const unsigned char* wptr[TB];
+  const int piece = lane & 3, prow = lane >> 2;
+  int iy0[NX], ix0[NX], rbase[NX], vo[NX];
 #pragma unroll
-  for (int j = 0; j < TB; ++j)
-    wptr[j] = BF16 ? (const unsigned char*)p.w + (((size_t)(nb0 + j) * p.S + sbeg) * 64 + lane) * 16
-                   : (const unsigned char*)p.w + ((((size_t)(nb0 + j) * p.S + sbeg) >> 1) * 192 + lane) * 16;
-
-  uint4 ar[D], br[D][TB];
-  bool av[D];
-  uint4 ar2[DP][2], bw[DP][TB][3];
-  bool av2[DP][2];
+  for (int j = 0; j < NX; ++j) {
+    const int m = m0 + 16 * j + prow;
+    const int y = fast_div(m, p.mg_wo), x = m - y * p.Wo;
+    iy0[j] = m < p.M ? y * p.stride - p.pad : kOutside / 2;  // (a pixel past the last one is outside for every tap)
+    ix0[j] = x * p.stride - p.pad;
+    rbase[j] = (int)(((uint32_t)(y * p.stride - p.pad) * (uint32_t)p.W + (uint32_t)ix0[j]) * (uint32_t)(p.Cin * ES)) + piece * 16;
+  }
+  const auto xrsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p.x), 0, (int)((uint32_t)(p.H * p.W) * (uint32_t)p.Cin * ES), 0x00027000);
+  int soff = ci * ES, rest = R == 32 ? nchunks : nsteps, left;  // rows of the slice behind this tap's, rows of this tap to go
+  auto enter_tap = [&]() {  // at (ky, kx, ci)
+    left = min((p.Cin - ci) / RK, rest);
+    rest -= left;
+    const int off = (ky * p.W + kx) * p.Cin * ES;
+#pragma unroll
+    for (int j = 0; j < NX; ++j) {
+      const bool in = left > 0 && (unsigned)(iy0[j] + ky) < (unsigned)p.H && (unsigned)(ix0[j] + kx) < (unsigned)p.W;
+      vo[j] = in ? rbase[j] + off : kOutside;
+    }
+  };
   auto next_row = [&]() {
-    ci += KS;
-    if (ci >= p.Cin) {  // wave-uniform
-      ci -= p.Cin;
+    soff += 64;
+    if (--left == 0) {  // wave-uniform; past the slice left is 0 and falls from there, and every row is outside
+      ci = soff = 0;
       if (++kx == p.kw) { kx = 0; ++ky; }
       enter_tap();
-    } else {
-      ap += KS * ES;
     }
   };
-  auto load_a = [&](int d) {
-    ar[d] = *(const uint4*)ap;
-    av[d] = a_valid;
-    next_row();
-  };
-  auto load_b = [&](int d) {
+  enter_tap();
+  uint4 rows[DC][2];
+  auto load_rows = [&](int s) {
 #pragma unroll
-    for (int j = 0; j < TB; ++j) {
-      br[d][j] = *(const uint4*)wptr[j];
-      wptr[j] += 1024;
+    for (int j = 0; j < 2; ++j) {
+      rows[s][j] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(xrsrc, vo[j % NX], soff, 0));
+      if (R == 16 || j == 1) next_row();
     }
   };
-  auto load_a_pair = [&](int d) {
+  const int wbytes = BF16 ? nsteps * 1024 : nchunks * NP * 1024;
+  const unsigned char* const wbase = (const unsigned char*)p.w + ((size_t)nb0 * p.S + sbeg) * (NP * 512);
+  __amdgpu_buffer_rsrc_t wrsrc[TN];
 #pragma unroll
-    for (int e = 0; e < 2; ++e) {
-      ar2[d][e] = *(const uint4*)ap;
-      av2[d][e] = a_valid;
-      next_row();
-    }
+  for (int j = 0; j < TN; ++j) wrsrc[j] = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(wbase) + (size_t)j * p.S * (NP * 512), 0, wbytes, 0x00027000);
+  int woff = 0;
+  uint4 bw[DC][TN][NP];
+  auto load_w = [&](int s) {
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int q = 0; q < NP; ++q) bw[s][j][q] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(wrsrc[j], lane * 16 + q * 1024, woff, 0));
+    woff += NP * 1024;
   };
-  auto load_b_pair = [&](int d) {
+  WaveEpilogue<BF16, R, TN, NW, true> fin;
+  WaveAcc<R> acc[TN];
 #pragma unroll
-    for (int j = 0; j < TB; ++j) {
-#pragma unroll
-      for (int q = 0; q < 3; ++q) bw[d][j][q] = *(const uint4*)(wptr[j] + q * 1024);
-      wptr[j] += 3072;
-    }
-  };
+  for (int j = 0; j < TN; ++j) acc[j] = WaveAcc<R>(0.f);
 
-  // epilogue operands fetched ahead of the K loop: this thread's quad of consecutive channels (see below)
-  constexpr int QUADS = TILE / 4;
-  const bool has_quad = tid < QUADS;
-  const int qe = 4 * tid;                                     // first tile element of the quad: (b * 4 + v) * 64 + lane
-  const int qb = qe >> 8, qv = (qe >> 6) & 3, ql = qe & 63;
-  const int qm = m0 + 4 * (ql >> 4) + qv;                      // pixel
-  const int qn = (nb0 + qb) * 16 + (ql & 15);                  // first channel
-  const bool q_ok = has_quad && qm < p.M && qn < p.Cout;
-  const bool own_epilogue = p.splitk == 1;
-  float4 bias = make_float4(0.f, 0.f, 0.f, 0.f);
-  if (q_ok) bias = *(const float4*)(p.bias + qn);
-  using ResVec = typename std::conditional<BF16, uint2, uint4>::type;
-  ResVec res_pre = ResVec();
-  const bool use_res = own_epilogue && p.res != nullptr;
-  if (use_res && q_ok) res_pre = *(const ResVec*)((const unsigned char*)p.res + ((size_t)qm * p.Cout + qn) * ES);
-
-  f32x4 acc[TB];
-#pragma unroll
-  for (int j = 0; j < TB; ++j)
-#pragma unroll
-    for (int v = 0; v < 4; ++v) acc[j][v] = 0.f;
-
-  auto compute = [&](int d) {
-    st[prow * 5 + piece] = keep_if(av[d], ar[d]);
-    // lanes exchange data through the wave's buffer: order the accesses of the whole wave, not only of each lane
+  uint4* const st = reinterpret_cast<uint4*>(red) + wave * 128;  // 32 rows of 4 pieces
+  const int li = lane % R, lh = lane / R;
+  // lanes exchange data through the wave's buffer: order the accesses of the whole wave, not only of each lane
+  auto wave_order = [&]() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    const uint4 a4 = st[li * 5 + lq];
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-#pragma unroll
-    for (int j = 0; j < TB; ++j)
-      acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a4), __builtin_bit_cast(bf16x8, br[d][j]), acc[j], 0, 0, 0);
   };
-  auto compute_pair = [&](int d) {
+  rows_pipeline<DC>(
+      nchunks,
+      [&](auto s) {
+        load_rows(s);
+        load_w(s);
+      },
+      [&]() { fin.fetch(p, m0, nb0, tid); },
+      [&](auto s, auto refill) {
+        wave_order();
 #pragma unroll
-    for (int e = 0; e < 2; ++e) st[e * SR + prow * 5 + piece] = keep_if(av2[d][e], ar2[d][e]);
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    const int at = (lq >> 1) * SR + li * 5 + 2 * (lq & 1);
-    const uint4 lo = st[at], hi = st[at + 1];
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    const Split8 a = split8(lo, hi);
-    constexpr int PA[6] = {2, 1, 0, 1, 0, 0}, PB[6] = {0, 1, 2, 0, 1, 0};  // from the smallest terms to the largest
+        for (int j = 0; j < 2; ++j) st[(16 * j + prow) * 4 + (piece ^ ((prow >> 1) & 3))] = rows[s][j];  // spread over the banks
+        if constexpr (refill) load_rows(s);
+        wave_order();
+        uint4 a[2];
 #pragma unroll
-    for (int t = 0; t < 6; ++t)
+        for (int h = 0; h < 2; ++h) {
+          // pieces of the lane's pixel from the chunk's first k on: bf16 R = 32: 2 h + lh, R = 16: 4 h + lh; fp32: 2 lh + h
+          const int at = BF16 ? (R == 32 ? 2 : 4) * h + lh : 2 * lh + h;
+          a[h] = st[(R == 32 ? li : 16 * (at >> 2) + li) * 4 + ((at & 3) ^ ((li >> 1) & 3))];
+        }
+        Split8 parts;
+        if constexpr (BF16) {
+          parts.p[0] = a[0];
+          parts.p[1] = a[1];
+        } else {
+          parts = split8(a[0], a[1]);
+        }
+        constexpr int PA[6] = {BF16 ? 0 : 2, 1, 0, 1, 0, 0}, PB[6] = {0, 1, 2, 0, 1, 0};  // fp32: from the smallest terms to the largest
 #pragma unroll
-      for (int j = 0; j < TB; ++j)
-        acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a.p[PA[t]]), __builtin_bit_cast(bf16x8, bw[d][j][PB[t]]), acc[j], 0, 0, 0);
-  };
-
-  // the same D-deep software pipeline as the 32-row kernel: unconditional loads, conditional computes only in the tail
-  int done = 0;
-  if constexpr (BF16) {
+        for (int t = 0; t < (BF16 ? 2 : 6); ++t)
 #pragma unroll
-    for (int d = 0; d < D; ++d) {
-      load_a(d);
-      load_b(d);
-    }
-    for (; done + D <= nsteps; done += D) {
-#pragma unroll
-      for (int d = 0; d < D; ++d) {
-        compute(d);
-        load_a(d);
-        load_b(d);
-      }
-    }
-#pragma unroll
-    for (int d = 0; d < D; ++d)
-      if (done + d < nsteps) compute(d);
-  } else {
-    const int np = nsteps >> 1;
-#pragma unroll
-    for (int d = 0; d < DP; ++d) {
-      load_a_pair(d);
-      load_b_pair(d);
-    }
-    for (; done + DP <= np; done += DP) {
-#pragma unroll
-      for (int d = 0; d < DP; ++d) {
-        compute_pair(d);
-        load_a_pair(d);
-        load_b_pair(d);
-      }
-    }
-#pragma unroll
-    for (int d = 0; d < DP - 1; ++d)
-      if (done + d < np) compute_pair(d);
-  }
-
-  // partial tiles of the NW waves summed in wave order; accumulator v of lane l is pixel 4 * (l / 16) + v, channel l % 16
-  auto park = [&]() {
-#pragma unroll
-    for (int j = 0; j < TB; ++j)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) red[wave * TILE + (j * 4 + v) * 64 + lane] = acc[j][v];
-  };
-  float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
-  auto add_up = [&]() {
-    if (wave >= QUADS / 64) {
-      if (!BF16) sum.x = red[lane % NW * TILE + lane];  // no part in the epilogue, but in the second walk where a tile is spoiled
-      return;
-    }
-    sum = *(const float4*)&red[qe];
-#pragma unroll
-    for (int w = 1; w < NW; ++w) {
-      const float4 t = *(const float4*)&red[w * TILE + qe];
-      sum.x += t.x; sum.y += t.y; sum.z += t.z; sum.w += t.w;
-    }
-  };
+          for (int j = 0; j < TN; ++j) {
+            if constexpr (R == 32) acc[j] = mfma_bf16(parts.p[PA[t]], bw[s][j][PB[t]], acc[j]);
+            else acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, parts.p[PA[t]]), __builtin_bit_cast(bf16x8, bw[s][j][PB[t]]), acc[j], 0, 0, 0);
+          }
+        __builtin_amdgcn_sched_barrier(0);  // the refill takes over the registers of the slot just used
+        if constexpr (refill) load_w(s);
+      });
   __syncthreads();  // the partial tiles reuse the LDS of every wave's staging buffer
-  park();
-  if constexpr (!BF16) spoil_unless_in_range(acc, red + wave * TILE, 4 * TB);
-  __syncthreads();
-  add_up();
-  if constexpr (!BF16) {
-    if (__builtin_expect(spoiled(sum.x), 0)) {
-      __syncthreads();
-      plain_products<3, 16, 1, TB>(p, DwFusedArgs(), m0, nb0, sbeg, nsteps, acc);
-      park();
-      __syncthreads();
-      add_up();
-    }
-  }
-  if (!q_ok) return;
-  const size_t o = (size_t)qm * p.Cout + qn;
-  if (!own_epilogue) {
-    put(p.ws + (size_t)zi * p.M * p.Cout + o, sum);
-    return;
-  }
-  float val[4] = {sum.x + bias.x, sum.y + bias.y, sum.z + bias.z, sum.w + bias.w};
-  if (use_res) {
-    if constexpr (BF16) {
-      val[0] += __uint_as_float(res_pre.x << 16); val[1] += __uint_as_float(res_pre.x & 0xffff0000u);
-      val[2] += __uint_as_float(res_pre.y << 16); val[3] += __uint_as_float(res_pre.y & 0xffff0000u);
-    } else {
-      val[0] += __uint_as_float(res_pre.x); val[1] += __uint_as_float(res_pre.y);
-      val[2] += __uint_as_float(res_pre.z); val[3] += __uint_as_float(res_pre.w);
-    }
-  }
-#pragma unroll
-  for (int i = 0; i < 4; ++i) val[i] = apply_act(val[i], p.act);
-  if (BF16) {
-    uint2 out;
-    out.x = pack_bf16_rne(val[0], val[1]);
-    out.y = pack_bf16_rne(val[2], val[3]);
-    put((uint16_t*)p.y + o, out);
-  } else {
-    put((float*)p.y + o, make_float4(val[0], val[1], val[2], val[3]));
-  }
+  fin.template finish<3>(p, DwFusedArgs(), acc, red, m0, nb0, zi, sbeg, nsteps);
+}
+template <int R, int TN, int NW>
+constexpr int conv_rows_lds() {  // floats of LDS
+  return NW * 512 > NW * TN * R * R ? NW * 512 : NW * TN * R * R;
 }
 
 // ---- pointwise layers: one thread per (output pixel, 16-byte channel vector) ----------------------------------------------

@@ -50,6 +50,11 @@ std::string build_plan(const daris_dnn& dnn, bool keep_activations, bool pair_la
   net.ingest.bytes = (size_t)net.ingest.H * net.ingest.W * net.ingest.Cs * es;
   const int n = dnn.n_layers;
   net.layers.resize(n);
+  // the channel stride that lets plan_conv choose 16-pixel tiles, which only whole 64-byte rows feed; 0: it may not
+  auto small_tile_stride = [&](const LayerPlan& L) {
+    const TensorInfo &in = net.tensor(L.in_t), &o = L.out;
+    return small_tiles && conv_rows_take(in.H, in.W, in.Cs, (uint64_t)o.H * (uint64_t)o.W, o.Cs, L.Kpad, net.bf16) ? in.Cs : 0;
+  };
 
   for (int l = 0; l < n; ++l) {
     LayerPlan& L = net.layers[l];
@@ -82,7 +87,7 @@ std::string build_plan(const daris_dnn& dnn, bool keep_activations, bool pair_la
           // the kernels divide pixel and k indices by Wo, Cin and kw with 32-bit multipliers: operands must stay small
           if ((uint64_t)(o.H * (uint64_t)o.W + 64) * (uint64_t)o.W >= (1ull << 32) || (uint64_t)(L.Kpad + 64) * (uint64_t)in.Cs >= (1ull << 32))
             return "layer " + std::to_string(l) + ": tensor too large for the kernels' index arithmetic";
-          L.cp = plan_conv(o.H * o.W, o.Cs, L.Kpad, net.bf16, staged_rows && conv_rows_staged(in.Cs, net.bf16) ? 2 : 1, small_tiles ? in.Cs : 0, plan_cus,
+          L.cp = plan_conv(o.H * o.W, o.Cs, L.Kpad, net.bf16, staged_rows && conv_rows_staged(in.Cs, net.bf16) ? 2 : 1, small_tile_stride(L), plan_cus,
                            conv_block_takes(in.H, in.W, in.Cs, d.k, d.pad, L.Kpad));
           L.kernel_id = L.cp.kernel;
           net.ws_bytes = std::max(net.ws_bytes, L.cp.ws_bytes);
@@ -144,10 +149,10 @@ std::string build_plan(const daris_dnn& dnn, bool keep_activations, bool pair_la
     const ConvPlan own = heavy.cp;
     const int sa = staged_rows && conv_rows_staged(net.tensor(heavy.in_t).Cs, net.bf16) ? 2 : 1;
     if (heavy.cp.rows == 64)
-      heavy.cp = plan_conv(heavy.out.H * heavy.out.W, heavy.out.Cs, heavy.Kpad, net.bf16, sa, small_tiles ? net.tensor(heavy.in_t).Cs : 0, plan_cus, false);
+      heavy.cp = plan_conv(heavy.out.H * heavy.out.W, heavy.out.Cs, heavy.Kpad, net.bf16, sa, small_tile_stride(heavy), plan_cus, false);
     const ConvPlan like = plan_conv_like(heavy.cp, light.out.H * light.out.W, light.out.Cs, light.Kpad, net.bf16,
                                          staged_rows && conv_rows_staged(net.tensor(light.in_t).Cs, net.bf16) ? 2 : 1, plan_cus);
-    if (like.kernel == K_NONE) {
+    if (like.kernel == K_NONE || (like.rows == 16 && small_tile_stride(light) == 0)) {
       heavy.cp = own;
       continue;
     }
