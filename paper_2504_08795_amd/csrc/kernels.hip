@@ -57,7 +57,7 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restr
 
 // ---- wave-tile implicit GEMM (layer_bodies.h), one tile per workgroup ------------------------------------------------------
 template <bool BF16, int TN, int NW, int MODE>
-__global__ __launch_bounds__(NW * 64, NW == 8 && TN == 1 ? 4 : 1) void conv_wave_kernel(const ConvArgs) {
+__global__ __launch_bounds__(NW * 64) void conv_wave_kernel(const ConvArgs) {
   const ConvArgs p = conv_args_at((ConstPtr)__builtin_amdgcn_kernarg_segment_ptr());
   __shared__ __align__(16) float red[conv_wave_lds<BF16, TN, NW, MODE>()];
   int mt, g;
@@ -82,7 +82,7 @@ __global__ __launch_bounds__(NW * 64) void conv_wave_dw_kernel(const ConvArgs, c
 // the 1x1 convolution of its shortcut read the same tensor): workgroups [0, n0) work on p0, the rest on p1.  n0 is
 // a multiple of 8, so the workgroup -> XCD relation of each problem is the one its plan assumed.
 template <bool BF16, int TN, int NW, int MODE>
-__global__ __launch_bounds__(NW * 64, NW == 8 && TN == 1 ? 4 : 1) void conv_wave_pair_kernel(const ConvArgs, const ConvArgs, const int n0) {
+__global__ __launch_bounds__(NW * 64) void conv_wave_pair_kernel(const ConvArgs, const ConvArgs, const int n0) {
   __shared__ __align__(16) float red[conv_wave_lds<BF16, TN, NW, MODE>()];
   const bool second = (int)blockIdx.x >= n0;
   const ConvArgs p = conv_args_at((ConstPtr)__builtin_amdgcn_kernarg_segment_ptr() + (second ? sizeof(ConvArgs) : 0));
@@ -93,11 +93,8 @@ __global__ __launch_bounds__(NW * 64, NW == 8 && TN == 1 ? 4 : 1) void conv_wave
   puts_done();
 }
 
-// (Eight waves of at most 128 registers leave room for a second workgroup on the CU, which counts where a launch has more
-// workgroups than CUs, as two problems in one launch do, or shares them: 784 x 128 x 576 with x 64 5.8 -> 4.8 us.  The fp32 tiles of two
-// channel blocks do not fit.)
 template <bool BF16, int TB, int NW>
-__global__ __launch_bounds__(NW * 64, NW == 8 && !(!BF16 && TB == 2) ? 4 : 1) void conv_wave16_kernel(const ConvArgs) {
+__global__ __launch_bounds__(NW * 64) void conv_wave16_kernel(const ConvArgs) {
   const ConvArgs p = conv_args_at((ConstPtr)__builtin_amdgcn_kernarg_segment_ptr());
   __shared__ __align__(16) float red[conv_rows_lds<16, TB, NW>()];
   int mt, g;
@@ -108,7 +105,7 @@ __global__ __launch_bounds__(NW * 64, NW == 8 && !(!BF16 && TB == 2) ? 4 : 1) vo
 
 // Two independent convolutions on one tensor in one launch, as conv_wave_pair_kernel: workgroups [0, n0) work on p0.
 template <bool BF16, int TB, int NW>
-__global__ __launch_bounds__(NW * 64, NW == 8 && !(!BF16 && TB == 2) ? 4 : 1) void conv_wave16_pair_kernel(const ConvArgs, const ConvArgs, const int n0) {
+__global__ __launch_bounds__(NW * 64) void conv_wave16_pair_kernel(const ConvArgs, const ConvArgs, const int n0) {
   __shared__ __align__(16) float red[conv_rows_lds<16, TB, NW>()];
   const bool second = (int)blockIdx.x >= n0;
   const ConvArgs p = conv_args_at((ConstPtr)__builtin_amdgcn_kernarg_segment_ptr() + (second ? sizeof(ConvArgs) : 0));
