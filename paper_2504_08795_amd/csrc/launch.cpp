@@ -27,7 +27,7 @@ static inline int cdiv(int a, int b) { return (a + b - 1) / b; }
 // round's worth of work.  1 = perfectly even; 98 workgroups on 96 CUs: 1.96.
 static double round_waste(int groups, int cus) { return (double)cdiv(groups, cus) * cus / groups; }
 
-static ConvPlan plan_conv_wave(int M, int N, int Kpad, int bf16, int step_align, int nominal_cus, bool allow_block, int force_tn = 0, int force_nw = 0) {
+static ConvPlan plan_conv_wave(int M, int N, int Kpad, int bf16, int step_align, int nominal_cus, bool allow_block, bool three_taps, int force_tn = 0, int force_nw = 0) {
   const int kNominalWaveSlots = 4 * nominal_cus;  // SIMDs of the partition size the plan is balanced for
   // What a launch of few tiles pays for is its fixed cost and idle CUs.  Best found on a 128-CU partition (ResNet-18 shapes): 8
   // waves per workgroup splitting K, and enough grid.z slices that tiles * z is about the number of CUs, while a wave keeps
@@ -55,6 +55,7 @@ static ConvPlan plan_conv_wave(int M, int N, int Kpad, int bf16, int step_align,
   // 8.8, 3072 x 64 x 576 on 64 CUs 9.9 against 12.7; but 784 x 512 x 128: 6.0 against 5.4)
   const bool block = allow_block && !bf16 && staged && nb % 2 == 0 && cdiv(M, 64) * (nb / 2) >= nominal_cus * 3 / 4 && S >= 32;
   if (block) tn = 2;
+  if (block && three_taps) step_align = 6;  // three chunks of two steps
   const int tiles = (block ? cdiv(M, 64) : cdiv(M, 32)) * (nb / tn);
   int nw = bf16 ? 4 : 8;  // bf16 steps are short: fewer waves to sum through LDS beat a finer K split (measured 0.4-0.8 us per layer)
   while (nw > 2 && (S / nw < 4 || tiles * nw > 8 * kNominalWaveSlots)) nw /= 2;  // >= 4 steps per wave, <= 8 waves per SIMD
@@ -103,6 +104,7 @@ static ConvPlan plan_conv_wave(int M, int N, int Kpad, int bf16, int step_align,
   pl.sw = cdiv(cdiv(sz, nw), step_align) * step_align;
   pl.step_align = step_align;
   pl.staged = staged;
+  pl.taps = block && three_taps;
   pl.splitk = z;
   pl.tiles = tiles;
   pl.threads = nw * 64;
@@ -191,10 +193,10 @@ static ConvPlan plan_conv_wave16(int M, int N, int Kpad, int bf16, int nominal_c
   return pl;
 }
 
-ConvPlan plan_conv(int M, int N, int Kpad, int bf16, int step_align, int cin_stride, int nominal_cus, bool allow_block) {
+ConvPlan plan_conv(int M, int N, int Kpad, int bf16, int step_align, int cin_stride, int nominal_cus, bool allow_block, bool three_taps) {
   if (nominal_cus < 8) nominal_cus = 8;
   if (nominal_cus > 256) nominal_cus = 256;
-  const ConvPlan pl = plan_conv_wave(M, N, Kpad, bf16, step_align, nominal_cus, allow_block);
+  const ConvPlan pl = plan_conv_wave(M, N, Kpad, bf16, step_align, nominal_cus, allow_block, three_taps);
   if (pl.splitk > 1 && cin_stride > 0 && cin_stride % (bf16 ? 32 : 16) == 0) {
     const ConvPlan p16 = plan_conv_wave16(M, N, Kpad, bf16, nominal_cus);
     if (p16.kernel != K_NONE) return p16;
@@ -208,7 +210,7 @@ ConvPlan plan_conv_like(const ConvPlan& first, int M, int N, int Kpad, int bf16,
   if (nominal_cus > 256) nominal_cus = 256;
   if (first.rows == 16) return plan_conv_wave16(M, N, Kpad, bf16, nominal_cus, first.tn, first.nw);
   if (cdiv(N, 32) % first.tn != 0) return none;
-  return plan_conv_wave(M, N, Kpad, bf16, step_align, nominal_cus, false, first.tn, first.nw);
+  return plan_conv_wave(M, N, Kpad, bf16, step_align, nominal_cus, false, false, first.tn, first.nw);
 }
 
 
@@ -298,7 +300,8 @@ std::string KernelTable::resolve(const AqlRuntime& rt) {
     ingest[b] = get("daris::ingest_kernel<" + B + ">", kIngestBytes);
     egress[b] = get("daris::egress_kernel<" + B + ">", kIngestBytes);
   }
-  for (int v = 0; v < 3; ++v) block[v] = get("daris::conv_block_kernel<" + std::to_string(nw_[v]) + ">", sizeof(ConvArgs));
+  for (int t = 0; t < 2; ++t)
+    for (int v = 0; v < 3; ++v) block[t][v] = get("daris::conv_block_kernel<" + std::to_string(nw_[v]) + (t ? ", true>" : ", false>"), sizeof(ConvArgs));
   cu_probe = get("daris::cu_probe_kernel", kProbeBytes);
   return missing;
 }
@@ -328,7 +331,9 @@ bool encode_conv(const KernelTable& kt, const ConvPlan& pl, const ConvArgs& a, i
     const int v64 = pl.kernel - K_CONV64_F32_T2W2;
     if (v64 < 0 || v64 >= 3 || pl.threads != 64 * pl.nw || bf16 || a.c_real > 0 || !pl.staged || pl.tn != 2 || pl.S % 2 || pl.sz % 2 || pl.sw % 2) return false;
     if (a.kh != a.kw || !conv_block_takes(a.H, a.W, a.Cin, a.kh, a.pad, a.Kpad) || (pl.splitk > 1 && !a.ws)) return false;
-    if (!push(out, kt.block[v64], pl.kernel, pl.grid_x, (uint32_t)pl.threads, &a, sizeof(a))) return false;
+    // ... and with three taps per fetch: its window, an output as large as the input, and K cut in threes of chunks
+    if (pl.taps && (!conv_three_taps(a.kh, a.stride, a.pad) || a.Ho != a.H || a.Wo != a.W || pl.S % 6 || pl.sz % 6 || pl.sw % 6)) return false;
+    if (!push(out, kt.block[pl.taps][v64], pl.kernel, pl.grid_x, (uint32_t)pl.threads, &a, sizeof(a))) return false;
     return push_reduce(kt, pl, a, bf16, out);
   }
   const int variant = pl.kernel - (bf16 ? K_CONVW_BF16_T1W2 : K_CONVW_F32_T1W2);

@@ -147,7 +147,12 @@ __device__ __forceinline__ void plain_products(const ConvArgs& p, const DwFusedA
     for (int i = 0; i < TM; ++i)
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
-        const float4 v = pixel_quad<MODE>(p, dwf, m0 + R * i + lane % R, c * CK + 8 * (lane / R) + 4 * h);
+        int k = c * CK;
+        if constexpr (MODE == 5) {  // chunks in the order (ky, 16 channels, kx) of three taps
+          const int gk = c / 3 * CK, ky = fast_div(gk, p.mg_cin);
+          k = (3 * ky + c % 3) * p.Cin + gk - ky * p.Cin;
+        }
+        const float4 v = pixel_quad<MODE>(p, dwf, m0 + R * i + lane % R, k + 8 * (lane / R) + 4 * h);
         a[i][4 * h] = v.x; a[i][4 * h + 1] = v.y; a[i][4 * h + 2] = v.z; a[i][4 * h + 3] = v.w;
       }
 #pragma unroll

@@ -75,6 +75,28 @@ def test_block_tiles(case):
     assert err <= 5e-7, err
 
 
+# (cin, h, w, cout): 3x3 windows with stride 1 and padding 1 on maps as wide as a tile, one pixel less or more, and one or two pixels wide
+# or high; three channel blocks of 16; waves with no group of taps to walk
+@pytest.mark.parametrize("cin,h,w,cout", [(32, 700, 1, 64), (32, 350, 2, 64), (32, 1, 700, 64), (48, 2, 333, 128), (32, 9, 63, 64), (32, 9, 64, 64), (32, 9, 65, 64),
+                                          (48, 23, 29, 192)])
+def test_three_taps_from_one_fetch_of_rows(cin, h, w, cout):
+    """Single pixels at corners, row ends and tile ends: nothing reaches a pixel on the other side of the image's edge."""
+    rng = np.random.default_rng(19)
+    x = np.zeros((cin, h * w), np.float32)
+    at = sorted({0, w - 1, w * (h // 2), w * (h // 2) + w - 1, h * w - w, h * w - 1, min(63, h * w - 1), min(64, h * w - 1)})
+    for i, m in enumerate(at):
+        x[(7 * i) % cin, m] = 1.0 + i
+    x = x.reshape(cin, h, w)
+    wt = rng.normal(0, 1, (cout, cin, 3, 3)).astype(np.float32)
+    L = [N.Layer(op=N.OP_CONV, c_in=cin, c_out=cout, k=3, stride=1, pad=1, act=0, in_from=-1)]
+    with GpuNet(L, [(wt, None)], (cin, h, w), "fp32", plan_cus=8) as g:
+        got = g.forward(x).astype(np.float64).reshape(cout, h, w)
+        assert D.daris_get_launch_plan(g.task, 0)["rows"] == 64
+    want = torch.nn.functional.conv2d(torch.from_numpy(x).double()[None], torch.from_numpy(wt).double(), padding=1).numpy()[0]
+    bound = torch.nn.functional.conv2d(torch.from_numpy(x).double()[None], torch.from_numpy(wt).double().abs(), padding=1).numpy()[0]
+    assert (np.abs(got - want) <= 2.0 ** -22 * bound).all()      # products to 2^-23 each, at most a few of them in a sum
+
+
 @pytest.mark.parametrize("case", [(64, 112, 112, 64, 7, 1, 3, 128), (64, 56, 56, 64, 6, 1, 3, 32), (16, 64, 64, 64, 9, 1, 4, 32), (256, 56, 56, 256, 1, 1, 1, 128)],
                          ids=lambda c: "x".join(map(str, c)))
 def test_large_layers_that_block_tiles_cannot_take(case):
