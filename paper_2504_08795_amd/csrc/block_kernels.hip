@@ -124,10 +124,10 @@ __global__ __launch_bounds__(NW * 64) void conv_block_kernel(const ConvArgs) {
     const int gk = (sbeg >> 1) / 3 * 16;
     int ky = fast_div(gk, p.mg_cin), ci = gk - ky * p.Cin;
     const int row_bytes = p.Cin * ES;
-    const int first = (m0 - 1 + prow - p.W) * row_bytes + piece * 16;  // of the row of pixel m0 - 1 + prow above, at channel 0
+    const uint32_t first = (uint32_t)(m0 - 1 + prow - p.W) * (uint32_t)row_bytes + (uint32_t)(piece * 16);  // of the row of pixel m0 - 1 + prow above, at channel 0
     uint4 rows[5];
     auto load_row = [&](int r) {  // r < 4: sixteen rows; 4: the last two, and zeros into rows 66 to 79
-      const int o = first + 16 * r * row_bytes + (ky * p.W * p.Cin + ci) * ES;
+      const int o = (int)(first + (uint32_t)(16 * r + ky * p.W) * (uint32_t)row_bytes + (uint32_t)(ci * ES));
       rows[r] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(xrsrc, r < 4 || prow < 2 ? o : (int)0x80000000, 0, 0));
     };
     auto advance = [&]() {

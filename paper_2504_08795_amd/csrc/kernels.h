@@ -104,7 +104,7 @@ struct ConvPlan {
   int tn, nw, S, sz, sw, MT, NTn, G, xmode;
   int step_align;                  // K slices are multiples of this many steps
   int staged;                      // the pixel operand may be fetched in whole 64-byte rows through LDS
-  int taps;                        // 64-pixel tiles: K in the order (ky, 16 channels, kx), one fetch of rows for three taps (see conv_block_kernel)
+  int taps;                        // K in the order (ky, channels of a chunk, kx), one fetch of rows for three taps (conv_taps_body, conv_block_kernel)
   int tiles;                       // output tiles per grid.z slice
   size_t ws_bytes;                 // split-K workspace this launch needs
   uint32_t grid_x;                 // workgroups of the launch
@@ -126,15 +126,15 @@ inline bool conv_block_takes(int H, int W, int cin_stride, int k, int pad, int K
   return k * k <= 31 && pad < k && conv_rows_staged(cin_stride, 0) && (uint64_t)(H + pad) * (uint64_t)W * (uint64_t)cin_stride * 4 < (1ull << 31) &&
          (uint64_t)(Kpad / 8) * 3072 + 12288 < (1ull << 31);
 }
-// Whether one fetch of rows can serve the three taps of a window's row (conv_block_kernel): the pixels of a tile and their
-// neighbours are then consecutive in the input.
+// Whether one fetch of rows can serve the three taps of a window's row (conv_taps_body, conv_block_kernel): the pixels of a tile and
+// their neighbours are then consecutive in the input.
 inline bool conv_three_taps(int k, int stride, int pad) { return k == 3 && stride == 1 && pad == 1; }
 // bf16 = 0/1.  Chooses tile shape, waves per workgroup and split-K from (M, N, Kpad), allow_block and the nominal partition
 // size (nominal_cus: how many CUs the grid is balanced for) only, so results do not depend on the partition a stage runs in.  step_align = 2 cuts K in whole chunks of two steps (for conv_rows_staged shapes), else 1.
 // cin_stride = the input tensor's channel stride: when it is a whole number of the 16-row kernel's K steps and the 32-row
 // plan would split K across workgroups, a 16-row plan that does not need to is chosen instead (cin_stride 0: never).
 // allow_block = false: no 64-pixel tiles (a convolution that conv_block_takes refuses, shares its launch or computes its input on the fly);
-// three_taps: conv_three_taps.
+// three_taps: conv_three_taps and conv_rows_take hold.
 ConvPlan plan_conv(int M, int N, int Kpad, int bf16, int step_align, int cin_stride, int nominal_cus, bool allow_block, bool three_taps = false);
 // Plan for a second convolution that is to share a launch with `first`: the same wave-tile kernel variant, K not split
 // across workgroups.  Returns a plan with kernel == K_NONE when that is not possible.
@@ -163,8 +163,9 @@ struct KernelLaunch {
 // Every kernel of the code object, looked up once.
 struct KernelTable {
   const AqlKernel* conv[2][6][4] = {};  // [bf16][(tn - 1) * 3 + log2(nw) - 1][gather mode 0..3] (fp32: no mode 0)
+  const AqlKernel* taps[2][6] = {};     // the same with one fetch of rows for three taps (gather mode 5)
   const AqlKernel* pair[2][6][3] = {};  // gather modes 0, 1, 3
-  const AqlKernel* conv16[2][6] = {};   // 16-row tiles: [bf16][(tn - 1) * 3 + log2(nw) - 1]
+  const AqlKernel* conv16[2][2][6] = {};  // 16-row tiles: [bf16][three taps per fetch][(tn - 1) * 3 + log2(nw) - 1]
   const AqlKernel* pair16[2][6] = {};
   const AqlKernel* block[2][3] = {};    // 64-pixel tiles: [three taps per fetch][log2(nw) - 1]
   const AqlKernel* convdw[2][6] = {};   // 1x1 convolution with a fused depthwise producer (fp32: tn = 1 only)

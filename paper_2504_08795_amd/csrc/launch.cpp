@@ -55,7 +55,6 @@ static ConvPlan plan_conv_wave(int M, int N, int Kpad, int bf16, int step_align,
   // 8.8, 3072 x 64 x 576 on 64 CUs 9.9 against 12.7; but 784 x 512 x 128: 6.0 against 5.4)
   const bool block = allow_block && !bf16 && staged && nb % 2 == 0 && cdiv(M, 64) * (nb / 2) >= nominal_cus * 3 / 4 && S >= 32;
   if (block) tn = 2;
-  if (block && three_taps) step_align = 6;  // three chunks of two steps
   const int tiles = (block ? cdiv(M, 64) : cdiv(M, 32)) * (nb / tn);
   int nw = bf16 ? 4 : 8;  // bf16 steps are short: fewer waves to sum through LDS beat a finer K split (measured 0.4-0.8 us per layer)
   while (nw > 2 && (S / nw < 4 || tiles * nw > 8 * kNominalWaveSlots)) nw /= 2;  // >= 4 steps per wave, <= 8 waves per SIMD
@@ -93,7 +92,9 @@ static ConvPlan plan_conv_wave(int M, int N, int Kpad, int bf16, int step_align,
     z = 1;
   }
   // K slices of workgroups and waves in whole multiples of step_align steps (2 when the kernel fetches the pixel
-  // operand in chunks of two steps; S is then even as well)
+  // operand in chunks of two steps; S is then even as well; 6 when a fetch serves three chunks, where every wave gets one at least)
+  const bool taps = three_taps && staged && (block || S / 6 >= nw * z);
+  if (taps) step_align = 6;
   const int sz = cdiv(cdiv(S, z), step_align) * step_align;
   z = cdiv(S, sz);
   pl.rows = block ? 64 : 32;
@@ -104,7 +105,7 @@ static ConvPlan plan_conv_wave(int M, int N, int Kpad, int bf16, int step_align,
   pl.sw = cdiv(cdiv(sz, nw), step_align) * step_align;
   pl.step_align = step_align;
   pl.staged = staged;
-  pl.taps = block && three_taps;
+  pl.taps = taps;
   pl.splitk = z;
   pl.tiles = tiles;
   pl.threads = nw * 64;
@@ -136,7 +137,7 @@ static ConvPlan plan_conv_wave(int M, int N, int Kpad, int bf16, int step_align,
 // bf16 of 8 steps 5.3 -> 3.8 and 5.4 -> 3.8, 18: 5.7 -> 4.8 and 5.9 -> 5.0.  The two meet at 24 to 32 steps: 18 leaves room.  Tiles that
 // fill three quarters are taken at any length, up to 32 steps with a gain (128 tiles on 128 CUs: 24 steps 7.5 -> 6.8, 32: 8.4 -> 8.2), at
 // 36 without one (8.8 -> 8.8; 104 tiles 8.7 -> 9.6).
-static ConvPlan plan_conv_wave16(int M, int N, int Kpad, int bf16, int nominal_cus, int force_tn = 0, int force_nw = 0) {
+static ConvPlan plan_conv_wave16(int M, int N, int Kpad, int bf16, int nominal_cus, bool three_taps, int force_tn = 0, int force_nw = 0) {
   ConvPlan pl = ConvPlan();
   const int ks = bf16 ? 32 : 16;
   if (Kpad % 32) return pl;  // whole steps (bf16), pairs of steps (fp32)
@@ -168,8 +169,9 @@ static ConvPlan plan_conv_wave16(int M, int N, int Kpad, int bf16, int nominal_c
   pl.nw = nw;
   pl.S = S;
   pl.sz = S;
-  pl.sw = bf16 ? cdiv(S, nw) : 2 * cdiv(S / 2, nw);
-  pl.step_align = bf16 ? 1 : 2;
+  pl.taps = three_taps && S % 6 == 0 && S / 6 >= nw;
+  pl.step_align = pl.taps ? 6 : bf16 ? 1 : 2;
+  pl.sw = pl.step_align * cdiv(S / pl.step_align, nw);
   pl.staged = 1;
   pl.splitk = 1;
   pl.tiles = tiles;
@@ -198,7 +200,7 @@ ConvPlan plan_conv(int M, int N, int Kpad, int bf16, int step_align, int cin_str
   if (nominal_cus > 256) nominal_cus = 256;
   const ConvPlan pl = plan_conv_wave(M, N, Kpad, bf16, step_align, nominal_cus, allow_block, three_taps);
   if (pl.splitk > 1 && cin_stride > 0 && cin_stride % (bf16 ? 32 : 16) == 0) {
-    const ConvPlan p16 = plan_conv_wave16(M, N, Kpad, bf16, nominal_cus);
+    const ConvPlan p16 = plan_conv_wave16(M, N, Kpad, bf16, nominal_cus, three_taps);
     if (p16.kernel != K_NONE) return p16;
   }
   return pl;
@@ -208,7 +210,7 @@ ConvPlan plan_conv_like(const ConvPlan& first, int M, int N, int Kpad, int bf16,
   ConvPlan none = ConvPlan();
   if (nominal_cus < 8) nominal_cus = 8;
   if (nominal_cus > 256) nominal_cus = 256;
-  if (first.rows == 16) return plan_conv_wave16(M, N, Kpad, bf16, nominal_cus, first.tn, first.nw);
+  if (first.rows == 16) return plan_conv_wave16(M, N, Kpad, bf16, nominal_cus, false, first.tn, first.nw);
   if (cdiv(N, 32) % first.tn != 0) return none;
   return plan_conv_wave(M, N, Kpad, bf16, step_align, nominal_cus, false, false, first.tn, first.nw);
 }
@@ -280,12 +282,14 @@ std::string KernelTable::resolve(const AqlRuntime& rt) {
     for (int v = 0; v < 6; ++v) {
       const std::string tp = B + ", " + std::to_string(tn_[v]) + ", " + std::to_string(nw_[v]) + ", ";
       // (fp32 has no gather mode 0: what it would gain, a walk in scalars, mode 1 does in closed form for quads of channels)
+      taps[b][v] = get("daris::conv_wave_kernel<" + tp + "5>", sizeof(ConvArgs));
       for (int m = b ? 0 : 1; m < 4; ++m) conv[b][v][m] = get("daris::conv_wave_kernel<" + tp + std::to_string(m) + ">", sizeof(ConvArgs));
       static const int pair_modes[3] = {0, 1, 3};
       for (int m = b ? 0 : 1; m < 3; ++m) pair[b][v][m] = get("daris::conv_wave_pair_kernel<" + tp + std::to_string(pair_modes[m]) + ">", kPairBytes);
     }
     for (int v = 0; v < 6; ++v) {
-      conv16[b][v] = get("daris::conv_wave16_kernel<" + B + ", " + std::to_string(tn_[v]) + ", " + std::to_string(nw_[v]) + ">", sizeof(ConvArgs));
+      for (int t = 0; t < 2; ++t)
+        conv16[b][t][v] = get("daris::conv_wave16_kernel<" + B + ", " + std::to_string(tn_[v]) + ", " + std::to_string(nw_[v]) + (t ? ", 5>" : ">"), sizeof(ConvArgs));
       pair16[b][v] = get("daris::conv_wave16_pair_kernel<" + B + ", " + std::to_string(tn_[v]) + ", " + std::to_string(nw_[v]) + ">", kPairBytes);
       if (b ? nw_[v] != 8 : tn_[v] == 1)
         convdw[b][v] = get("daris::conv_wave_dw_kernel<" + B + ", " + std::to_string(tn_[v]) + ", " + std::to_string(nw_[v]) + ">", sizeof(ConvDwArgs));
@@ -317,13 +321,18 @@ static bool push_reduce(const KernelTable& kt, const ConvPlan& pl, const ConvArg
   return push(out, kt.reduce[bf16], K_SPLITK_REDUCE, (uint32_t)((total4 + 255) / 256), 256, &r, sizeof(ReduceArgs));
 }
 
+// What a fetch of rows for three taps assumes: the window, an output as large as the input, and K cut in threes of chunks.
+static bool taps_agree(const ConvPlan& pl, const ConvArgs& a) {
+  return conv_three_taps(a.kh, a.stride, a.pad) && a.kw == a.kh && a.Ho == a.H && a.Wo == a.W && pl.S % 6 == 0 && pl.sz % 6 == 0 && pl.sw % 6 == 0;
+}
+
 bool encode_conv(const KernelTable& kt, const ConvPlan& pl, const ConvArgs& a, int bf16, std::vector<KernelLaunch>* out) {
   if (pl.rows == 16) {
     const int v16 = pl.kernel - (bf16 ? K_CONV16_BF16_T1W2 : K_CONV16_F32_T1W2);
     const int ks16 = bf16 ? 32 : 16;
     if (v16 < 0 || v16 >= 6 || pl.threads != 64 * pl.nw || !rows_take(a, bf16) || a.Kpad % 32 || pl.S * ks16 != a.Kpad || pl.sw % pl.step_align) return false;
-    if (pl.splitk > 1 && !a.ws) return false;
-    if (!push(out, kt.conv16[bf16][v16], pl.kernel, pl.grid_x, (uint32_t)pl.threads, &a, sizeof(a))) return false;
+    if ((pl.splitk > 1 && !a.ws) || (pl.taps && !taps_agree(pl, a))) return false;
+    if (!push(out, kt.conv16[bf16][pl.taps][v16], pl.kernel, pl.grid_x, (uint32_t)pl.threads, &a, sizeof(a))) return false;
     return push_reduce(kt, pl, a, bf16, out);
   }
   if (pl.rows == 64) {
@@ -331,8 +340,7 @@ bool encode_conv(const KernelTable& kt, const ConvPlan& pl, const ConvArgs& a, i
     const int v64 = pl.kernel - K_CONV64_F32_T2W2;
     if (v64 < 0 || v64 >= 3 || pl.threads != 64 * pl.nw || bf16 || a.c_real > 0 || !pl.staged || pl.tn != 2 || pl.S % 2 || pl.sz % 2 || pl.sw % 2) return false;
     if (a.kh != a.kw || !conv_block_takes(a.H, a.W, a.Cin, a.kh, a.pad, a.Kpad) || (pl.splitk > 1 && !a.ws)) return false;
-    // ... and with three taps per fetch: its window, an output as large as the input, and K cut in threes of chunks
-    if (pl.taps && (!conv_three_taps(a.kh, a.stride, a.pad) || a.Ho != a.H || a.Wo != a.W || pl.S % 6 || pl.sz % 6 || pl.sw % 6)) return false;
+    if (pl.taps && !taps_agree(pl, a)) return false;
     if (!push(out, kt.block[pl.taps][v64], pl.kernel, pl.grid_x, (uint32_t)pl.threads, &a, sizeof(a))) return false;
     return push_reduce(kt, pl, a, bf16, out);
   }
@@ -344,7 +352,8 @@ bool encode_conv(const KernelTable& kt, const ConvPlan& pl, const ConvArgs& a, i
   if ((mode == 3 || !bf16) && (pl.S % 2 || pl.sz % 2 || pl.sw % 2)) return false;
   if (mode == 2 && (a.Cin != (bf16 ? 8 : 4) || a.c_real > 4 || (uint64_t)a.c_real * a.H * a.W * 4 >= (1ull << 31))) return false;
   if (pl.splitk > 1 && !a.ws) return false;
-  if (!push(out, kt.conv[bf16][variant][mode], pl.kernel, pl.grid_x, (uint32_t)pl.threads, &a, sizeof(a))) return false;
+  if (pl.taps && (mode != 3 || !taps_agree(pl, a))) return false;
+  if (!push(out, pl.taps ? kt.taps[bf16][variant] : kt.conv[bf16][variant][mode], pl.kernel, pl.grid_x, (uint32_t)pl.threads, &a, sizeof(a))) return false;
   return push_reduce(kt, pl, a, bf16, out);
 }
 
@@ -378,7 +387,7 @@ bool encode_conv_pair(const KernelTable& kt, const ConvPlan& pl0, const ConvArgs
   if (pl0.rows == 16) {
     const int ks16 = bf16 ? 32 : 16;
     const int v16 = pl0.kernel - (bf16 ? K_CONV16_BF16_T1W2 : K_CONV16_F32_T1W2);
-    if (pl1.rows != 16 || pl0.kernel != pl1.kernel || v16 < 0 || v16 >= 6 || pl0.splitk != 1 || pl1.splitk != 1 || !rows_take(a0, bf16) || !rows_take(a1, bf16) ||
+    if (pl0.taps || pl1.taps || pl1.rows != 16 || pl0.kernel != pl1.kernel || v16 < 0 || v16 >= 6 || pl0.splitk != 1 || pl1.splitk != 1 || !rows_take(a0, bf16) || !rows_take(a1, bf16) ||
         a0.Kpad % 32 || a1.Kpad % 32 || pl0.sw % pl0.step_align || pl1.sw % pl1.step_align || pl0.S * ks16 != a0.Kpad || pl1.S * ks16 != a1.Kpad)
       return false;
     PairArgs pa;
@@ -389,7 +398,7 @@ bool encode_conv_pair(const KernelTable& kt, const ConvPlan& pl0, const ConvArgs
     return push(out, kt.pair16[bf16][v16], pl0.kernel, (uint32_t)pa.n0 + pl1.grid_x, (uint32_t)pl0.threads, &pa, kPairBytes);
   }
   const bool aligned = bf16 && a0.Cin % 16 == 0;
-  if (pl0.kernel != pl1.kernel || pl0.rows != 32 || pl1.rows != 32 || aligned != (bf16 && a1.Cin % 16 == 0) || pl1.splitk != 1 || a0.c_real > 0 || a1.c_real > 0) return false;
+  if (pl0.taps || pl1.taps || pl0.kernel != pl1.kernel || pl0.rows != 32 || pl1.rows != 32 || aligned != (bf16 && a1.Cin % 16 == 0) || pl1.splitk != 1 || a0.c_real > 0 || a1.c_real > 0) return false;
   const bool staged = rows_take(a0, bf16) && rows_take(a1, bf16) && pl0.staged && pl1.staged;
   if ((staged || !bf16) && (pl0.S % 2 || pl0.sz % 2 || pl0.sw % 2 || pl1.S % 2 || pl1.sz % 2 || pl1.sw % 2)) return false;
   const int variant = pl0.kernel - (bf16 ? K_CONVW_BF16_T1W2 : K_CONVW_F32_T1W2);

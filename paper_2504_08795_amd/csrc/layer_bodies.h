@@ -762,6 +762,18 @@ __device__ __forceinline__ void rows_pipeline(const int n, Load&& load, Begun&& 
     });
   }
 }
+// One chunk through the matrix pipe: the two steps (bf16), or the six products of the operands' parts from the smallest to the largest.
+template <bool BF16, int R, int TN>
+__device__ __forceinline__ void wave_mma(const Split8& a, const uint4 (&b)[TN][BF16 ? 2 : 3], WaveAcc<R> (&acc)[TN]) {
+  constexpr int PA[6] = {BF16 ? 0 : 2, 1, 0, 1, 0, 0}, PB[6] = {0, 1, 2, 0, 1, 0};
+#pragma unroll
+  for (int t = 0; t < (BF16 ? 2 : 6); ++t)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+      if constexpr (R == 32) acc[j] = mfma_bf16(a.p[PA[t]], b[j][PB[t]], acc[j]);
+      else acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a.p[PA[t]]), __builtin_bit_cast(bf16x8, b[j][PB[t]]), acc[j], 0, 0, 0);
+    }
+}
 template <bool BF16, int R, int TN, int NW>
 __device__ __forceinline__ void conv_rows_body(const ConvArgs& p, const int mt, const int g, float* const red) {
   constexpr int ES = BF16 ? 2 : 4;
@@ -883,23 +895,139 @@ __device__ __forceinline__ void conv_rows_body(const ConvArgs& p, const int mt, 
         } else {
           parts = split8(a[0], a[1]);
         }
-        constexpr int PA[6] = {BF16 ? 0 : 2, 1, 0, 1, 0, 0}, PB[6] = {0, 1, 2, 0, 1, 0};  // fp32: from the smallest terms to the largest
-#pragma unroll
-        for (int t = 0; t < (BF16 ? 2 : 6); ++t)
-#pragma unroll
-          for (int j = 0; j < TN; ++j) {
-            if constexpr (R == 32) acc[j] = mfma_bf16(parts.p[PA[t]], bw[s][j][PB[t]], acc[j]);
-            else acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, parts.p[PA[t]]), __builtin_bit_cast(bf16x8, bw[s][j][PB[t]]), acc[j], 0, 0, 0);
-          }
+        wave_mma<BF16, R, TN>(parts, bw[s], acc);
         __builtin_amdgcn_sched_barrier(0);  // the refill takes over the registers of the slot just used
         if constexpr (refill) load_w(s);
       });
   __syncthreads();  // the partial tiles reuse the LDS of every wave's staging buffer
   fin.template finish<3>(p, DwFusedArgs(), acc, red, m0, nb0, zi, sbeg, nsteps);
 }
+// ---- the same for 3 x 3 windows with stride 1 and padding 1: one fetch of rows serves three taps (gather mode 5) ---------------
+//
+// A tile's R pixels and their left and right neighbours are R + 2 consecutive pixels of the input, whatever row of the image they
+// lie in.  K is walked as (ky, channels of a chunk, kx): three load instructions bring the rows of three chunks instead of six.  They go
+// into 48 places of the wave's corner of LDS (R = 16: the chunk's two rows of a pixel 24 places apart); the places behind them are
+// filled with zeros, and there a lane finds its neighbour on the other side of the image's edge.  Above and below the image the
+// rows are offsets outside the tensor.  The plan makes every wave's K slice a whole number of groups of three chunks; a group's rows and
+// weights are in flight while the one before is computed.  us on 128 CUs without and with: fp32 784 x 128 x 1152 5.85, 5.48;
+// 196 x 256 x 2304 7.05, 6.57; 49 x 512 x 4608 7.95, 7.70; 3136 x 64 x 576 5.88, 5.87; bf16 784 x 128 x 1152 3.35, 2.89; 196 x 256 x 2304 4.00,
+// 3.57; 49 x 512 x 4608 4.25, 3.64.
+template <bool BF16, int R, int TN, int NW>
+__device__ __forceinline__ void conv_taps_body(const ConvArgs& p, const int mt, const int g, float* const red) {
+  constexpr int ES = BF16 ? 2 : 4;
+  constexpr int RK = 64 / ES;                    // k of a row
+  constexpr int CK = R == 32 ? RK : 2 * RK;      // k of a chunk, which is two steps
+  constexpr int NP = BF16 ? 2 : 3;               // 16-byte pieces of a chunk's weights per lane and channel block: steps, or parts
+  constexpr int HALF = 24;                       // places between a pixel's two rows (R = 16)
+  constexpr int kZeros = R == 32 ? 40 : 20;      // a place that holds zeros (R = 16: and the one HALF further on)
+  constexpr int kOutside = (int)0x80000000;      // an offset past the end of any tensor
+
+  if (p.wave_prio) __builtin_amdgcn_s_setprio(3);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform: keeps the K loop's control flow scalar
+  const int zi = p.splitk == 1 ? 0 : g / p.NTn;
+  const int m0 = mt * R, nb0 = (g - zi * p.NTn) * TN;
+  const int s_wg0 = zi * p.sz;
+  const int s_wg1 = min(s_wg0 + p.sz, p.S);
+  const int sbeg = min(s_wg0 + wave * p.sw, s_wg1);
+  const int nsteps = min(sbeg + p.sw, s_wg1) - sbeg;
+
+  const int gk = sbeg / 6 * CK;
+  int ky = fast_div(gk, p.mg_cin), ci = gk - ky * p.Cin;
+  const int piece = lane & 3, prow = lane >> 2, row_bytes = p.Cin * ES;
+  int first[3];  // byte offset of the lane's piece of its row in each load, at (ky = 0, ci = 0)
+  bool used[3];
+#pragma unroll
+  for (int r = 0; r < 3; ++r) {
+    const int place = 16 * r + prow, half = R == 16 && place >= HALF ? 1 : 0, row = place - HALF * half;
+    used[r] = row < R + 2;
+    first[r] = (int)((uint32_t)(m0 - 1 + row - p.W) * (uint32_t)row_bytes) + 64 * half + piece * 16;
+  }
+  const auto xrsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p.x), 0, p.H * p.W * row_bytes, 0x00027000);
+  uint4 rows[3];
+  auto load_rows = [&]() {
+    const uint32_t off = (uint32_t)(ky * p.W) * (uint32_t)row_bytes + (uint32_t)(ci * ES);
+#pragma unroll
+    for (int r = 0; r < 3; ++r) rows[r] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(xrsrc, used[r] ? (int)((uint32_t)first[r] + off) : kOutside, 0, 0));
+    ci += CK;
+    if (ci >= p.Cin) {
+      ci = 0;
+      ++ky;
+    }
+  };
+  const int wbytes = BF16 ? nsteps * 1024 : (nsteps >> 1) * NP * 1024;
+  const unsigned char* const wbase = (const unsigned char*)p.w + ((size_t)nb0 * p.S + sbeg) * (NP * 512);
+  __amdgpu_buffer_rsrc_t wrsrc[TN];
+#pragma unroll
+  for (int j = 0; j < TN; ++j) wrsrc[j] = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(wbase) + (size_t)j * p.S * (NP * 512), 0, wbytes, 0x00027000);
+  int woff = 0;
+  uint4 bw[3][TN][NP];
+  auto load_w = [&](int kx) {
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int q = 0; q < NP; ++q) bw[kx][j][q] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(wrsrc[j], lane * 16 + q * 1024, woff, 0));
+    woff += NP * 1024;
+  };
+  WaveEpilogue<BF16, R, TN, NW, true> fin;
+  fin.fetch(p, m0, nb0, tid);  // (behind the first rows it would leave the paths into the loop with different loads on their way, see rows_pipeline)
+  WaveAcc<R> acc[TN];
+#pragma unroll
+  for (int j = 0; j < TN; ++j) acc[j] = WaveAcc<R>(0.f);
+
+  uint4* const st = reinterpret_cast<uint4*>(red) + wave * 192;  // 48 places of 4 pieces
+  const int li = lane % R, lh = lane / R;
+  // pieces of the lane's pixel from the chunk's first k on: bf16 R = 32: 2 h + lh, R = 16: 4 h + lh; fp32: 2 lh + h (h = 0, 1)
+  const int at0 = BF16 ? lh : 2 * lh;
+  auto row_at = [&](int row) {  // where piece h = 0 of a row lies (spread over the banks)
+    const int place = row + (R == 16 ? HALF * (at0 >> 2) : 0);
+    return place * 4 + ((at0 & 3) ^ ((place >> 1) & 3));
+  };
+  const int m = m0 + li, x = m - fast_div(m, p.mg_wo) * p.Wo;
+  const int at[3] = {x == 0 ? row_at(kZeros) : row_at(li), row_at(li + 1), x == p.Wo - 1 ? row_at(kZeros) : row_at(li + 2)};
+  // lanes exchange data through the wave's buffer: order the accesses of the whole wave, not only of each lane
+  auto wave_order = [&]() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  };
+  auto chunk = [&](auto kx, auto more) {  // tap kx of a group; more: another group follows
+    if constexpr (kx == 0) {
+      wave_order();
+#pragma unroll
+      for (int r = 0; r < 3; ++r) st[(16 * r + prow) * 4 + (piece ^ ((prow >> 1) & 3))] = rows[r];
+      if constexpr (more) load_rows();
+      wave_order();
+    }
+    const uint4 a0 = st[at[kx]], a1 = st[BF16 ? (R == 32 ? at[kx] ^ 2 : at[kx] + 4 * HALF) : at[kx] ^ 1];
+    Split8 parts;
+    if constexpr (BF16) {
+      parts.p[0] = a0;
+      parts.p[1] = a1;
+    } else {
+      parts = split8(a0, a1);
+    }
+    wave_mma<BF16, R, TN>(parts, bw[kx], acc);
+    __builtin_amdgcn_sched_barrier(0);  // the refill takes over the registers of the weights just used
+    if constexpr (more) load_w(kx);
+  };
+  if (nsteps > 0) {
+    load_rows();
+    static_for<0, 3>(load_w);
+    for (int groups = nsteps / 6; groups > 1; --groups) static_for<0, 3>([&](auto kx) { chunk(kx, std::true_type()); });
+    static_for<0, 3>([&](auto kx) { chunk(kx, std::false_type()); });
+  }
+  __syncthreads();  // the partial tiles reuse the LDS of every wave's staging buffer
+  fin.template finish<5>(p, DwFusedArgs(), acc, red, m0, nb0, zi, sbeg, nsteps);
+}
+
 template <int R, int TN, int NW>
 constexpr int conv_rows_lds() {  // floats of LDS
   return NW * 512 > NW * TN * R * R ? NW * 512 : NW * TN * R * R;
+}
+template <int R, int TN, int NW>
+constexpr int conv_taps_lds() {
+  return NW * 768 > NW * TN * R * R ? NW * 768 : NW * TN * R * R;
 }
 
 // ---- pointwise layers: one thread per (output pixel, 16-byte channel vector) ----------------------------------------------

@@ -88,7 +88,8 @@ std::string build_plan(const daris_dnn& dnn, bool keep_activations, bool pair_la
           if ((uint64_t)(o.H * (uint64_t)o.W + 64) * (uint64_t)o.W >= (1ull << 32) || (uint64_t)(L.Kpad + 64) * (uint64_t)in.Cs >= (1ull << 32))
             return "layer " + std::to_string(l) + ": tensor too large for the kernels' index arithmetic";
           L.cp = plan_conv(o.H * o.W, o.Cs, L.Kpad, net.bf16, staged_rows && conv_rows_staged(in.Cs, net.bf16) ? 2 : 1, small_tile_stride(L), plan_cus,
-                           conv_block_takes(in.H, in.W, in.Cs, d.k, d.pad, L.Kpad), conv_three_taps(d.k, d.stride, d.pad));
+                           conv_block_takes(in.H, in.W, in.Cs, d.k, d.pad, L.Kpad),
+                           staged_rows && conv_three_taps(d.k, d.stride, d.pad) && conv_rows_take(in.H, in.W, in.Cs, (uint64_t)o.H * (uint64_t)o.W, o.Cs, L.Kpad, net.bf16));
           L.kernel_id = L.cp.kernel;
           net.ws_bytes = std::max(net.ws_bytes, L.cp.ws_bytes);
         } else {
@@ -148,7 +149,7 @@ std::string build_plan(const daris_dnn& dnn, bool keep_activations, bool pair_la
     LayerPlan& light = A.macs > B.macs ? B : A;
     const ConvPlan own = heavy.cp;
     const int sa = staged_rows && conv_rows_staged(net.tensor(heavy.in_t).Cs, net.bf16) ? 2 : 1;
-    if (heavy.cp.rows == 64)
+    if (heavy.cp.rows == 64 || heavy.cp.taps)  // (kernels that have no form for two problems)
       heavy.cp = plan_conv(heavy.out.H * heavy.out.W, heavy.out.Cs, heavy.Kpad, net.bf16, sa, small_tile_stride(heavy), plan_cus, false);
     const ConvPlan like = plan_conv_like(heavy.cp, light.out.H * light.out.W, light.out.Cs, light.Kpad, net.bf16,
                                          staged_rows && conv_rows_staged(net.tensor(light.in_t).Cs, net.bf16) ? 2 : 1, plan_cus);
@@ -309,11 +310,14 @@ void pack_conv(const NetPlan& net, const LayerPlan& L, const float* w, const flo
       for (int t = 0; t < kk; ++t) put<float>(wp, (size_t)t * in.Cs + c, w[(size_t)c * kk + t], bf);
     return;
   }
+  // Where weight (tap t, channel ci) lies along K: tap by tap, or, where a fetch of rows serves three taps, chunk by chunk in the order
+  // (ky, channels of a chunk, kx)
+  const int per_chunk = (L.cp.rows == 16 ? 128 : 64) / (int)es;
+  auto k_of = [&](int t, int ci) { return L.cp.taps ? ((t / 3 * (in.Cs / per_chunk) + ci / per_chunk) * 3 + t % 3) * per_chunk + ci % per_chunk : t * in.Cs + ci; };
   if (!bf) {
     // fp32: three bf16 parts per weight (see split8 in device_common.h), [channel block of R][chunk][part][lane = i + R q][8],
     // element e of lane (i, q) in chunk s is W[n = R nb + i][k = s * CK + 8 q + e]; a chunk is what one matrix instruction
-    // takes, CK = 16 (R = 32) or 32 (R = 16).  Tiles that fetch rows for three taps at once take their chunks of 16 in the order
-    // (ky, ci / 16, kx)
+    // takes, CK = 16 (R = 32) or 32 (R = 16)
     const int R = L.cp.rows == 16 ? 16 : 32, ck = R == 16 ? 32 : 16, nch = L.Kpad / ck;
     const int nblocks = (L.out.Cs + R - 1) / R;
     const int nb_alloc = (nblocks + L.cp.tn - 1) / L.cp.tn * L.cp.tn;
@@ -322,8 +326,8 @@ void pack_conv(const NetPlan& net, const LayerPlan& L, const float* w, const flo
     for (int o = 0; o < d.c_out; ++o)
       for (int ci = 0; ci < d.c_in; ++ci)
         for (int t = 0; t < kk; ++t) {
-          const int k = t * in.Cs + ci;
-          const int s = L.cp.taps ? (t / 3 * (in.Cs / 16) + ci / 16) * 3 + t % 3 : k / ck, q = (k % ck) / 8, e = k % 8;
+          const int k = k_of(t, ci);
+          const int s = k / ck, q = (k % ck) / 8, e = k % 8;
           const size_t at = ((size_t)(o / R) * nch + s) * 3 * 512 + (size_t)(o % R + R * q) * 8 + e;
           uint16_t part[3];
           split_bf16(w[((size_t)o * d.c_in + ci) * kk + t], part);
@@ -341,7 +345,7 @@ void pack_conv(const NetPlan& net, const LayerPlan& L, const float* w, const flo
     for (int o = 0; o < d.c_out; ++o)
       for (int ci = 0; ci < d.c_in; ++ci)
         for (int t = 0; t < kk; ++t) {
-          const int k = t * in.Cs + ci;
+          const int k = k_of(t, ci);
           const int st = k / ks, q = (k % ks) / vec, e = k % vec;
           const size_t lane = (size_t)(o % 16) + 16 * q;
           put<float>(wp, (((size_t)(o / 16) * S + st) * 64 + lane) * vec + e, w[((size_t)o * d.c_in + ci) * kk + t], bf);
@@ -357,7 +361,7 @@ void pack_conv(const NetPlan& net, const LayerPlan& L, const float* w, const flo
   for (int o = 0; o < d.c_out; ++o)
     for (int ci = 0; ci < d.c_in; ++ci)
       for (int t = 0; t < kk; ++t) {
-        const int k = t * in.Cs + ci;
+        const int k = k_of(t, ci);
         const int st = k / ks, h = (k % ks) / vec, e = k % vec;
         const size_t lane = (size_t)(o % 32) + 32 * h;
         put<float>(wp, (((size_t)(o / 32) * S + st) * 64 + lane) * vec + e, w[((size_t)o * d.c_in + ci) * kk + t], bf);

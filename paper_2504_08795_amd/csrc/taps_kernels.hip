@@ -1,0 +1,42 @@
+// Convolutions whose waves fetch rows once for three taps of a 3 x 3 window (conv_taps_body in layer_bodies.h).
+#include <hip/hip_runtime.h>
+
+#include "layer_bodies.h"
+#include "device_common.h"
+#include "kernels.h"
+
+namespace daris {
+
+template <bool BF16, int TN, int NW, int MODE>
+__global__ __launch_bounds__(NW * 64) void conv_wave_kernel(const ConvArgs) {
+  static_assert(MODE == 5, "the other gather modes have their own code object");
+  const ConvArgs p = conv_args_at((ConstPtr)__builtin_amdgcn_kernarg_segment_ptr());
+  __shared__ __align__(16) float red[conv_taps_lds<32, TN, NW>()];
+  int mt, g;
+  if (!conv_tile_of(p, (int)blockIdx.x, &mt, &g)) return;
+  conv_taps_body<BF16, 32, TN, NW>(p, mt, g, red);
+  puts_done();
+}
+
+template <bool BF16, int TB, int NW, int MODE>
+__global__ __launch_bounds__(NW * 64) void conv_wave16_kernel(const ConvArgs) {
+  static_assert(MODE == 5, "the other gather modes have their own code object");
+  const ConvArgs p = conv_args_at((ConstPtr)__builtin_amdgcn_kernarg_segment_ptr());
+  __shared__ __align__(16) float red[conv_taps_lds<16, TB, NW>()];
+  int mt, g;
+  if (!conv_tile_of(p, (int)blockIdx.x, &mt, &g)) return;
+  conv_taps_body<BF16, 16, TB, NW>(p, mt, g, red);
+  puts_done();
+}
+
+#define DARIS_INST_TAPS(B, T, W)                                         \
+  template __global__ void conv_wave_kernel<B, T, W, 5>(const ConvArgs); \
+  template __global__ void conv_wave16_kernel<B, T, W, 5>(const ConvArgs);
+#define DARIS_INST_TAPS_ALL(B) \
+  DARIS_INST_TAPS(B, 1, 2) DARIS_INST_TAPS(B, 1, 4) DARIS_INST_TAPS(B, 1, 8) DARIS_INST_TAPS(B, 2, 2) DARIS_INST_TAPS(B, 2, 4) DARIS_INST_TAPS(B, 2, 8)
+DARIS_INST_TAPS_ALL(false)
+DARIS_INST_TAPS_ALL(true)
+#undef DARIS_INST_TAPS_ALL
+#undef DARIS_INST_TAPS
+
+}  // namespace daris

@@ -74,6 +74,26 @@ def test_conv(case, dtype):
     run_case(layers, (cin, h, w), dtype)
 
 
+# 3x3 windows with stride 1 and padding 1 on maps one pixel wide or high, as wide as a tile and one less or more: 16-pixel tiles, 32-pixel
+# tiles with and without K split over workgroups; groups of three taps that fill the waves evenly, unevenly and not all of them
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("cin,h,w,cout", [(128, 1, 401, 64), (128, 390, 1, 64), (128, 13, 15, 64), (128, 13, 16, 64), (192, 13, 33, 40), (512, 3, 5, 64), (512, 1, 17, 520),
+                                          (576, 16, 2, 96), (640, 1, 1, 512), (64, 1, 3201, 64), (64, 3137, 1, 64), (96, 103, 31, 64), (64, 99, 32, 64), (64, 98, 33, 32)])
+def test_three_taps_from_one_fetch_of_rows(cin, h, w, cout, dtype):
+    """Single pixels at corners, row ends and tile ends: nothing reaches a pixel on the other side of the image's edge."""
+    x = np.zeros((cin, h * w), np.float32)
+    for i, m in enumerate(sorted({0, w - 1, w * (h // 2), w * (h // 2) + w - 1, h * w - w, h * w - 1, min(31, h * w - 1), min(32, h * w - 1)})):
+        x[(7 * i) % cin, m] = 1.0 + i
+    layers = [N.Layer(op=N.OP_CONV, c_in=cin, c_out=cout, k=3, stride=1, pad=1, act=0, in_from=-1)]
+    weights = [(rand_w(layers[0])[0], np.zeros(cout, np.float32))]
+    want = oracle_logits(layers, weights, x.reshape(cin, h, w), dtype)
+    with GpuNet(layers, weights, (cin, h, w), dtype) as net:
+        got = net.forward(x.reshape(cin, h, w))
+        assert D.daris_get_launch_plan(net.task, 0)["rows"] in (16, 32)
+    e_max, e_l2 = rel_err(got, want)
+    assert e_max <= LAYER_TOL[dtype] and e_l2 <= LAYER_TOL[dtype] and (np.asarray(got)[np.asarray(want) == 0] == 0).all(), (e_max, e_l2)
+
+
 @pytest.mark.parametrize("dtype", ["fp32", "bf16"])
 @pytest.mark.parametrize("cin,hw,cout,s", [(64, 28, 128, 2), (64, 14, 64, 1), (256, 7, 512, 2)])
 def test_conv_residual_block(cin, hw, cout, s, dtype):
