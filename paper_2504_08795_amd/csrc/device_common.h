@@ -188,6 +188,18 @@ __device__ __forceinline__ Split8 split8(const uint4& lo, const uint4& hi) {
   return s;
 }
 
+// The parts of four consecutive values.
+struct Split4 {
+  uint2 p[3];
+};
+__device__ __forceinline__ Split4 split4(const uint4& v) {
+  const Split8 s = split8(v, make_uint4(0u, 0u, 0u, 0u));
+  Split4 t;
+#pragma unroll
+  for (int q = 0; q < 3; ++q) t.p[q] = make_uint2(s.p[q].x, s.p[q].y);
+  return t;
+}
+
 __device__ __forceinline__ f32x16 mfma_bf16(const uint4& a, const uint4& b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }

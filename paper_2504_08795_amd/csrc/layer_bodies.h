@@ -908,10 +908,19 @@ __device__ __forceinline__ void conv_rows_body(const ConvArgs& p, const int mt, 
 // lie in.  K is walked as (ky, channels of a chunk, kx): three load instructions bring the rows of three chunks instead of six.  They go
 // into 48 places of the wave's corner of LDS (R = 16: the chunk's two rows of a pixel 24 places apart); the places behind them are
 // filled with zeros, and there a lane finds its neighbour on the other side of the image's edge.  Above and below the image the
-// rows are offsets outside the tensor.  The plan makes every wave's K slice a whole number of groups of three chunks; a group's rows and
-// weights are in flight while the one before is computed.  us on 128 CUs without and with: fp32 784 x 128 x 1152 5.85, 5.48;
-// 196 x 256 x 2304 7.05, 6.57; 49 x 512 x 4608 7.95, 7.70; 3136 x 64 x 576 5.88, 5.87; bf16 784 x 128 x 1152 3.35, 2.89; 196 x 256 x 2304 4.00,
+// rows are offsets outside the tensor.  In fp32 the rows are split into their parts on the way into LDS, once for three taps instead of
+// for each (split8 is two thirds of a chunk's vector instructions), each part in a plane of its own.  The plan makes every wave's K
+// slice a whole number of groups of three chunks; a group's rows and weights are in flight while the one before is computed.  us on 128 CUs without and with: fp32 784 x 128 x 1152 5.85, 5.38
+// (split behind LDS 5.48); 196 x 256 x 2304 7.05, 6.67; 49 x 512 x 4608 7.95, 7.25 (7.70); 3136 x 64 x 576 5.88, 5.68 (5.87); 196 x 512 x 4608 13.1, 12.4; bf16 784 x 128 x 1152 3.35, 2.89; 196 x 256 x 2304 4.00,
 // 3.57; 49 x 512 x 4608 4.25, 3.64.
+template <bool BF16>
+constexpr int conv_taps_stage() {  // floats of a wave's corner of LDS
+  return BF16 ? 48 * 16 : 3 * 48 * 8;
+}
+template <bool BF16, int R, int TN, int NW>
+constexpr int conv_taps_lds() {
+  return NW * conv_taps_stage<BF16>() > NW * TN * R * R ? NW * conv_taps_stage<BF16>() : NW * TN * R * R;
+}
 template <bool BF16, int R, int TN, int NW>
 __device__ __forceinline__ void conv_taps_body(const ConvArgs& p, const int mt, const int g, float* const red) {
   constexpr int ES = BF16 ? 2 : 4;
@@ -970,18 +979,24 @@ __device__ __forceinline__ void conv_taps_body(const ConvArgs& p, const int mt, 
     woff += NP * 1024;
   };
   WaveEpilogue<BF16, R, TN, NW, true> fin;
-  fin.fetch(p, m0, nb0, tid);  // (behind the first rows it would leave the paths into the loop with different loads on their way, see rows_pipeline)
+  // Bias and residual are requested first: behind the first rows they would leave the paths into the loop with different loads on
+  // their way (see rows_pipeline).  fp32 tiles of 16 x 32 keep their registers for the loop (eight waves fit 128, two workgroups a CU:
+  // 196 x 256 x 2304 on 64 CUs 10.2 us instead of 12.0) and request them ahead of the last group, which costs the others 0.1 us.
+  constexpr bool LATE = !BF16 && R == 16 && TN == 2;
+  if constexpr (!LATE) fin.fetch(p, m0, nb0, tid);
   WaveAcc<R> acc[TN];
 #pragma unroll
   for (int j = 0; j < TN; ++j) acc[j] = WaveAcc<R>(0.f);
 
-  uint4* const st = reinterpret_cast<uint4*>(red) + wave * 192;  // 48 places of 4 pieces
+  // bf16: 48 places of 4 pieces of 16 bytes; fp32: in each of three planes 48 places of 16 values in bf16, 2 pieces of 16 bytes
+  uint4* const st = reinterpret_cast<uint4*>(red) + wave * (conv_taps_stage<BF16>() / 4);
+  constexpr int PLANE = 48 * 2;
   const int li = lane % R, lh = lane / R;
-  // pieces of the lane's pixel from the chunk's first k on: bf16 R = 32: 2 h + lh, R = 16: 4 h + lh; fp32: 2 lh + h (h = 0, 1)
-  const int at0 = BF16 ? lh : 2 * lh;
-  auto row_at = [&](int row) {  // where piece h = 0 of a row lies (spread over the banks)
-    const int place = row + (R == 16 ? HALF * (at0 >> 2) : 0);
-    return place * 4 + ((at0 & 3) ^ ((place >> 1) & 3));
+  // Pieces of the lane's pixel from the chunk's first k on: bf16 R = 32: 2 h + lh, R = 16: 4 h + lh (h = 0, 1); fp32: 8 k from 8 lh on.
+  // row_at: where piece h = 0 of a row lies, or its part in the first plane (spread over the banks)
+  auto row_at = [&](int row) {
+    const int place = row + (R == 16 && !BF16 ? HALF * (lh >> 1) : 0);
+    return BF16 ? place * 4 + (lh ^ ((place >> 1) & 3)) : place * 2 + ((lh & 1) ^ ((place >> 2) & 1));
   };
   const int m = m0 + li, x = m - fast_div(m, p.mg_wo) * p.Wo;
   const int at[3] = {x == 0 ? row_at(kZeros) : row_at(li), row_at(li + 1), x == p.Wo - 1 ? row_at(kZeros) : row_at(li + 2)};
@@ -995,17 +1010,25 @@ __device__ __forceinline__ void conv_taps_body(const ConvArgs& p, const int mt, 
     if constexpr (kx == 0) {
       wave_order();
 #pragma unroll
-      for (int r = 0; r < 3; ++r) st[(16 * r + prow) * 4 + (piece ^ ((prow >> 1) & 3))] = rows[r];
+      for (int r = 0; r < 3; ++r) {
+        if constexpr (BF16) {
+          st[(16 * r + prow) * 4 + (piece ^ ((prow >> 1) & 3))] = rows[r];
+        } else {
+          const Split4 v = split4(rows[r]);
+#pragma unroll
+          for (int q = 0; q < 3; ++q) reinterpret_cast<uint2*>(st + q * PLANE + (16 * r + prow) * 2 + ((piece >> 1) ^ ((prow >> 2) & 1)))[piece & 1] = v.p[q];
+        }
+      }
       if constexpr (more) load_rows();
       wave_order();
     }
-    const uint4 a0 = st[at[kx]], a1 = st[BF16 ? (R == 32 ? at[kx] ^ 2 : at[kx] + 4 * HALF) : at[kx] ^ 1];
     Split8 parts;
     if constexpr (BF16) {
-      parts.p[0] = a0;
-      parts.p[1] = a1;
+      parts.p[0] = st[at[kx]];
+      parts.p[1] = st[R == 32 ? at[kx] ^ 2 : at[kx] + 4 * HALF];
     } else {
-      parts = split8(a0, a1);
+#pragma unroll
+      for (int q = 0; q < 3; ++q) parts.p[q] = st[q * PLANE + at[kx]];
     }
     wave_mma<BF16, R, TN>(parts, bw[kx], acc);
     __builtin_amdgcn_sched_barrier(0);  // the refill takes over the registers of the weights just used
@@ -1015,7 +1038,10 @@ __device__ __forceinline__ void conv_taps_body(const ConvArgs& p, const int mt, 
     load_rows();
     static_for<0, 3>(load_w);
     for (int groups = nsteps / 6; groups > 1; --groups) static_for<0, 3>([&](auto kx) { chunk(kx, std::true_type()); });
+    if constexpr (LATE) fin.fetch(p, m0, nb0, tid);
     static_for<0, 3>([&](auto kx) { chunk(kx, std::false_type()); });
+  } else if constexpr (LATE) {
+    fin.fetch(p, m0, nb0, tid);
   }
   __syncthreads();  // the partial tiles reuse the LDS of every wave's staging buffer
   fin.template finish<5>(p, DwFusedArgs(), acc, red, m0, nb0, zi, sbeg, nsteps);
@@ -1024,10 +1050,6 @@ __device__ __forceinline__ void conv_taps_body(const ConvArgs& p, const int mt, 
 template <int R, int TN, int NW>
 constexpr int conv_rows_lds() {  // floats of LDS
   return NW * 512 > NW * TN * R * R ? NW * 512 : NW * TN * R * R;
-}
-template <int R, int TN, int NW>
-constexpr int conv_taps_lds() {
-  return NW * 768 > NW * TN * R * R ? NW * 768 : NW * TN * R * R;
 }
 
 // ---- pointwise layers: one thread per (output pixel, 16-byte channel vector) ----------------------------------------------

@@ -11,7 +11,7 @@ template <bool BF16, int TN, int NW, int MODE>
 __global__ __launch_bounds__(NW * 64) void conv_wave_kernel(const ConvArgs) {
   static_assert(MODE == 5, "the other gather modes have their own code object");
   const ConvArgs p = conv_args_at((ConstPtr)__builtin_amdgcn_kernarg_segment_ptr());
-  __shared__ __align__(16) float red[conv_taps_lds<32, TN, NW>()];
+  __shared__ __align__(16) float red[conv_taps_lds<BF16, 32, TN, NW>()];
   int mt, g;
   if (!conv_tile_of(p, (int)blockIdx.x, &mt, &g)) return;
   conv_taps_body<BF16, 32, TN, NW>(p, mt, g, red);
@@ -19,10 +19,10 @@ __global__ __launch_bounds__(NW * 64) void conv_wave_kernel(const ConvArgs) {
 }
 
 template <bool BF16, int TB, int NW, int MODE>
-__global__ __launch_bounds__(NW * 64) void conv_wave16_kernel(const ConvArgs) {
+__global__ __launch_bounds__(NW * 64, NW == 8 ? 4 : 1) void conv_wave16_kernel(const ConvArgs) {
   static_assert(MODE == 5, "the other gather modes have their own code object");
   const ConvArgs p = conv_args_at((ConstPtr)__builtin_amdgcn_kernarg_segment_ptr());
-  __shared__ __align__(16) float red[conv_taps_lds<16, TB, NW>()];
+  __shared__ __align__(16) float red[conv_taps_lds<BF16, 16, TB, NW>()];
   int mt, g;
   if (!conv_tile_of(p, (int)blockIdx.x, &mt, &g)) return;
   conv_taps_body<BF16, 16, TB, NW>(p, mt, g, red);
