@@ -8,7 +8,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libdaris.so")
 # device source -> symbol prefix of its code object in the library
-DEVICE_SOURCES = {"kernels.hip": "daris_kernels", "taps_kernels.hip": "daris_taps_kernels", "block_kernels.hip": "daris_block_kernels",
+DEVICE_SOURCES = {"kernels.hip": "daris_kernels", "taps_kernels.hip": "daris_taps_kernels", "image_kernels.hip": "daris_image_kernels", "block_kernels.hip": "daris_block_kernels",
                   "point_kernels.hip": "daris_point_kernels"}
 HOST_SOURCES = ["aql.cpp", "launch.cpp", "sched_core.cpp", "net_plan.cpp", "daris_api.cpp"]
 COMMON = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-Wall", "-Wno-unused-function"]

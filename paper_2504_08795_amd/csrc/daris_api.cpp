@@ -33,11 +33,13 @@
 
 using namespace daris;
 
-// the device code objects (built from kernels.hip, taps_kernels.hip, block_kernels.hip and point_kernels.hip), linked into the library as data
+// the device code objects (built from kernels.hip, taps_kernels.hip, image_kernels.hip, block_kernels.hip and point_kernels.hip), linked into the library as data
 extern "C" const char daris_kernels_co[];
 extern "C" const char daris_kernels_co_end[];
 extern "C" const char daris_taps_kernels_co[];
 extern "C" const char daris_taps_kernels_co_end[];
+extern "C" const char daris_image_kernels_co[];
+extern "C" const char daris_image_kernels_co_end[];
 extern "C" const char daris_block_kernels_co[];
 extern "C" const char daris_block_kernels_co_end[];
 extern "C" const char daris_point_kernels_co[];
@@ -866,6 +868,7 @@ daris_status daris_init(int device, uint64_t seed, int flags) {
       err = g_rt.init(device, {{daris_kernels_co, (size_t)(daris_kernels_co_end - daris_kernels_co)},
                                {daris_block_kernels_co, (size_t)(daris_block_kernels_co_end - daris_block_kernels_co)},
                                {daris_taps_kernels_co, (size_t)(daris_taps_kernels_co_end - daris_taps_kernels_co)},
+                               {daris_image_kernels_co, (size_t)(daris_image_kernels_co_end - daris_image_kernels_co)},
                                {daris_point_kernels_co, (size_t)(daris_point_kernels_co_end - daris_point_kernels_co)}});
       if (err.empty()) {
         err = g_kt.resolve(g_rt);

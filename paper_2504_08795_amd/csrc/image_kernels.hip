@@ -1,0 +1,25 @@
+// The first convolution of a network, reading the caller's input (conv_image_body in layer_bodies.h).
+#include <hip/hip_runtime.h>
+
+#include "layer_bodies.h"
+#include "device_common.h"
+#include "kernels.h"
+
+namespace daris {
+
+template <bool BF16, int WN, int NW, int MODE>
+__global__ __launch_bounds__(NW * 64) void conv_wave_kernel(const ImageConvArgs) {
+  static_assert(MODE == 6 && NW == 4, "the other gather modes have their own code objects");
+  ImageConvArgs p = grab<ImageConvArgs>((ConstPtr)__builtin_amdgcn_kernarg_segment_ptr());
+  args_in_memory(p);
+  __shared__ __align__(16) float lds[conv_image_lds<BF16>()];
+  conv_image_body<BF16, WN>(p, (int)blockIdx.x, lds);
+  puts_done();
+}
+
+template __global__ void conv_wave_kernel<false, 1, 4, 6>(const ImageConvArgs);
+template __global__ void conv_wave_kernel<false, 2, 4, 6>(const ImageConvArgs);
+template __global__ void conv_wave_kernel<true, 1, 4, 6>(const ImageConvArgs);
+template __global__ void conv_wave_kernel<true, 2, 4, 6>(const ImageConvArgs);
+
+}  // namespace daris

@@ -48,6 +48,25 @@ struct ConvArgs {
   int wave_prio;          // 1: the waves raise their issue priority (stages of high-priority tasks on shared CUs)
 };
 
+// The first convolution of a network for conv_image_body: x is the network input as the caller gives it, float [c_real][H][W].
+// One size with ConvArgs.
+struct ImageConvArgs {
+  const void* x;
+  const void* w;  // as ConvArgs::w
+  const float* bias;
+  void* y;
+  int H, W, Ho, Wo, Cout, k, stride, pad;
+  int act, S, M, c_real, wave_prio;
+  int tiles, across;   // pixel tiles in all, from left to right
+  int patch_w, patch;  // input pixels of a tile: a row of them, all
+  int phase, pitch;    // places between columns of a row that differ by one (mod stride), between rows
+  uint32_t mg_tiles, mg_across, mg_patch_w, mg_stride, mg_wo, mg_k;  // multipliers for division
+  int unused[7];
+};
+constexpr int kImageCols = 16;     // output pixels of a tile's row
+constexpr int kImagePatch = 864;   // places for the input pixels of a tile
+constexpr int kImageTaps = 512;    // and for its taps: of whole chunks and two more
+
 // The 3x3 depthwise convolution (pad 1) that conv_wave_dw_kernel computes on the fly in front of a 1x1 convolution; the
 // ConvArgs beside it describe that 1x1 convolution, except that ConvArgs::x is the DEPTHWISE layer's input tensor
 // [H][W][Cin] (ConvArgs::H, W stay the 1x1 convolution's own input size = the depthwise layer's output size).
@@ -164,6 +183,7 @@ struct KernelLaunch {
 struct KernelTable {
   const AqlKernel* conv[2][6][4] = {};  // [bf16][(tn - 1) * 3 + log2(nw) - 1][gather mode 0..3] (fp32: no mode 0)
   const AqlKernel* taps[2][6] = {};     // the same with one fetch of rows for three taps (gather mode 5)
+  const AqlKernel* image[2][2] = {};    // the network input in patches (gather mode 6): [bf16][128 pixels x 32 channels, 64 x 64]
   const AqlKernel* pair[2][6][3] = {};  // gather modes 0, 1, 3
   const AqlKernel* conv16[2][2][6] = {};  // 16-row tiles: [bf16][three taps per fetch][(tn - 1) * 3 + log2(nw) - 1]
   const AqlKernel* pair16[2][6] = {};

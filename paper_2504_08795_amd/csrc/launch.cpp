@@ -244,6 +244,7 @@ struct ConvDwArgs {  // conv_wave_dw_kernel(p, d)
   ConvArgs p;
   DwFusedArgs d;
 };
+static_assert(sizeof(ImageConvArgs) == sizeof(ConvArgs) && offsetof(ImageConvArgs, x) == kConvInputOffset, "one argument block for every convolution");
 constexpr uint32_t kIngestBytes = 28, kProbeBytes = 12, kPairBytes = 2 * sizeof(ConvArgs) + 4;
 static_assert(sizeof(DwFusedArgs) == 32 && sizeof(ConvDwArgs) == 192 && offsetof(ConvDwArgs, d) == sizeof(ConvArgs), "fused depthwise arguments");
 static_assert(sizeof(ConvArgs) == 160 && sizeof(DwArgs) == 72 && sizeof(PoolArgs) == 48 && sizeof(FcArgs) == 56 && sizeof(ReduceArgs) == 48 && sizeof(DwWindowArgs) == 88 && sizeof(PoolWindowArgs) == 64,
@@ -287,6 +288,7 @@ std::string KernelTable::resolve(const AqlRuntime& rt) {
       static const int pair_modes[3] = {0, 1, 3};
       for (int m = b ? 0 : 1; m < 3; ++m) pair[b][v][m] = get("daris::conv_wave_pair_kernel<" + tp + std::to_string(pair_modes[m]) + ">", kPairBytes);
     }
+    for (int v = 0; v < 2; ++v) image[b][v] = get("daris::conv_wave_kernel<" + B + ", " + std::to_string(v + 1) + ", 4, 6>", sizeof(ImageConvArgs));
     for (int v = 0; v < 6; ++v) {
       for (int t = 0; t < 2; ++t)
         conv16[b][t][v] = get("daris::conv_wave16_kernel<" + B + ", " + std::to_string(tn_[v]) + ", " + std::to_string(nw_[v]) + (t ? ", 5>" : ">"), sizeof(ConvArgs));
@@ -326,6 +328,32 @@ static bool taps_agree(const ConvPlan& pl, const ConvArgs& a) {
   return conv_three_taps(a.kh, a.stride, a.pad) && a.kw == a.kh && a.Ho == a.H && a.Wo == a.W && pl.S % 6 == 0 && pl.sz % 6 == 0 && pl.sw % 6 == 0;
 }
 
+// The first convolution through conv_image_body, or nothing if that cannot run it: the input pixels of a tile have to fit the patch
+// (kernels of 7 x 7 up to stride 2, 11 x 11 with stride 1; conv_wave_body gathers for the others), byte offsets into the output 31 bits.
+// Where it can it was the faster one at every size measured (conv_image_body), so there is no other rule.
+static bool push_image(const KernelTable& kt, const ConvPlan& pl, const ConvArgs& a, int bf16, std::vector<KernelLaunch>* out) {
+  if (a.stride > 64 || a.kh > 64 || a.kh != a.kw) return false;
+  const int nb = cdiv(a.Cout, 32), wn = nb % 2 ? 1 : 2;
+  const int rows = 8 / wn;
+  const int patch_w = (kImageCols - 1) * a.stride + a.kw;
+  const int phase = cdiv(patch_w, a.stride);
+  int pitch = phase * a.stride;  // made so that the two rows of a block lie in different banks
+  for (int i = 0; i < 32 && pitch * a.stride % 32 != 16; ++i) ++pitch;
+  const int64_t patch_h = (int64_t)(rows - 1) * a.stride + a.kh;
+  const int across = cdiv(a.Wo, kImageCols);
+  const int64_t tiles = (int64_t)across * cdiv(a.Ho, rows);
+  if (pl.splitk != 1 || a.res || patch_h * pitch > kImagePatch || pl.S * 2 + 16 > kImageTaps || (uint64_t)a.M * a.Cout * (bf16 ? 2 : 4) >= (1ull << 31)) return false;
+  if ((uint64_t)(a.M + 16 * (uint64_t)a.Wo) * a.Wo >= (1ull << 32) || (uint64_t)tiles * (nb / wn) * (uint64_t)tiles >= (1ull << 32)) return false;
+  ImageConvArgs m = ImageConvArgs();
+  m.x = a.x; m.w = a.w; m.bias = a.bias; m.y = a.y;
+  m.H = a.H; m.W = a.W; m.Ho = a.Ho; m.Wo = a.Wo; m.Cout = a.Cout; m.k = a.kh; m.stride = a.stride; m.pad = a.pad;
+  m.act = a.act; m.S = pl.S; m.M = a.M; m.c_real = a.c_real; m.wave_prio = a.wave_prio;
+  m.tiles = (int)tiles; m.across = across; m.patch_w = patch_w; m.patch = (int)patch_h * patch_w; m.phase = phase; m.pitch = pitch;
+  m.mg_tiles = div_magic((uint32_t)tiles); m.mg_across = div_magic((uint32_t)across); m.mg_patch_w = div_magic((uint32_t)patch_w);
+  m.mg_stride = div_magic((uint32_t)a.stride); m.mg_wo = div_magic((uint32_t)a.Wo); m.mg_k = div_magic((uint32_t)a.kw);
+  return push(out, kt.image[bf16][wn - 1], pl.kernel, (uint32_t)tiles * (uint32_t)(nb / wn), 256, &m, sizeof(m));
+}
+
 bool encode_conv(const KernelTable& kt, const ConvPlan& pl, const ConvArgs& a, int bf16, std::vector<KernelLaunch>* out) {
   if (pl.rows == 16) {
     const int v16 = pl.kernel - (bf16 ? K_CONV16_BF16_T1W2 : K_CONV16_F32_T1W2);
@@ -353,6 +381,7 @@ bool encode_conv(const KernelTable& kt, const ConvPlan& pl, const ConvArgs& a, i
   if (mode == 2 && (a.Cin != (bf16 ? 8 : 4) || a.c_real > 4 || (uint64_t)a.c_real * a.H * a.W * 4 >= (1ull << 31))) return false;
   if (pl.splitk > 1 && !a.ws) return false;
   if (pl.taps && (mode != 3 || !taps_agree(pl, a))) return false;
+  if (mode == 2 && push_image(kt, pl, a, bf16, out)) return true;
   if (!push(out, pl.taps ? kt.taps[bf16][variant] : kt.conv[bf16][variant][mode], pl.kernel, pl.grid_x, (uint32_t)pl.threads, &a, sizeof(a))) return false;
   return push_reduce(kt, pl, a, bf16, out);
 }

@@ -71,7 +71,7 @@ __device__ __forceinline__ Args args_at(ConstPtr src) {
 // looked at closely: nothing that can be measured, where a second comparison costs 0.05 us a launch.  `tile` = the wave's
 // partial tile in LDS, `words` floats a lane.
 template <int N, typename Acc>
-__device__ __forceinline__ void spoil_unless_in_range(const Acc (&acc)[N], float* const tile, const int words) {
+__device__ __forceinline__ bool out_of_range(const Acc (&acc)[N]) {
   constexpr int V = sizeof(Acc) / sizeof(float);
   float t[2] = {0.f, 0.f};
 #pragma unroll
@@ -81,11 +81,14 @@ __device__ __forceinline__ void spoil_unless_in_range(const Acc (&acc)[N], float
       t[(v >> 1) & 1] = __builtin_elementwise_maximum(__builtin_elementwise_maximum(__builtin_fabsf(acc[j][v]), __builtin_fabsf(acc[j][v + 1])), t[(v >> 1) & 1]);
   const float largest = __builtin_elementwise_maximum(t[0], t[1]);
   constexpr int kNanInfDenormal = 0x283;  // signalling and quiet NaN, positive denormal, +infinity
-  if (__builtin_expect(__ballot(__builtin_amdgcn_classf(largest * 0x1p-23f, kNanInfDenormal)) != 0, 0)) {
-    if (__ballot(!(largest < INFINITY)) != 0 || __ballot(largest >= 0x1p-103f) == 0) {
+  return __builtin_expect(__ballot(__builtin_amdgcn_classf(largest * 0x1p-23f, kNanInfDenormal)) != 0, 0) &&
+         (__ballot(!(largest < INFINITY)) != 0 || __ballot(largest >= 0x1p-103f) == 0);
+}
+template <int N, typename Acc>
+__device__ __forceinline__ void spoil_unless_in_range(const Acc (&acc)[N], float* const tile, const int words) {
+  if (out_of_range(acc)) {
 #pragma unroll 1
-      for (int i = 0; i < words; ++i) tile[64 * i + (threadIdx.x & 63)] = __builtin_nanf("");
-    }
+    for (int i = 0; i < words; ++i) tile[64 * i + (threadIdx.x & 63)] = __builtin_nanf("");
   }
 }
 __device__ __forceinline__ bool spoiled(const float v) { return __ballot(__builtin_isnan(v)) != 0; }
@@ -152,7 +155,12 @@ __device__ __forceinline__ void plain_products(const ConvArgs& p, const DwFusedA
           const int gk = c / 3 * CK, ky = fast_div(gk, p.mg_cin);
           k = (3 * ky + c % 3) * p.Cin + gk - ky * p.Cin;
         }
-        const float4 v = pixel_quad<MODE>(p, dwf, m0 + R * i + lane % R, k + 8 * (lane / R) + 4 * h);
+        int m = m0 + R * i + lane % R;
+        if constexpr (MODE == 6) {  // two rows of 16 pixels, the first at m0
+          const int x = m0 - fast_div(m0, p.mg_wo) * p.Wo + lane % 16;
+          m = x < p.Wo ? m0 + (2 * i + lane % R / 16) * p.Wo + lane % 16 : p.M;
+        }
+        const float4 v = pixel_quad<MODE == 6 ? 2 : MODE>(p, dwf, m, k + 8 * (lane / R) + 4 * h);
         a[i][4 * h] = v.x; a[i][4 * h + 1] = v.y; a[i][4 * h + 2] = v.z; a[i][4 * h + 3] = v.w;
       }
 #pragma unroll
@@ -1050,6 +1058,177 @@ __device__ __forceinline__ void conv_taps_body(const ConvArgs& p, const int mt, 
 template <int R, int TN, int NW>
 constexpr int conv_rows_lds() {  // floats of LDS
   return NW * 512 > NW * TN * R * R ? NW * 512 : NW * TN * R * R;
+}
+
+// ---- the network input in patches (gather mode 6) ---------------------------------------------------------------------------
+//
+// An input of up to four channels leaves a lane nothing to load but single values, eight plane loads a chunk of 16 k, and every input
+// pixel is wanted by k * k / stride^2 taps: the vector memory unit, twenty cycles for every load instruction of a CU, bounds the gather
+// of conv_wave_body.  Here a workgroup of four waves fetches the input pixels of its tile once, a load a plane, splits them into their
+// parts (bf16: rounds them) and keeps them in LDS as pixels of four channels, 8 bytes a part; the zeros outside the image come from
+// the buffer descriptor.  A lane reads a tap with one instruction a part, one chunk ahead of the matrix pipe.  The columns of a row lie
+// by their remainder by the stride, so that neighbouring output pixels read neighbouring places whatever the stride.  Where a tap lies is
+// looked up in a table that the workgroup makes while its pixels are on their way (the same in scalars, tap by tap, took as long as
+// the products).  K is not split: WN waves side by side own 32 channels each, 4 / WN below one another two rows of 16 pixels each, and
+// each walks all of K, in the order (tap, channel) of the packed weights, with DC chunks of weights in flight; taps past the last one
+// are a place of zeros.  Two blocks of pixels to a wave (a weight serves both) need so many registers that fewer workgroups hide
+// each other's waits: 6.1 us, 4.6, 6.0, 8.7 in place of the following.  us on 128 CUs, gather -> patches: 12544 x 64 x 7 x 7 with stride 2 fp32
+// 10.3 -> 5.8 (192 CUs 10.0 -> 5.7, 64 CUs 16.4 -> 8.4), bf16 7.2 -> 4.3; 50176 x 64 x 3 x 3 10.7 -> 6.4; 12544 x 32 x 3 x 3 with stride 2 3.5 -> 3.2;
+// 1024 x 16 x 3 x 3 3.05 -> 2.8.
+template <bool BF16>
+constexpr int conv_image_lds() {  // floats of LDS
+  constexpr int kPatch = (BF16 ? 1 : 3) * (kImagePatch + 1) * 2 + kImageTaps;
+  return kPatch > 4 * 1024 ? kPatch : 4 * 1024;
+}
+template <bool BF16, int WN>
+__device__ __forceinline__ void conv_image_body(const ImageConvArgs& p, const int L, float* const lds) {
+  constexpr int ES = BF16 ? 2 : 4, NP = BF16 ? 1 : 3, DC = BF16 ? 4 : 2;
+  constexpr int PLANE = kImagePatch + 1, ROUNDS = (kImagePatch + 255) / 256;
+  constexpr int kOutside = (int)0x80000000;  // an offset past the end of any tensor
+  if (p.wave_prio) __builtin_amdgcn_s_setprio(3);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int li = lane & 31, lh = lane >> 5;
+  const int g = fast_div(L, p.mg_tiles), tile = L - g * p.tiles;
+  const int ty = fast_div(tile, p.mg_across), x0 = (tile - ty * p.across) * kImageCols, y0 = ty * (8 / WN);
+  const int nb = g * WN + wave % WN, row0 = wave / WN * 2;  // the wave's channel block and its first row of the tile
+
+  const int plane = p.H * p.W * 4;
+  const auto irsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p.x), 0, p.c_real * plane, 0x00027000);
+  const int po1 = min(1, p.c_real - 1) * plane, po2 = min(2, p.c_real - 1) * plane;
+  auto by_stride = [&](int x) {  // (a select; a branch of its own for strides of one costs more)
+    const int q = (int)__umulhi((uint32_t)x, p.mg_stride);
+    return p.stride == 1 ? x : q;
+  };
+  uint4 px[ROUNDS];
+  int place[ROUNDS];
+#pragma unroll
+  for (int r = 0; r < ROUNDS; ++r) {
+    place[r] = 0;
+    px[r] = make_uint4(0u, 0u, 0u, 0u);
+    if (256 * r < p.patch) {
+      const int i = tid + 256 * r, y = (int)__umulhi((uint32_t)i, p.mg_patch_w), x = i - y * p.patch_w, iy = y0 * p.stride - p.pad + y, ix = x0 * p.stride - p.pad + x;
+      const int col = by_stride(x);
+      place[r] = y * p.pitch + (x - col * p.stride) * p.phase + col;
+      const int o = i < p.patch && (unsigned)iy < (unsigned)p.H && (unsigned)ix < (unsigned)p.W ? (iy * p.W + ix) * 4 : kOutside;
+      px[r].x = __builtin_amdgcn_raw_buffer_load_b32(irsrc, o, 0, 0);
+      px[r].y = __builtin_amdgcn_raw_buffer_load_b32(irsrc, o, po1, 0);  // (planes past the last one repeat it; their weights are zero)
+      px[r].z = __builtin_amdgcn_raw_buffer_load_b32(irsrc, o, po2, 0);
+      if (p.c_real > 3) px[r].w = __builtin_amdgcn_raw_buffer_load_b32(irsrc, o, 3 * plane, 0);
+    }
+  }
+  const int n = nb * 32 + 4 * lane % 32;  // first channel of the lane's quads
+  const auto brsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p.bias), 0, p.Cout * 4, 0x00027000);
+  const float4 bias = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(brsrc, n * 4, 0, 0));
+
+  const int chunks = BF16 ? p.S : p.S >> 1;  // of 16 k
+  const auto wrsrc = __builtin_amdgcn_make_buffer_rsrc((unsigned char*)const_cast<void*>(p.w) + (size_t)nb * chunks * (NP * 1024), 0, chunks * (NP * 1024), 0x00027000);
+  int woff = 0;
+  uint4 bw[DC][NP];
+  auto load = [&](int s) {
+#pragma unroll
+    for (int q = 0; q < NP; ++q) bw[s][q] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(wrsrc, lane * 16 + q * 1024, woff, 0));
+    woff += NP * 1024;
+  };
+
+  uint2* const st = reinterpret_cast<uint2*>(lds);
+  const int base = (row0 + li / 16) * p.stride * p.pitch + li % 16;  // place of the lane's pixel under the first tap
+  const int* const taps = reinterpret_cast<const int*>(lds + NP * PLANE * 2) + (BF16 ? lh : 2 * lh);
+  int tap = 0;
+  int2 o = make_int2(0, 0);  // places of the next chunk's taps
+  auto read_taps = [&]() {
+    if constexpr (BF16) o.x = taps[tap];
+    else o = *(const int2*)(taps + tap);
+    tap += BF16 ? 2 : 4;
+  };
+  uint4 next[NP];  // the next chunk's pixels
+  auto read = [&]() {
+    const int at = min(base + o.x, kImagePatch), bt = min(base + o.y, kImagePatch);
+#pragma unroll
+    for (int q = 0; q < NP; ++q) {
+      const uint2 u = st[q * PLANE + at], v = BF16 ? make_uint2(0u, 0u) : st[q * PLANE + bt];  // (bf16: eight k are one tap, the upper four zero)
+      next[q] = make_uint4(u.x, u.y, v.x, v.y);
+    }
+    read_taps();
+  };
+  f32x16 acc[1] = {f32x16(0.f)};
+  // All slots are filled before the patch is waited for (weights past the last chunk are zeros, and so are its taps), what the chunks
+  // leave over by DC goes through the last slots first, so that there is one end.
+  const int n_chunks = max(chunks, DC), lead = n_chunks % DC;
+  static_for<0, DC>([&](auto r) {
+    if (lead == r) static_for<0, DC>([&](auto i) { load((DC - r + i) % DC); });
+  });
+  if (tid < NP) st[tid * PLANE + kImagePatch] = make_uint2(0u, 0u);
+#pragma unroll
+  for (int t = tid; t < kImageTaps; t += 256) {
+    const int ky = fast_div(t, p.mg_k), kx = t - ky * p.k, col = by_stride(kx);
+    reinterpret_cast<int*>(lds + NP * PLANE * 2)[t] = ky < p.k ? ky * p.pitch + (kx - col * p.stride) * p.phase + col : kImagePatch;
+  }
+#pragma unroll
+  for (int r = 0; r < ROUNDS; ++r) {
+    if (tid + 256 * r < p.patch) {
+      if constexpr (BF16) {
+        st[place[r]] = make_uint2(pack_bf16_rne(__uint_as_float(px[r].x), __uint_as_float(px[r].y)), pack_bf16_rne(__uint_as_float(px[r].z), __uint_as_float(px[r].w)));
+      } else {
+        const Split4 v = split4(px[r]);
+#pragma unroll
+        for (int q = 0; q < NP; ++q) st[q * PLANE + place[r]] = v.p[q];
+      }
+    }
+  }
+  __syncthreads();
+  read_taps();
+  read();
+  auto step = [&](auto s, auto refill) {
+    uint4 pixels[NP];
+#pragma unroll
+    for (int q = 0; q < NP; ++q) pixels[q] = next[q];
+    read();
+    constexpr int PA[6] = {BF16 ? 0 : 2, 1, 0, 1, 0, 0}, PB[6] = {0, 1, 2, 0, 1, 0};
+#pragma unroll
+    for (int t = 0; t < (BF16 ? 1 : 6); ++t) acc[0] = mfma_bf16(pixels[PA[t]], bw[s][PB[t]], acc[0]);
+    __builtin_amdgcn_sched_barrier(0);  // the refill takes over the registers of the weights just used
+    if constexpr (refill) load(s);
+  };
+  auto refilled = [&](auto s) { step(s, std::true_type()); };
+  static_for<0, DC>([&](auto r) {
+    if (lead == r) static_for<DC - r, DC>(refilled);
+  });
+  for (int rounds = n_chunks / DC; rounds > 1; --rounds) static_for<0, DC>(refilled);
+  static_for<0, DC>([&](auto s) { step(s, std::false_type()); });
+  const int m0 = (y0 + row0) * p.Wo + x0;
+  if constexpr (!BF16) {
+    if (out_of_range(acc)) {
+      ConvArgs c = ConvArgs();
+      c.x = p.x; c.w = p.w; c.H = p.H; c.W = p.W; c.Cin = 4; c.Wo = p.Wo; c.kh = c.kw = p.k; c.stride = p.stride; c.pad = p.pad;
+      c.M = p.M; c.S = p.S; c.mg_wo = p.mg_wo; c.mg_kw = p.mg_k; c.c_real = p.c_real;
+      plain_products<6, 32, 1, 1>(c, DwFusedArgs(), m0, nb, 0, p.S, acc);
+    }
+  }
+  __syncthreads();  // the tiles go through the patch's LDS, each wave's through its own corner
+  float* const out = lds + wave * 1024;
+  const auto yrsrc = __builtin_amdgcn_make_buffer_rsrc(p.y, 0, p.M * p.Cout * ES, 0x00027000);
+#pragma unroll
+  for (int v = 0; v < 16; ++v) out[64 * v + lane] = acc[0][v];
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  float val[16];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const float4 v = *(const float4*)&out[4 * lane + 256 * r];
+    val[4 * r] = v.x + bias.x; val[4 * r + 1] = v.y + bias.y; val[4 * r + 2] = v.z + bias.z; val[4 * r + 3] = v.w + bias.w;
+  }
+  apply_act(val, p.act);
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int pixel = 8 * r + (lane >> 3 & 1) * 4 + (lane >> 4);  // of the block (as in WaveEpilogue)
+    const int y = y0 + row0 + pixel / 16, x = x0 + pixel % 16;
+    const int at = y < p.Ho && x < p.Wo && n < p.Cout ? ((y * p.Wo + x) * p.Cout + n) * ES : kOutside;
+    const float* const v = val + 4 * r;
+    if constexpr (BF16) put_at(yrsrc, at, make_uint2(pack_bf16_rne(v[0], v[1]), pack_bf16_rne(v[2], v[3])));
+    else put_at(yrsrc, at, make_uint4(__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3])));
+  }
 }
 
 // ---- pointwise layers: one thread per (output pixel, 16-byte channel vector) ----------------------------------------------

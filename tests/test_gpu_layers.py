@@ -95,6 +95,31 @@ def test_three_taps_from_one_fetch_of_rows(cin, h, w, cout, dtype):
 
 
 @pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("cin,h,w,cout,k,s,p", [
+    (3, 45, 61, 64, 7, 2, 3),      # last tiles partly outside, input rows of an odd length
+    (1, 16, 16, 32, 3, 1, 1),      # whole tiles, one channel plane
+    (2, 9, 200, 40, 1, 1, 0),      # a single tap, channels that end inside a block
+    (4, 37, 33, 96, 5, 2, 2),      # three channel blocks, no pad channel
+    (3, 30, 31, 24, 3, 3, 1),      # more places than the patch has: gathered tap by tap
+    (3, 61, 47, 64, 3, 3, 0),      # stride 3
+    (3, 17, 19, 128, 11, 1, 5),    # 121 taps
+    (3, 66, 70, 64, 11, 4, 2),     # gathered tap by tap
+])
+def test_network_input_in_patches(cin, h, w, cout, k, s, p, dtype):
+    """The first convolution reads the caller's layout; also with pixels so small that fp32 takes its tiles a second time (2^-110: every
+    sum is below 2^-103 of 1).  The error bars are relative to the largest sum, and so hold at both scales."""
+    L = N.Layer(op=N.OP_CONV, c_in=cin, c_out=cout, k=k, stride=s, pad=p, act=0, in_from=-1)
+    weights = [(rand_w(L)[0], np.zeros(cout, np.float32))]
+    x = RNG.normal(0, 1, (cin, h, w)).astype(np.float32)
+    with GpuNet([L], weights, (cin, h, w), dtype) as net:
+        for scale in (1.0, 2.0 ** -110):
+            xs = (x * np.float32(scale)).astype(np.float32)
+            got, want = np.asarray(net.forward(xs), np.float64) / scale, np.asarray(oracle_logits([L], weights, x, dtype), np.float64)
+            e_max, e_l2 = rel_err(got, want)
+            assert e_max <= LAYER_TOL[dtype] and e_l2 <= LAYER_TOL[dtype], (scale, e_max, e_l2)
+
+
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
 @pytest.mark.parametrize("cin,hw,cout,s", [(64, 28, 128, 2), (64, 14, 64, 1), (256, 7, 512, 2)])
 def test_conv_residual_block(cin, hw, cout, s, dtype):
     """downsample 1x1 (or identity) + 3x3 + 3x3 with residual add before ReLU: the basic-block epilogue."""
