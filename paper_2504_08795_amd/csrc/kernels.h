@@ -151,7 +151,7 @@ inline bool conv_three_taps(int k, int stride, int pad) { return k == 3 && strid
 // bf16 = 0/1.  Chooses tile shape, waves per workgroup and split-K from (M, N, Kpad), allow_block and the nominal partition
 // size (nominal_cus: how many CUs the grid is balanced for) only, so results do not depend on the partition a stage runs in.  step_align = 2 cuts K in whole chunks of two steps (for conv_rows_staged shapes), else 1.
 // cin_stride = the input tensor's channel stride: when it is a whole number of the 16-row kernel's K steps and the 32-row
-// plan would split K across workgroups, a 16-row plan that does not need to is chosen instead (cin_stride 0: never).
+// plan would split K across workgroups or leave half of the CUs idle, a 16-row plan is chosen instead (cin_stride 0: never).
 // allow_block = false: no 64-pixel tiles (a convolution that conv_block_takes refuses, shares its launch or computes its input on the fly);
 // three_taps: conv_three_taps and conv_rows_take hold.
 ConvPlan plan_conv(int M, int N, int Kpad, int bf16, int step_align, int cin_stride, int nominal_cus, bool allow_block, bool three_taps = false);

@@ -129,7 +129,7 @@ static ConvPlan plan_conv_wave(int M, int N, int Kpad, int bf16, int step_align,
 }
 
 // 16-pixel tiles of tn 16-channel blocks, K split among the waves of a workgroup only.  Chosen for layers whose 32-row
-// plan needs a reduction launch; returns kernel == K_NONE when a wave would walk more than 18 steps while the shape does not fill
+// plan needs a reduction launch or leaves the partition idle (plan_conv); returns kernel == K_NONE when a wave would walk more than 18 steps while the shape does not fill
 // three quarters of the nominal partition either, or when it is too shallow to split eight (four) ways.  Up to 18 steps the walk is
 // shorter than the reduction launch, however few the tiles.  us with 32-pixel tiles and a reduction -> with 16-pixel tiles, 64 tiles
 // (49 x 256) on 128 CUs and 128 tiles (49 x 512) on 192: fp32 of 8 steps 6.3 -> 4.0 and 6.5 -> 4.1, 16: 6.7 -> 5.3 and 7.0 -> 5.5, 18: 6.4 ->
@@ -199,7 +199,14 @@ ConvPlan plan_conv(int M, int N, int Kpad, int bf16, int step_align, int cin_str
   if (nominal_cus < 8) nominal_cus = 8;
   if (nominal_cus > 256) nominal_cus = 256;
   const ConvPlan pl = plan_conv_wave(M, N, Kpad, bf16, step_align, nominal_cus, allow_block, three_taps);
-  if (pl.splitk > 1 && cin_stride > 0 && cin_stride % (bf16 ? 32 : 16) == 0) {
+  // Besides the plans with a reduction, what leaves half of the partition idle: half the pixels a tile, half the serial work of a wave and
+  // its share of the launch.  us with 32-pixel tiles -> with 16, fp32 on 128 CUs: 196 x 64 x 384 (14 tiles) 3.63 -> 2.75, 196 x 96 x 576 (21)
+  // 4.26 -> 3.41, 49 x 160 x 576 4.21 -> 3.35, 784 x 32 x 192 (25) 2.95 -> 2.60, 49 x 960 x 160 (60) 3.10 -> 2.83; bf16 2.37 -> 2.13, 2.68 -> 2.39,
+  // 2.68 -> 2.32; 64 and 192 CUs alike.  Between half of the partition and all of it a short K gains (196 x 384 x 64, 84 tiles,
+  // 2.73 -> 2.35; 196 x 576 x 96, 126, 2.97 -> 2.80), a longer one does not (784 x 128 x 512, 100, 4.10 -> 4.42; 196 x 1024 x 256 3.99 -> 4.54).
+  // (A short K with a single channel tile stays: it can take the depthwise layer in front of it into its launch, or is a single tile.)
+  const bool idle = Kpad > 128 ? pl.tiles <= nominal_cus / 2 : pl.NTn > 1 && pl.tiles <= nominal_cus;
+  if ((pl.splitk > 1 || idle) && cin_stride > 0 && cin_stride % (bf16 ? 32 : 16) == 0) {
     const ConvPlan p16 = plan_conv_wave16(M, N, Kpad, bf16, nominal_cus, three_taps);
     if (p16.kernel != K_NONE) return p16;
   }

@@ -95,6 +95,31 @@ def test_three_taps_from_one_fetch_of_rows(cin, h, w, cout, dtype):
 
 
 @pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("cin,h,w,cout,rows", [
+    (192, 28, 28, 32, 16),    # a fifth of the partition's CUs with 32-pixel tiles
+    (64, 14, 14, 384, 16),    # a short K, two thirds of the CUs
+    (96, 13, 15, 576, 16),    # the same, ragged, 126 of 128 CUs
+    (64, 17, 17, 384, 16),    # ... 120 of 128
+    (64, 18, 18, 384, 32),    # ... and 132: one workgroup a CU no longer
+    (128, 3, 3, 20, 32),      # a short K, a single channel tile
+    (160, 7, 7, 960, 16),     # wide
+    (256, 14, 14, 1024, 32),  # a longer K, more than half of the CUs
+])
+def test_small_tiles_where_large_ones_leave_cus_idle(cin, h, w, cout, rows, dtype):
+    """1x1 convolutions on either side of the line between 16- and 32-pixel tiles, with a residual operand."""
+    layers = [N.Layer(op=N.OP_CONV, c_in=cin, c_out=cout, k=1, stride=1, pad=0, act=1, in_from=-1),
+              N.Layer(op=N.OP_CONV, c_in=cin, c_out=cout, k=1, stride=1, pad=0, act=1, in_from=-1, res_from=0)]
+    weights = [rand_w(L) for L in layers]
+    x = RNG.normal(0, 1, (cin, h, w)).astype(np.float32)
+    with GpuNet(layers, weights, (cin, h, w), dtype, flags=D.NO_PAIR) as net:
+        got = net.forward(x)
+        assert D.daris_get_launch_plan(net.task, 1)["rows"] == (rows if dtype == "fp32" or cin >= 128 else 32)    # (bf16: two waves have four steps between them at least)
+    e_max, e_l2 = rel_err(got, oracle_logits(layers, weights, x, dtype))
+    tol = {"fp32": 2e-5, "bf16": 1.2e-2}[dtype]  # two layers' sums; two bf16 roundings and a margin
+    assert e_max <= tol and e_l2 <= tol, (e_max, e_l2)
+
+
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
 @pytest.mark.parametrize("cin,h,w,cout,k,s,p", [
     (3, 45, 61, 64, 7, 2, 3),      # last tiles partly outside, input rows of an odd length
     (1, 16, 16, 32, 3, 1, 1),      # whole tiles, one channel plane
