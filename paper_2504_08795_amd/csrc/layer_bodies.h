@@ -644,7 +644,7 @@ __device__ __forceinline__ void conv_wave_body(const ConvArgs& p, const int mt, 
     int cch = sbeg * KS;  // first channel of the wave's next chunk (wave-uniform)
     uint4 xv[2][9], wv[9];
     float4 bv[VEC / 4];
-    auto dw_issue = [&]() {  // loads of the chunk at cch; past the end of the slice the last chunk of the tensor is read again (never used)
+    auto dw_issue = [&]() {  // loads of the chunk at cch (bf16 past the end of the slice: the last chunk of the tensor once more, never used)
       const int c = min(cch, p.Cin - 2 * KS) + piece * VEC;
 #pragma unroll
       for (int t = 0; t < 9; ++t) wv[t] = *(const uint4*)(dww + ((size_t)t * p.Cin + c) * ES);
@@ -675,20 +675,25 @@ __device__ __forceinline__ void conv_wave_body(const ConvArgs& p, const int mt, 
       for (int i = 0; i < VEC; ++i) acc[i] = apply_act(acc[i], dwf.act);
       return pack<BF16>(acc);
     };
-    auto chunk_dw = [&](int cs) {
+    // more: another chunk follows, whose operands travel while this one goes through the matrix pipe.  Past the last chunk fp32 requests
+    // nothing: 28 loads of the CU's vector memory unit that a wave of one to three chunks pays for (12544 x 16 x 32 6.2 -> 5.05 us, 3136 x
+    // 24 x 96 6.33 -> 6.27, 3136 x 24 x 144 7.05 -> 6.88 on 128 CUs).  bf16, whose chunks go in twos, takes 70 registers more that way.
+    auto chunk_dw = [&](int cs, bool more) {
 #pragma unroll
       for (int j = 0; j < 2; ++j) st[(16 * j + prow) * 5 + piece] = dw_value(j);
-      dw_issue();  // the next chunk's operands travel while this one goes through the matrix pipe
+      if (BF16 || more) dw_issue();
       exchange_and_mma(cs);
     };
-    dw_issue();
-    load_w_all();
+    if (BF16 || nchunks > 0) {
+      dw_issue();
+      load_w_all();
+    }
     int c = 0;
     for (; c + CS <= nchunks; c += CS) {
-      chunk_dw(0);
-      if constexpr (CS == 2) chunk_dw(1);
+      chunk_dw(0, c + 1 < nchunks);
+      if constexpr (CS == 2) chunk_dw(1, c + 2 < nchunks);
     }
-    if (CS == 2 && c < nchunks) chunk_dw(0);
+    if (CS == 2 && c < nchunks) chunk_dw(0, false);
     __syncthreads();  // the partial tiles below reuse the LDS of every wave's staging buffer
   }
 
