@@ -208,10 +208,9 @@ bool encode_conv_dw(const KernelTable& kt, const ConvPlan& pl, const ConvArgs& a
 // launch.  Measured on MobileNetV2's blocks: the producer re-reads the depthwise input up to nine times through one CU's
 // vector cache and pays a memory latency per chunk of 64 bytes of channels, so it can only win where the convolution has enough
 // workgroups to fill a partition and a single channel block (no repetition per block, few chunks per wave); elsewhere the
-// separate, fully parallel depthwise launch is faster (by 1.3 to 5 us per block).  There it saves a launch, and since both separate
-// launches have become faster it is about even.  us fused / both separate, fp32, the three blocks: 128 CUs 6.7 / 6.9, 6.7 / 6.7, 6.9 / 7.1
-// (frame 211.1 / 211.6); 192 CUs 5.6 / 6.4, 6.8 / 6.2, 6.9 / 6.6 (207.7 / 206.8); 96 CUs 8.9 / 7.7, 7.7 / 7.2, 7.7 / 7.9 (223.5 / 219.9); 64 CUs 11.4 / 9.2,
-// 7.7 / 8.1, 8.1 / 9.1 (237.3 / 236.1); bf16 on 128 CUs 5.8 / 6.2, 6.6 / 5.9 (181.7 / 180.9).
+// separate, fully parallel depthwise launch is faster (by 1.3 to 5 us per block).  There it saves a launch: MobileNetV2's kernels fused / with
+// the three blocks' layers in launches of their own, fp32 128 CUs 148.5 / 150.4 us, 192 CUs 145.4 / 146.0, 96 CUs 156.0 / 156.9, 64 CUs 172.6 /
+// 175.3; bf16 on 128 CUs 133.4 / 132.7 (two blocks).
 bool conv_dw_fusable(const ConvPlan& pl, int bf16);
 bool encode_dwconv(const KernelTable& kt, const DwArgs& a, int bf16, std::vector<KernelLaunch>* out);
 bool encode_maxpool(const KernelTable& kt, const PoolArgs& a, int bf16, std::vector<KernelLaunch>* out);

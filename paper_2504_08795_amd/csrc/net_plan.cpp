@@ -135,11 +135,9 @@ std::string build_plan(const daris_dnn& dnn, bool keep_activations, bool pair_la
     o.bytes = (size_t)o.H * o.W * o.Cs * es;
   }
   // Launch pairs (a residual block's first convolution and its shortcut convolution).  A pair saves one launch and its gap; the
-  // kernel for pairs has no 64 x 64 tiles, so a heavy member that has them gives them up.  us of the pair against the sum of both on
-  // their own, 128 CUs: ResNet-18 fp32 5.3 / 7.7, 5.6 / 7.9, 5.9 / 9.2, bf16 (192 CUs) 3.3 / 5.7, 3.9 / 6.4, 4.2 / 6.5; ResNet-50 bf16 3.9 / 6.9, 6.1 / 7.7,
-  // 4.9 / 7.1, 4.8 / 7.4, fp32 5.5 / 8.9, 12.0 / 12.7, 11.0 / 12.5, but 16.5 / 14.2 where the tiles are given up (3136 x 128 x 256); on 64 CUs,
-  // where three of its pairs give them up, 28.5 / 20.5, 22.9 / 17.7, 18.4 / 18.8 (10.4 / 13.5 where not).  Whole frames of ResNet-50 fp32 with pairs
-  // and without: 374 us / 379 on 128 CUs, 537 / 558 on 96 with plans for 128, 535 / 528 on 64.
+  // kernel for pairs has no 64 x 64 tiles, so a heavy member that has them gives them up.  All kernels of a network with
+  // pairs and without, on 128 CUs: ResNet-18 fp32 109.0 us / 115.5, bf16 (192 CUs) 62.9 / 68.4; ResNet-50 bf16 161.8 / 169.3, fp32 270.9 /
+  // 275.8, and on 64 CUs, where a heavy member gives its 64 x 64 tiles up, 427.0 / 433.9.
   for (int l = 0; l + 1 < n && pair_launches; ++l) {
     LayerPlan& A = net.layers[l];
     LayerPlan& B = net.layers[l + 1];
