@@ -1011,8 +1011,10 @@ __device__ __forceinline__ void conv_taps_body(const ConvArgs& p, const int mt, 
     const int place = row + (R == 16 && !BF16 ? HALF * (lh >> 1) : 0);
     return BF16 ? place * 4 + (lh ^ ((place >> 1) & 3)) : place * 2 + ((lh & 1) ^ ((place >> 2) & 1));
   };
+  // (Pixels past the last one are zeros: their neighbours in the image would have a say in whether the tile is in range.)
   const int m = m0 + li, x = m - fast_div(m, p.mg_wo) * p.Wo;
-  const int at[3] = {x == 0 ? row_at(kZeros) : row_at(li), row_at(li + 1), x == p.Wo - 1 ? row_at(kZeros) : row_at(li + 2)};
+  const int zeros = row_at(kZeros);
+  const int at[3] = {x == 0 || m >= p.M ? zeros : row_at(li), m >= p.M ? zeros : row_at(li + 1), x == p.Wo - 1 || m >= p.M ? zeros : row_at(li + 2)};
   // lanes exchange data through the wave's buffer: order the accesses of the whole wave, not only of each lane
   auto wave_order = [&]() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -1137,7 +1139,9 @@ __device__ __forceinline__ void conv_image_body(const ImageConvArgs& p, const in
   };
 
   uint2* const st = reinterpret_cast<uint2*>(lds);
-  const int base = (row0 + li / 16) * p.stride * p.pitch + li % 16;  // place of the lane's pixel under the first tap
+  // place of the lane's pixel under the first tap; outside the output that of the zeros, so that a pixel nobody stores has no say in
+  // whether the tile is in range
+  const int base = y0 + row0 + li / 16 < p.Ho && x0 + li % 16 < p.Wo ? (row0 + li / 16) * p.stride * p.pitch + li % 16 : kImagePatch;
   const int* const taps = reinterpret_cast<const int*>(lds + NP * PLANE * 2) + (BF16 ? lh : 2 * lh);
   int tap = 0;
   int2 o = make_int2(0, 0);  // places of the next chunk's taps
