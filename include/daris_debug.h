@@ -13,14 +13,19 @@ extern "C" {
 #endif
 
 /* Launch plan of one layer, for inspection and for host-side checks of what the kernels assume (no device needed).
- * Writes 27 values into out (host int64[cap >= 27]) and returns 27: [0] kernel id (daris_kernel_name), [1] 1 = dense
+ * Writes 28 values into out (host int64[cap >= 28]) and returns 28, or with cap = 27 the first 27 and returns 27: [0] kernel id (daris_kernel_name), [1] 1 = dense
  * convolution (the rest is meaningful only then), [2] pixels per wave tile (32, 64, or 16: then channel blocks are 16 wide too), [3] M = output
  * pixels, [4] N = output channels incl. padding, [5] K, [6] K padded, [7] channel blocks per wave tile, [8] waves
  * per workgroup, [9] K steps in total, [10] per workgroup slice, [11] per wave, [12] split-K factor, [13] pixel tiles,
  * [14] channel tiles, [15] weight groups, [16] workgroup order mode, [17..19] grid x y z, [20] threads per workgroup,
  * [21] split-K workspace bytes, [22] layer it shares a launch with or -1, [23] 1 = the joint launch is issued at this
  * layer, [24] activation slot of the layer's output (-1: the caller's logits), [25] slot of its input, [26] slot of its
- * residual operand or -1.  A slot is a device buffer shared by tensors whose lifetimes do not overlap. */
+ * residual operand or -1.  A slot is a device buffer shared by tensors whose lifetimes do not overlap.  [27] how the waves come by their
+ * pixels: 0 straight into registers, no K step straddles a filter tap, 1 the same for any channel count, 2 the network input as the
+ * caller gives it straight into registers, 3 whole 64-byte rows, 4 computed from the input of the depthwise layer that shares the
+ * launch, 5 rows fetched once for three taps (K in the order window row, channels of a chunk, window column), 6 the network input in patches: there a wave
+ * owns two rows of 16 pixels and one channel block over all of K, [13] counts the pixel tiles of workgroups (16 columns wide,
+ * 8 rows high, or 4 where a workgroup has two channel blocks side by side), [15] the workgroups beside one another. */
 int32_t daris_get_launch_plan(daris_task t, int layer, int64_t* out, int32_t cap);
 /* After daris_forward with DARIS_KEEP_ACTIVATIONS: copy layer l's output to host float[c][h][w]. */
 daris_status daris_read_layer(daris_task t, int layer, float* host_out, int64_t cap_elems);

@@ -195,12 +195,14 @@ def daris_get_stage_cuts(t):
 
 
 PLAN_FIELDS = ("kernel_id", "dense_conv", "rows", "M", "N", "K", "Kpad", "tn", "nw", "S", "sz", "sw", "splitk", "MT", "NTn", "G", "xmode",
-               "grid_x", "grid_y", "grid_z", "threads", "ws_bytes", "pair_with", "pair_lead", "out_slot", "in_slot", "res_slot")
+               "grid_x", "grid_y", "grid_z", "threads", "ws_bytes", "pair_with", "pair_lead", "out_slot", "in_slot", "res_slot", "gather")
+# values of "gather": how a convolution's waves come by their pixels
+GATHER_ALIGNED, GATHER_GENERAL, GATHER_INPUT, GATHER_ROWS, GATHER_DEPTHWISE, GATHER_TAPS, GATHER_IMAGE = range(7)
 
 
 def daris_get_launch_plan(t, layer):
-    buf = (C.c_int64 * 27)()
-    _chk(lib().daris_get_launch_plan(t, layer, buf, 27))
+    buf = (C.c_int64 * 28)()
+    _chk(lib().daris_get_launch_plan(t, layer, buf, 28))
     return dict(zip(PLAN_FIELDS, (int(v) for v in buf)))
 
 

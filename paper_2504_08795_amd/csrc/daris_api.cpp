@@ -1094,12 +1094,14 @@ int32_t daris_get_launch_plan(daris_task t, int layer, int64_t* out, int32_t cap
   const LayerPlan& L = net.layers[layer];
   const ConvPlan& c = L.cp;
   const bool conv = L.d.op == DARIS_OP_CONV && !L.depthwise;
-  const int64_t v[27] = {L.kernel_id, conv ? 1 : 0, conv ? c.rows : 0, (int64_t)L.out.H * L.out.W, L.out.Cs, L.K, L.Kpad,
+  const int64_t v[28] = {L.kernel_id, conv ? 1 : 0, conv ? c.rows : 0, (int64_t)L.out.H * L.out.W, L.out.Cs, L.K, L.Kpad,
                          c.tn, c.nw, c.S, c.sz, c.sw, c.splitk, c.MT, c.NTn, c.G, c.xmode, (int64_t)c.grid_x, 1, 1,
                          c.threads, (int64_t)c.ws_bytes, L.pair_with, L.pair_lead ? 1 : 0,
-                         L.out.slot, net.tensor(L.in_t).slot, L.res_t >= 0 ? net.tensor(L.res_t).slot : -1};
-  for (int i = 0; i < 27; ++i) out[i] = v[i];
-  return 27;
+                         L.out.slot, net.tensor(L.in_t).slot, L.res_t >= 0 ? net.tensor(L.res_t).slot : -1,
+                         L.fused_dw ? kGatherDepthwise : c.gather};
+  const int n = cap < 28 ? 27 : 28;
+  for (int i = 0; i < n; ++i) out[i] = v[i];
+  return n;
 }
 
 daris_status daris_set_afet(daris_task t, int stage, int64_t ns) {

@@ -22,9 +22,28 @@ enum KernelId : int32_t {
   // the same with 64 pixels x 64 channels per wave (fp32 layers of many tiles)
   K_CONV64_F32_T2W2, K_CONV64_F32_T2W4, K_CONV64_F32_T2W8,
   K_SPLITK_REDUCE, K_DWCONV, K_MAXPOOL, K_GAVGPOOL, K_FC, K_INGEST, K_EGRESS,
-  K_COUNT
+  // one fetch of rows for the three taps of a window's row: the tiles that plan_conv chooses it for, 32-, 16- and 64-pixel ones
+  K_TAPS_F32_T1W2, K_TAPS_F32_T1W4, K_TAPS_F32_T1W8, K_TAPS_F32_T2W2, K_TAPS_F32_T2W8,
+  K_TAPS_BF16_T1W2, K_TAPS_BF16_T1W4, K_TAPS_BF16_T2W2, K_TAPS_BF16_T2W4,
+  K_TAPS16_F32_T1W8, K_TAPS16_F32_T2W8, K_TAPS16_BF16_T1W4, K_TAPS16_BF16_T1W8, K_TAPS16_BF16_T2W4, K_TAPS16_BF16_T2W8,
+  K_TAPS64_F32_T2W2, K_TAPS64_F32_T2W4, K_TAPS64_F32_T2W8,
+  // the network input in patches: workgroups of one channel block, or of two
+  K_IMAGE_F32_N1, K_IMAGE_F32_N2, K_IMAGE_BF16_N1, K_IMAGE_BF16_N2,
+  K_COUNT  // at most 64: what a caller of daris_kernel_timing_read has to provide
 };
+static_assert(K_COUNT <= 64, "see daris_kernel_timing_read");
 const char* kernel_name(int32_t id);
+
+// How a convolution's waves come by their pixels.
+enum ConvGather : int {
+  kGatherAligned = 0,    // straight into registers, no K step straddles a filter tap (bf16)
+  kGatherGeneral = 1,    // straight into registers, any channel count
+  kGatherInput = 2,      // layer 0: the caller's fp32 [C][H][W] input, straight into registers
+  kGatherRows = 3,       // whole 64-byte rows, through LDS
+  kGatherDepthwise = 4,  // computed from the input of the depthwise layer in front
+  kGatherTaps = 5,       // whole 64-byte rows, each fetch for the three taps of a 3 x 3 window's row; K in the order (ky, channels of a chunk, kx)
+  kGatherImage = 6,      // layer 0: the caller's input, a patch per workgroup through LDS
+};
 
 constexpr uint32_t kNoMagic = 0xffffffffu;
 
@@ -123,7 +142,7 @@ struct ConvPlan {
   int tn, nw, S, sz, sw, MT, NTn, G, xmode;
   int step_align;                  // K slices are multiples of this many steps
   int staged;                      // the pixel operand may be fetched in whole 64-byte rows through LDS
-  int taps;                        // K in the order (ky, channels of a chunk, kx), one fetch of rows for three taps (conv_taps_body, conv_block_kernel)
+  int gather;                      // ConvGather (kGatherDepthwise never: that is a matter of the launch, LayerPlan::fused_dw)
   int tiles;                       // output tiles per grid.z slice
   size_t ws_bytes;                 // split-K workspace this launch needs
   uint32_t grid_x;                 // workgroups of the launch
@@ -153,11 +172,16 @@ inline bool conv_three_taps(int k, int stride, int pad) { return k == 3 && strid
 // cin_stride = the input tensor's channel stride: when it is a whole number of the 16-row kernel's K steps and the 32-row
 // plan would split K across workgroups or leave half of the CUs idle, a 16-row plan is chosen instead (cin_stride 0: never).
 // allow_block = false: no 64-pixel tiles (a convolution that conv_block_takes refuses, shares its launch or computes its input on the fly);
-// three_taps: conv_three_taps and conv_rows_take hold.
+// three_taps: conv_three_taps and conv_rows_take hold.  The plan's gather is kGatherTaps or kGatherRows; plan_gather settles the rest.
 ConvPlan plan_conv(int M, int N, int Kpad, int bf16, int step_align, int cin_stride, int nominal_cus, bool allow_block, bool three_taps = false);
 // Plan for a second convolution that is to share a launch with `first`: the same wave-tile kernel variant, K not split
 // across workgroups.  Returns a plan with kernel == K_NONE when that is not possible.
 ConvPlan plan_conv_like(const ConvPlan& first, int M, int N, int Kpad, int bf16, int step_align, int nominal_cus = 128);
+// Settles the gather of a plan without kGatherTaps; rows = conv_rows_take holds (for both members of a launch pair).
+void plan_gather(ConvPlan* pl, int cin_stride, bool rows, int bf16);
+// The first convolution of a network, whose plan reads the caller's input: turns it into one for conv_image_body, or leaves it
+// (kGatherInput) where that cannot run.
+void plan_input(ConvPlan* pl, int Ho, int Wo, int cout_stride, int k, int stride, int bf16);
 // Multiplier for fast_div: floor(2^32 / d) + 1, or 0 for d == 1.  Exact for every n >= 0 with n * d < 2^32.
 inline uint32_t div_magic(uint32_t d) { return d <= 1 ? 0u : (uint32_t)((1ull << 32) / d) + 1u; }
 // ... for the tile order of a convolution: the multiplier for division of a workgroup number by MT.
@@ -181,13 +205,13 @@ struct KernelLaunch {
 
 // Every kernel of the code object, looked up once.
 struct KernelTable {
-  const AqlKernel* conv[2][6][4] = {};  // [bf16][(tn - 1) * 3 + log2(nw) - 1][gather mode 0..3] (fp32: no mode 0)
-  const AqlKernel* taps[2][6] = {};     // the same with one fetch of rows for three taps (gather mode 5)
-  const AqlKernel* image[2][2] = {};    // the network input in patches (gather mode 6): [bf16][128 pixels x 32 channels, 64 x 64]
-  const AqlKernel* pair[2][6][3] = {};  // gather modes 0, 1, 3
-  const AqlKernel* conv16[2][2][6] = {};  // 16-row tiles: [bf16][three taps per fetch][(tn - 1) * 3 + log2(nw) - 1]
+  const AqlKernel* conv[2][6][4] = {};  // [bf16][(tn - 1) * 3 + log2(nw) - 1][gather 0..3] (fp32: no kGatherAligned)
+  const AqlKernel* taps[2][6] = {};     // the same with kGatherTaps, where there is a kernel id
+  const AqlKernel* image[2][2] = {};    // kGatherImage: [bf16][128 pixels x 32 channels, 64 x 64]
+  const AqlKernel* pair[2][6][3] = {};  // kGatherAligned, kGatherGeneral, kGatherRows
+  const AqlKernel* conv16[2][2][6] = {};  // 16-row tiles: [bf16][kGatherTaps][(tn - 1) * 3 + log2(nw) - 1]
   const AqlKernel* pair16[2][6] = {};
-  const AqlKernel* block[2][3] = {};    // 64-pixel tiles: [three taps per fetch][log2(nw) - 1]
+  const AqlKernel* block[2][3] = {};    // 64-pixel tiles: [kGatherTaps][log2(nw) - 1]
   const AqlKernel* convdw[2][6] = {};   // 1x1 convolution with a fused depthwise producer (fp32: tn = 1 only)
   const AqlKernel *reduce[2] = {}, *dwconv[2] = {}, *maxpool[2] = {}, *gavgpool[2] = {}, *fc[2] = {}, *ingest[2] = {}, *egress[2] = {};
   const AqlKernel *dwconv3[2] = {}, *maxpool_k[2][2] = {};  // 3x3 windows; 2x2 and 3x3 windows

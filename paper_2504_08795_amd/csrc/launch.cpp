@@ -17,11 +17,36 @@ static const char* const kNames[K_COUNT] = {
     "conv_wave16_f32_t1w2", "conv_wave16_f32_t1w4", "conv_wave16_f32_t1w8", "conv_wave16_f32_t2w2", "conv_wave16_f32_t2w4", "conv_wave16_f32_t2w8",
     "conv_wave16_bf16_t1w2", "conv_wave16_bf16_t1w4", "conv_wave16_bf16_t1w8", "conv_wave16_bf16_t2w2", "conv_wave16_bf16_t2w4", "conv_wave16_bf16_t2w8",
     "conv_wave64_f32_t2w2", "conv_wave64_f32_t2w4", "conv_wave64_f32_t2w8",
-    "splitk_reduce", "dwconv", "maxpool", "gavgpool", "fc", "ingest", "egress"};
+    "splitk_reduce", "dwconv", "maxpool", "gavgpool", "fc", "ingest", "egress",
+    "conv_wave_taps_f32_t1w2", "conv_wave_taps_f32_t1w4", "conv_wave_taps_f32_t1w8", "conv_wave_taps_f32_t2w2", "conv_wave_taps_f32_t2w8",
+    "conv_wave_taps_bf16_t1w2", "conv_wave_taps_bf16_t1w4", "conv_wave_taps_bf16_t2w2", "conv_wave_taps_bf16_t2w4",
+    "conv_wave16_taps_f32_t1w8", "conv_wave16_taps_f32_t2w8", "conv_wave16_taps_bf16_t1w4", "conv_wave16_taps_bf16_t1w8", "conv_wave16_taps_bf16_t2w4", "conv_wave16_taps_bf16_t2w8",
+    "conv_wave64_taps_f32_t2w2", "conv_wave64_taps_f32_t2w4", "conv_wave64_taps_f32_t2w8",
+    "conv_wave_image_f32_n1_t1w4", "conv_wave_image_f32_n2_t1w4", "conv_wave_image_bf16_n1_t1w4", "conv_wave_image_bf16_n2_t1w4"};
 
 const char* kernel_name(int32_t id) { return (id >= 0 && id < K_COUNT) ? kNames[id] : "?"; }
 
 static inline int cdiv(int a, int b) { return (a + b - 1) / b; }
+
+// Index of a tile variant in the tables of kernels.
+static int variant_of(int tn, int nw) { return (tn - 1) * 3 + (nw == 2 ? 0 : nw == 4 ? 1 : 2); }
+
+// The kernel that fetches rows once for three taps with a tile of `rows` pixels, or K_NONE: there is one for every tile and number of
+// waves that the planner arrives at for 3 x 3 windows over whole rows.
+static int32_t taps_kernel(int rows, int bf16, int tn, int nw) {
+  static const int32_t k32[2][6] = {{K_TAPS_F32_T1W2, K_TAPS_F32_T1W4, K_TAPS_F32_T1W8, K_TAPS_F32_T2W2, K_NONE, K_TAPS_F32_T2W8},
+                                    {K_TAPS_BF16_T1W2, K_TAPS_BF16_T1W4, K_NONE, K_TAPS_BF16_T2W2, K_TAPS_BF16_T2W4, K_NONE}};
+  static const int32_t k16[2][6] = {{K_NONE, K_NONE, K_TAPS16_F32_T1W8, K_NONE, K_NONE, K_TAPS16_F32_T2W8},
+                                    {K_NONE, K_TAPS16_BF16_T1W4, K_TAPS16_BF16_T1W8, K_NONE, K_TAPS16_BF16_T2W4, K_TAPS16_BF16_T2W8}};
+  const int v = variant_of(tn, nw);
+  return rows == 64 ? K_TAPS64_F32_T2W2 + v - 3 : rows == 16 ? k16[bf16][v] : k32[bf16][v];
+}
+// The kernel of a plan.
+static int32_t conv_kernel(int rows, int bf16, int tn, int nw, bool taps) {
+  if (taps) return taps_kernel(rows, bf16, tn, nw);
+  const int v = variant_of(tn, nw);
+  return rows == 64 ? K_CONV64_F32_T2W2 + v - 3 : rows == 16 ? (bf16 ? K_CONV16_BF16_T1W2 : K_CONV16_F32_T1W2) + v : (bf16 ? K_CONVW_BF16_T1W2 : K_CONVW_F32_T1W2) + v;
+}
 
 // Launches of equal workgroups run in ceil(workgroups / CUs) rounds: how many rounds' worth of time the grid needs per
 // round's worth of work.  1 = perfectly even; 98 workgroups on 96 CUs: 1.96.
@@ -93,7 +118,7 @@ static ConvPlan plan_conv_wave(int M, int N, int Kpad, int bf16, int step_align,
   }
   // K slices of workgroups and waves in whole multiples of step_align steps (2 when the kernel fetches the pixel
   // operand in chunks of two steps; S is then even as well; 6 when a fetch serves three chunks, where every wave gets one at least)
-  const bool taps = three_taps && staged && (block || S / 6 >= nw * z);
+  const bool taps = three_taps && staged && (block || S / 6 >= nw * z) && taps_kernel(block ? 64 : 32, bf16, tn, nw) != K_NONE;
   if (taps) step_align = 6;
   const int sz = cdiv(cdiv(S, z), step_align) * step_align;
   z = cdiv(S, sz);
@@ -105,7 +130,7 @@ static ConvPlan plan_conv_wave(int M, int N, int Kpad, int bf16, int step_align,
   pl.sw = cdiv(cdiv(sz, nw), step_align) * step_align;
   pl.step_align = step_align;
   pl.staged = staged;
-  pl.taps = taps;
+  pl.gather = taps ? kGatherTaps : kGatherRows;
   pl.splitk = z;
   pl.tiles = tiles;
   pl.threads = nw * 64;
@@ -123,8 +148,7 @@ static ConvPlan plan_conv_wave(int M, int N, int Kpad, int bf16, int step_align,
     pl.grid_x = (uint32_t)(pl.G * pl.MT);
   }
   pl.ws_bytes = z > 1 ? (size_t)z * M * N * sizeof(float) : 0;
-  const int wi = nw == 2 ? 0 : (nw == 4 ? 1 : 2);
-  pl.kernel = block ? K_CONV64_F32_T2W2 + wi : (bf16 ? K_CONVW_BF16_T1W2 : K_CONVW_F32_T1W2) + (tn - 1) * 3 + wi;
+  pl.kernel = conv_kernel(pl.rows, bf16, tn, nw, taps);
   return pl;
 }
 
@@ -169,8 +193,9 @@ static ConvPlan plan_conv_wave16(int M, int N, int Kpad, int bf16, int nominal_c
   pl.nw = nw;
   pl.S = S;
   pl.sz = S;
-  pl.taps = three_taps && S % 6 == 0 && S / 6 >= nw;
-  pl.step_align = pl.taps ? 6 : bf16 ? 1 : 2;
+  const bool taps = three_taps && S % 6 == 0 && S / 6 >= nw && taps_kernel(16, bf16, tn, nw) != K_NONE;
+  pl.gather = taps ? kGatherTaps : kGatherRows;
+  pl.step_align = taps ? 6 : bf16 ? 1 : 2;
   pl.sw = pl.step_align * cdiv(S / pl.step_align, nw);
   pl.staged = 1;
   pl.splitk = 1;
@@ -190,8 +215,7 @@ static ConvPlan plan_conv_wave16(int M, int N, int Kpad, int bf16, int nominal_c
     pl.grid_x = (uint32_t)(pl.G * pl.MT);
   }
   pl.ws_bytes = 0;
-  const int wi = nw == 2 ? 0 : (nw == 4 ? 1 : 2);
-  pl.kernel = (bf16 ? K_CONV16_BF16_T1W2 : K_CONV16_F32_T1W2) + (tn - 1) * 3 + wi;
+  pl.kernel = conv_kernel(16, bf16, tn, nw, taps);
   return pl;
 }
 
@@ -289,15 +313,15 @@ std::string KernelTable::resolve(const AqlRuntime& rt) {
     const std::string B = b ? "true" : "false";
     for (int v = 0; v < 6; ++v) {
       const std::string tp = B + ", " + std::to_string(tn_[v]) + ", " + std::to_string(nw_[v]) + ", ";
-      // (fp32 has no gather mode 0: what it would gain, a walk in scalars, mode 1 does in closed form for quads of channels)
-      taps[b][v] = get("daris::conv_wave_kernel<" + tp + "5>", sizeof(ConvArgs));
+      // (fp32 has no kGatherAligned: what it would gain, a walk in scalars, kGatherGeneral does in closed form for quads of channels)
+      if (taps_kernel(32, b, tn_[v], nw_[v]) != K_NONE) taps[b][v] = get("daris::conv_wave_kernel<" + tp + "5>", sizeof(ConvArgs));
       for (int m = b ? 0 : 1; m < 4; ++m) conv[b][v][m] = get("daris::conv_wave_kernel<" + tp + std::to_string(m) + ">", sizeof(ConvArgs));
       static const int pair_modes[3] = {0, 1, 3};
       for (int m = b ? 0 : 1; m < 3; ++m) pair[b][v][m] = get("daris::conv_wave_pair_kernel<" + tp + std::to_string(pair_modes[m]) + ">", kPairBytes);
     }
     for (int v = 0; v < 2; ++v) image[b][v] = get("daris::conv_wave_kernel<" + B + ", " + std::to_string(v + 1) + ", 4, 6>", sizeof(ImageConvArgs));
     for (int v = 0; v < 6; ++v) {
-      for (int t = 0; t < 2; ++t)
+      for (int t = 0; t < (taps_kernel(16, b, tn_[v], nw_[v]) != K_NONE ? 2 : 1); ++t)
         conv16[b][t][v] = get("daris::conv_wave16_kernel<" + B + ", " + std::to_string(tn_[v]) + ", " + std::to_string(nw_[v]) + (t ? ", 5>" : ">"), sizeof(ConvArgs));
       pair16[b][v] = get("daris::conv_wave16_pair_kernel<" + B + ", " + std::to_string(tn_[v]) + ", " + std::to_string(nw_[v]) + ">", kPairBytes);
       if (b ? nw_[v] != 8 : tn_[v] == 1)
@@ -335,62 +359,101 @@ static bool taps_agree(const ConvPlan& pl, const ConvArgs& a) {
   return conv_three_taps(a.kh, a.stride, a.pad) && a.kw == a.kh && a.Ho == a.H && a.Wo == a.W && pl.S % 6 == 0 && pl.sz % 6 == 0 && pl.sw % 6 == 0;
 }
 
-// The first convolution through conv_image_body, or nothing if that cannot run it: the input pixels of a tile have to fit the patch
-// (kernels of 7 x 7 up to stride 2, 11 x 11 with stride 1; conv_wave_body gathers for the others), byte offsets into the output 31 bits.
-// Where it can it was the faster one at every size measured (conv_image_body), so there is no other rule.
-static bool push_image(const KernelTable& kt, const ConvPlan& pl, const ConvArgs& a, int bf16, std::vector<KernelLaunch>* out) {
-  if (a.stride > 64 || a.kh > 64 || a.kh != a.kw) return false;
-  const int nb = cdiv(a.Cout, 32), wn = nb % 2 ? 1 : 2;
-  const int rows = 8 / wn;
-  const int patch_w = (kImageCols - 1) * a.stride + a.kw;
-  const int phase = cdiv(patch_w, a.stride);
-  int pitch = phase * a.stride;  // made so that the two rows of a block lie in different banks
-  for (int i = 0; i < 32 && pitch * a.stride % 32 != 16; ++i) ++pitch;
-  const int64_t patch_h = (int64_t)(rows - 1) * a.stride + a.kh;
-  const int across = cdiv(a.Wo, kImageCols);
-  const int64_t tiles = (int64_t)across * cdiv(a.Ho, rows);
-  if (pl.splitk != 1 || a.res || patch_h * pitch > kImagePatch || pl.S * 2 + 16 > kImageTaps || (uint64_t)a.M * a.Cout * (bf16 ? 2 : 4) >= (1ull << 31)) return false;
-  if ((uint64_t)(a.M + 16 * (uint64_t)a.Wo) * a.Wo >= (1ull << 32) || (uint64_t)tiles * (nb / wn) * (uint64_t)tiles >= (1ull << 32)) return false;
+// Tiles and LDS places of conv_image_body; ok: it can run the convolution.
+struct ImageTiles {
+  bool ok;
+  int nb, wn, rows, patch_w, phase, pitch, across;  // channel blocks, side by side in a workgroup, rows of a tile, see ImageConvArgs
+  int64_t patch_h, tiles;
+};
+// The input pixels of a tile have to fit the patch (kernels of 7 x 7 up to stride 2, 11 x 11 with stride 1), its taps the table, byte
+// offsets into the output 31 bits.
+static ImageTiles image_tiles(int Ho, int Wo, int cout_stride, int k, int stride, int S, int bf16) {
+  ImageTiles t = ImageTiles();
+  if (stride > 64 || k > 64) return t;
+  t.nb = cdiv(cout_stride, 32);
+  t.wn = t.nb % 2 ? 1 : 2;
+  t.rows = 8 / t.wn;
+  t.patch_w = (kImageCols - 1) * stride + k;
+  t.phase = cdiv(t.patch_w, stride);
+  t.pitch = t.phase * stride;  // made so that the two rows of a block lie in different banks
+  for (int i = 0; i < 32 && t.pitch * stride % 32 != 16; ++i) ++t.pitch;
+  t.patch_h = (int64_t)(t.rows - 1) * stride + k;
+  t.across = cdiv(Wo, kImageCols);
+  t.tiles = (int64_t)t.across * cdiv(Ho, t.rows);
+  const uint64_t M = (uint64_t)Ho * (uint64_t)Wo;
+  t.ok = t.patch_h * t.pitch <= kImagePatch && S * 2 + 16 <= kImageTaps && M * cout_stride * (bf16 ? 2 : 4) < (1ull << 31) && (M + 16 * (uint64_t)Wo) * Wo < (1ull << 32) &&
+         (uint64_t)t.tiles * (t.nb / t.wn) * (uint64_t)t.tiles < (1ull << 32);
+  return t;
+}
+
+// The patches take every first convolution that they can run and whose plan does not split K over workgroups: where both run
+// they were the faster at every size measured (conv_image_body).
+void plan_input(ConvPlan* pl, int Ho, int Wo, int cout_stride, int k, int stride, int bf16) {
+  pl->gather = kGatherInput;
+  const ImageTiles t = image_tiles(Ho, Wo, cout_stride, k, stride, pl->S, bf16);
+  if (pl->splitk != 1 || pl->rows != 32 || !t.ok) return;
+  pl->gather = kGatherImage;
+  pl->kernel = (bf16 ? K_IMAGE_BF16_N1 : K_IMAGE_F32_N1) + t.wn - 1;
+  pl->tn = 1;
+  pl->nw = 4;
+  pl->sz = pl->sw = pl->S;
+  pl->MT = (int)t.tiles;
+  pl->NTn = t.nb;
+  pl->G = t.nb / t.wn;
+  pl->xmode = 0;
+  pl->tiles = (int)t.tiles * pl->G;
+  pl->grid_x = (uint32_t)pl->tiles;
+  pl->threads = 256;
+}
+
+void plan_gather(ConvPlan* pl, int cin_stride, bool rows, int bf16) {
+  if (pl->gather == kGatherTaps) return;
+  pl->gather = pl->rows != 32 || (rows && pl->staged) ? kGatherRows : bf16 && cin_stride % 16 == 0 ? kGatherAligned : kGatherGeneral;
+}
+
+static bool encode_image(const KernelTable& kt, const ConvPlan& pl, const ConvArgs& a, int bf16, std::vector<KernelLaunch>* out) {
+  const ImageTiles t = image_tiles(a.Ho, a.Wo, a.Cout, a.kh, a.stride, pl.S, bf16);
+  if (!t.ok || a.kh != a.kw || a.res || pl.splitk != 1 || pl.rows != 32 || pl.tn != 1 || pl.threads != 256 || pl.kernel != (bf16 ? K_IMAGE_BF16_N1 : K_IMAGE_F32_N1) + t.wn - 1 ||
+      pl.grid_x != (uint64_t)t.tiles * (t.nb / t.wn))
+    return false;
   ImageConvArgs m = ImageConvArgs();
   m.x = a.x; m.w = a.w; m.bias = a.bias; m.y = a.y;
   m.H = a.H; m.W = a.W; m.Ho = a.Ho; m.Wo = a.Wo; m.Cout = a.Cout; m.k = a.kh; m.stride = a.stride; m.pad = a.pad;
   m.act = a.act; m.S = pl.S; m.M = a.M; m.c_real = a.c_real; m.wave_prio = a.wave_prio;
-  m.tiles = (int)tiles; m.across = across; m.patch_w = patch_w; m.patch = (int)patch_h * patch_w; m.phase = phase; m.pitch = pitch;
-  m.mg_tiles = div_magic((uint32_t)tiles); m.mg_across = div_magic((uint32_t)across); m.mg_patch_w = div_magic((uint32_t)patch_w);
+  m.tiles = (int)t.tiles; m.across = t.across; m.patch_w = t.patch_w; m.patch = (int)t.patch_h * t.patch_w; m.phase = t.phase; m.pitch = t.pitch;
+  m.mg_tiles = div_magic((uint32_t)t.tiles); m.mg_across = div_magic((uint32_t)t.across); m.mg_patch_w = div_magic((uint32_t)t.patch_w);
   m.mg_stride = div_magic((uint32_t)a.stride); m.mg_wo = div_magic((uint32_t)a.Wo); m.mg_k = div_magic((uint32_t)a.kw);
-  return push(out, kt.image[bf16][wn - 1], pl.kernel, (uint32_t)tiles * (uint32_t)(nb / wn), 256, &m, sizeof(m));
+  return push(out, kt.image[bf16][t.wn - 1], pl.kernel, pl.grid_x, (uint32_t)pl.threads, &m, sizeof(m));
 }
 
 bool encode_conv(const KernelTable& kt, const ConvPlan& pl, const ConvArgs& a, int bf16, std::vector<KernelLaunch>* out) {
+  if (pl.tn < 1 || pl.tn > 2 || (pl.nw != 2 && pl.nw != 4 && pl.nw != 8) || pl.threads != 64 * pl.nw) return false;
+  const bool input = pl.gather == kGatherInput || pl.gather == kGatherImage, taps = pl.gather == kGatherTaps;
+  if (input != (a.c_real > 0)) return false;
+  if (input && (a.Cin != (bf16 ? 8 : 4) || a.c_real > 4 || (uint64_t)a.c_real * a.H * a.W * 4 >= (1ull << 31))) return false;
+  if (pl.gather == kGatherImage) return encode_image(kt, pl, a, bf16, out);
+  if (pl.kernel != conv_kernel(pl.rows, bf16, pl.tn, pl.nw, taps)) return false;
+  if ((pl.splitk > 1 && !a.ws) || (taps && !taps_agree(pl, a))) return false;
+  const int v = variant_of(pl.tn, pl.nw);
+  const AqlKernel* kernel;
   if (pl.rows == 16) {
-    const int v16 = pl.kernel - (bf16 ? K_CONV16_BF16_T1W2 : K_CONV16_F32_T1W2);
     const int ks16 = bf16 ? 32 : 16;
-    if (v16 < 0 || v16 >= 6 || pl.threads != 64 * pl.nw || !rows_take(a, bf16) || a.Kpad % 32 || pl.S * ks16 != a.Kpad || pl.sw % pl.step_align) return false;
-    if ((pl.splitk > 1 && !a.ws) || (pl.taps && !taps_agree(pl, a))) return false;
-    if (!push(out, kt.conv16[bf16][pl.taps][v16], pl.kernel, pl.grid_x, (uint32_t)pl.threads, &a, sizeof(a))) return false;
-    return push_reduce(kt, pl, a, bf16, out);
+    if ((pl.gather != kGatherRows && !taps) || !rows_take(a, bf16) || a.Kpad % 32 || pl.S * ks16 != a.Kpad || pl.sw % pl.step_align) return false;
+    kernel = kt.conv16[bf16][taps][v];
+  } else if (pl.rows == 64) {
+    // what the kernel assumes: whole 64-byte rows, one bit per filter tap, byte offsets that fit 32 bits, K in whole chunks
+    if ((pl.gather != kGatherRows && !taps) || bf16 || !pl.staged || pl.tn != 2 || pl.S % 2 || pl.sz % 2 || pl.sw % 2) return false;
+    if (a.kh != a.kw || !conv_block_takes(a.H, a.W, a.Cin, a.kh, a.pad, a.Kpad)) return false;
+    kernel = kt.block[taps][v - 3];
+  } else {
+    const bool rows = pl.gather == kGatherRows || taps;
+    if (pl.rows != 32 || pl.gather == kGatherDepthwise) return false;
+    if (rows && (!pl.staged || !rows_take(a, bf16))) return false;
+    if (pl.gather == kGatherAligned && (!bf16 || a.Cin % 16)) return false;
+    if ((rows || !bf16) && (pl.S % 2 || pl.sz % 2 || pl.sw % 2)) return false;
+    kernel = taps ? kt.taps[bf16][v] : kt.conv[bf16][v][pl.gather];
   }
-  if (pl.rows == 64) {
-    // what conv_block_kernel assumes: whole 64-byte rows, K cut in chunks of two steps, and the limits of conv_block_takes
-    const int v64 = pl.kernel - K_CONV64_F32_T2W2;
-    if (v64 < 0 || v64 >= 3 || pl.threads != 64 * pl.nw || bf16 || a.c_real > 0 || !pl.staged || pl.tn != 2 || pl.S % 2 || pl.sz % 2 || pl.sw % 2) return false;
-    if (a.kh != a.kw || !conv_block_takes(a.H, a.W, a.Cin, a.kh, a.pad, a.Kpad) || (pl.splitk > 1 && !a.ws)) return false;
-    if (pl.taps && !taps_agree(pl, a)) return false;
-    if (!push(out, kt.block[pl.taps][v64], pl.kernel, pl.grid_x, (uint32_t)pl.threads, &a, sizeof(a))) return false;
-    return push_reduce(kt, pl, a, bf16, out);
-  }
-  const int variant = pl.kernel - (bf16 ? K_CONVW_BF16_T1W2 : K_CONVW_F32_T1W2);
-  if (variant < 0 || variant >= 6 || pl.rows != 32 || pl.threads != 64 * pl.nw) return false;
-  // 0: a K step never straddles a filter tap (bf16); 1: general walk; 2: layer 0 reading the caller's fp32 [C][H][W] input;
-  // 3: a pixel's channels are whole 64-byte rows and the plan cuts K in chunks of two steps: pixel operand through LDS
-  const int mode = a.c_real > 0 ? 2 : (rows_take(a, bf16) && pl.staged ? 3 : (bf16 && a.Cin % 16 == 0 ? 0 : 1));
-  if ((mode == 3 || !bf16) && (pl.S % 2 || pl.sz % 2 || pl.sw % 2)) return false;
-  if (mode == 2 && (a.Cin != (bf16 ? 8 : 4) || a.c_real > 4 || (uint64_t)a.c_real * a.H * a.W * 4 >= (1ull << 31))) return false;
-  if (pl.splitk > 1 && !a.ws) return false;
-  if (pl.taps && (mode != 3 || !taps_agree(pl, a))) return false;
-  if (mode == 2 && push_image(kt, pl, a, bf16, out)) return true;
-  if (!push(out, pl.taps ? kt.taps[bf16][variant] : kt.conv[bf16][variant][mode], pl.kernel, pl.grid_x, (uint32_t)pl.threads, &a, sizeof(a))) return false;
-  return push_reduce(kt, pl, a, bf16, out);
+  return push(out, kernel, pl.kernel, pl.grid_x, (uint32_t)pl.threads, &a, sizeof(a)) && push_reduce(kt, pl, a, bf16, out);
 }
 
 bool conv_dw_fusable(const ConvPlan& pl, int bf16) {
@@ -420,32 +483,32 @@ bool encode_conv_dw(const KernelTable& kt, const ConvPlan& pl, const ConvArgs& a
 
 bool encode_conv_pair(const KernelTable& kt, const ConvPlan& pl0, const ConvArgs& a0, const ConvPlan& pl1, const ConvArgs& a1, int bf16,
                       std::vector<KernelLaunch>* out) {
+  if (pl0.kernel != pl1.kernel || pl0.rows != pl1.rows || pl0.gather != pl1.gather || pl0.tn != pl1.tn || pl0.nw != pl1.nw || pl0.threads != 64 * pl0.nw || pl1.splitk != 1 || a0.c_real > 0 ||
+      a1.c_real > 0 || pl0.rows == 64 || pl0.kernel != conv_kernel(pl0.rows, bf16, pl0.tn, pl0.nw, false))
+    return false;
+  const int v = variant_of(pl0.tn, pl0.nw);
+  const AqlKernel* kernel;
   if (pl0.rows == 16) {
     const int ks16 = bf16 ? 32 : 16;
-    const int v16 = pl0.kernel - (bf16 ? K_CONV16_BF16_T1W2 : K_CONV16_F32_T1W2);
-    if (pl0.taps || pl1.taps || pl1.rows != 16 || pl0.kernel != pl1.kernel || v16 < 0 || v16 >= 6 || pl0.splitk != 1 || pl1.splitk != 1 || !rows_take(a0, bf16) || !rows_take(a1, bf16) ||
-        a0.Kpad % 32 || a1.Kpad % 32 || pl0.sw % pl0.step_align || pl1.sw % pl1.step_align || pl0.S * ks16 != a0.Kpad || pl1.S * ks16 != a1.Kpad)
+    if (pl0.gather != kGatherRows || pl0.splitk != 1 || !rows_take(a0, bf16) || !rows_take(a1, bf16) || a0.Kpad % 32 || a1.Kpad % 32 || pl0.sw % pl0.step_align || pl1.sw % pl1.step_align ||
+        pl0.S * ks16 != a0.Kpad || pl1.S * ks16 != a1.Kpad)
       return false;
-    PairArgs pa;
-    std::memset(&pa, 0, sizeof(pa));
-    pa.p0 = a0;
-    pa.p1 = a1;
-    pa.n0 = (int)((pl0.grid_x + 7) / 8 * 8);
-    return push(out, kt.pair16[bf16][v16], pl0.kernel, (uint32_t)pa.n0 + pl1.grid_x, (uint32_t)pl0.threads, &pa, kPairBytes);
+    kernel = kt.pair16[bf16][v];
+  } else {
+    const bool rows = pl0.gather == kGatherRows;
+    if (rows && (!rows_take(a0, bf16) || !rows_take(a1, bf16) || !pl0.staged || !pl1.staged)) return false;
+    if (pl0.gather == kGatherAligned && (!bf16 || a0.Cin % 16 || a1.Cin % 16)) return false;
+    if (!rows && pl0.gather != kGatherAligned && pl0.gather != kGatherGeneral) return false;
+    if ((rows || !bf16) && (pl0.S % 2 || pl0.sz % 2 || pl0.sw % 2 || pl1.S % 2 || pl1.sz % 2 || pl1.sw % 2)) return false;
+    if (pl0.splitk > 1 && !a0.ws) return false;
+    kernel = kt.pair[bf16][v][rows ? 2 : pl0.gather];
   }
-  const bool aligned = bf16 && a0.Cin % 16 == 0;
-  if (pl0.taps || pl1.taps || pl0.kernel != pl1.kernel || pl0.rows != 32 || pl1.rows != 32 || aligned != (bf16 && a1.Cin % 16 == 0) || pl1.splitk != 1 || a0.c_real > 0 || a1.c_real > 0) return false;
-  const bool staged = rows_take(a0, bf16) && rows_take(a1, bf16) && pl0.staged && pl1.staged;
-  if ((staged || !bf16) && (pl0.S % 2 || pl0.sz % 2 || pl0.sw % 2 || pl1.S % 2 || pl1.sz % 2 || pl1.sw % 2)) return false;
-  const int variant = pl0.kernel - (bf16 ? K_CONVW_BF16_T1W2 : K_CONVW_F32_T1W2);
-  if (variant < 0 || variant >= 6 || (pl0.splitk > 1 && !a0.ws)) return false;
   PairArgs pa;
   std::memset(&pa, 0, sizeof(pa));
   pa.p0 = a0;
   pa.p1 = a1;
   pa.n0 = (int)((pl0.grid_x + 7) / 8 * 8);  // the second problem starts at a multiple of 8: its workgroup -> XCD relation is kept
-  if (!push(out, kt.pair[bf16][variant][staged ? 2 : (aligned ? 0 : 1)], pl0.kernel, (uint32_t)pa.n0 + pl1.grid_x, (uint32_t)pl0.threads, &pa, kPairBytes)) return false;
-  return push_reduce(kt, pl0, a0, bf16, out);
+  return push(out, kernel, pl0.kernel, (uint32_t)pa.n0 + pl1.grid_x, (uint32_t)pl0.threads, &pa, kPairBytes) && push_reduce(kt, pl0, a0, bf16, out);
 }
 
 // Grid and place finding of a window kernel (point_of): workgroups in multiples of 8, one band of them per XCD.

@@ -90,7 +90,6 @@ std::string build_plan(const daris_dnn& dnn, bool keep_activations, bool pair_la
           L.cp = plan_conv(o.H * o.W, o.Cs, L.Kpad, net.bf16, staged_rows && conv_rows_staged(in.Cs, net.bf16) ? 2 : 1, small_tile_stride(L), plan_cus,
                            conv_block_takes(in.H, in.W, in.Cs, d.k, d.pad, L.Kpad),
                            staged_rows && conv_three_taps(d.k, d.stride, d.pad) && conv_rows_take(in.H, in.W, in.Cs, (uint64_t)o.H * (uint64_t)o.W, o.Cs, L.Kpad, net.bf16));
-          L.kernel_id = L.cp.kernel;
           net.ws_bytes = std::max(net.ws_bytes, L.cp.ws_bytes);
         } else {
           L.kernel_id = K_DWCONV;
@@ -147,7 +146,7 @@ std::string build_plan(const daris_dnn& dnn, bool keep_activations, bool pair_la
     LayerPlan& light = A.macs > B.macs ? B : A;
     const ConvPlan own = heavy.cp;
     const int sa = staged_rows && conv_rows_staged(net.tensor(heavy.in_t).Cs, net.bf16) ? 2 : 1;
-    if (heavy.cp.rows == 64 || heavy.cp.taps)  // (kernels that have no form for two problems)
+    if (heavy.cp.rows == 64 || heavy.cp.gather == kGatherTaps)  // (kernels that have no form for two problems)
       heavy.cp = plan_conv(heavy.out.H * heavy.out.W, heavy.out.Cs, heavy.Kpad, net.bf16, sa, small_tile_stride(heavy), plan_cus, false);
     const ConvPlan like = plan_conv_like(heavy.cp, light.out.H * light.out.W, light.out.Cs, light.Kpad, net.bf16,
                                          staged_rows && conv_rows_staged(net.tensor(light.in_t).Cs, net.bf16) ? 2 : 1, plan_cus);
@@ -155,10 +154,8 @@ std::string build_plan(const daris_dnn& dnn, bool keep_activations, bool pair_la
       heavy.cp = own;
       continue;
     }
-    heavy.kernel_id = heavy.cp.kernel;
     net.ws_bytes = std::max(net.ws_bytes, heavy.cp.ws_bytes);
     light.cp = like;
-    light.kernel_id = like.kernel;
     A.pair_with = l + 1;
     B.pair_with = l;
     B.pair_lead = true;
@@ -179,7 +176,6 @@ std::string build_plan(const daris_dnn& dnn, bool keep_activations, bool pair_la
       cp = plan_conv(B.out.H * B.out.W, B.out.Cs, B.Kpad, net.bf16, 2, 0, plan_cus, false);
     if (!conv_dw_fusable(cp, net.bf16)) continue;  // the separate launch is faster (or no such kernel variant)
     B.cp = cp;
-    B.kernel_id = cp.kernel;
     net.ws_bytes = std::max(net.ws_bytes, cp.ws_bytes);
     A.pair_with = l + 1;
     B.pair_with = l;
@@ -197,6 +193,19 @@ std::string build_plan(const daris_dnn& dnn, bool keep_activations, bool pair_la
       if (net.layers[l].in_t == 0 || net.layers[l].res_t == 0) only_reader = false;
     net.fuse_ingest = !keep_activations && fuse_ingest && (uint64_t)dnn.in_c * dnn.in_h * dnn.in_w * 4 < (1ull << 31) && L0.d.op == DARIS_OP_CONV && !L0.depthwise &&
                       L0.in_t == 0 && L0.res_t < 0 && L0.pair_with < 0 && only_reader && net.ingest.Cs == vec && dnn.in_c <= 4;
+  }
+  // how each dense convolution comes by its pixels, which the layers' links decide too
+  auto rows_taken = [&](const LayerPlan& L) {
+    const TensorInfo& in = net.tensor(L.in_t);
+    return conv_rows_take(in.H, in.W, in.Cs, (uint64_t)L.out.H * (uint64_t)L.out.W, L.out.Cs, L.Kpad, net.bf16);
+  };
+  for (int l = 0; l < n; ++l) {
+    LayerPlan& L = net.layers[l];
+    if (L.d.op != DARIS_OP_CONV || L.depthwise) continue;
+    const bool joint = L.pair_with >= 0 && !net.layers[L.pair_with].depthwise;
+    if (l == 0 && net.fuse_ingest) plan_input(&L.cp, L.out.H, L.out.W, L.out.Cs, L.d.k, L.d.stride, net.bf16);
+    else plan_gather(&L.cp, net.tensor(L.in_t).Cs, rows_taken(L) && (!joint || (rows_taken(net.layers[L.pair_with]) && net.layers[L.pair_with].cp.staged)), net.bf16);
+    L.kernel_id = L.cp.kernel;
   }
   const TensorInfo& fin = net.layers[n - 1].out;
   net.n_out = fin.C * fin.H * fin.W;
@@ -311,7 +320,7 @@ void pack_conv(const NetPlan& net, const LayerPlan& L, const float* w, const flo
   // Where weight (tap t, channel ci) lies along K: tap by tap, or, where a fetch of rows serves three taps, chunk by chunk in the order
   // (ky, channels of a chunk, kx)
   const int per_chunk = (L.cp.rows == 16 ? 128 : 64) / (int)es;
-  auto k_of = [&](int t, int ci) { return L.cp.taps ? ((t / 3 * (in.Cs / per_chunk) + ci / per_chunk) * 3 + t % 3) * per_chunk + ci % per_chunk : t * in.Cs + ci; };
+  auto k_of = [&](int t, int ci) { return L.cp.gather == kGatherTaps ? ((t / 3 * (in.Cs / per_chunk) + ci / per_chunk) * 3 + t % 3) * per_chunk + ci % per_chunk : t * in.Cs + ci; };
   if (!bf) {
     // fp32: three bf16 parts per weight (see split8 in device_common.h), [channel block of R][chunk][part][lane = i + R q][8],
     // element e of lane (i, q) in chunk s is W[n = R nb + i][k = s * CK + 8 q + e]; a chunk is what one matrix instruction

@@ -29,14 +29,18 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 4 : 1) void conv_wave16_kernel(c
   puts_done();
 }
 
-#define DARIS_INST_TAPS(B, T, W)                                         \
-  template __global__ void conv_wave_kernel<B, T, W, 5>(const ConvArgs); \
-  template __global__ void conv_wave16_kernel<B, T, W, 5>(const ConvArgs);
-#define DARIS_INST_TAPS_ALL(B) \
-  DARIS_INST_TAPS(B, 1, 2) DARIS_INST_TAPS(B, 1, 4) DARIS_INST_TAPS(B, 1, 8) DARIS_INST_TAPS(B, 2, 2) DARIS_INST_TAPS(B, 2, 4) DARIS_INST_TAPS(B, 2, 8)
-DARIS_INST_TAPS_ALL(false)
-DARIS_INST_TAPS_ALL(true)
-#undef DARIS_INST_TAPS_ALL
+// The tiles and numbers of waves that the planner arrives at (taps_kernel in launch.cpp).  For 32 pixels these are two, four or eight in fp32 (not
+// four with 64 channels: what would have them has too few groups of taps, or 64 x 64 tiles), two or four in bf16; for 16 pixels
+// eight in fp32, four or eight in bf16.
+#define DARIS_INST_TAPS(B, T, W) template __global__ void conv_wave_kernel<B, T, W, 5>(const ConvArgs);
+#define DARIS_INST_TAPS16(B, W) \
+  template __global__ void conv_wave16_kernel<B, 1, W, 5>(const ConvArgs); \
+  template __global__ void conv_wave16_kernel<B, 2, W, 5>(const ConvArgs);
+DARIS_INST_TAPS(false, 1, 2) DARIS_INST_TAPS(false, 1, 4) DARIS_INST_TAPS(false, 1, 8) DARIS_INST_TAPS(false, 2, 2) DARIS_INST_TAPS(false, 2, 8)
+DARIS_INST_TAPS(true, 1, 2) DARIS_INST_TAPS(true, 1, 4) DARIS_INST_TAPS(true, 2, 2) DARIS_INST_TAPS(true, 2, 4)
+DARIS_INST_TAPS16(false, 8)
+DARIS_INST_TAPS16(true, 4) DARIS_INST_TAPS16(true, 8)
+#undef DARIS_INST_TAPS16
 #undef DARIS_INST_TAPS
 
 }  // namespace daris

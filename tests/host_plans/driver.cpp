@@ -2,7 +2,8 @@
 // encoders (net_plan.cpp, launch.cpp) against a kernel table without a device, so that a plan which its own encoder refuses is
 // found on the CPU.
 // Line: DTYPE(0 fp32, 1 bf16) C_IN H W C_OUT K STRIDE PAD PLAN_CUS, and of the second convolution C_OUT (0: none) K STRIDE PAD.
-// Answer, of the first convolution: ENCODED KERNEL_ID PIXELS_PER_WAVE THREADS SPLIT_K SHARES_A_LAUNCH; or -1 and why not.
+// Answer, of the first convolution: ENCODED KERNEL_ID PIXELS_PER_WAVE THREADS SPLIT_K SHARES_A_LAUNCH GATHER K_STEPS STEPS_OF_A_WORKGROUP STEPS_OF_A_WAVE WORKGROUPS,
+// and what its launch has: KERNEL_ID WORKGROUPS THREADS; or -1 and why not.
 #include <cstdio>
 #include <cstring>
 #include <string>
@@ -77,7 +78,9 @@ int main() {
     bool ok;
     if (pair) ok = B.macs >= A.macs ? encode_conv_pair(kt, B.cp, a[1], A.cp, a[0], net.bf16, &out) : encode_conv_pair(kt, A.cp, a[0], B.cp, a[1], net.bf16, &out);
     else ok = encode_conv(kt, A.cp, a[0], net.bf16, &out) && (d.n_layers == 1 || encode_conv(kt, B.cp, a[1], net.bf16, &out));
-    std::printf("%d %d %d %d %d %d\n", ok ? 1 : 0, A.cp.kernel, A.cp.rows, A.cp.threads, A.cp.splitk, pair ? 1 : 0);
+    const KernelLaunch first = out.empty() ? KernelLaunch() : out[0];
+    std::printf("%d %d %d %d %d %d %d %d %d %d %u %d %u %u\n", ok ? 1 : 0, A.cp.kernel, A.cp.rows, A.cp.threads, A.cp.splitk, pair ? 1 : 0, A.cp.gather, A.cp.S, A.cp.sz, A.cp.sw, A.cp.grid_x,
+                first.kernel_id, first.groups, first.threads);
   }
   return 0;
 }

@@ -64,10 +64,10 @@ int main(int argc, char** argv) {
       for (int j = 0; j < n; ++j) std::printf(" %d", cuts[j]);
       std::printf("\n");
       for (int l = 0; l < d.n_layers; ++l) {
-        int64_t pl[27];
-        if (daris_get_launch_plan(t, l, pl, 27) != 27) die("plan");
+        int64_t pl[28];
+        if (daris_get_launch_plan(t, l, pl, 28) != 28 || daris_get_launch_plan(t, l, pl, 27) != 27) die("plan");
         std::printf("plan %d %d", t, l);
-        for (int i = 0; i < 27; ++i) std::printf(" %" PRId64, pl[i]);
+        for (int i = 0; i < 28; ++i) std::printf(" %" PRId64, pl[i]);
         std::printf("\n");
       }
       layers.clear();

@@ -149,8 +149,21 @@ def _check_plan(pl, name):
     tn, nw = pl["tn"], pl["nw"]
     assert tn in (1, 2) and nw in (2, 4, 8) and pl["threads"] == 64 * nw, name
     kname = D.daris_kernel_name(pl["kernel_id"])
-    assert kname.endswith(f"t{tn}w{nw}") and kname.startswith({16: "conv_wave16_", 32: "conv_wave_", 64: "conv_wave64_f32_t2"}[rows]), name
+    gather = pl["gather"]
+    special = {D.GATHER_TAPS: "taps_", D.GATHER_IMAGE: "image_"}.get(gather, "")
+    family = {16: "conv_wave16_", 32: "conv_wave_", 64: "conv_wave64_"}[rows]
+    assert kname.endswith(f"t{tn}w{nw}") and kname.startswith((family + special + "f32_", family + special + "bf16_")), (name, kname, gather)
+    if rows != 32:
+        assert gather in (D.GATHER_ROWS, D.GATHER_TAPS), name
+    if rows == 64:
+        assert tn == 2 and "f32" in kname, name
     nb = (N + block - 1) // block
+    if gather == D.GATHER_IMAGE:                                             # a wave owns two rows of 16 pixels and a channel block over all of K
+        wn = 1 if nb % 2 else 2
+        assert rows == 32 and tn == 1 and nw == 4 and z == 1 and pl["ws_bytes"] == 0 and pl["sz"] == pl["sw"] == S, name
+        assert S * (8 if "f32" in kname else 16) == pl["Kpad"] and pl["NTn"] == nb and pl["G"] == nb // wn and pl["xmode"] == 0, name
+        assert pl["grid_x"] == pl["G"] * pl["MT"] and pl["MT"] * (128 // wn) >= M and f"_n{wn}_" in kname, name
+        return
     assert (nb + tn - 1) // tn == pl["NTn"] and pl["MT"] == (M + rows - 1) // rows, name
     if rows >= 32:
         assert nb % tn == 0, name

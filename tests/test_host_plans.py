@@ -64,6 +64,39 @@ def test_every_plan_can_be_encoded(plans):
     assert {p[2] for p in got if p[0] == 1} == {16, 32, 64} and sum(p[2] == 64 for p in got if p[0] == 1) > 50
 
 
+def test_a_plan_says_what_is_launched(plans):
+    """Kernel, workgroups and threads of a launch are those of the plan, for every gather; what the two special ones assume holds."""
+    rng = np.random.default_rng(19)
+    shapes = []
+    for i in range(40000):
+        cin = int(rng.choice([1, 2, 3, 4, 4, 16, 24, 32, 48, 64, 96, 128, 256, 512]))
+        k = int(rng.choice([1, 3, 3, 3, 5, 7, 11]))
+        h, w = (int(v) for v in 2 ** rng.uniform(0, 8, 2))
+        s, p = (1, 1) if k == 3 and rng.random() < 0.7 else (int(rng.integers(1, 5)), int(rng.integers(0, k // 2 + 1)))
+        if min(h, w) + 2 * p >= k:
+            shapes.append((i & 1, cin, h, w, int(rng.choice([4, 8, 32, 64, 96, 128, 192, 256, 512, 1000])), k, s, p, int(rng.choice([8, 32, 64, 96, 128, 192, 256]))))
+    kernels = {g: set() for g in range(7)}
+    for shape, got in zip(shapes, plans(shapes)):
+        ok, kernel, rows, threads, splitk, _, gather, S, sz, sw, groups = got[:11]
+        assert ok == 1 and got[11:] == [kernel, groups, threads], (shape, got)
+        dtype, cin, h, w, cout, k, s, p, _ = shape
+        kernels[gather].add(kernel)
+        if gather == 5:                                     # three taps per fetch: every K slice a whole number of groups of three chunks
+            assert (k, s, p) == (3, 1, 1) and S % 6 == 0 and sz % 6 == 0 and sw % 6 == 0, (shape, got)
+        if gather in (2, 6):
+            assert cin <= 4, (shape, got)
+        if gather == 6:                                     # patches of the input: K is not split, the pixels of a tile fit
+            nb = (cout + 31) // 32
+            wn = 1 if nb % 2 else 2
+            high, wide = (8 // wn - 1) * s + k, 15 * s + k
+            ho, wo = (h + 2 * p - k) // s + 1, (w + 2 * p - k) // s + 1
+            assert splitk == 1 and sz == sw == S and threads == 256 and high * wide <= 864 and 2 * S + 16 <= 512, (shape, got)
+            assert groups == (ho + 8 // wn - 1) // (8 // wn) * ((wo + 15) // 16) * nb // wn, (shape, got)
+    assert all(kernels[g] for g in (0, 1, 2, 3, 5, 6))
+    assert not any(kernels[g] & kernels[q] for g, q in ((5, 3), (5, 0), (5, 1), (6, 1), (6, 2), (6, 0)))      # kernels of their own, with names of their own
+    assert len(kernels[5]) == 18 and len(kernels[6]) == 4                                                     # ... and every one of them is planned for
+
+
 def test_every_joint_launch_can_be_encoded(plans):
     """Two convolutions that read the same tensor: whatever the planner joins, the encoder takes."""
     rng = np.random.default_rng(18)
