@@ -136,20 +136,19 @@ __global__ __launch_bounds__(NW * 64) void conv_block_kernel(const ConvArgs) {
       ci = next ? 0 : ci;
       ky += next ? 1 : 0;
     };
-    // (Pixels past the last one are zeros: their neighbours in the image would have a say in whether the tile is in range.)
-    int left_at[2], mid_at[2], right_at[2];
+    int left_at[2], right_at[2];
+    const int mid_at = row_at(li + 1);
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
       const int m = m0 + 32 * i + li, y = fast_div(m, p.mg_wo), x = m - y * p.Wo;
-      left_at[i] = x == 0 || m >= p.M ? row_at(66) : row_at(32 * i + li);
-      mid_at[i] = m >= p.M ? row_at(66) : row_at(32 * i + li + 1);
-      right_at[i] = x == p.Wo - 1 || m >= p.M ? row_at(66) : row_at(32 * i + li + 2);
+      left_at[i] = x == 0 ? row_at(66) : row_at(32 * i + li);
+      right_at[i] = x == p.Wo - 1 ? row_at(66) : row_at(32 * i + li + 2);
     }
     auto get_rows = [&](auto kx) {
 #pragma unroll
       for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int h = 0; h < 2; ++h) a4[i][h] = st[(kx == 0 ? left_at[i] : kx == 1 ? mid_at[i] : right_at[i]) ^ h];
+        for (int h = 0; h < 2; ++h) a4[i][h] = st[(kx == 0 ? left_at[i] : kx == 1 ? mid_at + 128 * i : right_at[i]) ^ h];
     };
     auto chunk = [&](auto kx, auto more) {  // tap kx of a group; more: another group follows
       constexpr bool next = kx < 2 || more;
@@ -315,6 +314,7 @@ __global__ __launch_bounds__(NW * 64) void conv_block_kernel(const ConvArgs) {
   };
   fetch_res(0);
   park(0);
+  if (TAPS && __builtin_expect(m0 + 64 > p.M, 0)) drop_pixels<32>(acc, [&](int b, int pixel) { return m0 + 32 * (b >> 1) + pixel >= p.M; });
   spoil_unless_in_range(acc, red + wave * BPP * 1024, BPP * 16);
   __syncthreads();
   if (__builtin_expect(spoiled(red[lane % NW * BPP * 1024 + lane]), 0)) {  // every thread of the workgroup or none

@@ -84,6 +84,20 @@ __device__ __forceinline__ bool out_of_range(const Acc (&acc)[N]) {
   return __builtin_expect(__ballot(__builtin_amdgcn_classf(largest * 0x1p-23f, kNanInfDenormal)) != 0, 0) &&
          (__ballot(!(largest < INFINITY)) != 0 || __ballot(largest >= 0x1p-103f) == 0);
 }
+// Kernels that load real neighbours for the pixels of a tile that lie past the output first set the sums of these to 0: nobody stores them, and
+// one of ordinary size would keep a tile of small sums from being walked again.  (Zeros in place of the neighbours cost 0.4 us of the 6.4
+// that the 50176 x 64 x 3 x 3 first convolution takes on 128 CUs; this is a branch for most tiles.)  past(j, pixel): pixel `pixel` of acc[j] is one.
+template <int R, int N, typename Acc, typename F>
+__device__ __forceinline__ void drop_pixels(Acc (&acc)[N], F&& past) {
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int j = 0; j < N; ++j)
+#pragma unroll
+    for (int v = 0; v < R * R / 64; ++v) {
+      const int pixel = R == 32 ? (v >> 2) * 8 + (lane >> 5) * 4 + (v & 3) : (lane >> 4) * 4 + v;
+      acc[j][v] = past(j, pixel) ? 0.f : acc[j][v];
+    }
+}
 template <int N, typename Acc>
 __device__ __forceinline__ void spoil_unless_in_range(const Acc (&acc)[N], float* const tile, const int words) {
   if (out_of_range(acc)) {
@@ -278,7 +292,10 @@ struct WaveEpilogue {
       }
     };
     park();
-    if constexpr (!BF16) spoil_unless_in_range(acc, red + wave * TILE, V * TN);
+    if constexpr (!BF16) {
+      if (MODE == kGatherTaps && __builtin_expect(m0 + R > p.M, 0)) drop_pixels<R>(acc, [&](int, int pixel) { return m0 + pixel >= p.M; });
+      spoil_unless_in_range(acc, red + wave * TILE, V * TN);
+    }
     __syncthreads();
     add_up();
     if constexpr (!BF16) {
@@ -1011,10 +1028,8 @@ __device__ __forceinline__ void conv_taps_body(const ConvArgs& p, const int mt, 
     const int place = row + (R == 16 && !BF16 ? HALF * (lh >> 1) : 0);
     return BF16 ? place * 4 + (lh ^ ((place >> 1) & 3)) : place * 2 + ((lh & 1) ^ ((place >> 2) & 1));
   };
-  // (Pixels past the last one are zeros: their neighbours in the image would have a say in whether the tile is in range.)
   const int m = m0 + li, x = m - fast_div(m, p.mg_wo) * p.Wo;
-  const int zeros = row_at(kZeros);
-  const int at[3] = {x == 0 || m >= p.M ? zeros : row_at(li), m >= p.M ? zeros : row_at(li + 1), x == p.Wo - 1 || m >= p.M ? zeros : row_at(li + 2)};
+  const int at[3] = {x == 0 ? row_at(kZeros) : row_at(li), row_at(li + 1), x == p.Wo - 1 ? row_at(kZeros) : row_at(li + 2)};
   // lanes exchange data through the wave's buffer: order the accesses of the whole wave, not only of each lane
   auto wave_order = [&]() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -1139,9 +1154,7 @@ __device__ __forceinline__ void conv_image_body(const ImageConvArgs& p, const in
   };
 
   uint2* const st = reinterpret_cast<uint2*>(lds);
-  // place of the lane's pixel under the first tap; outside the output that of the zeros, so that a pixel nobody stores has no say in
-  // whether the tile is in range
-  const int base = y0 + row0 + li / 16 < p.Ho && x0 + li % 16 < p.Wo ? (row0 + li / 16) * p.stride * p.pitch + li % 16 : kImagePatch;
+  const int base = (row0 + li / 16) * p.stride * p.pitch + li % 16;  // place of the lane's pixel under the first tap
   const int* const taps = reinterpret_cast<const int*>(lds + NP * PLANE * 2) + (BF16 ? lh : 2 * lh);
   int tap = 0;
   int2 o = make_int2(0, 0);  // places of the next chunk's taps
@@ -1207,6 +1220,8 @@ __device__ __forceinline__ void conv_image_body(const ImageConvArgs& p, const in
   static_for<0, DC>([&](auto s) { step(s, std::false_type()); });
   const int m0 = (y0 + row0) * p.Wo + x0;
   if constexpr (!BF16) {
+    const int rows_in = p.Ho - (y0 + row0), cols_in = p.Wo - x0;
+    if (__builtin_expect(rows_in < 2 || cols_in < kImageCols, 0)) drop_pixels<32>(acc, [&](int, int pixel) { return pixel / 16 >= rows_in || pixel % 16 >= cols_in; });
     if (out_of_range(acc)) {
       ConvArgs c = ConvArgs();
       c.x = p.x; c.w = p.w; c.H = p.H; c.W = p.W; c.Cin = 4; c.Wo = p.Wo; c.kh = c.kw = p.k; c.stride = p.stride; c.pad = p.pad;
