@@ -56,8 +56,14 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restr
 }
 
 // ---- wave-tile implicit GEMM (layer_bodies.h), one tile per workgroup ------------------------------------------------------
+// Waves that a SIMD is to have the registers for: three of the 32 x 64 tiles over whole rows in bf16, which stay within 168 each so (one more with two waves a
+// workgroup otherwise; see rows_pipeline).
 template <bool BF16, int TN, int NW, int MODE>
-__global__ __launch_bounds__(NW * 64) void conv_wave_kernel(const ConvArgs) {
+constexpr int waves_per_simd() {
+  return BF16 && TN == 2 && NW < 8 && MODE == 3 ? 3 : 1;
+}
+template <bool BF16, int TN, int NW, int MODE>
+__global__ __launch_bounds__(NW * 64, (waves_per_simd<BF16, TN, NW, MODE>())) void conv_wave_kernel(const ConvArgs) {
   const ConvArgs p = conv_args_at((ConstPtr)__builtin_amdgcn_kernarg_segment_ptr());
   __shared__ __align__(16) float red[conv_wave_lds<BF16, TN, NW, MODE>()];
   int mt, g;
@@ -82,7 +88,7 @@ __global__ __launch_bounds__(NW * 64) void conv_wave_dw_kernel(const ConvArgs, c
 // the 1x1 convolution of its shortcut read the same tensor): workgroups [0, n0) work on p0, the rest on p1.  n0 is
 // a multiple of 8, so the workgroup -> XCD relation of each problem is the one its plan assumed.
 template <bool BF16, int TN, int NW, int MODE>
-__global__ __launch_bounds__(NW * 64) void conv_wave_pair_kernel(const ConvArgs, const ConvArgs, const int n0) {
+__global__ __launch_bounds__(NW * 64, (waves_per_simd<BF16, TN, NW, MODE>())) void conv_wave_pair_kernel(const ConvArgs, const ConvArgs, const int n0) {
   __shared__ __align__(16) float red[conv_wave_lds<BF16, TN, NW, MODE>()];
   const bool second = (int)blockIdx.x >= n0;
   const ConvArgs p = conv_args_at((ConstPtr)__builtin_amdgcn_kernarg_segment_ptr() + (second ? sizeof(ConvArgs) : 0));

@@ -754,22 +754,26 @@ __device__ __forceinline__ void static_for(F&& f) {  // f(I), ..., f(N - 1), as 
 // requests the one DC chunks further on into the same slot, begun() is called once when the first chunks are on their way.
 // What n leaves over by DC goes behind the loop, with an end for each remainder, or (LEAD) in front of it, through the last slots, so
 // that one end serves every n.  LEAD takes fewer registers: fp32 tiles of 16 x 32 117 instead of 150, so that a CU has room for two
-// workgroups, 196 x 256 x 2304 on 64 CUs 12.7 -> 11.1 us, ResNet-50's frame of 189 x 253 there 494 -> 482.  But nothing may be
-// requested between the first chunks and the loop then, since the paths into the loop would differ in what is on its way and
-// the first steps wait for more than they need; bf16 has the registers, and its frames are 0.8 % faster with the ends behind the loop.
-template <int DC, bool LEAD, typename Load, typename Begun, typename Step>
+// workgroups, 196 x 256 x 2304 on 64 CUs 12.7 -> 11.1 us, ResNet-50's frame of 189 x 253 there 494 -> 482; bf16 tiles of 32 x 64 157 and
+// 163 (four waves, two) instead of 188 and 196, three waves on a SIMD instead of two, 900 x 384 x 384 on 64 CUs 5.6 -> 4.7, 4225 x 256 x 288 on 256 5.5 -> 4.8,
+// 400 such layers 5.3 % faster.  But nothing may be requested between the first chunks and the loop then, since the paths
+// into the loop would differ in what is on its way and the first steps wait for more than they need (begun() comes first);
+// the other bf16 tiles have the registers, and their frames are 0.8 % faster with the ends behind the loop.
+// AHEAD: begun() comes first for walks without a loop too (bf16 tiles of 32 x 64 with one or two chunks: 2.39 us that way, 2.26).
+template <int DC, bool LEAD, bool AHEAD, typename Load, typename Begun, typename Step>
 __device__ __forceinline__ void rows_pipeline(const int n, Load&& load, Begun&& begun, Step&& step) {
   auto refilled = [&](auto s) { step(s, std::true_type()); };
-  if constexpr (LEAD) begun();
+  if constexpr (AHEAD) begun();
   if (n < DC) {
     static_for<0, DC>([&](auto k) {
       if (n == k) {
         static_for<0, k>(load);
-        if constexpr (!LEAD) begun();
+        if constexpr (!AHEAD) begun();
         static_for<0, k>([&](auto s) { step(s, std::false_type()); });
       }
     });
   } else if constexpr (LEAD) {
+    if constexpr (!AHEAD) begun();
     const int lead = n % DC;
     static_for<0, DC>([&](auto r) {
       if (lead == r) {
@@ -781,7 +785,7 @@ __device__ __forceinline__ void rows_pipeline(const int n, Load&& load, Begun&& 
     static_for<0, DC>([&](auto s) { step(s, std::false_type()); });
   } else {
     static_for<0, DC>(load);
-    begun();
+    if constexpr (!AHEAD) begun();
     int left = n - DC;  // chunks still to be requested
     for (; left >= DC; left -= DC) static_for<0, DC>(refilled);
     static_for<0, DC>([&](auto r) {
@@ -898,7 +902,7 @@ __device__ __forceinline__ void conv_rows_body(const ConvArgs& p, const int mt, 
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   };
-  rows_pipeline<DC, !BF16>(
+  rows_pipeline<DC, !BF16 || (R == 32 && TN == 2), !BF16>(
       nchunks,
       [&](auto s) {
         load_rows(s);

@@ -489,26 +489,29 @@ def test_overrun_and_hp_queue_order():
         assert started == sorted(started) == list(range(6))
 
 
-def test_code_object_kernels_match_the_argument_structures():
-    """Every kernel of the device code object takes exactly the argument block the host encoders write (sizes of the
-    structures in csrc/kernels.h), needs no hidden arguments and no scratch: what a bare AQL packet can provide."""
+def _code_object_kernels(name):
+    """[(mangled name, {what: number})] of a device code object, as its metadata has them."""
     import shutil
     import subprocess
-    co = os.path.join(os.path.dirname(D.LIB_PATH), "csrc", "daris_kernels.co")
+    co = os.path.join(os.path.dirname(D.LIB_PATH), "csrc", name + ".co")
     tool = shutil.which("llvm-readelf") or "/opt/rocm/llvm/bin/llvm-readelf"
     if not (os.path.exists(co) and os.path.exists(tool)):
         pytest.skip("code object or llvm-readelf not available")
     notes = subprocess.run([tool, "--notes", co], check=True, capture_output=True, text=True).stdout
+    assert "hidden_" not in notes
+    what = ("kernarg_segment_size", "private_segment_fixed_size", "group_segment_fixed_size", "vgpr_count", "max_flat_workgroup_size")
+    return [(re.search(r"\.name:\s+(\S+)", block).group(1), {w: int(re.search(r"\." + w + r":\s+(\d+)", block).group(1)) for w in what}) for block in notes.split(".agpr_count:")[1:]]
+
+
+def test_code_object_kernels_match_the_argument_structures():
+    """Every kernel of the device code object takes exactly the argument block the host encoders write (sizes of the
+    structures in csrc/kernels.h), needs no hidden arguments and no scratch: what a bare AQL packet can provide."""
     want = {"conv_wave_kernel": 160, "conv_wave_pair_kernel": 324, "conv_wave16_kernel": 160, "conv_wave16_pair_kernel": 324, "conv_wave_dw_kernel": 192, "splitk_reduce_kernel": 48, "dwconv_kernel": 72,
             "maxpool_kernel": 48, "gavgpool_kernel": 48, "fc_kernel": 56, "ingest_kernel": 28, "egress_kernel": 28,
             "cu_probe_kernel": 12}
     seen = {}
-    assert "hidden_" not in notes
-    for block in notes.split(".agpr_count:")[1:]:
-        name = re.search(r"\.name:\s+(\S+)", block).group(1)
-        size = int(re.search(r"\.kernarg_segment_size:\s+(\d+)", block).group(1))
-        scratch = int(re.search(r"\.private_segment_fixed_size:\s+(\d+)", block).group(1))
-        lds = int(re.search(r"\.group_segment_fixed_size:\s+(\d+)", block).group(1))
+    for name, has in _code_object_kernels("daris_kernels"):
+        size, scratch, lds = has["kernarg_segment_size"], has["private_segment_fixed_size"], has["group_segment_fixed_size"]
         base = [k for k in want if re.search(r"\d+" + k + r"(I|E)", name)]
         assert len(base) == 1, name
         assert size == want[base[0]], (name, size)
@@ -517,6 +520,13 @@ def test_code_object_kernels_match_the_argument_structures():
     assert seen == {"conv_wave_kernel": 42, "conv_wave_pair_kernel": 30, "conv_wave16_kernel": 12, "conv_wave16_pair_kernel": 12, "conv_wave_dw_kernel": 7, "splitk_reduce_kernel": 2, "dwconv_kernel": 2,
                     "maxpool_kernel": 2, "gavgpool_kernel": 2, "fc_kernel": 2, "ingest_kernel": 2, "egress_kernel": 2,
                     "cu_probe_kernel": 1}
+
+
+def test_a_simd_has_room_for_three_wide_bf16_row_tiles():
+    """Tiles of 32 x 64 in bf16 over whole rows, in workgroups of two and four waves: grids of up to three such workgroups a CU run in one round
+    if a SIMD, whose lanes have 512 registers handed out in eights, has room for three of the waves."""
+    found = {name: has["vgpr_count"] for name, has in _code_object_kernels("daris_kernels") if re.search(r"conv_wave_(pair_)?kernelILb1ELi2ELi[24]ELi3E", name)}
+    assert len(found) == 4 and all(512 // (-(-v // 8) * 8) >= 3 for v in found.values()), found
 
 
 def test_layer_rooflines_follow_the_layer_tables():
