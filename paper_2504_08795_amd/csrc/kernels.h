@@ -180,8 +180,8 @@ ConvPlan plan_conv_like(const ConvPlan& first, int M, int N, int Kpad, int bf16,
 // Settles the gather of a plan without kGatherTaps; rows = conv_rows_take holds (for both members of a launch pair).
 void plan_gather(ConvPlan* pl, int cin_stride, bool rows, int bf16);
 // The first convolution of a network, whose plan reads the caller's input: turns it into one for conv_image_body, or leaves it
-// (kGatherInput) where that cannot run.
-void plan_input(ConvPlan* pl, int Ho, int Wo, int cout_stride, int k, int stride, int bf16);
+// (kGatherInput) where that cannot run or is the slower one.
+void plan_input(ConvPlan* pl, int Ho, int Wo, int cout_stride, int k, int stride, int nominal_cus, int bf16);
 // Multiplier for fast_div: floor(2^32 / d) + 1, or 0 for d == 1.  Exact for every n >= 0 with n * d < 2^32.
 inline uint32_t div_magic(uint32_t d) { return d <= 1 ? 0u : (uint32_t)((1ull << 32) / d) + 1u; }
 // ... for the tile order of a convolution: the multiplier for division of a workgroup number by MT.

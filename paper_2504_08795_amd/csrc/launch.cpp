@@ -2,6 +2,7 @@
 // into ready-to-dispatch launches (kernel, geometry, argument bytes).
 #include "kernels.h"
 
+#include <algorithm>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -386,11 +387,19 @@ static ImageTiles image_tiles(int Ho, int Wo, int cout_stride, int k, int stride
   return t;
 }
 
-// The patches take every first convolution that they can run and whose plan does not split K over workgroups: where both run
-// they were the faster at every size measured (conv_image_body).
-void plan_input(ConvPlan* pl, int Ho, int Wo, int cout_stride, int k, int stride, int bf16) {
+// Patches where the gather would have more blocks of 32 pixels x 32 channels than there are CUs.  A workgroup of the gather splits K among its waves; one of
+// the patches walks all of it in every wave and waits for its pixels first, so that the gather has the shorter launch while one
+// round of it is enough.  us, means over 600 random layers, gather, patches with fewer blocks than CUs | with two to four times as many: 7 x 7 with stride 2 fp32 3.8,
+// 4.4 | 6.8, 4.6, bf16 3.0, 3.7 | 5.6, 3.8; 5 x 5 with stride 2 fp32 3.55, 3.63 | 4.7, 3.7, bf16 2.85, 3.0 | 4.2, 3.3; 3 x 3 with stride 2 fp32 2.95, 3.15 | 4.2, 3.4,
+// bf16 2.46, 2.6 | 3.4, 2.9.  Two exceptions in fp32: windows of 3 x 3 to 5 x 5 with stride 1, whose patches are small, are no slower in
+// them on few blocks either (2.95, 2.93 and 3.55, 3.44); and a 1 x 1 window, which wants its pixels once, gains from four times as
+// many blocks as CUs on (few 2.5, 2.9; two to four times 3.0, 3.1; four to eight 3.5, 3.4; over 32 12, 9).
+void plan_input(ConvPlan* pl, int Ho, int Wo, int cout_stride, int k, int stride, int nominal_cus, int bf16) {
   pl->gather = kGatherInput;
   const ImageTiles t = image_tiles(Ho, Wo, cout_stride, k, stride, pl->S, bf16);
+  const int cus = std::min(std::max(nominal_cus, 8), 256);
+  const bool one_round = (int64_t)pl->tiles * pl->tn <= (int64_t)cus * (!bf16 && k == 1 ? 4 : 1);
+  if (one_round && (bf16 || stride > 1 || k < 3 || k > 5)) return;
   if (pl->splitk != 1 || pl->rows != 32 || !t.ok) return;
   pl->gather = kGatherImage;
   pl->kernel = (bf16 ? K_IMAGE_BF16_N1 : K_IMAGE_F32_N1) + t.wn - 1;

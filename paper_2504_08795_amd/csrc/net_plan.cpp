@@ -203,7 +203,7 @@ std::string build_plan(const daris_dnn& dnn, bool keep_activations, bool pair_la
     LayerPlan& L = net.layers[l];
     if (L.d.op != DARIS_OP_CONV || L.depthwise) continue;
     const bool joint = L.pair_with >= 0 && !net.layers[L.pair_with].depthwise;
-    if (l == 0 && net.fuse_ingest) plan_input(&L.cp, L.out.H, L.out.W, L.out.Cs, L.d.k, L.d.stride, net.bf16);
+    if (l == 0 && net.fuse_ingest) plan_input(&L.cp, L.out.H, L.out.W, L.out.Cs, L.d.k, L.d.stride, plan_cus, net.bf16);
     else plan_gather(&L.cp, net.tensor(L.in_t).Cs, rows_taken(L) && (!joint || (rows_taken(net.layers[L.pair_with]) && net.layers[L.pair_with].cp.staged)), net.bf16);
     L.kernel_id = L.cp.kernel;
   }

@@ -45,7 +45,7 @@ def test_small_pixels_keep_their_bits(cin, h, w, cout, k, scale_x, scale_w):
 
 
 # (cin, h, w, cout, k, stride, pad, plan_cus, pixels per wave tile)
-@pytest.mark.parametrize("case", [(64, 5, 40, 32, 3, 1, 1, 8, 32), (128, 5, 40, 64, 3, 1, 1, 128, 16), (64, 10, 40, 64, 3, 1, 1, 8, 64), (3, 36, 74, 32, 3, 2, 0, 128, 32), (3, 36, 74, 64, 3, 2, 0, 128, 32)],
+@pytest.mark.parametrize("case", [(64, 5, 40, 32, 3, 1, 1, 8, 32), (128, 5, 40, 64, 3, 1, 1, 128, 16), (64, 10, 40, 64, 3, 1, 1, 8, 64), (3, 36, 74, 32, 3, 2, 0, 8, 32), (3, 36, 74, 64, 3, 2, 0, 8, 32)],
                          ids=lambda c: "x".join(map(str, c)))
 def test_pixels_that_nobody_stores_have_no_say_in_the_range_of_a_tile(case):
     """Small pixels, and 1 where in the last tile only windows past the output reach: the first pixels of the last row (3x3 with
@@ -61,7 +61,8 @@ def test_pixels_that_nobody_stores_have_no_say_in_the_range_of_a_tile(case):
     L = [N.Layer(op=N.OP_CONV, c_in=cin, c_out=cout, k=k, stride=s, pad=p, act=0, in_from=-1)]
     with GpuNet(L, [(wt, np.zeros(cout, np.float32))], (cin, h, w), "fp32", plan_cus=cus) as g:
         got = g.forward(x).astype(np.float64).reshape(cout, -1)
-        assert D.daris_get_launch_plan(g.task, 0)["rows"] == rows
+        plan = D.daris_get_launch_plan(g.task, 0)
+    assert plan["rows"] == rows and plan["gather"] == (D.GATHER_TAPS if p else D.GATHER_IMAGE)      # the case runs the kernel it names
     want = torch.nn.functional.conv2d(torch.from_numpy(x).double()[None], torch.from_numpy(wt).double(), stride=s, padding=p).numpy().reshape(cout, -1)
     first = got.shape[1] // rows * rows if p else 0      # of the last tile; without padding every window misses the ones
     assert first < got.shape[1] and np.abs(want[:, first:]).max() < 1e-34

@@ -120,28 +120,32 @@ def test_small_tiles_where_large_ones_leave_cus_idle(cin, h, w, cout, rows, dtyp
 
 
 @pytest.mark.parametrize("dtype", ["fp32", "bf16"])
-@pytest.mark.parametrize("cin,h,w,cout,k,s,p", [
-    (3, 45, 61, 64, 7, 2, 3),      # last tiles partly outside, input rows of an odd length
-    (1, 16, 16, 32, 3, 1, 1),      # whole tiles, one channel plane
-    (2, 9, 200, 40, 1, 1, 0),      # a single tap, channels that end inside a block
-    (4, 37, 33, 96, 5, 2, 2),      # three channel blocks, no pad channel
-    (3, 30, 31, 24, 3, 3, 1),      # more places than the patch has: gathered tap by tap
-    (3, 61, 47, 64, 3, 3, 0),      # stride 3
-    (3, 17, 19, 128, 11, 1, 5),    # 121 taps
-    (3, 66, 70, 64, 11, 4, 2),     # gathered tap by tap
+@pytest.mark.parametrize("cin,h,w,cout,k,s,p,patched", [
+    (3, 45, 61, 64, 7, 2, 3, ("fp32", "bf16")),      # last tiles partly outside, input rows of an odd length
+    (1, 16, 16, 32, 3, 1, 1, ("fp32",)),             # whole tiles, one channel plane; no more blocks of 32 x 32 than CUs
+    (1, 16, 48, 32, 3, 1, 1, ("fp32", "bf16")),
+    (2, 9, 200, 40, 1, 1, 0, ("fp32", "bf16")),      # a single tap, channels that end inside a block
+    (4, 37, 33, 96, 5, 2, 2, ("fp32", "bf16")),      # three channel blocks, no pad channel
+    (3, 30, 31, 24, 3, 3, 1, ()),                    # more places than the patch has: gathered tap by tap
+    (3, 61, 47, 64, 3, 3, 0, ("fp32", "bf16")),      # stride 3
+    (3, 17, 19, 128, 11, 1, 5, ("fp32", "bf16")),    # 121 taps
+    (3, 66, 70, 64, 11, 4, 2, ()),                   # gathered tap by tap
 ])
-def test_network_input_in_patches(cin, h, w, cout, k, s, p, dtype):
+def test_network_input_in_patches(cin, h, w, cout, k, s, p, patched, dtype):
     """The first convolution reads the caller's layout; also with pixels so small that fp32 takes its tiles a second time (2^-110: every
-    sum is below 2^-103 of 1).  The error bars are relative to the largest sum, and so hold at both scales."""
+    sum is below 2^-103 of 1).  The error bars are relative to the largest sum, and so hold at both scales.  Planned for 8 CUs, where there
+    are more tiles than CUs, and for 256, where one round of the gather is enough (but for small windows with stride 1 in fp32)."""
     L = N.Layer(op=N.OP_CONV, c_in=cin, c_out=cout, k=k, stride=s, pad=p, act=0, in_from=-1)
     weights = [(rand_w(L)[0], np.zeros(cout, np.float32))]
     x = RNG.normal(0, 1, (cin, h, w)).astype(np.float32)
-    with GpuNet([L], weights, (cin, h, w), dtype) as net:
-        for scale in (1.0, 2.0 ** -110):
-            xs = (x * np.float32(scale)).astype(np.float32)
-            got, want = np.asarray(net.forward(xs), np.float64) / scale, np.asarray(oracle_logits([L], weights, x, dtype), np.float64)
-            e_max, e_l2 = rel_err(got, want)
-            assert e_max <= LAYER_TOL[dtype] and e_l2 <= LAYER_TOL[dtype], (scale, e_max, e_l2)
+    want = np.asarray(oracle_logits([L], weights, x, dtype), np.float64)
+    for cus, patches in ((8, dtype in patched), (256, dtype == "fp32" and dtype in patched and s == 1 and 3 <= k <= 5)):
+        with GpuNet([L], weights, (cin, h, w), dtype, plan_cus=cus) as net:
+            assert D.daris_get_launch_plan(net.task, 0)["gather"] == (D.GATHER_IMAGE if patches else D.GATHER_INPUT), cus
+            for scale in (1.0, 2.0 ** -110):
+                xs = (x * np.float32(scale)).astype(np.float32)
+                e_max, e_l2 = rel_err(np.asarray(net.forward(xs), np.float64) / scale, want)
+                assert e_max <= LAYER_TOL[dtype] and e_l2 <= LAYER_TOL[dtype], (cus, scale, e_max, e_l2)
 
 
 @pytest.mark.parametrize("dtype", ["fp32", "bf16"])

@@ -97,6 +97,27 @@ def test_a_plan_says_what_is_launched(plans):
     assert len(kernels[5]) == 18 and len(kernels[6]) == 4                                                     # ... and every one of them is planned for
 
 
+# (c_in, h, w, c_out, k, stride, pad, plan CUs), and whether the input is fetched in patches in (fp32, bf16)
+FIRST_LAYERS = [
+    ((3, 224, 224, 64, 7, 2, 3, 128), (True, True)),       # 392 tiles of two channel blocks
+    ((3, 63, 64, 64, 7, 2, 3, 64), (False, False)),        # 32 * 32 pixels = 32 tiles of two channel blocks: as many blocks as CUs
+    ((3, 65, 64, 64, 7, 2, 3, 64), (True, True)),          # 33 tiles
+    ((3, 64, 64, 32, 3, 2, 1, 32), (False, False)),
+    ((3, 32, 32, 16, 3, 1, 1, 128), (True, False)),        # few tiles, but small patches
+    ((3, 32, 32, 16, 5, 1, 2, 128), (True, False)),
+    ((3, 32, 32, 16, 7, 1, 3, 128), (False, False)),
+    ((3, 64, 64, 16, 1, 1, 0, 32), (False, True)),         # four times as many tiles as CUs
+    ((3, 64, 65, 16, 1, 1, 0, 32), (True, True)),
+    ((3, 300, 300, 64, 11, 4, 2, 32), (False, False)),     # more places than the patch has
+]
+
+
+def test_first_layers_in_patches_or_gathered(plans):
+    for dtype in (0, 1):
+        for (s, want), p in zip(FIRST_LAYERS, plans([(dtype,) + s for s, _ in FIRST_LAYERS])):
+            assert p[0] == 1 and p[6] == (6 if want[dtype] else 2), (s, dtype, p)
+
+
 def test_every_joint_launch_can_be_encoded(plans):
     """Two convolutions that read the same tensor: whatever the planner joins, the encoder takes."""
     rng = np.random.default_rng(18)
