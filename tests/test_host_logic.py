@@ -503,23 +503,36 @@ def _code_object_kernels(name):
     return [(re.search(r"\.name:\s+(\S+)", block).group(1), {w: int(re.search(r"\." + w + r":\s+(\d+)", block).group(1)) for w in what}) for block in notes.split(".agpr_count:")[1:]]
 
 
-def test_code_object_kernels_match_the_argument_structures():
-    """Every kernel of the device code object takes exactly the argument block the host encoders write (sizes of the
+# code object: {kernel: (bytes of its argument block, how many instances)}
+DEVICE_KERNELS = {
+    "daris_kernels": {"conv_wave_kernel": (160, 42), "conv_wave_pair_kernel": (324, 30), "conv_wave16_kernel": (160, 12), "conv_wave16_pair_kernel": (324, 12), "conv_wave_dw_kernel": (192, 7),
+                      "splitk_reduce_kernel": (48, 2), "dwconv_kernel": (72, 2), "maxpool_kernel": (48, 2), "gavgpool_kernel": (48, 2), "fc_kernel": (56, 2), "ingest_kernel": (28, 2),
+                      "egress_kernel": (28, 2), "cu_probe_kernel": (12, 1)},
+    "daris_taps_kernels": {"conv_wave_kernel": (160, 9), "conv_wave16_kernel": (160, 6)},
+    "daris_image_kernels": {"conv_wave_kernel": (160, 4)},
+    "daris_block_kernels": {"conv_block_kernel": (160, 6)},
+    "daris_point_kernels": {"dwconv_window_kernel": (88, 2), "maxpool_window_kernel": (64, 4)},
+}
+
+
+@pytest.mark.parametrize("co", sorted(DEVICE_KERNELS))
+def test_code_object_kernels_match_the_argument_structures(co):
+    """Every kernel of every device code object takes exactly the argument block the host encoders write (sizes of the
     structures in csrc/kernels.h), needs no hidden arguments and no scratch: what a bare AQL packet can provide."""
-    want = {"conv_wave_kernel": 160, "conv_wave_pair_kernel": 324, "conv_wave16_kernel": 160, "conv_wave16_pair_kernel": 324, "conv_wave_dw_kernel": 192, "splitk_reduce_kernel": 48, "dwconv_kernel": 72,
-            "maxpool_kernel": 48, "gavgpool_kernel": 48, "fc_kernel": 56, "ingest_kernel": 28, "egress_kernel": 28,
-            "cu_probe_kernel": 12}
-    seen = {}
-    for name, has in _code_object_kernels("daris_kernels"):
+    want, seen = DEVICE_KERNELS[co], {}
+    for name, has in _code_object_kernels(co):
         size, scratch, lds = has["kernarg_segment_size"], has["private_segment_fixed_size"], has["group_segment_fixed_size"]
         base = [k for k in want if re.search(r"\d+" + k + r"(I|E)", name)]
         assert len(base) == 1, name
-        assert size == want[base[0]], (name, size)
+        assert size == want[base[0]][0], (name, size)
         assert scratch == 0 and lds <= 65536, (name, scratch, lds)
         seen[base[0]] = seen.get(base[0], 0) + 1
-    assert seen == {"conv_wave_kernel": 42, "conv_wave_pair_kernel": 30, "conv_wave16_kernel": 12, "conv_wave16_pair_kernel": 12, "conv_wave_dw_kernel": 7, "splitk_reduce_kernel": 2, "dwconv_kernel": 2,
-                    "maxpool_kernel": 2, "gavgpool_kernel": 2, "fc_kernel": 2, "ingest_kernel": 2, "egress_kernel": 2,
-                    "cu_probe_kernel": 1}
+    assert seen == {k: n for k, (_, n) in want.items()}
+
+
+def test_every_code_object_is_checked():
+    from paper_2504_08795_amd import build
+    assert set(build.DEVICE_SOURCES.values()) == set(DEVICE_KERNELS)
 
 
 def test_a_simd_has_room_for_three_wide_bf16_row_tiles():
