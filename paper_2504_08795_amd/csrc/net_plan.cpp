@@ -225,11 +225,13 @@ std::string build_plan(const daris_dnn& dnn, bool keep_activations, bool pair_la
 
   // activation slots: a tensor's slot is free again once its last reader has been issued (same stream, in order)
   // The earlier member of a launch pair is issued with the later one (and its split-K reduction after that launch):
-  // what it reads must stay in place until then, so its reads count as reads of the later layer.
+  // what it reads must stay in place until then, so its reads count as reads of the later layer; and what it writes, read or not,
+  // must not be given to the later member.
   std::vector<int> last_use(n + 1, -1);
   for (int l = 0; l < n; ++l) {
     const LayerPlan& L = net.layers[l];
     const int at = std::max(l, L.pair_with);
+    last_use[l + 1] = at;
     last_use[L.in_t] = std::max(last_use[L.in_t], at);
     if (L.res_t >= 0) last_use[L.res_t] = std::max(last_use[L.res_t], at);
   }

@@ -630,6 +630,21 @@ def test_activation_slots_outlive_their_readers(net):
     assert len({p["out_slot"] for p in plans if p["out_slot"] >= 0}) <= 6         # and buffers are still shared
 
 
+@pytest.mark.parametrize("read", [0, 1])
+def test_members_of_a_joint_launch_write_to_places_of_their_own(read):
+    """... also where nothing reads one of them."""
+    layers = [N_.Layer(op=N_.OP_CONV, c_in=64, c_out=64, k=3, stride=2, pad=1, in_from=-1), N_.Layer(op=N_.OP_CONV, c_in=64, c_out=64, k=1, stride=2, in_from=-1),
+              N_.Layer(op=N_.OP_CONV, c_in=64, c_out=64, k=1, in_from=read)]
+    with Session(HOST):
+        D.daris_create_partition(64)
+        dnn, keep = D.make_dnn(layers, None, (64, 28, 28), "fp32")
+        t = D.daris_register_task(dnn, 10**7, 10**7, D.LP)
+        plans = [D.daris_get_launch_plan(t, l) for l in range(3)]
+    assert plans[0]["pair_with"] == 1
+    assert len({plans[0]["in_slot"], plans[0]["out_slot"], plans[1]["out_slot"]}) == 3, plans
+    _check_slot_lifetimes(layers, plans, "one member unread")
+
+
 def test_timeout_setter_validates():
     with pytest.raises(D.DarisError) as e:
         D.daris_set_timeout(0)
