@@ -157,6 +157,12 @@ inline bool conv_rows_take(int H, int W, int cin_stride, uint64_t M, int cout_st
   const uint64_t es = bf16 ? 2 : 4, limit = 1ull << 31;
   return conv_rows_staged(cin_stride, bf16) && (uint64_t)H * (uint64_t)W * (uint64_t)cin_stride * es < limit && M * (uint64_t)cout_stride * es < limit && (uint64_t)Kpad * 192 < limit;
 }
+// The same for larger tensors, of plans of two waves and 32 pixels (conv_large_kernel, conv_taps_large_kernel): the offsets of a tile
+// count from what it touches of the input and of the output.
+inline bool conv_rows_take_large(int H, int W, int cin_stride, int Wo, int cout_stride, int k, int stride, int Kpad, int bf16) {
+  const uint64_t es = bf16 ? 2 : 4, limit = 1ull << 31, tile_rows = (uint64_t)(31 / Wo + 1) * (uint64_t)stride + (uint64_t)k, rows = tile_rows < (uint64_t)H ? tile_rows : (uint64_t)H;
+  return conv_rows_staged(cin_stride, bf16) && rows * (uint64_t)W * (uint64_t)cin_stride * es < limit && 32 * (uint64_t)cout_stride * es < limit && (uint64_t)Kpad * 192 < limit;
+}
 // Whether the kernel of 64 x 64 tiles can run an fp32 convolution of this geometry: it keeps one bit per filter tap in a word
 // and walks the rows of taps inside the image as a rectangle of them, and its byte offsets into the input and into the weights
 // of two channel blocks are signed 32-bit numbers.
@@ -172,12 +178,14 @@ inline bool conv_three_taps(int k, int stride, int pad) { return k == 3 && strid
 // cin_stride = the input tensor's channel stride: when it is a whole number of the 16-row kernel's K steps and the 32-row
 // plan would split K across workgroups or leave half of the CUs idle, a 16-row plan is chosen instead (cin_stride 0: never).
 // allow_block = false: no 64-pixel tiles (a convolution that conv_block_takes refuses, shares its launch or computes its input on the fly);
-// three_taps: conv_three_taps and conv_rows_take hold.  The plan's gather is kGatherTaps or kGatherRows; plan_gather settles the rest.
-ConvPlan plan_conv(int M, int N, int Kpad, int bf16, int step_align, int cin_stride, int nominal_cus, bool allow_block, bool three_taps = false);
+// three_taps: kTaps where conv_three_taps and conv_rows_take hold, kTapsLarge where conv_rows_take_large does in the latter's place.  The
+// plan's gather is kGatherTaps or kGatherRows; plan_gather settles the rest.
+enum ThreeTaps : int { kNoTaps = 0, kTaps = 1, kTapsLarge = 2 };
+ConvPlan plan_conv(int M, int N, int Kpad, int bf16, int step_align, int cin_stride, int nominal_cus, bool allow_block, ThreeTaps three_taps = kNoTaps);
 // Plan for a second convolution that is to share a launch with `first`: the same wave-tile kernel variant, K not split
 // across workgroups.  Returns a plan with kernel == K_NONE when that is not possible.
 ConvPlan plan_conv_like(const ConvPlan& first, int M, int N, int Kpad, int bf16, int step_align, int nominal_cus = 128);
-// Settles the gather of a plan without kGatherTaps; rows = conv_rows_take holds (for both members of a launch pair).
+// Settles the gather of a plan without kGatherTaps; rows = conv_rows_take holds (for both members of a launch pair), or conv_rows_take_large.
 void plan_gather(ConvPlan* pl, int cin_stride, bool rows, int bf16);
 // The first convolution of a network, whose plan reads the caller's input: turns it into one for conv_image_body, or leaves it
 // (kGatherInput) where that cannot run or is the slower one.
@@ -207,6 +215,7 @@ struct KernelLaunch {
 struct KernelTable {
   const AqlKernel* conv[2][6][4] = {};  // [bf16][(tn - 1) * 3 + log2(nw) - 1][gather 0..3] (fp32: no kGatherAligned)
   const AqlKernel* taps[2][6] = {};     // the same with kGatherTaps, where there is a kernel id
+  const AqlKernel* large[2][2][2] = {}; // conv_rows_take_large: [bf16][kGatherTaps][tn - 1]
   const AqlKernel* image[2][2] = {};    // kGatherImage: [bf16][128 pixels x 32 channels, 64 x 64]
   const AqlKernel* pair[2][6][3] = {};  // kGatherAligned, kGatherGeneral, kGatherRows
   const AqlKernel* conv16[2][2][6] = {};  // 16-row tiles: [bf16][kGatherTaps][(tn - 1) * 3 + log2(nw) - 1]

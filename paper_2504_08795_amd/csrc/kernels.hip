@@ -73,6 +73,17 @@ __global__ __launch_bounds__(NW * 64, (waves_per_simd<BF16, TN, NW, MODE>())) vo
   puts_done();
 }
 
+// Whole rows of tensors of 2 GiB and more; their grids are large, so that their plans have two waves a workgroup.
+template <bool BF16, int TN>
+__global__ __launch_bounds__(128, (waves_per_simd<BF16, TN, 2, 3>())) void conv_large_kernel(const ConvArgs) {
+  const ConvArgs p = conv_args_at((ConstPtr)__builtin_amdgcn_kernarg_segment_ptr());
+  __shared__ __align__(16) float red[conv_wave_lds<BF16, TN, 2, 3>()];
+  int mt, g;
+  if (!conv_tile_of(p, (int)blockIdx.x, &mt, &g)) return;
+  conv_rows_body<BF16, 32, TN, 2, true>(p, mt, g, red);
+  puts_done();
+}
+
 // A 1x1 convolution with the 3x3 depthwise convolution in front of it computed on the fly (gather mode 4): one launch for
 // the second and third layer of an inverted residual block, and the depthwise output never touches memory.
 template <bool BF16, int TN, int NW>
@@ -207,6 +218,8 @@ __global__ __launch_bounds__(64) void cu_probe_kernel(uint32_t* out, int spin) {
   DARIS_INST_CONV(B, 1, 2) DARIS_INST_CONV(B, 1, 4) DARIS_INST_CONV(B, 1, 8)                        \
   DARIS_INST_CONV(B, 2, 2) DARIS_INST_CONV(B, 2, 4) DARIS_INST_CONV(B, 2, 8)                        \
   DARIS_INST_CONV16(B, 1) DARIS_INST_CONV16(B, 2)                                                   \
+  template __global__ void conv_large_kernel<B, 1>(const ConvArgs);                                 \
+  template __global__ void conv_large_kernel<B, 2>(const ConvArgs);                                 \
   template __global__ void splitk_reduce_kernel<B>(const float*, const float*, const void*, void*, int, int, int, int); \
   template __global__ void dwconv_kernel<B>(const DwArgs);                                         \
   template __global__ void maxpool_kernel<B>(const PoolArgs);                                      \

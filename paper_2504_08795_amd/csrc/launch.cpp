@@ -53,7 +53,7 @@ static int32_t conv_kernel(int rows, int bf16, int tn, int nw, bool taps) {
 // round's worth of work.  1 = perfectly even; 98 workgroups on 96 CUs: 1.96.
 static double round_waste(int groups, int cus) { return (double)cdiv(groups, cus) * cus / groups; }
 
-static ConvPlan plan_conv_wave(int M, int N, int Kpad, int bf16, int step_align, int nominal_cus, bool allow_block, bool three_taps, int force_tn = 0, int force_nw = 0) {
+static ConvPlan plan_conv_wave(int M, int N, int Kpad, int bf16, int step_align, int nominal_cus, bool allow_block, ThreeTaps three_taps, int force_tn = 0, int force_nw = 0) {
   const int kNominalWaveSlots = 4 * nominal_cus;  // SIMDs of the partition size the plan is balanced for
   // What a launch of few tiles pays for is its fixed cost and idle CUs.  Best found on a 128-CU partition (ResNet-18 shapes): 8
   // waves per workgroup splitting K, and enough grid.z slices that tiles * z is about the number of CUs, while a wave keeps
@@ -119,7 +119,7 @@ static ConvPlan plan_conv_wave(int M, int N, int Kpad, int bf16, int step_align,
   }
   // K slices of workgroups and waves in whole multiples of step_align steps (2 when the kernel fetches the pixel
   // operand in chunks of two steps; S is then even as well; 6 when a fetch serves three chunks, where every wave gets one at least)
-  const bool taps = three_taps && staged && (block || S / 6 >= nw * z) && taps_kernel(block ? 64 : 32, bf16, tn, nw) != K_NONE;
+  const bool taps = three_taps != kNoTaps && staged && (block || ((three_taps == kTaps || nw == 2) && S / 6 >= nw * z)) && taps_kernel(block ? 64 : 32, bf16, tn, nw) != K_NONE;
   if (taps) step_align = 6;
   const int sz = cdiv(cdiv(S, z), step_align) * step_align;
   z = cdiv(S, sz);
@@ -220,7 +220,7 @@ static ConvPlan plan_conv_wave16(int M, int N, int Kpad, int bf16, int nominal_c
   return pl;
 }
 
-ConvPlan plan_conv(int M, int N, int Kpad, int bf16, int step_align, int cin_stride, int nominal_cus, bool allow_block, bool three_taps) {
+ConvPlan plan_conv(int M, int N, int Kpad, int bf16, int step_align, int cin_stride, int nominal_cus, bool allow_block, ThreeTaps three_taps) {
   if (nominal_cus < 8) nominal_cus = 8;
   if (nominal_cus > 256) nominal_cus = 256;
   const ConvPlan pl = plan_conv_wave(M, N, Kpad, bf16, step_align, nominal_cus, allow_block, three_taps);
@@ -232,7 +232,7 @@ ConvPlan plan_conv(int M, int N, int Kpad, int bf16, int step_align, int cin_str
   // (A short K with a single channel tile stays: it can take the depthwise layer in front of it into its launch, or is a single tile.)
   const bool idle = Kpad > 128 ? pl.tiles <= nominal_cus / 2 : pl.NTn > 1 && pl.tiles <= nominal_cus;
   if ((pl.splitk > 1 || idle) && cin_stride > 0 && cin_stride % (bf16 ? 32 : 16) == 0) {
-    const ConvPlan p16 = plan_conv_wave16(M, N, Kpad, bf16, nominal_cus, three_taps);
+    const ConvPlan p16 = plan_conv_wave16(M, N, Kpad, bf16, nominal_cus, three_taps == kTaps);
     if (p16.kernel != K_NONE) return p16;
   }
   return pl;
@@ -244,7 +244,7 @@ ConvPlan plan_conv_like(const ConvPlan& first, int M, int N, int Kpad, int bf16,
   if (nominal_cus > 256) nominal_cus = 256;
   if (first.rows == 16) return plan_conv_wave16(M, N, Kpad, bf16, nominal_cus, false, first.tn, first.nw);
   if (cdiv(N, 32) % first.tn != 0) return none;
-  return plan_conv_wave(M, N, Kpad, bf16, step_align, nominal_cus, false, false, first.tn, first.nw);
+  return plan_conv_wave(M, N, Kpad, bf16, step_align, nominal_cus, false, kNoTaps, first.tn, first.nw);
 }
 
 
@@ -320,6 +320,7 @@ std::string KernelTable::resolve(const AqlRuntime& rt) {
       static const int pair_modes[3] = {0, 1, 3};
       for (int m = b ? 0 : 1; m < 3; ++m) pair[b][v][m] = get("daris::conv_wave_pair_kernel<" + tp + std::to_string(pair_modes[m]) + ">", kPairBytes);
     }
+    for (int v = 0; v < 4; ++v) large[b][v / 2][v % 2] = get((v < 2 ? "daris::conv_large_kernel<" : "daris::conv_taps_large_kernel<") + B + ", " + std::to_string(v % 2 + 1) + ">", sizeof(ConvArgs));
     for (int v = 0; v < 2; ++v) image[b][v] = get("daris::conv_wave_kernel<" + B + ", " + std::to_string(v + 1) + ", 4, 6>", sizeof(ImageConvArgs));
     for (int v = 0; v < 6; ++v) {
       for (int t = 0; t < (taps_kernel(16, b, tn_[v], nw_[v]) != K_NONE ? 2 : 1); ++t)
@@ -347,6 +348,8 @@ std::string KernelTable::resolve(const AqlRuntime& rt) {
 // ---- encoders ----------------------------------------------------------------------------------------------------------------
 
 static bool rows_take(const ConvArgs& a, int bf16) { return a.c_real == 0 && conv_rows_take(a.H, a.W, a.Cin, (uint64_t)a.M, a.Cout, a.Kpad, bf16); }
+
+static bool rows_take_large(const ConvArgs& a, int bf16) { return a.c_real == 0 && a.kh == a.kw && conv_rows_take_large(a.H, a.W, a.Cin, a.Wo, a.Cout, a.kh, a.stride, a.Kpad, bf16); }
 
 static bool push_reduce(const KernelTable& kt, const ConvPlan& pl, const ConvArgs& a, int bf16, std::vector<KernelLaunch>* out) {
   if (pl.splitk <= 1) return true;
@@ -457,10 +460,11 @@ bool encode_conv(const KernelTable& kt, const ConvPlan& pl, const ConvArgs& a, i
   } else {
     const bool rows = pl.gather == kGatherRows || taps;
     if (pl.rows != 32 || pl.gather == kGatherDepthwise) return false;
-    if (rows && (!pl.staged || !rows_take(a, bf16))) return false;
+    const bool large = rows && !rows_take(a, bf16);
+    if (rows && (!pl.staged || (large && (pl.nw != 2 || !rows_take_large(a, bf16))))) return false;
     if (pl.gather == kGatherAligned && (!bf16 || a.Cin % 16)) return false;
     if ((rows || !bf16) && (pl.S % 2 || pl.sz % 2 || pl.sw % 2)) return false;
-    kernel = taps ? kt.taps[bf16][v] : kt.conv[bf16][v][pl.gather];
+    kernel = large ? kt.large[bf16][taps][pl.tn - 1] : taps ? kt.taps[bf16][v] : kt.conv[bf16][v][pl.gather];
   }
   return push(out, kernel, pl.kernel, pl.grid_x, (uint32_t)pl.threads, &a, sizeof(a)) && push_reduce(kt, pl, a, bf16, out);
 }

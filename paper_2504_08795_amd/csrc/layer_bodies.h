@@ -210,8 +210,8 @@ __device__ __forceinline__ void plain_products(const ConvArgs& p, const DwFusedA
 template <int R>
 using WaveAcc = typename std::conditional<R == 32, f32x16, f32x4>::type;
 // BUFFER: everything goes through buffer descriptors, which give 0 past the end and drop what is stored there, so that nothing is
-// conditional and the compiler can count the loads (tensors below 2 GiB).
-template <bool BF16, int R, int TN, int NW, bool BUFFER>
+// conditional and the compiler can count the loads.  They hold the whole tensors, below 2 GiB, or (LARGE) the tile's pixels.
+template <bool BF16, int R, int TN, int NW, bool BUFFER, bool LARGE = false>
 struct WaveEpilogue {
   static constexpr int ES = BF16 ? 2 : 4, NT = NW * 64, V = R * R / 64, TILE = TN * R * R;  // V: accumulator rows of a block
   static constexpr int QUADS = TILE / 4, RQ = (QUADS + NT - 1) / NT;  // quads of the tile, of a thread
@@ -220,7 +220,7 @@ struct WaveEpilogue {
   static constexpr int kOutside = (int)0x80000000;  // an offset past the end of any tensor
   float4 bias_j[NB];
   ResVec res_pre[RQ];
-  int at[RQ];  // BUFFER: byte offset of the quad in the output and in the residual operand
+  int at[RQ];  // BUFFER: byte offset of the quad in the output and in the residual operand (LARGE: from the tile's first pixel on)
   bool own_epilogue, use_res;
 
   // channel block, pixel and first channel of the quad that starts at tile element e = (j*V + v)*64 + lane
@@ -230,11 +230,15 @@ struct WaveEpilogue {
     *mm = m0 + (R == 32 ? (v >> 2) * 8 + (l >> 5) * 4 + (v & 3) : (l >> 4) * 4 + v);
     *n = (nb0 + *j) * R + l % R;
   }
+  // LARGE: `t`, of the output's shape, from the tile's first pixel on
+  __device__ __forceinline__ static void* from_tile(const ConvArgs& p, const void* t, const int m0) {
+    return (unsigned char*)const_cast<void*>(t) + (size_t)(uint32_t)m0 * (uint32_t)(p.Cout * ES);
+  }
   __device__ __forceinline__ void fetch(const ConvArgs& p, const int m0, const int nb0, const int tid) {
     own_epilogue = p.splitk == 1;
     use_res = own_epilogue && p.res != nullptr;
     const auto brsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p.bias), 0, BUFFER ? p.Cout * 4 : 0, 0x00027000);
-    const auto rrsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p.res), 0, BUFFER && use_res ? p.M * p.Cout * ES : 0, 0x00027000);
+    const auto rrsrc = __builtin_amdgcn_make_buffer_rsrc(LARGE ? from_tile(p, p.res, m0) : const_cast<void*>(p.res), 0, BUFFER && use_res ? (LARGE ? min(R, p.M - m0) : p.M) * p.Cout * ES : 0, 0x00027000);
 #pragma unroll
     for (int k = 0; k < NB; ++k) {
       int j, mm, n;
@@ -251,7 +255,7 @@ struct WaveEpilogue {
       place(e, m0, nb0, &j, &mm, &n);
       const bool ok = (QUADS % NT == 0 || e < TILE) && mm < p.M && n < p.Cout;
       if constexpr (BUFFER) {
-        at[r] = ok ? (mm * p.Cout + n) * ES : kOutside;
+        at[r] = ok ? ((LARGE ? mm - m0 : mm) * p.Cout + n) * ES : kOutside;
         if constexpr (BF16) res_pre[r] = __builtin_bit_cast(ResVec, __builtin_amdgcn_raw_buffer_load_b64(rrsrc, at[r], 0, 0));
         else res_pre[r] = __builtin_bit_cast(ResVec, __builtin_amdgcn_raw_buffer_load_b128(rrsrc, at[r], 0, 0));
       } else if (use_res && ok) {
@@ -358,7 +362,7 @@ struct WaveEpilogue {
         out[r] = make_uint4(__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3]));
       }
     }
-    const auto yrsrc = __builtin_amdgcn_make_buffer_rsrc(p.y, 0, BUFFER ? p.M * p.Cout * ES : 0, 0x00027000);
+    const auto yrsrc = __builtin_amdgcn_make_buffer_rsrc(LARGE ? from_tile(p, p.y, m0) : p.y, 0, BUFFER ? (LARGE ? min(R, p.M - m0) : p.M) * p.Cout * ES : 0, 0x00027000);
 #pragma unroll
     for (int r = 0; r < RQ; ++r) {
       if constexpr (BUFFER) {
@@ -809,7 +813,11 @@ __device__ __forceinline__ void wave_mma(const Split8& a, const uint4 (&b)[TN][B
       else acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a.p[PA[t]]), __builtin_bit_cast(bf16x8, b[j][PB[t]]), acc[j], 0, 0, 0);
     }
 }
-template <bool BF16, int R, int TN, int NW>
+// LARGE: tensors of 2 GiB and more, whose byte offsets count from what the tile touches instead of from the tensor's start.  (Everywhere,
+// it would cost each launch 0.02 to 0.06 us in front of its first load: ResNet-18's frame 133.2 -> 134.5 us.)  Straight into registers
+// (gather mode 1), 2250000 x 64 x 256 in fp32 takes 1810 us instead of 1290 on 128 CUs, 2250000 x 64 x 2304 10070 instead of 5540 (with three
+// taps per fetch); bf16 with K twice as long 1580 instead of 1120, 8250 instead of 4310.
+template <bool BF16, int R, int TN, int NW, bool LARGE = false>
 __device__ __forceinline__ void conv_rows_body(const ConvArgs& p, const int mt, const int g, float* const red) {
   constexpr int ES = BF16 ? 2 : 4;
   constexpr int RK = 64 / ES;                     // k of a row
@@ -839,15 +847,19 @@ __device__ __forceinline__ void conv_rows_body(const ConvArgs& p, const int mt, 
   int ky = fast_div(tap, p.mg_kw), kx = tap - ky * p.kw;
   const int piece = lane & 3, prow = lane >> 2;
   int iy0[NX], ix0[NX], rbase[NX], vo[NX];
+  const int iy_first = LARGE ? min(max(fast_div(m0, p.mg_wo) * p.stride - p.pad, 0), p.H - 1) : 0;  // the first row of the image that the tile may read
 #pragma unroll
   for (int j = 0; j < NX; ++j) {
     const int m = min(m0 + 16 * j + prow, p.M - 1);  // (past the last pixel: the last one once more, whose sums nobody stores)
     const int y = fast_div(m, p.mg_wo), x = m - y * p.Wo;
     iy0[j] = y * p.stride - p.pad;
     ix0[j] = x * p.stride - p.pad;
-    rbase[j] = (int)(((uint32_t)iy0[j] * (uint32_t)p.W + (uint32_t)ix0[j]) * (uint32_t)(p.Cin * ES)) + piece * 16;
+    rbase[j] = (int)(((uint32_t)(iy0[j] - iy_first) * (uint32_t)p.W + (uint32_t)ix0[j]) * (uint32_t)(p.Cin * ES)) + piece * 16;
   }
-  const auto xrsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p.x), 0, (int)((uint32_t)(p.H * p.W) * (uint32_t)p.Cin * ES), 0x00027000);
+  // (LARGE: what lies outside the image is found by its coordinates, so that 2 GiB will do for the size)
+  void* from = const_cast<void*>(p.x);
+  if constexpr (LARGE) from = (unsigned char*)from + (size_t)(uint32_t)(iy_first * p.W) * (uint32_t)(p.Cin * ES);
+  const auto xrsrc = __builtin_amdgcn_make_buffer_rsrc(from, 0, LARGE ? kOutside : (int)((uint32_t)(p.H * p.W) * (uint32_t)p.Cin * ES), 0x00027000);
   int soff = ci * ES, rest = R == 32 ? nchunks : nsteps, left;  // rows of the slice behind this tap's, rows of this tap to go
   auto enter_tap = [&]() {  // at (ky, kx, ci)
     left = min((int)((uint32_t)(p.Cin - ci) / RK), rest);
@@ -890,7 +902,7 @@ __device__ __forceinline__ void conv_rows_body(const ConvArgs& p, const int mt, 
       for (int q = 0; q < NP; ++q) bw[s][j][q] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(wrsrc[j], lane * 16 + q * 1024, woff, 0));
     woff += NP * 1024;
   };
-  WaveEpilogue<BF16, R, TN, NW, true> fin;
+  WaveEpilogue<BF16, R, TN, NW, true, LARGE> fin;
   WaveAcc<R> acc[TN];
 #pragma unroll
   for (int j = 0; j < TN; ++j) acc[j] = WaveAcc<R>(0.f);
@@ -956,7 +968,7 @@ template <bool BF16, int R, int TN, int NW>
 constexpr int conv_taps_lds() {
   return NW * conv_taps_stage<BF16>() > NW * TN * R * R ? NW * conv_taps_stage<BF16>() : NW * TN * R * R;
 }
-template <bool BF16, int R, int TN, int NW>
+template <bool BF16, int R, int TN, int NW, bool LARGE = false>  // LARGE as in conv_rows_body
 __device__ __forceinline__ void conv_taps_body(const ConvArgs& p, const int mt, const int g, float* const red) {
   constexpr int ES = BF16 ? 2 : 4;
   constexpr int RK = 64 / ES;                    // k of a row
@@ -979,15 +991,23 @@ __device__ __forceinline__ void conv_taps_body(const ConvArgs& p, const int mt, 
   const int gk = sbeg / 6 * CK;
   int ky = fast_div(gk, p.mg_cin), ci = gk - ky * p.Cin;
   const int piece = lane & 3, prow = lane >> 2, row_bytes = p.Cin * ES;
+  const int base = LARGE ? max(m0 - 1 - p.W, 0) : 0;  // the first pixel that the tile may read
   int first[3];  // byte offset of the lane's piece of its row in each load, at (ky = 0, ci = 0)
   bool used[3];
 #pragma unroll
   for (int r = 0; r < 3; ++r) {
     const int place = 16 * r + prow, half = R == 16 && place >= HALF ? 1 : 0, row = place - HALF * half;
     used[r] = row < R + 2;
-    first[r] = (int)((uint32_t)(m0 - 1 + row - p.W) * (uint32_t)row_bytes) + 64 * half + piece * 16;
+    first[r] = (int)((uint32_t)(m0 - 1 + row - p.W - base) * (uint32_t)row_bytes) + 64 * half + piece * 16;
   }
-  const auto xrsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p.x), 0, p.H * p.W * row_bytes, 0x00027000);
+  void* from = const_cast<void*>(p.x);
+  int bytes = p.H * p.W * row_bytes;
+  if constexpr (LARGE) {
+    from = (unsigned char*)from + (size_t)(uint32_t)base * (uint32_t)row_bytes;
+    const uint64_t behind = (uint64_t)(uint32_t)(p.H * p.W - base) * (uint32_t)row_bytes;
+    bytes = behind < (uint32_t)kOutside ? (int)behind : kOutside;
+  }
+  const auto xrsrc = __builtin_amdgcn_make_buffer_rsrc(from, 0, bytes, 0x00027000);
   uint4 rows[3];
   auto load_rows = [&]() {
     const uint32_t off = (uint32_t)(ky * p.W) * (uint32_t)row_bytes + (uint32_t)(ci * ES);
@@ -1013,7 +1033,7 @@ __device__ __forceinline__ void conv_taps_body(const ConvArgs& p, const int mt, 
       for (int q = 0; q < NP; ++q) bw[kx][j][q] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(wrsrc[j], lane * 16 + q * 1024, woff, 0));
     woff += NP * 1024;
   };
-  WaveEpilogue<BF16, R, TN, NW, true> fin;
+  WaveEpilogue<BF16, R, TN, NW, true, LARGE> fin;
   // Bias and residual are requested first: behind the first rows they would leave the paths into the loop with different loads on
   // their way (see rows_pipeline).  fp32 tiles of 16 x 32 keep their registers for the loop (eight waves fit 128, two workgroups a CU:
   // 196 x 256 x 2304 on 64 CUs 10.2 us instead of 12.0) and request them ahead of the last group, which costs the others 0.1 us.

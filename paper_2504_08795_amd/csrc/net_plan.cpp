@@ -50,11 +50,16 @@ std::string build_plan(const daris_dnn& dnn, bool keep_activations, bool pair_la
   net.ingest.bytes = (size_t)net.ingest.H * net.ingest.W * net.ingest.Cs * es;
   const int n = dnn.n_layers;
   net.layers.resize(n);
-  // the channel stride that lets plan_conv choose 16-pixel tiles, which only whole 64-byte rows feed; 0: it may not
-  auto small_tile_stride = [&](const LayerPlan& L) {
-    const TensorInfo &in = net.tensor(L.in_t), &o = L.out;
-    return small_tiles && conv_rows_take(in.H, in.W, in.Cs, (uint64_t)o.H * (uint64_t)o.W, o.Cs, L.Kpad, net.bf16) ? in.Cs : 0;
+  auto rows_taken = [&](const LayerPlan& L) {
+    const TensorInfo& in = net.tensor(L.in_t);
+    return conv_rows_take(in.H, in.W, in.Cs, (uint64_t)L.out.H * (uint64_t)L.out.W, L.out.Cs, L.Kpad, net.bf16);
   };
+  auto rows_taken_large = [&](const LayerPlan& L) {
+    const TensorInfo& in = net.tensor(L.in_t);
+    return conv_rows_take_large(in.H, in.W, in.Cs, L.out.W, L.out.Cs, L.d.k, L.d.stride, L.Kpad, net.bf16);
+  };
+  // the channel stride that lets plan_conv choose 16-pixel tiles, which only whole 64-byte rows feed; 0: it may not
+  auto small_tile_stride = [&](const LayerPlan& L) { return small_tiles && rows_taken(L) ? net.tensor(L.in_t).Cs : 0; };
 
   for (int l = 0; l < n; ++l) {
     LayerPlan& L = net.layers[l];
@@ -89,7 +94,7 @@ std::string build_plan(const daris_dnn& dnn, bool keep_activations, bool pair_la
             return "layer " + std::to_string(l) + ": tensor too large for the kernels' index arithmetic";
           L.cp = plan_conv(o.H * o.W, o.Cs, L.Kpad, net.bf16, staged_rows && conv_rows_staged(in.Cs, net.bf16) ? 2 : 1, small_tile_stride(L), plan_cus,
                            conv_block_takes(in.H, in.W, in.Cs, d.k, d.pad, L.Kpad),
-                           staged_rows && conv_three_taps(d.k, d.stride, d.pad) && conv_rows_take(in.H, in.W, in.Cs, (uint64_t)o.H * (uint64_t)o.W, o.Cs, L.Kpad, net.bf16));
+                           !staged_rows || !conv_three_taps(d.k, d.stride, d.pad) ? kNoTaps : rows_taken(L) ? kTaps : rows_taken_large(L) ? kTapsLarge : kNoTaps);
           net.ws_bytes = std::max(net.ws_bytes, L.cp.ws_bytes);
         } else {
           L.kernel_id = K_DWCONV;
@@ -142,6 +147,7 @@ std::string build_plan(const daris_dnn& dnn, bool keep_activations, bool pair_la
     LayerPlan& B = net.layers[l + 1];
     if (A.d.op != DARIS_OP_CONV || B.d.op != DARIS_OP_CONV || A.depthwise || B.depthwise) continue;
     if (A.in_t != B.in_t || B.res_t == l + 1) continue;
+    if (conv_rows_staged(net.tensor(A.in_t).Cs, net.bf16) && (!rows_taken(A) || !rows_taken(B))) continue;  // large tensors: a launch matters little, fetching them in rows does
     LayerPlan& heavy = A.macs > B.macs ? A : B;
     LayerPlan& light = A.macs > B.macs ? B : A;
     const ConvPlan own = heavy.cp;
@@ -195,16 +201,13 @@ std::string build_plan(const daris_dnn& dnn, bool keep_activations, bool pair_la
                       L0.in_t == 0 && L0.res_t < 0 && L0.pair_with < 0 && only_reader && net.ingest.Cs == vec && dnn.in_c <= 4;
   }
   // how each dense convolution comes by its pixels, which the layers' links decide too
-  auto rows_taken = [&](const LayerPlan& L) {
-    const TensorInfo& in = net.tensor(L.in_t);
-    return conv_rows_take(in.H, in.W, in.Cs, (uint64_t)L.out.H * (uint64_t)L.out.W, L.out.Cs, L.Kpad, net.bf16);
-  };
   for (int l = 0; l < n; ++l) {
     LayerPlan& L = net.layers[l];
     if (L.d.op != DARIS_OP_CONV || L.depthwise) continue;
     const bool joint = L.pair_with >= 0 && !net.layers[L.pair_with].depthwise;
     if (l == 0 && net.fuse_ingest) plan_input(&L.cp, L.out.H, L.out.W, L.out.Cs, L.d.k, L.d.stride, plan_cus, net.bf16);
-    else plan_gather(&L.cp, net.tensor(L.in_t).Cs, rows_taken(L) && (!joint || (rows_taken(net.layers[L.pair_with]) && net.layers[L.pair_with].cp.staged)), net.bf16);
+    else if (joint) plan_gather(&L.cp, net.tensor(L.in_t).Cs, rows_taken(L) && rows_taken(net.layers[L.pair_with]) && net.layers[L.pair_with].cp.staged, net.bf16);
+    else plan_gather(&L.cp, net.tensor(L.in_t).Cs, rows_taken(L) || (L.cp.rows == 32 && L.cp.nw == 2 && rows_taken_large(L)), net.bf16);
     L.kernel_id = L.cp.kernel;
   }
   const TensorInfo& fin = net.layers[n - 1].out;

@@ -94,6 +94,30 @@ def test_three_taps_from_one_fetch_of_rows(cin, h, w, cout, dtype):
     assert e_max <= LAYER_TOL[dtype] and e_l2 <= LAYER_TOL[dtype] and (np.asarray(got)[np.asarray(want) == 0] == 0).all(), (e_max, e_l2)
 
 
+@pytest.mark.parametrize("dtype,c", [("fp32", 256), ("bf16", 512)])
+def test_tensors_of_more_than_2_GiB(dtype, c):
+    """1500 x 1500 pixels of 1024 bytes: written, read as a residual operand, by a 1x1 and by a 3x3 window; compared at the upper
+    and lower edge and around the byte 2^31."""
+    h = w = 1500
+    layers = [N.Layer(op=N.OP_CONV, c_in=1, c_out=32, k=1, stride=1, pad=0, act=1, in_from=-1),
+              N.Layer(op=N.OP_CONV, c_in=32, c_out=c, k=1, stride=1, pad=0, act=0, in_from=0),
+              N.Layer(op=N.OP_CONV, c_in=c, c_out=c, k=1, stride=1, pad=0, act=1, in_from=1, res_from=1),
+              N.Layer(op=N.OP_CONV, c_in=c, c_out=16, k=3, stride=1, pad=1, act=0, in_from=2)]
+    weights = [rand_w(L) for L in layers]
+    x = RNG.normal(0, 1, (1, h, w)).astype(np.float32)
+    with GpuNet(layers, weights, x.shape, dtype) as net:
+        got = np.asarray(net.forward(x)).reshape(16, h, w)
+        plans = [D.daris_get_launch_plan(net.task, i) for i in (1, 2, 3)]
+    assert [q["gather"] for q in plans] == [D.GATHER_ROWS, D.GATHER_ROWS, D.GATHER_TAPS]
+    middle = (1 << 31) // (1024 * w)
+    for a, b in ((0, 2), (middle - 1, middle + 2), (h - 2, h)):      # rows [a, b) of the output want one more on either side inside the image
+        a0, b0 = max(a - 1, 0), min(b + 1, h)
+        want = np.asarray(oracle_logits(layers, weights, x[:, a0:b0], dtype)).reshape(16, b0 - a0, w)[:, a - a0:b - a0]
+        e_max, e_l2 = rel_err(got[:, a:b], want)
+        tol = {"fp32": 4 * LAYER_TOL["fp32"], "bf16": 2e-2}[dtype]   # four layers' sums; their bf16 roundings
+        assert e_max <= tol and e_l2 <= tol, (a, e_max, e_l2)
+
+
 @pytest.mark.parametrize("dtype", ["fp32", "bf16"])
 @pytest.mark.parametrize("cin,h,w,cout,rows", [
     (192, 28, 28, 32, 16),    # a fifth of the partition's CUs with 32-pixel tiles

@@ -34,6 +34,25 @@ NOT_FOR_BLOCKS = [
 ]
 
 
+# (dtype, c_in, h, w, c_out, k, stride, pad, plan CUs), gather: tensors of 2 GiB and more, whose tiles lie within 2 GiB all the same
+LARGE_TENSORS = [
+    ((0, 256, 1500, 1500, 16, 3, 1, 1, 128), 5),
+    ((0, 256, 1500, 1500, 64, 1, 1, 0, 128), 3),
+    ((0, 256, 1500, 1500, 64, 3, 2, 1, 128), 3),
+    ((0, 32, 1500, 1500, 512, 1, 1, 0, 128), 3),
+    ((1, 512, 1500, 1500, 16, 3, 1, 1, 128), 5),
+    ((1, 512, 1500, 1500, 64, 1, 1, 0, 128), 3),
+    ((1, 32, 1500, 1500, 512, 1, 1, 0, 128), 3),
+]
+
+
+def test_large_tensors_are_fetched_in_whole_rows(plans):
+    for (s, gather), p in zip(LARGE_TENSORS, plans([s for s, _ in LARGE_TENSORS])):
+        assert p[0] == 1 and p[6] == gather, (s, p)
+    both = plans([(0, 256, 1500, 1500, 64, 3, 2, 1, 128, 64, 1, 2, 0)])[0]      # two that could share a launch, which has no kernel for them
+    assert both[0] == 1 and not both[5] and both[6] == 3, both
+
+
 def test_layers_that_the_64_pixel_tiles_cannot_take_keep_a_kernel(plans):
     for s, p in zip(NOT_FOR_BLOCKS, plans([(0,) + s for s in NOT_FOR_BLOCKS])):
         assert p[0] == 1 and p[2] != 64, (s, p)
