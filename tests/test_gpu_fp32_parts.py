@@ -132,19 +132,41 @@ def test_large_layers_that_block_tiles_cannot_take(case):
     assert err <= 5e-7, err
 
 
-# (cin, h, w, cout, k, stride, pad, plan_cus): the kernel that it runs
-NONFINITE_CASES = [
-    (3, 31, 29, 40, 3, 2, 1, 128),     # the network input as the caller gives it
-    (20, 13, 13, 40, 1, 1, 0, 128),    # pixels straight into registers, 32 x 32 tiles
-    (128, 14, 14, 128, 3, 1, 1, 16),   # staged rows
-    (128, 9, 7, 32, 3, 1, 1, 256),     # K split over workgroups, or 16-pixel tiles
-    (512, 7, 7, 512, 3, 1, 1, 128),    # 16-pixel tiles
-    (64, 41, 43, 64, 3, 1, 1, 32),     # 64 x 64 tiles
+# (cin, h, w, cout, k, stride, pad, plan_cus), pixels per wave tile, K split over workgroups, gather: every kernel that walks a tile again
+SECOND_WALK_CASES = [
+    ((3, 31, 29, 40, 3, 2, 1, 128), 32, 0, D.GATHER_INPUT),      # the network input as the caller gives it
+    ((3, 31, 29, 40, 3, 1, 1, 128), 32, 0, D.GATHER_IMAGE),      # ... in patches
+    ((20, 13, 13, 40, 1, 1, 0, 128), 32, 0, D.GATHER_GENERAL),   # pixels straight into registers
+    ((128, 29, 27, 128, 3, 2, 1, 16), 32, 0, D.GATHER_ROWS),     # whole rows, eight waves
+    ((16, 41, 43, 64, 1, 1, 0, 128), 32, 0, D.GATHER_ROWS),      # ... two, a single chunk between them
+    ((4096, 5, 5, 32, 1, 1, 0, 256), 32, 1, D.GATHER_ROWS),      # ... K split over workgroups
+    ((512, 9, 9, 32, 3, 2, 1, 256), 32, 1, D.GATHER_ROWS),
+    ((512, 7, 7, 512, 1, 1, 0, 128), 16, 0, D.GATHER_ROWS),
+    ((256, 14, 14, 512, 3, 2, 1, 128), 16, 0, D.GATHER_ROWS),
+    ((256, 23, 29, 64, 1, 1, 0, 8), 64, 0, D.GATHER_ROWS),
+    ((64, 48, 47, 128, 3, 2, 1, 8), 64, 0, D.GATHER_ROWS),
+    ((128, 14, 14, 128, 3, 1, 1, 16), 32, 0, D.GATHER_TAPS),
+    ((512, 5, 5, 32, 3, 1, 1, 256), 32, 1, D.GATHER_TAPS),
+    ((128, 9, 7, 32, 3, 1, 1, 256), 16, 0, D.GATHER_TAPS),
+    ((512, 7, 7, 512, 3, 1, 1, 128), 16, 0, D.GATHER_TAPS),
+    ((64, 41, 43, 64, 3, 1, 1, 32), 64, 0, D.GATHER_TAPS),
 ]
 
 
-@pytest.mark.parametrize("case", NONFINITE_CASES, ids=lambda c: "x".join(map(str, c)))
-def test_infinities_and_nan_pass_as_in_fp32_arithmetic(case):
+def _runs(plan, rows, split, gather):
+    return plan["rows"] == rows and (plan["splitk"] > 1) == bool(split) and plan["gather"] == gather
+
+
+@pytest.mark.parametrize("case,rows,split,gather", SECOND_WALK_CASES, ids=lambda c: "x".join(map(str, c)) if isinstance(c, tuple) else str(c))
+def test_small_pixels_keep_their_bits_in_every_kernel(case, rows, split, gather):
+    cin, h, w, cout, k, s, p, cus = case
+    err, plan = _conv(cin, h, w, cout, k, s, p, 1e-35, 1.0, plan_cus=cus)
+    assert _runs(plan, rows, split, gather), plan      # the case runs the kernel it names
+    assert err <= 5e-7, err
+
+
+@pytest.mark.parametrize("case,rows,split,gather", SECOND_WALK_CASES, ids=lambda c: "x".join(map(str, c)) if isinstance(c, tuple) else str(c))
+def test_infinities_and_nan_pass_as_in_fp32_arithmetic(case, rows, split, gather):
     cin, h, w, cout, k, s, p, cus = case
     rng = np.random.default_rng(11)
     x = rng.normal(0, 1, (cin, h, w)).astype(np.float32)
@@ -157,6 +179,7 @@ def test_infinities_and_nan_pass_as_in_fp32_arithmetic(case):
     L = [N.Layer(op=N.OP_CONV, c_in=cin, c_out=cout, k=k, stride=s, pad=p, act=0, in_from=-1)]
     with GpuNet(L, [(wt, b)], (cin, h, w), "fp32", plan_cus=cus) as g:
         got = g.forward(x).astype(np.float64).reshape(cout, -1)[1:]
+        assert _runs(D.daris_get_launch_plan(g.task, 0), rows, split, gather)
     want = torch.nn.functional.conv2d(torch.from_numpy(x).double()[None], torch.from_numpy(wt).double(), torch.from_numpy(b).double(),
                                       stride=s, padding=p).numpy().reshape(cout, -1)[1:]      # (channel 0: 0 * inf at the border)
     big = np.abs(want) > 1e30
@@ -164,6 +187,36 @@ def test_infinities_and_nan_pass_as_in_fp32_arithmetic(case):
     assert np.array_equal(got[np.isinf(want)], want[np.isinf(want)])
     for part in (np.isfinite(want) & ~big, np.isfinite(want) & big):
         assert np.linalg.norm(got[part] - want[part]) <= 5e-7 * max(np.linalg.norm(want[part]), 1e-30)
+
+
+# two convolutions on one tensor in one launch: (cin, h, w, cout, stride, plan_cus), pixels per wave tile
+@pytest.mark.parametrize("what", ["small", "infinite"])
+@pytest.mark.parametrize("case,rows", [((64, 28, 28, 64, 2, 16), 32), ((256, 14, 14, 512, 2, 128), 16)], ids=lambda c: "x".join(map(str, c)) if isinstance(c, tuple) else str(c))
+def test_second_walk_in_joint_launches(case, rows, what):
+    """A 3x3 convolution and a 1x1 one on the same tensor, and a depthwise 1x1 window over the first, one layer after the other as the
+    network's output, so that each of the two is seen by itself."""
+    cin, h, w, cout, s, cus = case
+    rng = np.random.default_rng(14)
+    x = rng.normal(0, 1, (cin, h, w)).astype(np.float32)
+    if what == "small":
+        x *= np.float32(1e-35)
+    else:
+        x[0, 0, 0], x[1, h // 2, w // 2], x[cin - 1, h - 2, w - 2] = np.inf, -np.inf, np.nan
+    pair = [N.Layer(op=N.OP_CONV, c_in=cin, c_out=cout, k=3, stride=s, pad=1, act=0, in_from=-1),
+            N.Layer(op=N.OP_CONV, c_in=cin, c_out=cout, k=1, stride=s, pad=0, act=0, in_from=-1)]
+    wts = [(rng.normal(0, np.sqrt(2.0 / (cin * L.k * L.k)), (cout, cin, L.k, L.k)).astype(np.float32), np.zeros(cout, np.float32)) for L in pair]
+    same = (np.ones((cout, 1, 1, 1), np.float32), np.zeros(cout, np.float32))
+    for i in (0, 1):
+        layers = pair + [N.Layer(op=N.OP_CONV, c_in=cout, c_out=cout, k=1, stride=1, pad=0, groups=cout, act=0, in_from=i)]
+        with GpuNet(layers, wts + [same], x.shape, "fp32", plan_cus=cus) as g:
+            got = g.forward(x).astype(np.float64)
+            plan = [D.daris_get_launch_plan(g.task, n) for n in (0, 1)]
+        assert plan[0]["pair_with"] == 1 and all(_runs(q, rows, 0, D.GATHER_ROWS) for q in plan), plan
+        want = torch.nn.functional.conv2d(torch.from_numpy(x).double()[None], torch.from_numpy(wts[i][0]).double(), stride=s, padding=pair[i].pad).numpy().ravel()
+        fin = np.isfinite(want)
+        assert np.array_equal(np.isnan(got), np.isnan(want)) and np.array_equal(got[np.isinf(want)], want[np.isinf(want)])
+        assert what == "small" or (np.isinf(want).any() and np.isnan(want).any())
+        assert np.linalg.norm(got[fin] - want[fin]) <= 5e-7 * np.linalg.norm(want[fin])
 
 
 def test_infinities_and_nan_through_a_fused_depthwise_layer():
@@ -189,19 +242,20 @@ def test_infinities_and_nan_through_a_fused_depthwise_layer():
     assert np.linalg.norm(got[fin] - want[fin]) <= 2e-6 * np.linalg.norm(want[fin])      # three layers of at most 32 terms in fp32
 
 
-def test_the_time_of_a_layer_is_bounded_whatever_its_input():
+@pytest.mark.parametrize("cin,hw,cout,k,gather", [(512, 28, 512, 3, D.GATHER_TAPS), (2048, 28, 512, 1, D.GATHER_ROWS)])
+def test_the_time_of_a_layer_is_bounded_whatever_its_input(cin, hw, cout, k, gather):
     """Stages are not preempted, so no frame may take a layer far longer than others do.  A frame through one layer whose
     sums all have to be taken again with fp32 products takes 2.4 times as long (the layer's matrix instructions: 1 + 8/3 times as
     long, plus what a frame costs besides); the bound leaves room for noise."""
-    cin = cout = 512
     rng = np.random.default_rng(13)
-    L = [N.Layer(op=N.OP_CONV, c_in=cin, c_out=cout, k=3, stride=1, pad=1, act=0, in_from=-1)]
-    wt = rng.normal(0, 0.02, (cout, cin, 3, 3)).astype(np.float32), np.zeros(cout, np.float32)
+    L = [N.Layer(op=N.OP_CONV, c_in=cin, c_out=cout, k=k, stride=1, pad=k // 2, act=0, in_from=-1)]
+    wt = rng.normal(0, 0.02, (cout, cin, k, k)).astype(np.float32), np.zeros(cout, np.float32)
     best = {}
-    with GpuNet(L, [wt], (cin, 28, 28), "fp32") as g:
+    with GpuNet(L, [wt], (cin, hw, hw), "fp32") as g:
+        assert D.daris_get_launch_plan(g.task, 0)["gather"] == gather
         y = torch.zeros(g.n_out, device="cuda")
         for what, v in (("ordinary", 1.0), ("infinite", float("inf")), ("nan", float("nan"))):
-            x = torch.randn((cin, 28, 28), device="cuda") * v
+            x = torch.randn((cin, hw, hw), device="cuda") * v
             torch.cuda.synchronize()
             for _ in range(10):
                 t0 = time.perf_counter()
