@@ -56,7 +56,9 @@ enum {
   DARIS_NO_PRIOR = 8,         /* ablation ("No Prior"): a missed predecessor gives no extra level              */
   DARIS_NO_FIXED = 16,        /* ablation ("No Fixed"): all stages share one level, EDF only                   */
   DARIS_HP_ADMISSION = 32,    /* Overload+HPA (Sec. VI-I): HP jobs must pass the test in their own context     */
-  DARIS_KEEP_ACTIVATIONS = 64, /* debugging: one buffer per layer output so daris_read_layer (daris_debug.h) works */
+  DARIS_KEEP_ACTIVATIONS = 64, /* debugging: one buffer per layer output so daris_read_layer (daris_debug.h) works;
+                                 the input is converted first, so the first convolution may run another kernel and
+                                 logits may differ from those without the flag by the rounding of its sums            */
   DARIS_WAVE_PRIORITY = 128,  /* the convolution waves of high-priority tasks raise their issue priority on the CU:
                                  where partitions overlap, HP stages run faster and LP stages slower (measured:
                                  HP response -5 %, LP +12 %, aggregate throughput -2 %); off by default          */

@@ -17,14 +17,15 @@ namespace daris {
 //
 // The NW waves of a workgroup own the same tile and split K, as in conv_wave_body: no barrier in the K loop, the pixel
 // rows pass through a corner of LDS of the wave's own (coalesced 64-byte rows in, matrix order out), two chunks of rows and
-// weights are in flight.  The four 32 x 32 blocks of the partial tiles are then summed in wave order, NT / 256 blocks at
-// a time, which bounds the LDS at 8, 16 and 64 KB for 2, 4 and 8 waves, and finished by the same epilogue.
+// weights are in flight (TAPS: the weights of three chunks, and one fetch of rows for them).  The four 32 x 32 blocks of the partial
+// tiles are then summed in wave order, NT / 256 blocks at a time, and finished by the same epilogue.  LDS for 2, 4 and 8 waves: 8, 16 and
+// 64 KB (TAPS: 10, 20 and 64, the corners being larger).
 //
 // TAPS: 3 x 3 windows with stride 1 and padding 1, where a tile's 64 pixels and their left and right neighbours are 66 consecutive
 // pixels of the input, whatever row of the image they lie in.  K is walked as (ky, 16 channels, kx): one fetch of the 66 rows
 // serves the three taps of a window's row, 23 load instructions for three chunks instead of 30, and these bind the walk together
-// with the matrix pipe (a CU's vector memory unit takes about twenty cycles for each, 1600 of the 1536 that eight waves' chunks
-// need on its four matrix pipes).  A neighbour on the other side of the image's edge is read from a row of zeros; above and below
+// with the matrix pipe (a CU's vector memory unit takes about twenty cycles for each: with ten loads a chunk 1600 cycles for eight waves' chunks,
+// which need 1536 on its four matrix pipes).  A neighbour on the other side of the image's edge is read from a row of zeros; above and below
 // the image the rows are offsets outside the tensor.  us on 128 CUs without and with: 50176 x 64 x
 // 576 48.0, 38.9; 12544 x 128 x 1152 41.7, 33.9; 3136 x 256 x 2304 41.3, 33.8; 784 x 512 x 4608 39.4, 31.8.
 template <int NW, bool TAPS>

@@ -698,7 +698,7 @@ __device__ __forceinline__ void conv_wave_body(const ConvArgs& p, const int mt, 
       return pack<BF16>(acc);
     };
     // more: another chunk follows, whose operands travel while this one goes through the matrix pipe.  Past the last chunk fp32 requests
-    // nothing: 28 loads of the CU's vector memory unit that a wave of one to three chunks pays for (12544 x 16 x 32 6.2 -> 5.05 us, 3136 x
+    // no pixels, taps or biases (the weights' refill, three loads from the slack behind them, stays): 28 loads of the CU's vector memory unit that a wave of one to three chunks pays for (12544 x 16 x 32 6.2 -> 5.05 us, 3136 x
     // 24 x 96 6.33 -> 6.27, 3136 x 24 x 144 7.05 -> 6.88 on 128 CUs).  bf16, whose chunks go in twos, takes 70 registers more that way.
     auto chunk_dw = [&](int cs, bool more) {
 #pragma unroll

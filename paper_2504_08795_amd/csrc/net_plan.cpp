@@ -333,7 +333,7 @@ void pack_conv(const NetPlan& net, const LayerPlan& L, const float* w, const flo
     const int R = L.cp.rows == 16 ? 16 : 32, ck = R == 16 ? 32 : 16, nch = L.Kpad / ck;
     const int nblocks = (L.out.Cs + R - 1) / R;
     const int nb_alloc = (nblocks + L.cp.tn - 1) / L.cp.tn * L.cp.tn;
-    wp->assign((size_t)nb_alloc * nch * 3 * 1024 + 12 * 1024, 0);  // + slack for the pipeline's refills past the last chunk
+    wp->assign((size_t)nb_alloc * nch * 3 * 1024 + 12 * 1024, 0);  // + slack for refills past the last chunk (32- and 64-pixel tiles)
     uint16_t* out = reinterpret_cast<uint16_t*>(wp->data());
     for (int o = 0; o < d.c_out; ++o)
       for (int ci = 0; ci < d.c_in; ++ci)
@@ -353,7 +353,7 @@ void pack_conv(const NetPlan& net, const LayerPlan& L, const float* w, const flo
     const int vec = bf ? 8 : 4, ks = 4 * vec, S = L.cp.S;
     const int nblocks = (L.out.Cs + 15) / 16;
     const int nb_alloc = (nblocks + L.cp.tn - 1) / L.cp.tn * L.cp.tn;
-    wp->assign((size_t)nb_alloc * S * 64 * 16 + 8 * 1024, 0);  // + slack for the pipeline's refills past the last step
+    wp->assign((size_t)nb_alloc * S * 64 * 16, 0);  // (nothing is requested past the last step)
     for (int o = 0; o < d.c_out; ++o)
       for (int ci = 0; ci < d.c_in; ++ci)
         for (int t = 0; t < kk; ++t) {
