@@ -7,9 +7,8 @@
 
 namespace daris {
 
-template <bool BF16, int WN, int NW, int MODE>
-__global__ __launch_bounds__(NW * 64) void conv_wave_kernel(const ImageConvArgs) {
-  static_assert(MODE == 6 && NW == 4, "the other gather modes have their own code objects");
+template <bool BF16, int WN>
+__global__ __launch_bounds__(256) void conv_image_kernel(const ImageConvArgs) {
   ImageConvArgs p = grab<ImageConvArgs>((ConstPtr)__builtin_amdgcn_kernarg_segment_ptr());
   args_in_memory(p);
   __shared__ __align__(16) float lds[conv_image_lds<BF16>()];
@@ -17,9 +16,9 @@ __global__ __launch_bounds__(NW * 64) void conv_wave_kernel(const ImageConvArgs)
   puts_done();
 }
 
-template __global__ void conv_wave_kernel<false, 1, 4, 6>(const ImageConvArgs);
-template __global__ void conv_wave_kernel<false, 2, 4, 6>(const ImageConvArgs);
-template __global__ void conv_wave_kernel<true, 1, 4, 6>(const ImageConvArgs);
-template __global__ void conv_wave_kernel<true, 2, 4, 6>(const ImageConvArgs);
+template __global__ void conv_image_kernel<false, 1>(const ImageConvArgs);
+template __global__ void conv_image_kernel<false, 2>(const ImageConvArgs);
+template __global__ void conv_image_kernel<true, 1>(const ImageConvArgs);
+template __global__ void conv_image_kernel<true, 2>(const ImageConvArgs);
 
 }  // namespace daris

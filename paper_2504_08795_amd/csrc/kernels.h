@@ -68,7 +68,6 @@ struct ConvArgs {
 };
 
 // The first convolution of a network for conv_image_body: x is the network input as the caller gives it, float [c_real][H][W].
-// One size with ConvArgs.
 struct ImageConvArgs {
   const void* x;
   const void* w;  // as ConvArgs::w
@@ -80,7 +79,7 @@ struct ImageConvArgs {
   int patch_w, patch;  // input pixels of a tile: a row of them, all
   int phase, pitch;    // places between columns of a row that differ by one (mod stride), between rows
   uint32_t mg_tiles, mg_across, mg_patch_w, mg_stride, mg_wo, mg_k;  // multipliers for division
-  int unused[7];
+  int unused[7];  // to one of the sizes that grab() reads
 };
 constexpr int kImageCols = 16;     // output pixels of a tile's row
 constexpr int kImagePatch = 864;   // places for the input pixels of a tile

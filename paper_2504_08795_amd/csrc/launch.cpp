@@ -280,7 +280,7 @@ struct ConvDwArgs {  // conv_wave_dw_kernel(p, d)
   ConvArgs p;
   DwFusedArgs d;
 };
-static_assert(sizeof(ImageConvArgs) == sizeof(ConvArgs) && offsetof(ImageConvArgs, x) == kConvInputOffset, "one argument block for every convolution");
+static_assert(sizeof(ImageConvArgs) == 160 && offsetof(ImageConvArgs, x) == kConvInputOffset, "the input is where every convolution has it");
 constexpr uint32_t kIngestBytes = 28, kProbeBytes = 12, kPairBytes = 2 * sizeof(ConvArgs) + 4;
 static_assert(sizeof(DwFusedArgs) == 32 && sizeof(ConvDwArgs) == 192 && offsetof(ConvDwArgs, d) == sizeof(ConvArgs), "fused depthwise arguments");
 static_assert(sizeof(ConvArgs) == 160 && sizeof(DwArgs) == 72 && sizeof(PoolArgs) == 48 && sizeof(FcArgs) == 56 && sizeof(ReduceArgs) == 48 && sizeof(DwWindowArgs) == 88 && sizeof(PoolWindowArgs) == 64,
@@ -319,16 +319,16 @@ std::string KernelTable::resolve(const AqlRuntime& rt) {
     for (int v = 0; v < 6; ++v) {
       const std::string tp = B + ", " + std::to_string(tn_[v]) + ", " + std::to_string(nw_[v]) + ", ";
       // (fp32 has no kGatherAligned: what it would gain, a walk in scalars, kGatherGeneral does in closed form for quads of channels)
-      if (taps_kernel(32, b, tn_[v], nw_[v]) != K_NONE) taps[b][v] = get("daris::conv_wave_kernel<" + tp + "5>", sizeof(ConvArgs));
+      if (taps_kernel(32, b, tn_[v], nw_[v]) != K_NONE) taps[b][v] = get("daris::conv_taps_kernel<" + B + ", " + std::to_string(tn_[v]) + ", " + std::to_string(nw_[v]) + ">", sizeof(ConvArgs));
       for (int m = b ? 0 : 1; m < 4; ++m) conv[b][v][m] = get("daris::conv_wave_kernel<" + tp + std::to_string(m) + ">", sizeof(ConvArgs));
       static const int pair_modes[3] = {0, 1, 3};
       for (int m = b ? 0 : 1; m < 3; ++m) pair[b][v][m] = get("daris::conv_wave_pair_kernel<" + tp + std::to_string(pair_modes[m]) + ">", kPairBytes);
     }
     for (int v = 0; v < 4; ++v) large[b][v / 2][v % 2] = get((v < 2 ? "daris::conv_large_kernel<" : "daris::conv_taps_large_kernel<") + B + ", " + std::to_string(v % 2 + 1) + ">", sizeof(ConvArgs));
-    for (int v = 0; v < 2; ++v) image[b][v] = get("daris::conv_wave_kernel<" + B + ", " + std::to_string(v + 1) + ", 4, 6>", sizeof(ImageConvArgs));
+    for (int v = 0; v < 2; ++v) image[b][v] = get("daris::conv_image_kernel<" + B + ", " + std::to_string(v + 1) + ">", sizeof(ImageConvArgs));
     for (int v = 0; v < 6; ++v) {
       for (int t = 0; t < (taps_kernel(16, b, tn_[v], nw_[v]) != K_NONE ? 2 : 1); ++t)
-        conv16[b][t][v] = get("daris::conv_wave16_kernel<" + B + ", " + std::to_string(tn_[v]) + ", " + std::to_string(nw_[v]) + (t ? ", 5>" : ">"), sizeof(ConvArgs));
+        conv16[b][t][v] = get((t ? "daris::conv_taps16_kernel<" : "daris::conv_wave16_kernel<") + B + ", " + std::to_string(tn_[v]) + ", " + std::to_string(nw_[v]) + ">", sizeof(ConvArgs));
       pair16[b][v] = get("daris::conv_wave16_pair_kernel<" + B + ", " + std::to_string(tn_[v]) + ", " + std::to_string(nw_[v]) + ">", kPairBytes);
       if (b ? nw_[v] != 8 : tn_[v] == 1)
         convdw[b][v] = get("daris::conv_wave_dw_kernel<" + B + ", " + std::to_string(tn_[v]) + ", " + std::to_string(nw_[v]) + ">", sizeof(ConvDwArgs));

@@ -7,9 +7,8 @@
 
 namespace daris {
 
-template <bool BF16, int TN, int NW, int MODE>
-__global__ __launch_bounds__(NW * 64) void conv_wave_kernel(const ConvArgs) {
-  static_assert(MODE == 5, "the other gather modes have their own code object");
+template <bool BF16, int TN, int NW>
+__global__ __launch_bounds__(NW * 64) void conv_taps_kernel(const ConvArgs) {
   const ConvArgs p = conv_args_at((ConstPtr)__builtin_amdgcn_kernarg_segment_ptr());
   __shared__ __align__(16) float red[conv_taps_lds<BF16, 32, TN, NW>()];
   int mt, g;
@@ -18,9 +17,8 @@ __global__ __launch_bounds__(NW * 64) void conv_wave_kernel(const ConvArgs) {
   puts_done();
 }
 
-template <bool BF16, int TB, int NW, int MODE>
-__global__ __launch_bounds__(NW * 64, NW == 8 ? 4 : 1) void conv_wave16_kernel(const ConvArgs) {
-  static_assert(MODE == 5, "the other gather modes have their own code object");
+template <bool BF16, int TB, int NW>
+__global__ __launch_bounds__(NW * 64, NW == 8 ? 4 : 1) void conv_taps16_kernel(const ConvArgs) {
   const ConvArgs p = conv_args_at((ConstPtr)__builtin_amdgcn_kernarg_segment_ptr());
   __shared__ __align__(16) float red[conv_taps_lds<BF16, 16, TB, NW>()];
   int mt, g;
@@ -43,10 +41,10 @@ __global__ __launch_bounds__(128) void conv_taps_large_kernel(const ConvArgs) {
 // The tiles and numbers of waves that the planner arrives at (taps_kernel in launch.cpp).  For 32 pixels these are two, four or eight in fp32 (not
 // four with 64 channels: what would have them has too few groups of taps, or 64 x 64 tiles), two or four in bf16; for 16 pixels
 // eight in fp32, four or eight in bf16.
-#define DARIS_INST_TAPS(B, T, W) template __global__ void conv_wave_kernel<B, T, W, 5>(const ConvArgs);
+#define DARIS_INST_TAPS(B, T, W) template __global__ void conv_taps_kernel<B, T, W>(const ConvArgs);
 #define DARIS_INST_TAPS16(B, W) \
-  template __global__ void conv_wave16_kernel<B, 1, W, 5>(const ConvArgs); \
-  template __global__ void conv_wave16_kernel<B, 2, W, 5>(const ConvArgs);
+  template __global__ void conv_taps16_kernel<B, 1, W>(const ConvArgs); \
+  template __global__ void conv_taps16_kernel<B, 2, W>(const ConvArgs);
 DARIS_INST_TAPS(false, 1, 2) DARIS_INST_TAPS(false, 1, 4) DARIS_INST_TAPS(false, 1, 8) DARIS_INST_TAPS(false, 2, 2) DARIS_INST_TAPS(false, 2, 8)
 DARIS_INST_TAPS(true, 1, 2) DARIS_INST_TAPS(true, 1, 4) DARIS_INST_TAPS(true, 2, 2) DARIS_INST_TAPS(true, 2, 4)
 DARIS_INST_TAPS16(false, 8)

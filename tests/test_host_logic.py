@@ -508,8 +508,8 @@ DEVICE_KERNELS = {
     "daris_kernels": {"conv_wave_kernel": (160, 42), "conv_wave_pair_kernel": (324, 30), "conv_wave16_kernel": (160, 12), "conv_wave16_pair_kernel": (324, 12), "conv_wave_dw_kernel": (192, 7), "conv_large_kernel": (160, 4),
                       "splitk_reduce_kernel": (48, 2), "dwconv_kernel": (72, 2), "maxpool_kernel": (48, 2), "gavgpool_kernel": (48, 2), "fc_kernel": (56, 2), "ingest_kernel": (28, 2),
                       "egress_kernel": (28, 2), "cu_probe_kernel": (12, 1)},
-    "daris_taps_kernels": {"conv_wave_kernel": (160, 9), "conv_wave16_kernel": (160, 6), "conv_taps_large_kernel": (160, 4)},
-    "daris_image_kernels": {"conv_wave_kernel": (160, 4)},
+    "daris_taps_kernels": {"conv_taps_kernel": (160, 9), "conv_taps16_kernel": (160, 6), "conv_taps_large_kernel": (160, 4)},
+    "daris_image_kernels": {"conv_image_kernel": (160, 4)},
     "daris_block_kernels": {"conv_block_kernel": (160, 6)},
     "daris_point_kernels": {"dwconv_window_kernel": (88, 2), "maxpool_window_kernel": (64, 4)},
 }
