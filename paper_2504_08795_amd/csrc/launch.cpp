@@ -229,12 +229,12 @@ ConvPlan plan_conv(int M, int N, int Kpad, int bf16, int step_align, int cin_str
   // 4.26 -> 3.41, 49 x 160 x 576 4.21 -> 3.35, 784 x 32 x 192 (25) 2.95 -> 2.60, 49 x 960 x 160 (60) 3.10 -> 2.83; bf16 2.37 -> 2.13, 2.68 -> 2.39,
   // 2.68 -> 2.32; 64 and 192 CUs alike.  Between half of the partition and all of it a short K gains (196 x 384 x 64, 84 tiles,
   // 2.73 -> 2.35; 196 x 576 x 96, 126, 2.97 -> 2.80), a longer one does not (784 x 128 x 512, 100, 4.10 -> 4.42; 196 x 1024 x 256 3.99 -> 4.54).
-  // A single channel tile with a short K gains too (196 x 32 x 64, 7 tiles, 2.53 -> 2.02; 2304 x 16 x 96, 72, 2.80 -> 2.56; 3136 x 64 x 64, 98 of 64
-  // channels, 3.17 -> 2.46; bf16 196 x 32 x 128 2.18 -> 1.83, 3136 x 32 x 128 2.26 -> 2.06), but 32 channels with K = 128 in fp32 on few tiles only
-  // (784 x 32 x 128, 25, 2.70 -> 2.40; 2304, 72, 2.80 -> 2.77; 3136, 98, 2.81 -> 2.92).  A launch of one tile stays (9 x 20 x 128 2.45, 2.32).
-  // (Where the depthwise layer in front joins the launch, build_plan plans 32-pixel tiles anew.)
-  const bool half = Kpad > 128 || (pl.NTn == 1 && pl.tn == 1 && !bf16 && Kpad == 128), single = Kpad <= 128 && pl.NTn == 1 && pl.tiles == 1;
-  const bool idle = pl.tiles <= (half ? nominal_cus / 2 : nominal_cus) && !single;
+  // A single channel tile with a short K is taken up to half of the partition as well: there it gains with every K (196 x 32 x 64, 7 tiles, 2.53 ->
+  // 2.02, 784 x 32 x 128, 25, 2.70 -> 2.40, bf16 2.22 -> 1.86), beyond less and less (2304 x 32 x 64, 72, 2.61 -> 2.29, x 128 2.80 -> 2.77; 3136, 98,
+  // 2.64 -> 2.31 and 2.81 -> 2.92), and there the depthwise layer in front may join the launch, which 32-pixel tiles are for.  A launch of one tile
+  // stays (9 x 20 x 128 2.45, 2.32).
+  const bool narrow = pl.NTn == 1 && Kpad <= 128;
+  const bool idle = pl.tiles <= (Kpad > 128 || narrow ? nominal_cus / 2 : nominal_cus) && !(narrow && pl.tiles == 1);
   if ((pl.splitk > 1 || idle) && cin_stride > 0 && cin_stride % (bf16 ? 32 : 16) == 0) {
     const ConvPlan p16 = plan_conv_wave16(M, N, Kpad, bf16, nominal_cus, three_taps == kTaps);
     if (p16.kernel != K_NONE) return p16;

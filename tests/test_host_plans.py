@@ -140,15 +140,13 @@ def test_first_layers_in_patches_or_gathered(plans):
 # (dtype, c_in, h, w, c_out, k, stride, pad, plan CUs), pixels per wave tile: 1x1 convolutions with a short K and a single channel tile
 SINGLE_CHANNEL_TILE = [
     ((0, 64, 14, 14, 32, 1, 1, 0, 128), 16),
-    ((0, 96, 48, 48, 16, 1, 1, 0, 128), 16),
-    ((0, 96, 56, 56, 24, 1, 1, 0, 96), 32),     # 98 tiles on 96 CUs
-    ((0, 64, 56, 56, 64, 1, 1, 0, 128), 16),    # ... of 64 channels
     ((0, 128, 28, 28, 32, 1, 1, 0, 128), 16),
-    ((0, 128, 56, 56, 32, 1, 1, 0, 128), 32),   # K = 128 in fp32: more tiles than half of the CUs
-    ((0, 128, 56, 56, 64, 1, 1, 0, 128), 16),
-    ((0, 64, 5, 6, 32, 1, 1, 0, 128), 32),      # one tile
+    ((0, 96, 32, 64, 24, 1, 1, 0, 128), 16),    # 64 tiles on 128 CUs
+    ((0, 96, 32, 65, 24, 1, 1, 0, 128), 32),    # 65
+    ((0, 64, 56, 56, 64, 1, 1, 0, 128), 32),    # 98 of 64 channels
+    ((0, 64, 5, 6, 32, 1, 1, 0, 128), 32),      # one
     ((1, 128, 14, 14, 32, 1, 1, 0, 128), 16),
-    ((1, 128, 56, 56, 32, 1, 1, 0, 128), 16),
+    ((1, 128, 56, 56, 32, 1, 1, 0, 128), 32),
     ((1, 128, 3, 3, 20, 1, 1, 0, 128), 32),
 ]
 
