@@ -116,7 +116,8 @@ def test_three_taps_from_one_fetch_of_rows(cin, h, w, cout):
     L = [N.Layer(op=N.OP_CONV, c_in=cin, c_out=cout, k=3, stride=1, pad=1, act=0, in_from=-1)]
     with GpuNet(L, [(wt, None)], (cin, h, w), "fp32", plan_cus=8) as g:
         got = g.forward(x).astype(np.float64).reshape(cout, h, w)
-        assert D.daris_get_launch_plan(g.task, 0)["rows"] == 64
+        plan = D.daris_get_launch_plan(g.task, 0)
+        assert plan["rows"] == 64 and plan["gather"] == D.GATHER_TAPS      # the case runs the kernel it names
     want = torch.nn.functional.conv2d(torch.from_numpy(x).double()[None], torch.from_numpy(wt).double(), padding=1).numpy()[0]
     bound = torch.nn.functional.conv2d(torch.from_numpy(x).double()[None], torch.from_numpy(wt).double().abs(), padding=1).numpy()[0]
     assert (np.abs(got - want) <= 2.0 ** -22 * bound).all()      # products to 2^-23 each, at most a few of them in a sum

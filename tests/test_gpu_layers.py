@@ -89,7 +89,8 @@ def test_three_taps_from_one_fetch_of_rows(cin, h, w, cout, dtype):
     want = oracle_logits(layers, weights, x.reshape(cin, h, w), dtype)
     with GpuNet(layers, weights, (cin, h, w), dtype) as net:
         got = net.forward(x.reshape(cin, h, w))
-        assert D.daris_get_launch_plan(net.task, 0)["rows"] in (16, 32)
+        plan = D.daris_get_launch_plan(net.task, 0)
+        assert plan["rows"] in (16, 32) and plan["gather"] == D.GATHER_TAPS      # the case runs the kernel it names
     e_max, e_l2 = rel_err(got, want)
     assert e_max <= LAYER_TOL[dtype] and e_l2 <= LAYER_TOL[dtype] and (np.asarray(got)[np.asarray(want) == 0] == 0).all(), (e_max, e_l2)
 
