@@ -671,8 +671,10 @@ def test_bench_roofline_helpers():
         else:
             assert r["bound"] == "hbm" and r["peak"] == 8000.0 and r["achieved"] is None, name
     assert i > 30
-    for config, kernels in ((4, ("conv_wave_f32_t2w8", "conv_wave_f32_t1w8", "conv_wave64_f32_t2w2", "conv_wave64_f32_t2w4", "conv_wave64_f32_t2w8", "fc")), (3, ("conv_wave_bf16_t2w4", "conv_wave16_bf16_t2w4")),
-                            (2, ("conv_wave16_f32_t1w8", "conv_wave_f32_t2w8"))):
+    for config, kernels in ((4, ("conv_wave_f32_t2w8", "conv_wave_f32_t1w8", "conv_wave_taps_f32_t1w8", "conv_wave_taps_f32_t2w8", "conv_wave16_taps_f32_t1w8", "conv_wave16_taps_f32_t2w8",
+                                 "conv_wave64_taps_f32_t2w2", "conv_wave64_taps_f32_t2w4", "conv_wave64_taps_f32_t2w8", "fc")),
+                            (3, ("conv_wave_bf16_t2w4", "conv_wave_bf16_t1w4", "conv_wave16_bf16_t2w4", "conv_wave16_taps_bf16_t1w8", "conv_wave16_taps_bf16_t2w8")),
+                            (2, ("conv_wave16_f32_t1w8", "conv_wave16_taps_f32_t1w8", "conv_wave16_taps_f32_t2w8", "conv_wave_taps_f32_t2w8"))):
         for k in kernels:
             t = bench.read_traffic(config, k)
             assert isinstance(t, int) and t > 10_000, (config, k, t)
