@@ -218,8 +218,6 @@ __global__ __launch_bounds__(64) void cu_probe_kernel(uint32_t* out, int spin) {
   DARIS_INST_CONV(B, 1, 2) DARIS_INST_CONV(B, 1, 4) DARIS_INST_CONV(B, 1, 8)                        \
   DARIS_INST_CONV(B, 2, 2) DARIS_INST_CONV(B, 2, 4) DARIS_INST_CONV(B, 2, 8)                        \
   DARIS_INST_CONV16(B, 1) DARIS_INST_CONV16(B, 2)                                                   \
-  template __global__ void conv_large_kernel<B, 1>(const ConvArgs);                                 \
-  template __global__ void conv_large_kernel<B, 2>(const ConvArgs);                                 \
   template __global__ void splitk_reduce_kernel<B>(const float*, const float*, const void*, void*, int, int, int, int); \
   template __global__ void dwconv_kernel<B>(const DwArgs);                                         \
   template __global__ void maxpool_kernel<B>(const PoolArgs);                                      \
@@ -236,6 +234,11 @@ DARIS_INST_CONV_ALIGNED(2, 2) DARIS_INST_CONV_ALIGNED(2, 4) DARIS_INST_CONV_ALIG
 // does not provide.
 DARIS_INST_CONVDW(false, 1, 2) DARIS_INST_CONVDW(false, 1, 4) DARIS_INST_CONVDW(false, 1, 8)
 DARIS_INST_CONVDW(true, 1, 2) DARIS_INST_CONVDW(true, 1, 4) DARIS_INST_CONVDW(true, 2, 2) DARIS_INST_CONVDW(true, 2, 4)
+// (Behind the others: where a kernel's code lies shows in the shortest launches, the small network's FC layer 2.48 us or 2.60.)
+template __global__ void conv_large_kernel<false, 1>(const ConvArgs);
+template __global__ void conv_large_kernel<false, 2>(const ConvArgs);
+template __global__ void conv_large_kernel<true, 1>(const ConvArgs);
+template __global__ void conv_large_kernel<true, 2>(const ConvArgs);
 #undef DARIS_INST_CONVDW
 #undef DARIS_INST_ALL
 #undef DARIS_INST_CONV
