@@ -317,7 +317,7 @@ __global__ __launch_bounds__(NW * 64) void conv_block_kernel(const ConvArgs) {
   park(0);
   if (TAPS && __builtin_expect(m0 + 64 > p.M, 0)) {
 #pragma unroll
-    for (int k = 0; k < 4; ++k) drop_pixels<32>(acc[k], p.M - m0 - 32 * (k >> 1));
+    for (int k = 0; k < 4; ++k) drop_pixels(acc[k], p.M - m0 - 32 * (k >> 1));
   }
   spoil_unless_in_range(acc, red + wave * BPP * 1024, BPP * 16);
   __syncthreads();

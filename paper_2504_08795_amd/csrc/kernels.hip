@@ -234,7 +234,6 @@ DARIS_INST_CONV_ALIGNED(2, 2) DARIS_INST_CONV_ALIGNED(2, 4) DARIS_INST_CONV_ALIG
 // does not provide.
 DARIS_INST_CONVDW(false, 1, 2) DARIS_INST_CONVDW(false, 1, 4) DARIS_INST_CONVDW(false, 1, 8)
 DARIS_INST_CONVDW(true, 1, 2) DARIS_INST_CONVDW(true, 1, 4) DARIS_INST_CONVDW(true, 2, 2) DARIS_INST_CONVDW(true, 2, 4)
-// (Behind the others: where a kernel's code lies shows in the shortest launches, the small network's FC layer 2.48 us or 2.60.)
 template __global__ void conv_large_kernel<false, 1>(const ConvArgs);
 template __global__ void conv_large_kernel<false, 2>(const ConvArgs);
 template __global__ void conv_large_kernel<true, 1>(const ConvArgs);

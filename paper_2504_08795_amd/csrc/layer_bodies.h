@@ -84,17 +84,16 @@ __device__ __forceinline__ bool out_of_range(const Acc (&acc)[N]) {
   return __builtin_expect(__ballot(__builtin_amdgcn_classf(largest * 0x1p-23f, kNanInfDenormal)) != 0, 0) &&
          (__ballot(!(largest < INFINITY)) != 0 || __ballot(largest >= 0x1p-103f) == 0);
 }
-// Kernels that load real neighbours for the pixels of a tile that lie past the output first set the sums of these to 0: nobody stores them, and
-// one of ordinary size would keep a tile of small sums from being walked again.  One comparison with a constant and one select a sum, behind a
-// branch that most tiles do not take: fp32 layers whose last tile is ragged take 0.05 us longer for it.  (Zeros in place of the
-// neighbours take 0.02 us, but those whose tiles are whole as well: ResNet-18's frame 133.3 -> 134.2 us, saturated 0.9 % less.)
-// Tiles of 16 pixels, few of which are whole on the maps that they are for, have no branch (0.02 us instead of 0.03).
+// Kernels that load real neighbours for the pixels of a tile that lie past the output keep these out of the test: nobody stores their sums, and
+// one of ordinary size would keep a tile of small sums from being walked again.  Where lanes find their pixels in LDS by a place (conv_taps_body,
+// conv_image_body), such a pixel is the place of zeros, chosen in a branch that whole tiles do not take, while the first loads are on their way.
+// The 64 x 64 tiles, whose lanes have one place for several pixels, set the sums to 0 before the test: one comparison with a constant and one
+// select a sum, behind such a branch; tiles of 32 pixels took 0.05 to 0.17 us longer that way.
 // inside: how many of the block's pixels lie inside the output.
-template <int R, typename Acc>
-__device__ __forceinline__ void drop_pixels(Acc& acc, const int inside) {
-  const int lane = threadIdx.x & 63, left = inside - (R == 32 ? (lane >> 5) * 4 : (lane >> 4) * 4);
+__device__ __forceinline__ void drop_pixels(f32x16& acc, const int inside) {
+  const int left = inside - ((threadIdx.x & 63) >> 5) * 4;
 #pragma unroll
-  for (int v = 0; v < R * R / 64; ++v) acc[v] = (R == 32 ? (v >> 2) * 8 + (v & 3) : v) < left ? acc[v] : 0.f;
+  for (int v = 0; v < 16; ++v) acc[v] = (v >> 2) * 8 + (v & 3) < left ? acc[v] : 0.f;
 }
 template <int N, typename Acc>
 __device__ __forceinline__ void spoil_unless_in_range(const Acc (&acc)[N], float* const tile, const int words) {
@@ -295,10 +294,6 @@ struct WaveEpilogue {
     };
     park();
     if constexpr (!BF16) {
-      if (MODE == kGatherTaps && (R == 16 || __builtin_expect(m0 + R > p.M, 0))) {
-#pragma unroll
-        for (int j = 0; j < TN; ++j) drop_pixels<R>(acc[j], p.M - m0);
-      }
       spoil_unless_in_range(acc, red + wave * TILE, V * TN);
     }
     __syncthreads();
@@ -1054,7 +1049,7 @@ __device__ __forceinline__ void conv_taps_body(const ConvArgs& p, const int mt, 
     return BF16 ? place * 4 + (lh ^ ((place >> 1) & 3)) : place * 2 + ((lh & 1) ^ ((place >> 2) & 1));
   };
   const int m = m0 + li, x = m - fast_div(m, p.mg_wo) * p.Wo;
-  const int at[3] = {x == 0 ? row_at(kZeros) : row_at(li), row_at(li + 1), x == p.Wo - 1 ? row_at(kZeros) : row_at(li + 2)};
+  int at[3] = {x == 0 ? row_at(kZeros) : row_at(li), row_at(li + 1), x == p.Wo - 1 ? row_at(kZeros) : row_at(li + 2)};
   // lanes exchange data through the wave's buffer: order the accesses of the whole wave, not only of each lane
   auto wave_order = [&]() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -1092,6 +1087,12 @@ __device__ __forceinline__ void conv_taps_body(const ConvArgs& p, const int mt, 
   if (nsteps > 0) {
     load_rows();
     static_for<0, 3>(load_w);
+    // (A pixel past the output is a pixel of zeros: see drop_pixels.  25 x 512 x 4608 with K split over 240 CUs: 7.05 us with the neighbours' sums,
+    // 7.22 with sums dropped, 7.10 so.)
+    if (!BF16 && __builtin_expect(m0 + R > p.M, 0)) {
+#pragma unroll
+      for (int k = 0; k < 3; ++k) at[k] = m < p.M ? at[k] : row_at(kZeros);
+    }
     for (int groups = nsteps / 6; groups > 1; --groups) static_for<0, 3>([&](auto kx) { chunk(kx, std::true_type()); });
     if constexpr (LATE) fin.fetch(p, m0, nb0, tid);
     static_for<0, 3>([&](auto kx) { chunk(kx, std::false_type()); });
