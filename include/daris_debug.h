@@ -19,7 +19,8 @@ extern "C" {
  * per workgroup, [9] K steps in total, [10] per workgroup slice, [11] per wave, [12] split-K factor, [13] pixel tiles,
  * [14] channel tiles, [15] weight groups, [16] workgroup order mode, [17..19] grid x y z, [20] threads per workgroup,
  * [21] split-K workspace bytes, [22] layer it shares a launch with or -1, [23] 1 = the joint launch is issued at this
- * layer, [24] activation slot of the layer's output (-1: the caller's logits), [25] slot of its input, [26] slot of its
+ * layer (a convolution that names a pooling layer here is computed and pooled in that layer's launch, whose kernel id is that layer's),
+ * [24] activation slot of the layer's output (-1: the caller's logits, or never stored), [25] slot of its input, [26] slot of its
  * residual operand or -1.  A slot is a device buffer shared by tensors whose lifetimes do not overlap.  [27] how the waves come by their
  * pixels: 0 straight into registers, no K step straddles a filter tap, 1 the same for any channel count, 2 the network input as the
  * caller gives it straight into registers, 3 whole 64-byte rows, 4 computed from the input of the depthwise layer that shares the

@@ -10,6 +10,8 @@ LIB = os.path.join(HERE, "libdaris.so")
 # device source -> symbol prefix of its code object in the library
 DEVICE_SOURCES = {"kernels.hip": "daris_kernels", "taps_kernels.hip": "daris_taps_kernels", "image_kernels.hip": "daris_image_kernels", "block_kernels.hip": "daris_block_kernels",
                   "point_kernels.hip": "daris_point_kernels"}
+# ... of the kernels that compute several layers in a row
+JOINED_SOURCES = {"joined_kernels.hip": "daris_joined_kernels"}
 HOST_SOURCES = ["aql.cpp", "launch.cpp", "sched_core.cpp", "net_plan.cpp", "daris_api.cpp"]
 COMMON = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-Wall", "-Wno-unused-function"]
 # no packed fp32 arithmetic in device code (some forms have given wrong results on this hardware)
@@ -38,7 +40,7 @@ def _run(cmd, verbose):
 def build(verbose: bool = False) -> str:
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     asm = ""
-    for src, name in DEVICE_SOURCES.items():
+    for src, name in {**DEVICE_SOURCES, **JOINED_SOURCES}.items():
         code_object = os.path.join(CSRC, name + ".co")
         _run([hipcc] + DEVICE_FLAGS + ["-c", os.path.join(CSRC, src), "-o", code_object], verbose)
         asm += BLOB_ASM.format(name=name, path=code_object)

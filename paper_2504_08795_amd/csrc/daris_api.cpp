@@ -42,6 +42,8 @@ extern "C" const char daris_image_kernels_co[];
 extern "C" const char daris_image_kernels_co_end[];
 extern "C" const char daris_block_kernels_co[];
 extern "C" const char daris_block_kernels_co_end[];
+extern "C" const char daris_joined_kernels_co[];
+extern "C" const char daris_joined_kernels_co_end[];
 extern "C" const char daris_point_kernels_co[];
 extern "C" const char daris_point_kernels_co_end[];
 
@@ -216,6 +218,7 @@ bool on_own_device(const void* p) {
 // The loaded code object and its kernels: set up by the first daris_init with a device and kept until the process ends.
 AqlRuntime g_rt;
 KernelTable g_kt;
+JoinedTable g_joined;
 int g_rt_device = -1;
 
 ConvArgs conv_args(TaskRt& T, int l, void* y, const std::vector<void*>& slots, float* ws) {
@@ -319,6 +322,16 @@ std::string encode_network(TaskRt& T, const std::vector<void*>& slots, float* ws
         PoolArgs a = PoolArgs();
         a.x = x; a.y = y; a.H = in.H; a.W = in.W; a.C = in.Cs; a.Ho = L.out.H; a.Wo = L.out.W;
         a.k = L.d.k; a.stride = L.d.stride; a.pad = L.d.pad;
+        if (L.pools >= 0) {  // the convolution's launch pools its sums
+          LayerPlan& O = net.layers[L.pools];
+          flops = 2.0 * (double)O.macs;
+          if (L.pools == 0 && net.fuse_ingest) {
+            seq->in_launch = (int)seq->launches.size();
+            seq->in_off = kConvInputOffset;
+          }
+          ok = encode_image_pool(g_joined, O.cp, conv_args(T, L.pools, nullptr, slots, ws), a, bf16, &ks);
+          break;
+        }
         ok = L.d.op == DARIS_OP_MAXPOOL ? encode_maxpool(g_kt, a, bf16, &ks) : encode_gavgpool(g_kt, a, bf16, &ks);
         break;
       }
@@ -869,9 +882,11 @@ daris_status daris_init(int device, uint64_t seed, int flags) {
                                {daris_block_kernels_co, (size_t)(daris_block_kernels_co_end - daris_block_kernels_co)},
                                {daris_taps_kernels_co, (size_t)(daris_taps_kernels_co_end - daris_taps_kernels_co)},
                                {daris_image_kernels_co, (size_t)(daris_image_kernels_co_end - daris_image_kernels_co)},
+                               {daris_joined_kernels_co, (size_t)(daris_joined_kernels_co_end - daris_joined_kernels_co)},
                                {daris_point_kernels_co, (size_t)(daris_point_kernels_co_end - daris_point_kernels_co)}});
       if (err.empty()) {
         err = g_kt.resolve(g_rt);
+        if (err.empty()) err = g_joined.resolve(g_rt);
         if (!err.empty()) err = "kernel " + err;
       }
       if (err.empty()) g_rt_device = device;
@@ -1052,22 +1067,7 @@ daris_status daris_split_stages(daris_task t, int k) {
   if (k < 1) return fail(DARIS_EINVAL, "k must be >= 1");
   if (k > 255) return fail(DARIS_ERANGE, "k must be <= 255");
   if (!split_stages(&net, k)) return fail(DARIS_ERANGE, "k = %d exceeds the %zu legal cut points + 1", k, net.legal_cuts.size());
-  // A depthwise layer is computed inside the next layer's launch only while both lie in one stage: a cut between them makes
-  // the depthwise layer's output the tensor that crosses the boundary (and a stage of that layer alone would have no launch).
-  bool refused = false;
-  for (size_t l = 0; l + 1 < net.layers.size(); ++l) {
-    LayerPlan& A = net.layers[l];
-    LayerPlan& B = net.layers[l + 1];
-    if (!A.fusable_dw || !A.depthwise) continue;
-    const bool cut = std::find(net.stage_first.begin(), net.stage_first.end(), (int)l + 1) != net.stage_first.end();
-    if (A.fused_dw == !cut) continue;
-    A.fused_dw = B.fused_dw = !cut;
-    A.pair_with = cut ? -1 : (int)l + 1;
-    B.pair_with = cut ? -1 : (int)l;
-    B.pair_lead = !cut;
-    refused = true;
-  }
-  if (refused && !G->nodev) {
+  if (join_layers(&net) && !G->nodev) {
     TaskRt& T = *G->tasks[t];
     const std::string err = build_launches(T);
     if (!err.empty()) return fail(DARIS_EHIP, "%s", err.c_str());
@@ -1097,7 +1097,7 @@ int32_t daris_get_launch_plan(daris_task t, int layer, int64_t* out, int32_t cap
   const int64_t v[28] = {L.kernel_id, conv ? 1 : 0, conv ? c.rows : 0, (int64_t)L.out.H * L.out.W, L.out.Cs, L.K, L.Kpad,
                          c.tn, c.nw, c.S, c.sz, c.sw, c.splitk, c.MT, c.NTn, c.G, c.xmode, (int64_t)c.grid_x, 1, 1,
                          c.threads, (int64_t)c.ws_bytes, L.pair_with, L.pair_lead ? 1 : 0,
-                         L.out.slot, net.tensor(L.in_t).slot, L.res_t >= 0 ? net.tensor(L.res_t).slot : -1,
+                         net.pooled_away(layer) ? -1 : L.out.slot, L.in_t > 0 && net.pooled_away(L.in_t - 1) ? -1 : net.tensor(L.in_t).slot, L.res_t >= 0 ? net.tensor(L.res_t).slot : -1,
                          L.fused_dw ? kGatherDepthwise : c.gather};
   const int n = cap < 28 ? 27 : 28;
   for (int i = 0; i < n; ++i) out[i] = v[i];

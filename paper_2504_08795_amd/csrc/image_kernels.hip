@@ -11,8 +11,8 @@ template <bool BF16, int WN>
 __global__ __launch_bounds__(256) void conv_image_kernel(const ImageConvArgs) {
   ImageConvArgs p = grab<ImageConvArgs>((ConstPtr)__builtin_amdgcn_kernarg_segment_ptr());
   args_in_memory(p);
-  __shared__ __align__(16) float lds[conv_image_lds<BF16>()];
-  conv_image_body<BF16, WN>(p, (int)blockIdx.x, lds);
+  __shared__ __align__(16) float lds[conv_image_lds<BF16, false>()];
+  conv_image_body<BF16, WN, false>(p, (int)blockIdx.x, lds);
   puts_done();
 }
 

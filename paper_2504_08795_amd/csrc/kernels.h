@@ -29,6 +29,7 @@ enum KernelId : int32_t {
   K_TAPS64_F32_T2W2, K_TAPS64_F32_T2W4, K_TAPS64_F32_T2W8,
   // the network input in patches: workgroups of one channel block, or of two
   K_IMAGE_F32_N1, K_IMAGE_F32_N2, K_IMAGE_BF16_N1, K_IMAGE_BF16_N2,
+  K_IMAGE_POOL_F32, K_IMAGE_POOL_BF16,  // ... with the 3 x 3 max pooling behind it
   K_COUNT  // at most 64: what a caller of daris_kernel_timing_read has to provide
 };
 static_assert(K_COUNT <= 64, "see daris_kernel_timing_read");
@@ -79,11 +80,14 @@ struct ImageConvArgs {
   int patch_w, patch;  // input pixels of a tile: a row of them, all
   int phase, pitch;    // places between columns of a row that differ by one (mod stride), between rows
   uint32_t mg_tiles, mg_across, mg_patch_w, mg_stride, mg_wo, mg_k;  // multipliers for division
-  int unused[7];  // to one of the sizes that grab() reads
+  int pool_h, pool_w;  // size of the pooled output (conv_image_kernel with POOL, where y is that output)
+  int unused[5];  // to one of the sizes that grab() reads
 };
 constexpr int kImageCols = 16;     // output pixels of a tile's row
 constexpr int kImagePatch = 864;   // places for the input pixels of a tile
 constexpr int kImageTaps = 512;    // and for its taps: of whole chunks and two more
+constexpr int kImagePoolRows = 4, kImagePoolCols = 7;  // conv_image_pool_kernel: a workgroup's pooled pixels, from 9 x 15 convolution outputs
+constexpr int kImagePoolPatch = 1024;  // and the places for their input pixels
 
 // The 3x3 depthwise convolution (pad 1) that conv_wave_dw_kernel computes on the fly in front of a 1x1 convolution; the
 // ConvArgs beside it describe that 1x1 convolution, except that ConvArgs::x is the DEPTHWISE layer's input tensor
@@ -228,6 +232,12 @@ struct KernelTable {
   std::string resolve(const AqlRuntime& rt);
 };
 
+// The kernels that compute several layers in a row.
+struct JoinedTable {
+  const AqlKernel* image_pool[2] = {};  // kGatherImage and the 3 x 3 max pooling behind it
+  std::string resolve(const AqlRuntime& rt);  // as KernelTable::resolve
+};
+
 // Dense convolution: the main kernel, then the split-K reduction if the plan has one.  False on an inconsistent plan.
 bool encode_conv(const KernelTable& kt, const ConvPlan& pl, const ConvArgs& a, int bf16, std::vector<KernelLaunch>* out);
 // Two independent convolutions in one launch: pl0/a0 as planned by plan_conv, pl1/a1 by plan_conv_like(pl0, ...).
@@ -244,6 +254,14 @@ bool encode_conv_dw(const KernelTable& kt, const ConvPlan& pl, const ConvArgs& a
 // the three blocks' layers in launches of their own, fp32 128 CUs 148.5 / 150.4 us, 192 CUs 145.4 / 146.0, 96 CUs 156.0 / 156.9, 64 CUs 172.6 /
 // 175.3; bf16 on 128 CUs 133.4 / 132.7 (two blocks).
 bool conv_dw_fusable(const ConvPlan& pl, int bf16);
+// The first convolution and the 3 x 3 max pooling with stride 2 and padding 1 that alone reads it, in one launch: whether the convolution planned
+// as pl should be computed so, and the launch itself (pool: the pooling layer).  us of the two launches / of one, 12544 x 64 x 7 x 7 with stride 2: fp32 on
+// 128 CUs 8.2 / 7.2, bf16 on 192 CUs 6.3 / 4.9; in the chain of a frame the pooling launch takes 1.3 more than alone, and ResNet-18's frame goes from 133.9 to
+// 132.1 us in fp32 and from 81.8 to 79.0 in bf16.  fp32 is bound by the matrix pipe, which has 1.4 times the work, so that it gains only while the grid
+// is one round of the CUs: planned for 96 CUs (112 workgroups) ResNet-18's job takes 194.8 us instead of 193.3, for 64 CUs (120) ResNet-50's frame of 189 x
+// 253 455.3 instead of 454.4.
+bool image_pool_takes(const ConvPlan& pl, int Ho, int Wo, int cout_stride, int k, int stride, int nominal_cus, int bf16);
+bool encode_image_pool(const JoinedTable& kt, const ConvPlan& pl, const ConvArgs& a, const PoolArgs& pool, int bf16, std::vector<KernelLaunch>* out);
 bool encode_dwconv(const KernelTable& kt, const DwArgs& a, int bf16, std::vector<KernelLaunch>* out);
 bool encode_maxpool(const KernelTable& kt, const PoolArgs& a, int bf16, std::vector<KernelLaunch>* out);
 bool encode_gavgpool(const KernelTable& kt, const PoolArgs& a, int bf16, std::vector<KernelLaunch>* out);

@@ -23,7 +23,8 @@ static const char* const kNames[K_COUNT] = {
     "conv_wave_taps_bf16_t1w2", "conv_wave_taps_bf16_t1w4", "conv_wave_taps_bf16_t2w2", "conv_wave_taps_bf16_t2w4",
     "conv_wave16_taps_f32_t1w8", "conv_wave16_taps_f32_t2w8", "conv_wave16_taps_bf16_t1w4", "conv_wave16_taps_bf16_t1w8", "conv_wave16_taps_bf16_t2w4", "conv_wave16_taps_bf16_t2w8",
     "conv_wave64_taps_f32_t2w2", "conv_wave64_taps_f32_t2w4", "conv_wave64_taps_f32_t2w8",
-    "conv_wave_image_f32_n1_t1w4", "conv_wave_image_f32_n2_t1w4", "conv_wave_image_bf16_n1_t1w4", "conv_wave_image_bf16_n2_t1w4"};
+    "conv_wave_image_f32_n1_t1w4", "conv_wave_image_f32_n2_t1w4", "conv_wave_image_bf16_n1_t1w4", "conv_wave_image_bf16_n2_t1w4",
+    "conv_wave_image_pool_f32_n2_t1w10", "conv_wave_image_pool_bf16_n2_t1w10"};
 
 const char* kernel_name(int32_t id) { return (id >= 0 && id < K_COUNT) ? kNames[id] : "?"; }
 
@@ -305,14 +306,17 @@ bool push(std::vector<KernelLaunch>* out, const AqlKernel* k, int32_t id, uint32
 
 }  // namespace
 
+// A kernel by its name; missing keeps the first that is not there, or takes another argument block.
+static const AqlKernel* find_kernel(const AqlRuntime& rt, const std::string& name, uint32_t want_bytes, std::string* missing) {
+  const AqlKernel* k = rt.kernel(name);
+  if ((!k || k->kernarg_size != want_bytes) && missing->empty())
+    *missing = name + (k ? " (argument block of " + std::to_string(k->kernarg_size) + " bytes, expected " + std::to_string(want_bytes) + ")" : " (not in the code object)");
+  return k;
+}
+
 std::string KernelTable::resolve(const AqlRuntime& rt) {
   std::string missing;
-  auto get = [&](const std::string& name, uint32_t want_bytes) -> const AqlKernel* {
-    const AqlKernel* k = rt.kernel(name);
-    if ((!k || k->kernarg_size != want_bytes) && missing.empty())
-      missing = name + (k ? " (argument block of " + std::to_string(k->kernarg_size) + " bytes, expected " + std::to_string(want_bytes) + ")" : " (not in the code object)");
-    return k;
-  };
+  auto get = [&](const std::string& name, uint32_t want_bytes) { return find_kernel(rt, name, want_bytes, &missing); };
   static const int tn_[6] = {1, 1, 1, 2, 2, 2}, nw_[6] = {2, 4, 8, 2, 4, 8};
   for (int b = 0; b < 2; ++b) {
     const std::string B = b ? "true" : "false";
@@ -349,6 +353,16 @@ std::string KernelTable::resolve(const AqlRuntime& rt) {
   return missing;
 }
 
+std::string JoinedTable::resolve(const AqlRuntime& rt) {
+  std::string missing;
+  auto get = [&](const std::string& name, uint32_t want_bytes) { return find_kernel(rt, name, want_bytes, &missing); };
+  for (int b = 0; b < 2; ++b) {
+    const std::string B = b ? "true" : "false";
+    image_pool[b] = get("daris::conv_image_pool_kernel<" + B + ">", sizeof(ImageConvArgs));
+  }
+  return missing;
+}
+
 // ---- encoders ----------------------------------------------------------------------------------------------------------------
 
 static bool rows_take(const ConvArgs& a, int bf16) { return a.c_real == 0 && conv_rows_take(a.H, a.W, a.Cin, (uint64_t)a.M, a.Cout, a.Kpad, bf16); }
@@ -375,22 +389,23 @@ struct ImageTiles {
 };
 // The input pixels of a tile have to fit the patch (kernels of 7 x 7 up to stride 2, 11 x 11 with stride 1), its taps the table, byte
 // offsets into the output 31 bits.
-static ImageTiles image_tiles(int Ho, int Wo, int cout_stride, int k, int stride, int S, int bf16) {
+// pool: tiles that become pooled pixels where they are computed (two channel blocks and ten rows each).
+static ImageTiles image_tiles(int Ho, int Wo, int cout_stride, int k, int stride, int S, int bf16, bool pool = false) {
   ImageTiles t = ImageTiles();
   if (stride > 64 || k > 64) return t;
   t.nb = cdiv(cout_stride, 32);
   t.wn = t.nb % 2 ? 1 : 2;
-  t.rows = 8 / t.wn;
+  t.rows = pool ? 2 * kImagePoolRows + 2 : 8 / t.wn;
   t.patch_w = (kImageCols - 1) * stride + k;
   t.phase = cdiv(t.patch_w, stride);
   t.pitch = t.phase * stride;  // made so that the two rows of a block lie in different banks
   for (int i = 0; i < 32 && t.pitch * stride % 32 != 16; ++i) ++t.pitch;
   t.patch_h = (int64_t)(t.rows - 1) * stride + k;
-  t.across = cdiv(Wo, kImageCols);
-  t.tiles = (int64_t)t.across * cdiv(Ho, t.rows);
+  t.across = pool ? cdiv((Wo - 1) / 2 + 1, kImagePoolCols) : cdiv(Wo, kImageCols);
+  t.tiles = (int64_t)t.across * (pool ? cdiv((Ho - 1) / 2 + 1, kImagePoolRows) : cdiv(Ho, t.rows));
   const uint64_t M = (uint64_t)Ho * (uint64_t)Wo;
-  t.ok = t.patch_h * t.pitch <= kImagePatch && S * 2 + 16 <= kImageTaps && M * cout_stride * (bf16 ? 2 : 4) < (1ull << 31) && (M + 16 * (uint64_t)Wo) * Wo < (1ull << 32) &&
-         (uint64_t)t.tiles * (t.nb / t.wn) * (uint64_t)t.tiles < (1ull << 32);
+  t.ok = t.patch_h * t.pitch <= (pool ? kImagePoolPatch : kImagePatch) && S * 2 + 16 <= kImageTaps && M * cout_stride * (bf16 ? 2 : 4) < (1ull << 31) && (M + 16 * (uint64_t)Wo) * Wo < (1ull << 32) &&
+         (uint64_t)t.tiles * (t.nb / t.wn) * (uint64_t)t.tiles < (1ull << 32) && (!pool || (t.wn == 2 && ((uint64_t)Ho + 16) * ((uint64_t)Wo + 17) * ((uint64_t)Wo + 1) < (1ull << 32)));
   return t;
 }
 
@@ -427,19 +442,47 @@ void plan_gather(ConvPlan* pl, int cin_stride, bool rows, int bf16) {
   pl->gather = pl->rows != 32 || (rows && pl->staged) ? kGatherRows : bf16 && cin_stride % 16 == 0 ? kGatherAligned : kGatherGeneral;
 }
 
-static bool encode_image(const KernelTable& kt, const ConvPlan& pl, const ConvArgs& a, int bf16, std::vector<KernelLaunch>* out) {
-  const ImageTiles t = image_tiles(a.Ho, a.Wo, a.Cout, a.kh, a.stride, pl.S, bf16);
-  if (!t.ok || a.kh != a.kw || a.res || pl.splitk != 1 || pl.rows != 32 || pl.tn != 1 || pl.threads != 256 || pl.kernel != (bf16 ? K_IMAGE_BF16_N1 : K_IMAGE_F32_N1) + t.wn - 1 ||
-      pl.grid_x != (uint64_t)t.tiles * (t.nb / t.wn))
-    return false;
-  ImageConvArgs m = ImageConvArgs();
+static void image_args(const ImageTiles& t, const ConvPlan& pl, const ConvArgs& a, ImageConvArgs* out) {
+  ImageConvArgs& m = *out;
+  m = ImageConvArgs();
   m.x = a.x; m.w = a.w; m.bias = a.bias; m.y = a.y;
   m.H = a.H; m.W = a.W; m.Ho = a.Ho; m.Wo = a.Wo; m.Cout = a.Cout; m.k = a.kh; m.stride = a.stride; m.pad = a.pad;
   m.act = a.act; m.S = pl.S; m.M = a.M; m.c_real = a.c_real; m.wave_prio = a.wave_prio;
   m.tiles = (int)t.tiles; m.across = t.across; m.patch_w = t.patch_w; m.patch = (int)t.patch_h * t.patch_w; m.phase = t.phase; m.pitch = t.pitch;
   m.mg_tiles = div_magic((uint32_t)t.tiles); m.mg_across = div_magic((uint32_t)t.across); m.mg_patch_w = div_magic((uint32_t)t.patch_w);
   m.mg_stride = div_magic((uint32_t)a.stride); m.mg_wo = div_magic((uint32_t)a.Wo); m.mg_k = div_magic((uint32_t)a.kw);
+}
+
+// What both launches of patches assume of a plan and its arguments.
+static bool image_agrees(const ConvPlan& pl, const ConvArgs& a, int bf16) {
+  return pl.gather == kGatherImage && a.kh == a.kw && !a.res && pl.splitk == 1 && pl.rows == 32 && pl.tn == 1 && pl.threads == 256 && a.c_real > 0 && a.c_real <= 4 &&
+         a.Cin == (bf16 ? 8 : 4) && (uint64_t)a.c_real * a.H * a.W * 4 < (1ull << 31);
+}
+
+static bool encode_image(const KernelTable& kt, const ConvPlan& pl, const ConvArgs& a, int bf16, std::vector<KernelLaunch>* out) {
+  const ImageTiles t = image_tiles(a.Ho, a.Wo, a.Cout, a.kh, a.stride, pl.S, bf16);
+  if (!t.ok || !image_agrees(pl, a, bf16) || pl.kernel != (bf16 ? K_IMAGE_BF16_N1 : K_IMAGE_F32_N1) + t.wn - 1 || pl.grid_x != (uint64_t)t.tiles * (t.nb / t.wn)) return false;
+  ImageConvArgs m;
+  image_args(t, pl, a, &m);
   return push(out, kt.image[bf16][t.wn - 1], pl.kernel, pl.grid_x, (uint32_t)pl.threads, &m, sizeof(m));
+}
+
+bool image_pool_takes(const ConvPlan& pl, int Ho, int Wo, int cout_stride, int k, int stride, int nominal_cus, int bf16) {
+  const ImageTiles t = image_tiles(Ho, Wo, cout_stride, k, stride, pl.S, bf16, true);
+  return pl.gather == kGatherImage && t.ok && (bf16 || t.tiles * (t.nb / t.wn) <= nominal_cus);
+}
+
+bool encode_image_pool(const JoinedTable& kt, const ConvPlan& pl, const ConvArgs& a, const PoolArgs& pool, int bf16, std::vector<KernelLaunch>* out) {
+  const ImageTiles t = image_tiles(a.Ho, a.Wo, a.Cout, a.kh, a.stride, pl.S, bf16, true);
+  if (!t.ok || !image_agrees(pl, a, bf16) || pool.k != 3 || pool.stride != 2 || pool.pad != 1 || pool.H != a.Ho || pool.W != a.Wo || pool.C != a.Cout ||
+      pool.Ho != (a.Ho - 1) / 2 + 1 || pool.Wo != (a.Wo - 1) / 2 + 1)
+    return false;
+  ImageConvArgs m;
+  image_args(t, pl, a, &m);
+  m.y = pool.y;
+  m.pool_h = pool.Ho;
+  m.pool_w = pool.Wo;
+  return push(out, kt.image_pool[bf16], bf16 ? K_IMAGE_POOL_BF16 : K_IMAGE_POOL_F32, (uint32_t)(t.tiles * (t.nb / t.wn)), 64 * 2 * (kImagePoolRows + 1), &m, sizeof(m));
 }
 
 bool encode_conv(const KernelTable& kt, const ConvPlan& pl, const ConvArgs& a, int bf16, std::vector<KernelLaunch>* out) {

@@ -1123,22 +1123,27 @@ constexpr int conv_rows_lds() {  // floats of LDS
 // each other's waits: 6.1 us, 4.6, 6.0, 8.7 in place of the following.  us on 128 CUs, gather -> patches: 12544 x 64 x 7 x 7 with stride 2 fp32
 // 10.3 -> 5.8 (192 CUs 10.0 -> 5.7, 64 CUs 16.4 -> 8.4), bf16 7.2 -> 4.3; 50176 x 64 x 3 x 3 10.7 -> 6.4; 12544 x 32 x 3 x 3 with stride 2 3.5 -> 3.2;
 // 1024 x 16 x 3 x 3 3.05 -> 2.8.
-template <bool BF16>
+// POOL: the 3 x 3 max pooling with stride 2 and padding 1 behind the convolution in the same launch, for two channel blocks side by side.  A workgroup of
+// ten waves computes ten rows of 16 outputs, of which nine rows of 15 are the windows of 4 x 7 pooled pixels, and passes them through LDS; they
+// are never stored.  1.4 outputs are computed for one that counts, in place of a launch.
+template <bool BF16, bool POOL>
 constexpr int conv_image_lds() {  // floats of LDS
-  constexpr int kPatch = (BF16 ? 1 : 3) * (kImagePatch + 1) * 2 + kImageTaps;
-  return kPatch > 4 * 1024 ? kPatch : 4 * 1024;
+  constexpr int kPatch = (BF16 ? 1 : 3) * ((POOL ? kImagePoolPatch : kImagePatch) + 1) * 2 + kImageTaps, kTiles = (POOL ? 2 * kImagePoolRows + 2 : 4) * 1024;
+  return kPatch > kTiles ? kPatch : kTiles;
 }
-template <bool BF16, int WN>
+template <bool BF16, int WN, bool POOL>
 __device__ __forceinline__ void conv_image_body(const ImageConvArgs& p, const int L, float* const lds) {
-  constexpr int ES = BF16 ? 2 : 4, NP = BF16 ? 1 : 3, DC = BF16 ? 4 : 2;
-  constexpr int PLANE = kImagePatch + 1, ROUNDS = (kImagePatch + 255) / 256;
+  static_assert(!POOL || WN == 2, "pooled tiles are two channel blocks wide");
+  constexpr int ES = BF16 ? 2 : 4, NP = BF16 ? 1 : 3, DC = BF16 ? 4 : 2, NT = POOL ? 128 * (kImagePoolRows + 1) : 256;
+  constexpr int PATCH = POOL ? kImagePoolPatch : kImagePatch, PLANE = PATCH + 1, ROUNDS = (PATCH + NT - 1) / NT;
   constexpr int kOutside = (int)0x80000000;  // an offset past the end of any tensor
   if (p.wave_prio) __builtin_amdgcn_s_setprio(3);
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int li = lane & 31, lh = lane >> 5;
   const int g = fast_div(L, p.mg_tiles), tile = L - g * p.tiles;
-  const int ty = fast_div(tile, p.mg_across), x0 = (tile - ty * p.across) * kImageCols, y0 = ty * (8 / WN);
+  const int ty = fast_div(tile, p.mg_across), tx = tile - ty * p.across;
+  const int x0 = POOL ? tx * 2 * kImagePoolCols - 1 : tx * kImageCols, y0 = POOL ? ty * 2 * kImagePoolRows - 1 : ty * (8 / WN);  // (POOL: from -1 on)
   const int nb = g * WN + wave % WN, row0 = wave / WN * 2;  // the wave's channel block and its first row of the tile
 
   const int plane = p.H * p.W * 4;
@@ -1154,8 +1159,8 @@ __device__ __forceinline__ void conv_image_body(const ImageConvArgs& p, const in
   for (int r = 0; r < ROUNDS; ++r) {
     place[r] = 0;
     px[r] = make_uint4(0u, 0u, 0u, 0u);
-    if (256 * r < p.patch) {
-      const int i = tid + 256 * r, y = (int)__umulhi((uint32_t)i, p.mg_patch_w), x = i - y * p.patch_w, iy = y0 * p.stride - p.pad + y, ix = x0 * p.stride - p.pad + x;
+    if (NT * r < p.patch) {
+      const int i = tid + NT * r, y = (int)__umulhi((uint32_t)i, p.mg_patch_w), x = i - y * p.patch_w, iy = y0 * p.stride - p.pad + y, ix = x0 * p.stride - p.pad + x;
       const int col = by_stride(x);
       place[r] = y * p.pitch + (x - col * p.stride) * p.phase + col;
       const int o = i < p.patch && (unsigned)iy < (unsigned)p.H && (unsigned)ix < (unsigned)p.W ? (iy * p.W + ix) * 4 : kOutside;
@@ -1165,7 +1170,7 @@ __device__ __forceinline__ void conv_image_body(const ImageConvArgs& p, const in
       if (p.c_real > 3) px[r].w = __builtin_amdgcn_raw_buffer_load_b32(irsrc, o, 3 * plane, 0);
     }
   }
-  const int n = nb * 32 + 4 * lane % 32;  // first channel of the lane's quads
+  const int n = POOL ? g * 64 + 4 * (tid & 15) : nb * 32 + 4 * lane % 32;  // first channel of the lane's quads
   const auto brsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p.bias), 0, p.Cout * 4, 0x00027000);
   const float4 bias = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(brsrc, n * 4, 0, 0));
 
@@ -1191,7 +1196,7 @@ __device__ __forceinline__ void conv_image_body(const ImageConvArgs& p, const in
   };
   uint4 next[NP];  // the next chunk's pixels
   auto read = [&]() {
-    const int at = min(base + o.x, kImagePatch), bt = min(base + o.y, kImagePatch);
+    const int at = min(base + o.x, PATCH), bt = min(base + o.y, PATCH);
 #pragma unroll
     for (int q = 0; q < NP; ++q) {
       const uint2 u = st[q * PLANE + at], v = BF16 ? make_uint2(0u, 0u) : st[q * PLANE + bt];  // (bf16: eight k are one tap, the upper four zero)
@@ -1206,15 +1211,15 @@ __device__ __forceinline__ void conv_image_body(const ImageConvArgs& p, const in
   static_for<0, DC>([&](auto r) {
     if (lead == r) static_for<0, DC>([&](auto i) { load((DC - r + i) % DC); });
   });
-  if (tid < NP) st[tid * PLANE + kImagePatch] = make_uint2(0u, 0u);
+  if (tid < NP) st[tid * PLANE + PATCH] = make_uint2(0u, 0u);
 #pragma unroll
-  for (int t = tid; t < kImageTaps; t += 256) {
+  for (int t = tid; t < kImageTaps; t += NT) {
     const int ky = fast_div(t, p.mg_k), kx = t - ky * p.k, col = by_stride(kx);
-    reinterpret_cast<int*>(lds + NP * PLANE * 2)[t] = ky < p.k ? ky * p.pitch + (kx - col * p.stride) * p.phase + col : kImagePatch;
+    reinterpret_cast<int*>(lds + NP * PLANE * 2)[t] = ky < p.k ? ky * p.pitch + (kx - col * p.stride) * p.phase + col : PATCH;
   }
 #pragma unroll
   for (int r = 0; r < ROUNDS; ++r) {
-    if (tid + 256 * r < p.patch) {
+    if (tid + NT * r < p.patch) {
       if constexpr (BF16) {
         st[place[r]] = make_uint2(pack_bf16_rne(__uint_as_float(px[r].x), __uint_as_float(px[r].y)), pack_bf16_rne(__uint_as_float(px[r].z), __uint_as_float(px[r].w)));
       } else {
@@ -1226,7 +1231,8 @@ __device__ __forceinline__ void conv_image_body(const ImageConvArgs& p, const in
   }
   // (A pixel past the output is a pixel of zeros: see drop_pixels.  Here that is the cheaper way: first convolutions of few tiles take 0.07 us longer
   // for it and 0.14 for dropped sums.)
-  if (!BF16 && (y0 + row0 + 2 > p.Ho || x0 + kImageCols > p.Wo)) base = y0 + row0 + li / 16 < p.Ho && x0 + li % 16 < p.Wo ? base : kImagePatch;
+  if (!BF16 && (y0 + row0 + 2 > p.Ho || x0 + kImageCols > p.Wo || (POOL && (y0 < 0 || x0 < 0))))
+    base = (unsigned)(y0 + row0 + li / 16) < (unsigned)p.Ho && (unsigned)(x0 + li % 16) < (unsigned)p.Wo ? base : PATCH;
   __syncthreads();
   read_taps();
   read();
@@ -1247,17 +1253,51 @@ __device__ __forceinline__ void conv_image_body(const ImageConvArgs& p, const in
   });
   for (int rounds = n_chunks / DC; rounds > 1; --rounds) static_for<0, DC>(refilled);
   static_for<0, DC>([&](auto s) { step(s, std::false_type()); });
-  const int m0 = (y0 + row0) * p.Wo + x0;
   if constexpr (!BF16) {
     if (out_of_range(acc)) {
       ConvArgs c = ConvArgs();
       c.x = p.x; c.w = p.w; c.H = p.H; c.W = p.W; c.Cin = 4; c.Wo = p.Wo; c.kh = c.kw = p.k; c.stride = p.stride; c.pad = p.pad;
       c.M = p.M; c.S = p.S; c.mg_wo = p.mg_wo; c.mg_kw = p.mg_k; c.c_real = p.c_real;
-      plain_products<6, 32, 1, 1>(c, DwFusedArgs(), m0, nb, 0, p.S, acc);
+      if constexpr (POOL) {  // pixels are counted from -1 on in both directions: an output one row and one column larger, and as much more padding
+        c.Wo = p.Wo + 1;
+        c.pad = p.pad + p.stride;
+        c.M = (p.Ho + 1) * c.Wo;
+        c.mg_wo = 0xffffffffu / (uint32_t)c.Wo + 1u;
+        plain_products<6, 32, 1, 1>(c, DwFusedArgs(), (y0 + 1 + row0) * c.Wo + x0 + 1, nb, 0, p.S, acc);
+      } else {
+        plain_products<6, 32, 1, 1>(c, DwFusedArgs(), (y0 + row0) * p.Wo + x0, nb, 0, p.S, acc);
+      }
     }
   }
   __syncthreads();  // the tiles go through the patch's LDS, each wave's through its own corner
   float* const out = lds + wave * 1024;
+  if constexpr (POOL) {
+#pragma unroll
+    for (int v = 0; v < 16; ++v) out[64 * v + lane] = acc[0][v];
+    __syncthreads();
+    // A thread has four channels of a pooled pixel.  The largest sum is taken before bias and activation, which change no order (NaN never wins).
+    const int quad = tid & 15, pp = tid >> 4, py = pp / kImagePoolCols, px2 = 2 * (pp - py * kImagePoolCols);
+    const int oy = ty * kImagePoolRows + py, ox = tx * kImagePoolCols + (px2 >> 1);
+    if (pp >= kImagePoolRows * kImagePoolCols || oy >= p.pool_h || ox >= p.pool_w) return;
+    float best[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+#pragma unroll
+    for (int ky = 0; ky < 3; ++ky)
+#pragma unroll
+      for (int kx = 0; kx < 3; ++kx) {
+        const int r = 2 * py + ky, pixel = r % 2 * 16 + px2 + kx;
+        const float4 v = *(const float4*)&lds[(r / 2 * 2 + (quad >> 3)) * 1024 + ((pixel >> 3) * 4 + (pixel & 3)) * 64 + (pixel >> 2 & 1) * 32 + 4 * (quad & 7)];
+        const bool in = (unsigned)(y0 + r) < (unsigned)p.Ho && (unsigned)(x0 + px2 + kx) < (unsigned)p.Wo;
+        best[0] = in ? fmaxf(best[0], v.x) : best[0]; best[1] = in ? fmaxf(best[1], v.y) : best[1];
+        best[2] = in ? fmaxf(best[2], v.z) : best[2]; best[3] = in ? fmaxf(best[3], v.w) : best[3];
+      }
+    if (n >= p.Cout) return;
+    best[0] += bias.x; best[1] += bias.y; best[2] += bias.z; best[3] += bias.w;
+    apply_act(best, p.act);
+    unsigned char* const to = (unsigned char*)p.y + ((size_t)(oy * p.pool_w + ox) * p.Cout + n) * ES;
+    if constexpr (BF16) put(to, make_uint2(pack_bf16_rne(best[0], best[1]), pack_bf16_rne(best[2], best[3])));
+    else put(to, make_float4(best[0], best[1], best[2], best[3]));
+    return;
+  }
   const auto yrsrc = __builtin_amdgcn_make_buffer_rsrc(p.y, 0, p.M * p.Cout * ES, 0x00027000);
 #pragma unroll
   for (int v = 0; v < 16; ++v) out[64 * v + lane] = acc[0][v];

@@ -210,6 +210,17 @@ std::string build_plan(const daris_dnn& dnn, bool keep_activations, bool pair_la
     else plan_gather(&L.cp, net.tensor(L.in_t).Cs, rows_taken(L) || (L.cp.rows == 32 && L.cp.nw == 2 && rows_taken_large(L)), net.bf16);
     L.kernel_id = L.cp.kernel;
   }
+  // max pooling in the launch of the convolution that it alone reads
+  for (int l = 0; l + 1 < n && !keep_activations && fuse_ingest; ++l) {
+    LayerPlan& A = net.layers[l];
+    LayerPlan& B = net.layers[l + 1];
+    if (A.d.op != DARIS_OP_CONV || A.depthwise || A.pair_with >= 0 || B.d.op != DARIS_OP_MAXPOOL || B.in_t != l + 1) continue;
+    bool only_reader = true;
+    for (int q = l + 2; q < n; ++q)
+      if (net.layers[q].in_t == l + 1 || net.layers[q].res_t == l + 1) only_reader = false;
+    if (!only_reader) continue;
+    if (B.d.k == 3 && B.d.stride == 2 && B.d.pad == 1 && image_pool_takes(A.cp, A.out.H, A.out.W, A.out.Cs, A.d.k, A.d.stride, plan_cus, net.bf16)) B.can_pool = l;
+  }
   const TensorInfo& fin = net.layers[n - 1].out;
   net.n_out = fin.C * fin.H * fin.W;
   net.final_direct = net.layers[n - 1].d.op == DARIS_OP_FC;
@@ -225,6 +236,7 @@ std::string build_plan(const daris_dnn& dnn, bool keep_activations, bool pair_la
     if (ok) net.legal_cuts.push_back(l);
   }
   net.stage_first.assign(1, 0);
+  join_layers(&net);
 
   // activation slots: a tensor's slot is free again once its last reader has been issued (same stream, in order)
   // The earlier member of a launch pair is issued with the later one (and its split-K reduction after that launch):
@@ -261,6 +273,32 @@ std::string build_plan(const daris_dnn& dnn, bool keep_activations, bool pair_la
     net.layers[l].out.slot = take_slot(l + 1, net.layers[l].out.bytes);
   }
   return "";
+}
+
+bool join_layers(NetPlan* net) {
+  bool changed = false;
+  for (int l = 0; l + 1 < (int)net->layers.size(); ++l) {
+    LayerPlan& A = net->layers[l];
+    LayerPlan& B = net->layers[l + 1];
+    const bool cut = std::find(net->stage_first.begin(), net->stage_first.end(), l + 1) != net->stage_first.end();
+    // A depthwise layer is computed inside the next layer's launch only while both lie in one stage: a cut between them makes
+    // the depthwise layer's output the tensor that crosses the boundary (and a stage of that layer alone would have no launch).
+    if (A.fusable_dw && A.depthwise && A.fused_dw == cut) {
+      A.fused_dw = B.fused_dw = !cut;
+      A.pair_with = cut ? -1 : l + 1;
+      B.pair_with = cut ? -1 : l;
+      B.pair_lead = !cut;
+      changed = true;
+    }
+    // ... and so with a convolution and the pooling layer behind it.
+    if (B.can_pool == l && (B.pools == l) == cut) {
+      B.pools = cut ? -1 : l;
+      A.pair_with = cut ? -1 : l + 1;
+      B.kernel_id = cut ? K_MAXPOOL : net->bf16 ? K_IMAGE_POOL_BF16 : K_IMAGE_POOL_F32;
+      changed = true;
+    }
+  }
+  return changed;
 }
 
 bool split_stages(NetPlan* net, int k) {

@@ -1,0 +1,55 @@
+"""What the launches of joined layers assume, checked without a device."""
+import re
+
+import pytest
+
+import paper_2504_08795_amd as D
+import workloads as wl
+from lib_helpers import Session
+from paper_2504_08795_amd import build
+from test_host_logic import _code_object_kernels
+
+HOST = D.VIRTUAL_TIME | D.NO_DEVICE
+N = wl.nets
+
+# code object: {kernel: (bytes of its argument block, how many instances)}
+JOINED_KERNELS = {"daris_joined_kernels": {"conv_image_pool_kernel": (160, 2)}}
+
+
+@pytest.mark.parametrize("co", sorted(JOINED_KERNELS))
+def test_joined_kernels_match_the_argument_structures(co):
+    want, seen = JOINED_KERNELS[co], {}
+    for name, has in _code_object_kernels(co):
+        base = [k for k in want if re.search(r"\d+" + k + r"(I|E)", name)]
+        assert len(base) == 1, name
+        assert has["kernarg_segment_size"] == want[base[0]][0], name
+        assert has["private_segment_fixed_size"] == 0 and has["group_segment_fixed_size"] <= 65536, (name, has)
+        seen[base[0]] = seen.get(base[0], 0) + 1
+    assert seen == {k: n for k, (_, n) in want.items()}
+    assert set(build.JOINED_SOURCES.values()) == set(JOINED_KERNELS)
+
+
+def _plans(layers, shp, dtype, k=1, cus=128):
+    with Session(HOST):
+        D.daris_set_plan_cus(cus)
+        D.daris_create_partition(64)
+        dnn, keep = D.make_dnn(layers, None, shp, dtype)
+        t = D.daris_register_task(dnn, 10**7, 10**7, D.LP)
+        if k > 1:
+            D.daris_split_stages(t, k)
+        return [D.daris_get_launch_plan(t, l) for l in range(len(layers))]
+
+
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("net", ["resnet18", "resnet50"])
+def test_first_pooling_layer_joins_the_convolution(net, dtype):
+    layers, shp = wl.build_net(net)
+    p = _plans(layers, shp, dtype)
+    assert p[0]["pair_with"] == 1 and not p[0]["pair_lead"] and p[0]["out_slot"] == p[1]["in_slot"] == -1 and p[1]["pair_with"] == -1
+    assert "image_pool" in D.daris_kernel_name(p[1]["kernel_id"])
+    legal = 1 + sum(1 for l in range(len(layers) - 1) if all(q.in_from >= l and not 0 <= q.res_from < l for q in layers[l + 1:]))
+    p = _plans(layers, shp, dtype, k=legal)                             # a cut between the two
+    assert p[0]["pair_with"] == -1 and p[0]["out_slot"] == p[1]["in_slot"] >= 0 and D.daris_kernel_name(p[1]["kernel_id"]) == "maxpool"
+    other = [N.Layer(op=N.OP_CONV, c_in=3, c_out=64, k=7, stride=2, pad=3, in_from=-1), N.Layer(op=N.OP_MAXPOOL, c_in=64, c_out=64, k=3, stride=2, pad=1, in_from=0),
+             N.Layer(op=N.OP_CONV, c_in=64, c_out=64, k=3, stride=2, pad=1, in_from=1), N.Layer(op=N.OP_CONV, c_in=64, c_out=64, k=1, in_from=0)]
+    assert _plans(other, shp, dtype)[0]["pair_with"] == -1              # somebody else reads the convolution
