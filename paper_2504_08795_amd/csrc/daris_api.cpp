@@ -280,14 +280,19 @@ std::string encode_network(TaskRt& T, const std::vector<void*>& slots, float* ws
     double flops = 0;
     switch (L.d.op) {
       case DARIS_OP_CONV:
-        if (L.depthwise && L.fused_dw) {
+        if ((L.depthwise && L.fused_dw) || net.joined_away(l)) {
           ok = true;  // computed inside the next layer's launch
         } else if (L.depthwise) {
           DwArgs a = DwArgs();
           a.x = x; a.w = L.w_dev; a.bias = L.b_dev; a.y = y;
           a.H = in.H; a.W = in.W; a.C = in.Cs; a.Ho = L.out.H; a.Wo = L.out.W;
           a.k = L.d.k; a.stride = L.d.stride; a.pad = L.d.pad; a.act = L.d.act;
-          ok = encode_dwconv(g_kt, a, bf16, &ks);
+          if (L.joins >= 0) {
+            flops = 2.0 * (double)(L.macs + net.layers[L.joins].macs);
+            ok = encode_expand_dw(g_joined, net.layers[L.joins].cp, conv_args(T, L.joins, nullptr, slots, ws), a, net.plan_cus, bf16, &ks);
+          } else {
+            ok = encode_dwconv(g_kt, a, bf16, &ks);
+          }
         } else if (L.pair_with >= 0 && !L.pair_lead) {
           ok = true;  // issued together with the next layer
         } else {
@@ -322,14 +327,14 @@ std::string encode_network(TaskRt& T, const std::vector<void*>& slots, float* ws
         PoolArgs a = PoolArgs();
         a.x = x; a.y = y; a.H = in.H; a.W = in.W; a.C = in.Cs; a.Ho = L.out.H; a.Wo = L.out.W;
         a.k = L.d.k; a.stride = L.d.stride; a.pad = L.d.pad;
-        if (L.pools >= 0) {  // the convolution's launch pools its sums
-          LayerPlan& O = net.layers[L.pools];
+        if (L.joins >= 0) {  // the convolution in front, which pools its outputs
+          LayerPlan& O = net.layers[L.joins];
           flops = 2.0 * (double)O.macs;
-          if (L.pools == 0 && net.fuse_ingest) {
+          if (L.joins == 0 && net.fuse_ingest) {
             seq->in_launch = (int)seq->launches.size();
             seq->in_off = kConvInputOffset;
           }
-          ok = encode_image_pool(g_joined, O.cp, conv_args(T, L.pools, nullptr, slots, ws), a, bf16, &ks);
+          ok = encode_image_pool(g_joined, O.cp, conv_args(T, L.joins, nullptr, slots, ws), a, bf16, &ks);
           break;
         }
         ok = L.d.op == DARIS_OP_MAXPOOL ? encode_maxpool(g_kt, a, bf16, &ks) : encode_gavgpool(g_kt, a, bf16, &ks);
@@ -1097,7 +1102,7 @@ int32_t daris_get_launch_plan(daris_task t, int layer, int64_t* out, int32_t cap
   const int64_t v[28] = {L.kernel_id, conv ? 1 : 0, conv ? c.rows : 0, (int64_t)L.out.H * L.out.W, L.out.Cs, L.K, L.Kpad,
                          c.tn, c.nw, c.S, c.sz, c.sw, c.splitk, c.MT, c.NTn, c.G, c.xmode, (int64_t)c.grid_x, 1, 1,
                          c.threads, (int64_t)c.ws_bytes, L.pair_with, L.pair_lead ? 1 : 0,
-                         net.pooled_away(layer) ? -1 : L.out.slot, L.in_t > 0 && net.pooled_away(L.in_t - 1) ? -1 : net.tensor(L.in_t).slot, L.res_t >= 0 ? net.tensor(L.res_t).slot : -1,
+                         net.joined_away(layer) ? -1 : L.out.slot, L.in_t > 0 && net.joined_away(L.in_t - 1) ? -1 : net.tensor(L.in_t).slot, L.res_t >= 0 ? net.tensor(L.res_t).slot : -1,
                          L.fused_dw ? kGatherDepthwise : c.gather};
   const int n = cap < 28 ? 27 : 28;
   for (int i = 0; i < n; ++i) out[i] = v[i];

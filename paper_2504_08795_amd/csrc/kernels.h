@@ -30,6 +30,7 @@ enum KernelId : int32_t {
   // the network input in patches: workgroups of one channel block, or of two
   K_IMAGE_F32_N1, K_IMAGE_F32_N2, K_IMAGE_BF16_N1, K_IMAGE_BF16_N2,
   K_IMAGE_POOL_F32, K_IMAGE_POOL_BF16,  // ... with the 3 x 3 max pooling behind it
+  K_EXPAND_DW_F32, K_EXPAND_DW_BF16,    // a 1 x 1 convolution and the depthwise one behind it
   K_COUNT  // at most 64: what a caller of daris_kernel_timing_read has to provide
 };
 static_assert(K_COUNT <= 64, "see daris_kernel_timing_read");
@@ -98,6 +99,26 @@ struct DwFusedArgs {
   int H = 0, W = 0;             // the depthwise layer's input size
   int stride = 1, act = 0;
 };
+
+// A 1x1 convolution and the 3x3 depthwise convolution (pad 1) behind it for conv_expand_dw_kernel.
+struct ExpandDwArgs {
+  const void* x;         // [H][W][Cin]
+  const void* w;         // the 1x1 convolution's weights, packed for 16-pixel tiles
+  const float* bias;     // [C]
+  const void* dw_w;      // [9][C]
+  const float* dw_bias;  // [C]
+  void* y;               // [Ho][Wo][C]
+  int H, W, Cin, Ho, Wo, C;
+  int stride, act, dw_act;  // the depthwise layer's stride, both activations
+  int band, bands;          // output rows of a workgroup, workgroups of a channel block
+  int S;                    // K steps, as ConvArgs::S
+  int threads, wave_prio;
+  uint32_t mg_bands, mg_w, mg_wo;  // multipliers for division
+  int unused[11];  // to one of the sizes that grab() reads
+};
+constexpr int kExpandPixels = 320;  // most input pixels of a workgroup
+constexpr int kExpandRow = 20;      // floats of a pixel's 16 channels in LDS, spread over the banks
+constexpr int kExpandChunks = 5;    // most chunks of 32 k
 
 struct DwArgs {
   const void* x;      // [H][W][C]
@@ -235,6 +256,7 @@ struct KernelTable {
 // The kernels that compute several layers in a row.
 struct JoinedTable {
   const AqlKernel* image_pool[2] = {};  // kGatherImage and the 3 x 3 max pooling behind it
+  const AqlKernel* expand_dw[2][kExpandChunks] = {};
   std::string resolve(const AqlRuntime& rt);  // as KernelTable::resolve
 };
 
@@ -262,6 +284,10 @@ bool conv_dw_fusable(const ConvPlan& pl, int bf16);
 // 253 455.3 instead of 454.4.
 bool image_pool_takes(const ConvPlan& pl, int Ho, int Wo, int cout_stride, int k, int stride, int nominal_cus, int bf16);
 bool encode_image_pool(const JoinedTable& kt, const ConvPlan& pl, const ConvArgs& a, const PoolArgs& pool, int bf16, std::vector<KernelLaunch>* out);
+// A 1x1 convolution and the 3x3 depthwise convolution with padding 1 that alone reads it, in one launch.  Turns pl into the plan of the convolution by
+// itself whose sums have the same order, and returns whether the two should be joined.
+bool plan_expand_dw(ConvPlan* pl, int H, int W, int cin_stride, int c_stride, int Kpad, int dw_stride, int nominal_cus, int bf16);
+bool encode_expand_dw(const JoinedTable& kt, const ConvPlan& pl, const ConvArgs& a, const DwArgs& d, int nominal_cus, int bf16, std::vector<KernelLaunch>* out);
 bool encode_dwconv(const KernelTable& kt, const DwArgs& a, int bf16, std::vector<KernelLaunch>* out);
 bool encode_maxpool(const KernelTable& kt, const PoolArgs& a, int bf16, std::vector<KernelLaunch>* out);
 bool encode_gavgpool(const KernelTable& kt, const PoolArgs& a, int bf16, std::vector<KernelLaunch>* out);

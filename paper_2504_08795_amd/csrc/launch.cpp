@@ -24,7 +24,8 @@ static const char* const kNames[K_COUNT] = {
     "conv_wave16_taps_f32_t1w8", "conv_wave16_taps_f32_t2w8", "conv_wave16_taps_bf16_t1w4", "conv_wave16_taps_bf16_t1w8", "conv_wave16_taps_bf16_t2w4", "conv_wave16_taps_bf16_t2w8",
     "conv_wave64_taps_f32_t2w2", "conv_wave64_taps_f32_t2w4", "conv_wave64_taps_f32_t2w8",
     "conv_wave_image_f32_n1_t1w4", "conv_wave_image_f32_n2_t1w4", "conv_wave_image_bf16_n1_t1w4", "conv_wave_image_bf16_n2_t1w4",
-    "conv_wave_image_pool_f32_n2_t1w10", "conv_wave_image_pool_bf16_n2_t1w10"};
+    "conv_wave_image_pool_f32_n2_t1w10", "conv_wave_image_pool_bf16_n2_t1w10",
+    "conv_wave16_expand_dw_f32", "conv_wave16_expand_dw_bf16"};
 
 const char* kernel_name(int32_t id) { return (id >= 0 && id < K_COUNT) ? kNames[id] : "?"; }
 
@@ -284,6 +285,7 @@ struct ConvDwArgs {  // conv_wave_dw_kernel(p, d)
 static_assert(sizeof(ImageConvArgs) == 160 && offsetof(ImageConvArgs, x) == kConvInputOffset, "the input is where every convolution has it");
 constexpr uint32_t kIngestBytes = 28, kProbeBytes = 12, kPairBytes = 2 * sizeof(ConvArgs) + 4;
 static_assert(sizeof(DwFusedArgs) == 32 && sizeof(ConvDwArgs) == 192 && offsetof(ConvDwArgs, d) == sizeof(ConvArgs), "fused depthwise arguments");
+static_assert(sizeof(ExpandDwArgs) == 160, "a size that grab() reads");
 static_assert(sizeof(ConvArgs) == 160 && sizeof(DwArgs) == 72 && sizeof(PoolArgs) == 48 && sizeof(FcArgs) == 56 && sizeof(ReduceArgs) == 48 && sizeof(DwWindowArgs) == 88 && sizeof(PoolWindowArgs) == 64,
               "argument structures must match what the kernels were compiled for");
 static_assert(offsetof(ConvArgs, x) == kConvInputOffset && offsetof(FcArgs, y) == kFcOutputOffset && offsetof(IngestArgs, x) == kIngestInputOffset &&
@@ -359,6 +361,7 @@ std::string JoinedTable::resolve(const AqlRuntime& rt) {
   for (int b = 0; b < 2; ++b) {
     const std::string B = b ? "true" : "false";
     image_pool[b] = get("daris::conv_image_pool_kernel<" + B + ">", sizeof(ImageConvArgs));
+    for (int v = 0; v < kExpandChunks; ++v) expand_dw[b][v] = get("daris::conv_expand_dw_kernel<" + B + ", " + std::to_string(v + 1) + ">", sizeof(ExpandDwArgs));
   }
   return missing;
 }
@@ -569,6 +572,45 @@ bool encode_conv_pair(const KernelTable& kt, const ConvPlan& pl0, const ConvArgs
   pa.p1 = a1;
   pa.n0 = (int)((pl0.grid_x + 7) / 8 * 8);  // the second problem starts at a multiple of 8: its workgroup -> XCD relation is kept
   return push(out, kernel, pl0.kernel, (uint32_t)pa.n0 + pl1.grid_x, (uint32_t)pl0.threads, &pa, kPairBytes) && push_reduce(kt, pl0, a0, bf16, out);
+}
+
+// Bands of output rows that the workgroups of a channel block share: as many as fill the CUs once, and no band with more input pixels than LDS has room for.
+static bool expand_bands(int H, int W, int c_stride, int dw_stride, int nominal_cus, int* band, int* bands) {
+  const int Ho = (H - 1) / dw_stride + 1, groups = c_stride / 16, cus = std::min(std::max(nominal_cus, 8), 256);
+  *band = cdiv(Ho, std::min(std::max(cus / groups, 1), Ho));
+  const int most = (kExpandPixels / W - 3) / dw_stride + 1;  // rows of a band: (band - 1) * stride + 3 of the input
+  if (kExpandPixels / W < 3 || most < 1) return false;
+  *band = std::min(*band, most);
+  *bands = cdiv(Ho, *band);
+  return true;
+}
+
+bool plan_expand_dw(ConvPlan* pl, int H, int W, int cin_stride, int c_stride, int Kpad, int dw_stride, int nominal_cus, int bf16) {
+  int band, bands;
+  if (Kpad != cin_stride || Kpad % 32 || Kpad / 32 > kExpandChunks || c_stride % 16 || (uint64_t)H * W * std::max(cin_stride, c_stride) * 4 >= (1ull << 31) ||
+      (uint64_t)H * W * W >= (1ull << 32) || !expand_bands(H, W, c_stride, dw_stride, nominal_cus, &band, &bands) || (uint64_t)bands * bands * (c_stride / 16) >= (1ull << 32))
+    return false;
+  const ConvPlan own = plan_conv_wave16(H * W, c_stride, Kpad, bf16, std::min(std::max(nominal_cus, 8), 256), false, 0, 2);
+  if (own.kernel == K_NONE) return false;
+  *pl = own;
+  return true;
+}
+
+bool encode_expand_dw(const JoinedTable& kt, const ConvPlan& pl, const ConvArgs& a, const DwArgs& d, int nominal_cus, int bf16, std::vector<KernelLaunch>* out) {
+  ConvPlan own;
+  if (a.kh != 1 || a.kw != 1 || a.stride != 1 || a.pad != 0 || a.res || a.c_real > 0 || d.k != 3 || d.pad != 1 || (d.stride != 1 && d.stride != 2) || d.H != a.Ho || d.W != a.Wo ||
+      d.C != a.Cout || d.Ho != (d.H - 1) / d.stride + 1 || d.Wo != (d.W - 1) / d.stride + 1 || !plan_expand_dw(&own, a.H, a.W, a.Cin, a.Cout, a.Kpad, d.stride, nominal_cus, bf16))
+    return false;
+  if (pl.rows != 16 || pl.nw != 2 || pl.splitk != 1 || pl.S != own.S || pl.sw != own.sw) return false;  // (the order of the sums)
+  ExpandDwArgs e = ExpandDwArgs();
+  e.x = a.x; e.w = a.w; e.bias = a.bias; e.dw_w = d.w; e.dw_bias = d.bias; e.y = d.y;
+  e.H = a.H; e.W = a.W; e.Cin = a.Cin; e.Ho = d.Ho; e.Wo = d.Wo; e.C = a.Cout; e.stride = d.stride; e.act = a.act; e.dw_act = d.act; e.S = pl.S; e.wave_prio = a.wave_prio;
+  if (!expand_bands(a.H, a.W, a.Cout, d.stride, nominal_cus, &e.band, &e.bands)) return false;
+  e.mg_bands = div_magic((uint32_t)e.bands); e.mg_w = div_magic((uint32_t)e.W); e.mg_wo = div_magic((uint32_t)e.Wo);
+  // a wave for every tile, and a thread for every four channels of an output pixel (a second round of either takes as long as the first)
+  const int tiles = cdiv(std::min((e.band - 1) * d.stride + 3, a.H) * a.W, 16), chunks = a.Kpad / 32;
+  e.threads = 64 * std::min(std::max(std::max(tiles, cdiv(std::min(e.band, e.Ho) * e.Wo * 4, 64)), 2), 8);
+  return push(out, kt.expand_dw[bf16][chunks - 1], bf16 ? K_EXPAND_DW_BF16 : K_EXPAND_DW_F32, (uint32_t)(e.bands * (a.Cout / 16)), (uint32_t)e.threads, &e, sizeof(e));
 }
 
 // Grid and place finding of a window kernel (point_of): workgroups in multiples of 8, one band of them per XCD.

@@ -1322,6 +1322,125 @@ __device__ __forceinline__ void conv_image_body(const ImageConvArgs& p, const in
   }
 }
 
+// ---- a 1x1 convolution and the 3x3 depthwise convolution behind it --------------------------------------------------------------
+//
+// A depthwise channel reads only its own channel of the layer in front, so a workgroup that owns 16 channels of a band of output rows computes those
+// channels of the convolution for the rows that the band reads (neighbouring bands compute the rows between them twice), leaves them in LDS, and
+// convolves them there: one launch, and the widest tensor of an inverted residual block is never stored.  K is short, NCH chunks of 32 k, so that a wave
+// has all pixels and weights of its 16-pixel tile on their way at once; the 16 bytes that lanes load straight into registers are whole cache lines.
+// The sums have the order that the convolution by itself has with two waves: the first chunks and the others in accumulators of their own.
+// Bound by its chain of waits (arguments, pixels and weights, LDS, stores), behind which two launches have as much again.  us of the two launches / of one, fp32
+// on 128 CUs: 784 x 192 x 32 5.4 / 4.0, 196 x 384 x 64 4.5 / 3.85, 196 x 576 x 96 5.0 / 4.7, 49 x 960 x 160 5.0 / 4.2.  Two tiles to a wave (fewer loads of
+// weights, twice as long a chain) 3.95, 4.0, 5.1 and 4.85; bands of half as many rows 4.2, 4.1, 4.9 and 4.65, of twice as many 5.4, 4.4, 7.3 and 4.65.
+template <bool BF16, int NCH>
+__device__ __forceinline__ void conv_expand_dw_body(const ExpandDwArgs& p, const int L, float* const lds) {
+  constexpr int ES = BF16 ? 2 : 4, NP = BF16 ? 1 : 3, NA = BF16 ? 1 : 2;
+  constexpr int FIRST = (NCH + 1) / 2;    // chunks of the first accumulator
+  constexpr int ROW = kExpandRow;
+  constexpr int kOutside = (int)0x80000000;
+  float* const taps = lds + kExpandPixels * ROW;  // [9][16] weights and [16] biases of the depthwise layer
+  if (p.wave_prio) __builtin_amdgcn_s_setprio(3);
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int li = lane & 15, lq = lane >> 4;
+  const int g = fast_div(L, p.mg_bands), oy0 = (L - g * p.bands) * p.band, oy1 = min(oy0 + p.band, p.Ho);
+  const int y0 = max(oy0 * p.stride - 1, 0), y1 = min((oy1 - 1) * p.stride + 1, p.H - 1);  // rows of the convolution
+  const int first = y0 * p.W, pixels = (y1 - y0 + 1) * p.W, tiles = (pixels + 15) >> 4;
+
+  const auto xrsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p.x), 0, p.H * p.W * p.Cin * ES, 0x00027000);
+  uint4 a[NCH][NA];
+  auto load_pixels = [&](const int t) {  // lane (i, q): pixel i of tile t, k = 8 q .. 8 q + 7 of each chunk
+    const int i = 16 * t + li;
+    const int at = i < pixels ? (first + i) * p.Cin * ES + lq * 8 * ES : kOutside;  // (a pixel past the band's is a pixel of zeros: see drop_pixels)
+#pragma unroll
+    for (int c = 0; c < NCH; ++c)
+#pragma unroll
+      for (int h = 0; h < NA; ++h) a[c][h] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(xrsrc, at, c * 32 * ES + h * 16, 0));
+  };
+  load_pixels(wave);
+  const unsigned char* const wb = (const unsigned char*)p.w + (size_t)g * (NCH * NP * 1024) + lane * 16;
+  uint4 b[NCH][NP];
+#pragma unroll
+  for (int c = 0; c < NCH; ++c)
+#pragma unroll
+    for (int q = 0; q < NP; ++q) b[c][q] = *(const uint4*)(wb + (c * NP + q) * 1024);
+  const float bias = p.bias[g * 16 + li];
+  const int at_taps = (tid >> 2) * p.C + g * 16 + 4 * (tid & 3);  // (of the first 36 threads; the next four have the biases)
+  float4 tap = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (tid < 36) {
+    if constexpr (BF16) {
+      const uint2 u = *(const uint2*)((const uint16_t*)p.dw_w + at_taps);
+      tap = make_float4(__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xffff0000u), __uint_as_float(u.y << 16), __uint_as_float(u.y & 0xffff0000u));
+    } else {
+      tap = *(const float4*)((const float*)p.dw_w + at_taps);
+    }
+  } else if (tid < 40) {
+    tap = *(const float4*)(p.dw_bias + g * 16 + 4 * (tid & 3));
+  }
+
+  auto keep = [&](const int t, const f32x4& sum) {  // outputs of tile t of the convolution
+    float v[4] = {sum[0] + bias, sum[1] + bias, sum[2] + bias, sum[3] + bias};
+    apply_act(v, p.act);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int i = 16 * t + 4 * lq + r;
+      if (i < pixels) lds[i * ROW + li] = BF16 ? bf16_bits_to_f32(f32_to_bf16_bits(v[r])) : v[r];
+    }
+  };
+  for (int t = wave; t < tiles; t += p.threads >> 6) {
+    if (t != wave) load_pixels(t);
+    f32x4 acc[2][1] = {{f32x4(0.f)}, {f32x4(0.f)}};
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) {
+      Split8 parts;
+      if constexpr (BF16) parts.p[0] = a[c][0];
+      else parts = split8(a[c][0], a[c][NA - 1]);
+      constexpr int PA[6] = {BF16 ? 0 : 2, 1, 0, 1, 0, 0}, PB[6] = {0, 1, 2, 0, 1, 0};
+      f32x4& s = acc[c >= FIRST][0];
+#pragma unroll
+      for (int k = 0; k < (BF16 ? 1 : 6); ++k)
+        s = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, parts.p[PA[k]]), __builtin_bit_cast(bf16x8, b[c][PB[k]]), s, 0, 0, 0);
+    }
+    if constexpr (!BF16) {
+      if (__builtin_expect(out_of_range(acc[0]) || (NCH > 1 && out_of_range(acc[1])), 0)) {
+        ConvArgs c = ConvArgs();
+        c.x = p.x; c.w = p.w; c.H = p.H; c.W = c.Wo = p.W; c.Cin = p.Cin; c.kh = c.kw = c.stride = 1; c.M = p.H * p.W; c.S = p.S; c.mg_wo = p.mg_w;
+        c.mg_cin = 1;  // (every k is below Cin)
+#pragma unroll 1
+        for (int h = 0; h < 2; ++h) {
+          f32x4 s[1];
+          plain_products<3, 16, 1, 1>(c, DwFusedArgs(), first + 16 * t, g, h * 2 * FIRST, h ? 2 * (NCH - FIRST) : 2 * FIRST, s);
+          acc[0][0] = h ? acc[0][0] + s[0] : s[0];
+        }
+        acc[1][0] = f32x4(0.f);
+      }
+    }
+    keep(t, acc[0][0] + acc[1][0]);
+  }
+  if (tid < 40) *(float4*)&taps[4 * tid] = tap;
+  __syncthreads();
+
+  const int items = (oy1 - oy0) * p.Wo * 4;  // a thread has four channels of an output pixel
+  for (int it = tid; it < items; it += p.threads) {
+    const int quad = it & 3, m = it >> 2, r = fast_div(m, p.mg_wo), ox = m - r * p.Wo, oy = oy0 + r;
+    const int iy0 = oy * p.stride - 1, ix0 = ox * p.stride - 1;
+    const float4 s = *(const float4*)&taps[144 + 4 * quad];
+    float v[4] = {s.x, s.y, s.z, s.w};
+#pragma unroll
+    for (int t = 0; t < 9; ++t) {  // (the order of dwconv_point)
+      const int iy = iy0 + t / 3, ix = ix0 + t % 3;
+      const bool in = (unsigned)iy < (unsigned)p.H && (unsigned)ix < (unsigned)p.W;
+      const float4 e = *(const float4*)&lds[(in ? (iy - y0) * p.W + ix : 0) * ROW + 4 * quad], w = *(const float4*)&taps[16 * t + 4 * quad];
+      v[0] = in ? fmaf(e.x, w.x, v[0]) : v[0]; v[1] = in ? fmaf(e.y, w.y, v[1]) : v[1];
+      v[2] = in ? fmaf(e.z, w.z, v[2]) : v[2]; v[3] = in ? fmaf(e.w, w.w, v[3]) : v[3];
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = apply_act(v[i], p.dw_act);
+    unsigned char* const to = (unsigned char*)p.y + ((size_t)(oy * p.Wo + ox) * p.C + g * 16 + 4 * quad) * ES;
+    if constexpr (BF16) put(to, make_uint2(pack_bf16_rne(v[0], v[1]), pack_bf16_rne(v[2], v[3])));
+    else put(to, make_float4(v[0], v[1], v[2], v[3]));
+  }
+}
+
 // ---- pointwise layers: one thread per (output pixel, 16-byte channel vector) ----------------------------------------------
 //
 // Bound by the trip to memory, not by bytes: a layer of MobileNetV2 has one to two waves per SIMD and nothing to hide a load

@@ -39,6 +39,7 @@ std::string build_plan(const daris_dnn& dnn, bool keep_activations, bool pair_la
   if (dnn.in_c < 1 || dnn.in_h < 1 || dnn.in_w < 1) return "bad input shape";
   if (dnn.dtype != DARIS_FP32 && dnn.dtype != DARIS_BF16) return "bad dtype";
   net.bf16 = dnn.dtype == DARIS_BF16;
+  net.plan_cus = plan_cus;
   const int vec = net.bf16 ? 8 : 4, es = net.bf16 ? 2 : 4;
   net.in_c = dnn.in_c;
   net.in_h = dnn.in_h;
@@ -210,16 +211,24 @@ std::string build_plan(const daris_dnn& dnn, bool keep_activations, bool pair_la
     else plan_gather(&L.cp, net.tensor(L.in_t).Cs, rows_taken(L) || (L.cp.rows == 32 && L.cp.nw == 2 && rows_taken_large(L)), net.bf16);
     L.kernel_id = L.cp.kernel;
   }
-  // max pooling in the launch of the convolution that it alone reads
-  for (int l = 0; l + 1 < n && !keep_activations && fuse_ingest; ++l) {
+  // layers that join the one in front, which nobody else reads
+  for (int l = 0; l + 1 < n && !keep_activations; ++l) {
     LayerPlan& A = net.layers[l];
     LayerPlan& B = net.layers[l + 1];
-    if (A.d.op != DARIS_OP_CONV || A.depthwise || A.pair_with >= 0 || B.d.op != DARIS_OP_MAXPOOL || B.in_t != l + 1) continue;
+    if (A.d.op != DARIS_OP_CONV || A.depthwise || A.pair_with >= 0 || B.in_t != l + 1 || B.pair_with >= 0) continue;
     bool only_reader = true;
     for (int q = l + 2; q < n; ++q)
       if (net.layers[q].in_t == l + 1 || net.layers[q].res_t == l + 1) only_reader = false;
     if (!only_reader) continue;
-    if (B.d.k == 3 && B.d.stride == 2 && B.d.pad == 1 && image_pool_takes(A.cp, A.out.H, A.out.W, A.out.Cs, A.d.k, A.d.stride, plan_cus, net.bf16)) B.can_pool = l;
+    if (B.d.op == DARIS_OP_MAXPOOL) {
+      if (fuse_ingest && B.d.k == 3 && B.d.stride == 2 && B.d.pad == 1 && image_pool_takes(A.cp, A.out.H, A.out.W, A.out.Cs, A.d.k, A.d.stride, plan_cus, net.bf16)) B.can_join = l;
+    } else if (B.d.op == DARIS_OP_CONV && B.depthwise && fuse_dw && staged_rows && small_tiles) {
+      if (B.d.k == 3 && B.d.pad == 1 && (B.d.stride == 1 || B.d.stride == 2) && A.d.k == 1 && A.d.stride == 1 && A.d.pad == 0 && A.res_t < 0 && rows_taken(A) && !(l == 0 && net.fuse_ingest) &&
+          plan_expand_dw(&A.cp, A.out.H, A.out.W, net.tensor(A.in_t).Cs, A.out.Cs, A.Kpad, B.d.stride, plan_cus, net.bf16)) {
+        B.can_join = l;
+        A.kernel_id = A.cp.kernel;
+      }
+    }
   }
   const TensorInfo& fin = net.layers[n - 1].out;
   net.n_out = fin.C * fin.H * fin.W;
@@ -245,7 +254,7 @@ std::string build_plan(const daris_dnn& dnn, bool keep_activations, bool pair_la
   std::vector<int> last_use(n + 1, -1);
   for (int l = 0; l < n; ++l) {
     const LayerPlan& L = net.layers[l];
-    const int at = std::max(l, L.pair_with);
+    const int at = net.joined_away(l) ? l + 1 : std::max(l, L.pair_with);
     last_use[l + 1] = at;
     last_use[L.in_t] = std::max(last_use[L.in_t], at);
     if (L.res_t >= 0) last_use[L.res_t] = std::max(last_use[L.res_t], at);
@@ -290,11 +299,13 @@ bool join_layers(NetPlan* net) {
       B.pair_lead = !cut;
       changed = true;
     }
-    // ... and so with a convolution and the pooling layer behind it.
-    if (B.can_pool == l && (B.pools == l) == cut) {
-      B.pools = cut ? -1 : l;
-      A.pair_with = cut ? -1 : l + 1;
-      B.kernel_id = cut ? K_MAXPOOL : net->bf16 ? K_IMAGE_POOL_BF16 : K_IMAGE_POOL_F32;
+    // ... and so with the layers that are computed in the next one's launch.
+    if (B.can_join == l && (B.joins == l) == cut) {
+      const bool pool = B.d.op == DARIS_OP_MAXPOOL;
+      B.joins = cut ? -1 : l;
+      if (pool) A.pair_with = cut ? -1 : l + 1;
+      if (cut) B.kernel_id = pool ? K_MAXPOOL : K_DWCONV;
+      else B.kernel_id = (pool ? K_IMAGE_POOL_F32 : K_EXPAND_DW_F32) + net->bf16;
       changed = true;
     }
   }

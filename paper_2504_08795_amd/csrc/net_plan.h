@@ -33,10 +33,10 @@ struct LayerPlan {
   // nothing, the 1x1 convolution leads) and both carry this mark.
   bool fused_dw = false;
   bool fusable_dw = false;  // the plan allows it; fused_dw is switched off while a stage cut separates the two layers
-  // A convolution whose only reader is the max pooling layer right after it, and whose sums that layer's launch pools where they are computed: the
-  // convolution issues nothing (pair_with = the pooling layer, as for the earlier member of a launch pair) and its output is never
-  // stored; pools = the convolution, at the pooling layer.  can_pool: the plan allows it; switched off while a stage cut separates the two.
-  int pools = -1, can_pool = -1;
+  // Two layers in a row whose first is read by the second alone and never stored: the first is computed in the second one's launch and issues nothing.
+  // joins = the first layer, at the second, and how; can_join: the plan allows it; switched off while a stage cut separates the two.  (A
+  // convolution that a pooling layer joins has that layer as pair_with, like the earlier member of a launch pair.)
+  int joins = -1, can_join = -1;
   int32_t kernel_id = K_NONE;
   void* w_dev = nullptr;
   float* b_dev = nullptr;
@@ -44,6 +44,7 @@ struct LayerPlan {
 
 struct NetPlan {
   int bf16 = 0;
+  int plan_cus = 128;             // the partition size that the plans are made for
   int in_c = 0, in_h = 0, in_w = 0;
   TensorInfo ingest;              // tensor 0
   std::vector<LayerPlan> layers;
@@ -56,8 +57,8 @@ struct NetPlan {
   bool fuse_ingest = false;       // layer 0 reads the caller's fp32 [C][H][W] input itself: no layout conversion launch
 
   const TensorInfo& tensor(int t) const { return t == 0 ? ingest : layers[t - 1].out; }
-  // Whether the output of layer l is pooled in the launch that computes it and never stored.
-  bool pooled_away(int l) const { return l + 1 < (int)layers.size() && layers[l + 1].pools == l; }
+  // Whether layer l is computed in the launch of the next one, and its output never stored.
+  bool joined_away(int l) const { return l + 1 < (int)layers.size() && layers[l + 1].joins == l; }
 };
 
 // Builds shapes, MACs, legal cuts, buffer slots and kernel plans.  pair_launches: two independent convolutions on one
@@ -68,7 +69,7 @@ struct NetPlan {
 // plan_cus: the partition size the convolution grids are balanced for.
 std::string build_plan(const daris_dnn& dnn, bool keep_activations, bool pair_launches, bool fuse_ingest, bool staged_rows, bool small_tiles, bool fuse_dw,
                        int plan_cus, NetPlan* out);
-// Joins what can share a launch across layers (pooled convolutions, fused depthwise layers) wherever no stage cut separates the layers, and
+// Joins what can share a launch across layers (LayerPlan::joins, fused depthwise layers) wherever no stage cut separates the layers, and
 // parts the others.  Returns whether anything changed.
 bool join_layers(NetPlan* net);
 // Chooses k - 1 cuts minimising the largest per-stage MAC count, ties to the lexicographically smallest cut

@@ -45,3 +45,41 @@ def test_first_convolution_and_its_pooling(stem, dtype):
     np.testing.assert_allclose(*outs[1], rtol=1e-5, atol=1e-4 if dtype == "fp32" else 0)
     e_max, e_l2 = rel_err(outs[0][0], oracle_logits(layers, weights, x, dtype))
     assert e_max <= TOL[dtype] and e_l2 <= TOL[dtype], (e_max, e_l2)
+
+
+# c_in, h, w, c_out, stride of the depthwise layer, plan CUs: one to five chunks of K, a band of all rows, bands of one row, a last band of fewer rows, tiles that end
+# inside a row, maps of one pixel and as wide as LDS has room for
+EXPANSIONS = [(160, 7, 7, 960, 1, 128), (96, 14, 14, 576, 2, 128), (64, 14, 14, 384, 1, 128), (32, 28, 28, 192, 2, 128), (32, 28, 28, 192, 1, 96), (128, 13, 17, 48, 2, 32),
+              (64, 1, 1, 16, 1, 128), (32, 40, 106, 32, 1, 256), (96, 5, 100, 16, 2, 8), (160, 21, 9, 32, 1, 64)]
+
+
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("shape", EXPANSIONS)
+def test_expansion_and_its_depthwise_layer(shape, dtype):
+    cin, h, w, cout, s, cus = shape
+    layers = [N.Layer(op=N.OP_CONV, c_in=cin, c_out=cout, k=1, act=2, in_from=-1, has_bn=False),
+              N.Layer(op=N.OP_CONV, c_in=cout, c_out=cout, k=3, stride=s, pad=1, groups=cout, act=2, in_from=0, has_bn=False)]
+    weights = wl.make_weights(layers, 3)
+    x = wl.make_inputs((cin, h, w), 3, 1, "normal")[0]
+    bad = x.copy()
+    bad[0, h // 2, w // 3], bad[cin - 1, 0, w - 1] = np.nan, np.inf
+    outs, plans = _joined_and_parted(layers, weights, (cin, h, w), dtype, [x, bad], plan_cus=cus)
+    assert "expand_dw" in D.daris_kernel_name(plans[1]["kernel_id"]) and plans[0]["out_slot"] == -1, plans
+    np.testing.assert_array_equal(*outs[0])
+    # (which tiles are walked again in plain fp32 depends on the tiles: see above; K is 160 at most)
+    np.testing.assert_allclose(*outs[1], rtol=1e-5, atol=1e-4 if dtype == "fp32" else 0)
+    e_max, e_l2 = rel_err(outs[0][0], oracle_logits(layers, weights, x, dtype))
+    assert e_max <= TOL[dtype] and e_l2 <= TOL[dtype], (e_max, e_l2)
+
+
+def test_expansion_of_small_numbers_keeps_its_precision():
+    """Pixels of 1e-37, whose third parts fall below the smallest bf16 number: the joined launch walks such tiles in plain fp32 as well."""
+    layers = [N.Layer(op=N.OP_CONV, c_in=96, c_out=64, k=1, act=0, in_from=-1, has_bn=False),
+              N.Layer(op=N.OP_CONV, c_in=64, c_out=64, k=3, pad=1, groups=64, act=0, in_from=0, has_bn=False)]
+    weights = [(w, np.zeros_like(b)) for w, b in wl.make_weights(layers, 3)]
+    x = wl.make_inputs((96, 14, 14), 3, 1, "normal")[0]
+    with GpuNet(layers, weights, (96, 14, 14), "fp32") as g:
+        assert "expand_dw" in D.daris_kernel_name(D.daris_get_launch_plan(g.task, 1)["kernel_id"])
+        one, small = g.forward(x), g.forward(x * np.float32(2.0 ** -122))
+    # sums of 96 terms near 2^-122 have no denormal results; what is lost are bits of single products below 2^-149, 2^-27 of a sum's terms
+    np.testing.assert_allclose(small * np.float64(2.0 ** 122), one, rtol=0, atol=2e-6 * np.abs(one).max())
