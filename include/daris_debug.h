@@ -19,7 +19,9 @@ extern "C" {
  * per workgroup, [9] K steps in total, [10] per workgroup slice, [11] per wave, [12] split-K factor, [13] pixel tiles,
  * [14] channel tiles, [15] weight groups, [16] workgroup order mode, [17..19] grid x y z, [20] threads per workgroup,
  * [21] split-K workspace bytes, [22] layer it shares a launch with or -1, [23] 1 = the joint launch is issued at this
- * layer (a convolution that names a pooling layer here is computed and pooled in that layer's launch, whose kernel id is that layer's),
+ * layer (a convolution that names a pooling layer here is computed and pooled in that layer's launch, whose kernel id is that layer's; one that names the FC
+ * layer behind a global average pooling leaves sums over its pixels for that FC layer, and the pooling layer between them, which then
+ * has the convolution's kernel id, issues nothing),
  * [24] activation slot of the layer's output (-1: the caller's logits, or never stored), [25] slot of its input, [26] slot of its
  * residual operand or -1.  A slot is a device buffer shared by tensors whose lifetimes do not overlap.  [27] how the waves come by their
  * pixels: 0 straight into registers, no K step straddles a filter tap, 1 the same for any channel count, 2 the network input as the

@@ -230,7 +230,7 @@ ConvArgs conv_args(TaskRt& T, int l, void* y, const std::vector<void*>& slots, f
   a.res = L.res_t >= 0 ? slots[net.tensor(L.res_t).slot] : nullptr;
   a.H = in.H; a.W = in.W; a.Cin = in.Cs; a.Ho = L.out.H; a.Wo = L.out.W; a.Cout = L.out.Cs;
   a.kh = a.kw = L.d.k; a.stride = L.d.stride; a.pad = L.d.pad;
-  a.Kpad = L.Kpad; a.M = L.out.H * L.out.W; a.act = L.d.act;
+  a.Kpad = L.Kpad; a.M = L.out.H * L.out.W; a.act = L.d.act | (L.sums_pixels ? kActSumPixels : 0);
   a.splitk = L.cp.splitk; a.S = L.cp.S; a.sz = L.cp.sz; a.sw = L.cp.sw;
   a.MT = L.cp.MT; a.NTn = L.cp.NTn; a.G = L.cp.G; a.xmode = L.cp.xmode;
   a.mg_wo = div_magic((uint32_t)a.Wo); a.mg_cin = div_magic((uint32_t)a.Cin); a.mg_kw = div_magic((uint32_t)a.kw); a.mg_mt = tile_magic(L.cp.grid_x, a.MT);
@@ -293,7 +293,7 @@ std::string encode_network(TaskRt& T, const std::vector<void*>& slots, float* ws
           } else {
             ok = encode_dwconv(g_kt, a, bf16, &ks);
           }
-        } else if (L.pair_with >= 0 && !L.pair_lead) {
+        } else if (L.pair_with >= 0 && !L.pair_lead && !L.sums_pixels) {
           ok = true;  // issued together with the next layer
         } else {
           const ConvArgs a = conv_args(T, l, y, slots, ws);
@@ -307,7 +307,7 @@ std::string encode_network(TaskRt& T, const std::vector<void*>& slots, float* ws
             d.w = O.w_dev; d.bias = O.b_dev; d.H = din.H; d.W = din.W; d.stride = O.d.stride; d.act = O.d.act;
             flops += 2.0 * (double)O.macs;
             ok = encode_conv_dw(g_kt, L.cp, b, d, bf16, &ks);
-          } else if (L.pair_with >= 0) {
+          } else if (L.pair_with >= 0 && !L.sums_pixels) {
             LayerPlan& O = net.layers[L.pair_with];
             const ConvArgs b = conv_args(T, L.pair_with, slots[O.out.slot], slots, ws);
             flops += 2.0 * (double)O.macs;
@@ -324,6 +324,11 @@ std::string encode_network(TaskRt& T, const std::vector<void*>& slots, float* ws
         break;
       case DARIS_OP_MAXPOOL:
       case DARIS_OP_GAVGPOOL: {
+        if (L.average_of >= 0) {
+          const LayerPlan& O = net.layers[L.average_of];
+          ok = !L.lonely || encode_pooled_sums(g_kt, (const float*)x, (float*)y, in.Cs, O.cp.MT, in.H * in.W, &ks);
+          break;
+        }
         PoolArgs a = PoolArgs();
         a.x = x; a.y = y; a.H = in.H; a.W = in.W; a.C = in.Cs; a.Ho = L.out.H; a.Wo = L.out.W;
         a.k = L.d.k; a.stride = L.d.stride; a.pad = L.d.pad;
@@ -348,6 +353,13 @@ std::string encode_network(TaskRt& T, const std::vector<void*>& slots, float* ws
         if (direct) {
           seq->out_launch = (int)seq->launches.size();
           seq->out_off = kFcOutputOffset;
+        }
+        if (L.in_t > 0 && net.layers[L.in_t - 1].average_of >= 0) {
+          const LayerPlan& B = net.layers[L.in_t - 1];
+          const LayerPlan& O = net.layers[B.average_of];
+          a.x = B.lonely ? x : slots[O.out.slot];
+          ok = encode_fc_pooled(g_joined, a, B.lonely ? 1 : O.cp.MT, B.lonely ? 1 : O.out.H * O.out.W, bf16, &ks);
+          break;
         }
         ok = encode_fc(g_kt, a, bf16, &ks);
         break;

@@ -49,6 +49,8 @@ enum ConvGather : int {
 
 constexpr uint32_t kNoMagic = 0xffffffffu;
 
+// ConvArgs::act: the activation, and whether the launch stores its outputs' sums over the pixels of each tile (float [MT][Cout]) in place of the outputs.
+constexpr int kActMask = 3, kActSumPixels = 4;
 struct ConvArgs {
   const void* x;      // [H][W][Cin]; with c_real > 0: the network input as the caller gives it, float [c_real][H][W]
   const void* w;      // packed weights in MFMA fragment order (see pack_conv)
@@ -158,6 +160,20 @@ struct FcArgs {
   int stream;    // 1: the matrix is read past the last cache (set by encode_fc)
 };
 
+// An FC layer behind a global average pooling whose convolution has added its outputs up over the pixels of its tiles.
+struct FcPooledArgs {
+  const float* x;  // [tiles][K]
+  const void* w;
+  const float* bias;
+  void* y;         // as FcArgs::y
+  int K, N, Ns, act, out_f32;
+  int tiles, pixels;  // sums of a channel, pixels they are the sums of
+  int unused;
+};
+constexpr int kPooledTiles = 8;       // most sums of a channel
+constexpr int kPooledRows = 8;        // rows of the FC layer's matrix, and waves, in a workgroup
+constexpr int kPooledInputs = 4096;   // most channels: they lie in LDS
+
 // Kernel and tile configuration chosen on the host for one dense convolution.
 struct ConvPlan {
   int32_t kernel;  // KernelId
@@ -257,6 +273,7 @@ struct KernelTable {
 struct JoinedTable {
   const AqlKernel* image_pool[2] = {};  // kGatherImage and the 3 x 3 max pooling behind it
   const AqlKernel* expand_dw[2][kExpandChunks] = {};
+  const AqlKernel* fc_pooled[2] = {};
   std::string resolve(const AqlRuntime& rt);  // as KernelTable::resolve
 };
 
@@ -291,6 +308,12 @@ bool encode_expand_dw(const JoinedTable& kt, const ConvPlan& pl, const ConvArgs&
 bool encode_dwconv(const KernelTable& kt, const DwArgs& a, int bf16, std::vector<KernelLaunch>* out);
 bool encode_maxpool(const KernelTable& kt, const PoolArgs& a, int bf16, std::vector<KernelLaunch>* out);
 bool encode_gavgpool(const KernelTable& kt, const PoolArgs& a, int bf16, std::vector<KernelLaunch>* out);
+// Global average pooling without a launch: the convolution in front adds its outputs up over the pixels of each tile (kActSumPixels), the FC layer behind adds
+// those sums, divides by the number of pixels and rounds.  Whether a convolution planned as pl can; the average alone from its sums (where stage cuts
+// leave the pooling layer by itself; y: float [C], which the FC layer then takes as the sums of one tile of one pixel); the FC layer.
+bool sums_pixels(const ConvPlan& pl, int channels);
+bool encode_pooled_sums(const KernelTable& kt, const float* x, float* y, int C, int tiles, int pixels, std::vector<KernelLaunch>* out);
+bool encode_fc_pooled(const JoinedTable& kt, const FcArgs& a, int tiles, int pixels, int bf16, std::vector<KernelLaunch>* out);
 bool encode_fc(const KernelTable& kt, const FcArgs& a, int bf16, std::vector<KernelLaunch>* out);
 // x: float [C][H][W] -> y: [H][W][Cs]
 bool encode_ingest(const KernelTable& kt, const float* x, void* y, int C, int Cs, int H, int W, int bf16, std::vector<KernelLaunch>* out);

@@ -285,6 +285,7 @@ struct ConvDwArgs {  // conv_wave_dw_kernel(p, d)
 static_assert(sizeof(ImageConvArgs) == 160 && offsetof(ImageConvArgs, x) == kConvInputOffset, "the input is where every convolution has it");
 constexpr uint32_t kIngestBytes = 28, kProbeBytes = 12, kPairBytes = 2 * sizeof(ConvArgs) + 4;
 static_assert(sizeof(DwFusedArgs) == 32 && sizeof(ConvDwArgs) == 192 && offsetof(ConvDwArgs, d) == sizeof(ConvArgs), "fused depthwise arguments");
+static_assert(sizeof(FcPooledArgs) == 64 && offsetof(FcPooledArgs, y) == kFcOutputOffset, "the logits are where every FC layer has them");
 static_assert(sizeof(ExpandDwArgs) == 160, "a size that grab() reads");
 static_assert(sizeof(ConvArgs) == 160 && sizeof(DwArgs) == 72 && sizeof(PoolArgs) == 48 && sizeof(FcArgs) == 56 && sizeof(ReduceArgs) == 48 && sizeof(DwWindowArgs) == 88 && sizeof(PoolWindowArgs) == 64,
               "argument structures must match what the kernels were compiled for");
@@ -361,6 +362,7 @@ std::string JoinedTable::resolve(const AqlRuntime& rt) {
   for (int b = 0; b < 2; ++b) {
     const std::string B = b ? "true" : "false";
     image_pool[b] = get("daris::conv_image_pool_kernel<" + B + ">", sizeof(ImageConvArgs));
+    fc_pooled[b] = get("daris::fc_pooled_kernel<" + B + ">", sizeof(FcPooledArgs));
     for (int v = 0; v < kExpandChunks; ++v) expand_dw[b][v] = get("daris::conv_expand_dw_kernel<" + B + ", " + std::to_string(v + 1) + ">", sizeof(ExpandDwArgs));
   }
   return missing;
@@ -647,8 +649,27 @@ bool encode_maxpool(const KernelTable& kt, const PoolArgs& a, int bf16, std::vec
   const size_t total = (size_t)a.Ho * a.Wo * (a.C / (bf16 ? 8 : 4));
   return push(out, kt.maxpool[bf16], K_MAXPOOL, (uint32_t)((total + 255) / 256), 256, &a, sizeof(a));
 }
-bool encode_gavgpool(const KernelTable& kt, const PoolArgs& a, int bf16, std::vector<KernelLaunch>* out) {
+bool encode_gavgpool(const KernelTable& kt, const PoolArgs& layer, int bf16, std::vector<KernelLaunch>* out) {
+  PoolArgs a = layer;
+  a.k = a.H * a.W;  // what the sums are divided by
   return push(out, kt.gavgpool[bf16], K_GAVGPOOL, (uint32_t)cdiv(a.C, 64), 256, &a, sizeof(a));
+}
+bool sums_pixels(const ConvPlan& pl, int channels) {
+  return (pl.rows == 16 || pl.rows == 32) && pl.splitk == 1 && pl.gather != kGatherInput && pl.gather != kGatherImage && pl.MT <= kPooledTiles && channels <= kPooledInputs;
+}
+bool encode_pooled_sums(const KernelTable& kt, const float* x, float* y, int C, int tiles, int pixels, std::vector<KernelLaunch>* out) {
+  if (tiles < 1 || tiles > kPooledTiles) return false;
+  PoolArgs a = PoolArgs();
+  a.x = x; a.y = y; a.H = tiles; a.W = 1; a.C = C; a.Ho = a.Wo = 1;
+  a.k = pixels;
+  return push(out, kt.gavgpool[0], K_GAVGPOOL, (uint32_t)cdiv(C, 64), 256, &a, sizeof(a));
+}
+bool encode_fc_pooled(const JoinedTable& kt, const FcArgs& f, int tiles, int pixels, int bf16, std::vector<KernelLaunch>* out) {
+  if (tiles < 1 || tiles > kPooledTiles || f.K > kPooledInputs || f.K % (bf16 ? 8 : 4)) return false;
+  FcPooledArgs a = FcPooledArgs();
+  a.x = (const float*)f.x; a.w = f.w; a.bias = f.bias; a.y = f.y;
+  a.K = f.K; a.N = f.N; a.Ns = f.Ns; a.act = f.act; a.out_f32 = f.out_f32; a.tiles = tiles; a.pixels = pixels;
+  return push(out, kt.fc_pooled[bf16], K_FC, (uint32_t)cdiv(a.Ns, kPooledRows), 64 * kPooledRows, &a, sizeof(a));
 }
 bool encode_fc(const KernelTable& kt, const FcArgs& layer, int bf16, std::vector<KernelLaunch>* out) {
   FcArgs a = layer;

@@ -345,7 +345,37 @@ struct WaveEpilogue {
         }
       }
     }
-    apply_act(val, p.act);
+    apply_act(val, p.act & kActMask);
+    if (__builtin_expect(p.act & kActSumPixels, 0)) {  // the sums of the tile's outputs over its pixels, for the global average behind the layer
+      __syncthreads();  // (every thread has read its partial sums)
+#pragma unroll
+      for (int r = 0; r < RQ; ++r) {
+        const int e = 4 * (tid + r * NT);
+        int j, mm, n;
+        place(e, m0, nb0, &j, &mm, &n);
+        const bool in = mm < p.M;
+        float4 v;
+        v.x = in ? val[4 * r] : 0.f; v.y = in ? val[4 * r + 1] : 0.f; v.z = in ? val[4 * r + 2] : 0.f; v.w = in ? val[4 * r + 3] : 0.f;
+        if constexpr (BF16) {
+          const uint32_t a = pack_bf16_rne(v.x, v.y), b = pack_bf16_rne(v.z, v.w);
+          v = make_float4(__uint_as_float(a << 16), __uint_as_float(a & 0xffff0000u), __uint_as_float(b << 16), __uint_as_float(b & 0xffff0000u));
+        }
+        if (QUADS % NT == 0 || e < TILE) *(float4*)&red[e] = v;
+      }
+      __syncthreads();
+      const int c = tid % R, n = nb0 * R + tid;
+      if (tid < TN * R && n < p.Cout) {
+        const float* const from = red + tid / R * (R * R) + c;
+        float s = 0.f;
+#pragma unroll
+        for (int i = 0; i < R; ++i) {  // in the order of the pixels
+          const int v = R == 32 ? (i >> 3) * 4 + (i & 3) : i & 3, lanes = R == 32 ? (i >> 2 & 1) * 32 : (i >> 2) * 16;
+          s += from[v * 64 + lanes];
+        }
+        put((float*)p.y + (size_t)(m0 / R) * p.Cout + n, s);
+      }
+      return;
+    }
     ResVec out[RQ];
 #pragma unroll
     for (int r = 0; r < RQ; ++r) {
@@ -1606,7 +1636,7 @@ __device__ __forceinline__ void gavgpool_group(const PoolArgs& a, const int grou
   }
   part[q][cl] = s;
   __syncthreads();
-  if (q == 0 && c < a.C) put_elem<BF16>(a.y, c, (part[0][cl] + part[1][cl] + part[2][cl] + part[3][cl]) / (float)hw);
+  if (q == 0 && c < a.C) put_elem<BF16>(a.y, c, (part[0][cl] + part[1][cl] + part[2][cl] + part[3][cl]) / (float)a.k);
 }
 
 // ---- FC, batch 1: one wave per output, 16-byte loads along K, butterfly reduction ------------------------------------

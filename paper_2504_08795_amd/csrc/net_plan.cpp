@@ -230,6 +230,23 @@ std::string build_plan(const daris_dnn& dnn, bool keep_activations, bool pair_la
       }
     }
   }
+  // convolution, global average pooling and FC layer, which nobody else reads
+  for (int l = 0; l + 2 < n && !keep_activations && pair_launches; ++l) {
+    LayerPlan& A = net.layers[l];
+    LayerPlan& B = net.layers[l + 1];
+    LayerPlan& C = net.layers[l + 2];
+    if (A.d.op != DARIS_OP_CONV || A.depthwise || A.pair_with >= 0 || A.joins >= 0 || B.d.op != DARIS_OP_GAVGPOOL || B.in_t != l + 1 || C.d.op != DARIS_OP_FC || C.in_t != l + 2) continue;
+    bool only_reader = true;
+    for (int q = l + 2; q < n; ++q)
+      if (net.layers[q].in_t == l + 1 || net.layers[q].res_t == l + 1 || (q > l + 2 && net.layers[q].in_t == l + 2) || net.layers[q].res_t == l + 2) only_reader = false;
+    if (!only_reader || !sums_pixels(A.cp, A.out.Cs)) continue;
+    A.sums_pixels = true;
+    A.pair_with = l + 2;
+    A.out.bytes = std::max(A.out.bytes, (size_t)A.cp.MT * A.out.Cs * 4);
+    B.out.bytes = std::max(B.out.bytes, (size_t)B.out.Cs * 4);
+    B.average_of = l;
+    B.kernel_id = A.kernel_id;
+  }
   const TensorInfo& fin = net.layers[n - 1].out;
   net.n_out = fin.C * fin.H * fin.W;
   net.final_direct = net.layers[n - 1].d.op == DARIS_OP_FC;
@@ -255,7 +272,7 @@ std::string build_plan(const daris_dnn& dnn, bool keep_activations, bool pair_la
   for (int l = 0; l < n; ++l) {
     const LayerPlan& L = net.layers[l];
     const int at = net.joined_away(l) ? l + 1 : std::max(l, L.pair_with);
-    last_use[l + 1] = at;
+    last_use[l + 1] = std::max(last_use[l + 1], at);
     last_use[L.in_t] = std::max(last_use[L.in_t], at);
     if (L.res_t >= 0) last_use[L.res_t] = std::max(last_use[L.res_t], at);
   }
@@ -308,6 +325,15 @@ bool join_layers(NetPlan* net) {
       else B.kernel_id = (pool ? K_IMAGE_POOL_F32 : K_EXPAND_DW_F32) + net->bf16;
       changed = true;
     }
+  }
+  for (int l = 0; l + 1 < (int)net->layers.size(); ++l) {
+    LayerPlan& B = net->layers[l];
+    if (B.average_of < 0) continue;
+    auto starts = [&](int q) { return std::find(net->stage_first.begin(), net->stage_first.end(), q) != net->stage_first.end(); };
+    const bool lonely = starts(l) && starts(l + 1);
+    if (B.lonely != lonely) changed = true;
+    B.lonely = lonely;
+    B.kernel_id = lonely ? (int32_t)K_GAVGPOOL : net->layers[B.average_of].kernel_id;
   }
   return changed;
 }

@@ -37,6 +37,10 @@ struct LayerPlan {
   // joins = the first layer, at the second, and how; can_join: the plan allows it; switched off while a stage cut separates the two.  (A
   // convolution that a pooling layer joins has that layer as pair_with, like the earlier member of a launch pair.)
   int joins = -1, can_join = -1;
+  // A global average pooling that issues nothing: average_of = the convolution in front, which leaves sums over the pixels of its tiles in place of its
+  // output (sums_pixels; pair_with = the FC layer behind, which takes the sums).  lonely: alone in its stage, where it makes the averages from the sums.
+  int average_of = -1;
+  bool sums_pixels = false, lonely = false;
   int32_t kernel_id = K_NONE;
   void* w_dev = nullptr;
   float* b_dev = nullptr;

@@ -2,6 +2,7 @@
 two layers parts them)."""
 import numpy as np
 import pytest
+import torch
 
 import paper_2504_08795_amd as D
 import workloads as wl
@@ -83,3 +84,43 @@ def test_expansion_of_small_numbers_keeps_its_precision():
         one, small = g.forward(x), g.forward(x * np.float32(2.0 ** -122))
     # sums of 96 terms near 2^-122 have no denormal results; what is lost are bits of single products below 2^-149, 2^-27 of a sum's terms
     np.testing.assert_allclose(small * np.float64(2.0 ** 122), one, rtol=0, atol=2e-6 * np.abs(one).max())
+
+
+# c_in, h, w, c_out of the convolution, its window, FC outputs, plan CUs; one to four tiles of 16 or 32 pixels, the last one full or of one pixel; more channels than a lane has
+# loads in flight for, and not a multiple of a wave's
+AVERAGES = [(64, 7, 7, 512, 3, 1000, 128), (320, 7, 7, 1280, 1, 37, 128), (64, 7, 7, 2048, 1, 10, 128), (32, 1, 1, 64, 1, 5, 128), (32, 4, 8, 96, 1, 16, 8), (64, 3, 11, 4000, 1, 9, 256),
+            (64, 10, 10, 512, 1, 21, 128), (128, 8, 8, 24, 3, 1000, 64), (32, 8, 16, 40, 3, 3, 8)]
+
+
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("shape", AVERAGES)
+def test_convolution_global_average_and_fc(shape, dtype):
+    cin, h, w, cout, k, n_out, cus = shape
+    layers = [N.Layer(op=N.OP_CONV, c_in=cin, c_out=cout, k=k, pad=k // 2, act=1, in_from=-1, has_bn=False),
+              N.Layer(op=N.OP_GAVGPOOL, c_in=cout, c_out=cout, in_from=0), N.Layer(op=N.OP_FC, c_in=cout, c_out=n_out, in_from=1)]
+    weights = wl.make_weights(layers, 3)
+    x = wl.make_inputs((cin, h, w), 3, 1, "normal")[0]
+    outs, plans = _joined_and_parted(layers, weights, (cin, h, w), dtype, [x, x[::-1].copy()], plan_cus=cus)
+    assert plans[0]["pair_with"] == 2 and not plans[0]["pair_lead"] and plans[1]["kernel_id"] == plans[0]["kernel_id"], plans
+    for o in outs:
+        np.testing.assert_array_equal(*o)                     # the pooling layer alone in its stage makes the averages from the same sums
+    e_max, e_l2 = rel_err(outs[0][0], oracle_logits(layers, weights, x, dtype))
+    assert e_max <= TOL[dtype] and e_l2 <= TOL[dtype], (e_max, e_l2)
+    with GpuNet(layers, weights, (cin, h, w), dtype, flags=D.NO_PAIR, plan_cus=cus) as g:   # pooling in a launch of its own: the same sums in another order
+        assert D.daris_kernel_name(D.daris_get_launch_plan(g.task, 1)["kernel_id"]) == "gavgpool"
+        e_max, e_l2 = rel_err(outs[0][0], g.forward(x))
+    assert e_max <= (2e-6 if dtype == "fp32" else 2 ** -7), e_max
+
+
+def test_infinite_averages_stay_infinite():
+    layers = [N.Layer(op=N.OP_CONV, c_in=32, c_out=100, k=1, act=1, in_from=-1, has_bn=False), N.Layer(op=N.OP_GAVGPOOL, c_in=100, c_out=100, in_from=0),
+              N.Layer(op=N.OP_FC, c_in=100, c_out=8, in_from=1)]
+    weights = [(np.abs(w), np.abs(b)) for w, b in wl.make_weights(layers, 3)[:1]] + [(None, None)] + [(np.abs(w) + 1, b) for w, b in wl.make_weights(layers, 3)[2:]]
+    x = np.ones((32, 5, 5), np.float32)
+    x[0, 2, 2] = np.inf
+    with GpuNet(layers, weights, x.shape, "fp32") as g:
+        assert D.daris_get_launch_plan(g.task, 0)["pair_with"] == 2
+        x_d, y_d = torch.from_numpy(x).cuda(), torch.zeros(8, device="cuda")
+        torch.cuda.synchronize()
+        D.daris_forward(g.task, x_d, y_d, g.parts[0])
+        assert torch.isposinf(y_d).all(), y_d

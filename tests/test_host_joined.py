@@ -13,7 +13,7 @@ HOST = D.VIRTUAL_TIME | D.NO_DEVICE
 N = wl.nets
 
 # code object: {kernel: (bytes of its argument block, how many instances)}
-JOINED_KERNELS = {"daris_joined_kernels": {"conv_image_pool_kernel": (160, 2), "conv_expand_dw_kernel": (160, 10)}}
+JOINED_KERNELS = {"daris_joined_kernels": {"conv_image_pool_kernel": (160, 2), "conv_expand_dw_kernel": (160, 10), "fc_pooled_kernel": (64, 2)}}
 
 
 @pytest.mark.parametrize("co", sorted(JOINED_KERNELS))
@@ -53,3 +53,15 @@ def test_first_pooling_layer_joins_the_convolution(net, dtype):
     other = [N.Layer(op=N.OP_CONV, c_in=3, c_out=64, k=7, stride=2, pad=3, in_from=-1), N.Layer(op=N.OP_MAXPOOL, c_in=64, c_out=64, k=3, stride=2, pad=1, in_from=0),
              N.Layer(op=N.OP_CONV, c_in=64, c_out=64, k=3, stride=2, pad=1, in_from=1), N.Layer(op=N.OP_CONV, c_in=64, c_out=64, k=1, in_from=0)]
     assert _plans(other, shp, dtype)[0]["pair_with"] == -1              # somebody else reads the convolution
+
+
+@pytest.mark.parametrize("net", ["resnet18", "resnet50", "mobilenet_v2"])
+def test_global_average_without_a_launch(net):
+    layers, shp = wl.build_net(net)
+    for dtype in ("fp32", "bf16"):
+        p = _plans(layers, shp, dtype)
+        n = len(layers)
+        assert p[n - 3]["pair_with"] == n - 1 and p[n - 2]["pair_with"] == -1 and p[n - 2]["kernel_id"] == p[n - 3]["kernel_id"]
+        assert len({p[n - 3]["in_slot"], p[n - 3]["out_slot"], p[n - 2]["out_slot"]} - {-1}) == 3   # the sums live until the FC layer has read them
+        legal = 1 + sum(1 for l in range(n - 1) if all(q.in_from >= l and not 0 <= q.res_from < l for q in layers[l + 1:]))
+        assert D.daris_kernel_name(_plans(layers, shp, dtype, k=legal)[n - 2]["kernel_id"]) == "gavgpool"    # alone in its stage
