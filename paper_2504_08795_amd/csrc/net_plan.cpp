@@ -32,7 +32,7 @@ static void split_bf16(float f, uint16_t out[3]) {
 }
 
 std::string build_plan(const daris_dnn& dnn, bool keep_activations, bool pair_launches, bool fuse_ingest, bool staged_rows, bool small_tiles, bool fuse_dw,
-                       int plan_cus, NetPlan* out) {
+                       int plan_cus, NetPlan* out, bool tall_tiles) {
   NetPlan& net = *out;
   net = NetPlan();
   if (dnn.n_layers < 1 || !dnn.layers) return "DNN has no layers";
@@ -222,11 +222,11 @@ std::string build_plan(const daris_dnn& dnn, bool keep_activations, bool pair_la
     if (!only_reader) continue;
     if (B.d.op == DARIS_OP_MAXPOOL) {
       if (fuse_ingest && B.d.k == 3 && B.d.stride == 2 && B.d.pad == 1 && image_pool_takes(A.cp, A.out.H, A.out.W, A.out.Cs, A.d.k, A.d.stride, plan_cus, net.bf16)) B.can_join = l;
-    } else if (B.d.op == DARIS_OP_CONV && B.depthwise && fuse_dw && staged_rows && small_tiles) {
+    } else if (B.d.op == DARIS_OP_CONV && B.depthwise && staged_rows && small_tiles) {
       if (B.d.k == 3 && B.d.pad == 1 && (B.d.stride == 1 || B.d.stride == 2) && A.d.k == 1 && A.d.stride == 1 && A.d.pad == 0 && A.res_t < 0 && rows_taken(A) && !(l == 0 && net.fuse_ingest) &&
           plan_expand_dw(&A.cp, A.out.H, A.out.W, net.tensor(A.in_t).Cs, A.out.Cs, A.Kpad, B.d.stride, plan_cus, net.bf16)) {
-        B.can_join = l;
-        A.kernel_id = A.cp.kernel;
+        if (fuse_dw) B.can_join = l;
+        A.kernel_id = A.cp.kernel;  // (launches of their own give the same sums)
       }
     }
   }
