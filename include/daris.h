@@ -75,6 +75,8 @@ enum {
                                  instead of fetching whole 64-byte rows through LDS where the shape allows (A/B)   */
   DARIS_NO_SMALL_TILES = 4096, /* ... and keep 32-pixel tiles with a K split across workgroups (and its reduction launch)
                                  for deep layers of few pixels, instead of 16-pixel tiles (A/B)                  */
+  DARIS_NO_TALL_TILES = 16384, /* ... and give a wave two blocks of channels instead of two blocks of pixels where three taps
+                                 share a fetch (A/B and tests; the same sums bit for bit)                         */
   DARIS_NO_FUSED_DW = 8192     /* ... and run a 3x3 depthwise convolution in a launch of its own instead of computing it
                                  inside the 1x1 convolution that is its only reader (A/B and tests)              */
 };

@@ -44,6 +44,8 @@ extern "C" const char daris_block_kernels_co[];
 extern "C" const char daris_block_kernels_co_end[];
 extern "C" const char daris_joined_kernels_co[];
 extern "C" const char daris_joined_kernels_co_end[];
+extern "C" const char daris_tall_kernels_co[];
+extern "C" const char daris_tall_kernels_co_end[];
 extern "C" const char daris_point_kernels_co[];
 extern "C" const char daris_point_kernels_co_end[];
 
@@ -318,7 +320,7 @@ std::string encode_network(TaskRt& T, const std::vector<void*>& slots, float* ws
               seq->in_launch = (int)seq->launches.size();
               seq->in_off = kConvInputOffset;
             }
-            ok = encode_conv(g_kt, L.cp, a, bf16, &ks);
+            ok = L.tall ? encode_conv_tall(g_joined, L.cp, a, bf16, &ks) : encode_conv(g_kt, L.cp, a, bf16, &ks);
           }
         }
         break;
@@ -900,6 +902,7 @@ daris_status daris_init(int device, uint64_t seed, int flags) {
                                {daris_taps_kernels_co, (size_t)(daris_taps_kernels_co_end - daris_taps_kernels_co)},
                                {daris_image_kernels_co, (size_t)(daris_image_kernels_co_end - daris_image_kernels_co)},
                                {daris_joined_kernels_co, (size_t)(daris_joined_kernels_co_end - daris_joined_kernels_co)},
+                               {daris_tall_kernels_co, (size_t)(daris_tall_kernels_co_end - daris_tall_kernels_co)},
                                {daris_point_kernels_co, (size_t)(daris_point_kernels_co_end - daris_point_kernels_co)}});
       if (err.empty()) {
         err = g_kt.resolve(g_rt);
@@ -1018,7 +1021,7 @@ daris_task daris_register_task(const daris_dnn* dnn, int64_t period_ns, int64_t 
   if (priority != DARIS_HP && priority != DARIS_LP) return fail(DARIS_EINVAL, "priority must be DARIS_HP or DARIS_LP");
   if (G->tasks.size() >= 65535) return fail(DARIS_ERANGE, "too many tasks");
   std::unique_ptr<TaskRt> T(new TaskRt());
-  std::string err = build_plan(*dnn, G->flags & DARIS_KEEP_ACTIVATIONS, !(G->flags & DARIS_NO_PAIR), !(G->flags & DARIS_NO_FUSED_INGEST), !(G->flags & DARIS_NO_STAGED_ROWS), !(G->flags & DARIS_NO_SMALL_TILES), !(G->flags & DARIS_NO_FUSED_DW), G->plan_cus, &T->net);
+  std::string err = build_plan(*dnn, G->flags & DARIS_KEEP_ACTIVATIONS, !(G->flags & DARIS_NO_PAIR), !(G->flags & DARIS_NO_FUSED_INGEST), !(G->flags & DARIS_NO_STAGED_ROWS), !(G->flags & DARIS_NO_SMALL_TILES), !(G->flags & DARIS_NO_FUSED_DW), G->plan_cus, &T->net, !(G->flags & DARIS_NO_TALL_TILES));
   if (!err.empty()) return fail(DARIS_EINVAL, "%s", err.c_str());
   if (!G->nodev) {
     NetPlan& net = T->net;

@@ -269,16 +269,21 @@ struct KernelTable {
   std::string resolve(const AqlRuntime& rt);
 };
 
-// The kernels that compute several layers in a row.
+// The kernels that compute several layers in a row, and those that run a plan of KernelTable's in tiles of another shape.
 struct JoinedTable {
   const AqlKernel* image_pool[2] = {};  // kGatherImage and the 3 x 3 max pooling behind it
   const AqlKernel* expand_dw[2][kExpandChunks] = {};
   const AqlKernel* fc_pooled[2] = {};
+  const AqlKernel* tall[2][3] = {};     // [bf16][log2(nw) - 1]
   std::string resolve(const AqlRuntime& rt);  // as KernelTable::resolve
 };
 
 // Dense convolution: the main kernel, then the split-K reduction if the plan has one.  False on an inconsistent plan.
 bool encode_conv(const KernelTable& kt, const ConvPlan& pl, const ConvArgs& a, int bf16, std::vector<KernelLaunch>* out);
+// A plan of 16-pixel tiles with three taps per fetch and two blocks of channels to a wave, run with two blocks of pixels in place of them (conv_taps_body,
+// TM = 2): the same K slices, hence the same sums.  Whether it should be (not where it would take more rounds of the CUs), and the launch.
+bool tall_takes(const ConvPlan& pl, int M, int nominal_cus);
+bool encode_conv_tall(const JoinedTable& kt, const ConvPlan& pl, const ConvArgs& a, int bf16, std::vector<KernelLaunch>* out);
 // Two independent convolutions in one launch: pl0/a0 as planned by plan_conv, pl1/a1 by plan_conv_like(pl0, ...).
 bool encode_conv_pair(const KernelTable& kt, const ConvPlan& pl0, const ConvArgs& a0, const ConvPlan& pl1, const ConvArgs& a1, int bf16,
                       std::vector<KernelLaunch>* out);

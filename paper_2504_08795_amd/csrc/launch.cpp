@@ -55,6 +55,12 @@ static int32_t conv_kernel(int rows, int bf16, int tn, int nw, bool taps) {
 // round's worth of work.  1 = perfectly even; 98 workgroups on 96 CUs: 1.96.
 static double round_waste(int groups, int cus) { return (double)cdiv(groups, cus) * cus / groups; }
 
+// Workgroups of a launch of MT pixel tiles and G weight groups in the order of conv_tile_of.
+static uint32_t tile_order(int MT, int G, int* xmode) {
+  *xmode = G % 8 == 0 ? 1 : 8 % G == 0 ? 2 : 0;
+  return (uint32_t)(*xmode == 2 ? 8 * cdiv(MT, 8 / G) : G * MT);
+}
+
 static ConvPlan plan_conv_wave(int M, int N, int Kpad, int bf16, int step_align, int nominal_cus, bool allow_block, ThreeTaps three_taps, int force_tn = 0, int force_nw = 0) {
   const int kNominalWaveSlots = 4 * nominal_cus;  // SIMDs of the partition size the plan is balanced for
   // What a launch of few tiles pays for is its fixed cost and idle CUs.  Best found on a 128-CU partition (ResNet-18 shapes): 8
@@ -140,16 +146,7 @@ static ConvPlan plan_conv_wave(int M, int N, int Kpad, int bf16, int step_align,
   pl.MT = cdiv(M, pl.rows);  // (the division multipliers are filled in by the caller, which knows Wo, Cin and kw)
   pl.NTn = nb / tn;
   pl.G = pl.NTn * z;
-  if (pl.G % 8 == 0) {
-    pl.xmode = 1;
-    pl.grid_x = (uint32_t)(pl.G * pl.MT);
-  } else if (8 % pl.G == 0) {
-    pl.xmode = 2;
-    pl.grid_x = (uint32_t)(8 * cdiv(pl.MT, 8 / pl.G));
-  } else {
-    pl.xmode = 0;
-    pl.grid_x = (uint32_t)(pl.G * pl.MT);
-  }
+  pl.grid_x = tile_order(pl.MT, pl.G, &pl.xmode);
   pl.ws_bytes = z > 1 ? (size_t)z * M * N * sizeof(float) : 0;
   pl.kernel = conv_kernel(pl.rows, bf16, tn, nw, taps);
   return pl;
@@ -207,16 +204,7 @@ static ConvPlan plan_conv_wave16(int M, int N, int Kpad, int bf16, int nominal_c
   pl.MT = mt;
   pl.NTn = nb / tn;
   pl.G = pl.NTn;
-  if (pl.G % 8 == 0) {
-    pl.xmode = 1;
-    pl.grid_x = (uint32_t)(pl.G * pl.MT);
-  } else if (8 % pl.G == 0) {
-    pl.xmode = 2;
-    pl.grid_x = (uint32_t)(8 * cdiv(pl.MT, 8 / pl.G));
-  } else {
-    pl.xmode = 0;
-    pl.grid_x = (uint32_t)(pl.G * pl.MT);
-  }
+  pl.grid_x = tile_order(pl.MT, pl.G, &pl.xmode);
   pl.ws_bytes = 0;
   pl.kernel = conv_kernel(16, bf16, tn, nw, taps);
   return pl;
@@ -362,6 +350,8 @@ std::string JoinedTable::resolve(const AqlRuntime& rt) {
   for (int b = 0; b < 2; ++b) {
     const std::string B = b ? "true" : "false";
     image_pool[b] = get("daris::conv_image_pool_kernel<" + B + ">", sizeof(ImageConvArgs));
+    for (int v = 0; v < 3; ++v)  // the variants that taps_kernel has with two blocks
+      if (taps_kernel(16, b, 2, 2 << v) != K_NONE) tall[b][v] = get("daris::conv_taps16_tall_kernel<" + B + ", " + std::to_string(2 << v) + ">", sizeof(ConvArgs));
     fc_pooled[b] = get("daris::fc_pooled_kernel<" + B + ">", sizeof(FcPooledArgs));
     for (int v = 0; v < kExpandChunks; ++v) expand_dw[b][v] = get("daris::conv_expand_dw_kernel<" + B + ", " + std::to_string(v + 1) + ">", sizeof(ExpandDwArgs));
   }
@@ -519,6 +509,24 @@ bool encode_conv(const KernelTable& kt, const ConvPlan& pl, const ConvArgs& a, i
     kernel = large ? kt.large[bf16][taps][pl.tn - 1] : taps ? kt.taps[bf16][v] : kt.conv[bf16][v][pl.gather];
   }
   return push(out, kernel, pl.kernel, pl.grid_x, (uint32_t)pl.threads, &a, sizeof(a)) && push_reduce(kt, pl, a, bf16, out);
+}
+
+bool tall_takes(const ConvPlan& pl, int M, int nominal_cus) {
+  if (pl.gather != kGatherTaps || pl.tn != 2 || pl.rows != 16 || pl.splitk != 1) return false;
+  const int cus = std::min(std::max(nominal_cus, 8), 256);
+  return cdiv(cdiv(M, 32) * pl.NTn * 2, cus) <= cdiv(pl.tiles, cus);
+}
+
+bool encode_conv_tall(const JoinedTable& kt, const ConvPlan& pl, const ConvArgs& layer, int bf16, std::vector<KernelLaunch>* out) {
+  if (pl.gather != kGatherTaps || pl.tn != 2 || pl.rows != 16 || pl.splitk != 1 || pl.threads != 64 * pl.nw || pl.kernel != conv_kernel(16, bf16, 2, pl.nw, true) || !taps_agree(pl, layer) ||
+      !rows_take(layer, bf16) || pl.S * (bf16 ? 32 : 16) != layer.Kpad)
+    return false;
+  ConvArgs a = layer;
+  a.MT = cdiv(a.M, 32);
+  a.NTn = a.G = pl.NTn * 2;
+  const uint32_t groups = tile_order(a.MT, a.G, &a.xmode);
+  a.mg_mt = tile_magic(groups, a.MT);
+  return push(out, kt.tall[bf16][variant_of(2, pl.nw) - 3], pl.kernel, groups, (uint32_t)pl.threads, &a, sizeof(a));
 }
 
 bool conv_dw_fusable(const ConvPlan& pl, int bf16) {

@@ -210,9 +210,11 @@ template <int R>
 using WaveAcc = typename std::conditional<R == 32, f32x16, f32x4>::type;
 // BUFFER: everything goes through buffer descriptors, which give 0 past the end and drop what is stored there, so that nothing is
 // conditional and the compiler can count the loads.  They hold the whole tensors, below 2 GiB, or (LARGE) the tile's pixels.
-template <bool BF16, int R, int TN, int NW, bool BUFFER, bool LARGE = false>
+// TM = 2 (with TN = 1): two blocks of pixels in place of two of channels.
+template <bool BF16, int R, int TN, int NW, bool BUFFER, bool LARGE = false, int TM = 1>
 struct WaveEpilogue {
-  static constexpr int ES = BF16 ? 2 : 4, NT = NW * 64, V = R * R / 64, TILE = TN * R * R;  // V: accumulator rows of a block
+  static_assert(TM == 1 || (R == 16 && TN == 1 && !LARGE), "blocks of pixels or of channels");
+  static constexpr int ES = BF16 ? 2 : 4, NT = NW * 64, V = R * R / 64, TILE = TM * TN * R * R;  // V: accumulator rows of a block
   static constexpr int QUADS = TILE / 4, RQ = (QUADS + NT - 1) / NT;  // quads of the tile, of a thread
   static constexpr int NB = RQ == 1 ? 1 : TN;
   using ResVec = typename std::conditional<BF16, uint2, uint4>::type;
@@ -224,9 +226,9 @@ struct WaveEpilogue {
 
   // channel block, pixel and first channel of the quad that starts at tile element e = (j*V + v)*64 + lane
   __device__ __forceinline__ void place(const int e, const int m0, const int nb0, int* j, int* mm, int* n) const {
-    const int v = (e >> 6) % V, l = e & 63;
-    *j = (e >> 6) / V;
-    *mm = m0 + (R == 32 ? (v >> 2) * 8 + (l >> 5) * 4 + (v & 3) : (l >> 4) * 4 + v);
+    const int v = (e >> 6) % V, l = e & 63, block = (e >> 6) / V;
+    *j = TM == 1 ? block : 0;
+    *mm = m0 + (TM == 1 ? 0 : block * R) + (R == 32 ? (v >> 2) * 8 + (l >> 5) * 4 + (v & 3) : (l >> 4) * 4 + v);
     *n = (nb0 + *j) * R + l % R;
   }
   // LARGE: `t`, of the output's shape, from the tile's first pixel on
@@ -265,12 +267,12 @@ struct WaveEpilogue {
 
   // MODE as in conv_wave_body; acc = the wave's partial tile over K steps [sbeg, sbeg + nsteps)
   template <int MODE>
-  __device__ __forceinline__ void finish(const ConvArgs& p, const DwFusedArgs& dwf, WaveAcc<R> (&acc)[TN], float* const red, const int m0, const int nb0, const int zi,
+  __device__ __forceinline__ void finish(const ConvArgs& p, const DwFusedArgs& dwf, WaveAcc<R> (&acc)[TM * TN], float* const red, const int m0, const int nb0, const int zi,
                                          const int sbeg, const int nsteps) {
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     auto park = [&]() {
 #pragma unroll
-      for (int j = 0; j < TN; ++j)
+      for (int j = 0; j < TM * TN; ++j)
 #pragma unroll
         for (int v = 0; v < V; ++v) red[wave * TILE + (j * V + v) * 64 + lane] = acc[j][v];
     };
@@ -294,14 +296,14 @@ struct WaveEpilogue {
     };
     park();
     if constexpr (!BF16) {
-      spoil_unless_in_range(acc, red + wave * TILE, V * TN);
+      spoil_unless_in_range(acc, red + wave * TILE, V * TM * TN);
     }
     __syncthreads();
     add_up();
     if constexpr (!BF16) {
       if (__builtin_expect(spoiled(sums[0].x), 0)) {  // every thread of the workgroup or none (out of the way: a launch fetches its code anew, and a longer path costs 0.2 us)
         __syncthreads();
-        plain_products<MODE, R, 1, TN>(p, dwf, m0, nb0, sbeg, nsteps, acc);
+        plain_products<MODE, R, TM, TN>(p, dwf, m0, nb0, sbeg, nsteps, acc);
         park();
         __syncthreads();
         add_up();
@@ -363,16 +365,17 @@ struct WaveEpilogue {
         if (QUADS % NT == 0 || e < TILE) *(float4*)&red[e] = v;
       }
       __syncthreads();
-      const int c = tid % R, n = nb0 * R + tid;
-      if (tid < TN * R && n < p.Cout) {
-        const float* const from = red + tid / R * (R * R) + c;
+      const int c = threadIdx.x % R, block = threadIdx.x / R, n = (nb0 + (TM == 1 ? block : 0)) * R + c;
+      if (block < TM * TN && n < p.Cout) {
+        const float* const from = red + block * (R * R) + c;
         float s = 0.f;
 #pragma unroll
         for (int i = 0; i < R; ++i) {  // in the order of the pixels
           const int v = R == 32 ? (i >> 3) * 4 + (i & 3) : i & 3, lanes = R == 32 ? (i >> 2 & 1) * 32 : (i >> 2) * 16;
           s += from[v * 64 + lanes];
         }
-        put((float*)p.y + (size_t)(m0 / R) * p.Cout + n, s);
+        const int mt = m0 / R + (TM == 1 ? 0 : block);
+        if (mt * R < p.M) put((float*)p.y + (size_t)mt * p.Cout + n, s);
       }
       return;
     }
@@ -827,15 +830,16 @@ __device__ __forceinline__ void rows_pipeline(const int n, Load&& load, Begun&& 
   }
 }
 // One chunk through the matrix pipe: the two steps (bf16), or the six products of the operands' parts from the smallest to the largest.
-template <bool BF16, int R, int TN>
-__device__ __forceinline__ void wave_mma(const Split8& a, const uint4 (&b)[TN][BF16 ? 2 : 3], WaveAcc<R> (&acc)[TN]) {
+template <bool BF16, int R, int TN, int TM = 1>
+__device__ __forceinline__ void wave_mma(const Split8 (&a)[TM], const uint4 (&b)[TN][BF16 ? 2 : 3], WaveAcc<R> (&acc)[TM * TN]) {
   constexpr int PA[6] = {BF16 ? 0 : 2, 1, 0, 1, 0, 0}, PB[6] = {0, 1, 2, 0, 1, 0};
 #pragma unroll
   for (int t = 0; t < (BF16 ? 2 : 6); ++t)
 #pragma unroll
-    for (int j = 0; j < TN; ++j) {
-      if constexpr (R == 32) acc[j] = mfma_bf16(a.p[PA[t]], b[j][PB[t]], acc[j]);
-      else acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a.p[PA[t]]), __builtin_bit_cast(bf16x8, b[j][PB[t]]), acc[j], 0, 0, 0);
+    for (int j = 0; j < TM * TN; ++j) {
+      const uint4 l = a[j / TN].p[PA[t]], r = b[j % TN][PB[t]];
+      if constexpr (R == 32) acc[j] = mfma_bf16(l, r, acc[j]);
+      else acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, l), __builtin_bit_cast(bf16x8, r), acc[j], 0, 0, 0);
     }
 }
 // LARGE: tensors of 2 GiB and more, whose byte offsets count from what the tile touches instead of from the tensor's start.  (Everywhere,
@@ -960,12 +964,12 @@ __device__ __forceinline__ void conv_rows_body(const ConvArgs& p, const int mt, 
           const int at = BF16 ? (R == 32 ? 2 : 4) * h + lh : 2 * lh + h;
           a[h] = st[(R == 32 ? li : 16 * (at >> 2) + li) * 4 + ((at & 3) ^ ((li >> 1) & 3))];
         }
-        Split8 parts;
+        Split8 parts[1];
         if constexpr (BF16) {
-          parts.p[0] = a[0];
-          parts.p[1] = a[1];
+          parts[0].p[0] = a[0];
+          parts[0].p[1] = a[1];
         } else {
-          parts = split8(a[0], a[1]);
+          parts[0] = split8(a[0], a[1]);
         }
         wave_mma<BF16, R, TN>(parts, bw[s], acc);
         __builtin_amdgcn_sched_barrier(0);  // the refill takes over the registers of the slot just used
@@ -985,29 +989,38 @@ __device__ __forceinline__ void conv_rows_body(const ConvArgs& p, const int mt, 
 // slice a whole number of groups of three chunks; a group's rows and weights are in flight while the one before is computed.  us on 128 CUs without and with: fp32 784 x 128 x 1152 5.85, 5.38
 // (split behind LDS 5.48); 196 x 256 x 2304 7.05, 6.67; 49 x 512 x 4608 7.95, 7.25 (7.70); 3136 x 64 x 576 5.88, 5.68 (5.87); 196 x 512 x 4608 13.1, 12.4; bf16 784 x 128 x 1152 3.35, 2.89; 196 x 256 x 2304 4.00,
 // 3.57; 49 x 512 x 4608 4.25, 3.64.
-template <bool BF16>
+// TM = 2 (R = 16): two blocks of pixels (a run of 2 R + 2) and one of channels to a wave, in place of one and two.  A group of three chunks takes 3 load
+// instructions for the rows of a block of pixels, 5 for those of two, and 9 (bf16 6) for the weights of a block of channels: 14 (11) for two blocks of
+// pixels, 21 (15) for two of channels.  Every sum has the same terms in the same order.  us with two blocks of channels / of pixels: fp32 196 x 256 x 2304 on
+// 128 CUs 6.65 / 6.33, 48 x 512 x 4608 on 64 CUs 10.3 / 9.6, bf16 196 x 256 x 2304 3.56 / 3.48.  With R = 32 the loop is shorter and more rows to split in
+// front of it cost what fewer loads give: 3136 x 64 x 576 fp32 5.7 / 5.8, bf16 3.1 / 3.3.
+template <int TM>
+constexpr int conv_taps_places() {  // rows that a wave's corner of LDS holds
+  return TM == 1 ? 48 : 80;
+}
+template <bool BF16, int TM = 1>
 constexpr int conv_taps_stage() {  // floats of a wave's corner of LDS
-  return BF16 ? 48 * 16 : 3 * 48 * 8;
+  return BF16 ? conv_taps_places<TM>() * 16 : 3 * conv_taps_places<TM>() * 8;
 }
-template <bool BF16, int R, int TN, int NW>
+template <bool BF16, int R, int TN, int NW, int TM = 1>
 constexpr int conv_taps_lds() {
-  return NW * conv_taps_stage<BF16>() > NW * TN * R * R ? NW * conv_taps_stage<BF16>() : NW * TN * R * R;
+  return NW * conv_taps_stage<BF16, TM>() > NW * TM * TN * R * R ? NW * conv_taps_stage<BF16, TM>() : NW * TM * TN * R * R;
 }
-template <bool BF16, int R, int TN, int NW, bool LARGE = false>  // LARGE as in conv_rows_body
+template <bool BF16, int R, int TN, int NW, bool LARGE = false, int TM = 1>  // LARGE as in conv_rows_body
 __device__ __forceinline__ void conv_taps_body(const ConvArgs& p, const int mt, const int g, float* const red) {
   constexpr int ES = BF16 ? 2 : 4;
   constexpr int RK = 64 / ES;                    // k of a row
   constexpr int CK = R == 32 ? RK : 2 * RK;      // k of a chunk, which is two steps
   constexpr int NP = BF16 ? 2 : 3;               // 16-byte pieces of a chunk's weights per lane and channel block: steps, or parts
-  constexpr int HALF = 24;                       // places between a pixel's two rows (R = 16)
-  constexpr int kZeros = R == 32 ? 40 : 20;      // a place that holds zeros (R = 16: and the one HALF further on)
+  constexpr int LOADS = conv_taps_places<TM>() / 16, HALF = conv_taps_places<TM>() / 2;  // HALF: places between a pixel's two rows (R = 16)
+  constexpr int kZeros = TM * R + (R == 32 ? 8 : 4);  // a place that holds zeros (R = 16: and the one HALF further on)
   constexpr int kOutside = (int)0x80000000;      // an offset past the end of any tensor
 
   if (p.wave_prio) __builtin_amdgcn_s_setprio(3);
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform: keeps the K loop's control flow scalar
   const int zi = p.splitk == 1 ? 0 : g / p.NTn;
-  const int m0 = mt * R, nb0 = (g - zi * p.NTn) * TN;
+  const int m0 = mt * R * TM, nb0 = (g - zi * p.NTn) * TN;
   const int s_wg0 = zi * p.sz;
   const int s_wg1 = min(s_wg0 + p.sz, p.S);
   const int sbeg = min(s_wg0 + wave * p.sw, s_wg1);
@@ -1017,12 +1030,12 @@ __device__ __forceinline__ void conv_taps_body(const ConvArgs& p, const int mt, 
   int ky = fast_div(gk, p.mg_cin), ci = gk - ky * p.Cin;
   const int piece = lane & 3, prow = lane >> 2, row_bytes = p.Cin * ES;
   const int base = LARGE ? max(m0 - 1 - p.W, 0) : 0;  // the first pixel that the tile may read
-  int first[3];  // byte offset of the lane's piece of its row in each load, at (ky = 0, ci = 0)
-  bool used[3];
+  int first[LOADS];  // byte offset of the lane's piece of its row in each load, at (ky = 0, ci = 0)
+  bool used[LOADS];
 #pragma unroll
-  for (int r = 0; r < 3; ++r) {
+  for (int r = 0; r < LOADS; ++r) {
     const int place = 16 * r + prow, half = R == 16 && place >= HALF ? 1 : 0, row = place - HALF * half;
-    used[r] = row < R + 2;
+    used[r] = row < TM * R + 2;
     first[r] = (int)((uint32_t)(m0 - 1 + row - p.W - base) * (uint32_t)row_bytes) + 64 * half + piece * 16;
   }
   void* from = const_cast<void*>(p.x);
@@ -1033,11 +1046,11 @@ __device__ __forceinline__ void conv_taps_body(const ConvArgs& p, const int mt, 
     bytes = behind < (uint32_t)kOutside ? (int)behind : kOutside;
   }
   const auto xrsrc = __builtin_amdgcn_make_buffer_rsrc(from, 0, bytes, 0x00027000);
-  uint4 rows[3];
+  uint4 rows[LOADS];
   auto load_rows = [&]() {
     const uint32_t off = (uint32_t)(ky * p.W) * (uint32_t)row_bytes + (uint32_t)(ci * ES);
 #pragma unroll
-    for (int r = 0; r < 3; ++r) rows[r] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(xrsrc, used[r] ? (int)((uint32_t)first[r] + off) : kOutside, 0, 0));
+    for (int r = 0; r < LOADS; ++r) rows[r] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(xrsrc, used[r] ? (int)((uint32_t)first[r] + off) : kOutside, 0, 0));
     ci += CK;
     if (ci >= p.Cin) {
       ci = 0;
@@ -1058,19 +1071,19 @@ __device__ __forceinline__ void conv_taps_body(const ConvArgs& p, const int mt, 
       for (int q = 0; q < NP; ++q) bw[kx][j][q] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(wrsrc[j], lane * 16 + q * 1024, woff, 0));
     woff += NP * 1024;
   };
-  WaveEpilogue<BF16, R, TN, NW, true, LARGE> fin;
+  WaveEpilogue<BF16, R, TN, NW, true, LARGE, TM> fin;
   // Bias and residual are requested first: behind the first rows they would leave the paths into the loop with different loads on
   // their way (see rows_pipeline).  fp32 tiles of 16 x 32 keep their registers for the loop (eight waves fit 128, two workgroups a CU:
   // 196 x 256 x 2304 on 64 CUs 10.2 us instead of 12.0) and request them ahead of the last group, which costs the others 0.1 us.
-  constexpr bool LATE = !BF16 && R == 16 && TN == 2;
+  constexpr bool LATE = !BF16 && R == 16 && TM * TN == 2;
   if constexpr (!LATE) fin.fetch(p, m0, nb0, tid);
-  WaveAcc<R> acc[TN];
+  WaveAcc<R> acc[TM * TN];
 #pragma unroll
-  for (int j = 0; j < TN; ++j) acc[j] = WaveAcc<R>(0.f);
+  for (int j = 0; j < TM * TN; ++j) acc[j] = WaveAcc<R>(0.f);
 
-  // bf16: 48 places of 4 pieces of 16 bytes; fp32: in each of three planes 48 places of 16 values in bf16, 2 pieces of 16 bytes
-  uint4* const st = reinterpret_cast<uint4*>(red) + wave * (conv_taps_stage<BF16>() / 4);
-  constexpr int PLANE = 48 * 2;
+  // bf16: places of 4 pieces of 16 bytes; fp32: in each of three planes places of 16 values in bf16, 2 pieces of 16 bytes
+  uint4* const st = reinterpret_cast<uint4*>(red) + wave * (conv_taps_stage<BF16, TM>() / 4);
+  constexpr int PLANE = conv_taps_places<TM>() * 2;
   const int li = lane % R, lh = lane / R;
   // Pieces of the lane's pixel from the chunk's first k on: bf16 R = 32: 2 h + lh, R = 16: 4 h + lh (h = 0, 1); fp32: 8 k from 8 lh on.
   // row_at: where piece h = 0 of a row lies, or its part in the first plane (spread over the banks)
@@ -1079,7 +1092,13 @@ __device__ __forceinline__ void conv_taps_body(const ConvArgs& p, const int mt, 
     return BF16 ? place * 4 + (lh ^ ((place >> 1) & 3)) : place * 2 + ((lh & 1) ^ ((place >> 2) & 1));
   };
   const int m = m0 + li, x = m - fast_div(m, p.mg_wo) * p.Wo;
-  int at[3] = {x == 0 ? row_at(kZeros) : row_at(li), row_at(li + 1), x == p.Wo - 1 ? row_at(kZeros) : row_at(li + 2)};
+  int at[TM][3] = {{x == 0 ? row_at(kZeros) : row_at(li), row_at(li + 1), x == p.Wo - 1 ? row_at(kZeros) : row_at(li + 2)}};
+  if constexpr (TM == 2) {
+    const int x2 = m + R - fast_div(m + R, p.mg_wo) * p.Wo;
+    at[TM - 1][0] = x2 == 0 ? row_at(kZeros) : row_at(R + li);
+    at[TM - 1][1] = row_at(R + li + 1);
+    at[TM - 1][2] = x2 == p.Wo - 1 ? row_at(kZeros) : row_at(R + li + 2);
+  }
   // lanes exchange data through the wave's buffer: order the accesses of the whole wave, not only of each lane
   auto wave_order = [&]() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -1090,7 +1109,7 @@ __device__ __forceinline__ void conv_taps_body(const ConvArgs& p, const int mt, 
     if constexpr (kx == 0) {
       wave_order();
 #pragma unroll
-      for (int r = 0; r < 3; ++r) {
+      for (int r = 0; r < LOADS; ++r) {
         if constexpr (BF16) {
           st[(16 * r + prow) * 4 + (piece ^ ((prow >> 1) & 3))] = rows[r];
         } else {
@@ -1102,15 +1121,18 @@ __device__ __forceinline__ void conv_taps_body(const ConvArgs& p, const int mt, 
       if constexpr (more) load_rows();
       wave_order();
     }
-    Split8 parts;
-    if constexpr (BF16) {
-      parts.p[0] = st[at[kx]];
-      parts.p[1] = st[R == 32 ? at[kx] ^ 2 : at[kx] + 4 * HALF];
-    } else {
+    Split8 parts[TM];
 #pragma unroll
-      for (int q = 0; q < 3; ++q) parts.p[q] = st[q * PLANE + at[kx]];
+    for (int i = 0; i < TM; ++i) {
+      if constexpr (BF16) {
+        parts[i].p[0] = st[at[i][kx]];
+        parts[i].p[1] = st[R == 32 ? at[i][kx] ^ 2 : at[i][kx] + 4 * HALF];
+      } else {
+#pragma unroll
+        for (int q = 0; q < 3; ++q) parts[i].p[q] = st[q * PLANE + at[i][kx]];
+      }
     }
-    wave_mma<BF16, R, TN>(parts, bw[kx], acc);
+    wave_mma<BF16, R, TN, TM>(parts, bw[kx], acc);
     __builtin_amdgcn_sched_barrier(0);  // the refill takes over the registers of the weights just used
     if constexpr (more) load_w(kx);
   };
@@ -1119,9 +1141,11 @@ __device__ __forceinline__ void conv_taps_body(const ConvArgs& p, const int mt, 
     static_for<0, 3>(load_w);
     // (A pixel past the output is a pixel of zeros: see drop_pixels.  25 x 512 x 4608 with K split over 240 CUs: 7.05 us with the neighbours' sums,
     // 7.22 with sums dropped, 7.10 so.)
-    if (!BF16 && __builtin_expect(m0 + R > p.M, 0)) {
+    if (!BF16 && __builtin_expect(m0 + TM * R > p.M, 0)) {
 #pragma unroll
-      for (int k = 0; k < 3; ++k) at[k] = m < p.M ? at[k] : row_at(kZeros);
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int k = 0; k < 3; ++k) at[i][k] = m + R * i < p.M ? at[i][k] : row_at(kZeros);
     }
     for (int groups = nsteps / 6; groups > 1; --groups) static_for<0, 3>([&](auto kx) { chunk(kx, std::true_type()); });
     if constexpr (LATE) fin.fetch(p, m0, nb0, tid);

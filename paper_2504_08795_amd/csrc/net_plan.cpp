@@ -210,6 +210,7 @@ std::string build_plan(const daris_dnn& dnn, bool keep_activations, bool pair_la
     else if (joint) plan_gather(&L.cp, net.tensor(L.in_t).Cs, rows_taken(L) && rows_taken(net.layers[L.pair_with]) && net.layers[L.pair_with].cp.staged, net.bf16);
     else plan_gather(&L.cp, net.tensor(L.in_t).Cs, rows_taken(L) || (L.cp.rows == 32 && L.cp.nw == 2 && rows_taken_large(L)), net.bf16);
     L.kernel_id = L.cp.kernel;
+    L.tall = tall_tiles && tall_takes(L.cp, L.out.H * L.out.W, plan_cus) && rows_taken(L);
   }
   // layers that join the one in front, which nobody else reads
   for (int l = 0; l + 1 < n && !keep_activations; ++l) {

@@ -124,3 +124,30 @@ def test_infinite_averages_stay_infinite():
         torch.cuda.synchronize()
         D.daris_forward(g.task, x_d, y_d, g.parts[0])
         assert torch.isposinf(y_d).all(), y_d
+
+
+# c_in, h, w, c_out, plan CUs: tiles of 16 pixels and two blocks of channels whose second block of pixels is whole, ragged, of one pixel or empty, images narrower than
+# a block, a single row; four waves (bf16, K = 1152) and eight
+TALL = [(256, 14, 14, 256, 128), (256, 7, 7, 512, 64), (512, 7, 7, 512, 64), (256, 1, 49, 256, 32), (256, 1, 33, 256, 32), (256, 16, 15, 128, 64)]
+
+
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("shape", TALL)
+def test_two_blocks_of_pixels_or_of_channels(shape, dtype):
+    """The same sums, bit for bit, whichever blocks share a wave; with infinities and NaN the tiles that are walked again differ."""
+    cin, h, w, cout, cus = shape
+    layers = [N.Layer(op=N.OP_CONV, c_in=cin, c_out=cout, k=3, pad=1, act=1, in_from=-1, has_bn=False),
+              N.Layer(op=N.OP_CONV, c_in=cout, c_out=cout, k=3, pad=1, act=1, in_from=0, res_from=0, has_bn=False)]
+    weights = wl.make_weights(layers, 3)
+    x = wl.make_inputs((cin, h, w), 3, 1, "normal")[0]
+    bad = x.copy()
+    bad[0, h // 2, w // 3], bad[cin - 1, 0, w - 1] = np.nan, np.inf
+    outs = []
+    for flags in (0, D.NO_TALL_TILES):
+        with GpuNet(layers, weights, (cin, h, w), dtype, flags=flags, plan_cus=cus) as g:
+            assert "conv_wave16_taps" in D.daris_kernel_name(D.daris_get_launch_plan(g.task, 0)["kernel_id"]) and D.daris_get_launch_plan(g.task, 0)["tn"] == 2, D.daris_get_launch_plan(g.task, 0)
+            outs.append([g.forward(x), g.forward(bad)])
+    np.testing.assert_array_equal(outs[0][0], outs[1][0])
+    np.testing.assert_allclose(outs[0][1], outs[1][1], rtol=1e-4, atol=1e-3 if dtype == "fp32" else 0)
+    e_max, e_l2 = rel_err(outs[0][0], oracle_logits(layers, weights, x, dtype))
+    assert e_max <= TOL[dtype] and e_l2 <= TOL[dtype], (e_max, e_l2)

@@ -13,7 +13,8 @@ HOST = D.VIRTUAL_TIME | D.NO_DEVICE
 N = wl.nets
 
 # code object: {kernel: (bytes of its argument block, how many instances)}
-JOINED_KERNELS = {"daris_joined_kernels": {"conv_image_pool_kernel": (160, 2), "conv_expand_dw_kernel": (160, 10), "fc_pooled_kernel": (64, 2)}}
+JOINED_KERNELS = {"daris_joined_kernels": {"conv_image_pool_kernel": (160, 2), "conv_expand_dw_kernel": (160, 10), "fc_pooled_kernel": (64, 2)},
+                  "daris_tall_kernels": {"conv_taps16_tall_kernel": (160, 3)}}
 
 
 @pytest.mark.parametrize("co", sorted(JOINED_KERNELS))
