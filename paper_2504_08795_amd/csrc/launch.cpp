@@ -61,6 +61,16 @@ static uint32_t tile_order(int MT, int G, int* xmode) {
   return (uint32_t)(*xmode == 2 ? 8 * cdiv(MT, 8 / G) : G * MT);
 }
 
+// Waves of a workgroup of 32-pixel tiles, nw if there are no more tiles than CUs.  K is split so finely to shorten the launch of a workgroup a CU; where a CU has
+// several, they fill it by themselves, and fewer waves have fewer partial tiles to sum and less LDS each.  us with eight waves / four, fp32: 3136 x 64
+// x 576 on 96 CUs (196 tiles) 7.6 / 6.3, 784 x 128 x 512 on 96 (100) 5.5 / 5.0, 784 x 128 x 1152 on 48 12.4 / 11.6, 1520 x 256 x 512 on 160 8.0 / 7.4, 6000 x 64 x
+// 256 on 160 6.0 / 5.0, 196 x 256 x 1024 on 48 8.05 / 7.35.  bf16 with four / two: 3136 x 64 x 576 on 32 CUs (98 tiles) 5.45 / 4.95, 3136 x 256 x 1152 on 128 (392)
+// 8.3 / 7.6, 784 x 512 x 4608 on 64 (200) 22.9 / 22.2, but on 32 38.4 / 39.4; with fewer tiles 784 x 256 x 512 beside 196 x 1024 x 512 on 128 (212) 4.2 / 4.5.
+static int fewer_waves(int tiles, int cus, int bf16, int nw) {
+  if (!bf16) return tiles > cus ? std::min(nw, 4) : nw;
+  return 2 * tiles > 5 * cus && tiles < 6 * cus ? std::min(nw, 2) : nw;
+}
+
 static ConvPlan plan_conv_wave(int M, int N, int Kpad, int bf16, int step_align, int nominal_cus, bool allow_block, ThreeTaps three_taps, int force_tn = 0, int force_nw = 0) {
   const int kNominalWaveSlots = 4 * nominal_cus;  // SIMDs of the partition size the plan is balanced for
   // What a launch of few tiles pays for is its fixed cost and idle CUs.  Best found on a 128-CU partition (ResNet-18 shapes): 8
@@ -92,6 +102,7 @@ static ConvPlan plan_conv_wave(int M, int N, int Kpad, int bf16, int step_align,
   const int tiles = (block ? cdiv(M, 64) : cdiv(M, 32)) * (nb / tn);
   int nw = bf16 ? 4 : 8;  // bf16 steps are short: fewer waves to sum through LDS beat a finer K split (measured 0.4-0.8 us per layer)
   while (nw > 2 && (S / nw < 4 || tiles * nw > 8 * kNominalWaveSlots)) nw /= 2;  // >= 4 steps per wave, <= 8 waves per SIMD
+  nw = fewer_waves(tiles, nominal_cus, bf16, nw);
   // ... whose workgroups are the smaller the more of them a CU gets: 104 tiles on 128 CUs 41 us with 8 waves, 51 with 4 (784 x
   // 512 x 4608); 196 tiles 46, 43 and, with 2 waves, 72 (3136 x 256 x 2304); 392 tiles 56, 47 and 43 (12544 x 128 x 1152)
   if (block) nw = tiles > nominal_cus * 5 / 2 ? 2 : tiles > nominal_cus * 3 / 2 ? 4 : 8;
@@ -230,6 +241,13 @@ ConvPlan plan_conv(int M, int N, int Kpad, int bf16, int step_align, int cin_str
     if (p16.kernel != K_NONE) return p16;
   }
   return pl;
+}
+
+ConvPlan plan_conv_beside(const ConvPlan& own, const ConvPlan& light, int M, int N, int Kpad, int bf16, int step_align, int nominal_cus) {
+  const int cus = std::min(std::max(nominal_cus, 8), 256);
+  if (own.rows != 32 || own.splitk != 1 || own.gather == kGatherTaps || light.kernel == K_NONE) return own;
+  const int nw = fewer_waves(own.tiles + (int)((int64_t)light.tiles * std::min(light.S, own.S) / own.S), cus, bf16, own.nw);
+  return nw == own.nw ? own : plan_conv_wave(M, N, Kpad, bf16, step_align, cus, false, kNoTaps, own.tn, nw);
 }
 
 ConvPlan plan_conv_like(const ConvPlan& first, int M, int N, int Kpad, int bf16, int step_align, int nominal_cus) {

@@ -155,8 +155,10 @@ std::string build_plan(const daris_dnn& dnn, bool keep_activations, bool pair_la
     const int sa = staged_rows && conv_rows_staged(net.tensor(heavy.in_t).Cs, net.bf16) ? 2 : 1;
     if (heavy.cp.rows == 64 || heavy.cp.gather == kGatherTaps)  // (kernels that have no form for two problems)
       heavy.cp = plan_conv(heavy.out.H * heavy.out.W, heavy.out.Cs, heavy.Kpad, net.bf16, sa, small_tile_stride(heavy), plan_cus, false);
-    const ConvPlan like = plan_conv_like(heavy.cp, light.out.H * light.out.W, light.out.Cs, light.Kpad, net.bf16,
-                                         staged_rows && conv_rows_staged(net.tensor(light.in_t).Cs, net.bf16) ? 2 : 1, plan_cus);
+    const int sb = staged_rows && conv_rows_staged(net.tensor(light.in_t).Cs, net.bf16) ? 2 : 1;
+    ConvPlan like = plan_conv_like(heavy.cp, light.out.H * light.out.W, light.out.Cs, light.Kpad, net.bf16, sb, plan_cus);
+    heavy.cp = plan_conv_beside(heavy.cp, like, heavy.out.H * heavy.out.W, heavy.out.Cs, heavy.Kpad, net.bf16, sa, plan_cus);
+    like = plan_conv_like(heavy.cp, light.out.H * light.out.W, light.out.Cs, light.Kpad, net.bf16, sb, plan_cus);
     if (like.kernel == K_NONE || (like.rows == 16 && small_tile_stride(light) == 0)) {
       heavy.cp = own;
       continue;
