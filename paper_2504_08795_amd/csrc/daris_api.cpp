@@ -282,8 +282,14 @@ std::string encode_network(TaskRt& T, const std::vector<void*>& slots, float* ws
     double flops = 0;
     switch (L.d.op) {
       case DARIS_OP_CONV:
-        if ((L.depthwise && L.fused_dw) || net.joined_away(l)) {
+        if ((L.depthwise && L.fused_dw) || net.joined_away(l) || net.followed(l)) {
           ok = true;  // computed inside the next layer's launch
+        } else if (!L.depthwise && (L.joins >= 0 || L.follows >= 0)) {
+          const int wide = L.follows >= 0 ? L.follows : l, first = net.layers[wide].joins;
+          LayerPlan& W = net.layers[wide];
+          const ConvArgs a = conv_args(T, first, nullptr, slots, ws), b = conv_args(T, wide, slots[W.out.slot], slots, ws), c = conv_args(T, l, y, slots, ws);
+          flops = 2.0 * (double)(net.layers[first].macs + W.macs + (wide == l ? 0 : L.macs));
+          ok = encode_chain(g_joined, net.layers[first].cp, a, W.cp, b, wide == l ? nullptr : &L.cp, wide == l ? nullptr : &c, bf16, &ks);
         } else if (L.depthwise) {
           DwArgs a = DwArgs();
           a.x = x; a.w = L.w_dev; a.bias = L.b_dev; a.y = y;

@@ -32,6 +32,23 @@ __global__ __launch_bounds__(512) void conv_expand_dw_kernel(const ExpandDwArgs)
   puts_done();
 }
 
+// A 3x3 convolution and the one or two 1x1 convolutions behind it: ConvArgs, then ChainArgs.
+template <bool BF16, int NW>
+__global__ __launch_bounds__(NW * 64) void conv_chain_kernel(const ConvArgs, const ChainArgs) {
+  const ConstPtr src = (ConstPtr)__builtin_amdgcn_kernarg_segment_ptr();
+  const ConvArgs p = conv_args_at(src);
+  ChainArgs c = grab<ChainArgs>(src + sizeof(ConvArgs));
+  c.w3 = in_memory(c.w3); c.bias3 = in_memory(c.bias3); c.res3 = in_memory(c.res3); c.y3 = in_memory(c.y3);
+  c.w1 = in_memory(c.w1); c.bias1 = in_memory(c.bias1); c.y1 = in_memory(c.y1);
+  __shared__ __align__(16) float lds[conv_chain_lds<BF16, NW>()];
+  int mt, g;
+  if (!conv_tile_of(p, (int)blockIdx.x, &mt, &g)) return;
+  conv_chain_body<BF16, NW>(p, c, mt, lds);
+  puts_done();
+}
+template __global__ void conv_chain_kernel<false, 8>(const ConvArgs, const ChainArgs);
+template __global__ void conv_chain_kernel<true, 4>(const ConvArgs, const ChainArgs);
+
 // FC, batch 1, behind a global average pooling of which the convolution has left sums.  Eight rows of the matrix to a workgroup, a wave each; the averages
 // are made once per workgroup and lie in LDS, while the first weights are on their way.
 template <bool BF16>

@@ -31,6 +31,7 @@ enum KernelId : int32_t {
   K_IMAGE_F32_N1, K_IMAGE_F32_N2, K_IMAGE_BF16_N1, K_IMAGE_BF16_N2,
   K_IMAGE_POOL_F32, K_IMAGE_POOL_BF16,  // ... with the 3 x 3 max pooling behind it
   K_EXPAND_DW_F32, K_EXPAND_DW_BF16,    // a 1 x 1 convolution and the depthwise one behind it
+  K_CHAIN_F32, K_CHAIN_BF16,            // a 3 x 3 convolution and the one or two 1 x 1 behind it
   K_COUNT  // at most 64: what a caller of daris_kernel_timing_read has to provide
 };
 static_assert(K_COUNT <= 64, "see daris_kernel_timing_read");
@@ -121,6 +122,23 @@ struct ExpandDwArgs {
 constexpr int kExpandPixels = 320;  // most input pixels of a workgroup
 constexpr int kExpandRow = 20;      // floats of a pixel's 16 channels in LDS, spread over the banks
 constexpr int kExpandChunks = 5;    // most chunks of 32 k
+
+// The 1x1 convolutions behind the 3x3 one, whose ConvArgs these follow in the arguments of conv_chain_kernel.
+struct ChainArgs {
+  const void* w3;      // the first: [n3][64], packed for 32-pixel tiles
+  const float* bias3;  // [n3]
+  const void* res3;    // [M][n3] or nullptr
+  void* y3;            // [M][n3]
+  const void* w1;      // the second, which reads y3: [n1][n3], as packed
+  const float* bias1;  // [n1]
+  void* y1;            // [M][n1]
+  int n3, act3;
+  int n1, act1;        // n1 = 0: there is no second
+  int slice1;          // 16 k each of a wave's share of the second
+  uint32_t mg_row;     // multiplier for division by the 16-byte vectors of a pixel of y3
+  int unused[2];       // to one of the sizes that grab() reads
+};
+constexpr int kChainWide = 256;  // most channels of the first
 
 struct DwArgs {
   const void* x;      // [H][W][C]
@@ -278,6 +296,7 @@ struct JoinedTable {
   const AqlKernel* image_pool[2] = {};  // kGatherImage and the 3 x 3 max pooling behind it
   const AqlKernel* expand_dw[2][kExpandChunks] = {};
   const AqlKernel* fc_pooled[2] = {};
+  const AqlKernel* chain[2] = {};
   const AqlKernel* tall[2][3] = {};     // [bf16][log2(nw) - 1]
   std::string resolve(const AqlRuntime& rt);  // as KernelTable::resolve
 };
@@ -314,6 +333,11 @@ bool encode_image_pool(const JoinedTable& kt, const ConvPlan& pl, const ConvArgs
 // itself whose sums have the same order, and returns whether the two should be joined.
 bool plan_expand_dw(ConvPlan* pl, int H, int W, int cin_stride, int c_stride, int Kpad, int dw_stride, int nominal_cus, int bf16);
 bool encode_expand_dw(const JoinedTable& kt, const ConvPlan& pl, const ConvArgs& a, const DwArgs& d, int nominal_cus, int bf16, std::vector<KernelLaunch>* out);
+// A 3x3 convolution planned as `conv`, the 1x1 convolution that alone reads it (`wide`) and, unless null, the 1x1 convolution that reads that one
+// (`narrow`), all with the same pixels, in one launch: whether the kernel has the plans' tiles and K slices, and the launch.
+bool chain_takes(const ConvPlan& conv, int channels, const ConvPlan& wide, int wide_channels, const ConvPlan* narrow, int bf16);
+bool encode_chain(const JoinedTable& kt, const ConvPlan& conv, const ConvArgs& a, const ConvPlan& wide, const ConvArgs& b, const ConvPlan* narrow, const ConvArgs* c, int bf16,
+                  std::vector<KernelLaunch>* out);
 bool encode_dwconv(const KernelTable& kt, const DwArgs& a, int bf16, std::vector<KernelLaunch>* out);
 bool encode_maxpool(const KernelTable& kt, const PoolArgs& a, int bf16, std::vector<KernelLaunch>* out);
 bool encode_gavgpool(const KernelTable& kt, const PoolArgs& a, int bf16, std::vector<KernelLaunch>* out);

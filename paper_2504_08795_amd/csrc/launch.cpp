@@ -25,7 +25,7 @@ static const char* const kNames[K_COUNT] = {
     "conv_wave64_taps_f32_t2w2", "conv_wave64_taps_f32_t2w4", "conv_wave64_taps_f32_t2w8",
     "conv_wave_image_f32_n1_t1w4", "conv_wave_image_f32_n2_t1w4", "conv_wave_image_bf16_n1_t1w4", "conv_wave_image_bf16_n2_t1w4",
     "conv_wave_image_pool_f32_n2_t1w10", "conv_wave_image_pool_bf16_n2_t1w10",
-    "conv_wave16_expand_dw_f32", "conv_wave16_expand_dw_bf16"};
+    "conv_wave16_expand_dw_f32", "conv_wave16_expand_dw_bf16", "conv_wave_chain_f32_t2w8", "conv_wave_chain_bf16_t2w4"};
 
 const char* kernel_name(int32_t id) { return (id >= 0 && id < K_COUNT) ? kNames[id] : "?"; }
 
@@ -292,7 +292,12 @@ static_assert(sizeof(ImageConvArgs) == 160 && offsetof(ImageConvArgs, x) == kCon
 constexpr uint32_t kIngestBytes = 28, kProbeBytes = 12, kPairBytes = 2 * sizeof(ConvArgs) + 4;
 static_assert(sizeof(DwFusedArgs) == 32 && sizeof(ConvDwArgs) == 192 && offsetof(ConvDwArgs, d) == sizeof(ConvArgs), "fused depthwise arguments");
 static_assert(sizeof(FcPooledArgs) == 64 && offsetof(FcPooledArgs, y) == kFcOutputOffset, "the logits are where every FC layer has them");
-static_assert(sizeof(ExpandDwArgs) == 160, "a size that grab() reads");
+static_assert(sizeof(ExpandDwArgs) == 160 && sizeof(ChainArgs) == 88, "sizes that grab() reads");
+struct ChainLaunchArgs {  // conv_chain_kernel(p, c)
+  ConvArgs p;
+  ChainArgs c;
+};
+static_assert(sizeof(ChainLaunchArgs) == 248 && offsetof(ChainLaunchArgs, c) == sizeof(ConvArgs), "chain arguments");
 static_assert(sizeof(ConvArgs) == 160 && sizeof(DwArgs) == 72 && sizeof(PoolArgs) == 48 && sizeof(FcArgs) == 56 && sizeof(ReduceArgs) == 48 && sizeof(DwWindowArgs) == 88 && sizeof(PoolWindowArgs) == 64,
               "argument structures must match what the kernels were compiled for");
 static_assert(offsetof(ConvArgs, x) == kConvInputOffset && offsetof(FcArgs, y) == kFcOutputOffset && offsetof(IngestArgs, x) == kIngestInputOffset &&
@@ -370,6 +375,7 @@ std::string JoinedTable::resolve(const AqlRuntime& rt) {
     image_pool[b] = get("daris::conv_image_pool_kernel<" + B + ">", sizeof(ImageConvArgs));
     for (int v = 0; v < 3; ++v)  // the variants that taps_kernel has with two blocks
       if (taps_kernel(16, b, 2, 2 << v) != K_NONE) tall[b][v] = get("daris::conv_taps16_tall_kernel<" + B + ", " + std::to_string(2 << v) + ">", sizeof(ConvArgs));
+    chain[b] = get("daris::conv_chain_kernel<" + B + ", " + (b ? "4" : "8") + ">", sizeof(ChainLaunchArgs));
     fc_pooled[b] = get("daris::fc_pooled_kernel<" + B + ">", sizeof(FcPooledArgs));
     for (int v = 0; v < kExpandChunks; ++v) expand_dw[b][v] = get("daris::conv_expand_dw_kernel<" + B + ", " + std::to_string(v + 1) + ">", sizeof(ExpandDwArgs));
   }
@@ -642,6 +648,34 @@ bool encode_expand_dw(const JoinedTable& kt, const ConvPlan& pl, const ConvArgs&
 }
 
 // Grid and place finding of a window kernel (point_of): workgroups in multiples of 8, one band of them per XCD.
+// The kernel has one wave tile of 64 channels over all K slices of a workgroup, four waves in bf16 and eight in fp32, and takes the first 1x1 in two halves of K,
+// as plans of few steps have it.
+bool chain_takes(const ConvPlan& conv, int channels, const ConvPlan& wide, int wide_channels, const ConvPlan* narrow, int bf16) {
+  const int nw = bf16 ? 4 : 8, unit = bf16 ? 1 : 2;  // steps of 16 k
+  if (conv.rows != 32 || conv.gather != kGatherTaps || conv.splitk != 1 || conv.tn != 2 || conv.nw != nw || conv.NTn != 1 || channels != 64) return false;
+  if (wide.rows != 32 || wide.gather != kGatherRows || wide.splitk != 1 || wide.S != 4 * unit || wide.nw != 2 || wide.sw != 2 * unit || wide_channels % 32 || wide_channels > kChainWide) return false;
+  if (!narrow) return true;
+  return narrow->rows == 32 && narrow->gather == kGatherRows && narrow->splitk == 1 && narrow->tn == 2 && narrow->NTn == 1 && narrow->nw == nw && narrow->S * 16 == wide_channels * unit && narrow->sw % unit == 0 &&
+         narrow->sw / unit <= kChainWide / 16 / nw;
+}
+
+bool encode_chain(const JoinedTable& kt, const ConvPlan& conv, const ConvArgs& a, const ConvPlan& wide, const ConvArgs& b, const ConvPlan* narrow, const ConvArgs* c, int bf16,
+                  std::vector<KernelLaunch>* out) {
+  if (!chain_takes(conv, a.Cout, wide, b.Cout, narrow, bf16) || !rows_take(a, bf16) || !rows_take(b, bf16) || !taps_agree(conv, a) || a.res || (a.act & kActSumPixels) || (b.act & kActSumPixels) || b.M != a.M ||
+      b.kh != 1 || b.kw != 1 || b.stride != 1 || b.pad != 0 || b.Cin != a.Cout)
+    return false;
+  ChainLaunchArgs l = {a, ChainArgs()};
+  l.p.y = nullptr;
+  l.c.w3 = b.w; l.c.bias3 = b.bias; l.c.res3 = b.res; l.c.y3 = b.y;
+  l.c.n3 = b.Cout; l.c.act3 = b.act; l.c.mg_row = div_magic((uint32_t)(b.Cout * (bf16 ? 2 : 4) / 16));
+  if (narrow) {
+    if (!rows_take(*c, bf16) || c->res || (c->act & kActSumPixels) || c->M != a.M || c->kh != 1 || c->kw != 1 || c->stride != 1 || c->pad != 0 || c->Cin != b.Cout || c->Cout > 64) return false;
+    l.c.w1 = c->w; l.c.bias1 = c->bias; l.c.y1 = c->y;
+    l.c.n1 = c->Cout; l.c.act1 = c->act; l.c.slice1 = narrow->sw / (bf16 ? 1 : 2);
+  }
+  return push(out, kt.chain[bf16], K_CHAIN_F32 + bf16, conv.grid_x, (uint32_t)conv.threads, &l, sizeof(l));
+}
+
 template <typename Args>
 static uint32_t point_grid(const Args& a, int bf16, PointPlace* at) {
   const uint32_t cvn = (uint32_t)(a.C / (bf16 ? 8 : 4));

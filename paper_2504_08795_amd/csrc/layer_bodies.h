@@ -265,10 +265,12 @@ struct WaveEpilogue {
     }
   }
 
-  // MODE as in conv_wave_body; acc = the wave's partial tile over K steps [sbeg, sbeg + nsteps)
-  template <int MODE>
+  // MODE as in conv_wave_body; acc = the wave's partial tile over K steps [sbeg, sbeg + nsteps); kNoWalk: there is no second walk.
+  // KEEP: the outputs go to `kept` in LDS, rows of kept_row bytes (zeros past the last pixel), instead of to memory.
+  static constexpr int kNoWalk = -1;
+  template <int MODE, bool KEEP = false>
   __device__ __forceinline__ void finish(const ConvArgs& p, const DwFusedArgs& dwf, WaveAcc<R> (&acc)[TM * TN], float* const red, const int m0, const int nb0, const int zi,
-                                         const int sbeg, const int nsteps) {
+                                         const int sbeg, const int nsteps, unsigned char* const kept = nullptr, const int kept_row = 0) {
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     auto park = [&]() {
 #pragma unroll
@@ -295,12 +297,12 @@ struct WaveEpilogue {
       }
     };
     park();
-    if constexpr (!BF16) {
+    if constexpr (!BF16 && MODE != kNoWalk) {
       spoil_unless_in_range(acc, red + wave * TILE, V * TM * TN);
     }
     __syncthreads();
     add_up();
-    if constexpr (!BF16) {
+    if constexpr (!BF16 && MODE != kNoWalk) {
       if (__builtin_expect(spoiled(sums[0].x), 0)) {  // every thread of the workgroup or none (out of the way: a launch fetches its code anew, and a longer path costs 0.2 us)
         __syncthreads();
         plain_products<MODE, R, TM, TN>(p, dwf, m0, nb0, sbeg, nsteps, acc);
@@ -309,7 +311,7 @@ struct WaveEpilogue {
         add_up();
       }
     }
-    if (!own_epilogue) {  // partial sums of this K slice; splitk_reduce_kernel finishes the layer
+    if (!KEEP && !own_epilogue) {  // partial sums of this K slice; splitk_reduce_kernel finishes the layer
 #pragma unroll
       for (int r = 0; r < RQ; ++r) {
         const int e = 4 * (tid + r * NT);
@@ -348,7 +350,7 @@ struct WaveEpilogue {
       }
     }
     apply_act(val, p.act & kActMask);
-    if (__builtin_expect(p.act & kActSumPixels, 0)) {  // the sums of the tile's outputs over its pixels, for the global average behind the layer
+    if (!KEEP && __builtin_expect(p.act & kActSumPixels, 0)) {  // the sums of the tile's outputs over its pixels, for the global average behind the layer
       __syncthreads();  // (every thread has read its partial sums)
 #pragma unroll
       for (int r = 0; r < RQ; ++r) {
@@ -389,6 +391,20 @@ struct WaveEpilogue {
       } else {
         out[r] = make_uint4(__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3]));
       }
+    }
+    if constexpr (KEEP) {
+      static_assert(BUFFER && QUADS % NT == 0, "every thread has quads, and their places");
+#pragma unroll
+      for (int r = 0; r < RQ; ++r) {
+        int j, mm, n;
+        place(4 * (tid + r * NT), m0, nb0, &j, &mm, &n);
+        const bool in = at[r] != kOutside;
+        ResVec v = out[r];
+        v.x = in ? v.x : 0u; v.y = in ? v.y : 0u;
+        if constexpr (!BF16) { v.z = in ? v.z : 0u; v.w = in ? v.w : 0u; }
+        *(ResVec*)(kept + (mm - m0) * kept_row + n * ES) = v;
+      }
+      return;
     }
     const auto yrsrc = __builtin_amdgcn_make_buffer_rsrc(LARGE ? from_tile(p, p.y, m0) : p.y, 0, BUFFER ? (LARGE ? min(R, p.M - m0) : p.M) * p.Cout * ES : 0, 0x00027000);
 #pragma unroll
@@ -1006,8 +1022,12 @@ template <bool BF16, int R, int TN, int NW, int TM = 1>
 constexpr int conv_taps_lds() {
   return NW * conv_taps_stage<BF16, TM>() > NW * TM * TN * R * R ? NW * conv_taps_stage<BF16, TM>() : NW * TM * TN * R * R;
 }
-template <bool BF16, int R, int TN, int NW, bool LARGE = false, int TM = 1>  // LARGE as in conv_rows_body
-__device__ __forceinline__ void conv_taps_body(const ConvArgs& p, const int mt, const int g, float* const red) {
+// ahead(): what else is to be on its way while the last group is multiplied; kept: as WaveEpilogue::finish with KEEP, or nullptr.
+struct Nothing {
+  __device__ __forceinline__ void operator()() const {}
+};
+template <bool BF16, int R, int TN, int NW, bool LARGE = false, int TM = 1, bool KEEP = false, typename Ahead = Nothing>  // LARGE as in conv_rows_body
+__device__ __forceinline__ void conv_taps_body(const ConvArgs& p, const int mt, const int g, float* const red, Ahead&& ahead = Ahead(), unsigned char* const kept = nullptr, const int kept_row = 0) {
   constexpr int ES = BF16 ? 2 : 4;
   constexpr int RK = 64 / ES;                    // k of a row
   constexpr int CK = R == 32 ? RK : 2 * RK;      // k of a chunk, which is two steps
@@ -1149,12 +1169,14 @@ __device__ __forceinline__ void conv_taps_body(const ConvArgs& p, const int mt, 
     }
     for (int groups = nsteps / 6; groups > 1; --groups) static_for<0, 3>([&](auto kx) { chunk(kx, std::true_type()); });
     if constexpr (LATE) fin.fetch(p, m0, nb0, tid);
+    ahead();
     static_for<0, 3>([&](auto kx) { chunk(kx, std::false_type()); });
-  } else if constexpr (LATE) {
-    fin.fetch(p, m0, nb0, tid);
+  } else {
+    if constexpr (LATE) fin.fetch(p, m0, nb0, tid);
+    ahead();
   }
   __syncthreads();  // the partial tiles reuse the LDS of every wave's staging buffer
-  fin.template finish<5>(p, DwFusedArgs(), acc, red, m0, nb0, zi, sbeg, nsteps);
+  fin.template finish<5, KEEP>(p, DwFusedArgs(), acc, red, m0, nb0, zi, sbeg, nsteps, kept, kept_row);
 }
 
 template <int R, int TN, int NW>
@@ -1493,6 +1515,177 @@ __device__ __forceinline__ void conv_expand_dw_body(const ExpandDwArgs& p, const
     if constexpr (BF16) put(to, make_uint2(pack_bf16_rne(v[0], v[1]), pack_bf16_rne(v[2], v[3])));
     else put(to, make_float4(v[0], v[1], v[2], v[3]));
   }
+}
+
+// ---- the 3x3 convolution of a bottleneck, the 1x1 behind it and the next block's 1x1 -----------------------------------------
+//
+// Both 1x1 convolutions need nothing but the pixels of the tile, so the workgroup that owns a tile of the 3x3 convolution (32 pixels, all of its 64
+// channels: conv_taps_body) leaves it in LDS and goes on: the first 1x1 (up to kChainWide channels) takes its residual, is stored and stays in LDS, and
+// the second (up to 64 channels) reads it there.  Bound by the launch and its chain of waits like the launches that it takes the place of; the weights and
+// the residual of each are requested before the one in front is finished, so that nothing of them is waited for.  ResNet-50's first group, five launches fewer:
+// frame in bf16 on 128 CUs 202.2 -> 198.2 us, six tasks saturated 7243 -> 7089, the mixed set (fp32) 10410 -> 10117.
+// The sums have the order that launches of their own have: of the first 1x1 two halves of K, each in an accumulator, of the second as many slices as
+// waves.  The first has weights and pixels in each other's place in the matrix instruction: a lane then holds four channels in a row of its pixel.
+template <bool BF16, int NW>
+constexpr int conv_chain_lds() {  // floats of LDS
+  return conv_taps_lds<BF16, 32, 2, NW>() + 32 * (64 * (BF16 ? 2 : 4) + 16) / 4 + kChainWide;
+}
+template <bool BF16, int NW>
+__device__ __forceinline__ void conv_chain_body(const ConvArgs& p, const ChainArgs& c, const int mt, float* const lds) {
+  constexpr int ES = BF16 ? 2 : 4, NT = NW * 64, NP = BF16 ? 1 : 3;
+  constexpr int UNITS = 4, HALF = UNITS / 2;            // 16 k each of the first 1x1
+  constexpr int NB = kChainWide / 32 / NW;              // its channel blocks of a wave
+  constexpr int U1 = kChainWide / 16 / NW;              // 16 k each of a wave's slice of the second
+  constexpr int ROW = 64 * ES + 16, WIDE = kChainWide * ES + 16;  // bytes of a pixel in LDS, spread over the banks
+  constexpr int NV = 32 * kChainWide * ES / 16 / NT;    // 16-byte vectors of the wide tile to a thread
+  static_assert(32 * WIDE <= conv_taps_lds<BF16, 32, 2, NW>() * 4, "the wide tile lies where the partial tiles were");
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int li = lane & 31, lh = lane >> 5, m0 = mt * 32;
+  unsigned char* const kept = (unsigned char*)(lds + conv_taps_lds<BF16, 32, 2, NW>());  // [32][ROW]
+  unsigned char* const wide = (unsigned char*)lds;                                       // [32][WIDE]
+  float* const biases = lds + conv_taps_lds<BF16, 32, 2, NW>() + 32 * ROW / 4;
+
+  const int row_vecs = c.n3 * ES / 16, vecs = 32 * row_vecs, blocks = c.n3 >> 5;
+  const int s1 = c.n3 >> 4, u0 = min(wave * c.slice1, s1), units1 = min(u0 + c.slice1, s1) - u0;  // 16 k each
+  uint4 w3[NB][UNITS][NP], w1[U1][2][NP], res[NV];
+  float4 bias3;
+  const int at0 = m0 * c.n3 * ES;  // a tile's rows lie one behind the other
+  WaveEpilogue<BF16, 32, 2, NW, true> fin;
+  ConvArgs q = ConvArgs();  // the second 1x1 as the epilogue wants it
+  q.bias = c.bias1; q.y = c.y1; q.Cout = c.n1; q.M = p.M; q.act = c.act1; q.splitk = 1;
+  auto ahead = [&]() {
+    const auto w3rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(c.w3), 0, blocks * UNITS * NP * 1024, 0x00027000);
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+      for (int u = 0; u < UNITS * NP; ++u) w3[b][u / NP][u % NP] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(w3rsrc, lane * 16 + (wave + b * NW) * (UNITS * NP * 1024) + u * 1024, 0, 0));
+    const auto rrsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(c.res3), 0, c.res3 ? p.M * c.n3 * ES : 0, 0x00027000);  // (past the end, and without a residual: zeros)
+#pragma unroll
+    for (int r = 0; r < NV; ++r) res[r] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rrsrc, at0 + (tid + r * NT) * 16, 0, 0));
+    bias3 = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (4 * tid < c.n3) bias3 = *(const float4*)(c.bias3 + 4 * tid);
+  };
+  conv_taps_body<BF16, 32, 2, NW, false, 1, true>(p, mt, 0, lds, ahead, kept, ROW);
+  if (c.n1) {
+    const auto w1rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(c.w1), 0, 2 * s1 * NP * 1024, 0x00027000);
+#pragma unroll
+    for (int u = 0; u < U1; ++u)
+#pragma unroll
+      for (int k = 0; k < 2 * NP; ++k) w1[u][k / NP][k % NP] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(w1rsrc, lane * 16 + ((k / NP * s1 + u0 + u) * NP + k % NP) * 1024, 0, 0));
+    fin.fetch(q, m0, 0, tid);
+  }
+  if (4 * tid < kChainWide) *(float4*)&biases[4 * tid] = bias3;
+  __syncthreads();
+
+  auto pixels_of = [&](const unsigned char* const row, const int u) {  // the lane's pixel, k = 16 u + 8 lh .. + 7
+    Split8 s;
+    if constexpr (BF16) s.p[0] = *(const uint4*)(row + (16 * u + 8 * lh) * ES);
+    else s = split8(*(const uint4*)(row + (16 * u + 8 * lh) * ES), *(const uint4*)(row + (16 * u + 8 * lh) * ES + 16));
+    return s;
+  };
+  constexpr int PA[6] = {BF16 ? 0 : 2, 1, 0, 1, 0, 0}, PB[6] = {0, 1, 2, 0, 1, 0};  // (as wave_mma)
+#pragma unroll
+  for (int r = 0; r < NV; ++r) {
+    const int v = tid + r * NT, px = fast_div(v, c.mg_row);
+    if (v < vecs) *(uint4*)(wide + px * WIDE + (v - px * row_vecs) * 16) = res[r];
+  }
+  f32x16 sum[NB];
+  {
+    f32x16 acc[NB][2];
+#pragma unroll
+    for (int b = 0; b < NB; ++b) acc[b][0] = acc[b][1] = f32x16(0.f);
+#pragma unroll
+    for (int u = 0; u < UNITS; ++u) {
+      const Split8 a = pixels_of(kept + li * ROW, u);
+#pragma unroll
+      for (int k = 0; k < (BF16 ? 1 : 6); ++k)
+#pragma unroll
+        for (int b = 0; b < NB; ++b) acc[b][u / HALF] = mfma_bf16(w3[b][u][PB[k]], a.p[PA[k]], acc[b][u / HALF]);
+    }
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+      if constexpr (!BF16) {
+        if (__builtin_expect(out_of_range(acc[b]), 0)) {  // the wave's block once more, on the fp32 matrix instructions
+#pragma unroll
+          for (int h = 0; h < 2; ++h) acc[b][h] = f32x16(0.f);
+#pragma unroll
+          for (int u = 0; u < UNITS; ++u) {
+            float w[3][8];
+#pragma unroll
+            for (int k = 0; k < 3; ++k) unpack<true>(w3[b][u][k], w[k]);
+            const float* const x = (const float*)(kept + li * ROW) + 16 * u + 8 * lh;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) acc[b][u / HALF] = __builtin_amdgcn_mfma_f32_32x32x2f32((w[2][e] + w[1][e]) + w[0][e], x[e], acc[b][u / HALF], 0, 0, 0);
+          }
+        }
+      }
+      sum[b] = acc[b][0] + acc[b][1];
+    }
+  }
+  __syncthreads();  // the residual lies in `wide`: a lane adds its sums and leaves the outputs in its place
+  const bool inside = m0 + li < p.M;
+#pragma unroll
+  for (int b = 0; b < NB; ++b) {
+    const int n0 = (wave + b * NW) * 32 + 4 * lh;
+    if (wave + b * NW >= blocks) break;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int n = n0 + 8 * k;
+      unsigned char* const at = wide + li * WIDE + n * ES;
+      const float4 bi = *(const float4*)&biases[n];
+      float v[4] = {sum[b][4 * k] + bi.x, sum[b][4 * k + 1] + bi.y, sum[b][4 * k + 2] + bi.z, sum[b][4 * k + 3] + bi.w};
+      if constexpr (BF16) {
+        if (c.res3) {
+          const uint2 r = *(const uint2*)at;
+          v[0] += __uint_as_float(r.x << 16); v[1] += __uint_as_float(r.x & 0xffff0000u); v[2] += __uint_as_float(r.y << 16); v[3] += __uint_as_float(r.y & 0xffff0000u);
+        }
+        apply_act(v, c.act3);
+        *(uint2*)at = make_uint2(inside ? pack_bf16_rne(v[0], v[1]) : 0u, inside ? pack_bf16_rne(v[2], v[3]) : 0u);
+      } else {
+        if (c.res3) {
+          const float4 r = *(const float4*)at;
+          v[0] += r.x; v[1] += r.y; v[2] += r.z; v[3] += r.w;
+        }
+        apply_act(v, c.act3);
+        *(float4*)at = make_float4(inside ? v[0] : 0.f, inside ? v[1] : 0.f, inside ? v[2] : 0.f, inside ? v[3] : 0.f);
+      }
+    }
+  }
+  __syncthreads();
+
+  const auto yrsrc = __builtin_amdgcn_make_buffer_rsrc(c.y3, 0, p.M * c.n3 * ES, 0x00027000);
+  auto store_wide = [&]() {
+#pragma unroll
+    for (int r = 0; r < NV; ++r) {
+      const int v = tid + r * NT, px = fast_div(v, c.mg_row);
+      if (v < vecs) put_at(yrsrc, at0 + v * 16, *(const uint4*)(wide + px * WIDE + (v - px * row_vecs) * 16));
+    }
+  };
+  if (c.n1 == 0) {
+    store_wide();
+    return;
+  }
+  f32x16 acc[2] = {f32x16(0.f), f32x16(0.f)};
+#pragma unroll
+  for (int u = 0; u < U1; ++u) {
+    if (u >= units1) break;
+    const Split8 a = pixels_of(wide + li * WIDE, u0 + u);
+#pragma unroll
+    for (int k = 0; k < (BF16 ? 1 : 6); ++k)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) acc[j] = mfma_bf16(a.p[PA[k]], w1[u][j][PB[k]], acc[j]);
+  }
+  store_wide();
+  if constexpr (!BF16) {
+    if (__builtin_expect(out_of_range(acc), 0)) {  // (the epilogue's second walk would find `wide` gone)
+      ConvArgs x = ConvArgs();  // one row of 32 pixels in LDS
+      x.x = wide; x.w = c.w1; x.H = 1; x.W = x.M = 32; x.Cin = WIDE / 4; x.kh = x.kw = x.stride = 1; x.S = 2 * s1;
+      x.mg_wo = x.mg_cin = 1;  // (every pixel and every k is below Wo and Cin)
+      plain_products<3, 32, 1, 2>(x, DwFusedArgs(), 0, 0, 2 * u0, 2 * units1, acc);
+    }
+  }
+  __syncthreads();  // the partial tiles come where `wide` was
+  fin.template finish<fin.kNoWalk>(q, DwFusedArgs(), acc, lds, m0, 0, 0, 0, 0);
 }
 
 // ---- pointwise layers: one thread per (output pixel, 16-byte channel vector) ----------------------------------------------

@@ -250,6 +250,22 @@ std::string build_plan(const daris_dnn& dnn, bool keep_activations, bool pair_la
     B.average_of = l;
     B.kernel_id = A.kernel_id;
   }
+  // a 3x3 convolution, the 1x1 that alone reads it, and the 1x1 behind that
+  for (int l = 0; l + 1 < n && !keep_activations && pair_launches && staged_rows; ++l) {
+    LayerPlan& A = net.layers[l];
+    LayerPlan& B = net.layers[l + 1];
+    auto plain = [&](const LayerPlan& L) { return L.d.op == DARIS_OP_CONV && !L.depthwise && L.pair_with < 0 && L.joins < 0 && L.can_join < 0 && !L.sums_pixels && rows_taken(L); };
+    auto point = [&](const LayerPlan& L) { return plain(L) && L.d.k == 1 && L.d.stride == 1 && L.d.pad == 0; };
+    if (!plain(A) || A.res_t >= 0 || (l == 0 && net.fuse_ingest) || !point(B) || B.in_t != l + 1 || B.res_t == l + 1 || !chain_takes(A.cp, A.out.Cs, B.cp, B.out.Cs, nullptr, net.bf16)) continue;
+    bool only_reader = true;
+    for (int q = l + 2; q < n; ++q)
+      if (net.layers[q].in_t == l + 1 || net.layers[q].res_t == l + 1) only_reader = false;
+    if (!only_reader) continue;
+    B.can_join = l;
+    if (l + 2 >= n) break;
+    LayerPlan& C = net.layers[l + 2];
+    if (point(C) && C.in_t == l + 2 && C.res_t < 0 && C.out.Cs <= 64 && chain_takes(A.cp, A.out.Cs, B.cp, B.out.Cs, &C.cp, net.bf16)) C.can_follow = l + 1;
+  }
   const TensorInfo& fin = net.layers[n - 1].out;
   net.n_out = fin.C * fin.H * fin.W;
   net.final_direct = net.layers[n - 1].d.op == DARIS_OP_FC;
@@ -274,7 +290,8 @@ std::string build_plan(const daris_dnn& dnn, bool keep_activations, bool pair_la
   std::vector<int> last_use(n + 1, -1);
   for (int l = 0; l < n; ++l) {
     const LayerPlan& L = net.layers[l];
-    const int at = net.joined_away(l) ? l + 1 : std::max(l, L.pair_with);
+    int at = net.joined_away(l) ? l + 1 : std::max(l, L.pair_with);
+    if (net.followed(at)) ++at;
     last_use[l + 1] = std::max(last_use[l + 1], at);
     last_use[L.in_t] = std::max(last_use[L.in_t], at);
     if (L.res_t >= 0) last_use[L.res_t] = std::max(last_use[L.res_t], at);
@@ -324,8 +341,13 @@ bool join_layers(NetPlan* net) {
       const bool pool = B.d.op == DARIS_OP_MAXPOOL;
       B.joins = cut ? -1 : l;
       if (pool) A.pair_with = cut ? -1 : l + 1;
-      if (cut) B.kernel_id = pool ? K_MAXPOOL : K_DWCONV;
-      else B.kernel_id = (pool ? K_IMAGE_POOL_F32 : K_EXPAND_DW_F32) + net->bf16;
+      if (pool) B.kernel_id = cut ? (int32_t)K_MAXPOOL : K_IMAGE_POOL_F32 + net->bf16;
+      else if (B.depthwise) B.kernel_id = cut ? (int32_t)K_DWCONV : K_EXPAND_DW_F32 + net->bf16;  // (a dense convolution keeps the name of the plan whose sums it has)
+      changed = true;
+    }
+    const bool follows = B.can_follow == l && A.joins >= 0 && !cut;
+    if (follows != (B.follows >= 0)) {
+      B.follows = follows ? l : -1;
       changed = true;
     }
   }

@@ -38,6 +38,9 @@ struct LayerPlan {
   // joins = the first layer, at the second, and how; can_join: the plan allows it; switched off while a stage cut separates the two.  (A
   // convolution that a pooling layer joins has that layer as pair_with, like the earlier member of a launch pair.)
   int joins = -1, can_join = -1;
+  // The 1x1 convolution behind such a pair (a 3x3 convolution that joins a 1x1), which nobody else needs to wait for: follows = that pair's second layer,
+  // whose launch is then issued here and stores both outputs.  can_follow as can_join.
+  int follows = -1, can_follow = -1;
   // A global average pooling that issues nothing: average_of = the convolution in front, which leaves sums over the pixels of its tiles in place of its
   // output (sums_pixels; pair_with = the FC layer behind, which takes the sums).  lonely: alone in its stage, where it makes the averages from the sums.
   int average_of = -1;
@@ -64,6 +67,8 @@ struct NetPlan {
   const TensorInfo& tensor(int t) const { return t == 0 ? ingest : layers[t - 1].out; }
   // Whether layer l is computed in the launch of the next one, and its output never stored.
   bool joined_away(int l) const { return l + 1 < (int)layers.size() && layers[l + 1].joins == l; }
+  // Whether layer l's launch is the next one's.
+  bool followed(int l) const { return l + 1 < (int)layers.size() && layers[l + 1].follows == l; }
 };
 
 // Builds shapes, MACs, legal cuts, buffer slots and kernel plans.  pair_launches: two independent convolutions on one

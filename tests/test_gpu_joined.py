@@ -86,6 +86,39 @@ def test_expansion_of_small_numbers_keeps_its_precision():
     np.testing.assert_allclose(small * np.float64(2.0 ** 122), one, rtol=0, atol=2e-6 * np.abs(one).max())
 
 
+# h, w, channels of the first 1x1, of the second (0: none), input of the first as residual, plan CUs: whole and ragged last tiles, one of a single pixel, images narrower than
+# a tile, fewer channels than a workgroup's waves have blocks, a second 1x1 that stays by itself
+CHAINS = [(56, 56, 256, 64, True, 128), (56, 56, 256, 0, True, 128), (48, 65, 256, 64, False, 128), (13, 17, 256, 40, True, 8), (193, 1, 256, 64, False, 8), (3, 75, 160, 0, True, 8),
+          (15, 15, 96, 64, True, 8)]
+
+
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("shape", CHAINS)
+def test_bottleneck_in_one_launch(shape, dtype):
+    """A convolution in front makes the residual's channels.  NO_PAIR parts all of it, a stage cut the 3x3 from the first 1x1 or that from the second: bit for bit the same."""
+    h, w, n3, n1, res, cus = shape
+    layers = [N.Layer(op=N.OP_CONV, c_in=32, c_out=n3, k=1, act=1, in_from=-1, has_bn=False), N.Layer(op=N.OP_CONV, c_in=n3, c_out=64, k=1, act=1, in_from=0, has_bn=False),
+              N.Layer(op=N.OP_CONV, c_in=64, c_out=64, k=3, pad=1, act=1, in_from=1, has_bn=False),
+              N.Layer(op=N.OP_CONV, c_in=64, c_out=n3, k=1, act=1, in_from=2, res_from=0 if res else -1, has_bn=False)]
+    if n1:
+        layers.append(N.Layer(op=N.OP_CONV, c_in=n3, c_out=n1, k=1, act=2, in_from=3, has_bn=False))
+    weights = wl.make_weights(layers, 3)
+    x = wl.make_inputs((32, h, w), 3, 1, "normal")[0]
+    bad = x.copy()
+    bad[0, h // 2, w // 3], bad[31, 0, w - 1] = np.nan, np.inf
+    outs = []
+    for flags, k in ((0, 1), (0, 2), (D.NO_PAIR, 1)):
+        with GpuNet(layers, weights, (32, h, w), dtype, flags=flags, k=k, plan_cus=cus) as g:
+            assert (D.daris_get_launch_plan(g.task, 2)["out_slot"] == -1) == (flags == 0 and 3 not in D.daris_get_stage_cuts(g.task))
+            outs.append([g.forward(x), g.forward(bad)])
+    for other in outs[1:]:
+        np.testing.assert_array_equal(outs[0][0], other[0])
+        # (which tiles are walked again in plain fp32 depends on the tiles)
+        np.testing.assert_allclose(outs[0][1], other[1], rtol=1e-4, atol=1e-3 if dtype == "fp32" else 0)
+    e_max, e_l2 = rel_err(outs[0][0], oracle_logits(layers, weights, x, dtype))
+    assert e_max <= TOL[dtype] and e_l2 <= TOL[dtype], (e_max, e_l2)
+
+
 # c_in, h, w, c_out of the convolution, its window, FC outputs, plan CUs; one to four tiles of 16 or 32 pixels, the last one full or of one pixel; more channels than a lane has
 # loads in flight for, and not a multiple of a wave's
 AVERAGES = [(64, 7, 7, 512, 3, 1000, 128), (320, 7, 7, 1280, 1, 37, 128), (64, 7, 7, 2048, 1, 10, 128), (32, 1, 1, 64, 1, 5, 128), (32, 4, 8, 96, 1, 16, 8), (64, 3, 11, 4000, 1, 9, 256),

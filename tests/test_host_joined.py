@@ -13,7 +13,7 @@ HOST = D.VIRTUAL_TIME | D.NO_DEVICE
 N = wl.nets
 
 # code object: {kernel: (bytes of its argument block, how many instances)}
-JOINED_KERNELS = {"daris_joined_kernels": {"conv_image_pool_kernel": (160, 2), "conv_expand_dw_kernel": (160, 10), "fc_pooled_kernel": (64, 2)},
+JOINED_KERNELS = {"daris_joined_kernels": {"conv_image_pool_kernel": (160, 2), "conv_expand_dw_kernel": (160, 10), "fc_pooled_kernel": (64, 2), "conv_chain_kernel": (248, 2)},
                   "daris_tall_kernels": {"conv_taps16_tall_kernel": (160, 3)}}
 
 
@@ -24,7 +24,7 @@ def test_joined_kernels_match_the_argument_structures(co):
         base = [k for k in want if re.search(r"\d+" + k + r"(I|E)", name)]
         assert len(base) == 1, name
         assert has["kernarg_segment_size"] == want[base[0]][0], name
-        assert has["private_segment_fixed_size"] == 0 and has["group_segment_fixed_size"] <= 65536, (name, has)
+        assert has["private_segment_fixed_size"] == 0 and has["group_segment_fixed_size"] <= (81920 if "chain" in name else 65536), (name, has)
         seen[base[0]] = seen.get(base[0], 0) + 1
     assert seen == {k: n for k, (_, n) in want.items()}
     assert set(build.JOINED_SOURCES.values()) == set(JOINED_KERNELS)
@@ -66,3 +66,25 @@ def test_global_average_without_a_launch(net):
         assert len({p[n - 3]["in_slot"], p[n - 3]["out_slot"], p[n - 2]["out_slot"]} - {-1}) == 3   # the sums live until the FC layer has read them
         legal = 1 + sum(1 for l in range(n - 1) if all(q.in_from >= l and not 0 <= q.res_from < l for q in layers[l + 1:]))
         assert D.daris_kernel_name(_plans(layers, shp, dtype, k=legal)[n - 2]["kernel_id"]) == "gavgpool"    # alone in its stage
+
+
+def test_bottlenecks_of_64_channels_share_a_launch():
+    for dtype, cus in (("bf16", 128), ("fp32", 128)):
+        layers, shp = wl.build_net("resnet50")
+        p = _plans(layers, shp, dtype, cus=cus)
+        first = [l for l in range(len(layers)) if p[l]["out_slot"] == -1 and l > 0 and l + 1 < len(layers)]
+        assert len(first) == 3 and all(layers[l].k == 3 for l in first) and first[1] - first[0] == first[2] - first[1] == 3, first
+        for l in first:
+            assert p[l + 1]["in_slot"] == -1
+            live = [p[l]["in_slot"], p[l + 1]["out_slot"], p[l + 1]["res_slot"]] + ([p[l + 2]["out_slot"]] if l != first[2] else [])  # (the last one's successor shares its launch with a shortcut)
+            assert -1 not in live and len(set(live)) == len(live), live                            # what the launch reads and writes lies in places of its own
+    chain = [N.Layer(op=N.OP_CONV, c_in=64, c_out=64, k=3, pad=1, in_from=-1), N.Layer(op=N.OP_CONV, c_in=64, c_out=256, k=1, in_from=0), N.Layer(op=N.OP_CONV, c_in=256, c_out=64, k=1, in_from=1)]
+    for k, joined in ((1, True), (2, True), (3, False)):                                           # two stages: the cut that balances them lies behind the first layer or the second
+        p = _plans(chain, (64, 56, 56), "bf16", k=k)
+        with Session(HOST):
+            D.daris_create_partition(64)
+            dnn, keep = D.make_dnn(chain, None, (64, 56, 56), "bf16")
+            t = D.daris_register_task(dnn, 10**7, 10**7, D.LP)
+            D.daris_split_stages(t, k)
+            cuts = D.daris_get_stage_cuts(t)
+        assert (p[0]["out_slot"] == -1) == (1 not in cuts) and (joined or 1 in cuts), (p, cuts)
