@@ -125,20 +125,18 @@ constexpr int kExpandChunks = 5;    // most chunks of 32 k
 
 // The 1x1 convolutions behind the 3x3 one, whose ConvArgs these follow in the arguments of conv_chain_kernel.
 struct ChainArgs {
-  const void* w3;      // the first: [n3][64], packed for 32-pixel tiles
-  const float* bias3;  // [n3]
-  const void* res3;    // [M][n3] or nullptr
-  void* y3;            // [M][n3]
-  const void* w1;      // the second, which reads y3: [n1][n3], as packed
+  const void* w3;      // the first: [kChainWide][64], packed for 32-pixel tiles
+  const float* bias3;  // [kChainWide]
+  const void* res3;    // [M][kChainWide] or nullptr
+  void* y3;            // [M][kChainWide]
+  const void* w1;      // the second, which reads y3: [n1][kChainWide], as packed
   const float* bias1;  // [n1]
   void* y1;            // [M][n1]
-  int n3, act3;
+  int act3;
   int n1, act1;        // n1 = 0: there is no second
-  int slice1;          // 16 k each of a wave's share of the second
-  uint32_t mg_row;     // multiplier for division by the 16-byte vectors of a pixel of y3
-  int unused[2];       // to one of the sizes that grab() reads
+  int unused[5];       // to one of the sizes that grab() reads
 };
-constexpr int kChainWide = 256;  // most channels of the first
+constexpr int kChainWide = 256;  // channels of the first
 
 struct DwArgs {
   const void* x;      // [H][W][C]

@@ -653,10 +653,9 @@ bool encode_expand_dw(const JoinedTable& kt, const ConvPlan& pl, const ConvArgs&
 bool chain_takes(const ConvPlan& conv, int channels, const ConvPlan& wide, int wide_channels, const ConvPlan* narrow, int bf16) {
   const int nw = bf16 ? 4 : 8, unit = bf16 ? 1 : 2;  // steps of 16 k
   if (conv.rows != 32 || conv.gather != kGatherTaps || conv.splitk != 1 || conv.tn != 2 || conv.nw != nw || conv.NTn != 1 || channels != 64) return false;
-  if (wide.rows != 32 || wide.gather != kGatherRows || wide.splitk != 1 || wide.S != 4 * unit || wide.nw != 2 || wide.sw != 2 * unit || wide_channels % 32 || wide_channels > kChainWide) return false;
+  if (wide.rows != 32 || wide.gather != kGatherRows || wide.splitk != 1 || wide.S != 4 * unit || wide.nw != 2 || wide.sw != 2 * unit || wide_channels != kChainWide) return false;
   if (!narrow) return true;
-  return narrow->rows == 32 && narrow->gather == kGatherRows && narrow->splitk == 1 && narrow->tn == 2 && narrow->NTn == 1 && narrow->nw == nw && narrow->S * 16 == wide_channels * unit && narrow->sw % unit == 0 &&
-         narrow->sw / unit <= kChainWide / 16 / nw;
+  return narrow->rows == 32 && narrow->gather == kGatherRows && narrow->splitk == 1 && narrow->tn == 2 && narrow->NTn == 1 && narrow->nw == nw && narrow->S == kChainWide / 16 * unit && narrow->sw * nw == narrow->S;
 }
 
 bool encode_chain(const JoinedTable& kt, const ConvPlan& conv, const ConvArgs& a, const ConvPlan& wide, const ConvArgs& b, const ConvPlan* narrow, const ConvArgs* c, int bf16,
@@ -667,11 +666,11 @@ bool encode_chain(const JoinedTable& kt, const ConvPlan& conv, const ConvArgs& a
   ChainLaunchArgs l = {a, ChainArgs()};
   l.p.y = nullptr;
   l.c.w3 = b.w; l.c.bias3 = b.bias; l.c.res3 = b.res; l.c.y3 = b.y;
-  l.c.n3 = b.Cout; l.c.act3 = b.act; l.c.mg_row = div_magic((uint32_t)(b.Cout * (bf16 ? 2 : 4) / 16));
+  l.c.act3 = b.act;
   if (narrow) {
     if (!rows_take(*c, bf16) || c->res || (c->act & kActSumPixels) || c->M != a.M || c->kh != 1 || c->kw != 1 || c->stride != 1 || c->pad != 0 || c->Cin != b.Cout || c->Cout > 64) return false;
     l.c.w1 = c->w; l.c.bias1 = c->bias; l.c.y1 = c->y;
-    l.c.n1 = c->Cout; l.c.act1 = c->act; l.c.slice1 = narrow->sw / (bf16 ? 1 : 2);
+    l.c.n1 = c->Cout; l.c.act1 = c->act;
   }
   return push(out, kt.chain[bf16], K_CHAIN_F32 + bf16, conv.grid_x, (uint32_t)conv.threads, &l, sizeof(l));
 }

@@ -1022,7 +1022,7 @@ template <bool BF16, int R, int TN, int NW, int TM = 1>
 constexpr int conv_taps_lds() {
   return NW * conv_taps_stage<BF16, TM>() > NW * TM * TN * R * R ? NW * conv_taps_stage<BF16, TM>() : NW * TM * TN * R * R;
 }
-// ahead(): what else is to be on its way while the last group is multiplied; kept: as WaveEpilogue::finish with KEEP, or nullptr.
+// KEEP as in WaveEpilogue::finish; ahead(): what else is to be on its way while the last group is multiplied.
 struct Nothing {
   __device__ __forceinline__ void operator()() const {}
 };
@@ -1169,11 +1169,13 @@ __device__ __forceinline__ void conv_taps_body(const ConvArgs& p, const int mt, 
     }
     for (int groups = nsteps / 6; groups > 1; --groups) static_for<0, 3>([&](auto kx) { chunk(kx, std::true_type()); });
     if constexpr (LATE) fin.fetch(p, m0, nb0, tid);
+    if constexpr (!KEEP) static_for<0, 3>([&](auto kx) { chunk(kx, std::false_type()); });
+  } else if constexpr (LATE) {
+    fin.fetch(p, m0, nb0, tid);
+  }
+  if constexpr (KEEP) {  // (in both branches above, its loads would count as on their way in the other one as well, and every wait would be for all)
     ahead();
-    static_for<0, 3>([&](auto kx) { chunk(kx, std::false_type()); });
-  } else {
-    if constexpr (LATE) fin.fetch(p, m0, nb0, tid);
-    ahead();
+    if (nsteps > 0) static_for<0, 3>([&](auto kx) { chunk(kx, std::false_type()); });
   }
   __syncthreads();  // the partial tiles reuse the LDS of every wave's staging buffer
   fin.template finish<5, KEEP>(p, DwFusedArgs(), acc, red, m0, nb0, zi, sbeg, nsteps, kept, kept_row);
@@ -1520,7 +1522,7 @@ __device__ __forceinline__ void conv_expand_dw_body(const ExpandDwArgs& p, const
 // ---- the 3x3 convolution of a bottleneck, the 1x1 behind it and the next block's 1x1 -----------------------------------------
 //
 // Both 1x1 convolutions need nothing but the pixels of the tile, so the workgroup that owns a tile of the 3x3 convolution (32 pixels, all of its 64
-// channels: conv_taps_body) leaves it in LDS and goes on: the first 1x1 (up to kChainWide channels) takes its residual, is stored and stays in LDS, and
+// channels: conv_taps_body) leaves it in LDS and goes on: the first 1x1 (kChainWide channels) takes its residual, is stored and stays in LDS, and
 // the second (up to 64 channels) reads it there.  Bound by the launch and its chain of waits like the launches that it takes the place of; the weights and
 // the residual of each are requested before the one in front is finished, so that nothing of them is waited for.  ResNet-50's first group, five launches fewer:
 // frame in bf16 on 128 CUs 202.2 -> 198.2 us, six tasks saturated 7243 -> 7089, the mixed set (fp32) 10410 -> 10117.
@@ -1535,46 +1537,47 @@ __device__ __forceinline__ void conv_chain_body(const ConvArgs& p, const ChainAr
   constexpr int ES = BF16 ? 2 : 4, NT = NW * 64, NP = BF16 ? 1 : 3;
   constexpr int UNITS = 4, HALF = UNITS / 2;            // 16 k each of the first 1x1
   constexpr int NB = kChainWide / 32 / NW;              // its channel blocks of a wave
-  constexpr int U1 = kChainWide / 16 / NW;              // 16 k each of a wave's slice of the second
+  constexpr int S1 = kChainWide / 16, U1 = S1 / NW;     // 16 k each of the second, of a wave's slice of it
   constexpr int ROW = 64 * ES + 16, WIDE = kChainWide * ES + 16;  // bytes of a pixel in LDS, spread over the banks
-  constexpr int NV = 32 * kChainWide * ES / 16 / NT;    // 16-byte vectors of the wide tile to a thread
+  constexpr int ROW_VECS = kChainWide * ES / 16;        // 16-byte vectors of a pixel of the wide tile
+  constexpr int NV = 32 * ROW_VECS / NT;                // ... of the tile to a thread
   static_assert(32 * WIDE <= conv_taps_lds<BF16, 32, 2, NW>() * 4, "the wide tile lies where the partial tiles were");
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int li = lane & 31, lh = lane >> 5, m0 = mt * 32;
+  using ResVec = typename std::conditional<BF16, uint2, uint4>::type;
   unsigned char* const kept = (unsigned char*)(lds + conv_taps_lds<BF16, 32, 2, NW>());  // [32][ROW]
   unsigned char* const wide = (unsigned char*)lds;                                       // [32][WIDE]
   float* const biases = lds + conv_taps_lds<BF16, 32, 2, NW>() + 32 * ROW / 4;
 
-  const int row_vecs = c.n3 * ES / 16, vecs = 32 * row_vecs, blocks = c.n3 >> 5;
-  const int s1 = c.n3 >> 4, u0 = min(wave * c.slice1, s1), units1 = min(u0 + c.slice1, s1) - u0;  // 16 k each
+  const int u0 = wave * U1;
   uint4 w3[NB][UNITS][NP], w1[U1][2][NP], res[NV];
   float4 bias3;
-  const int at0 = m0 * c.n3 * ES;  // a tile's rows lie one behind the other
+  const int at0 = mt * (32 * kChainWide * ES);  // a tile's rows lie one behind the other
   WaveEpilogue<BF16, 32, 2, NW, true> fin;
   ConvArgs q = ConvArgs();  // the second 1x1 as the epilogue wants it
   q.bias = c.bias1; q.y = c.y1; q.Cout = c.n1; q.M = p.M; q.act = c.act1; q.splitk = 1;
   auto ahead = [&]() {
-    const auto w3rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(c.w3), 0, blocks * UNITS * NP * 1024, 0x00027000);
+    const auto w3rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(c.w3), 0, kChainWide / 32 * UNITS * NP * 1024, 0x00027000);
 #pragma unroll
     for (int b = 0; b < NB; ++b)
 #pragma unroll
-      for (int u = 0; u < UNITS * NP; ++u) w3[b][u / NP][u % NP] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(w3rsrc, lane * 16 + (wave + b * NW) * (UNITS * NP * 1024) + u * 1024, 0, 0));
-    const auto rrsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(c.res3), 0, c.res3 ? p.M * c.n3 * ES : 0, 0x00027000);  // (past the end, and without a residual: zeros)
+      for (int u = 0; u < UNITS * NP; ++u) w3[b][u / NP][u % NP] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(w3rsrc, lane * 16 + u * 1024, (wave + b * NW) * (UNITS * NP * 1024), 0));
+    const auto rrsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(c.res3), 0, c.res3 ? p.M * (kChainWide * ES) : 0, 0x00027000);  // (past the end, and without a residual: zeros)
 #pragma unroll
     for (int r = 0; r < NV; ++r) res[r] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rrsrc, at0 + (tid + r * NT) * 16, 0, 0));
-    bias3 = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (4 * tid < c.n3) bias3 = *(const float4*)(c.bias3 + 4 * tid);
+    const auto brsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(c.bias3), 0, kChainWide * 4, 0x00027000);
+    bias3 = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(brsrc, tid * 16, 0, 0));  // (of the threads past the last channel: zeros)
   };
   conv_taps_body<BF16, 32, 2, NW, false, 1, true>(p, mt, 0, lds, ahead, kept, ROW);
-  if (c.n1) {
-    const auto w1rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(c.w1), 0, 2 * s1 * NP * 1024, 0x00027000);
+  {
+    const auto w1rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(c.w1), 0, c.n1 ? 2 * S1 * NP * 1024 : 0, 0x00027000);
 #pragma unroll
     for (int u = 0; u < U1; ++u)
 #pragma unroll
-      for (int k = 0; k < 2 * NP; ++k) w1[u][k / NP][k % NP] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(w1rsrc, lane * 16 + ((k / NP * s1 + u0 + u) * NP + k % NP) * 1024, 0, 0));
+      for (int k = 0; k < 2 * NP; ++k) w1[u][k / NP][k % NP] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(w1rsrc, lane * 16 + ((k / NP * S1 + u0 + u) * NP + k % NP) * 1024, 0, 0));
     fin.fetch(q, m0, 0, tid);
   }
-  if (4 * tid < kChainWide) *(float4*)&biases[4 * tid] = bias3;
+  if (tid < kChainWide / 4) *(float4*)&biases[4 * tid] = bias3;
   __syncthreads();
 
   auto pixels_of = [&](const unsigned char* const row, const int u) {  // the lane's pixel, k = 16 u + 8 lh .. + 7
@@ -1586,8 +1589,8 @@ __device__ __forceinline__ void conv_chain_body(const ConvArgs& p, const ChainAr
   constexpr int PA[6] = {BF16 ? 0 : 2, 1, 0, 1, 0, 0}, PB[6] = {0, 1, 2, 0, 1, 0};  // (as wave_mma)
 #pragma unroll
   for (int r = 0; r < NV; ++r) {
-    const int v = tid + r * NT, px = fast_div(v, c.mg_row);
-    if (v < vecs) *(uint4*)(wide + px * WIDE + (v - px * row_vecs) * 16) = res[r];
+    const int v = tid + r * NT;
+    *(uint4*)(wide + v / ROW_VECS * WIDE + v % ROW_VECS * 16) = res[r];
   }
   f32x16 sum[NB];
   {
@@ -1626,40 +1629,49 @@ __device__ __forceinline__ void conv_chain_body(const ConvArgs& p, const ChainAr
   const bool inside = m0 + li < p.M;
 #pragma unroll
   for (int b = 0; b < NB; ++b) {
-    const int n0 = (wave + b * NW) * 32 + 4 * lh;
-    if (wave + b * NW >= blocks) break;
+    unsigned char* const at = wide + li * WIDE + ((wave + b * NW) * 32 + 4 * lh) * ES;  // four quads of channels, eight channels apart
+    const float* const bi = biases + (wave + b * NW) * 32 + 4 * lh;
+    float v[16];
+    ResVec old[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) old[k] = *(const ResVec*)(at + 8 * k * ES);
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-      const int n = n0 + 8 * k;
-      unsigned char* const at = wide + li * WIDE + n * ES;
-      const float4 bi = *(const float4*)&biases[n];
-      float v[4] = {sum[b][4 * k] + bi.x, sum[b][4 * k + 1] + bi.y, sum[b][4 * k + 2] + bi.z, sum[b][4 * k + 3] + bi.w};
-      if constexpr (BF16) {
-        if (c.res3) {
-          const uint2 r = *(const uint2*)at;
-          v[0] += __uint_as_float(r.x << 16); v[1] += __uint_as_float(r.x & 0xffff0000u); v[2] += __uint_as_float(r.y << 16); v[3] += __uint_as_float(r.y & 0xffff0000u);
+      const float4 t = *(const float4*)(bi + 8 * k);
+      v[4 * k] = sum[b][4 * k] + t.x; v[4 * k + 1] = sum[b][4 * k + 1] + t.y; v[4 * k + 2] = sum[b][4 * k + 2] + t.z; v[4 * k + 3] = sum[b][4 * k + 3] + t.w;
+    }
+    if (c.res3) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        if constexpr (BF16) {
+          v[4 * k] += __uint_as_float(old[k].x << 16); v[4 * k + 1] += __uint_as_float(old[k].x & 0xffff0000u);
+          v[4 * k + 2] += __uint_as_float(old[k].y << 16); v[4 * k + 3] += __uint_as_float(old[k].y & 0xffff0000u);
+        } else {
+          v[4 * k] += __uint_as_float(old[k].x); v[4 * k + 1] += __uint_as_float(old[k].y); v[4 * k + 2] += __uint_as_float(old[k].z); v[4 * k + 3] += __uint_as_float(old[k].w);
         }
-        apply_act(v, c.act3);
-        *(uint2*)at = make_uint2(inside ? pack_bf16_rne(v[0], v[1]) : 0u, inside ? pack_bf16_rne(v[2], v[3]) : 0u);
-      } else {
-        if (c.res3) {
-          const float4 r = *(const float4*)at;
-          v[0] += r.x; v[1] += r.y; v[2] += r.z; v[3] += r.w;
-        }
-        apply_act(v, c.act3);
-        *(float4*)at = make_float4(inside ? v[0] : 0.f, inside ? v[1] : 0.f, inside ? v[2] : 0.f, inside ? v[3] : 0.f);
       }
+    }
+    apply_act(v, c.act3);
+#pragma unroll
+    for (int k = 0; k < 16; ++k) v[k] = inside ? v[k] : 0.f;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      if constexpr (BF16) *(uint2*)(at + 8 * k * ES) = make_uint2(pack_bf16_rne(v[4 * k], v[4 * k + 1]), pack_bf16_rne(v[4 * k + 2], v[4 * k + 3]));
+      else *(float4*)(at + 8 * k * ES) = make_float4(v[4 * k], v[4 * k + 1], v[4 * k + 2], v[4 * k + 3]);
     }
   }
   __syncthreads();
 
-  const auto yrsrc = __builtin_amdgcn_make_buffer_rsrc(c.y3, 0, p.M * c.n3 * ES, 0x00027000);
+  const auto yrsrc = __builtin_amdgcn_make_buffer_rsrc(c.y3, 0, p.M * (kChainWide * ES), 0x00027000);
   auto store_wide = [&]() {
+    uint4 out[NV];
 #pragma unroll
     for (int r = 0; r < NV; ++r) {
-      const int v = tid + r * NT, px = fast_div(v, c.mg_row);
-      if (v < vecs) put_at(yrsrc, at0 + v * 16, *(const uint4*)(wide + px * WIDE + (v - px * row_vecs) * 16));
+      const int v = tid + r * NT;
+      out[r] = *(const uint4*)(wide + v / ROW_VECS * WIDE + v % ROW_VECS * 16);
     }
+#pragma unroll
+    for (int r = 0; r < NV; ++r) put_at(yrsrc, at0 + (tid + r * NT) * 16, out[r]);
   };
   if (c.n1 == 0) {
     store_wide();
@@ -1668,7 +1680,6 @@ __device__ __forceinline__ void conv_chain_body(const ConvArgs& p, const ChainAr
   f32x16 acc[2] = {f32x16(0.f), f32x16(0.f)};
 #pragma unroll
   for (int u = 0; u < U1; ++u) {
-    if (u >= units1) break;
     const Split8 a = pixels_of(wide + li * WIDE, u0 + u);
 #pragma unroll
     for (int k = 0; k < (BF16 ? 1 : 6); ++k)
@@ -1679,9 +1690,9 @@ __device__ __forceinline__ void conv_chain_body(const ConvArgs& p, const ChainAr
   if constexpr (!BF16) {
     if (__builtin_expect(out_of_range(acc), 0)) {  // (the epilogue's second walk would find `wide` gone)
       ConvArgs x = ConvArgs();  // one row of 32 pixels in LDS
-      x.x = wide; x.w = c.w1; x.H = 1; x.W = x.M = 32; x.Cin = WIDE / 4; x.kh = x.kw = x.stride = 1; x.S = 2 * s1;
+      x.x = wide; x.w = c.w1; x.H = 1; x.W = x.M = 32; x.Cin = WIDE / 4; x.kh = x.kw = x.stride = 1; x.S = 2 * S1;
       x.mg_wo = x.mg_cin = 1;  // (every pixel and every k is below Wo and Cin)
-      plain_products<3, 32, 1, 2>(x, DwFusedArgs(), 0, 0, 2 * u0, 2 * units1, acc);
+      plain_products<3, 32, 1, 2>(x, DwFusedArgs(), 0, 0, 2 * u0, 2 * U1, acc);
     }
   }
   __syncthreads();  // the partial tiles come where `wide` was

@@ -87,9 +87,9 @@ def test_expansion_of_small_numbers_keeps_its_precision():
 
 
 # h, w, channels of the first 1x1, of the second (0: none), input of the first as residual, plan CUs: whole and ragged last tiles, one of a single pixel, images narrower than
-# a tile, fewer channels than a workgroup's waves have blocks, a second 1x1 that stays by itself
-CHAINS = [(56, 56, 256, 64, True, 128), (56, 56, 256, 0, True, 128), (48, 65, 256, 64, False, 128), (13, 17, 256, 40, True, 8), (193, 1, 256, 64, False, 8), (3, 75, 160, 0, True, 8),
-          (15, 15, 96, 64, True, 8)]
+# a tile, other channels (which stay by themselves)
+CHAINS = [(56, 56, 256, 64, True, 128), (56, 56, 256, 0, True, 128), (48, 65, 256, 64, False, 128), (13, 17, 256, 40, True, 8), (193, 1, 256, 64, False, 8), (3, 75, 256, 36, True, 8),
+          (15, 15, 256, 0, False, 8), (15, 15, 160, 64, True, 8)]
 
 
 @pytest.mark.parametrize("dtype", ["fp32", "bf16"])
@@ -109,7 +109,7 @@ def test_bottleneck_in_one_launch(shape, dtype):
     outs = []
     for flags, k in ((0, 1), (0, 2), (D.NO_PAIR, 1)):
         with GpuNet(layers, weights, (32, h, w), dtype, flags=flags, k=k, plan_cus=cus) as g:
-            assert (D.daris_get_launch_plan(g.task, 2)["out_slot"] == -1) == (flags == 0 and 3 not in D.daris_get_stage_cuts(g.task))
+            assert (D.daris_get_launch_plan(g.task, 2)["out_slot"] == -1) == (flags == 0 and n3 == 256 and 3 not in D.daris_get_stage_cuts(g.task))
             outs.append([g.forward(x), g.forward(bad)])
     for other in outs[1:]:
         np.testing.assert_array_equal(outs[0][0], other[0])
