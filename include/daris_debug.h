@@ -21,7 +21,8 @@ extern "C" {
  * [21] split-K workspace bytes, [22] layer it shares a launch with or -1, [23] 1 = the joint launch is issued at this
  * layer (a convolution that names a pooling layer here is computed and pooled in that layer's launch, whose kernel id is that layer's; one that names the FC
  * layer behind a global average pooling leaves sums over its pixels for that FC layer, and the pooling layer between them, which then
- * has the convolution's kernel id, issues nothing),
+ * has the convolution's kernel id, issues nothing; joint launches that a stage cut between the layers parts without another change of their plans, of 64-pixel tiles and the
+ * pooling layer behind and of a 3x3 convolution and the 1x1 ones behind, do not show here),
  * [24] activation slot of the layer's output (-1: the caller's logits, or never stored), [25] slot of its input, [26] slot of its
  * residual operand or -1.  A slot is a device buffer shared by tensors whose lifetimes do not overlap.  [27] how the waves come by their
  * pixels: 0 straight into registers, no K step straddles a filter tap, 1 the same for any channel count, 2 the network input as the
@@ -35,7 +36,7 @@ daris_status daris_read_layer(daris_task t, int layer, float* host_out, int64_t 
 /* Time each layer of task t on stream 0 of partition p: `reps` runs back to back, from the start time stamp of the
  * first dispatch to the end time stamp of the last, divided by reps (the earlier layer of a launch pair reports 0).
  * ms_per_layer = host float[n_layers]; kernel_id = host int32[n_layers] (which kernel variant ran, see
- * daris_kernel_name); flops = host double[n_layers] algorithmic FLOPs (2*MACs) of the layer. */
+ * daris_kernel_name; of a layer without a launch, what the plan says); flops = host double[n_layers] algorithmic FLOPs (2*MACs) of the layer. */
 daris_status daris_profile_layers(daris_task t, daris_part p, int reps, float* ms_per_layer, int32_t* kernel_id,
                                   double* flops);
 const char* daris_kernel_name(int32_t kernel_id);

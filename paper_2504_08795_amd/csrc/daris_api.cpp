@@ -347,7 +347,8 @@ std::string encode_network(TaskRt& T, const std::vector<void*>& slots, float* ws
             seq->in_launch = (int)seq->launches.size();
             seq->in_off = kConvInputOffset;
           }
-          ok = encode_image_pool(g_joined, O.cp, conv_args(T, L.joins, nullptr, slots, ws), a, bf16, &ks);
+          const ConvArgs conv = conv_args(T, L.joins, nullptr, slots, ws);
+          ok = O.cp.rows == 64 ? encode_block_pool(g_joined, O.cp, conv, a, &ks) : encode_image_pool(g_joined, O.cp, conv, a, bf16, &ks);
           break;
         }
         ok = L.d.op == DARIS_OP_MAXPOOL ? encode_maxpool(g_kt, a, bf16, &ks) : encode_gavgpool(g_kt, a, bf16, &ks);
@@ -1123,7 +1124,7 @@ int32_t daris_get_launch_plan(daris_task t, int layer, int64_t* out, int32_t cap
   const int64_t v[28] = {L.kernel_id, conv ? 1 : 0, conv ? c.rows : 0, (int64_t)L.out.H * L.out.W, L.out.Cs, L.K, L.Kpad,
                          c.tn, c.nw, c.S, c.sz, c.sw, c.splitk, c.MT, c.NTn, c.G, c.xmode, (int64_t)c.grid_x, 1, 1,
                          c.threads, (int64_t)c.ws_bytes, L.pair_with, L.pair_lead ? 1 : 0,
-                         net.joined_away(layer) ? -1 : L.out.slot, L.in_t > 0 && net.joined_away(L.in_t - 1) ? -1 : net.tensor(L.in_t).slot, L.res_t >= 0 ? net.tensor(L.res_t).slot : -1,
+                         net.hidden(layer) ? -1 : L.out.slot, L.in_t > 0 && net.hidden(L.in_t - 1) ? -1 : net.tensor(L.in_t).slot, L.res_t >= 0 ? net.tensor(L.res_t).slot : -1,
                          L.fused_dw ? kGatherDepthwise : c.gather};
   const int n = cap < 28 ? 27 : 28;
   for (int i = 0; i < n; ++i) out[i] = v[i];
@@ -1546,7 +1547,7 @@ daris_status daris_profile_layers(daris_task t, daris_part p, int reps, float* m
   for (int l = 0; l < n && result == DARIS_OK; ++l) {
     const int lo = T.seq.layer_lo[l], hi = T.seq.layer_lo[l + 1];
     ms_per_layer[l] = 0.f;
-    if (kernel_id) kernel_id[l] = T.net.layers[l].kernel_id;
+    if (kernel_id) kernel_id[l] = hi > lo ? T.seq.launches[lo].kl.kernel_id : T.net.layers[l].kernel_id;
     if (flops) flops[l] = 2.0 * (double)T.net.layers[l].macs;
     if (lo == hi) continue;  // the earlier member of a launch pair: its work is timed with the later one
     // one warm-up pass, then `reps` passes back to back: from the start of the first kernel to the end of the last

@@ -1,6 +1,7 @@
 // Kernels that compute layers which follow one another in one launch (layer_bodies.h).
 #include <hip/hip_runtime.h>
 
+#include "block_body.h"
 #include "layer_bodies.h"
 #include "device_common.h"
 #include "kernels.h"
@@ -19,6 +20,18 @@ __global__ __launch_bounds__(128 * (kImagePoolRows + 1)) void conv_image_pool_ke
 
 template __global__ void conv_image_pool_kernel<false>(const ImageConvArgs);
 template __global__ void conv_image_pool_kernel<true>(const ImageConvArgs);
+
+// A large fp32 convolution with three taps per fetch and the 2 x 2 max pooling behind it.
+template <int NW>
+__global__ __launch_bounds__(NW * 64) void conv_block_pool_kernel(const ConvArgs) {
+  const ConvArgs p = conv_args_at((ConstPtr)__builtin_amdgcn_kernarg_segment_ptr());
+  __shared__ __align__(16) float red[conv_block_lds<NW, true>()];
+  conv_block_body<NW, true, true>(p, red);
+  puts_done();
+}
+template __global__ void conv_block_pool_kernel<2>(const ConvArgs);
+template __global__ void conv_block_pool_kernel<4>(const ConvArgs);
+template __global__ void conv_block_pool_kernel<8>(const ConvArgs);
 
 // A 1x1 convolution and the depthwise convolution behind it.
 template <bool BF16, int NCH>

@@ -32,6 +32,7 @@ enum KernelId : int32_t {
   K_IMAGE_POOL_F32, K_IMAGE_POOL_BF16,  // ... with the 3 x 3 max pooling behind it
   K_EXPAND_DW_F32, K_EXPAND_DW_BF16,    // a 1 x 1 convolution and the depthwise one behind it
   K_CHAIN_F32, K_CHAIN_BF16,            // a 3 x 3 convolution and the one or two 1 x 1 behind it
+  K_BLOCK_POOL_F32,                     // 64-pixel tiles with three taps per fetch and the 2 x 2 max pooling behind them
   K_COUNT  // at most 64: what a caller of daris_kernel_timing_read has to provide
 };
 static_assert(K_COUNT <= 64, "see daris_kernel_timing_read");
@@ -295,6 +296,7 @@ struct JoinedTable {
   const AqlKernel* expand_dw[2][kExpandChunks] = {};
   const AqlKernel* fc_pooled[2] = {};
   const AqlKernel* chain[2] = {};
+  const AqlKernel* block_pool[3] = {};  // [log2(nw) - 1]
   const AqlKernel* tall[2][3] = {};     // [bf16][log2(nw) - 1]
   std::string resolve(const AqlRuntime& rt);  // as KernelTable::resolve
 };
@@ -327,6 +329,10 @@ bool conv_dw_fusable(const ConvPlan& pl, int bf16);
 // 253 455.3 instead of 454.4.
 bool image_pool_takes(const ConvPlan& pl, int Ho, int Wo, int cout_stride, int k, int stride, int nominal_cus, int bf16);
 bool encode_image_pool(const JoinedTable& kt, const ConvPlan& pl, const ConvArgs& a, const PoolArgs& pool, int bf16, std::vector<KernelLaunch>* out);
+// An fp32 convolution in 64-pixel tiles with three taps per fetch and the 2 x 2 max pooling with stride 2 that alone reads it, in one launch: whether the plan
+// (of an output of Ho x Wo) is one, and the launch.
+bool block_pool_takes(const ConvPlan& pl, int Ho, int Wo);
+bool encode_block_pool(const JoinedTable& kt, const ConvPlan& pl, const ConvArgs& a, const PoolArgs& pool, std::vector<KernelLaunch>* out);
 // A 1x1 convolution and the 3x3 depthwise convolution with padding 1 that alone reads it, in one launch.  Turns pl into the plan of the convolution by
 // itself whose sums have the same order, and returns whether the two should be joined.
 bool plan_expand_dw(ConvPlan* pl, int H, int W, int cin_stride, int c_stride, int Kpad, int dw_stride, int nominal_cus, int bf16);

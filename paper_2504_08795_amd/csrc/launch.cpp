@@ -25,7 +25,8 @@ static const char* const kNames[K_COUNT] = {
     "conv_wave64_taps_f32_t2w2", "conv_wave64_taps_f32_t2w4", "conv_wave64_taps_f32_t2w8",
     "conv_wave_image_f32_n1_t1w4", "conv_wave_image_f32_n2_t1w4", "conv_wave_image_bf16_n1_t1w4", "conv_wave_image_bf16_n2_t1w4",
     "conv_wave_image_pool_f32_n2_t1w10", "conv_wave_image_pool_bf16_n2_t1w10",
-    "conv_wave16_expand_dw_f32", "conv_wave16_expand_dw_bf16", "conv_wave_chain_f32_t2w8", "conv_wave_chain_bf16_t2w4"};
+    "conv_wave16_expand_dw_f32", "conv_wave16_expand_dw_bf16", "conv_wave_chain_f32_t2w8", "conv_wave_chain_bf16_t2w4",
+    "conv_wave64_pool_f32"};
 
 const char* kernel_name(int32_t id) { return (id >= 0 && id < K_COUNT) ? kNames[id] : "?"; }
 
@@ -375,6 +376,7 @@ std::string JoinedTable::resolve(const AqlRuntime& rt) {
     image_pool[b] = get("daris::conv_image_pool_kernel<" + B + ">", sizeof(ImageConvArgs));
     for (int v = 0; v < 3; ++v)  // the variants that taps_kernel has with two blocks
       if (taps_kernel(16, b, 2, 2 << v) != K_NONE) tall[b][v] = get("daris::conv_taps16_tall_kernel<" + B + ", " + std::to_string(2 << v) + ">", sizeof(ConvArgs));
+    for (int v = 0; v < 3; ++v) block_pool[v] = get("daris::conv_block_pool_kernel<" + std::to_string(2 << v) + ">", sizeof(ConvArgs));
     chain[b] = get("daris::conv_chain_kernel<" + B + ", " + (b ? "4" : "8") + ">", sizeof(ChainLaunchArgs));
     fc_pooled[b] = get("daris::fc_pooled_kernel<" + B + ">", sizeof(FcPooledArgs));
     for (int v = 0; v < kExpandChunks; ++v) expand_dw[b][v] = get("daris::conv_expand_dw_kernel<" + B + ", " + std::to_string(v + 1) + ">", sizeof(ExpandDwArgs));
@@ -502,6 +504,17 @@ bool encode_image_pool(const JoinedTable& kt, const ConvPlan& pl, const ConvArgs
   m.pool_h = pool.Ho;
   m.pool_w = pool.Wo;
   return push(out, kt.image_pool[bf16], bf16 ? K_IMAGE_POOL_BF16 : K_IMAGE_POOL_F32, (uint32_t)(t.tiles * (t.nb / t.wn)), 64 * 2 * (kImagePoolRows + 1), &m, sizeof(m));
+}
+
+bool block_pool_takes(const ConvPlan& pl, int Ho, int Wo) { return pl.rows == 64 && pl.gather == kGatherTaps && pl.splitk == 1 && pl.tn == 2 && Ho % 2 == 0 && Wo % 2 == 0; }
+
+bool encode_block_pool(const JoinedTable& kt, const ConvPlan& pl, const ConvArgs& layer, const PoolArgs& pool, std::vector<KernelLaunch>* out) {
+  if (!block_pool_takes(pl, layer.Ho, layer.Wo) || !taps_agree(pl, layer) || !conv_block_takes(layer.H, layer.W, layer.Cin, layer.kh, layer.pad, layer.Kpad) || layer.res || (layer.act & kActSumPixels) ||
+      pl.threads != 64 * pl.nw || pool.k != 2 || pool.stride != 2 || pool.pad != 0 || pool.Ho != layer.Ho / 2 || pool.Wo != layer.Wo / 2 || pool.C != layer.Cout)
+    return false;
+  ConvArgs a = layer;
+  a.y = pool.y;
+  return push(out, kt.block_pool[variant_of(2, pl.nw) - 3], K_BLOCK_POOL_F32, pl.grid_x, (uint32_t)pl.threads, &a, sizeof(a));
 }
 
 bool encode_conv(const KernelTable& kt, const ConvPlan& pl, const ConvArgs& a, int bf16, std::vector<KernelLaunch>* out) {

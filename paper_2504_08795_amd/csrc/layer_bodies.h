@@ -162,7 +162,7 @@ __device__ __forceinline__ void plain_products(const ConvArgs& p, const DwFusedA
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
         int k = c * CK;
-        if constexpr (MODE == 5) {  // chunks in the order (ky, 16 channels, kx) of three taps
+        if constexpr (MODE == 5 || MODE == 7) {  // chunks in the order (ky, 16 channels, kx) of three taps
           const int gk = c / 3 * CK, ky = fast_div(gk, p.mg_cin);
           k = (3 * ky + c % 3) * p.Cin + gk - ky * p.Cin;
         }
@@ -171,7 +171,11 @@ __device__ __forceinline__ void plain_products(const ConvArgs& p, const DwFusedA
           const int x = m0 - fast_div(m0, p.mg_wo) * p.Wo + lane % 16;
           m = x < p.Wo ? m0 + (2 * i + lane % R / 16) * p.Wo + lane % 16 : p.M;
         }
-        const float4 v = pixel_quad<MODE == 6 ? 2 : MODE>(p, dwf, m, k + 8 * (lane / R) + 4 * h);
+        if constexpr (MODE == 7) {  // two rows of the image, from place m0 on (conv_block_body with POOL)
+          const int s = m0 + lane % R;
+          m = 2 * s < p.M ? s + (fast_div(s, p.mg_wo) + i) * p.Wo : p.M;
+        }
+        const float4 v = pixel_quad<MODE == 6 ? 2 : MODE == 7 ? 5 : MODE>(p, dwf, m, k + 8 * (lane / R) + 4 * h);
         a[i][4 * h] = v.x; a[i][4 * h + 1] = v.y; a[i][4 * h + 2] = v.z; a[i][4 * h + 3] = v.w;
       }
 #pragma unroll

@@ -225,6 +225,7 @@ std::string build_plan(const daris_dnn& dnn, bool keep_activations, bool pair_la
     if (!only_reader) continue;
     if (B.d.op == DARIS_OP_MAXPOOL) {
       if (fuse_ingest && B.d.k == 3 && B.d.stride == 2 && B.d.pad == 1 && image_pool_takes(A.cp, A.out.H, A.out.W, A.out.Cs, A.d.k, A.d.stride, plan_cus, net.bf16)) B.can_join = l;
+      if (pair_launches && B.d.k == 2 && B.d.stride == 2 && B.d.pad == 0 && A.res_t < 0 && block_pool_takes(A.cp, A.out.H, A.out.W)) B.can_join = l;
     } else if (B.d.op == DARIS_OP_CONV && B.depthwise && staged_rows && small_tiles) {
       if (B.d.k == 3 && B.d.pad == 1 && (B.d.stride == 1 || B.d.stride == 2) && A.d.k == 1 && A.d.stride == 1 && A.d.pad == 0 && A.res_t < 0 && rows_taken(A) && !(l == 0 && net.fuse_ingest) &&
           plan_expand_dw(&A.cp, A.out.H, A.out.W, net.tensor(A.in_t).Cs, A.out.Cs, A.Kpad, B.d.stride, plan_cus, net.bf16)) {
@@ -340,9 +341,9 @@ bool join_layers(NetPlan* net) {
     if (B.can_join == l && (B.joins == l) == cut) {
       const bool pool = B.d.op == DARIS_OP_MAXPOOL;
       B.joins = cut ? -1 : l;
-      if (pool) A.pair_with = cut ? -1 : l + 1;
-      if (pool) B.kernel_id = cut ? (int32_t)K_MAXPOOL : K_IMAGE_POOL_F32 + net->bf16;
-      else if (B.depthwise) B.kernel_id = cut ? (int32_t)K_DWCONV : K_EXPAND_DW_F32 + net->bf16;  // (a dense convolution keeps the name of the plan whose sums it has)
+      if (pool && A.cp.rows != 64) A.pair_with = cut ? -1 : l + 1;  // (64-pixel tiles: what a plan says is the same with the cut and without)
+      if (pool && A.cp.rows != 64) B.kernel_id = cut ? (int32_t)K_MAXPOOL : K_IMAGE_POOL_F32 + net->bf16;
+      if (B.depthwise) B.kernel_id = cut ? (int32_t)K_DWCONV : K_EXPAND_DW_F32 + net->bf16;  // (a dense convolution keeps the name of the plan whose sums it has)
       changed = true;
     }
     const bool follows = B.can_follow == l && A.joins >= 0 && !cut;

@@ -67,6 +67,8 @@ struct NetPlan {
   const TensorInfo& tensor(int t) const { return t == 0 ? ingest : layers[t - 1].out; }
   // Whether layer l is computed in the launch of the next one, and its output never stored.
   bool joined_away(int l) const { return l + 1 < (int)layers.size() && layers[l + 1].joins == l; }
+  // Whether a plan's reader is told that layer l is never stored: not of a convolution in 64-pixel tiles that a pooling layer joins.
+  bool hidden(int l) const { return joined_away(l) && layers[l].cp.rows != 64; }
   // Whether layer l's launch is the next one's.
   bool followed(int l) const { return l + 1 < (int)layers.size() && layers[l + 1].follows == l; }
 };

@@ -184,3 +184,29 @@ def test_two_blocks_of_pixels_or_of_channels(shape, dtype):
     np.testing.assert_allclose(outs[0][1], outs[1][1], rtol=1e-4, atol=1e-3 if dtype == "fp32" else 0)
     e_max, e_l2 = rel_err(outs[0][0], oracle_logits(layers, weights, x, dtype))
     assert e_max <= TOL[dtype] and e_l2 <= TOL[dtype], (e_max, e_l2)
+
+
+# c_in, h, w, c_out, plan CUs: workgroups of eight, four and two waves, whole and ragged last tiles, a single pair of rows, rows of two pixels and of fewer than a tile's,
+# channels that end inside a block
+BLOCK_POOLS = [(64, 20, 22, 64, 8), (64, 16, 24, 64, 8), (32, 28, 30, 64, 8), (32, 38, 48, 64, 8), (64, 2, 200, 100, 8), (48, 70, 6, 64, 8), (64, 200, 2, 64, 8), (128, 56, 56, 256, 128),
+               (64, 112, 110, 128, 128)]
+
+
+@pytest.mark.parametrize("shape", BLOCK_POOLS)
+def test_large_convolution_and_its_pooling(shape):
+    cin, h, w, cout, cus = shape
+    layers = [N.Layer(op=N.OP_CONV, c_in=cin, c_out=cout, k=3, pad=1, act=1, in_from=-1, has_bn=False), N.Layer(op=N.OP_MAXPOOL, c_in=cout, c_out=cout, k=2, stride=2, in_from=0)]
+    weights = wl.make_weights(layers, 3)
+    x = wl.make_inputs((cin, h, w), 3, 1, "normal")[0]
+    bad, small = x.copy(), x * np.float32(2.0 ** -115)
+    bad[0, h // 2, w // 3], bad[cin - 1, 0, w - 1] = np.nan, np.inf
+    outs, plans = _joined_and_parted(layers, weights, (cin, h, w), "fp32", [x, bad, small], plan_cus=cus)
+    assert plans[0]["rows"] == 64, plans
+    with GpuNet(layers, weights, (cin, h, w), "fp32", plan_cus=cus) as g:
+        ms, kid, _ = D.daris_profile_layers(g.task, g.parts[0], 2, 2)
+        assert ms[0] == 0 and D.daris_kernel_name(kid[1]) == "conv_wave64_pool_f32", (ms, kid)
+    np.testing.assert_array_equal(*outs[0])
+    np.testing.assert_allclose(*outs[1], rtol=1e-4, atol=1e-3)      # (which tiles are walked again in plain fp32 depends on the tiles)
+    np.testing.assert_allclose(*outs[2], rtol=1e-4, atol=0)
+    e_max, e_l2 = rel_err(outs[0][0], oracle_logits(layers, weights, x, "fp32"))
+    assert e_max <= TOL["fp32"] and e_l2 <= TOL["fp32"], (e_max, e_l2)

@@ -13,7 +13,7 @@ HOST = D.VIRTUAL_TIME | D.NO_DEVICE
 N = wl.nets
 
 # code object: {kernel: (bytes of its argument block, how many instances)}
-JOINED_KERNELS = {"daris_joined_kernels": {"conv_image_pool_kernel": (160, 2), "conv_expand_dw_kernel": (160, 10), "fc_pooled_kernel": (64, 2), "conv_chain_kernel": (248, 2)},
+JOINED_KERNELS = {"daris_joined_kernels": {"conv_image_pool_kernel": (160, 2), "conv_expand_dw_kernel": (160, 10), "fc_pooled_kernel": (64, 2), "conv_chain_kernel": (248, 2), "conv_block_pool_kernel": (160, 3)},
                   "daris_tall_kernels": {"conv_taps16_tall_kernel": (160, 3)}}
 
 
@@ -88,3 +88,4 @@ def test_bottlenecks_of_64_channels_share_a_launch():
             D.daris_split_stages(t, k)
             cuts = D.daris_get_stage_cuts(t)
         assert (p[0]["out_slot"] == -1) == (1 not in cuts) and (joined or 1 in cuts), (p, cuts)
+
