@@ -63,8 +63,9 @@ __device__ __forceinline__ void conv_block_body(const ConvArgs& p, float* const 
   const int m0 = mt * 64, s0 = mt * 32, nb0 = (g - zi * p.NTn) * 2;
   const int s_wg0 = zi * p.sz;
   const int s_wg1 = min(s_wg0 + p.sz, p.S);
-  const int sbeg = min(s_wg0 + wave * p.sw, s_wg1);
-  const int nchunks = (min(sbeg + p.sw, s_wg1) - sbeg) >> 1;  // TAPS: in threes
+  int sbeg = min(s_wg0 + wave * p.sw, s_wg1), nsteps = min(sbeg + p.sw, s_wg1) - sbeg;
+  if constexpr (TAPS) tap_slice<false, NW>(s_wg0, s_wg1, p.sw, wave, &sbeg, &nsteps);
+  const int nchunks = nsteps >> 1;  // TAPS: in threes
 
   const auto xrsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p.x), 0, (int)((uint32_t)(p.H * p.W) * (uint32_t)p.Cin * ES), 0x00027000);
   const int piece = lane & 3, prow = lane >> 2;

@@ -210,3 +210,20 @@ def test_large_convolution_and_its_pooling(shape):
     np.testing.assert_allclose(*outs[2], rtol=1e-4, atol=0)
     e_max, e_l2 = rel_err(outs[0][0], oracle_logits(layers, weights, x, "fp32"))
     assert e_max <= TOL["fp32"] and e_l2 <= TOL["fp32"], (e_max, e_l2)
+
+
+# c_in, h, w, c_out, plan CUs: 12, 13, 15 and 18 groups of taps on eight waves, in 32-pixel tiles of one and two blocks, 64-pixel and 16-pixel ones; K split across
+# workgroups whose last share is the smallest
+SHARES = [(64, 13, 17, 64, 8), (64, 56, 56, 64, 128), (208, 7, 9, 32, 8), (80, 13, 17, 64, 8), (96, 13, 17, 64, 8), (64, 48, 64, 64, 64), (96, 20, 21, 64, 8), (416, 7, 7, 256, 64), (512, 5, 5, 512, 240)]
+
+
+@pytest.mark.parametrize("shape", SHARES)
+def test_uneven_shares_of_k(shape):
+    cin, h, w, cout, cus = shape
+    layers = [N.Layer(op=N.OP_CONV, c_in=cin, c_out=cout, k=3, pad=1, act=1, in_from=-1, has_bn=False)]
+    weights = wl.make_weights(layers, 3)
+    x = wl.make_inputs((cin, h, w), 3, 1, "normal")[0]
+    with GpuNet(layers, weights, (cin, h, w), "fp32", plan_cus=cus) as g:
+        assert "taps" in D.daris_kernel_name(D.daris_get_launch_plan(g.task, 0)["kernel_id"])
+        e_max, e_l2 = rel_err(g.forward(x), oracle_logits(layers, weights, x, "fp32"))
+    assert e_max <= 2e-6 and e_l2 <= 1e-6, (e_max, e_l2)            # a group too many or too few is an error of the order of a sum
