@@ -11,7 +11,7 @@ LIB = os.path.join(HERE, "libdaris.so")
 DEVICE_SOURCES = {"kernels.hip": "daris_kernels", "taps_kernels.hip": "daris_taps_kernels", "image_kernels.hip": "daris_image_kernels", "block_kernels.hip": "daris_block_kernels",
                   "point_kernels.hip": "daris_point_kernels"}
 # ... of the kernels that compute several layers in a row
-JOINED_SOURCES = {"joined_kernels.hip": "daris_joined_kernels", "tall_kernels.hip": "daris_tall_kernels"}
+JOINED_SOURCES = {"joined_kernels.hip": "daris_joined_kernels", "tall_kernels.hip": "daris_tall_kernels", "pointwise_kernels.hip": "daris_pointwise_kernels"}
 HOST_SOURCES = ["aql.cpp", "launch.cpp", "sched_core.cpp", "net_plan.cpp", "daris_api.cpp"]
 COMMON = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-Wall", "-Wno-unused-function"]
 # no packed fp32 arithmetic in device code (some forms have given wrong results on this hardware)

@@ -44,6 +44,8 @@ extern "C" const char daris_block_kernels_co[];
 extern "C" const char daris_block_kernels_co_end[];
 extern "C" const char daris_joined_kernels_co[];
 extern "C" const char daris_joined_kernels_co_end[];
+extern "C" const char daris_pointwise_kernels_co[];
+extern "C" const char daris_pointwise_kernels_co_end[];
 extern "C" const char daris_tall_kernels_co[];
 extern "C" const char daris_tall_kernels_co_end[];
 extern "C" const char daris_point_kernels_co[];
@@ -909,6 +911,7 @@ daris_status daris_init(int device, uint64_t seed, int flags) {
                                {daris_taps_kernels_co, (size_t)(daris_taps_kernels_co_end - daris_taps_kernels_co)},
                                {daris_image_kernels_co, (size_t)(daris_image_kernels_co_end - daris_image_kernels_co)},
                                {daris_joined_kernels_co, (size_t)(daris_joined_kernels_co_end - daris_joined_kernels_co)},
+                               {daris_pointwise_kernels_co, (size_t)(daris_pointwise_kernels_co_end - daris_pointwise_kernels_co)},
                                {daris_tall_kernels_co, (size_t)(daris_tall_kernels_co_end - daris_tall_kernels_co)},
                                {daris_point_kernels_co, (size_t)(daris_point_kernels_co_end - daris_point_kernels_co)}});
       if (err.empty()) {

@@ -866,7 +866,11 @@ __device__ __forceinline__ void wave_mma(const Split8 (&a)[TM], const uint4 (&b)
 // it would cost each launch 0.02 to 0.06 us in front of its first load: ResNet-18's frame 133.2 -> 134.5 us.)  Straight into registers
 // (gather mode 1), 2250000 x 64 x 256 in fp32 takes 1810 us instead of 1290 on 128 CUs, 2250000 x 64 x 2304 10070 instead of 5540 (with three
 // taps per fetch); bf16 with K twice as long 1580 instead of 1120, 8250 instead of 4310.
-template <bool BF16, int R, int TN, int NW, bool LARGE = false>
+// POINT: 1 x 1 windows without padding.  There is one tap, which every pixel has, so a lane's rows lie one behind the other, and the walk from tap to tap, some
+// fifty instructions for every request, is gone: the first matrix instruction of a wave is the 360th instead of the 620th.  us on 128 CUs without and with: bf16
+// 784 x 128 x 512 2.69, 2.45, 196 x 256 x 1024 2.83, 2.65, 49 x 2048 x 512 2.76, 2.56; fp32 784 x 128 x 512 4.09, 3.86, 196 x 64 x 384 2.59, 2.37, 49 x 2048 x 512
+// 4.18, 3.95; but bf16 784 x 512 x 128 2.82, 2.86.
+template <bool BF16, int R, int TN, int NW, bool LARGE = false, bool POINT = false>
 __device__ __forceinline__ void conv_rows_body(const ConvArgs& p, const int mt, const int g, float* const red) {
   constexpr int ES = BF16 ? 2 : 4;
   constexpr int RK = 64 / ES;                     // k of a row
@@ -874,7 +878,7 @@ __device__ __forceinline__ void conv_rows_body(const ConvArgs& p, const int mt, 
   constexpr int NP = BF16 ? 2 : 3;                // 16-byte pieces of a chunk's weights per lane and channel block: steps, or parts
   // chunks of rows and of weights in flight (bf16 tiles of 32 x 64, 784 x 512 x 128: three 2.9 us, two 3.1; 49 x 512 x 4608 in fp32:
   // 8.3, 8.0; four, in bf16, take so many registers that 3136 x 256 x 64 goes from 3.0 to 4.2)
-  constexpr int DC = BF16 && R == 32 && TN == 2 ? 3 : 2;
+  constexpr int DC = BF16 && R == 32 && TN == 2 && !POINT ? 3 : 2;  // (POINT: with three the tiles of 32 x 64 have no registers for three waves on a SIMD)
   constexpr int kOutside = (int)0x80000000;       // an offset past the end of any tensor
 
   if (p.wave_prio) __builtin_amdgcn_s_setprio(3);
@@ -889,17 +893,27 @@ __device__ __forceinline__ void conv_rows_body(const ConvArgs& p, const int mt, 
 
   // Walk over k = (tap, ci): a row never straddles a tap, so the walk is wave-uniform and lives in scalars.  A lane's row offsets
   // change only from tap to tap; inside one, a scalar offset advances.
+  static_assert(!LARGE || !POINT, "one form or the other");
   constexpr int NX = R / 16;  // pixels of a lane
   const int kbeg = sbeg * KS;
-  const int tap = fast_div(kbeg, p.mg_cin);
+  const int tap = POINT ? 0 : fast_div(kbeg, p.mg_cin);
   int ci = kbeg - tap * p.Cin;
-  int ky = fast_div(tap, p.mg_kw), kx = tap - ky * p.kw;
+  int ky = POINT ? 0 : fast_div(tap, p.mg_kw), kx = tap - ky * p.kw;
   const int piece = lane & 3, prow = lane >> 2;
   int iy0[NX], ix0[NX], rbase[NX], vo[NX];
   const int iy_first = LARGE ? min(max(fast_div(m0, p.mg_wo) * p.stride - p.pad, 0), p.H - 1) : 0;  // the first row of the image that the tile may read
 #pragma unroll
   for (int j = 0; j < NX; ++j) {
     const int m = min(m0 + 16 * j + prow, p.M - 1);  // (past the last pixel: the last one once more, whose sums nobody stores)
+    if constexpr (POINT) {
+      int from = m;
+      if (p.stride != 1) {
+        const int y = fast_div(m, p.mg_wo);
+        from = y * (p.stride * p.W) + (m - y * p.Wo) * p.stride;
+      }
+      vo[j] = (int)((uint32_t)from * (uint32_t)(p.Cin * ES)) + piece * 16;
+      continue;
+    }
     const int y = fast_div(m, p.mg_wo), x = m - y * p.Wo;
     iy0[j] = y * p.stride - p.pad;
     ix0[j] = x * p.stride - p.pad;
@@ -928,11 +942,18 @@ __device__ __forceinline__ void conv_rows_body(const ConvArgs& p, const int mt, 
       enter_tap();
     }
   };
-  enter_tap();
+  if constexpr (!POINT) enter_tap();
   uint4 rows[DC][2];
   auto load_rows = [&](int s) {
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
+      if constexpr (POINT) {
+        const bool past = BF16 && R == 16 && rest <= 0;  // (the second step of a chunk of one)
+        rows[s][j] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(xrsrc, past ? kOutside : vo[j % NX], soff, 0));
+        if (BF16 && R == 16) --rest;
+        if (R == 16 || j == 1) soff += 64;
+        continue;
+      }
       rows[s][j] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(xrsrc, vo[j % NX], soff, 0));
       if (R == 16 || j == 1) next_row();
     }
