@@ -289,6 +289,7 @@ struct KernelTable {
   const AqlKernel* cu_probe = nullptr;
   // "" or the name of the first kernel that is missing or whose argument size is not what this header declares
   std::string resolve(const AqlRuntime& rt);
+  std::string resolve_pointwise(const AqlRuntime& rt);  // ... for `point` and `point_pair`, without which the general kernels run
 };
 
 // The kernels that compute several layers in a row, and those that run a plan of KernelTable's in tiles of another shape.
@@ -319,8 +320,8 @@ bool encode_conv_dw(const KernelTable& kt, const ConvPlan& pl, const ConvArgs& a
 // vector cache and pays a memory latency per chunk of 64 bytes of channels, so it can only win where the convolution has enough
 // workgroups to fill a partition and a single channel block (no repetition per block, few chunks per wave); elsewhere the
 // separate, fully parallel depthwise launch is faster (by 1.3 to 5 us per block).  There it saves a launch: MobileNetV2's kernels fused / with
-// the three blocks' layers in launches of their own, fp32 128 CUs 148.5 / 150.4 us, 192 CUs 145.4 / 146.0, 96 CUs 156.0 / 156.9, 64 CUs 172.6 /
-// 175.3; bf16 on 128 CUs 133.4 / 132.7 (two blocks).
+// the three blocks' layers in launches of their own, fp32 128 CUs 134.5 / 135.5 us, 64 CUs 163.5 / 165.1 (the frame on 128 169.7 / 172.4); bf16 on 128 CUs 109.6 /
+// 108.7 (two blocks).
 bool conv_dw_fusable(const ConvPlan& pl, int bf16);
 // The first convolution and the 3 x 3 max pooling with stride 2 and padding 1 that alone reads it, in one launch: whether the convolution planned
 // as pl should be computed so, and the launch itself (pool: the pooling layer).  us of the two launches / of one, 12544 x 64 x 7 x 7 with stride 2: fp32 on
