@@ -1032,7 +1032,16 @@ daris_task daris_register_task(const daris_dnn* dnn, int64_t period_ns, int64_t 
   if (priority != DARIS_HP && priority != DARIS_LP) return fail(DARIS_EINVAL, "priority must be DARIS_HP or DARIS_LP");
   if (G->tasks.size() >= 65535) return fail(DARIS_ERANGE, "too many tasks");
   std::unique_ptr<TaskRt> T(new TaskRt());
-  std::string err = build_plan(*dnn, G->flags & DARIS_KEEP_ACTIVATIONS, !(G->flags & DARIS_NO_PAIR), !(G->flags & DARIS_NO_FUSED_INGEST), !(G->flags & DARIS_NO_STAGED_ROWS), !(G->flags & DARIS_NO_SMALL_TILES), !(G->flags & DARIS_NO_FUSED_DW), G->plan_cus, &T->net, !(G->flags & DARIS_NO_TALL_TILES));
+  auto plan = [&](NetPlan* net, bool join) {
+    return build_plan(*dnn, G->flags & DARIS_KEEP_ACTIVATIONS, !(G->flags & DARIS_NO_PAIR), !(G->flags & DARIS_NO_FUSED_INGEST), !(G->flags & DARIS_NO_STAGED_ROWS), !(G->flags & DARIS_NO_SMALL_TILES), !(G->flags & DARIS_NO_FUSED_DW), G->plan_cus, net, !(G->flags & DARIS_NO_TALL_TILES), join);
+  };
+  std::string err = plan(&T->net, true);
+  // What layers in a joint launch read lives until that launch, so their plan may take a buffer more.  A network that fits the static scratch only without joins
+  // has none.
+  if (err.empty() && static_layout(T->net, nullptr, nullptr, nullptr) > (size_t)DARIS_STATIC_SCRATCH_BYTES) {
+    NetPlan apart;
+    if (plan(&apart, false).empty() && static_layout(apart, nullptr, nullptr, nullptr) <= (size_t)DARIS_STATIC_SCRATCH_BYTES) T->net = std::move(apart);
+  }
   if (!err.empty()) return fail(DARIS_EINVAL, "%s", err.c_str());
   if (!G->nodev) {
     NetPlan& net = T->net;

@@ -32,7 +32,7 @@ static void split_bf16(float f, uint16_t out[3]) {
 }
 
 std::string build_plan(const daris_dnn& dnn, bool keep_activations, bool pair_launches, bool fuse_ingest, bool staged_rows, bool small_tiles, bool fuse_dw,
-                       int plan_cus, NetPlan* out, bool tall_tiles) {
+                       int plan_cus, NetPlan* out, bool tall_tiles, bool join) {
   NetPlan& net = *out;
   net = NetPlan();
   if (dnn.n_layers < 1 || !dnn.layers) return "DNN has no layers";
@@ -215,7 +215,7 @@ std::string build_plan(const daris_dnn& dnn, bool keep_activations, bool pair_la
     L.tall = tall_tiles && tall_takes(L.cp, L.out.H * L.out.W, plan_cus) && rows_taken(L);
   }
   // layers that join the one in front, which nobody else reads
-  for (int l = 0; l + 1 < n && !keep_activations; ++l) {
+  for (int l = 0; l + 1 < n && !keep_activations && join; ++l) {
     LayerPlan& A = net.layers[l];
     LayerPlan& B = net.layers[l + 1];
     if (A.d.op != DARIS_OP_CONV || A.depthwise || A.pair_with >= 0 || B.in_t != l + 1 || B.pair_with >= 0) continue;
@@ -235,7 +235,7 @@ std::string build_plan(const daris_dnn& dnn, bool keep_activations, bool pair_la
     }
   }
   // convolution, global average pooling and FC layer, which nobody else reads
-  for (int l = 0; l + 2 < n && !keep_activations && pair_launches; ++l) {
+  for (int l = 0; l + 2 < n && !keep_activations && pair_launches && join; ++l) {
     LayerPlan& A = net.layers[l];
     LayerPlan& B = net.layers[l + 1];
     LayerPlan& C = net.layers[l + 2];
@@ -252,7 +252,7 @@ std::string build_plan(const daris_dnn& dnn, bool keep_activations, bool pair_la
     B.kernel_id = A.kernel_id;
   }
   // a 3x3 convolution, the 1x1 that alone reads it, and the 1x1 behind that
-  for (int l = 0; l + 1 < n && !keep_activations && pair_launches && staged_rows; ++l) {
+  for (int l = 0; l + 1 < n && !keep_activations && pair_launches && staged_rows && join; ++l) {
     LayerPlan& A = net.layers[l];
     LayerPlan& B = net.layers[l + 1];
     auto plain = [&](const LayerPlan& L) { return L.d.op == DARIS_OP_CONV && !L.depthwise && L.pair_with < 0 && L.joins < 0 && L.can_join < 0 && !L.sums_pixels && rows_taken(L); };
