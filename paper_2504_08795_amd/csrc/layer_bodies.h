@@ -1567,8 +1567,9 @@ __device__ __forceinline__ void conv_expand_dw_body(const ExpandDwArgs& p, const
 // Both 1x1 convolutions need nothing but the pixels of the tile, so the workgroup that owns a tile of the 3x3 convolution (32 pixels, all of its 64
 // channels: conv_taps_body) leaves it in LDS and goes on: the first 1x1 (kChainWide channels) takes its residual, is stored and stays in LDS, and
 // the second (up to 64 channels) reads it there.  Bound by the launch and its chain of waits like the launches that it takes the place of; the weights and
-// the residual of each are requested before the one in front is finished, so that nothing of them is waited for.  ResNet-50's first group, five launches fewer:
-// frame in bf16 on 128 CUs 202.2 -> 198.2 us, six tasks saturated 7243 -> 7089, the mixed set (fp32) 10410 -> 10117.
+// the residual of each are requested before the one in front is finished, so that nothing of them is waited for.  us of the launches by themselves / of one, 3136 pixels on
+// 128 CUs: bf16 with both 1x1 8.7 / 5.6, with the first 6.0 / 5.0; fp32 14.0 / 10.4 and 10.0 / 9.0.  ResNet-50's first group, five launches fewer: frame in bf16
+// 202.2 -> 193.1, six tasks saturated 7243 -> 7003, the mixed set (fp32) 10410 -> 10117.
 // The sums have the order that launches of their own have: of the first 1x1 two halves of K, each in an accumulator, of the second as many slices as
 // waves.  The first has weights and pixels in each other's place in the matrix instruction: a lane then holds four channels in a row of its pixel.
 template <bool BF16, int NW>
