@@ -482,6 +482,16 @@ hipError_t build_variants(TaskRt& T, const void* in_base, int n_in, size_t in_st
   return hipSuccess;
 }
 
+// ... for the buffers of T's I/O pool, from the launches that T has now.
+daris_status build_pool(TaskRt& T) {
+  free_variants(&T.pool);
+  if (T.n_inputs < 1 || (int64_t)T.n_inputs + T.n_slots > (1 << 20)) return DARIS_OK;
+  const NetPlan& n = T.net;
+  hipError_t e = build_variants(T, T.pool_in, T.n_inputs, (size_t)n.in_c * n.in_h * n.in_w * sizeof(float), T.pool_out, T.n_slots, (size_t)n.n_out * sizeof(float), &T.pool);
+  if (e != hipSuccess) return fail(e == hipErrorOutOfMemory ? DARIS_ENOMEM : DARIS_EHIP, "argument blocks of the I/O pool: %s", hipGetErrorString(e));
+  return DARIS_OK;
+}
+
 struct EnqueueOpts {
   hsa_signal_t done{0};   // completes with the last launch
   hsa_signal_t first{0};  // completes with the first launch (ignored when that launch carries `done`, or when sampling)
@@ -1111,6 +1121,9 @@ daris_status daris_split_stages(daris_task t, int k) {
     TaskRt& T = *G->tasks[t];
     const std::string err = build_launches(T);
     if (!err.empty()) return fail(DARIS_EHIP, "%s", err.c_str());
+    // the blocks of an I/O pool that is there already are copies of the launches before: of another kernel's arguments, where the first layers joined or parted
+    st = build_pool(T);
+    if (st != DARIS_OK) return st;
   }
   G->core.set_stage_count(t, k);
   G->tasks[t]->vt.clear();
@@ -1309,13 +1322,7 @@ daris_status daris_task_set_io(daris_task t, const void* d_inputs, int32_t n_inp
     HIP_TRY(hipDeviceSynchronize());
     T.pool_in_elsewhere = !on_own_device(d_inputs);
     // argument blocks for every buffer of the two pools, so that a release writes nothing but packets
-    free_variants(&T.pool);
-    if ((int64_t)n_inputs + n_slots <= (1 << 20)) {
-      const NetPlan& n = T.net;
-      hipError_t e = build_variants(T, d_inputs, n_inputs, (size_t)n.in_c * n.in_h * n.in_w * sizeof(float), d_logits, n_slots,
-                                    (size_t)n.n_out * sizeof(float), &T.pool);
-      if (e != hipSuccess) return fail(e == hipErrorOutOfMemory ? DARIS_ENOMEM : DARIS_EHIP, "argument blocks of the I/O pool: %s", hipGetErrorString(e));
-    }
+    return build_pool(T);
   }
   return DARIS_OK;
 }

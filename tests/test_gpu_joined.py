@@ -227,3 +227,24 @@ def test_uneven_shares_of_k(shape):
         assert "taps" in D.daris_kernel_name(D.daris_get_launch_plan(g.task, 0)["kernel_id"])
         e_max, e_l2 = rel_err(g.forward(x), oracle_logits(layers, weights, x, "fp32"))
     assert e_max <= 2e-6 and e_l2 <= 1e-6, (e_max, e_l2)            # a group too many or too few is an error of the order of a sum
+
+
+@pytest.mark.parametrize("first,then", [(1, 4), (4, 1)])
+def test_stages_chosen_behind_the_io_pool(first, then):
+    """The argument blocks of a pool are those of the launches that run: a cut that parts or joins the first layers gives the pool new ones."""
+    layers = [N.Layer(op=N.OP_CONV, c_in=3, c_out=64, k=7, stride=2, pad=3, act=1, in_from=-1, has_bn=False), N.Layer(op=N.OP_MAXPOOL, c_in=64, c_out=64, k=3, stride=2, pad=1, in_from=0),
+              N.Layer(op=N.OP_GAVGPOOL, c_in=64, c_out=64, in_from=1), N.Layer(op=N.OP_FC, c_in=64, c_out=10, in_from=2)]
+    x = torch.from_numpy(wl.make_inputs((3, 96, 100), 3, 3, "normal")).cuda()
+    with GpuNet(layers, wl.make_weights(layers, 3), (3, 96, 100), "fp32", k=first, plan_cus=64) as g:
+        want, got = torch.zeros((3, 10), device="cuda"), torch.zeros((3, 10), device="cuda")
+        D.daris_task_set_io(g.task, x, 3, got, 3)
+        D.daris_split_stages(g.task, then)
+        joined = "image_pool" in D.daris_kernel_name(D.daris_get_launch_plan(g.task, 1)["kernel_id"])
+        assert joined == (1 not in D.daris_get_stage_cuts(g.task)) == (then == 1)
+        D.daris_commit()
+        D.daris_run_closed_loop([3])
+        for i in range(3):
+            D.daris_forward(g.task, x[i], want[i], g.parts[0])
+        torch.cuda.synchronize()
+    assert want.abs().min() > 0
+    np.testing.assert_array_equal(got.cpu().numpy(), want.cpu().numpy())
