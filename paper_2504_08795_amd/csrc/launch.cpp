@@ -647,12 +647,22 @@ static bool expand_bands(int H, int W, int c_stride, int dw_stride, int nominal_
   return true;
 }
 
+// 16-pixel tiles of a band.
+static int expand_tiles(int H, int W, int dw_stride, int band) { return cdiv(std::min((band - 1) * dw_stride + 3, H) * W, 16); }
+
 bool plan_expand_dw(ConvPlan* pl, int H, int W, int cin_stride, int c_stride, int Kpad, int dw_stride, int nominal_cus, int bf16) {
   int band, bands;
   if (Kpad != cin_stride || Kpad % 32 || Kpad / 32 > kExpandChunks || c_stride % 16 || (uint64_t)H * W * std::max(cin_stride, c_stride) * 4 >= (1ull << 31) ||
       (uint64_t)H * W * W >= (1ull << 32) || !expand_bands(H, W, c_stride, dw_stride, nominal_cus, &band, &bands) || (uint64_t)bands * bands * (c_stride / 16) >= (1ull << 32))
     return false;
-  const ConvPlan own = plan_conv_wave16(H * W, c_stride, Kpad, bf16, std::min(std::max(nominal_cus, 8), 256), false, 0, 2);
+  // A workgroup computes all pixels of its band with eight waves at most, and the rows between bands twice, so that the joint launch wins while it is short.  Chunks of 32 k
+  // that a CU takes through the matrix pipe (bf16, whose products take no time: tiles), over 260 random layers in fp32 and 260 in bf16 (K of 32 to 160, maps of 5 to 60 a
+  // side, 32 to 256 CUs), us of the joint launch less those of the two: up to 24 (12) -1.7 to 1.3 (-2.1 to 1.3) and more than 0.6, what a launch costs in the chain of a
+  // frame beside its own time, in 6 of 151 (2 of 175); above, up to 114 (28): 160 x 960 at 29 x 55 on 40 CUs 176.0 against 61.2.  MobileNetV2's frame at 307 x 240 on 40 CUs
+  // joined everywhere 364, by this rule 320, with no expansion joined 326.
+  const int cus = std::min(std::max(nominal_cus, 8), 256), tiles = expand_tiles(H, W, dw_stride, band);
+  if ((int64_t)tiles * (bf16 ? 1 : Kpad / 32) * bands * (c_stride / 16) > (int64_t)(bf16 ? 12 : 24) * cus) return false;
+  const ConvPlan own = plan_conv_wave16(H * W, c_stride, Kpad, bf16, cus, false, 0, 2);
   if (own.kernel == K_NONE) return false;
   *pl = own;
   return true;
@@ -670,7 +680,7 @@ bool encode_expand_dw(const JoinedTable& kt, const ConvPlan& pl, const ConvArgs&
   if (!expand_bands(a.H, a.W, a.Cout, d.stride, nominal_cus, &e.band, &e.bands)) return false;
   e.mg_bands = div_magic((uint32_t)e.bands); e.mg_w = div_magic((uint32_t)e.W); e.mg_wo = div_magic((uint32_t)e.Wo);
   // a wave for every tile, and a thread for every four channels of an output pixel (a second round of either takes as long as the first)
-  const int tiles = cdiv(std::min((e.band - 1) * d.stride + 3, a.H) * a.W, 16), chunks = a.Kpad / 32;
+  const int tiles = expand_tiles(a.H, a.W, d.stride, e.band), chunks = a.Kpad / 32;
   e.threads = 64 * std::min(std::max(std::max(tiles, cdiv(std::min(e.band, e.Ho) * e.Wo * 4, 64)), 2), 8);
   return push(out, kt.expand_dw[bf16][chunks - 1], bf16 ? K_EXPAND_DW_BF16 : K_EXPAND_DW_F32, (uint32_t)(e.bands * (a.Cout / 16)), (uint32_t)e.threads, &e, sizeof(e));
 }

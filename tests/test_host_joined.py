@@ -98,3 +98,22 @@ def test_joins_do_not_cost_a_network_the_static_scratch():
     for side, buffers in (((160, 160), 3), ((160, 193), 2), ((194, 160), 2), ((224, 224), 3)):   # small enough either way, only without joins, and neither
         layers, shp = cases._net("vgg16", *side)
         assert len({v for p in _plans(layers, shp, "fp32") for v in (p["out_slot"], p["in_slot"])} - {-1}) == buffers, side
+
+
+# (c_in, h, w, channels, stride of the depthwise layer, plan CUs), joined in (fp32, bf16): what a CU has to compute decides
+EXPANSIONS = [((32, 28, 28, 192, 1, 128), (True, True)), ((96, 14, 14, 576, 1, 128), (True, True)), ((160, 7, 7, 960, 1, 128), (True, True)), ((160, 10, 10, 960, 1, 128), (True, True)),
+              ((160, 10, 10, 960, 1, 120), (False, True)), ((96, 14, 14, 576, 1, 64), (True, True)), ((32, 28, 28, 192, 1, 64), (True, False)), ((64, 15, 20, 384, 1, 40), (False, False)),
+              ((96, 15, 20, 576, 1, 40), (False, False)), ((160, 29, 55, 960, 1, 40), (False, False))]
+
+
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("shape,want", EXPANSIONS)
+def test_expansions_join_their_depthwise_layer_while_the_launch_is_short(shape, want, dtype):
+    cin, h, w, cout, s, cus = shape
+    layers = [N.Layer(op=N.OP_CONV, c_in=cin, c_out=cout, k=1, act=2, in_from=-1), N.Layer(op=N.OP_CONV, c_in=cout, c_out=cout, k=3, stride=s, pad=1, groups=cout, act=2, in_from=0)]
+    p = _plans(layers, (cin, h, w), dtype, cus=cus)
+    joined = "expand_dw" in D.daris_kernel_name(p[1]["kernel_id"])
+    assert joined == want[dtype == "bf16"] == (p[0]["out_slot"] == -1)
+    if not joined:                                                      # the convolution by itself, with the plan that it has without a depthwise layer behind it
+        own = _plans(layers[:1], (cin, h, w), dtype, cus=cus)[0]
+        assert all(p[0][k] == own[k] for k in ("kernel_id", "rows", "tn", "nw", "sw")), (p[0], own)
