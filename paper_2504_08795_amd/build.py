@@ -12,7 +12,7 @@ DEVICE_SOURCES = {"kernels.hip": "daris_kernels", "taps_kernels.hip": "daris_tap
                   "point_kernels.hip": "daris_point_kernels"}
 # ... of the kernels that compute several layers in a row
 JOINED_SOURCES = {"joined_kernels.hip": "daris_joined_kernels", "tall_kernels.hip": "daris_tall_kernels", "pointwise_kernels.hip": "daris_pointwise_kernels"}
-HOST_SOURCES = ["aql.cpp", "launch.cpp", "sched_core.cpp", "net_plan.cpp", "daris_api.cpp"]
+HOST_SOURCES = ["aql.cpp", "launch.cpp", "sched_core.cpp", "net_plan.cpp", "net_encode.cpp", "daris_api.cpp"]
 COMMON = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-Wall", "-Wno-unused-function"]
 # no packed fp32 arithmetic in device code (some forms have given wrong results on this hardware)
 DEVICE_FLAGS = COMMON + ["-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "--cuda-device-only", "--no-gpu-bundle-output"]

@@ -27,6 +27,7 @@
 #include "../../include/daris_debug.h"
 #include "aql.h"
 #include "kernels.h"
+#include "net_encode.h"
 #include "net_plan.h"
 #include "sched_core.h"
 #include "static_scratch.h"
@@ -79,21 +80,6 @@ struct JobIo {
   // the block is patched at launch time and travels through the queue's argument ring
   const void* in_args = nullptr;
   const void* out_args = nullptr;
-};
-
-struct LaunchRt {
-  KernelLaunch kl;
-  const void* dev = nullptr;  // the launch's argument block inside the task's device buffer
-  double flops = 0;           // arithmetic of the layer(s) a dense-convolution launch computes, else 0
-};
-
-// A whole network as launches in execution order, encoded at registration; layer l issues launches [layer_lo[l],
-// layer_lo[l + 1]) (none for the earlier member of a launch pair).
-struct LaunchSeq {
-  std::vector<LaunchRt> launches;
-  std::vector<int> layer_lo;
-  int in_launch = -1, out_launch = -1;  // the launches that read the job's input / write its logits
-  uint32_t in_off = 0, out_off = 0;     // byte offset of that pointer inside the argument block
 };
 
 // Argument blocks of the input-reading and the logits-writing launch, one per buffer of a set of I/O buffers.
@@ -225,170 +211,7 @@ KernelTable g_kt;
 JoinedTable g_joined;
 int g_rt_device = -1;
 
-ConvArgs conv_args(TaskRt& T, int l, void* y, const std::vector<void*>& slots, float* ws) {
-  NetPlan& net = T.net;
-  LayerPlan& L = net.layers[l];
-  const TensorInfo& in = net.tensor(L.in_t);
-  ConvArgs a;
-  a.x = slots[in.slot]; a.w = L.w_dev; a.bias = L.b_dev; a.y = y; a.ws = ws; a.wave_prio = (T.prio == DARIS_HP && (G->flags & DARIS_WAVE_PRIORITY)) ? 1 : 0;
-  a.res = L.res_t >= 0 ? slots[net.tensor(L.res_t).slot] : nullptr;
-  a.H = in.H; a.W = in.W; a.Cin = in.Cs; a.Ho = L.out.H; a.Wo = L.out.W; a.Cout = L.out.Cs;
-  a.kh = a.kw = L.d.k; a.stride = L.d.stride; a.pad = L.d.pad;
-  a.Kpad = L.Kpad; a.M = L.out.H * L.out.W; a.act = L.d.act | (L.sums_pixels ? kActSumPixels : 0);
-  a.splitk = L.cp.splitk; a.S = L.cp.S; a.sz = L.cp.sz; a.sw = L.cp.sw;
-  a.MT = L.cp.MT; a.NTn = L.cp.NTn; a.G = L.cp.G; a.xmode = L.cp.xmode;
-  a.mg_wo = div_magic((uint32_t)a.Wo); a.mg_cin = div_magic((uint32_t)a.Cin); a.mg_kw = div_magic((uint32_t)a.kw); a.mg_mt = tile_magic(L.cp.grid_x, a.MT);
-  a.c_real = 0;
-  if (l == 0 && net.fuse_ingest) {  // layer 0 gathers from the job's fp32 [C][H][W] input: the pointer is filled in per job
-    a.x = nullptr;
-    a.c_real = net.in_c;
-  }
-  return a;
-}
-
-// Encodes the whole network of T as launches in execution order, with its activation tensors in `slots` (one device
-// buffer per slot of the plan) and its split-K partial sums in `ws`; the weights must be on the device.  The two pointers
-// that change from job to job (the input of the first launch, the logits of the last) stay null in the argument blocks.
-// Returns "" or an error text.
-std::string encode_network(TaskRt& T, const std::vector<void*>& slots, float* ws, LaunchSeq* seq) {
-  NetPlan& net = T.net;
-  const int n = (int)net.layers.size();
-  const int bf16 = net.bf16;
-  std::vector<KernelLaunch> ks;
-  *seq = LaunchSeq();
-  seq->layer_lo.assign(n + 1, 0);
-  auto take = [&](double flops) {
-    for (size_t i = 0; i < ks.size(); ++i) {
-      LaunchRt r;
-      r.kl = ks[i];
-      r.flops = i == 0 ? flops : 0;
-      seq->launches.push_back(r);
-    }
-    ks.clear();
-  };
-  if (!net.fuse_ingest) {
-    if (!encode_ingest(g_kt, nullptr, slots[net.ingest.slot], net.ingest.C, net.ingest.Cs, net.ingest.H, net.ingest.W, bf16, &ks))
-      return "input conversion launch";
-    seq->in_launch = 0;
-    seq->in_off = kIngestInputOffset;
-    take(0);
-  }
-  for (int l = 0; l < n; ++l) {
-    seq->layer_lo[l] = (int)seq->launches.size();
-    LayerPlan& L = net.layers[l];
-    const TensorInfo& in = net.tensor(L.in_t);
-    const void* x = slots[in.slot];
-    const bool direct = l == n - 1 && net.final_direct;  // writes the job's logits
-    void* y = direct ? nullptr : slots[L.out.slot];
-    bool ok = false;
-    double flops = 0;
-    switch (L.d.op) {
-      case DARIS_OP_CONV:
-        if ((L.depthwise && L.fused_dw) || net.joined_away(l) || net.followed(l)) {
-          ok = true;  // computed inside the next layer's launch
-        } else if (!L.depthwise && (L.joins >= 0 || L.follows >= 0)) {
-          const int wide = L.follows >= 0 ? L.follows : l, first = net.layers[wide].joins;
-          LayerPlan& W = net.layers[wide];
-          const ConvArgs a = conv_args(T, first, nullptr, slots, ws), b = conv_args(T, wide, slots[W.out.slot], slots, ws), c = conv_args(T, l, y, slots, ws);
-          flops = 2.0 * (double)(net.layers[first].macs + W.macs + (wide == l ? 0 : L.macs));
-          ok = encode_chain(g_joined, net.layers[first].cp, a, W.cp, b, wide == l ? nullptr : &L.cp, wide == l ? nullptr : &c, bf16, &ks);
-        } else if (L.depthwise) {
-          DwArgs a = DwArgs();
-          a.x = x; a.w = L.w_dev; a.bias = L.b_dev; a.y = y;
-          a.H = in.H; a.W = in.W; a.C = in.Cs; a.Ho = L.out.H; a.Wo = L.out.W;
-          a.k = L.d.k; a.stride = L.d.stride; a.pad = L.d.pad; a.act = L.d.act;
-          if (L.joins >= 0) {
-            flops = 2.0 * (double)(L.macs + net.layers[L.joins].macs);
-            ok = encode_expand_dw(g_joined, net.layers[L.joins].cp, conv_args(T, L.joins, nullptr, slots, ws), a, net.plan_cus, bf16, &ks);
-          } else {
-            ok = encode_dwconv(g_kt, a, bf16, &ks);
-          }
-        } else if (L.pair_with >= 0 && !L.pair_lead && !L.sums_pixels) {
-          ok = true;  // issued together with the next layer
-        } else {
-          const ConvArgs a = conv_args(T, l, y, slots, ws);
-          flops = 2.0 * (double)L.macs;
-          if (L.fused_dw) {
-            LayerPlan& O = net.layers[L.pair_with];  // the depthwise layer: this launch reads ITS input
-            const TensorInfo& din = net.tensor(O.in_t);
-            ConvArgs b = a;
-            b.x = slots[din.slot];
-            DwFusedArgs d;
-            d.w = O.w_dev; d.bias = O.b_dev; d.H = din.H; d.W = din.W; d.stride = O.d.stride; d.act = O.d.act;
-            flops += 2.0 * (double)O.macs;
-            ok = encode_conv_dw(g_kt, L.cp, b, d, bf16, &ks);
-          } else if (L.pair_with >= 0 && !L.sums_pixels) {
-            LayerPlan& O = net.layers[L.pair_with];
-            const ConvArgs b = conv_args(T, L.pair_with, slots[O.out.slot], slots, ws);
-            flops += 2.0 * (double)O.macs;
-            // the heavier convolution is the first problem (its plan was kept)
-            ok = L.macs >= O.macs ? encode_conv_pair(g_kt, L.cp, a, O.cp, b, bf16, &ks) : encode_conv_pair(g_kt, O.cp, b, L.cp, a, bf16, &ks);
-          } else {
-            if (l == 0 && net.fuse_ingest) {
-              seq->in_launch = (int)seq->launches.size();
-              seq->in_off = kConvInputOffset;
-            }
-            ok = L.tall ? encode_conv_tall(g_joined, L.cp, a, bf16, &ks) : encode_conv(g_kt, L.cp, a, bf16, &ks);
-          }
-        }
-        break;
-      case DARIS_OP_MAXPOOL:
-      case DARIS_OP_GAVGPOOL: {
-        if (L.average_of >= 0) {
-          const LayerPlan& O = net.layers[L.average_of];
-          ok = !L.lonely || encode_pooled_sums(g_kt, (const float*)x, (float*)y, in.Cs, O.cp.MT, in.H * in.W, &ks);
-          break;
-        }
-        PoolArgs a = PoolArgs();
-        a.x = x; a.y = y; a.H = in.H; a.W = in.W; a.C = in.Cs; a.Ho = L.out.H; a.Wo = L.out.W;
-        a.k = L.d.k; a.stride = L.d.stride; a.pad = L.d.pad;
-        if (L.joins >= 0) {  // the convolution in front, which pools its outputs
-          LayerPlan& O = net.layers[L.joins];
-          flops = 2.0 * (double)O.macs;
-          if (L.joins == 0 && net.fuse_ingest) {
-            seq->in_launch = (int)seq->launches.size();
-            seq->in_off = kConvInputOffset;
-          }
-          const ConvArgs conv = conv_args(T, L.joins, nullptr, slots, ws);
-          ok = O.cp.rows == 64 ? encode_block_pool(g_joined, O.cp, conv, a, &ks) : encode_image_pool(g_joined, O.cp, conv, a, bf16, &ks);
-          break;
-        }
-        ok = L.d.op == DARIS_OP_MAXPOOL ? encode_maxpool(g_kt, a, bf16, &ks) : encode_gavgpool(g_kt, a, bf16, &ks);
-        break;
-      }
-      case DARIS_OP_FC: {
-        FcArgs a = FcArgs();
-        a.x = x; a.w = L.w_dev; a.bias = L.b_dev; a.y = y;
-        a.K = L.K; a.N = L.d.c_out; a.Ns = direct ? L.d.c_out : L.out.Cs;
-        a.act = L.d.act; a.out_f32 = direct ? 1 : 0;
-        if (direct) {
-          seq->out_launch = (int)seq->launches.size();
-          seq->out_off = kFcOutputOffset;
-        }
-        if (L.in_t > 0 && net.layers[L.in_t - 1].average_of >= 0) {
-          const LayerPlan& B = net.layers[L.in_t - 1];
-          const LayerPlan& O = net.layers[B.average_of];
-          a.x = B.lonely ? x : slots[O.out.slot];
-          ok = encode_fc_pooled(g_joined, a, B.lonely ? 1 : O.cp.MT, B.lonely ? 1 : O.out.H * O.out.W, bf16, &ks);
-          break;
-        }
-        ok = encode_fc(g_kt, a, bf16, &ks);
-        break;
-      }
-    }
-    if (!ok) return "launch of layer " + std::to_string(l) + " (" + kernel_name(L.kernel_id) + ")";
-    take(flops);
-  }
-  seq->layer_lo[n] = (int)seq->launches.size();
-  if (!net.final_direct) {
-    const TensorInfo& o = net.layers[n - 1].out;
-    if (!encode_egress(g_kt, slots[o.slot], nullptr, o.C, o.Cs, o.H, o.W, bf16, &ks)) return "output conversion launch";
-    seq->out_launch = (int)seq->launches.size();
-    seq->out_off = kEgressOutputOffset;
-    take(0);
-  }
-  return "";
-}
+bool wave_prio(const TaskRt& T) { return T.prio == DARIS_HP && (G->flags & DARIS_WAVE_PRIORITY); }
 
 // Layout of T's network on the static device scratch: the plan's activation slots one after the other, 256 bytes apart at
 // least, then the split-K workspace.  Returns the bytes it takes; slots may be null.
@@ -406,7 +229,7 @@ size_t static_layout(const NetPlan& net, unsigned char* base, std::vector<void*>
 // Encodes T's network on its own buffers and, where it fits, on the static scratch, and uploads the argument blocks into
 // one device buffer; a job brings its own copies of the two job-dependent blocks (JobIo).  Returns "" or an error text.
 std::string build_launches(TaskRt& T) {
-  std::string err = encode_network(T, T.slots, T.ws, &T.seq);
+  std::string err = encode_network(T.net, wave_prio(T), g_kt, g_joined, T.slots, T.ws, &T.seq);
   if (!err.empty()) return err;
   T.static_seq = LaunchSeq();
   unsigned char* base = static_cast<unsigned char*>(static_scratch_ptr(G->device));
@@ -414,7 +237,7 @@ std::string build_launches(TaskRt& T) {
     std::vector<void*> slots;
     float* ws = nullptr;
     static_layout(T.net, base, &slots, &ws);
-    err = encode_network(T, slots, ws, &T.static_seq);
+    err = encode_network(T.net, wave_prio(T), g_kt, g_joined, slots, ws, &T.static_seq);
     if (!err.empty()) return err;
   }
   // one device buffer for all argument blocks, 64 bytes apart at least

@@ -30,7 +30,7 @@ SAN = ["-Xarch_host", "-fsanitize=address", "-Xarch_host", "-fsanitize=undefined
 @pytest.fixture(scope="module")
 def driver():
     """Builds the sanitized executable (about a minute; reused while it is newer than every source)."""
-    srcs = [os.path.join(CSRC, f) for f in ("aql.cpp", "launch.cpp", "sched_core.cpp", "net_plan.cpp", "daris_api.cpp")] + \
+    srcs = [os.path.join(CSRC, f) for f in ("aql.cpp", "launch.cpp", "sched_core.cpp", "net_plan.cpp", "net_encode.cpp", "daris_api.cpp")] + \
            [os.path.join(HERE, "host_sanitize", "driver.cpp")]
     deps = srcs + [os.path.join(CSRC, f) for f in os.listdir(CSRC) if f.endswith(".h")] + [os.path.join(ROOT, "include", "daris.h")]
     blob, scratch = os.path.join(CSRC, "kernels_blob.o"), os.path.join(CSRC, "static_scratch.hip.o")
