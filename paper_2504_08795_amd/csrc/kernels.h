@@ -299,14 +299,16 @@ struct JoinedTable {
   const AqlKernel* fc_pooled[2] = {};
   const AqlKernel* chain[2] = {};
   const AqlKernel* block_pool[3] = {};  // [log2(nw) - 1]
-  const AqlKernel* tall[2][3] = {};     // [bf16][log2(nw) - 1]
+  const AqlKernel* tall[2] = {};
   std::string resolve(const AqlRuntime& rt);  // as KernelTable::resolve
 };
 
 // Dense convolution: the main kernel, then the split-K reduction if the plan has one.  False on an inconsistent plan.
 bool encode_conv(const KernelTable& kt, const ConvPlan& pl, const ConvArgs& a, int bf16, std::vector<KernelLaunch>* out);
 // A plan of 16-pixel tiles with three taps per fetch and two blocks of channels to a wave, run with two blocks of pixels in place of them (conv_taps_body,
-// TM = 2): the same K slices, hence the same sums.  Whether it should be (not where it would take more rounds of the CUs), and the launch.
+// TM = 2): the same K slices, hence the same sums.  Whether it should be, and the launch.  Not where it would take more rounds of the CUs, nor with four waves (bf16 with
+// K below 2048), whose loop is short: us with blocks of channels / of pixels, 450 x 256 x 1152 on 256 CUs 2.83 / 2.97, 252 x 128 x 1728 on 64 2.95 / 3.23, 210 x 512 x 1728 on
+// 256 3.13 / 3.34; with eight, 374 x 64 x 2304 on 64 3.43 / 3.35, 84 x 512 x 4608 on 128 4.62 / 4.36.
 bool tall_takes(const ConvPlan& pl, int M, int nominal_cus);
 bool encode_conv_tall(const JoinedTable& kt, const ConvPlan& pl, const ConvArgs& a, int bf16, std::vector<KernelLaunch>* out);
 // Two independent convolutions in one launch: pl0/a0 as planned by plan_conv, pl1/a1 by plan_conv_like(pl0, ...).

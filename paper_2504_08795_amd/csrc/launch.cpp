@@ -386,8 +386,7 @@ std::string JoinedTable::resolve(const AqlRuntime& rt) {
   for (int b = 0; b < 2; ++b) {
     const std::string B = b ? "true" : "false";
     image_pool[b] = get("daris::conv_image_pool_kernel<" + B + ">", sizeof(ImageConvArgs));
-    for (int v = 0; v < 3; ++v)  // the variants that taps_kernel has with two blocks
-      if (taps_kernel(16, b, 2, 2 << v) != K_NONE) tall[b][v] = get("daris::conv_taps16_tall_kernel<" + B + ", " + std::to_string(2 << v) + ">", sizeof(ConvArgs));
+    tall[b] = get("daris::conv_taps16_tall_kernel<" + B + ">", sizeof(ConvArgs));
     for (int v = 0; v < 3; ++v) block_pool[v] = get("daris::conv_block_pool_kernel<" + std::to_string(2 << v) + ">", sizeof(ConvArgs));
     chain[b] = get("daris::conv_chain_kernel<" + B + ", " + (b ? "4" : "8") + ">", sizeof(ChainLaunchArgs));
     fc_pooled[b] = get("daris::fc_pooled_kernel<" + B + ">", sizeof(FcPooledArgs));
@@ -564,13 +563,13 @@ bool encode_conv(const KernelTable& kt, const ConvPlan& pl, const ConvArgs& a, i
 }
 
 bool tall_takes(const ConvPlan& pl, int M, int nominal_cus) {
-  if (pl.gather != kGatherTaps || pl.tn != 2 || pl.rows != 16 || pl.splitk != 1) return false;
+  if (pl.gather != kGatherTaps || pl.tn != 2 || pl.nw != 8 || pl.rows != 16 || pl.splitk != 1) return false;
   const int cus = std::min(std::max(nominal_cus, 8), 256);
   return cdiv(cdiv(M, 32) * pl.NTn * 2, cus) <= cdiv(pl.tiles, cus);
 }
 
 bool encode_conv_tall(const JoinedTable& kt, const ConvPlan& pl, const ConvArgs& layer, int bf16, std::vector<KernelLaunch>* out) {
-  if (pl.gather != kGatherTaps || pl.tn != 2 || pl.rows != 16 || pl.splitk != 1 || pl.threads != 64 * pl.nw || pl.kernel != conv_kernel(16, bf16, 2, pl.nw, true) || !taps_agree(pl, layer) ||
+  if (pl.gather != kGatherTaps || pl.tn != 2 || pl.nw != 8 || pl.rows != 16 || pl.splitk != 1 || pl.threads != 64 * pl.nw || pl.kernel != conv_kernel(16, bf16, 2, pl.nw, true) || !taps_agree(pl, layer) ||
       !rows_take(layer, bf16) || pl.S * (bf16 ? 32 : 16) != layer.Kpad)
     return false;
   ConvArgs a = layer;
@@ -578,7 +577,7 @@ bool encode_conv_tall(const JoinedTable& kt, const ConvPlan& pl, const ConvArgs&
   a.NTn = a.G = pl.NTn * 2;
   const uint32_t groups = tile_order(a.MT, a.G, &a.xmode);
   a.mg_mt = tile_magic(groups, a.MT);
-  return push(out, kt.tall[bf16][variant_of(2, pl.nw) - 3], pl.kernel, groups, (uint32_t)pl.threads, &a, sizeof(a));
+  return push(out, kt.tall[bf16], pl.kernel, groups, (uint32_t)pl.threads, &a, sizeof(a));
 }
 
 bool conv_dw_fusable(const ConvPlan& pl, int bf16) {

@@ -7,19 +7,18 @@
 
 namespace daris {
 
-template <bool BF16, int NW>
-__global__ __launch_bounds__(NW * 64, NW == 8 ? 4 : 1) void conv_taps16_tall_kernel(const ConvArgs) {
+template <bool BF16>
+__global__ __launch_bounds__(512, 4) void conv_taps16_tall_kernel(const ConvArgs) {
   const ConvArgs p = conv_args_at((ConstPtr)__builtin_amdgcn_kernarg_segment_ptr());
-  __shared__ __align__(16) float red[conv_taps_lds<BF16, 16, 1, NW, 2>()];
+  __shared__ __align__(16) float red[conv_taps_lds<BF16, 16, 1, 8, 2>()];
   int mt, g;
   if (!conv_tile_of(p, (int)blockIdx.x, &mt, &g)) return;
-  conv_taps_body<BF16, 16, 1, NW, false, 2>(p, mt, g, red);
+  conv_taps_body<BF16, 16, 1, 8, false, 2>(p, mt, g, red);
   puts_done();
 }
 
-// for the plans of conv_taps16_kernel<., 2, .>
-template __global__ void conv_taps16_tall_kernel<false, 8>(const ConvArgs);
-template __global__ void conv_taps16_tall_kernel<true, 4>(const ConvArgs);
-template __global__ void conv_taps16_tall_kernel<true, 8>(const ConvArgs);
+// for the plans of conv_taps16_kernel<., 2, 8>
+template __global__ void conv_taps16_tall_kernel<false>(const ConvArgs);
+template __global__ void conv_taps16_tall_kernel<true>(const ConvArgs);
 
 }  // namespace daris

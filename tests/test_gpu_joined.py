@@ -160,7 +160,7 @@ def test_infinite_averages_stay_infinite():
 
 
 # c_in, h, w, c_out, plan CUs: tiles of 16 pixels and two blocks of channels whose second block of pixels is whole, ragged, of one pixel or empty, images narrower than
-# a block, a single row; four waves (bf16, K = 1152) and eight
+# a block, a single row; eight waves (the second layer of the last in bf16, K = 1152: four, which keep two blocks of channels)
 TALL = [(256, 14, 14, 256, 128), (256, 7, 7, 512, 64), (512, 7, 7, 512, 64), (256, 1, 49, 256, 32), (256, 1, 33, 256, 32), (256, 16, 15, 128, 64)]
 
 
