@@ -66,10 +66,13 @@ static uint32_t tile_order(int MT, int G, int* xmode) {
 // several, they fill it by themselves, and fewer waves have fewer partial tiles to sum and less LDS each.  us with eight waves / four, fp32: 3136 x 64
 // x 576 on 96 CUs (196 tiles) 7.6 / 6.3, 784 x 128 x 512 on 96 (100) 5.5 / 5.0, 784 x 128 x 1152 on 48 12.4 / 11.6, 1520 x 256 x 512 on 160 8.0 / 7.4, 6000 x 64 x
 // 256 on 160 6.0 / 5.0, 196 x 256 x 1024 on 48 8.05 / 7.35.  bf16 with four / two: 3136 x 64 x 576 on 32 CUs (98 tiles) 5.45 / 4.95, 3136 x 256 x 1152 on 128 (392)
-// 8.3 / 7.6, 784 x 512 x 4608 on 64 (200) 22.9 / 22.2, but on 32 38.4 / 39.4; with fewer tiles 784 x 256 x 512 beside 196 x 1024 x 512 on 128 (212) 4.2 / 4.5.
-static int fewer_waves(int tiles, int cus, int bf16, int nw) {
-  if (!bf16) return tiles > cus ? std::min(nw, 4) : nw;
-  return 2 * tiles > 5 * cus && tiles < 6 * cus ? std::min(nw, 2) : nw;
+// 8.3 / 7.6, 1364 x 512 x 1152 on 80 11.3 / 10.7; with fewer tiles 784 x 256 x 512 beside 196 x 1024 x 512 on 128 (212) 4.2 / 4.5; with K so long that the partial tiles are
+// no matter 1363 x 512 x 2304 on 128 11.2 / 11.4, 840 x 512 x 4608 on 40 38.2 / 39.3 (and 204 x 512 x 4608 on 40 14.6 / 14.2, the most that K of 2304 and more gains).
+// In fp32 they are no matter for tiles one block of channels wide without three taps per fetch: 256 x 1024 x 4608 beside 256 x 1024 x 512 on 96 (256 and 256 tiles) 46.2 / 50.5, but with
+// three taps per fetch 385 x 256 x 4608 on 48 49.0 / 39.5, and two blocks wide 300 x 1024 x 4608 beside 300 x 1024 x 512 on 48 166 / 124.
+static int fewer_waves(int tiles, int cus, int bf16, int nw, int S, int tn, bool three_taps) {
+  if (!bf16) return tiles > cus && (tn == 2 || three_taps || S <= 36 * nw) ? std::min(nw, 4) : nw;
+  return 2 * tiles > 5 * cus && tiles < 6 * cus && S < 36 * nw ? std::min(nw, 2) : nw;
 }
 
 static ConvPlan plan_conv_wave(int M, int N, int Kpad, int bf16, int step_align, int nominal_cus, bool allow_block, ThreeTaps three_taps, int force_tn = 0, int force_nw = 0) {
@@ -103,7 +106,7 @@ static ConvPlan plan_conv_wave(int M, int N, int Kpad, int bf16, int step_align,
   const int tiles = (block ? cdiv(M, 64) : cdiv(M, 32)) * (nb / tn);
   int nw = bf16 ? 4 : 8;  // bf16 steps are short: fewer waves to sum through LDS beat a finer K split (measured 0.4-0.8 us per layer)
   while (nw > 2 && (S / nw < 4 || tiles * nw > 8 * kNominalWaveSlots)) nw /= 2;  // >= 4 steps per wave, <= 8 waves per SIMD
-  nw = fewer_waves(tiles, nominal_cus, bf16, nw);
+  nw = fewer_waves(tiles, nominal_cus, bf16, nw, S, tn, three_taps != kNoTaps);
   // ... whose workgroups are the smaller the more of them a CU gets: 104 tiles on 128 CUs 41 us with 8 waves, 51 with 4 (784 x
   // 512 x 4608); 196 tiles 46, 43 and, with 2 waves, 72 (3136 x 256 x 2304); 392 tiles 56, 47 and 43 (12544 x 128 x 1152)
   if (block) nw = tiles > nominal_cus * 5 / 2 ? 2 : tiles > nominal_cus * 3 / 2 ? 4 : 8;
@@ -247,7 +250,10 @@ ConvPlan plan_conv(int M, int N, int Kpad, int bf16, int step_align, int cin_str
 ConvPlan plan_conv_beside(const ConvPlan& own, const ConvPlan& light, int M, int N, int Kpad, int bf16, int step_align, int nominal_cus) {
   const int cus = std::min(std::max(nominal_cus, 8), 256);
   if (own.rows != 32 || own.splitk != 1 || own.gather == kGatherTaps || light.kernel == K_NONE) return own;
-  const int nw = fewer_waves(own.tiles + (int)((int64_t)light.tiles * std::min(light.S, own.S) / own.S), cus, bf16, own.nw);
+  // The tiles of a lighter one with a short K do not count: they are gone early and leave a CU to the few waves of one heavy tile.  us, fp32 with eight waves / four: 232 x 512 x
+  // 2304 beside 232 x 512 x 256 on 128 CUs (128 tiles and 128) 9.9 / 12.4, 102 x 256 x 1152 beside 102 x 256 x 128 on 32 (32 and 32) 6.1 / 7.1.  (What loses all the same:
+  // some of K = 2304 with 2.3 to 2.5 tiles a CU, 300 x 512 x 2304 on 64 CUs 19.9 / 21.0; most of them gain 4 to 20 %.)
+  const int nw = fewer_waves(own.tiles + (2 * light.S >= own.S ? (int)((int64_t)light.tiles * std::min(light.S, own.S) / own.S) : 0), cus, bf16, own.nw, own.S, own.tn, false);
   return nw == own.nw ? own : plan_conv_wave(M, N, Kpad, bf16, step_align, cus, false, kNoTaps, own.tn, nw);
 }
 

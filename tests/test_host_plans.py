@@ -156,6 +156,26 @@ def test_single_channel_tiles_on_16_or_32_pixels(plans):
         assert p[0] == 1 and p[2] == rows, (s, p)
 
 
+# (dtype, c_in, h, w, c_out, k, stride, pad, plan CUs[, c_out, k, stride, pad of one that shares the launch]), waves of a workgroup: fewer where a CU has several tiles,
+# but not beside a lighter one that is soon done, nor where K is long
+FEWER_WAVES = [
+    ((0, 512, 28, 28, 256, 1, 1, 0, 128, 1024, 1, 2, 0), 4),
+    ((0, 256, 57, 16, 512, 3, 2, 1, 128, 512, 1, 2, 0), 8),       # 128 tiles, and 128 of a ninth of K
+    ((0, 512, 16, 6, 1024, 3, 2, 1, 32, 1024, 1, 2, 0), 8),
+    ((0, 256, 64, 20, 512, 3, 2, 1, 128, 512, 1, 2, 0), 4),       # 160
+    ((0, 512, 32, 32, 1024, 3, 2, 1, 96, 1024, 1, 2, 0), 8),      # 256 of a long K
+    ((0, 64, 44, 44, 64, 3, 1, 1, 48, 0, 1, 1, 0), 4),
+    ((1, 128, 28, 35, 256, 3, 1, 1, 48, 0, 1, 1, 0), 2),
+    ((1, 256, 29, 47, 512, 3, 1, 1, 128, 0, 1, 1, 0), 4),         # K = 2304
+    ((1, 512, 21, 40, 512, 3, 1, 1, 40, 0, 1, 1, 0), 4),
+]
+
+
+def test_waves_of_a_workgroup(plans):
+    for (s, waves), p in zip(FEWER_WAVES, plans([s for s, _ in FEWER_WAVES])):
+        assert p[0] == 1 and p[5] == (s[9] > 0) and p[3] == 64 * waves, (s, waves, p)
+
+
 def test_every_joint_launch_can_be_encoded(plans):
     """Two convolutions that read the same tensor: whatever the planner joins, the encoder takes."""
     rng = np.random.default_rng(18)
