@@ -1035,17 +1035,17 @@ __device__ __forceinline__ void conv_rows_body(const ConvArgs& p, const int mt, 
 // pixels, 21 (15) for two of channels.  Every sum has the same terms in the same order.  us with two blocks of channels / of pixels: fp32 196 x 256 x 2304 on
 // 128 CUs 6.65 / 6.33, 48 x 512 x 4608 on 64 CUs 10.3 / 9.6, bf16 196 x 256 x 2304 3.56 / 3.48.  With R = 32 the loop is shorter and more rows to split in
 // front of it cost what fewer loads give: 3136 x 64 x 576 fp32 5.7 / 5.8, bf16 3.1 / 3.3.
-// A wave's share of K = steps [s0, s1) where a fetch serves three taps: groups of six steps, `most` at most, the first waves that many and the last ones a group
-// less where it does not come out even.  Waves w and w + 4 run on one SIMD, so twelve groups on eight waves are three to a SIMD; shares of two as long as there are
-// any were four on two SIMDs and two on the others (fp32 on 128 CUs, 3136 x 64 x 576 5.75 -> 5.25 us; on 64 in 64-pixel tiles 9.9 -> 9.2).  bf16 has
-// shares of `most`, or what is left: its four waves have a SIMD each, and the launch is 0.06 us longer this way.
+// A wave's share of K = steps [s0, s1) where a fetch serves three taps: groups of six steps, `most` at most, each wave that many as long as there are any.
+// Waves w and w + 4 run on one SIMD, so that twelve groups on eight waves were four on two SIMDs and two on the others: where that spares a SIMD a group, the
+// first waves have `most` and the last ones a group less (fp32 on 128 CUs, 3136 x 64 x 576 5.75 -> 5.25 us; on 64 in 64-pixel tiles 9.9 -> 9.2).  Elsewhere all that more waves
+// have is their start: nine groups, three on the busiest SIMD either way, 161 x 64 x 864 on 160 CUs 3.29 -> 3.47.  bf16's four waves have a SIMD each.
 template <bool BF16, int NW>
 __device__ __forceinline__ void tap_slice(const int s0, const int s1, const int most, const int wave, int* const begin, int* const steps) {
   *begin = min(s0 + wave * most, s1);
   *steps = min(*begin + most, s1) - *begin;
-  if constexpr (!BF16) {
+  if constexpr (!BF16 && NW == 8) {
     const int lack = NW * most - (s1 - s0), less = 6 * (wave - NW) + lack;
-    if (lack < 6 * NW) {  // (a workgroup that has the rest of K split across workgroups may have less)
+    if (lack >= 24 && lack <= min(3 * most, 42)) {  // four to seven groups, and the fifth wave would have `most` (a workgroup that has the rest of K split across workgroups may lack more)
       *begin = s0 + wave * most - max(less, 0);
       *steps = most - (less >= 0 ? 6 : 0);
     }
