@@ -307,8 +307,9 @@ struct JoinedTable {
 bool encode_conv(const KernelTable& kt, const ConvPlan& pl, const ConvArgs& a, int bf16, std::vector<KernelLaunch>* out);
 // A plan of 16-pixel tiles with three taps per fetch and two blocks of channels to a wave, run with two blocks of pixels in place of them (conv_taps_body,
 // TM = 2): the same K slices, hence the same sums.  Whether it should be, and the launch.  Not where it would take more rounds of the CUs, nor with four waves (bf16 with
-// K below 2048), whose loop is short: us with blocks of channels / of pixels, 450 x 256 x 1152 on 256 CUs 2.83 / 2.97, 252 x 128 x 1728 on 64 2.95 / 3.23, 210 x 512 x 1728 on
-// 256 3.13 / 3.34; with eight, 374 x 64 x 2304 on 64 3.43 / 3.35, 84 x 512 x 4608 on 128 4.62 / 4.36.
+// K below 2048) or less than twelve groups of taps for eight, whose loops are short: us with blocks of channels / of pixels, 450 x 256 x 1152 on 256 CUs 2.83 / 2.97, 252 x 128 x 1728 on 64 2.95 / 3.23, 210 x 512 x 1728 on
+// 256 3.13 / 3.34; with eight, 374 x 64 x 2304 on 64 3.43 / 3.35, 84 x 512 x 4608 on 128 4.62 / 4.36;
+// fp32 375 x 128 x 864 on 128 4.10 / 4.42, 304 x 256 x 864 on 160 4.41 / 4.50, 377 x 64 x 1152 on 64 4.61 / 4.30.
 bool tall_takes(const ConvPlan& pl, int M, int nominal_cus);
 bool encode_conv_tall(const JoinedTable& kt, const ConvPlan& pl, const ConvArgs& a, int bf16, std::vector<KernelLaunch>* out);
 // Two independent convolutions in one launch: pl0/a0 as planned by plan_conv, pl1/a1 by plan_conv_like(pl0, ...).

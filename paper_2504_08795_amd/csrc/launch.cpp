@@ -569,7 +569,7 @@ bool encode_conv(const KernelTable& kt, const ConvPlan& pl, const ConvArgs& a, i
 }
 
 bool tall_takes(const ConvPlan& pl, int M, int nominal_cus) {
-  if (pl.gather != kGatherTaps || pl.tn != 2 || pl.nw != 8 || pl.rows != 16 || pl.splitk != 1) return false;
+  if (pl.gather != kGatherTaps || pl.tn != 2 || pl.nw != 8 || pl.S < 72 || pl.rows != 16 || pl.splitk != 1) return false;
   const int cus = std::min(std::max(nominal_cus, 8), 256);
   return cdiv(cdiv(M, 32) * pl.NTn * 2, cus) <= cdiv(pl.tiles, cus);
 }

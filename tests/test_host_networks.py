@@ -142,10 +142,10 @@ def test_every_launch_of_random_networks_is_sound(walk):
     assert all(ran[k] >= 10 for k in JOINED), ran
 
 
-def test_two_blocks_of_pixels_for_eight_waves_only(walk):
-    """16-pixel tiles with three taps per fetch: the short loop of four waves, bf16 with K below 2048, keeps two blocks of channels."""
+def test_two_blocks_of_pixels_for_long_loops_only(walk):
+    """16-pixel tiles with three taps per fetch: the short loops of four waves, bf16 with K below 2048, and of fewer than twelve groups of taps keep two blocks of channels."""
     shapes = [("bf16", 128, 15, 16, 256, 128, False), ("bf16", 192, 14, 18, 128, 64, False), ("bf16", 256, 15, 25, 64, 64, True), ("bf16", 256, 14, 14, 256, 128, True),
-              ("fp32", 128, 16, 24, 128, 96, True), ("fp32", 256, 14, 14, 256, 128, True)]
+              ("fp32", 96, 25, 15, 128, 128, False), ("fp32", 128, 16, 24, 128, 96, True), ("fp32", 256, 14, 14, 256, 128, True)]
     cases = [(dtype, (c, h, w), cus, 1, [N.Layer(op=N.OP_CONV, c_in=c, c_out=c_out, k=3, pad=1, in_from=-1)]) for dtype, c, h, w, c_out, cus, _ in shapes]
     for s, (_, ls) in zip(shapes, walk(cases)):
         assert [k for _, k, _ in ls] == ["conv_taps16_tall_kernel" if s[-1] else "conv_taps16_kernel"], (s, ls)
