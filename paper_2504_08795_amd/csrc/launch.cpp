@@ -560,6 +560,7 @@ bool encode_conv(const KernelTable& kt, const ConvPlan& pl, const ConvArgs& a, i
     const bool rows = pl.gather == kGatherRows || taps;
     if (pl.rows != 32 || pl.gather == kGatherDepthwise) return false;
     const bool large = rows && !rows_take(a, bf16);
+    if ((a.act & kActSumPixels) && (!rows || large)) return false;
     if (rows && (!pl.staged || (large && (pl.nw != 2 || !rows_take_large(a, bf16))))) return false;
     if (pl.gather == kGatherAligned && (!bf16 || a.Cin % 16)) return false;
     if ((rows || !bf16) && (pl.S % 2 || pl.sz % 2 || pl.sw % 2)) return false;
@@ -757,7 +758,7 @@ bool encode_gavgpool(const KernelTable& kt, const PoolArgs& layer, int bf16, std
   return push(out, kt.gavgpool[bf16], K_GAVGPOOL, (uint32_t)cdiv(a.C, 64), 256, &a, sizeof(a));
 }
 bool sums_pixels(const ConvPlan& pl, int channels) {
-  return (pl.rows == 16 || pl.rows == 32) && pl.splitk == 1 && pl.gather != kGatherInput && pl.gather != kGatherImage && pl.MT <= kPooledTiles && channels <= kPooledInputs;
+  return (pl.rows == 16 || pl.rows == 32) && pl.splitk == 1 && (pl.gather == kGatherRows || pl.gather == kGatherTaps) && pl.MT <= kPooledTiles && channels <= kPooledInputs;
 }
 bool encode_pooled_sums(const KernelTable& kt, const float* x, float* y, int C, int tiles, int pixels, std::vector<KernelLaunch>* out) {
   if (tiles < 1 || tiles > kPooledTiles) return false;

@@ -245,7 +245,7 @@ std::string build_plan(const daris_dnn& dnn, bool keep_activations, bool pair_la
     bool only_reader = true;
     for (int q = l + 2; q < n; ++q)
       if (net.layers[q].in_t == l + 1 || net.layers[q].res_t == l + 1 || (q > l + 2 && net.layers[q].in_t == l + 2) || net.layers[q].res_t == l + 2) only_reader = false;
-    if (!only_reader || !sums_pixels(A.cp, A.out.Cs)) continue;
+    if (!only_reader || !rows_taken(A) || !sums_pixels(A.cp, A.out.Cs)) continue;
     A.sums_pixels = true;
     A.pair_with = l + 2;
     A.out.bytes = std::max(A.out.bytes, (size_t)A.cp.MT * A.out.Cs * 4);

@@ -149,3 +149,11 @@ def test_two_blocks_of_pixels_for_long_loops_only(walk):
     cases = [(dtype, (c, h, w), cus, 1, [N.Layer(op=N.OP_CONV, c_in=c, c_out=c_out, k=3, pad=1, in_from=-1)]) for dtype, c, h, w, c_out, cus, _ in shapes]
     for s, (_, ls) in zip(shapes, walk(cases)):
         assert [k for _, k, _ in ls] == ["conv_taps16_tall_kernel" if s[-1] else "conv_taps16_kernel"], (s, ls)
+
+
+def test_only_convolutions_over_whole_rows_leave_sums_for_the_average(walk):
+    """The other kernels store their outputs, which a pooling layer of its own averages."""
+    tail = lambda c: [N.Layer(op=N.OP_CONV, c_in=c, c_out=96, k=1, in_from=-1), N.Layer(op=N.OP_GAVGPOOL, c_in=96, c_out=96, in_from=0), N.Layer(op=N.OP_FC, c_in=96, c_out=10, in_from=1)]
+    shapes = [("fp32", 32, True), ("fp32", 24, False), ("bf16", 64, True), ("bf16", 48, False)]
+    for (dtype, c, sums), (_, ls) in zip(shapes, walk([(dtype, (c, 7, 7), 128, 1, tail(c)) for dtype, c, _ in shapes])):
+        assert [k for _, k, _ in ls][1:] == (["fc_pooled_kernel"] if sums else ["gavgpool_kernel", "fc_kernel"]), (dtype, c, ls)
