@@ -57,6 +57,19 @@ def test_first_pooling_layer_joins_the_convolution(net, dtype):
     assert _plans(other, shp, dtype)[0]["pair_with"] == -1              # somebody else reads the convolution
 
 
+# h, w, plan CUs, joined in (fp32, bf16): workgroups of 4 x 7 pooled pixels to a CU
+STEMS = [(224, 224, 128, (True, True)), (224, 224, 112, (False, True)), (224, 224, 96, (False, True)), (224, 224, 64, (False, True)), (224, 224, 56, (False, False)), (178, 123, 72, (True, True)),
+         (130, 215, 80, (False, True)), (274, 183, 128, (True, True)), (274, 183, 120, (False, True)), (211, 285, 96, (False, True)), (211, 285, 80, (False, False)), (96, 96, 32, (True, True))]
+
+
+@pytest.mark.parametrize("h,w,cus,want", STEMS)
+def test_first_pooling_layer_joins_while_a_cu_has_few_workgroups(h, w, cus, want):
+    layers = wl.build_net("resnet18")[0][:2]
+    for dtype in ("fp32", "bf16"):
+        p = _plans(layers, (3, h, w), dtype, cus=cus)
+        assert ("image_pool" in D.daris_kernel_name(p[1]["kernel_id"])) == want[dtype == "bf16"], (dtype, p[1])
+
+
 @pytest.mark.parametrize("net", ["resnet18", "resnet50", "mobilenet_v2"])
 def test_global_average_without_a_launch(net):
     layers, shp = wl.build_net(net)
