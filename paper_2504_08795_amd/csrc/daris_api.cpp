@@ -749,7 +749,6 @@ daris_status daris_init(int device, uint64_t seed, int flags) {
                                {daris_point_kernels_co, (size_t)(daris_point_kernels_co_end - daris_point_kernels_co)}});
       if (err.empty()) {
         err = g_kt.resolve(g_rt);
-        if (err.empty()) err = g_kt.resolve_pointwise(g_rt);
         if (err.empty()) err = g_joined.resolve(g_rt);
         if (!err.empty()) err = "kernel " + err;
       }

@@ -285,11 +285,10 @@ struct KernelTable {
   const AqlKernel* convdw[2][6] = {};   // 1x1 convolution with a fused depthwise producer (fp32: tn = 1 only)
   const AqlKernel *reduce[2] = {}, *dwconv[2] = {}, *maxpool[2] = {}, *gavgpool[2] = {}, *fc[2] = {}, *ingest[2] = {}, *egress[2] = {};
   const AqlKernel *dwconv3[2] = {}, *maxpool_k[2][2] = {};  // 3x3 windows; 2x2 and 3x3 windows
-  const AqlKernel *point[2][2][6] = {}, *point_pair[2][2][6] = {};  // 1x1 windows without padding over whole rows: [bf16][16-row tiles][(tn - 1) * 3 + log2(nw) - 1]
+  const AqlKernel *point[2][2][6] = {}, *point_pair[2][2][6] = {};  // 1x1 windows without padding over whole rows: [bf16][16-row tiles][(tn - 1) * 3 + log2(nw) - 1] (bf16 32-row tiles: no eight waves)
   const AqlKernel* cu_probe = nullptr;
   // "" or the name of the first kernel that is missing or whose argument size is not what this header declares
   std::string resolve(const AqlRuntime& rt);
-  std::string resolve_pointwise(const AqlRuntime& rt);  // ... for `point` and `point_pair`, without which the general kernels run
 };
 
 // The kernels that compute several layers in a row, and those that run a plan of KernelTable's in tiles of another shape.

@@ -370,19 +370,15 @@ std::string KernelTable::resolve(const AqlRuntime& rt) {
   }
   for (int t = 0; t < 2; ++t)
     for (int v = 0; v < 3; ++v) block[t][v] = get("daris::conv_block_kernel<" + std::to_string(nw_[v]) + (t ? ", true>" : ", false>"), sizeof(ConvArgs));
-  cu_probe = get("daris::cu_probe_kernel", kProbeBytes);
-  return missing;
-}
-
-std::string KernelTable::resolve_pointwise(const AqlRuntime& rt) {
-  std::string missing;
   for (int b = 0; b < 2; ++b)
     for (int r = 0; r < 2; ++r)
       for (int v = 0; v < 6; ++v) {
-        const std::string tp = std::string(b ? "true" : "false") + (r ? ", 16, " : ", 32, ") + std::to_string(v / 3 + 1) + ", " + std::to_string(2 << v % 3) + ">";
-        point[b][r][v] = find_kernel(rt, "daris::conv_point_kernel<" + tp, sizeof(ConvArgs), &missing);
-        point_pair[b][r][v] = find_kernel(rt, "daris::conv_point_pair_kernel<" + tp, kPairBytes, &missing);
+        if (b && !r && nw_[v] == 8) continue;  // (no bf16 plan of 32-pixel tiles has eight waves)
+        const std::string tp = std::string(b ? "true" : "false") + (r ? ", 16, " : ", 32, ") + std::to_string(tn_[v]) + ", " + std::to_string(nw_[v]) + ">";
+        point[b][r][v] = get("daris::conv_point_kernel<" + tp, sizeof(ConvArgs));
+        point_pair[b][r][v] = get("daris::conv_point_pair_kernel<" + tp, kPairBytes);
       }
+  cu_probe = get("daris::cu_probe_kernel", kProbeBytes);
   return missing;
 }
 
@@ -556,7 +552,7 @@ bool encode_conv(const KernelTable& kt, const ConvPlan& pl, const ConvArgs& a, i
   if (pl.rows == 16) {
     const int ks16 = bf16 ? 32 : 16;
     if ((pl.gather != kGatherRows && !taps) || !rows_take(a, bf16) || a.Kpad % 32 || pl.S * ks16 != a.Kpad || pl.sw % pl.step_align) return false;
-    kernel = point_window(a) && kt.point[bf16][1][v] ? kt.point[bf16][1][v] : kt.conv16[bf16][taps][v];
+    kernel = point_window(a) ? kt.point[bf16][1][v] : kt.conv16[bf16][taps][v];
   } else if (pl.rows == 64) {
     // what the kernel assumes: whole 64-byte rows, one bit per filter tap, byte offsets that fit 32 bits, K in whole chunks
     if ((pl.gather != kGatherRows && !taps) || bf16 || !pl.staged || pl.tn != 2 || pl.S % 2 || pl.sz % 2 || pl.sw % 2) return false;
@@ -570,7 +566,7 @@ bool encode_conv(const KernelTable& kt, const ConvPlan& pl, const ConvArgs& a, i
     if (rows && (!pl.staged || (large && (pl.nw != 2 || !rows_take_large(a, bf16))))) return false;
     if (pl.gather == kGatherAligned && (!bf16 || a.Cin % 16)) return false;
     if ((rows || !bf16) && (pl.S % 2 || pl.sz % 2 || pl.sw % 2)) return false;
-    kernel = large ? kt.large[bf16][taps][pl.tn - 1] : rows && point_alone(pl, a, bf16) && kt.point[bf16][0][v] ? kt.point[bf16][0][v] : taps ? kt.taps[bf16][v] : kt.conv[bf16][v][pl.gather];
+    kernel = large ? kt.large[bf16][taps][pl.tn - 1] : rows && point_alone(pl, a, bf16) ? kt.point[bf16][0][v] : taps ? kt.taps[bf16][v] : kt.conv[bf16][v][pl.gather];
   }
   return push(out, kernel, pl.kernel, pl.grid_x, (uint32_t)pl.threads, &a, sizeof(a)) && push_reduce(kt, pl, a, bf16, out);
 }
@@ -630,7 +626,7 @@ bool encode_conv_pair(const KernelTable& kt, const ConvPlan& pl0, const ConvArgs
     if (pl0.gather != kGatherRows || pl0.splitk != 1 || !rows_take(a0, bf16) || !rows_take(a1, bf16) || a0.Kpad % 32 || a1.Kpad % 32 || pl0.sw % pl0.step_align || pl1.sw % pl1.step_align ||
         pl0.S * ks16 != a0.Kpad || pl1.S * ks16 != a1.Kpad)
       return false;
-    kernel = point_window(a0) && point_window(a1) && kt.point_pair[bf16][1][v] ? kt.point_pair[bf16][1][v] : kt.pair16[bf16][v];
+    kernel = point_window(a0) && point_window(a1) ? kt.point_pair[bf16][1][v] : kt.pair16[bf16][v];
   } else {
     const bool rows = pl0.gather == kGatherRows;
     if (rows && (!rows_take(a0, bf16) || !rows_take(a1, bf16) || !pl0.staged || !pl1.staged)) return false;
@@ -638,7 +634,7 @@ bool encode_conv_pair(const KernelTable& kt, const ConvPlan& pl0, const ConvArgs
     if (!rows && pl0.gather != kGatherAligned && pl0.gather != kGatherGeneral) return false;
     if ((rows || !bf16) && (pl0.S % 2 || pl0.sz % 2 || pl0.sw % 2 || pl1.S % 2 || pl1.sz % 2 || pl1.sw % 2)) return false;
     if (pl0.splitk > 1 && !a0.ws) return false;
-    kernel = rows && point_window(a0) && point_window(a1) && kt.point_pair[bf16][0][v] ? kt.point_pair[bf16][0][v] : kt.pair[bf16][v][rows ? 2 : pl0.gather];
+    kernel = rows && point_window(a0) && point_window(a1) ? kt.point_pair[bf16][0][v] : kt.pair[bf16][v][rows ? 2 : pl0.gather];
   }
   PairArgs pa;
   std::memset(&pa, 0, sizeof(pa));

@@ -13,7 +13,7 @@ constexpr int point_lds() {  // floats of LDS
 }
 // (three waves a SIMD as conv_wave_kernel has them)
 template <bool BF16, int R, int TN, int NW>
-__global__ __launch_bounds__(NW * 64, BF16 && R == 32 && TN == 2 && NW < 8 ? 3 : 1) void conv_point_kernel(const ConvArgs) {
+__global__ __launch_bounds__(NW * 64, BF16 && R == 32 && TN == 2 ? 3 : 1) void conv_point_kernel(const ConvArgs) {
   const ConvArgs p = conv_args_at((ConstPtr)__builtin_amdgcn_kernarg_segment_ptr());
   __shared__ __align__(16) float red[point_lds<BF16, R, TN, NW>()];
   int mt, g;
@@ -24,7 +24,7 @@ __global__ __launch_bounds__(NW * 64, BF16 && R == 32 && TN == 2 && NW < 8 ? 3 :
 
 // As conv_wave_pair_kernel: workgroups [0, n0) work on the first problem.
 template <bool BF16, int R, int TN, int NW>
-__global__ __launch_bounds__(NW * 64, BF16 && R == 32 && TN == 2 && NW < 8 ? 3 : 1) void conv_point_pair_kernel(const ConvArgs, const ConvArgs, const int n0) {
+__global__ __launch_bounds__(NW * 64, BF16 && R == 32 && TN == 2 ? 3 : 1) void conv_point_pair_kernel(const ConvArgs, const ConvArgs, const int n0) {
   __shared__ __align__(16) float red[point_lds<BF16, R, TN, NW>()];
   const bool second = (int)blockIdx.x >= n0;
   const ConvArgs p = conv_args_at((ConstPtr)__builtin_amdgcn_kernarg_segment_ptr() + (second ? sizeof(ConvArgs) : 0));
@@ -40,7 +40,7 @@ __global__ __launch_bounds__(NW * 64, BF16 && R == 32 && TN == 2 && NW < 8 ? 3 :
 #define DARIS_INST_POINT_W(B, R, T) DARIS_INST_POINT(B, R, T, 2) DARIS_INST_POINT(B, R, T, 4) DARIS_INST_POINT(B, R, T, 8)
 #define DARIS_INST_POINT_T(B, R) DARIS_INST_POINT_W(B, R, 1) DARIS_INST_POINT_W(B, R, 2)
 DARIS_INST_POINT_T(false, 32)
-DARIS_INST_POINT_T(true, 32)
+DARIS_INST_POINT(true, 32, 1, 2) DARIS_INST_POINT(true, 32, 1, 4) DARIS_INST_POINT(true, 32, 2, 2) DARIS_INST_POINT(true, 32, 2, 4)  // (no bf16 plan of 32-pixel tiles has eight waves)
 DARIS_INST_POINT_T(false, 16)
 DARIS_INST_POINT_T(true, 16)
 #undef DARIS_INST_POINT_T

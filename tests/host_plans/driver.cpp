@@ -20,7 +20,7 @@ const AqlKernel* AqlRuntime::kernel(const std::string& name) const {
   static const struct { const char* base; uint32_t bytes; } sizes[] = {
       {"conv_wave_kernel", sizeof(ConvArgs)}, {"conv_taps_kernel", sizeof(ConvArgs)}, {"conv_taps16_kernel", sizeof(ConvArgs)}, {"conv_image_kernel", sizeof(ImageConvArgs)}, {"conv_wave_pair_kernel", 2 * sizeof(ConvArgs) + 4}, {"conv_wave16_kernel", sizeof(ConvArgs)},
       {"conv_wave16_pair_kernel", 2 * sizeof(ConvArgs) + 4}, {"conv_wave_dw_kernel", sizeof(ConvArgs) + sizeof(DwFusedArgs)},
-      {"conv_block_kernel", sizeof(ConvArgs)}, {"conv_large_kernel", sizeof(ConvArgs)}, {"conv_taps_large_kernel", sizeof(ConvArgs)}, {"splitk_reduce_kernel", 48}, {"dwconv_kernel", sizeof(DwArgs)}, {"dwconv_window_kernel", sizeof(DwWindowArgs)},
+      {"conv_block_kernel", sizeof(ConvArgs)}, {"conv_large_kernel", sizeof(ConvArgs)}, {"conv_point_kernel", sizeof(ConvArgs)}, {"conv_point_pair_kernel", 2 * sizeof(ConvArgs) + 4}, {"conv_taps_large_kernel", sizeof(ConvArgs)}, {"splitk_reduce_kernel", 48}, {"dwconv_kernel", sizeof(DwArgs)}, {"dwconv_window_kernel", sizeof(DwWindowArgs)},
       {"maxpool_kernel", sizeof(PoolArgs)}, {"maxpool_window_kernel", sizeof(PoolWindowArgs)}, {"gavgpool_kernel", sizeof(PoolArgs)}, {"fc_kernel", sizeof(FcArgs)},
       {"ingest_kernel", 28}, {"egress_kernel", 28}, {"cu_probe_kernel", 12}};
   static AqlKernel known[sizeof(sizes) / sizeof(sizes[0])];

@@ -268,7 +268,6 @@ int main() {
   KernelTable kt;
   JoinedTable joined;
   std::string missing = kt.resolve(rt);
-  if (missing.empty()) missing = kt.resolve_pointwise(rt);
   if (missing.empty()) missing = joined.resolve(rt);
   if (!missing.empty()) {
     std::fprintf(stderr, "kernel %s\n", missing.c_str());

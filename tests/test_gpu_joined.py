@@ -248,3 +248,37 @@ def test_stages_chosen_behind_the_io_pool(first, then):
         torch.cuda.synchronize()
     assert want.abs().min() > 0
     np.testing.assert_array_equal(got.cpu().numpy(), want.cpu().numpy())
+
+
+# dtype, c_in, h, w, c_out, stride, plan CUs, whether a second 1x1 of 64 channels shares the launch: tiles of 16 and 32 pixels, one and two blocks of channels, two to eight waves,
+# whole and ragged last tiles, K that leaves a wave a chunk less or none, K split across workgroups
+WINDOWS = [("bf16", 224, 6, 19, 24, 2, 8, False), ("bf16", 512, 13, 8, 24, 2, 8, False), ("bf16", 2048, 11, 8, 96, 2, 32, False), ("bf16", 160, 13, 24, 24, 2, 8, False), ("bf16", 512, 22, 18, 64, 1, 64, False),
+           ("bf16", 2048, 26, 34, 64, 1, 128, False), ("bf16", 128, 31, 17, 96, 1, 8, False), ("bf16", 256, 14, 21, 96, 2, 8, False), ("bf16", 256, 37, 37, 256, 1, 8, False), ("bf16", 512, 25, 27, 64, 2, 8, False),
+           ("fp32", 96, 5, 28, 24, 2, 8, False), ("fp32", 256, 25, 29, 24, 2, 32, False), ("fp32", 512, 2, 29, 24, 2, 8, False), ("fp32", 128, 33, 14, 256, 2, 32, False), ("fp32", 256, 14, 28, 64, 1, 64, False),
+           ("fp32", 2048, 17, 17, 256, 2, 64, False), ("fp32", 96, 23, 19, 96, 1, 8, False), ("fp32", 1024, 7, 19, 96, 1, 8, False), ("fp32", 256, 11, 27, 64, 2, 8, False), ("fp32", 160, 34, 26, 1000, 1, 8, False),
+           ("fp32", 224, 17, 26, 256, 2, 8, False), ("fp32", 512, 23, 31, 256, 2, 32, False),
+           ("bf16", 224, 3, 29, 24, 2, 32, True), ("bf16", 512, 7, 10, 96, 1, 32, True), ("bf16", 2048, 2, 29, 96, 2, 32, True), ("bf16", 224, 18, 22, 96, 2, 64, True), ("bf16", 1024, 19, 13, 96, 1, 64, True),
+           ("bf16", 2048, 21, 37, 64, 1, 128, True), ("bf16", 224, 17, 6, 96, 2, 8, True), ("bf16", 512, 6, 5, 256, 2, 8, True), ("bf16", 160, 30, 14, 1000, 2, 8, True), ("bf16", 512, 3, 13, 512, 2, 8, True),
+           ("fp32", 224, 6, 9, 64, 2, 32, True), ("fp32", 256, 2, 19, 64, 2, 32, True), ("fp32", 512, 5, 2, 64, 1, 8, True), ("fp32", 96, 7, 9, 96, 2, 8, True), ("fp32", 1024, 15, 26, 24, 1, 64, True),
+           ("fp32", 96, 26, 8, 96, 1, 8, True), ("fp32", 160, 39, 7, 24, 2, 8, True), ("fp32", 512, 39, 8, 24, 2, 32, True), ("fp32", 32, 18, 25, 64, 1, 8, True), ("fp32", 224, 9, 3, 512, 1, 8, True),
+           ("fp32", 1024, 19, 19, 1000, 1, 240, True), ("fp32", 2048, 24, 25, 1000, 2, 32, True)]
+
+
+@pytest.mark.parametrize("case", WINDOWS, ids=lambda c: "-".join(map(str, c)))
+def test_windows_of_one_by_one_without_padding_and_with(case):
+    """With padding the general kernels run; inside, the same plan has the same sums, bit for bit."""
+    dtype, cin, h, w, cout, s, cus, two = case
+    x = wl.make_inputs((cin, h, w), 3, 1, "normal")[0]
+    outs, plans = [], []
+    for padded in (False, True):
+        last = dict(k=1, act=1, in_from=-1, has_bn=False)
+        layers = [N.Layer(op=N.OP_CONV, c_in=cin, c_out=cout, stride=s, pad=s if padded else 0, **last)]
+        if two:
+            layers.append(N.Layer(op=N.OP_CONV, c_in=cin, c_out=64, pad=1 if padded else 0, **last))
+        with GpuNet(layers, wl.make_weights(layers, 3), (cin, h, w), dtype, plan_cus=cus) as g:
+            plans.append([{q: p[q] for q in ("rows", "tn", "nw", "S", "sz", "sw", "splitk", "gather", "pair_with")} for p in (D.daris_get_launch_plan(g.task, l) for l in range(len(layers)))])
+            outs.append(g.forward(x).reshape(wl.layer_shapes(layers, (cin, h, w))[-1]))
+    assert plans[0] == plans[1] and plans[0][0]["gather"] == D.GATHER_ROWS and (plans[0][0]["pair_with"] == 1) == two
+    inside = outs[1][:, 1:1 + outs[0].shape[1], 1:1 + outs[0].shape[2]]       # (stride 2 has two pixels of padding)
+    np.testing.assert_array_equal(outs[0], inside)
+    assert np.abs(outs[0]).max() > 0

@@ -15,7 +15,7 @@ N = wl.nets
 # code object: {kernel: (bytes of its argument block, how many instances)}
 JOINED_KERNELS = {"daris_joined_kernels": {"conv_image_pool_kernel": (160, 2), "conv_expand_dw_kernel": (160, 10), "fc_pooled_kernel": (64, 2), "conv_chain_kernel": (248, 2), "conv_block_pool_kernel": (160, 3)},
                   "daris_tall_kernels": {"conv_taps16_tall_kernel": (160, 2)},
-                  "daris_pointwise_kernels": {"conv_point_kernel": (160, 24), "conv_point_pair_kernel": (324, 24)}}
+                  "daris_pointwise_kernels": {"conv_point_kernel": (160, 22), "conv_point_pair_kernel": (324, 22)}}
 
 
 @pytest.mark.parametrize("co", sorted(JOINED_KERNELS))
