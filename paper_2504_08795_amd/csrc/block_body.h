@@ -346,7 +346,11 @@ __device__ __forceinline__ void conv_block_body(const ConvArgs& p, float* const 
   spoil_unless_in_range(acc, red + wave * BPP * 1024, BPP * 16);
   __syncthreads();
   if (__builtin_expect(spoiled(red[lane % NW * BPP * 1024 + lane]), 0)) {  // every thread of the workgroup or none
+    const bool small = all_small(acc);
+    const f32x16 had[4] = {acc[0], acc[1], acc[2], acc[3]};
     plain_products<POOL ? 7 : TAPS ? 5 : 3, 32, 2, 2>(p, DwFusedArgs(), POOL ? s0 : m0, nb0, sbeg, 2 * nchunks, acc);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) take_second(small, had[k], acc[k]);
     park(0);
     __syncthreads();
   }

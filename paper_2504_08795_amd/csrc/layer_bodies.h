@@ -63,7 +63,8 @@ __device__ __forceinline__ Args args_at(ConstPtr src) {
 // infinite, and pixels so small that their third part falls below the smallest bf16 number leave sums below 2^-103 short of
 // bits.  A wave that finds its partial tile not finite, or all of it below 2^-103 (and not all of it 0), spoils the whole tile, so
 // every thread of the workgroup meets a NaN in the sums that it reads anyway, and the workgroup walks its K slice a second time
-// on the fp32 matrix instructions (plain_products).  Nothing else in the launch depends on the data, so a launch in which every
+// on the fp32 matrix instructions (plain_products).  What is not finite takes the second walk's sum, and so does all of a wave's tile that has nothing of 2^-103 and
+// more that is finite; the other sums stay, so that a NaN or an infinity changes no sum but those that it is part of, whichever tile these lie in.  Nothing else in the launch depends on the data, so a launch in which every
 // tile is taken twice is the longest there can be: the second walk, 8/3 of the first one's matrix time and with one chunk in
 // flight, is bounded by the same K.
 // The look at the partial tile is one instruction for two values, v_maximum3_f32 of their magnitudes, which keeps NaN.  A lane's
@@ -101,6 +102,35 @@ __device__ __forceinline__ void spoil_unless_in_range(const Acc (&acc)[N], float
 #pragma unroll 1
     for (int i = 0; i < words; ++i) tile[64 * i + (threadIdx.x & 63)] = __builtin_nanf("");
   }
+}
+// Which of a wave's sums the second walk replaces: all of a partial tile without a finite sum of 2^-103 and more, or those that are not finite.
+template <typename Acc>
+__device__ __forceinline__ bool all_small(const Acc& acc) {
+  float largest = 0.f;
+#pragma unroll
+  for (int v = 0; v < (int)(sizeof(Acc) / sizeof(float)); ++v) {
+    const float a = __builtin_fabsf(acc[v]);
+    largest = a < INFINITY ? fmaxf(largest, a) : largest;
+  }
+  return __ballot(largest >= 0x1p-103f) == 0;
+}
+template <int N, typename Acc>
+__device__ __forceinline__ bool all_small(const Acc (&acc)[N]) {
+  bool small = true;
+#pragma unroll
+  for (int j = 0; j < N; ++j) small = all_small(acc[j]) && small;
+  return small;
+}
+__device__ __forceinline__ float second(const bool small, const float first, const float again) {
+  const float kept = small ? __builtin_nanf("") : first;
+  const float sum = __builtin_fabsf(kept) < INFINITY ? kept : again;
+  __builtin_amdgcn_sched_barrier(0);  // (one after the other: all comparisons first would take more scalar registers than there are)
+  return sum;
+}
+template <typename Acc>
+__device__ __forceinline__ void take_second(const bool small, const Acc& first, Acc& again) {
+#pragma unroll
+  for (int v = 0; v < (int)(sizeof(Acc) / sizeof(float)); ++v) again[v] = second(small, first[v], again[v]);
 }
 __device__ __forceinline__ bool spoiled(const float v) { return __ballot(__builtin_isnan(v)) != 0; }
 
@@ -309,8 +339,16 @@ struct WaveEpilogue {
     if constexpr (!BF16 && MODE != kNoWalk) {
       if (__builtin_expect(spoiled(sums[0].x), 0)) {  // every thread of the workgroup or none (out of the way: a launch fetches its code anew, and a longer path costs 0.2 us)
         __syncthreads();
-        plain_products<MODE, R, TM, TN>(p, dwf, m0, nb0, sbeg, nsteps, acc);
         park();
+        const bool small = all_small(acc);
+        plain_products<MODE, R, TM, TN>(p, dwf, m0, nb0, sbeg, nsteps, acc);
+#pragma unroll
+        for (int j = 0; j < TM * TN; ++j)
+#pragma unroll
+          for (int v = 0; v < V; ++v) {
+            float& at = red[wave * TILE + (j * V + v) * 64 + lane];
+            at = second(small, at, acc[j][v]);
+          }
         __syncthreads();
         add_up();
       }
@@ -1378,6 +1416,8 @@ __device__ __forceinline__ void conv_image_body(const ImageConvArgs& p, const in
   static_for<0, DC>([&](auto s) { step(s, std::false_type()); });
   if constexpr (!BF16) {
     if (out_of_range(acc)) {
+      const bool small = all_small(acc);
+      const f32x16 first = acc[0];
       ConvArgs c = ConvArgs();
       c.x = p.x; c.w = p.w; c.H = p.H; c.W = p.W; c.Cin = 4; c.Wo = p.Wo; c.kh = c.kw = p.k; c.stride = p.stride; c.pad = p.pad;
       c.M = p.M; c.S = p.S; c.mg_wo = p.mg_wo; c.mg_kw = p.mg_k; c.c_real = p.c_real;
@@ -1390,6 +1430,7 @@ __device__ __forceinline__ void conv_image_body(const ImageConvArgs& p, const in
       } else {
         plain_products<6, 32, 1, 1>(c, DwFusedArgs(), (y0 + row0) * p.Wo + x0, nb, 0, p.S, acc);
       }
+      take_second(small, first, acc[0]);
     }
   }
   __syncthreads();  // the tiles go through the patch's LDS, each wave's through its own corner
@@ -1532,9 +1573,11 @@ __device__ __forceinline__ void conv_expand_dw_body(const ExpandDwArgs& p, const
         for (int h = 0; h < 2; ++h) {
           f32x4 s[1];
           plain_products<3, 16, 1, 1>(c, DwFusedArgs(), first + 16 * t, g, h * 2 * FIRST, h ? 2 * (NCH - FIRST) : 2 * FIRST, s);
-          acc[0][0] = h ? acc[0][0] + s[0] : s[0];
+          const f32x4 had = h ? acc[1][0] : acc[0][0];
+          take_second(all_small(had), had, s[0]);
+          if (h) acc[1][0] = s[0];
+          else acc[0][0] = s[0];
         }
-        acc[1][0] = f32x4(0.f);
       }
     }
     keep(t, acc[0][0] + acc[1][0]);
@@ -1655,6 +1698,7 @@ __device__ __forceinline__ void conv_chain_body(const ConvArgs& p, const ChainAr
     for (int b = 0; b < NB; ++b) {
       if constexpr (!BF16) {
         if (__builtin_expect(out_of_range(acc[b]), 0)) {  // the wave's block once more, on the fp32 matrix instructions
+          const f32x16 had[2] = {acc[b][0], acc[b][1]};
 #pragma unroll
           for (int h = 0; h < 2; ++h) acc[b][h] = f32x16(0.f);
 #pragma unroll
@@ -1666,6 +1710,8 @@ __device__ __forceinline__ void conv_chain_body(const ConvArgs& p, const ChainAr
 #pragma unroll
             for (int e = 0; e < 8; ++e) acc[b][u / HALF] = __builtin_amdgcn_mfma_f32_32x32x2f32((w[2][e] + w[1][e]) + w[0][e], x[e], acc[b][u / HALF], 0, 0, 0);
           }
+#pragma unroll
+          for (int h = 0; h < 2; ++h) take_second(all_small(had[h]), had[h], acc[b][h]);
         }
       }
       sum[b] = acc[b][0] + acc[b][1];
@@ -1738,7 +1784,11 @@ __device__ __forceinline__ void conv_chain_body(const ConvArgs& p, const ChainAr
       ConvArgs x = ConvArgs();  // one row of 32 pixels in LDS
       x.x = wide; x.w = c.w1; x.H = 1; x.W = x.M = 32; x.Cin = WIDE / 4; x.kh = x.kw = x.stride = 1; x.S = 2 * S1;
       x.mg_wo = x.mg_cin = 1;  // (every pixel and every k is below Wo and Cin)
+      const bool small = all_small(acc);
+      const f32x16 had[2] = {acc[0], acc[1]};
       plain_products<3, 32, 1, 2>(x, DwFusedArgs(), 0, 0, 2 * u0, 2 * U1, acc);
+#pragma unroll
+      for (int j = 0; j < 2; ++j) take_second(small, had[j], acc[j]);
     }
   }
   __syncthreads();  // the partial tiles come where `wide` was
