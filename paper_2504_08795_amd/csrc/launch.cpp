@@ -693,7 +693,6 @@ bool encode_expand_dw(const JoinedTable& kt, const ConvPlan& pl, const ConvArgs&
   return push(out, kt.expand_dw[bf16][chunks - 1], bf16 ? K_EXPAND_DW_BF16 : K_EXPAND_DW_F32, (uint32_t)(e.bands * (a.Cout / 16)), (uint32_t)e.threads, &e, sizeof(e));
 }
 
-// Grid and place finding of a window kernel (point_of): workgroups in multiples of 8, one band of them per XCD.
 // The kernel has one wave tile of 64 channels over all K slices of a workgroup, four waves in bf16 and eight in fp32, and takes the first 1x1 in two halves of K,
 // as plans of few steps have it.
 bool chain_takes(const ConvPlan& conv, int channels, const ConvPlan& wide, int wide_channels, const ConvPlan* narrow, int bf16) {
@@ -721,6 +720,7 @@ bool encode_chain(const JoinedTable& kt, const ConvPlan& conv, const ConvArgs& a
   return push(out, kt.chain[bf16], K_CHAIN_F32 + bf16, conv.grid_x, (uint32_t)conv.threads, &l, sizeof(l));
 }
 
+// Grid and place finding of a window kernel (point_of): workgroups in multiples of 8, one band of them per XCD.
 template <typename Args>
 static uint32_t point_grid(const Args& a, int bf16, PointPlace* at) {
   const uint32_t cvn = (uint32_t)(a.C / (bf16 ? 8 : 4));

@@ -241,7 +241,7 @@ std::string build_plan(const daris_dnn& dnn, bool keep_activations, bool pair_la
     LayerPlan& A = net.layers[l];
     LayerPlan& B = net.layers[l + 1];
     LayerPlan& C = net.layers[l + 2];
-    if (A.d.op != DARIS_OP_CONV || A.depthwise || A.pair_with >= 0 || A.joins >= 0 || B.d.op != DARIS_OP_GAVGPOOL || B.in_t != l + 1 || C.d.op != DARIS_OP_FC || C.in_t != l + 2) continue;
+    if (A.d.op != DARIS_OP_CONV || A.depthwise || A.pair_with >= 0 || B.d.op != DARIS_OP_GAVGPOOL || B.in_t != l + 1 || C.d.op != DARIS_OP_FC || C.in_t != l + 2) continue;
     bool only_reader = true;
     for (int q = l + 2; q < n; ++q)
       if (net.layers[q].in_t == l + 1 || net.layers[q].res_t == l + 1 || (q > l + 2 && net.layers[q].in_t == l + 2) || net.layers[q].res_t == l + 2) only_reader = false;
@@ -257,7 +257,7 @@ std::string build_plan(const daris_dnn& dnn, bool keep_activations, bool pair_la
   for (int l = 0; l + 1 < n && !keep_activations && pair_launches && staged_rows && join; ++l) {
     LayerPlan& A = net.layers[l];
     LayerPlan& B = net.layers[l + 1];
-    auto plain = [&](const LayerPlan& L) { return L.d.op == DARIS_OP_CONV && !L.depthwise && L.pair_with < 0 && L.joins < 0 && L.can_join < 0 && !L.sums_pixels && rows_taken(L); };
+    auto plain = [&](const LayerPlan& L) { return L.d.op == DARIS_OP_CONV && !L.depthwise && L.pair_with < 0 && L.can_join < 0 && !L.sums_pixels && rows_taken(L); };
     auto point = [&](const LayerPlan& L) { return plain(L) && L.d.k == 1 && L.d.stride == 1 && L.d.pad == 0; };
     if (!plain(A) || A.res_t >= 0 || (l == 0 && net.fuse_ingest) || !point(B) || B.in_t != l + 1 || B.res_t == l + 1 || !chain_takes(A.cp, A.out.Cs, B.cp, B.out.Cs, nullptr, net.bf16)) continue;
     bool only_reader = true;

@@ -24,7 +24,7 @@ def _joined_and_parted(layers, weights, shp, dtype, xs, n_cu=128, plan_cus=0):
     return outs, plans
 
 
-# c_in, h, w, c_out, k, stride, pad: the edges of a workgroup's 3 x 7 pooled pixels, outputs of odd and even sizes, and frames larger than one round
+# c_in, h, w, c_out, k, stride, pad: the edges of a workgroup's 4 x 7 pooled pixels, outputs of odd and even sizes, and frames larger than one round
 # (in fp32 planned for as many CUs as there are workgroups at least)
 STEMS = [(3, 224, 224, 64, 7, 2, 3), (3, 189, 253, 64, 7, 2, 3), (3, 130, 131, 64, 7, 2, 3), (4, 61, 83, 128, 5, 1, 2), (1, 70, 90, 192, 3, 1, 1), (3, 97, 61, 60, 3, 1, 0)]
 

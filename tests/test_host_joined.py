@@ -8,6 +8,7 @@ import workloads as wl
 from lib_helpers import Session
 from paper_2504_08795_amd import build
 from test_host_logic import _code_object_kernels
+from test_host_networks import _resized
 
 HOST = D.VIRTUAL_TIME | D.NO_DEVICE
 N = wl.nets
@@ -104,12 +105,10 @@ def test_bottlenecks_of_64_channels_share_a_launch():
         assert (p[0]["out_slot"] == -1) == (1 not in cuts) and (joined or 1 in cuts), (p, cuts)
 
 
-
 def test_joins_do_not_cost_a_network_the_static_scratch():
     """Joint launches keep what they read until they are issued, which takes VGG-16 a third buffer: 16.0 MiB instead of 15.1 at 160 x 193 pixels, where the scratch holds 16."""
-    import perf.cases as cases
     for side, buffers in (((160, 160), 3), ((160, 193), 2), ((194, 160), 2), ((224, 224), 3)):   # small enough either way, only without joins, and neither
-        layers, shp = cases._net("vgg16", *side)
+        layers, shp = _resized("vgg16", *side)
         assert len({v for p in _plans(layers, shp, "fp32") for v in (p["out_slot"], p["in_slot"])} - {-1}) == buffers, side
 
 
