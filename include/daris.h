@@ -57,8 +57,9 @@ enum {
   DARIS_NO_FIXED = 16,        /* ablation ("No Fixed"): all stages share one level, EDF only                   */
   DARIS_HP_ADMISSION = 32,    /* Overload+HPA (Sec. VI-I): HP jobs must pass the test in their own context     */
   DARIS_KEEP_ACTIVATIONS = 64, /* debugging: one buffer per layer output so daris_read_layer (daris_debug.h) works;
-                                 the input is converted first, so the first convolution may run another kernel and
-                                 logits may differ from those without the flag by the rounding of its sums            */
+                                 the input is converted first and no layer joins another's launch, so that the first
+                                 convolution, one in front of a 3x3 depthwise layer and a global average may have their
+                                 sums in another order, and logits differ from those without the flag by its rounding  */
   DARIS_WAVE_PRIORITY = 128,  /* the convolution waves of high-priority tasks raise their issue priority on the CU:
                                  where partitions overlap, HP stages run faster and LP stages slower (measured:
                                  HP response -5 %, LP +12 %, aggregate throughput -2 %); off by default          */
@@ -75,10 +76,17 @@ enum {
                                  instead of fetching whole 64-byte rows through LDS where the shape allows (A/B)   */
   DARIS_NO_SMALL_TILES = 4096, /* ... and keep 32-pixel tiles with a K split across workgroups (and its reduction launch)
                                  for deep layers of few pixels, instead of 16-pixel tiles (A/B)                  */
+  DARIS_NO_JOIN = 32768,      /* ... and launch every layer by itself that otherwise runs in the launch of the one behind it: a convolution
+                                 and the max pooling or the 3x3 depthwise layer that alone reads it, a bottleneck's convolutions in a row, a
+                                 global average between a convolution and the FC layer (whose sums are then in another order, like those of
+                                 the convolution in front of a depthwise layer).  Pairs, the input's conversion and depthwise layers inside
+                                 1x1 convolutions have flags of their own; without fused ingest no pooling layer joins the first convolution,
+                                 and without staged rows or small tiles no depthwise layer joins (without rows no bottleneck either)   */
   DARIS_NO_TALL_TILES = 16384, /* ... and give a wave two blocks of channels instead of two blocks of pixels where three taps
                                  share a fetch (A/B and tests; the same sums bit for bit)                         */
   DARIS_NO_FUSED_DW = 8192     /* ... and run a 3x3 depthwise convolution in a launch of its own instead of computing it
-                                 inside the 1x1 convolution that is its only reader (A/B and tests)              */
+                                 inside the 1x1 convolution that is its only reader, or together with the one that it alone reads
+                                 (A/B and tests)                                                                  */
 };
 
 enum { DARIS_LP = 0, DARIS_HP = 1 };

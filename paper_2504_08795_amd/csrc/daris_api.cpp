@@ -865,7 +865,7 @@ daris_task daris_register_task(const daris_dnn* dnn, int64_t period_ns, int64_t 
   if (G->tasks.size() >= 65535) return fail(DARIS_ERANGE, "too many tasks");
   std::unique_ptr<TaskRt> T(new TaskRt());
   auto plan = [&](NetPlan* net, bool join) {
-    return build_plan(*dnn, G->flags & DARIS_KEEP_ACTIVATIONS, !(G->flags & DARIS_NO_PAIR), !(G->flags & DARIS_NO_FUSED_INGEST), !(G->flags & DARIS_NO_STAGED_ROWS), !(G->flags & DARIS_NO_SMALL_TILES), !(G->flags & DARIS_NO_FUSED_DW), G->plan_cus, net, !(G->flags & DARIS_NO_TALL_TILES), join);
+    return build_plan(*dnn, G->flags & DARIS_KEEP_ACTIVATIONS, !(G->flags & DARIS_NO_PAIR), !(G->flags & DARIS_NO_FUSED_INGEST), !(G->flags & DARIS_NO_STAGED_ROWS), !(G->flags & DARIS_NO_SMALL_TILES), !(G->flags & DARIS_NO_FUSED_DW), G->plan_cus, net, !(G->flags & DARIS_NO_TALL_TILES), join && !(G->flags & DARIS_NO_JOIN));
   };
   std::string err = plan(&T->net, true);
   // What layers in a joint launch read lives until that launch, so their plan may take a buffer more.  A network that fits the static scratch only without joins

@@ -224,8 +224,8 @@ std::string build_plan(const daris_dnn& dnn, bool keep_activations, bool pair_la
       if (net.layers[q].in_t == l + 1 || net.layers[q].res_t == l + 1) only_reader = false;
     if (!only_reader) continue;
     if (B.d.op == DARIS_OP_MAXPOOL) {
-      if (fuse_ingest && B.d.k == 3 && B.d.stride == 2 && B.d.pad == 1 && image_pool_takes(A.cp, A.out.H, A.out.W, A.out.Cs, A.d.k, A.d.stride, plan_cus, net.bf16)) B.can_join = l;
-      if (pair_launches && B.d.k == 2 && B.d.stride == 2 && B.d.pad == 0 && A.res_t < 0 && block_pool_takes(A.cp, A.out.H, A.out.W)) B.can_join = l;
+      if (B.d.k == 3 && B.d.stride == 2 && B.d.pad == 1 && image_pool_takes(A.cp, A.out.H, A.out.W, A.out.Cs, A.d.k, A.d.stride, plan_cus, net.bf16)) B.can_join = l;
+      if (B.d.k == 2 && B.d.stride == 2 && B.d.pad == 0 && A.res_t < 0 && block_pool_takes(A.cp, A.out.H, A.out.W)) B.can_join = l;
     } else if (B.d.op == DARIS_OP_CONV && B.depthwise && staged_rows && small_tiles) {
       if (B.d.k == 3 && B.d.pad == 1 && (B.d.stride == 1 || B.d.stride == 2) && A.d.k == 1 && A.d.stride == 1 && A.d.pad == 0 && A.res_t < 0 && rows_taken(A) && !(l == 0 && net.fuse_ingest) &&
           plan_expand_dw(&A.cp, A.out.H, A.out.W, net.tensor(A.in_t).Cs, A.out.Cs, A.Kpad, B.d.stride, plan_cus, net.bf16)) {
@@ -237,7 +237,7 @@ std::string build_plan(const daris_dnn& dnn, bool keep_activations, bool pair_la
     }
   }
   // convolution, global average pooling and FC layer, which nobody else reads
-  for (int l = 0; l + 2 < n && !keep_activations && pair_launches && join; ++l) {
+  for (int l = 0; l + 2 < n && !keep_activations && join; ++l) {
     LayerPlan& A = net.layers[l];
     LayerPlan& B = net.layers[l + 1];
     LayerPlan& C = net.layers[l + 2];
@@ -254,7 +254,7 @@ std::string build_plan(const daris_dnn& dnn, bool keep_activations, bool pair_la
     B.kernel_id = A.kernel_id;
   }
   // a 3x3 convolution, the 1x1 that alone reads it, and the 1x1 behind that
-  for (int l = 0; l + 1 < n && !keep_activations && pair_launches && staged_rows && join; ++l) {
+  for (int l = 0; l + 1 < n && !keep_activations && staged_rows && join; ++l) {
     LayerPlan& A = net.layers[l];
     LayerPlan& B = net.layers[l + 1];
     auto plain = [&](const LayerPlan& L) { return L.d.op == DARIS_OP_CONV && !L.depthwise && L.pair_with < 0 && L.can_join < 0 && !L.sums_pixels && rows_taken(L); };

@@ -77,7 +77,7 @@ struct NetPlan {
 // tensor share a launch; fuse_ingest: the first convolution may read the caller's input layout itself; staged_rows:
 // convolutions whose pixels are whole 64-byte rows fetch them coalesced through LDS; small_tiles: deep, skinny layers
 // get 16-pixel tiles instead of a K split across workgroups; fuse_dw: a depthwise convolution is computed inside the 1x1
-// convolution that alone reads it; tall_tiles: LayerPlan::tall; join: LayerPlan::joins,
+// convolution that alone reads it, or the 1x1 in front in its; tall_tiles: LayerPlan::tall; join: LayerPlan::joins,
 // follows and average_of.  Returns "" or an error text.
 // plan_cus: the partition size the convolution grids are balanced for.
 std::string build_plan(const daris_dnn& dnn, bool keep_activations, bool pair_launches, bool fuse_ingest, bool staged_rows, bool small_tiles, bool fuse_dw,

@@ -93,7 +93,7 @@ CHAINS = [(56, 56, 256, 64, True, 128), (56, 56, 256, 0, True, 128), (48, 65, 25
 @pytest.mark.parametrize("dtype", ["fp32", "bf16"])
 @pytest.mark.parametrize("shape", CHAINS)
 def test_bottleneck_in_one_launch(shape, dtype):
-    """A convolution in front makes the residual's channels.  NO_PAIR parts all of it, a stage cut the 3x3 from the first 1x1 or that from the second: bit for bit the same."""
+    """A convolution in front makes the residual's channels.  NO_JOIN parts all of it, a stage cut the 3x3 from the first 1x1 or that from the second: bit for bit the same."""
     h, w, n3, n1, res, cus = shape
     layers = [N.Layer(op=N.OP_CONV, c_in=32, c_out=n3, k=1, act=1, in_from=-1, has_bn=False), N.Layer(op=N.OP_CONV, c_in=n3, c_out=64, k=1, act=1, in_from=0, has_bn=False),
               N.Layer(op=N.OP_CONV, c_in=64, c_out=64, k=3, pad=1, act=1, in_from=1, has_bn=False),
@@ -105,7 +105,7 @@ def test_bottleneck_in_one_launch(shape, dtype):
     bad = x.copy()
     bad[0, h // 2, w // 3], bad[31, 0, w - 1] = np.nan, np.inf
     outs = []
-    for flags, k in ((0, 1), (0, 2), (D.NO_PAIR, 1)):
+    for flags, k in ((0, 1), (0, 2), (D.NO_JOIN, 1)):
         with GpuNet(layers, weights, (32, h, w), dtype, flags=flags, k=k, plan_cus=cus) as g:
             assert (D.daris_get_launch_plan(g.task, 2)["out_slot"] == -1) == (flags == 0 and n3 == 256 and 3 not in D.daris_get_stage_cuts(g.task))
             outs.append([g.forward(x), g.forward(bad)])
@@ -136,7 +136,7 @@ def test_convolution_global_average_and_fc(shape, dtype):
         np.testing.assert_array_equal(*o)                     # the pooling layer alone in its stage makes the averages from the same sums
     e_max, e_l2 = rel_err(outs[0][0], oracle_logits(layers, weights, x, dtype))
     assert e_max <= TOL[dtype] and e_l2 <= TOL[dtype], (e_max, e_l2)
-    with GpuNet(layers, weights, (cin, h, w), dtype, flags=D.NO_PAIR, plan_cus=cus) as g:   # pooling in a launch of its own: the same sums in another order
+    with GpuNet(layers, weights, (cin, h, w), dtype, flags=D.NO_JOIN, plan_cus=cus) as g:   # pooling in a launch of its own: the same sums in another order
         assert D.daris_kernel_name(D.daris_get_launch_plan(g.task, 1)["kernel_id"]) == "gavgpool"
         e_max, e_l2 = rel_err(outs[0][0], g.forward(x))
     assert e_max <= (2e-6 if dtype == "fp32" else 2 ** -7), e_max

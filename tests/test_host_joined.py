@@ -129,3 +129,29 @@ def test_expansions_join_their_depthwise_layer_while_the_launch_is_short(shape, 
     if not joined:                                                      # the convolution by itself, with the plan that it has without a depthwise layer behind it
         own = _plans(layers[:1], (cin, h, w), dtype, cus=cus)[0]
         assert all(p[0][k] == own[k] for k in ("kernel_id", "rows", "tn", "nw", "sw")), (p[0], own)
+
+
+def _shared(net, dtype, flags):
+    """How many (launch pairs, layers joined to another's launch, buffers) a network has under the flags."""
+    layers, shp = wl.build_net(net)
+    with Session(HOST | flags):
+        D.daris_create_partition(64)
+        dnn, keep = D.make_dnn(layers, None, shp, dtype)
+        t = D.daris_register_task(dnn, 10**7, 10**7, D.LP)
+        p = [D.daris_get_launch_plan(t, l) for l in range(len(layers))]
+    pairs = sum(1 for l, q in enumerate(p) if q["pair_lead"] and layers[l - 1].groups == 1)
+    kernel = [D.daris_kernel_name(q["kernel_id"]) for q in p]
+    joined = sum(1 for l, q in enumerate(p) if ("pool" in kernel[l] or "expand_dw" in kernel[l]) and kernel[l] not in ("maxpool", "gavgpool"))
+    joined += sum(1 for l, L in enumerate(layers) if L.op == N.OP_GAVGPOOL and kernel[l] != "gavgpool")
+    joined += sum(1 for l in range(len(layers) - 1) if layers[l + 1].op == layers[l].op == N.OP_CONV and p[l]["out_slot"] == -1 and layers[l + 1].groups == layers[l].groups == 1)
+    return pairs, joined, len({v for q in p for v in (q["out_slot"], q["in_slot"])} - {-1})
+
+
+@pytest.mark.parametrize("net,dtype", [("resnet18", "fp32"), ("resnet50", "bf16"), ("vgg16", "fp32"), ("mobilenet_v2", "fp32")])
+def test_flags_part_what_they_name_and_nothing_else(net, dtype):
+    pairs, joined, buffers = _shared(net, dtype, 0)
+    assert (pairs > 0) == net.startswith("resnet") and (joined > 0) == (net != "vgg16")   # (of pooling behind 64-pixel tiles plans show the third buffer)
+    assert _shared(net, dtype, D.NO_PAIR)[1:] == (joined, buffers) and _shared(net, dtype, D.NO_PAIR)[0] == 0
+    assert _shared(net, dtype, D.NO_JOIN)[:2] == (pairs, 0) and (net != "vgg16" or buffers == 3 and _shared(net, dtype, D.NO_JOIN)[2] == 2)
+    assert _shared(net, dtype, D.NO_FUSED_DW)[:2] == (pairs, 1 if net == "mobilenet_v2" else joined)   # (the global average)
+    assert _shared(net, dtype, D.NO_TALL_TILES) == (pairs, joined, buffers)
