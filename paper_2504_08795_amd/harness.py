@@ -160,31 +160,43 @@ PEAK_TFLOPS = {"fp32": 416.7, "bf16": 2500.0}
 PEAK_HBM_GBS = 8000.0
 
 
-def layer_rooflines(layers, shp, dtype):
-    """Per layer: (algorithmic FLOPs, algorithmic bytes, t_roof in us on the whole chip).  Bytes = weights once + one fp32
-    bias per output channel + the input tensor(s) read once + the output written once, at the element size of the task;
+def launch_roofline(layers, shp, dtype, members):
+    """(algorithmic FLOPs, algorithmic bytes, t_roof in us on the whole chip) of layers in one launch.  Bytes = weights once + one fp32 bias per output
+    channel + every tensor from outside read once + every output that somebody outside reads written once, at the element size of the task;
     FLOPs = 2 x MACs; t_roof = max(FLOPs / dense MFMA peak of the dtype, bytes / HBM peak).  (In device memory a weight of an
-    fp32 dense convolution takes 6 bytes, its three bf16 parts; what the layer cannot do without is 4.)  Host arithmetic on
-    the layer table only."""
+    fp32 dense convolution takes 6 bytes, its three bf16 parts; what the layer cannot do without is 4.)  Host arithmetic on the layer table only."""
     import workloads as wl
     es = 4 if dtype == "fp32" else 2
     shapes = wl.layer_shapes(layers, shp)
     macs = wl.net_macs(layers, shp)
-    out = []
-    for l, L in enumerate(layers):
-        c, h, w = shapes[l]
-        ci, hi, wi = shp if L.in_from < 0 else shapes[L.in_from]
-        if L.op == wl.nets.OP_CONV:
-            w_elems, b_elems = L.c_out * (L.c_in // L.groups) * L.k * L.k, L.c_out
-        elif L.op == wl.nets.OP_FC:
-            w_elems, b_elems = L.c_out * L.c_in, L.c_out
-        else:
-            w_elems = b_elems = 0
-        by = w_elems * es + b_elems * 4 + ci * hi * wi * es + c * h * w * es
-        if L.res_from >= 0:
-            by += c * h * w * es
-        fl = 2.0 * macs[l]
-        out.append((fl, by, max(fl / (PEAK_TFLOPS[dtype] * 1e12), by / (PEAK_HBM_GBS * 1e9)) * 1e6))
+    inside, read, by = set(members), set(), 0
+    for l in members:
+        L = layers[l]
+        if L.op in (wl.nets.OP_CONV, wl.nets.OP_FC):
+            by += es * L.c_out * (L.c_in // L.groups * L.k * L.k if L.op == wl.nets.OP_CONV else L.c_in) + 4 * L.c_out
+        read |= {t for t in ([L.in_from] + ([L.res_from] if L.res_from >= 0 else [])) if t not in inside}
+        if l == len(layers) - 1 or any(l in (q.in_from, q.res_from) for k, q in enumerate(layers) if k not in inside):
+            by += es * shapes[l][0] * shapes[l][1] * shapes[l][2]
+    for t in read:
+        c, y, x = shp if t < 0 else shapes[t]
+        by += es * c * y * x
+    fl = 2.0 * sum(macs[l] for l in members)
+    return fl, by, max(fl / (PEAK_TFLOPS[dtype] * 1e12), by / (PEAK_HBM_GBS * 1e9)) * 1e6
+
+
+def layer_rooflines(layers, shp, dtype):
+    """launch_roofline of every layer by itself."""
+    return [launch_roofline(layers, shp, dtype, [l]) for l in range(len(layers))]
+
+
+def launches_of(us):
+    """The layers of each launch, from the times of a layer profile: a layer without a time of its own is computed in the launch of the next one that has one."""
+    out, members = [], []
+    for l, t in enumerate(us):
+        members.append(l)
+        if t > 0:
+            out.append(members)
+            members = []
     return out
 
 
@@ -201,9 +213,8 @@ def taskset_roofline_us(ts):
 
 
 def layer_profile(net, dtype, n_cu, reps=50, plan_cus=0):
-    """Every layer of one DNN alone on an n_cu partition: kernel, time, and its roofline.  Algorithmic bytes of a layer =
-    its weights and biases once + its input tensor(s) read once + its output written once (element size of the
-    task); algorithmic FLOPs = 2 x MACs.  t_roof = max(FLOPs / MFMA peak of the dtype, bytes / HBM peak), whole chip."""
+    """Every layer of one DNN alone on an n_cu partition: kernel, time, and its roofline (launch_roofline); where a launch computes several layers, the figures
+    of the launch stand at the last one, and only the layer's own FLOPs, bytes and t_roof at the others."""
     import torch
     import workloads as wl
     layers, shp = wl.build_net(net)
@@ -220,7 +231,6 @@ def layer_profile(net, dtype, n_cu, reps=50, plan_cus=0):
         y = torch.zeros(layers[-1].c_out, device="cuda")
         D.daris_forward(t, x, y, p)
         ms, kid, fl = D.daris_profile_layers(t, p, reps, len(layers))
-        plans = [D.daris_get_launch_plan(t, l) for l in range(len(layers))]
         # one job after the other through the scheduler (one stage per job, buffers of an I/O pool): the production path
         xs = x.unsqueeze(0).contiguous()
         ys = torch.zeros(4, layers[-1].c_out, device="cuda")
@@ -235,20 +245,20 @@ def layer_profile(net, dtype, n_cu, reps=50, plan_cus=0):
         D.daris_shutdown()
     shapes = wl.layer_shapes(layers, shp)
     roofs = layer_rooflines(layers, shp, dtype)
+    launch_of = {l: g for g in launches_of(ms) for l in g}
     rows = []
     for l, L in enumerate(layers):
         c, h, w = shapes[l]
-        by, t_roof = roofs[l][1], roofs[l][2]
         assert roofs[l][0] == fl[l], (l, roofs[l][0], fl[l])      # the library counts the same MACs as the layer table
-        us = float(ms[l]) * 1e3
+        us, own = float(ms[l]) * 1e3, launch_of[l]
+        flops, by, t_roof = launch_roofline(layers, shp, dtype, own) if us > 0 else roofs[l]
         rows.append(dict(layer=l, name=L.name, kernel=D.daris_kernel_name(kid[l]), M=h * w, N=c, us=round(us, 2),
-                         gflop=round(fl[l] / 1e9, 4), mbytes=round(by / 1e6, 3),
-                         tflops=round(fl[l] / us / 1e6, 2) if us > 0.2 else None, gbs=round(by / us / 1e3, 1) if us > 0.2 else None,
-                         bound="mfma" if fl[l] / (PEAK_TFLOPS[dtype] * 1e12) > by / (PEAK_HBM_GBS * 1e9) else "hbm",
-                         t_roof_us=round(t_roof, 3), frac=round(t_roof / us, 4) if us > 0.2 else None,
-                         joint_launch_with=plans[l]["pair_with"] if plans[l]["pair_with"] >= 0 else None))
+                         gflop=round(flops / 1e9, 4), mbytes=round(by / 1e6, 3),
+                         tflops=round(flops / us / 1e6, 2) if us > 0.2 else None, gbs=round(by / us / 1e3, 1) if us > 0.2 else None,
+                         bound="mfma" if flops / (PEAK_TFLOPS[dtype] * 1e12) > by / (PEAK_HBM_GBS * 1e9) else "hbm",
+                         t_roof_us=round(t_roof, 3), frac=round(t_roof / us, 4) if us > 0.2 else None, launch=own))
     return dict(net=net, dtype=dtype, n_cu=n_cu, kernel_time_us=round(float(sum(r["us"] for r in rows)), 1), job_latency_us=round(latency_us, 1),
-                t_roof_us=round(sum(r["t_roof_us"] for r in rows), 2), layers=rows)
+                t_roof_us=round(sum(r[2] for r in roofs), 2), layers=rows)
 
 
 def queue_scaling(net, dtype, n_max=8, jobs_per_task=150, n_stages=3):
@@ -361,7 +371,7 @@ def main():
               f"sum of layer rooflines {r['t_roof_us']} us\n")
         print("| # | layer | kernel | M | N | us | GFLOP | MB | TFLOP/s | GB/s | bound | t_roof us | frac |\n|---|---|---|---|---|---|---|---|---|---|---|---|---|")
         for x in r["layers"]:
-            note = f" (launched with layer {x['joint_launch_with']})" if x["joint_launch_with"] is not None else ""
+            note = f" (in the launch of layer {x['launch'][-1]})" if x["launch"][-1] != x["layer"] else f" (and {', '.join(map(str, x['launch'][:-1]))})" if len(x["launch"]) > 1 else ""
             print(f"| {x['layer']} | {x['name']}{note} | {x['kernel']} | {x['M']} | {x['N']} | {x['us']} | {x['gflop']} | {x['mbytes']} | {x['tflops']} | {x['gbs']} | "
                   f"{x['bound']} | {x['t_roof_us']} | {x['frac']} |")
         return

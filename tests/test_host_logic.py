@@ -561,6 +561,14 @@ def test_layer_rooflines_follow_the_layer_tables():
     for (net, dtype), us in want_us.items():
         layers, shp = wl.build_net(net)
         assert round(sum(x[2] for x in harness.layer_rooflines(layers, shp, dtype)), 2) == us
+    # a launch of several layers: the tensors between them are neither read nor written
+    assert harness.launches_of([0, 0, 3, 1, 0, 2]) == [[0, 1, 2], [3], [4, 5]]
+    layers, shp = wl.build_net("resnet18")
+    (f0, b0, _), (f1, b1, _) = harness.layer_rooflines(layers, shp, "fp32")[:2]
+    assert harness.launch_roofline(layers, shp, "fp32", [0, 1])[:2] == (f0 + f1, b0 + b1 - 2 * 4 * 64 * 112 * 112)
+    ds = next(l for l, L in enumerate(layers) if layers[l + 1].in_from == L.in_from)                        # a shortcut and its block's first convolution read one tensor
+    (f0, b0, _), (f1, b1, _) = harness.layer_rooflines(layers, shp, "fp32")[ds:ds + 2]
+    assert harness.launch_roofline(layers, shp, "fp32", [ds, ds + 1])[:2] == (f0 + f1, b0 + b1 - 4 * 64 * 56 * 56)
     ts = wl.make_taskset(2)
     assert [round(v, 2) for v in harness.taskset_roofline_us(ts)] == [12.06] * 4
 
