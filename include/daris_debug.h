@@ -29,12 +29,14 @@ extern "C" {
  * caller gives it straight into registers, 3 whole 64-byte rows, 4 computed from the input of the depthwise layer that shares the
  * launch, 5 rows fetched once for three taps (K in the order window row, channels of a chunk, window column), 6 the network input in patches: there a wave
  * owns two rows of 16 pixels and one channel block over all of K, [13] counts the pixel tiles of workgroups (16 columns wide,
- * 8 rows high, or 4 where a workgroup has two channel blocks side by side), [15] the workgroups beside one another. */
+ * 8 rows high, or 4 where a workgroup has two channel blocks side by side), [15] the workgroups beside one another.
+ * Two forms of a plan have the same sums and do not show: 16-pixel tiles with three taps per fetch and two channel blocks may run as two blocks of pixels instead (unless
+ * DARIS_NO_TALL_TILES; [7], [13], [14], [16] and [17] are then those of the channel blocks), and 1x1 windows run in kernels of their own under the kernel id of the plan. */
 int32_t daris_get_launch_plan(daris_task t, int layer, int64_t* out, int32_t cap);
 /* After daris_forward with DARIS_KEEP_ACTIVATIONS: copy layer l's output to host float[c][h][w]. */
 daris_status daris_read_layer(daris_task t, int layer, float* host_out, int64_t cap_elems);
 /* Time each layer of task t on stream 0 of partition p: `reps` runs back to back, from the start time stamp of the
- * first dispatch to the end time stamp of the last, divided by reps (the earlier layer of a launch pair reports 0).
+ * first dispatch to the end time stamp of the last, divided by reps (a layer that runs in the launch of a later one reports 0, and that one the launch's time).
  * ms_per_layer = host float[n_layers]; kernel_id = host int32[n_layers] (which kernel variant ran, see
  * daris_kernel_name; of a layer without a launch, what the plan says); flops = host double[n_layers] algorithmic FLOPs (2*MACs) of the layer. */
 daris_status daris_profile_layers(daris_task t, daris_part p, int reps, float* ms_per_layer, int32_t* kernel_id,
