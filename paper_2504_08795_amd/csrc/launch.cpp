@@ -403,11 +403,10 @@ static bool rows_take(const ConvArgs& a, int bf16) { return a.c_real == 0 && con
 
 static bool rows_take_large(const ConvArgs& a, int bf16) { return a.c_real == 0 && a.kh == a.kw && conv_rows_take_large(a.H, a.W, a.Cin, a.Wo, a.Cout, a.kh, a.stride, a.Kpad, bf16); }
 
-// 1x1 windows without padding, which kernels of their own take over whole rows: the same plans and sums, fewer instructions.
+// 1x1 windows without padding, which kernels of their own take over whole rows: the same plans and sums, fewer instructions.  Alone, a bf16 layer whose waves walk two chunks (K =
+// 128 on two waves) takes a little longer with them, 784 x 512 on 128 CUs 2.82 us -> 2.86, but not in a frame, where kernels change from launch to launch: ResNet-50's bf16 frame
+// with the general kernel for such layers / with these, 48 random sizes on 32 to 208 CUs, 1.003 in the geometric mean, and longer in 39.
 static bool point_window(const ConvArgs& a) { return a.kh == 1 && a.kw == 1 && a.pad == 0; }
-// ... by themselves not where a wave of bf16 tiles of 32 x 64 walks two chunks, K = 128 on two waves: 160 random layers, general kernels / these, up to six tiles a CU 1.00 / 1.01
-// (1290 x 512 on 64 CUs 3.79 us / 4.01, 784 x 512 on 128 2.82 / 2.86), above 1.00 / 0.97.  K = 64 0.945, K = 192 0.96.
-static bool point_alone(const ConvPlan& pl, const ConvArgs& a, int bf16) { return point_window(a) && !(bf16 && pl.rows == 32 && pl.tn == 2 && pl.nw == 2 && pl.sw == 4); }
 
 static bool push_reduce(const KernelTable& kt, const ConvPlan& pl, const ConvArgs& a, int bf16, std::vector<KernelLaunch>* out) {
   if (pl.splitk <= 1) return true;
@@ -566,7 +565,7 @@ bool encode_conv(const KernelTable& kt, const ConvPlan& pl, const ConvArgs& a, i
     if (rows && (!pl.staged || (large && (pl.nw != 2 || !rows_take_large(a, bf16))))) return false;
     if (pl.gather == kGatherAligned && (!bf16 || a.Cin % 16)) return false;
     if ((rows || !bf16) && (pl.S % 2 || pl.sz % 2 || pl.sw % 2)) return false;
-    kernel = large ? kt.large[bf16][taps][pl.tn - 1] : rows && point_alone(pl, a, bf16) ? kt.point[bf16][0][v] : taps ? kt.taps[bf16][v] : kt.conv[bf16][v][pl.gather];
+    kernel = large ? kt.large[bf16][taps][pl.tn - 1] : rows && point_window(a) ? kt.point[bf16][0][v] : taps ? kt.taps[bf16][v] : kt.conv[bf16][v][pl.gather];
   }
   return push(out, kernel, pl.kernel, pl.grid_x, (uint32_t)pl.threads, &a, sizeof(a)) && push_reduce(kt, pl, a, bf16, out);
 }
