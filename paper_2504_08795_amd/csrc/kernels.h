@@ -328,11 +328,10 @@ bool conv_dw_fusable(const ConvPlan& pl, int bf16);
 // The first convolution and the 3 x 3 max pooling with stride 2 and padding 1 that alone reads it, in one launch: whether the convolution planned
 // as pl should be computed so, and the launch itself (pool: the pooling layer).  us of the two launches / of one, 12544 x 64 x 7 x 7 with stride 2: fp32 on
 // 128 CUs 8.2 / 7.2, bf16 on 192 CUs 6.3 / 4.9; in the chain of a frame the pooling launch takes 1.3 more than alone, and ResNet-18's frame goes from 133.9 to
-// 132.1 us in fp32 and from 81.8 to 79.0 in bf16.  It computes 1.4 outputs for one that counts, so that it gains while a CU has few workgroups: fp32, bound by
-// the matrix pipe, up to one, and where the CUs of an XCD do not come out even over its four shader engines (multiples of 32 in all) up to five sixths, above which some CU gets two
-// while others idle; bf16 up to 7/4.  ResNet-18's frame joined / apart by workgroups a CU, fp32: 212 x 216 on 112 CUs (1.0) 156.5 / 154.1, 188 x 304 on 152 (0.87)
-// 132.6 / 130.9, 178 x 123 on 72 (0.83) 128.5 / 129.5, 274 x 183 on 128 (0.98) 129.5 / 130.9, planned for 96 with 112 194.8 / 193.3; bf16: 211 x 285 on 72 (2.1) 99.8 / 98.4, on
-// 80 (1.9) 98.3 / 97.3, on 96 (1.6) 99.2 / 100.6, 224 x 224 on 64 (1.75) 94.8 / 96.4.
+// 132.1 us in fp32 and from 81.8 to 79.0 in bf16.  It computes 1.4 outputs for one that counts, and fp32 is bound by the matrix pipe, so that it gains while a CU has one
+// workgroup at most: up to one, and where the CUs of an XCD do not come out even over its four shader engines (multiples of 32 in all) up to eight ninths, above which some CU gets
+// two while others idle.  Frames of the ResNets of 40 random sizes on such partitions, apart / joined in the geometric mean: 0.84 to 0.885 workgroups a CU 1.008, 0.89 to 1 0.993 (ResNet-18 planned
+// for 96 with 112 workgroups 193.3 us / 194.8); bf16, 40 sizes with 1.8 to 6.2 workgroups a CU, 1.003, with no trend.
 bool image_pool_takes(const ConvPlan& pl, int Ho, int Wo, int cout_stride, int k, int stride, int nominal_cus, int bf16);
 bool encode_image_pool(const JoinedTable& kt, const ConvPlan& pl, const ConvArgs& a, const PoolArgs& pool, int bf16, std::vector<KernelLaunch>* out);
 // An fp32 convolution in 64-pixel tiles with three taps per fetch and the 2 x 2 max pooling with stride 2 that alone reads it, in one launch: whether the plan

@@ -510,8 +510,7 @@ bool image_pool_takes(const ConvPlan& pl, int Ho, int Wo, int cout_stride, int k
   const ImageTiles t = image_tiles(Ho, Wo, cout_stride, k, stride, pl.S, bf16, true);
   if (pl.gather != kGatherImage || !t.ok) return false;
   const int64_t groups = t.tiles * (t.nb / t.wn), cus = nominal_cus;
-  if (bf16) return 4 * groups <= 7 * cus;
-  return cus % 32 == 0 ? groups <= cus : 6 * groups <= 5 * cus;
+  return bf16 || (cus % 32 == 0 ? groups <= cus : 9 * groups <= 8 * cus);
 }
 
 bool encode_image_pool(const JoinedTable& kt, const ConvPlan& pl, const ConvArgs& a, const PoolArgs& pool, int bf16, std::vector<KernelLaunch>* out) {
