@@ -66,13 +66,13 @@ static uint32_t tile_order(int MT, int G, int* xmode) {
 // several, they fill it by themselves, and fewer waves have fewer partial tiles to sum and less LDS each.  us with eight waves / four, fp32: 3136 x 64
 // x 576 on 96 CUs (196 tiles) 7.6 / 6.3, 784 x 128 x 512 on 96 (100) 5.5 / 5.0, 784 x 128 x 1152 on 48 12.4 / 11.6, 1520 x 256 x 512 on 160 8.0 / 7.4, 6000 x 64 x
 // 256 on 160 6.0 / 5.0, 196 x 256 x 1024 on 48 8.05 / 7.35.  bf16 with four / two: 3136 x 64 x 576 on 32 CUs (98 tiles) 5.45 / 4.95, 3136 x 256 x 1152 on 128 (392)
-// 8.3 / 7.6, 1364 x 512 x 1152 on 80 11.3 / 10.7; with fewer tiles 784 x 256 x 512 beside 196 x 1024 x 512 on 128 (212) 4.2 / 4.5; with K so long that the partial tiles are
-// no matter 1363 x 512 x 2304 on 128 11.2 / 11.4, 840 x 512 x 4608 on 40 38.2 / 39.3 (and 204 x 512 x 4608 on 40 14.6 / 14.2, the most that K of 2304 and more gains).
-// In fp32 they are no matter for tiles one block of channels wide without three taps per fetch: 256 x 1024 x 4608 beside 256 x 1024 x 512 on 96 (256 and 256 tiles) 46.2 / 50.5, but with
+// 8.3 / 7.6, 1364 x 512 x 1152 on 80 11.3 / 10.7, 2728 x 256 x 2304 on 232 9.7 / 8.6; with fewer tiles 784 x 256 x 512 beside 196 x 1024 x 512 on 128 (212) 4.2 / 4.5.  (Some layers of a long
+// K lose alone, 840 x 512 x 4608 on 40 38.2 / 39.3; VGG-16's frames that have such layers of K >= 2304, 59 random sizes, are 0.8 % shorter with two waves in the geometric mean, 46 of them.)
+// In fp32 the partial tiles are no matter for a long K of tiles one block of channels wide without three taps per fetch: 256 x 1024 x 4608 beside 256 x 1024 x 512 on 96 (256 and 256 tiles) 46.2 / 50.5, but with
 // three taps per fetch 385 x 256 x 4608 on 48 49.0 / 39.5, and two blocks wide 300 x 1024 x 4608 beside 300 x 1024 x 512 on 48 166 / 124.
 static int fewer_waves(int tiles, int cus, int bf16, int nw, int S, int tn, bool three_taps) {
   if (!bf16) return tiles > cus && (tn == 2 || three_taps || S <= 36 * nw) ? std::min(nw, 4) : nw;
-  return 2 * tiles > 5 * cus && tiles < 6 * cus && S < 36 * nw ? std::min(nw, 2) : nw;
+  return 2 * tiles > 5 * cus && tiles < 6 * cus ? std::min(nw, 2) : nw;
 }
 
 static ConvPlan plan_conv_wave(int M, int N, int Kpad, int bf16, int step_align, int nominal_cus, bool allow_block, ThreeTaps three_taps, int force_tn = 0, int force_nw = 0) {

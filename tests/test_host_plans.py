@@ -166,8 +166,8 @@ FEWER_WAVES = [
     ((0, 512, 32, 32, 1024, 3, 2, 1, 96, 1024, 1, 2, 0), 8),      # 256 of a long K
     ((0, 64, 44, 44, 64, 3, 1, 1, 48, 0, 1, 1, 0), 4),
     ((1, 128, 28, 35, 256, 3, 1, 1, 48, 0, 1, 1, 0), 2),
-    ((1, 256, 29, 47, 512, 3, 1, 1, 128, 0, 1, 1, 0), 4),         # K = 2304
-    ((1, 512, 21, 40, 512, 3, 1, 1, 40, 0, 1, 1, 0), 4),
+    ((1, 256, 29, 47, 512, 3, 1, 1, 128, 0, 1, 1, 0), 2),
+    ((1, 512, 21, 40, 512, 3, 1, 1, 40, 0, 1, 1, 0), 2),
 ]
 
 
