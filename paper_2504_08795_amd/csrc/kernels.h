@@ -243,7 +243,7 @@ ConvPlan plan_conv(int M, int N, int Kpad, int bf16, int step_align, int cin_str
 // across workgroups.  Returns a plan with kernel == K_NONE when that is not possible.
 ConvPlan plan_conv_like(const ConvPlan& first, int M, int N, int Kpad, int bf16, int step_align, int nominal_cus = 128);
 // The plan `own` of the heavier convolution once `light` shares its launch: with the waves a workgroup that so many tiles want (those of the lighter one
-// count by their share of K, if that is half of the heavier one's at least).  us on 128 CUs, fp32: 3136 x 128 x 256 beside 784 x 512 x 256 13.6 -> 8.6, 784 x 256 x 512 beside 196 x 1024 x 512 9.9 -> 7.5, 196 x 512 x
+// count by their share of K).  us on 128 CUs, fp32: 3136 x 128 x 256 beside 784 x 512 x 256 13.6 -> 8.6, 784 x 256 x 512 beside 196 x 1024 x 512 9.9 -> 7.5, 196 x 512 x
 // 1024 beside 49 x 2048 x 1024 9.0 -> 8.6; bf16 the first of them 4.9 -> 4.2.
 ConvPlan plan_conv_beside(const ConvPlan& own, const ConvPlan& light, int M, int N, int Kpad, int bf16, int step_align, int nominal_cus);
 // Settles the gather of a plan without kGatherTaps; rows = conv_rows_take holds (for both members of a launch pair), or conv_rows_take_large.

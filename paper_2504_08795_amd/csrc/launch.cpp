@@ -250,10 +250,11 @@ ConvPlan plan_conv(int M, int N, int Kpad, int bf16, int step_align, int cin_str
 ConvPlan plan_conv_beside(const ConvPlan& own, const ConvPlan& light, int M, int N, int Kpad, int bf16, int step_align, int nominal_cus) {
   const int cus = std::min(std::max(nominal_cus, 8), 256);
   if (own.rows != 32 || own.splitk != 1 || own.gather == kGatherTaps || light.kernel == K_NONE) return own;
-  // The tiles of a lighter one with a short K do not count: they are gone early and leave a CU to the few waves of one heavy tile.  us, fp32 with eight waves / four: 232 x 512 x
-  // 2304 beside 232 x 512 x 256 on 128 CUs (128 tiles and 128) 9.9 / 12.4, 102 x 256 x 1152 beside 102 x 256 x 128 on 32 (32 and 32) 6.1 / 7.1.  (What loses all the same:
-  // some of K = 2304 with 2.3 to 2.5 tiles a CU, 300 x 512 x 2304 on 64 CUs 19.9 / 21.0; most of them gain 4 to 20 %.)
-  const int nw = fewer_waves(own.tiles + (2 * light.S >= own.S ? (int)((int64_t)light.tiles * std::min(light.S, own.S) / own.S) : 0), cus, bf16, own.nw, own.S, own.tn, false);
+  // Beside a long K the tiles of a lighter one with a short K do not count: they are gone early and leave a CU to the few waves of one heavy tile.  us, fp32 with eight waves / four: 232 x
+  // 512 x 2304 beside 232 x 512 x 256 on 128 CUs (128 tiles and 128) 9.9 / 12.4.  Not so with a shorter K or tiles two blocks of channels wide: ResNet-18's frames in which such
+  // pairs have 0.9 to 1 heavy tile a CU, 40 random sizes, are 0.7 % longer with eight waves in the geometric mean, up to 3 % (two blocks: 316 x 174 on 56 CUs).
+  const bool soon_done = !bf16 && own.tn == 1 && own.S >= 36 * own.nw && 2 * light.S < own.S;
+  const int nw = fewer_waves(own.tiles + (soon_done ? 0 : (int)((int64_t)light.tiles * std::min(light.S, own.S) / own.S)), cus, bf16, own.nw, own.S, own.tn, false);
   return nw == own.nw ? own : plan_conv_wave(M, N, Kpad, bf16, step_align, cus, false, kNoTaps, own.tn, nw);
 }
 

@@ -157,7 +157,7 @@ def test_single_channel_tiles_on_16_or_32_pixels(plans):
 
 
 # (dtype, c_in, h, w, c_out, k, stride, pad, plan CUs[, c_out, k, stride, pad of one that shares the launch]), waves of a workgroup: fewer where a CU has several tiles,
-# but not beside a lighter one that is soon done, nor where K is long
+# but in fp32 not where K is long, nor beside a lighter one that is then soon done
 FEWER_WAVES = [
     ((0, 512, 28, 28, 256, 1, 1, 0, 128, 1024, 1, 2, 0), 4),
     ((0, 256, 57, 16, 512, 3, 2, 1, 128, 512, 1, 2, 0), 8),       # 128 tiles, and 128 of a ninth of K
@@ -166,6 +166,7 @@ FEWER_WAVES = [
     ((0, 512, 32, 32, 1024, 3, 2, 1, 96, 1024, 1, 2, 0), 8),      # 256 of a long K
     ((0, 64, 44, 44, 64, 3, 1, 1, 48, 0, 1, 1, 0), 4),
     ((1, 128, 28, 35, 256, 3, 1, 1, 48, 0, 1, 1, 0), 2),
+    ((0, 128, 12, 34, 256, 3, 2, 1, 32, 256, 1, 2, 0), 4),        # 32, and 32 of a ninth, beside a shorter K
     ((1, 256, 29, 47, 512, 3, 1, 1, 128, 0, 1, 1, 0), 2),
     ((1, 512, 21, 40, 512, 3, 1, 1, 40, 0, 1, 1, 0), 2),
 ]
